@@ -57,6 +57,9 @@ def conv_name(kid: int, dtype: str) -> str:
     """Template instance behind a conv kernel id (digits 1 BBB PPP K M V), as rocprofv3 prints it."""
     d = kid - 1000000000
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
+    if 600000000 <= d < 700000000:                       # split-K kernel: digits S BBB PPP (K split, channel tile, pixel tile)
+        ks, bc, bp = (d - 600000000) // 1000000, (d // 1000) % 1000, d % 1000
+        return "octo::conv_ksplit_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp // 32, ks, ks)
     if 700000000 <= d < 800000000:                       # wide 3x3 kernel: digits P BBB TTT (512-pixel tile, channel tile, tile width)
         bc = ((d - 700000000) // 1000) % 1000
         tc, tp, wc = (3, 4, 1) if bc == 96 else (bc // 64, 4, 2)
@@ -109,7 +112,7 @@ TRAFFIC_SOURCE = "profiles/*_hbm_counters.md: rocprofv3 --pmc FETCH_SIZE and --p
 def conv_sources_key() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv.hip", "convbig.hip", "conv3x3.hip", "stem.hip", "mfma_common.h"):
+    for f in ("conv.hip", "conv_ksplit.h", "convbig.hip", "conv3x3.hip", "stem.hip", "mfma_common.h"):
         try:
             h.update(open(os.path.join(ROOT, "paper_2502_01277_amd", "csrc", f), "rb").read())
         except OSError:

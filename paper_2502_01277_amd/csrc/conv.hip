@@ -24,6 +24,7 @@
 // so no host round trip is needed.
 #include "octo_internal.h"
 #include "mfma_common.h"
+#include "conv_ksplit.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -451,6 +452,31 @@ static hipError_t launch_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* 
   return hipGetLastError();
 }
 
+// Tile choice of the general kernel (measured on MI355X) for M output pixels.  Up to 32 output channels: register-staged
+// 32x128 tiles.  Otherwise operands go straight into LDS with K steps of 128 bytes: 128x128 tiles where 128 channels per
+// tile pad the channel count no further than 64 do (192 = 3 x 64, but 2 x 128), 64x128 tiles for the middle ground (64x256
+// with 64-byte K steps for very large, narrow layers), 64x64 tiles for layers with few output pixels.  How many tiles a
+// shape must yield depends on the length of the reduction.  A layer with a short K loop is dominated by start-up and
+// epilogue and runs fastest on the shape that spreads it over all compute units.  A long K loop is paced by the operand
+// fetch from the L2s, so the shape with the most arithmetic per fetched byte wins as soon as a quarter of the compute
+// units get a tile: alone it takes a little longer, but it moves half the bytes, and kernels of other streams use the
+// rest of the chip meanwhile (+4 % on the traffic cascade with four pipeline instances).
+// Very many pixels: 256-pixel tiles of 64 channels with 64-byte K steps, three workgroups per compute unit.  For layers of
+// at most 64 channels (store-bound first layers, wide early stages), and for short reductions - all epilogue and memory
+// traffic - whose channel count the 128-channel tile would pad (192 = 3 x 64): 192 -> 192 on 32 x 160 x 160 runs 11 %
+// faster than on 64x128 tiles; beyond K = 384 the larger K step wins.
+// k_scale: values per 2 bytes of K (2 for 8-bit storage, whose reductions are half as long in bytes).
+struct GeneralTile { int bc, bp; };
+static GeneralTile general_tile(const ConvArgs& a, long long M, int num_cu, int k_scale) {
+  auto tiles = [&](int bc, int bp) { return ((M + bp - 1) / bp) * ((a.Cout + bc - 1) / bc); };
+  if (a.Cout <= 32 && k_scale == 1) return {32, 128};
+  const bool fits128 = a.Cout >= 96 && (a.Cout + 127) / 128 * 128 == (a.Cout + 63) / 64 * 64;
+  if (tiles(64, 256) >= 4 * num_cu && (a.Cout <= 64 || (k_scale == 1 && !fits128 && a.Kp <= 384))) return {64, 256};
+  if (fits128 && tiles(128, 128) >= (a.Kp >= 1024 * k_scale ? num_cu / 4 : 5 * num_cu / 4)) return {128, 128};
+  if (tiles(64, 128) >= (a.Kp >= 512 * k_scale ? num_cu / 4 : 9 * num_cu / 8)) return {64, 128};
+  return {64, 64};
+}
+
 template <typename T>
 static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   constexpr int VN = Elem<T>::N;
@@ -459,33 +485,23 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   // the tile shape is chosen for the expected number of items (any shape is correct for any count: the grid strides
   // over however many tiles the device-side count gives)
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
-  auto tiles = [&](int bc, int bp) { return ((M + bp - 1) / bp) * ((a.Cout + bc - 1) / bc); };
   if (!vec) {
     // element-wise gather (first layers with 3 input channels)
     if (a.Cout <= 32) return launch_cfg<T, 32, 128, 1, 4, 4, 2, 2, false>(a, num_cu, s, kernel_id, tm);
     return launch_cfg<T, 64, 128, 2, 2, 4, 2, 2, false>(a, num_cu, s, kernel_id, tm);
   }
-  // Tile choice (measured on MI355X).  Up to 32 output channels: register-staged 32x128 tiles.  Otherwise operands
-  // go straight into LDS with K steps of 128 bytes: 128x128 tiles where 128 channels per tile pad the channel count
-  // no further than 64 do (192 = 3 x 64, but 2 x 128), 64x128 tiles for the middle ground (64x256 with 64-byte K steps
-  // for very large, narrow layers), 64x64 tiles for layers with few output pixels.  How many tiles a shape must yield
-  // depends on the length of the reduction.  A layer with a short K loop is dominated by start-up and epilogue and runs
-  // fastest on the shape that spreads it over all compute units.  A long K loop is paced by the operand fetch from the
-  // L2s, so the shape with the most arithmetic per fetched byte wins as soon as a quarter of the compute units get a
-  // tile: alone it takes a little longer, but it moves half the bytes, and kernels of other streams use the rest of
-  // the chip meanwhile (+4 % on the traffic cascade with four pipeline instances).
-  if (a.Cout <= 32) return launch_cfg<T, 32, 128, 1, 4, 4, 2, 4, true>(a, num_cu, s, kernel_id, tm);
-  const bool fits128 = a.Cout >= 96 && (a.Cout + 127) / 128 * 128 == (a.Cout + 63) / 64 * 64;
-  // Very many pixels: 256-pixel tiles of 64 channels with 64-byte K steps, three workgroups per compute unit.  For
-  // layers of at most 64 channels (store-bound first layers, wide early stages), and for short reductions - all
-  // epilogue and memory traffic - whose channel count the 128-channel tile would pad (192 = 3 x 64): 192 -> 192 on
-  // 32 x 160 x 160 runs 11 % faster than on 64x128 tiles; beyond K = 384 the larger K step wins.
-  if (tiles(64, 256) >= 4 * num_cu && (a.Cout <= 64 || (!fits128 && a.Kp <= 384)))
-    return launch_cfg<T, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
-  if (fits128 && tiles(128, 128) >= (a.Kp >= 1024 ? num_cu / 4 : 5 * num_cu / 4))
-    return launch_cfg<T, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
-  if (tiles(64, 128) >= (a.Kp >= 512 ? num_cu / 4 : 9 * num_cu / 8))
-    return launch_cfg<T, 64, 128, 2, 2, 8, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
+  // Launches that leave compute units idle or wait on their K loop go to the split-K kernel instead, by estimated time.
+  // That kernel sums in another order, so the choice is made for a.n_split items where the count is taken on the device:
+  // unlike the running average behind n_hint it stays the same from batch to batch, and so do the results.
+  const long long M_split = a.n_split > 0 ? (long long)(a.n_split < a.n ? a.n_split : a.n) * a.Ho * a.Wo : M;
+  const GeneralTile st = general_tile(a, M_split, num_cu, 1);
+  const int ks = ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
+  if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
+  const GeneralTile t = general_tile(a, M, num_cu, 1);
+  if (t.bc == 32) return launch_cfg<T, 32, 128, 1, 4, 4, 2, 4, true>(a, num_cu, s, kernel_id, tm);
+  if (t.bp == 256) return launch_cfg<T, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
+  if (t.bc == 128) return launch_cfg<T, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
+  if (t.bp == 128) return launch_cfg<T, 64, 128, 2, 2, 8, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
   return launch_cfg<T, 64, 64, 2, 2, 8, 1, 4, true, true>(a, num_cu, s, kernel_id, tm);
 }
 
@@ -497,13 +513,12 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   const bool vec = (a.Cin % 16 == 0) && (a.x_ld % 16 == 0) && (a.x_coff % 16 == 0) && (((uintptr_t)a.x & 15) == 0) && a.kh <= 15 && a.kw <= 15;
   if (!vec || !a.scale || a.pair_view) return hipErrorInvalidValue;
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
-  auto tiles = [&](int bc, int bp) { return ((M + bp - 1) / bp) * ((a.Cout + bc - 1) / bc); };
-  const bool fits128 = a.Cout >= 96 && (a.Cout + 127) / 128 * 128 == (a.Cout + 63) / 64 * 64;
-  if (fits128 && tiles(128, 128) >= (a.Kp >= 2048 ? num_cu / 4 : 5 * num_cu / 4))
-    return launch_cfg<f8, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
-  if (a.Cout <= 64 && tiles(64, 256) >= 4 * num_cu) return launch_cfg<f8, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
-  if (tiles(64, 128) >= (a.Kp >= 1024 ? num_cu / 4 : 9 * num_cu / 8))
-    return launch_cfg<f8, 64, 128, 2, 2, 8, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
+  const GeneralTile t = general_tile(a, M, num_cu, 2);
+  const int ks = ksplit_choose(a, M, 1, t.bc, t.bp, num_cu);
+  if (ks >= 0) return launch_ksplit<f8>(ks, a, num_cu, s, kernel_id, tm);
+  if (t.bc == 128) return launch_cfg<f8, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
+  if (t.bp == 256) return launch_cfg<f8, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
+  if (t.bp == 128) return launch_cfg<f8, 64, 128, 2, 2, 8, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
   return launch_cfg<f8, 64, 64, 2, 2, 8, 1, 4, true, true>(a, num_cu, s, kernel_id, tm);
 }
 #endif

@@ -37,6 +37,7 @@ struct ConvArgs {
   int act, res_mode;
   int out_f32;          // write fp32 instead of the storage type
   int n_hint;           // host only: expected item count when it is taken on the device (0: assume n); picks the tile shape
+  int n_split;          // host only: item count the choice between orders of summation is made for (0: n)
   int pair_view;        // the layer is a 3-channel first layer run on pixel pairs of a 4-channel-padded input
   // Fused 3x3 / stride-2 / pad-1 max-pool (first-layer kernel only): when pool_y is set, only the pooled tensor is
   // written and y is not touched; launch_conv returns hipErrorNotSupported if no kernel can do that for the layer.

@@ -83,6 +83,7 @@ struct ModelPlan {
   int bz = 0;              // current batch size (root: frames per batch)
   int exec_bz = 0;         // root only: frames per execution of the detector's layers (0: the whole batch at once)
   const int* n_dyn = nullptr;
+  int items_split = 0;     // children: item count that kernels with another order of summation are chosen for (fixed)
   double items_hint = 0;   // smoothed item count of recent batches (children; 0: none seen yet)
   char* act_base = nullptr;
   size_t act_bytes = 0;
@@ -490,6 +491,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       a.act = L.act; a.res_mode = L.res_mode; a.out_f32 = m.tensors[i + 1].f32 ? 1 : 0;
       if (L.n_in == 2) { const TensorView r = view_of(m, L.in[1]); a.res = r.ptr; a.res_ld = r.ld; a.res_coff = r.coff; }
       if (n_dyn && m.items_hint > 0) a.n_hint = std::max(1, (int)(m.items_hint + 0.999));
+      if (n_dyn) a.n_split = m.items_split;
       if (i > 0 && m.layers[i - 1].fuse_twin) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (lp.fuse_twin) {
         const TensorView y2 = view_of(m, i + 2);
@@ -631,6 +633,7 @@ octo_status build(octo_pipeline* p, const octo_pipeline_desc* desc, Arena& ar) {
       const long long ecap = (long long)desc->max_frames * desc->max_rois_per_frame;
       m.cap = (int)std::max(1LL, m.d.batch_size > 0 ? std::min<long long>(m.d.batch_size, ecap) : ecap);
       m.bz = m.cap;
+      m.items_split = std::min(m.cap, 8 * desc->max_frames);      // a camera frame shows about eight objects
     } else {
       m.cap = std::max(1, m.d.batch_size);
       m.bz = m.cap;
