@@ -43,6 +43,7 @@ struct ConvArgs {
   // written and y is not touched; launch_conv returns hipErrorNotSupported if no kernel can do that for the layer.
   void* pool_y;
   int pool_ho, pool_wo, pool_ld, pool_coff;
+  int pool_seg;                   // tiles per segment of a strip (set by launch_stem)
   // Two layers in one launch (general kernel, 16-bit types, no residual): output channels below `split` go to y as
   // usual, channels split .. Cout - 1 to y2 as its channels 0 ..; split is a multiple of 8 and 0 when unused.
   void* y2;
@@ -75,6 +76,10 @@ struct PoolArgs {
   int H, W, C, x_ld, x_coff, Ho, Wo, y_ld, y_coff, k, stride, pad;
 };
 hipError_t launch_maxpool(int dtype, const PoolArgs& a, hipStream_t s);
+// Three chained stride-1 "same" pools (window a.k) of a.x, every stage's result written; a.y is not used.
+// hipErrorNotSupported when the map does not fit LDS or a tensor is not in whole 16-byte vectors.
+struct PoolChain { void* y[3]; int ld[3], coff[3]; };
+hipError_t launch_maxpool_chain(int dtype, const PoolArgs& a, const PoolChain& ch, hipStream_t s);
 hipError_t launch_upsample2x(int dtype, const PoolArgs& a, hipStream_t s);       // uses H, W, C, lds/coffs
 hipError_t launch_copy_channels(int dtype, const PoolArgs& a, hipStream_t s);    // y[:, :, :, coff:coff+C] = x
 struct AddArgs {
@@ -83,7 +88,10 @@ struct AddArgs {
 };
 hipError_t launch_add(int dtype, const AddArgs& a, hipStream_t s);
 hipError_t launch_gap(int dtype, const PoolArgs& a, hipStream_t s);              // y [n][C] mean over H*W
-hipError_t launch_argmax(const float* logits, int ld, int n_out, const int* n_dyn, int n, int* labels, hipStream_t s);
+// Where the labels of a child's items go besides its own label array: child_label[slot] of the box that item r was cropped
+// from (rois[r]: frame, rank).  boxes == nullptr: nowhere.
+struct LabelDest { octo_box* boxes = nullptr; const octo_roi* rois = nullptr; int max_det = 0, slot = 0; };
+hipError_t launch_argmax(const float* logits, int ld, int n_out, const int* n_dyn, int n, int* labels, const LabelDest& d, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int value, int count, hipStream_t s);
 
 // floor(n / d) for n < 2^31 by multiply-high and shift; built on the host
@@ -146,6 +154,7 @@ struct NmsArgs {
   unsigned long long* mask;                                  // [n][k_cap][k_cap/64]
   int* keep; int* n_keep;                                    // keep[item*max_det ...]
   int n; const int* n_dyn;
+  LabelDest dest;                                            // child detectors: the number of kept boxes is the item's label
 };
 hipError_t launch_nms(const NmsArgs& a, hipStream_t s);
 size_t nms_mask_bytes(int n, int k_cap);
@@ -165,11 +174,23 @@ struct CompactArgs {
 };
 hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
 
-struct LabelArgs {
-  octo_box* boxes; const int* n_keep; int max_det; int n;
-  int n_edges; const int* roi_of[OCTO_MAX_EDGES]; const int* labels[OCTO_MAX_EDGES]; const int* n_roi[OCTO_MAX_EDGES];
+// First launch of a batch: the frame table (passed by value, at most MAX frames per launch) and cleared counters.
+struct BeginArgs {
+  static constexpr int MAX = 64, REGIONS = 4;
+  const uint8_t* ptr[MAX]; size_t pitch[MAX];
+  int n;                                   // frames of this launch
+  const uint8_t** d_ptr; size_t* d_pitch;
+  int* clear[REGIONS]; int clear_count[REGIONS];      // ranges of ints to zero (nullptr / 0: unused)
 };
-hipError_t launch_scatter_labels(const LabelArgs& a, hipStream_t s);
+hipError_t launch_begin(const BeginArgs& a, hipStream_t s);
+
+// Last launch of a batch: the result block's header and the boxes in use go straight to pinned host memory.
+struct PublishArgs {
+  const char* src; char* dst;              // result block on the device, its mirror in host memory
+  int header_bytes;                        // counters in front of the boxes (a multiple of 16)
+  const int* n_keep; int max_det; int n;
+};
+hipError_t launch_publish(const PublishArgs& a, hipStream_t s);
 
 // ---- host-side scheduling (no GPU) ------------------------------------------
 int cwd_search(octo_sched_pipeline* p);

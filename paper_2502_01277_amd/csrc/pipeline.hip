@@ -53,6 +53,9 @@ struct LayerPlan {
   // convolution kernel pools its own tile and writes the pooled tensor, the pool layer does nothing (its kernel id
   // then reads KID_NONE).  Cleared for good the first time no kernel accepts the fused form.
   bool fuse_pool = false;
+  // This and the next two layers are chained stride-1 max-pools of one size (a spatial-pyramid block): one launch does all
+  // three; the next two layers then do nothing.  Cleared for good the first time no kernel accepts the chain.
+  bool fuse_chain = false;
   // The next layer is a 1x1 convolution of the same input with the same activation (the two entry convolutions of a
   // cross-stage block): one launch computes both - the weight matrices stacked, the second layer's channels written to
   // its own tensor - so the input is read once.  The next layer then does nothing (kernel id KID_NONE).  Cleared for
@@ -133,10 +136,9 @@ struct octo_pipeline {
   // result block (device) and its pinned host mirrors
   char* d_result = nullptr; size_t result_bytes = 0;
   size_t off_nkeep = 0, off_flags = 0, off_nroi = 0, off_boxes = 0;
-  char* h_result[RING]{};
+  char* h_result[RING]{}; char* h_result_dev[RING]{};      // host address and the address kernels write to
   // frame pointer tables
   const uint8_t** d_frames[RING]{}; size_t* d_pitch[RING]{};
-  char* h_tables[RING]{};
   // geometry
   int nw = 0, nh = 0, left = 0, top = 0;
   std::deque<QueuedFrame> queue;
@@ -331,6 +333,13 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
       for (int k = 0; k < q.L.n_in; ++k) readers += q.L.in[k] == i + 1;
     lp.fuse_pool = readers == 1;
   }
+  // three chained stride-1 max-pools of one size
+  for (int i = 0; i + 2 < (int)m.layers.size(); ++i) {
+    const octo_layer &A = m.layers[i].L, &B = m.layers[i + 1].L, &C = m.layers[i + 2].L;
+    auto same = [](const octo_layer& L) { return L.op == OCTO_MAXPOOL && L.stride == 1 && (L.kh & 1) && L.kh > 1 && L.pad == L.kh / 2; };
+    m.layers[i].fuse_chain = allow_fusion && same(A) && same(B) && same(C) && A.kh == B.kh && B.kh == C.kh && B.in[0] == i + 1 && C.in[0] == i + 2 &&
+                             !(i > 0 && (m.layers[i - 1].fuse_pool || m.layers[i - 1].fuse_chain)) && !(i > 1 && m.layers[i - 2].fuse_chain);
+  }
   // two 1x1 convolutions in a row that read the same tensor: one launch (16-bit types; channel counts and output
   // views in whole 16-byte vectors; no residual, not the first layer, no fp32 output)
   for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_twin = false;
@@ -356,6 +365,9 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
       const int r = m.tensors[i + 2].root;
       birth[r] = std::min(birth[r], i);
     }
+  for (int i = 0; i < (int)m.layers.size(); ++i)
+    if (m.layers[i].fuse_chain)
+      for (int q = 2; q <= 3; ++q) { const int r = m.tensors[i + q].root; birth[r] = std::min(birth[r], i); }
   for (int i = 0; i < (int)m.layers.size(); ++i)
     for (int k = 0; k < m.layers[i].L.n_in; ++k) {
       const int r = m.tensors[m.layers[i].L.in[k]].root;
@@ -514,8 +526,16 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
     }
     case OCTO_MAXPOOL: {
       if (i > 0 && m.layers[i - 1].fuse_pool) { lp.kernel_id = KID_NONE; return hipSuccess; }
+      if ((i > 0 && m.layers[i - 1].fuse_chain) || (i > 1 && m.layers[i - 2].fuse_chain)) { lp.kernel_id = KID_NONE; return hipSuccess; }
       PoolArgs a{x.ptr, y.ptr, n_dyn, n, x.h, x.w, x.c, x.ld, x.coff, y.h, y.w, y.ld, y.coff, L.kh, L.stride, L.pad};
       lp.kernel_id = KID_MAXPOOL;
+      if (lp.fuse_chain) {
+        PoolChain ch;
+        for (int q = 0; q < 3; ++q) { const TensorView v = view_of(m, i + 1 + q); ch.y[q] = v.ptr; ch.ld[q] = v.ld; ch.coff[q] = v.coff; }
+        const hipError_t e = launch_maxpool_chain(m.d.dtype, a, ch, s);
+        if (e != hipErrorNotSupported) return e;
+        lp.fuse_chain = false;
+      }
       return launch_maxpool(m.d.dtype, a, s);
     }
     case OCTO_UPSAMPLE2X: {
@@ -568,10 +588,9 @@ hipError_t run_layers(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, h
 
 // decode -> top-k -> NMS of a detector (root or child) for n items.  The head tensors hold items 0 .. n-1 of this
 // execution; their results go to slots item0 .. item0 + n - 1 of the model's per-item arrays (item0 > 0 when the
-// detector of one batch runs in several executions).
-hipError_t run_detect_tail(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, hipStream_t s, hipEvent_t* evs, int item0 = 0) {
-  hipError_t e = launch_fill_i32(m.cand_count + (size_t)item0 * CNT_STRIDE, 0, n * CNT_STRIDE, s);
-  if (e != hipSuccess) return e;
+// detector of one batch runs in several executions).  The candidate counters must have been cleared.
+hipError_t run_detect_tail(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, hipStream_t s, hipEvent_t* evs, int item0 = 0, LabelDest dest = LabelDest()) {
+  hipError_t e;
   DecodeArgs da{};
   da.n_levels = m.d.n_outputs;
   const int es = dtype_size(m.d.dtype);
@@ -591,7 +610,7 @@ hipError_t run_detect_tail(octo_pipeline* p, ModelPlan& m, int n, const int* n_d
   if ((e = launch_topk(ta, s)) != hipSuccess) return e;
   if (evs) hipEventRecord(evs[1], s);
   // the suppression bit mask is scratch of one execution: every execution uses the first n items' worth of it
-  NmsArgs na{ta.out, ta.out_count, m.k_cap, m.d.iou_thr, m.d.max_det, m.mask, m.keep + (size_t)item0 * m.d.max_det, m.n_keep + item0, n, n_dyn};
+  NmsArgs na{ta.out, ta.out_count, m.k_cap, m.d.iou_thr, m.d.max_det, m.mask, m.keep + (size_t)item0 * m.d.max_det, m.n_keep + item0, n, n_dyn, dest};
   if ((e = launch_nms(na, s)) != hipSuccess) return e;
   if (evs) hipEventRecord(evs[2], s);
   return hipSuccess;
@@ -742,13 +761,7 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched) {
         hipEvent_t e = get_event(p); if (e) b.layer_ev[k].push_back(e); else ok = false;
       }
   if (!ok) { give_back(b); *launched = 0; return fail(p, OCTO_EHIP, "hipEventCreate failed"); }
-  const void** hp = (const void**)p->h_tables[b.slot];
-  size_t* hpitch = (size_t*)(p->h_tables[b.slot] + (size_t)p->max_frames * sizeof(void*));
-  for (int i = 0; i < n; ++i) {
-    const QueuedFrame& q = p->queue[i];
-    hp[i] = q.ptr; hpitch[i] = q.pitch;
-    b.ids.push_back(q.id); b.arrival.push_back(q.arrival);
-  }
+  for (int i = 0; i < n; ++i) { b.ids.push_back(p->queue[i].id); b.arrival.push_back(p->queue[i].arrival); }
   b.t_launch = octo_now_ms();
   b.model_ran.assign(p->models.size(), false);
   p->inflight.push_back(std::move(b));
@@ -772,18 +785,42 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched) {
 octo_status enqueue_root(octo_pipeline* p, hipStream_t s, int n) {
   ModelPlan& root = p->models[0];
   Batch& B = p->inflight.back();
-  const void** hp = (const void**)p->h_tables[B.slot];
-  size_t* hpitch = (size_t*)(p->h_tables[B.slot] + (size_t)p->max_frames * sizeof(void*));
   hipEvent_t* ev = p->stage_timing ? B.stage_ev.data() : nullptr;
-  HIPCHK(p, hipMemcpyAsync(p->d_frames[B.slot], hp, n * sizeof(void*), hipMemcpyHostToDevice, s));
-  HIPCHK(p, hipMemcpyAsync(p->d_pitch[B.slot], hpitch, n * sizeof(size_t), hipMemcpyHostToDevice, s));
+  // frame table and cleared counters (result header, candidate counters and flags of every detector) in one launch; more
+  // frames or detectors than one launch takes are handed to further ones
+  {
+    BeginArgs ba{};
+    int r = 0, at = 0;
+    auto flush = [&]() -> hipError_t { const hipError_t e = launch_begin(ba, s); ba = BeginArgs{}; r = 0; return e; };
+    auto clear = [&](int* ptr, int count) -> hipError_t {
+      if (!ptr || count <= 0) return hipSuccess;
+      hipError_t e = hipSuccess;
+      if (r == BeginArgs::REGIONS) e = flush();
+      ba.clear[r] = ptr; ba.clear_count[r++] = count;
+      return e;
+    };
+    HIPCHK(p, clear((int*)p->d_result, (int)(p->off_boxes / sizeof(int))));      // n_keep, flags, n_roi
+    HIPCHK(p, clear(root.cand_count, n * CNT_STRIDE));
+    for (const octo_edge& ed : p->edges) {
+      ModelPlan& c = p->models[ed.child];
+      if (c.d.kind != OCTO_DETECTOR) continue;
+      HIPCHK(p, clear(c.cand_count, c.cap * CNT_STRIDE));
+      HIPCHK(p, clear(c.flags, c.cap));
+    }
+    do {
+      ba.n = std::min(n - at, BeginArgs::MAX);
+      for (int i = 0; i < ba.n; ++i) { ba.ptr[i] = (const uint8_t*)p->queue[at + i].ptr; ba.pitch[i] = p->queue[at + i].pitch; }
+      ba.d_ptr = p->d_frames[B.slot] + at; ba.d_pitch = p->d_pitch[B.slot] + at;
+      at += ba.n;
+      HIPCHK(p, flush());
+    } while (at < n);
+  }
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
   ResizeArgs ra{};
   ra.src_h = p->d.src_h; ra.src_w = p->d.src_w;
   ra.dst = view_of(root, 0).ptr; ra.dst_h = root.d.in_h; ra.dst_w = root.d.in_w; ra.dst_c = root.input_c4 ? 4 : 3;
   for (int c = 0; c < 3; ++c) { ra.scale[c] = root.d.norm_scale[c]; ra.bias[c] = root.d.norm_bias[c]; }
   ra.pad_value = root.d.pad_value;
-  HIPCHK(p, launch_fill_i32((int*)p->d_result, 0, (int)((p->off_boxes) / sizeof(int)), s));   // n_keep, flags, n_roi
   // The detector runs on exec_bz frames at a time (its own batch size; by default the whole batch), every execution
   // through the same activation buffers; candidates, top-k lists and keep lists are per frame and collect in place.
   // Stage events (when enabled) bracket the last execution's stages; the letterbox and layer stages of the earlier
@@ -829,12 +866,13 @@ octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool wai
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
   HIPCHK(p, run_layers(p, c, c.cap, c.n_dyn, s, p->layer_timing ? &B.layer_ev[p->edges[e].child] : nullptr));
   if (ev) HIPCHK(p, hipEventRecord(ev[1], s));
+  LabelDest dest;                        // the results of the first edges go into the boxes the items came from
+  if (e < OCTO_MAX_CHILD_LABELS) dest = LabelDest{(octo_box*)(p->d_result + p->off_boxes), p->rois[e], p->models[0].d.max_det, e};
   if (c.d.kind == OCTO_CLASSIFIER) {
     const TensorView lg = view_of(c, c.d.outputs[0]);
-    HIPCHK(p, launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, c.n_logits, c.n_dyn, c.cap, c.labels, s));
+    HIPCHK(p, launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, c.n_logits, c.n_dyn, c.cap, c.labels, dest, s));
   } else {
-    HIPCHK(p, launch_fill_i32(c.flags, 0, c.cap, s));
-    HIPCHK(p, run_detect_tail(p, c, c.cap, c.n_dyn, s, nullptr));
+    HIPCHK(p, run_detect_tail(p, c, c.cap, c.n_dyn, s, nullptr, 0, dest));
   }
   if (ev) HIPCHK(p, hipEventRecord(ev[2], s));
   HIPCHK(p, hipEventRecord(p->ev_child[e], s));
@@ -849,13 +887,8 @@ octo_status finalize_batch(octo_pipeline* p, Batch& B, hipStream_t s, bool cross
     HIPCHK(p, hipStreamWaitEvent(s, p->ev_det, 0));
     for (int e = 0; e < (int)p->edges.size(); ++e) HIPCHK(p, hipStreamWaitEvent(s, p->ev_child[e], 0));
   }
-  LabelArgs la{};
-  la.boxes = (octo_box*)(p->d_result + p->off_boxes); la.n_keep = root.n_keep; la.max_det = root.d.max_det; la.n = B.n;
-  la.n_edges = (int)p->edges.size();
-  for (int e = 0; e < la.n_edges; ++e) { la.roi_of[e] = p->roi_of[e]; la.labels[e] = p->models[p->edges[e].child].labels; la.n_roi[e] = p->n_roi[e]; }
-  HIPCHK(p, launch_scatter_labels(la, s));
-  const size_t bytes = p->off_boxes + (size_t)B.n * root.d.max_det * sizeof(octo_box);
-  HIPCHK(p, hipMemcpyAsync(p->h_result[B.slot], p->d_result, bytes, hipMemcpyDeviceToHost, s));
+  PublishArgs pa{p->d_result, p->h_result_dev[B.slot], (int)p->off_boxes, root.n_keep, root.d.max_det, B.n};
+  HIPCHK(p, launch_publish(pa, s));
   HIPCHK(p, hipEventRecord(B.done, s));
   B.finalized = true;
   return OCTO_OK;
@@ -893,8 +926,8 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
     int dev = 0; hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) p->num_cu = prop.multiProcessorCount;
     for (int r = 0; r < RING && st == OCTO_OK; ++r) {
-      if (hipHostMalloc((void**)&p->h_result[r], p->result_bytes, hipHostMallocDefault) != hipSuccess ||
-          hipHostMalloc((void**)&p->h_tables[r], (size_t)p->max_frames * (sizeof(void*) + sizeof(size_t)), hipHostMallocDefault) != hipSuccess)
+      if (hipHostMalloc((void**)&p->h_result[r], p->result_bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+          hipHostGetDevicePointer((void**)&p->h_result_dev[r], p->h_result[r], 0) != hipSuccess)
         st = fail(p, OCTO_ENOMEM, "pinned host allocation failed");
     }
     if (st == OCTO_OK && hipEventCreate(&p->ev_det) != hipSuccess) st = fail(p, OCTO_EHIP, "hipEventCreate failed");
@@ -919,7 +952,7 @@ octo_status octo_pipeline_destroy(octo_pipeline* p) {
   for (hipEvent_t e : p->event_pool) hipEventDestroy(e);
   if (p->ev_det) hipEventDestroy(p->ev_det);
   for (hipEvent_t e : p->ev_child) hipEventDestroy(e);
-  for (int r = 0; r < RING; ++r) { if (p->h_result[r]) hipHostFree(p->h_result[r]); if (p->h_tables[r]) hipHostFree(p->h_tables[r]); }
+  for (int r = 0; r < RING; ++r) if (p->h_result[r]) hipHostFree(p->h_result[r]);
   delete p;
   return OCTO_OK;
 }
@@ -1230,10 +1263,11 @@ octo_status octo_debug_run_model(octo_pipeline* p, int32_t model, const void* d_
   HIPCHK(p, run_layers(p, m, n, nullptr, s));
   if (m.d.kind == OCTO_DETECTOR) {
     if (m.flags) HIPCHK(p, launch_fill_i32(m.flags, 0, m.cap, s));
+    HIPCHK(p, launch_fill_i32(m.cand_count, 0, n * CNT_STRIDE, s));
     HIPCHK(p, run_detect_tail(p, m, n, nullptr, s, nullptr));
   } else if (m.labels) {
     const TensorView lg = view_of(m, m.d.outputs[0]);
-    HIPCHK(p, launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, m.n_logits, nullptr, n, m.labels, s));
+    HIPCHK(p, launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, m.n_logits, nullptr, n, m.labels, LabelDest(), s));
   }
   return OCTO_OK;
 }

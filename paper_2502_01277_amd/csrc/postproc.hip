@@ -1,5 +1,5 @@
 // Detector post-processing: box decode + score threshold, per-item top-k,
-// class-wise greedy NMS, ROI compaction and label scatter.
+// class-wise greedy NMS, ROI compaction, and the first and last launch of a batch.
 //
 // Every decision that produces an integer (threshold, order, suppression) is
 // taken in fp32 with individually rounded operations (no contraction to FMA),
@@ -432,7 +432,10 @@ __global__ __launch_bounds__(64) void nms_reduce_kernel(const NmsArgs a) {
         }
       }
     }
-    if (lane == 0) a.n_keep[item] = n_keep;
+    if (lane == 0) {
+      a.n_keep[item] = n_keep;
+      if (a.dest.boxes) a.dest.boxes[(size_t)a.dest.rois[item].frame * a.dest.max_det + a.dest.rois[item].rank].child_label[a.dest.slot] = n_keep;
+    }
   }
 }
 
@@ -561,24 +564,39 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void scatter_labels_kernel(const LabelArgs a) {
-  const long long total = (long long)a.n * a.max_det;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-    const int item = (int)(i / a.max_det), r = (int)(i % a.max_det);
-    int nk = a.n_keep[item]; if (nk > a.max_det) nk = a.max_det;
-    if (r >= nk) continue;
-    for (int e = 0; e < a.n_edges && e < OCTO_MAX_CHILD_LABELS; ++e) {
-      const int id = a.roi_of[e][i];
-      a.boxes[i].child_label[e] = (id >= 0 && id < *a.n_roi[e]) ? a.labels[e][id] : -1;
-    }
-  }
+__global__ __launch_bounds__(256) void begin_kernel(const BeginArgs a) {
+  const int i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (i0 < a.n) { a.d_ptr[i0] = a.ptr[i0]; a.d_pitch[i0] = a.pitch[i0]; }
+#pragma unroll
+  for (int r = 0; r < BeginArgs::REGIONS; ++r)
+    for (int i = i0; i < a.clear_count[r]; i += step) a.clear[r][i] = 0;
 }
 
-hipError_t launch_scatter_labels(const LabelArgs& a, hipStream_t s) {
-  if (a.n <= 0 || a.n_edges <= 0) return hipSuccess;
-  long long total = (long long)a.n * a.max_det;
-  unsigned g = (unsigned)((total + 255) / 256);
-  hipLaunchKernelGGL(scatter_labels_kernel, dim3(g > 1024 ? 1024 : g), dim3(256), 0, s, a);
+hipError_t launch_begin(const BeginArgs& a, hipStream_t s) {
+  if (a.n < 0 || a.n > BeginArgs::MAX) return hipErrorInvalidValue;
+  long long most = 256;
+  for (int r = 0; r < BeginArgs::REGIONS; ++r) if (a.clear_count[r] > most) most = a.clear_count[r];
+  const long long g = (most + 255) / 256;
+  hipLaunchKernelGGL(begin_kernel, dim3((unsigned)(g > 1024 ? 1024 : g)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// One workgroup per frame.  Only boxes in use cross the bus; a copy of the block by the runtime is a launch (or a trip
+// through a copy engine) of its own and takes 3 - 5 us more.
+__global__ __launch_bounds__(256) void publish_kernel(const PublishArgs a) {
+  const int item = blockIdx.x;
+  if (item == 0)
+    for (int i = threadIdx.x; i < a.header_bytes / 16; i += blockDim.x) ((uint4*)a.dst)[i] = ((const uint4*)a.src)[i];
+  int nk = a.n_keep[item]; if (nk > a.max_det) nk = a.max_det;
+  const size_t off = (size_t)a.header_bytes + (size_t)item * a.max_det * sizeof(octo_box);
+  const uint4* s = (const uint4*)(a.src + off);
+  uint4* d = (uint4*)(a.dst + off);
+  for (int i = threadIdx.x; i < nk * (int)(sizeof(octo_box) / 16); i += blockDim.x) d[i] = s[i];
+}
+
+hipError_t launch_publish(const PublishArgs& a, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(publish_kernel, dim3(a.n), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -60,9 +60,9 @@ __global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a)
   if (a.n_dyn) { int d = *a.n_dyn; n_items = d < a.n ? d : a.n; }
   const int tiles_y = (a.Ho + TH - 1) / TH;
   const int tiles_x = POOL ? (a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS : (a.Wo + TW - 1) / TW;
-  // unit of work: a tile, or (POOL) a strip of tiles_y tiles
-  const int per_img = POOL ? tiles_x : tiles_x * tiles_y;
-  const int tiles_per_unit = POOL ? tiles_y : 1;
+  // unit of work: a tile, or (POOL) a segment of pool_seg tiles of a strip
+  const int seg = POOL ? a.pool_seg : 1;
+  const int per_img = tiles_x * ((tiles_y + seg - 1) / seg);
   const long long n_units = (long long)n_items * per_img;
   const T* __restrict__ xg = (const T*)a.x + a.x_coff;
   const long long img_elems = (long long)a.H * a.W * a.x_ld;
@@ -92,14 +92,17 @@ __global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a)
     while (t < t_end && unit_of(t) >= n_units) t += gridDim.x;
     return t;
   };
-  // (position in the unit list, tile of the unit) -> image, tile row and column
+  // (position in the unit list, tile of the unit) -> image, tile row and column.  Tile -1 of a segment that does not start
+  // at the top of its strip is the last tile of the segment above, computed once more for the row it carries over.
   auto locate = [&](long long t, int k, int& img, int& ty, int& tx) {
     const long long unit = unit_of(t);
     img = (int)(unit / per_img);
     const int rem = (int)(unit - (long long)img * per_img);
-    ty = POOL ? k : rem / tiles_x;
-    tx = POOL ? rem : rem - ty * tiles_x;
+    const int row = rem / tiles_x;
+    ty = row * seg + k;
+    tx = rem - row * tiles_x;
   };
+  auto first_tile = [&](long long t) -> int { return POOL && unit_of(t) % per_img >= tiles_x ? -1 : 0; };
   // global loads of a tile's input patch (zeros outside the image); one image per buffer: 32-bit offsets suffice
   u32x4 pv[PLOADS];
   auto load_patch = [&](long long t, int k) {
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a)
 
   long long t = next_valid(blockIdx.x);
   int k = 0;
-  if (t < t_end) load_patch(t, k);
+  if (t < t_end) { k = first_tile(t); load_patch(t, k); }
   while (t < t_end) {
     int img, ty, tx;
     locate(t, k, img, ty, tx);
@@ -157,7 +160,10 @@ __global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a)
     // the next tile's patch is fetched while this one is staged and written (or pooled)
     long long nt = t;
     int nk = k + 1;
-    if (nk == tiles_per_unit) { nk = 0; nt = next_valid(t + gridDim.x); }
+    if (nk == seg || ty + 1 == tiles_y || !POOL) {
+      nt = next_valid(t + gridDim.x);
+      if (nt < t_end) nk = first_tile(nt);
+    }
     if (nt < t_end) load_patch(nt, nk);
 
     __syncthreads();                     // everyone is done with the patch: the region now stages the output
@@ -195,6 +201,7 @@ __global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a)
     __syncthreads();
     constexpr int VPR = BC / 8;                  // 16-byte vectors per pixel
     if constexpr (POOL) {
+      if (k < 0) { t = nt; k = nk; continue; }
       // pooled rows 4 ty .. 4 ty + 3: window rows 2 py - 1 .. 2 py + 1 = staged rows -1 (the carry) .. 7; window columns
       // 2 pc .. 2 pc + 2 of the tile (convolution column = ox0 + tile column)
       constexpr int POOL_ROWS = TH / 2;
@@ -263,7 +270,7 @@ int stem_kernel_id(int bc, int kh, int pkw, bool pool) { return 1900000000 + (po
 template <typename T, int BC, int KH, int PKW, bool POOL>
 static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (kernel_id) *kernel_id = stem_kernel_id(BC, KH, PKW, POOL);
-  const long long units = POOL ? (long long)a.n * ((a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS)
+  const long long units = POOL ? (long long)a.n * ((a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS) * (((a.Ho + STEM_TH - 1) / STEM_TH + a.pool_seg - 1) / a.pool_seg)
                                : (long long)a.n * ((a.Wo + STEM_TW - 1) / STEM_TW) * ((a.Ho + STEM_TH - 1) / STEM_TH);
   if (units <= 0) return hipSuccess;
   long long grid = (units + 7) / 8 * 8;
@@ -279,8 +286,20 @@ static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, 
 template <typename T>
 static hipError_t launch_stem_typed(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (a.pool_y) {
-    if (a.kh == 7 && a.kw == 4 && a.Cout <= 64) return launch_stem_cfg<T, 64, 7, 4, true>(a, num_cu, s, kernel_id, tm);
-    return hipErrorNotSupported;
+    if (a.kh != 7 || a.kw != 4 || a.Cout > 64) return hipErrorNotSupported;
+    // Tiles per segment: a strip walked by one workgroup is a serial chain (11 crops of 224 x 224 have 44 strips of 14
+    // tiles: 68 us on 44 of the chip's 512 workgroup slots).  Cut into segments it costs one more tile for each cut; the
+    // length with the shortest busiest slot is taken, for the expected number of items.
+    ConvArgs b = a;
+    const int tiles_y = (a.Ho + STEM_TH - 1) / STEM_TH;
+    const long long strips = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * ((a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS);
+    long long best = 0;
+    for (int seg = tiles_y; seg >= 1; --seg) {
+      const long long units = strips * ((tiles_y + seg - 1) / seg), rounds = (units + 2 * num_cu - 1) / (2 * num_cu);
+      const long long tiles = rounds * (seg == tiles_y ? seg : seg + 1);
+      if (seg == tiles_y || tiles < best) { best = tiles; b.pool_seg = seg; }
+    }
+    return launch_stem_cfg<T, 64, 7, 4, true>(b, num_cu, s, kernel_id, tm);
   }
   if (a.kh == 7 && a.kw == 4 && a.Cout <= 64) return launch_stem_cfg<T, 64, 7, 4, false>(a, num_cu, s, kernel_id, tm);
   if (a.kh == 6 && a.kw == 3 && a.Cout <= 32) return launch_stem_cfg<T, 32, 6, 3, false>(a, num_cu, s, kernel_id, tm);
