@@ -497,6 +497,7 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   const GeneralTile st = general_tile(a, M_split, num_cu, 1);
   const int ks = ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
   if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
+  if (a.up_y) return hipErrorNotSupported;
   const GeneralTile t = general_tile(a, M, num_cu, 1);
   if (t.bc == 32) return launch_cfg<T, 32, 128, 1, 4, 4, 2, 4, true>(a, num_cu, s, kernel_id, tm);
   if (t.bp == 256) return launch_cfg<T, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
@@ -582,6 +583,15 @@ hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s,
     // two layers in one launch: only the general kernel's staged epilogue knows the second output tensor
     const bool ok = (dtype == OCTO_F16 || dtype == OCTO_BF16) && a.y2 && !a.res && !a.out_f32 && !a.pair_view && !a.pool_y && a.split < a.Cout &&
                     ((a.split | a.Cout | a.y_ld | a.y_coff | a.y2_ld | a.y2_coff) & 7) == 0 && ((((uintptr_t)a.y | (uintptr_t)a.y2) & 15) == 0);
+    if (!ok) return hipErrorNotSupported;
+    return dtype == OCTO_F16 ? launch_general_f16(a, num_cu, s, kernel_id, tm) : launch_general_bf16(a, num_cu, s, kernel_id, tm);
+  }
+  if (a.up_y) {
+    // the output and its upsampled copy from one launch: the split-K kernel (launch_typed refuses the others; in the
+    // general kernel's epilogue the test for it alone cost every layer 2 %)
+    const bool ok = (dtype == OCTO_F16 || dtype == OCTO_BF16) && !a.out_f32 && !a.pair_view && !a.pool_y && a.kh == 1 && a.kw == 1 &&
+                    ((a.Cout | a.y_ld | a.y_coff | a.up_ld | a.up_coff) & 7) == 0 && (a.Cin & 7) == 0 && ((a.x_ld | a.x_coff) & 7) == 0 &&
+                    ((((uintptr_t)a.x | (uintptr_t)a.y | (uintptr_t)a.up_y) & 15) == 0);
     if (!ok) return hipErrorNotSupported;
     return dtype == OCTO_F16 ? launch_general_f16(a, num_cu, s, kernel_id, tm) : launch_general_bf16(a, num_cu, s, kernel_id, tm);
   }

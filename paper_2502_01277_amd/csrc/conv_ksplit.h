@@ -273,14 +273,20 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(const ConvArgs a, 
             typedef T t8 __attribute__((ext_vector_type(8)));
             const t8 w = {(T)v[0][0], (T)v[0][1], (T)v[0][2], (T)v[0][3], (T)v[1][0], (T)v[1][1], (T)v[1][2], (T)v[1][3]};
             *(u32x4*)((T*)yb + o) = __builtin_bit_cast(u32x4, w);
+            if (a.up_y) store_upsampled<T>(a, (unsigned)p, c, __builtin_bit_cast(u32x4, w));
             continue;
           }
         }
         {
 #pragma unroll
           for (int h = 0; h < VG / 4; ++h) {
-            if (y_vec) store4<T>((T*)yb + o + h * 4, v[h]);
-            else {
+            if (y_vec) {
+              store4<T>((T*)yb + o + h * 4, v[h]);
+              if constexpr (ES == 2) {
+                typedef T t4 __attribute__((ext_vector_type(4)));
+                if (a.up_y) store_upsampled<T>(a, (unsigned)p, c + h * 4, __builtin_bit_cast(u32x2, t4{(T)v[h][0], (T)v[h][1], (T)v[h][2], (T)v[h][3]}));
+              }
+            } else {
 #pragma unroll
               for (int e = 0; e < 4; ++e) if (c + h * 4 + e < a.Cout) ((T*)yb)[o + h * 4 + e] = from_f32<T>(v[h][e]);
             }

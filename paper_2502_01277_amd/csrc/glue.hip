@@ -343,9 +343,10 @@ template <typename T> static hipError_t maxpool_chain_t(const PoolArgs& a, const
   for (int st = 0; st < 3; ++st)
     if (!vec_ok<T>(a.x, a.x_ld, a.x_coff, ch.y[st], ch.ld[st], ch.coff[st], a.C)) return hipErrorNotSupported;
   // as many channel vectors per workgroup as keep two maps within 52 KB (three workgroups per compute unit), so that a
-  // workgroup reads 64 contiguous bytes of a pixel where the map is small
+  // workgroup reads 64 contiguous bytes of a pixel where the map is small and there are workgroups enough
+  // (8 workgroups on one 20 x 20 x 256 map: 22 us)
   int nv = 4;
-  while (nv > 1 && (a.C / V % nv || (long long)a.H * a.W * nv * 32 > 52 * 1024)) nv /= 2;
+  while (nv > 1 && (a.C / V % nv || (long long)a.H * a.W * nv * 32 > 52 * 1024 || (long long)a.n * (a.C / V / nv) < 512)) nv /= 2;
   const long long lds = (long long)a.H * a.W * nv * 32;
   if (lds > 64 * 1024 || (long long)a.n * (a.C / V) >= 0x7FFFFFF0LL) return hipErrorNotSupported;
   const long long units = ((long long)a.n * (a.C / V / nv) + 7) / 8 * 8;

@@ -147,6 +147,19 @@ __device__ __forceinline__ void with_epilogue_mode(int res_mode, bool is_silu, F
   }
 }
 
+// One vector (8 or 16 bytes) of output pixel p, channels c .., to the 2x upsampled copy of the output.
+template <typename T, typename V>
+__device__ __forceinline__ void store_upsampled(const ConvArgs& a, unsigned p, int c, V val) {
+  const unsigned img = a.HoWo_is_one ? p : udiv(p, a.magic_howo, a.shift_howo);
+  const unsigned rem = p - img * (unsigned)(a.Ho * a.Wo);
+  const unsigned ho = a.Wo == 1 ? rem : udiv(rem, a.magic_wo, a.shift_wo);
+  const unsigned wo = rem - ho * (unsigned)a.Wo;
+  const size_t row = (size_t)(2 * a.Wo) * a.up_ld;
+  T* q = (T*)a.up_y + (((size_t)img * (2 * a.Ho) + 2 * ho) * (2 * a.Wo) + 2 * wo) * a.up_ld + a.up_coff + c;
+  *(V*)q = val; *(V*)(q + a.up_ld) = val;
+  *(V*)(q + row) = val; *(V*)(q + row + a.up_ld) = val;
+}
+
 constexpr int THREADS = 256;
 constexpr unsigned BUF_FLAGS = 0x00020000u;      // raw buffer, 32-bit data format
 constexpr int OOB = (int)0x80000000;             // offset beyond any buffer range: the load returns zeros

@@ -3,6 +3,7 @@
 // cascade pass, result collection, and the profiling / parity hooks.
 // No device code lives here.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -19,6 +20,7 @@ using namespace octo;
 namespace {
 
 thread_local std::string g_create_error;
+std::atomic<int> g_busy_pipelines{0};     // pipelines of this process with a batch in flight
 
 struct Arena {
   char* base = nullptr;   // nullptr: sizing pass
@@ -53,6 +55,9 @@ struct LayerPlan {
   // convolution kernel pools its own tile and writes the pooled tensor, the pool layer does nothing (its kernel id
   // then reads KID_NONE).  Cleared for good the first time no kernel accepts the fused form.
   bool fuse_pool = false;
+  // The next layer is a nearest 2x upsampling of this convolution's output.  Where the kernel chosen for the launch can
+  // write both tensors it does (up_done) and the next layer does nothing.
+  bool fuse_up = false, up_done = false;
   // This and the next two layers are chained stride-1 max-pools of one size (a spatial-pyramid block): one launch does all
   // three; the next two layers then do nothing.  Cleared for good the first time no kernel accepts the chain.
   bool fuse_chain = false;
@@ -87,7 +92,8 @@ struct ModelPlan {
   int exec_bz = 0;         // root only: frames per execution of the detector's layers (0: the whole batch at once)
   const int* n_dyn = nullptr;
   int items_split = 0;     // children: item count that kernels with another order of summation are chosen for (fixed)
-  double items_hint = 0;   // smoothed item count of recent batches (children; 0: none seen yet)
+  double items_mean = 0;   // smoothed item count of recent batches (children; 0: none seen yet)
+  int items_hint = 0;      // the same rounded up to the next of 1, 2, 3, 4, 6, 8, 12, 16 ... (what kernel shapes are chosen for)
   char* act_base = nullptr;
   size_t act_bytes = 0;
   // detector
@@ -116,9 +122,22 @@ struct Batch {
   std::vector<bool> model_ran;
 };
 
+// The launches of one whole batch between the frame table and the results, recorded once and replayed as a graph: the
+// sequence depends only on this key.
+struct GraphKey {
+  int n = 0, heads = 0, hint[OCTO_MAX_EDGES]{};
+  bool operator==(const GraphKey& o) const {
+    bool same = n == o.n && heads == o.heads;
+    for (int e = 0; e < OCTO_MAX_EDGES; ++e) same = same && hint[e] == o.hint[e];
+    return same;
+  }
+};
+struct GraphEntry { GraphKey key; hipGraphExec_t exec = nullptr; unsigned long long used = 0; };
+
 struct QueuedFrame { const void* ptr; size_t pitch; double arrival; int64_t id; };
 
 constexpr int RING = 8;
+constexpr size_t MAX_GRAPHS = 8;
 constexpr int CNT_STRIDE = 32;   // candidate counters sit 128 bytes apart: same-line atomics serialise in L2
 
 }  // namespace
@@ -138,12 +157,22 @@ struct octo_pipeline {
   size_t off_nkeep = 0, off_flags = 0, off_nroi = 0, off_boxes = 0;
   char* h_result[RING]{}; char* h_result_dev[RING]{};      // host address and the address kernels write to
   // frame pointer tables
-  const uint8_t** d_frames[RING]{}; size_t* d_pitch[RING]{};
+  const uint8_t** d_frames = nullptr; size_t* d_pitch = nullptr;      // of the batch on the GPU: batches of a pipeline follow one another
   // geometry
   int nw = 0, nh = 0, left = 0, top = 0;
   std::deque<QueuedFrame> queue;
   std::deque<Batch> inflight;
-  std::vector<hipEvent_t> event_pool;
+  std::vector<hipEvent_t> event_pool, done_pool;      // with timing; without
+  // recorded launch sequences: at most MAX_GRAPHS, the least recently used one makes room; one that may still be running
+  // waits in `retired` until nothing is in flight
+  std::vector<GraphEntry> graphs;
+  std::vector<hipGraphExec_t> retired;
+  hipStream_t capture_stream = nullptr;
+  unsigned long long graph_clock = 0;
+  int heads_version = 0;
+  bool counted_busy = false;       // counted in g_busy_pipelines: a batch is in flight
+  bool overlapped = false;         // another pipeline had a batch in flight beside this one's last batch
+  bool graphs_off = false;
   int next_slot = 0;
   bool stage_timing = false, layer_timing = false;
   std::vector<float> last_stage_ms;
@@ -333,6 +362,13 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
       for (int k = 0; k < q.L.n_in; ++k) readers += q.L.in[k] == i + 1;
     lp.fuse_pool = readers == 1;
   }
+  // a 1x1 convolution followed by the upsampling of its output
+  for (int i = 0; i + 1 < (int)m.layers.size(); ++i) {
+    LayerPlan& lp = m.layers[i];
+    const octo_layer& U = m.layers[i + 1].L;
+    lp.fuse_up = allow_fusion && dtype_size(m.d.dtype) == 2 && lp.L.op == OCTO_CONV && lp.L.kh == 1 && lp.L.kw == 1 && !lp.pair_view && !lp.fuse_pool &&
+                 U.op == OCTO_UPSAMPLE2X && U.in[0] == i + 1;
+  }
   // three chained stride-1 max-pools of one size
   for (int i = 0; i + 2 < (int)m.layers.size(); ++i) {
     const octo_layer &A = m.layers[i].L, &B = m.layers[i + 1].L, &C = m.layers[i + 2].L;
@@ -346,7 +382,7 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
   for (int i = 0; i + 1 < (int)m.layers.size(); ++i) {
     LayerPlan& a = m.layers[i];
     const LayerPlan& b = m.layers[i + 1];
-    if (!allow_fusion || dtype_size(m.d.dtype) != 2 || a.fuse_pool || (i > 0 && m.layers[i - 1].fuse_twin)) continue;
+    if (!allow_fusion || dtype_size(m.d.dtype) != 2 || a.fuse_pool || a.fuse_up || (i > 0 && m.layers[i - 1].fuse_twin)) continue;
     if (a.L.op != OCTO_CONV || b.L.op != OCTO_CONV || a.L.n_in != 1 || b.L.n_in != 1 || a.L.in[0] != b.L.in[0] || a.pair_view || b.pair_view) continue;
     if (a.L.kh != 1 || a.L.kw != 1 || b.L.kh != 1 || b.L.kw != 1 || a.L.stride != 1 || b.L.stride != 1 || a.L.pad != 0 || b.L.pad != 0 || a.L.act != b.L.act) continue;
     const TensorPlan &ta = m.tensors[i + 1], &tb = m.tensors[i + 2];
@@ -361,7 +397,7 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     death[r] = std::max(death[r], t - 1);
   }
   for (int i = 0; i < (int)m.layers.size(); ++i)
-    if (m.layers[i].fuse_pool || m.layers[i].fuse_twin) {      // the next layer's output is written one step early, by this layer
+    if (m.layers[i].fuse_pool || m.layers[i].fuse_twin || m.layers[i].fuse_up) {      // the next layer's output is written one step early, by this layer
       const int r = m.tensors[i + 2].root;
       birth[r] = std::min(birth[r], i);
     }
@@ -502,7 +538,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (lp.pair_view) { a.W = x.w / 2; a.Cin = 8; a.x_ld = 8; a.kw = lp.pair_kw; a.stride_w = 1; a.pad_w = lp.pair_pad; a.pair_view = 1; }
       a.act = L.act; a.res_mode = L.res_mode; a.out_f32 = m.tensors[i + 1].f32 ? 1 : 0;
       if (L.n_in == 2) { const TensorView r = view_of(m, L.in[1]); a.res = r.ptr; a.res_ld = r.ld; a.res_coff = r.coff; }
-      if (n_dyn && m.items_hint > 0) a.n_hint = std::max(1, (int)(m.items_hint + 0.999));
+      if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
       if (i > 0 && m.layers[i - 1].fuse_twin) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (lp.fuse_twin) {
@@ -513,6 +549,14 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
         const hipError_t e = launch_conv(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
         if (e != hipErrorNotSupported) return e;
         lp.fuse_twin = false;
+      }
+      if (lp.fuse_up) {
+        const TensorView u = view_of(m, i + 2);
+        ConvArgs f = a;
+        f.up_y = u.ptr; f.up_ld = u.ld; f.up_coff = u.coff;
+        const hipError_t e = launch_conv(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
+        lp.up_done = e == hipSuccess;
+        if (e != hipErrorNotSupported) return e;
       }
       if (lp.fuse_pool) {
         const TensorView py = view_of(m, i + 2);
@@ -539,6 +583,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       return launch_maxpool(m.d.dtype, a, s);
     }
     case OCTO_UPSAMPLE2X: {
+      if (i > 0 && m.layers[i - 1].fuse_up && m.layers[i - 1].up_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
       PoolArgs a{x.ptr, y.ptr, n_dyn, n, x.h, x.w, x.c, x.ld, x.coff, y.h, y.w, y.ld, y.coff, 1, 1, 0};
       lp.kernel_id = KID_UPSAMPLE;
       return launch_upsample2x(m.d.dtype, a, s);
@@ -695,10 +740,8 @@ octo_status build(octo_pipeline* p, const octo_pipeline_desc* desc, Arena& ar) {
     p->roi_of[e] = (int*)ar.alloc(mf * root.d.max_det * sizeof(int));
     p->roi_cnt[e] = (int*)ar.alloc(mf * sizeof(int));
   }
-  for (int r = 0; r < RING; ++r) {
-    p->d_frames[r] = (const uint8_t**)ar.alloc(mf * sizeof(void*));
-    p->d_pitch[r] = (size_t*)ar.alloc(mf * sizeof(size_t));
-  }
+  p->d_frames = (const uint8_t**)ar.alloc(mf * sizeof(void*));
+  p->d_pitch = (size_t*)ar.alloc(mf * sizeof(size_t));
   if (ar.base) {
     if (ar.failed) return fail(p, OCTO_ENOMEM, "workspace too small: need %zu bytes", ar.off);
     root.n_keep = (int*)(p->d_result + p->off_nkeep);
@@ -725,12 +768,28 @@ hipEvent_t get_event(octo_pipeline* p) {
   return e;
 }
 
+// keeps g_busy_pipelines right after the list of batches in flight has changed
+void note_busy(octo_pipeline* p) {
+  const bool busy = !p->inflight.empty();
+  if (busy != p->counted_busy) g_busy_pipelines.fetch_add(busy ? 1 : -1, std::memory_order_relaxed);
+  p->counted_busy = busy;
+}
+
+// an event that marks the end of a batch: no timing, so that recording it costs the stream nothing but the signal
+hipEvent_t get_done_event(octo_pipeline* p) {
+  if (!p->done_pool.empty()) { hipEvent_t e = p->done_pool.back(); p->done_pool.pop_back(); return e; }
+  hipEvent_t e = nullptr;
+  if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;
+  return e;
+}
+
 enum { ST_LETTERBOX = 0, ST_DET_LAYERS, ST_DECODE, ST_TOPK, ST_NMS, ST_COMPACT, ST_FIXED };
 // per edge: crop, layers, tail
 
-octo_status enqueue_root(octo_pipeline* p, hipStream_t s, int n);
+octo_status enqueue_batch(octo_pipeline* p, hipStream_t s, int n, bool whole);
 
-octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched) {
+// whole: all models of the batch on this stream (octo_run); otherwise the root model only
+octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched, bool whole) {
   ModelPlan& root = p->models[0];
   const int n = (int)std::min<size_t>(p->queue.size(), (size_t)root.bz);
   *launched = n;
@@ -743,12 +802,12 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched) {
   Batch b;
   b.n = n; b.slot = p->next_slot;
   auto give_back = [&](Batch& x) {
-    if (x.done) p->event_pool.push_back(x.done);
+    if (x.done) p->done_pool.push_back(x.done);
     for (hipEvent_t e : x.stage_ev) p->event_pool.push_back(e);
     for (auto& v : x.layer_ev) for (hipEvent_t e : v) p->event_pool.push_back(e);
     x.done = nullptr; x.stage_ev.clear(); x.layer_ev.clear();
   };
-  b.done = get_event(p);
+  b.done = get_done_event(p);
   bool ok = b.done != nullptr;
   if (ok && p->stage_timing) {
     const int ne = 1 + ST_FIXED + 3 * (int)p->edges.size();
@@ -765,12 +824,14 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched) {
   b.t_launch = octo_now_ms();
   b.model_ran.assign(p->models.size(), false);
   p->inflight.push_back(std::move(b));
+  note_busy(p);
   // If enqueueing fails half-way, the batch is withdrawn again: its frames stay queued (a later run forms the batch anew;
   // whatever part was enqueued only wrote this pipeline's own buffers), and the handle stays usable.
-  const octo_status st = enqueue_root(p, s, n);
+  const octo_status st = enqueue_batch(p, s, n, whole);
   if (st != OCTO_OK) {
     give_back(p->inflight.back());
     p->inflight.pop_back();
+    note_busy(p);
     *launched = 0;
     return st;
   }
@@ -780,9 +841,66 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched) {
   return OCTO_OK;
 }
 
-// Enqueues the root model's part of the newest batch in flight (copy of the frame table, letterbox, detector, decode,
-// top-k, NMS, ROI compaction) on `s`.
-octo_status enqueue_root(octo_pipeline* p, hipStream_t s, int n) {
+octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool own_stream);
+octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n);
+
+// All launches of a whole batch after the frame table, one after the other on `s`.
+octo_status enqueue_models(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
+  octo_status st = enqueue_root(p, B, s, n);
+  for (int e = 0; e < (int)p->edges.size() && st == OCTO_OK; ++e) st = run_child(p, B, e, s, false);
+  return st;
+}
+
+// The same from a recorded graph: 0.9 us of host time per launch instead of 2.6.  That pays where several pipelines share
+// the GPU - while one batch's 110 launches are enqueued, the GPU waits for the next pipeline's (four instances of the
+// traffic cascade: 3.52 -> 3.21 ms for a batch of each).  A pipeline alone on the GPU is faster without (2 % here): its
+// launches are enqueued faster than they run, and nothing of a graph runs before all of it has been handed over.  So a
+// graph is used while another pipeline has a batch in flight, or had one beside this pipeline's previous batch.  A
+// sequence is recorded the second time it is needed; whatever goes wrong while recording only switches recording off.
+// False: not available, nothing was enqueued.
+bool launch_graph(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
+  const int exec_bz = p->models[0].exec_bz;
+  const bool shared = p->overlapped || g_busy_pipelines.load(std::memory_order_relaxed) > (p->counted_busy ? 1 : 0);
+  if (!shared || p->graphs_off || p->stage_timing || p->layer_timing || (exec_bz > 0 && exec_bz < n)) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return false; }
+  GraphKey key;
+  key.n = n; key.heads = p->heads_version;
+  for (size_t e = 0; e < p->edges.size(); ++e) key.hint[e] = p->models[p->edges[e].child].items_hint;
+  GraphEntry* g = nullptr;
+  for (GraphEntry& x : p->graphs) if (x.key == key) g = &x;
+  if (!g) {
+    if (p->graphs.size() >= MAX_GRAPHS) {
+      auto old = std::min_element(p->graphs.begin(), p->graphs.end(), [](const GraphEntry& a, const GraphEntry& b) { return a.used < b.used; });
+      if (old->exec) p->retired.push_back(old->exec);
+      p->graphs.erase(old);
+    }
+    GraphEntry x;
+    x.key = key; x.used = ++p->graph_clock;
+    p->graphs.push_back(x);
+    return false;
+  }
+  g->used = ++p->graph_clock;
+  if (!g->exec) {
+    hipGraph_t graph = nullptr;
+    bool ok = p->capture_stream || hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking) == hipSuccess;
+    if (ok && hipStreamBeginCapture(p->capture_stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+      ok = enqueue_models(p, B, p->capture_stream, n) == OCTO_OK;
+      ok = hipStreamEndCapture(p->capture_stream, &graph) == hipSuccess && ok && graph;
+      ok = ok && hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0) == hipSuccess;
+    } else {
+      ok = false;
+    }
+    if (graph) hipGraphDestroy(graph);
+    if (!ok) { g->exec = nullptr; p->graphs_off = true; (void)hipGetLastError(); return false; }
+  }
+  if (hipGraphLaunch(g->exec, s) != hipSuccess) { p->graphs_off = true; (void)hipGetLastError(); return false; }
+  return true;
+}
+
+// Enqueues the newest batch in flight on `s`: copy of the frame table, then the root model (letterbox, detector, decode,
+// top-k, NMS, ROI compaction) or, `whole`, all models.
+octo_status enqueue_batch(octo_pipeline* p, hipStream_t s, int n, bool whole) {
   ModelPlan& root = p->models[0];
   Batch& B = p->inflight.back();
   hipEvent_t* ev = p->stage_timing ? B.stage_ev.data() : nullptr;
@@ -810,12 +928,24 @@ octo_status enqueue_root(octo_pipeline* p, hipStream_t s, int n) {
     do {
       ba.n = std::min(n - at, BeginArgs::MAX);
       for (int i = 0; i < ba.n; ++i) { ba.ptr[i] = (const uint8_t*)p->queue[at + i].ptr; ba.pitch[i] = p->queue[at + i].pitch; }
-      ba.d_ptr = p->d_frames[B.slot] + at; ba.d_pitch = p->d_pitch[B.slot] + at;
+      ba.d_ptr = p->d_frames + at; ba.d_pitch = p->d_pitch + at;
       at += ba.n;
       HIPCHK(p, flush());
     } while (at < n);
   }
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
+  if (whole) {
+    if (launch_graph(p, B, s, n)) return OCTO_OK;
+    return enqueue_models(p, B, s, n);
+  }
+  const octo_status st = enqueue_root(p, B, s, n);
+  if (st == OCTO_OK) HIPCHK(p, hipEventRecord(p->ev_det, s));       // the children may run on streams of their own
+  return st;
+}
+
+octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
+  ModelPlan& root = p->models[0];
+  hipEvent_t* ev = p->stage_timing ? B.stage_ev.data() : nullptr;
   ResizeArgs ra{};
   ra.src_h = p->d.src_h; ra.src_w = p->d.src_w;
   ra.dst = view_of(root, 0).ptr; ra.dst_h = root.d.in_h; ra.dst_w = root.d.in_w; ra.dst_c = root.input_c4 ? 4 : 3;
@@ -829,7 +959,7 @@ octo_status enqueue_root(octo_pipeline* p, hipStream_t s, int n) {
   for (int c0 = 0; c0 < n; c0 += chunk) {
     const int cn = std::min(chunk, n - c0);
     const bool last = c0 + cn >= n;
-    ra.frames = p->d_frames[B.slot] + c0; ra.pitches = p->d_pitch[B.slot] + c0; ra.n = cn; ra.n_frames = cn;
+    ra.frames = p->d_frames + c0; ra.pitches = p->d_pitch + c0; ra.n = cn; ra.n_frames = cn;
     HIPCHK(p, launch_letterbox(root.d.dtype, ra, s));
     if (ev && last) HIPCHK(p, hipEventRecord(ev[1 + ST_LETTERBOX], s));
     HIPCHK(p, run_layers(p, root, cn, nullptr, s, p->layer_timing && last ? &B.layer_ev[0] : nullptr));
@@ -849,16 +979,16 @@ octo_status enqueue_root(octo_pipeline* p, hipStream_t s, int n) {
   ca.boxes = (octo_box*)(p->d_result + p->off_boxes); ca.flags = root.flags;
   HIPCHK(p, launch_compact(ca, s));
   if (ev) HIPCHK(p, hipEventRecord(ev[1 + ST_COMPACT], s));
-  HIPCHK(p, hipEventRecord(p->ev_det, s));
   return OCTO_OK;
 }
 
-octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool wait_det) {
+// own_stream: the stream may not be the root's, so its end is waited for and the child's own end is marked
+octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool own_stream) {
   ModelPlan& c = p->models[p->edges[e].child];
   hipEvent_t* ev = p->stage_timing ? B.stage_ev.data() + 1 + ST_FIXED + 3 * e : nullptr;
-  if (wait_det) HIPCHK(p, hipStreamWaitEvent(s, p->ev_det, 0));
+  if (own_stream) HIPCHK(p, hipStreamWaitEvent(s, p->ev_det, 0));
   ResizeArgs ra{};
-  ra.frames = p->d_frames[B.slot]; ra.pitches = p->d_pitch[B.slot]; ra.src_h = p->d.src_h; ra.src_w = p->d.src_w;
+  ra.frames = p->d_frames; ra.pitches = p->d_pitch; ra.src_h = p->d.src_h; ra.src_w = p->d.src_w;
   ra.dst = view_of(c, 0).ptr; ra.dst_h = c.d.in_h; ra.dst_w = c.d.in_w; ra.dst_c = c.input_c4 ? 4 : 3;
   for (int k = 0; k < 3; ++k) { ra.scale[k] = c.d.norm_scale[k]; ra.bias[k] = c.d.norm_bias[k]; }
   ra.n = c.cap; ra.n_dyn = c.n_dyn; ra.rois = p->rois[e]; ra.n_frames = B.n;
@@ -875,7 +1005,7 @@ octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool wai
     HIPCHK(p, run_detect_tail(p, c, c.cap, c.n_dyn, s, nullptr, 0, dest));
   }
   if (ev) HIPCHK(p, hipEventRecord(ev[2], s));
-  HIPCHK(p, hipEventRecord(p->ev_child[e], s));
+  if (own_stream) HIPCHK(p, hipEventRecord(p->ev_child[e], s));
   B.model_ran[p->edges[e].child] = true;
   return OCTO_OK;
 }
@@ -944,12 +1074,17 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
 
 octo_status octo_pipeline_destroy(octo_pipeline* p) {
   if (!p) return OCTO_EINVAL;
+  if (p->counted_busy) g_busy_pipelines.fetch_add(-1, std::memory_order_relaxed);
   for (Batch& b : p->inflight) {
     if (b.done) { hipEventSynchronize(b.done); hipEventDestroy(b.done); }
     for (hipEvent_t e : b.stage_ev) hipEventDestroy(e);
     for (auto& v : b.layer_ev) for (hipEvent_t e : v) hipEventDestroy(e);
   }
   for (hipEvent_t e : p->event_pool) hipEventDestroy(e);
+  for (hipEvent_t e : p->done_pool) hipEventDestroy(e);
+  for (const GraphEntry& g : p->graphs) if (g.exec) hipGraphExecDestroy(g.exec);
+  for (hipGraphExec_t g : p->retired) hipGraphExecDestroy(g);
+  if (p->capture_stream) hipStreamDestroy(p->capture_stream);
   if (p->ev_det) hipEventDestroy(p->ev_det);
   for (hipEvent_t e : p->ev_child) hipEventDestroy(e);
   for (int r = 0; r < RING; ++r) if (p->h_result[r]) hipHostFree(p->h_result[r]);
@@ -995,7 +1130,7 @@ octo_status octo_run_model(octo_pipeline* p, int32_t model, void* hip_stream, in
   int* out = n_items_launched ? n_items_launched : &dummy;
   if (model == 0) {
     if (!p->inflight.empty() && !p->inflight.back().finalized) return fail(p, OCTO_ESTATE, "previous batch still has models to run");
-    octo_status st = start_batch(p, s, out);
+    octo_status st = start_batch(p, s, out, false);
     if (st != OCTO_OK || *out == 0) return st;
     if (p->edges.empty()) return finalize_batch(p, p->inflight.back(), s, false);
     return OCTO_OK;
@@ -1021,11 +1156,10 @@ octo_status octo_run(octo_pipeline* p, void* hip_stream, int32_t* n_frames_launc
   int dummy = 0;
   int* out = n_frames_launched ? n_frames_launched : &dummy;
   if (!p->inflight.empty() && !p->inflight.back().finalized) return fail(p, OCTO_ESTATE, "previous batch still has models to run");
-  octo_status st = start_batch(p, s, out);
+  octo_status st = start_batch(p, s, out, true);
   if (st != OCTO_OK || *out == 0) return st;
   Batch& B = p->inflight.back();
-  for (int e = 0; e < (int)p->edges.size(); ++e)
-    if ((st = run_child(p, B, e, s, false)) != OCTO_OK) return st;
+  B.model_ran.assign(p->models.size(), true);
   return finalize_batch(p, B, s, false);   // same stream throughout: stream order already serialises the stages
 }
 
@@ -1055,7 +1189,10 @@ octo_status octo_collect(octo_pipeline* p, octo_frame_result* frames, int32_t fr
       // what the children saw: the next batches' kernels are shaped for about as many items
       ModelPlan& c = p->models[p->edges[e].child];
       const double obs = std::min(nroi[e], c.cap);
-      c.items_hint = c.items_hint > 0 ? 0.75 * c.items_hint + 0.25 * obs : obs;
+      c.items_mean = c.items_mean > 0 ? 0.75 * c.items_mean + 0.25 * obs : obs;
+      int h = 1;
+      while (h < c.items_mean) h = (h & (h - 1)) == 0 && h > 1 ? h / 2 * 3 : (h == 1 ? 2 : h / 3 * 4);
+      c.items_hint = h;
     }
     int total = 0;
     for (int i = 0; i < B.n; ++i) total += std::min(nk[i], max_det);
@@ -1101,8 +1238,14 @@ octo_status octo_collect(octo_pipeline* p, octo_frame_result* frames, int32_t fr
       }
       for (hipEvent_t e : le) p->event_pool.push_back(e);
     }
-    p->event_pool.push_back(B.done);
+    p->done_pool.push_back(B.done);
+    p->overlapped = g_busy_pipelines.load(std::memory_order_relaxed) > 1;
     p->inflight.pop_front();
+    note_busy(p);
+  }
+  if (p->inflight.empty()) {
+    for (hipGraphExec_t g : p->retired) hipGraphExecDestroy(g);
+    p->retired.clear();
   }
   if (*n_frames == 0) return blocking ? fail(p, OCTO_ESTATE, "nothing in flight") : OCTO_ENOTREADY;
   return overflow ? OCTO_ECAP : OCTO_OK;
@@ -1242,6 +1385,7 @@ octo_status octo_debug_set_head(octo_pipeline* p, int32_t model, int32_t level, 
   if (model < 0 || model >= (int)p->models.size() || p->models[model].d.kind != OCTO_DETECTOR || level < 0 || level >= p->models[model].d.n_outputs)
     return fail(p, OCTO_EINVAL, "bad model or level");
   p->models[model].head_override[level] = d_head;
+  ++p->heads_version;
   return OCTO_OK;
 }
 

@@ -1,0 +1,46 @@
+"""Several pipelines with batches in flight at once: their launches are then replayed from recorded graphs.  Every replay
+must give what the pipeline gives alone, for frames that change from batch to batch, partial batches and swapped heads."""
+import numpy as np
+import pytest
+
+from paper_2502_01277_amd import synth, zoo
+
+pytestmark = pytest.mark.gpu
+
+
+def test_replayed_batches_equal_batches_alone(octo):
+    import torch
+    spec = zoo.traffic_cascade("f16", det_batch=4, max_rois_per_frame=12)
+    det = spec.models[0]
+    rng = np.random.default_rng(zoo.SEED0 + 77)
+    sets = []
+    for k in range(3):
+        scene = synth.make_scene(rng, 4, 1080, 1920, [3, 0, 7, 5 + k], 24, 360, log_uniform=True)
+        heads = synth.planted_heads(rng, det, scene, 1080, 1920, octo.letterbox_geometry(1080, 1920, det.in_h, det.in_w))
+        sets.append(([torch.from_numpy(f).cuda() for f in scene.frames], [octo.to_device(h, det.dtype) for h in heads]))
+
+    def batch(P, s, n, collect=True):
+        for l, h in enumerate(sets[s][1]):
+            P.set_head(0, l, h)
+        P.submit(sets[s][0][:n])
+        assert P.run() == n
+        return P.collect()[1].tobytes() if collect else None
+
+    solo = octo.Pipeline(spec)
+    want = {(s, n): batch(solo, s, n) for s in range(3) for n in (4, 3)}
+    solo.close()
+    pipes = [octo.Pipeline(spec) for _ in range(2)]
+    for r in range(6):
+        # the same heads for three rounds: recorded in the second, replayed in the third
+        for k, P in enumerate(pipes):
+            if r % 3 == 0:
+                for l, h in enumerate(sets[(r // 3 + k) % 3][1]):
+                    P.set_head(0, l, h)
+            for n in (4, 3):
+                P.submit(sets[(r // 3 + k) % 3][0][:n])
+                assert P.run() == n
+        for k, P in enumerate(pipes):
+            got = [P.collect(frame_cap=4)[1] for _ in range(2)]
+            assert [g.tobytes() for g in got] == [want[(r // 3 + k) % 3, n] for n in (4, 3)], (r, k)
+    for P in pipes:
+        P.close()
