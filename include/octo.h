@@ -443,6 +443,10 @@ octo_status octo_debug_get_labels(octo_pipeline* p, int32_t edge, int32_t* label
 octo_status octo_letterbox_geometry(int32_t src_h, int32_t src_w, int32_t dst_h, int32_t dst_w,
                                     int32_t* nw, int32_t* nh, int32_t* left, int32_t* top);
 
+/* Device table of frames for octo_op_letterbox / octo_op_crop_resize: writes the n frame pointers to d_table and the n row
+ * pitches behind them (16 n bytes in all; device, 8-byte aligned).  frames / pitches: host arrays, passed to the kernel by
+ * value, so the call only enqueues and the arrays may be reused at once. */
+octo_status octo_op_frame_table(const void* const* frames, const size_t* pitches, int32_t n, void* d_table, void* hip_stream);
 /* Letterbox + normalise: aspect-preserving bilinear resize (half-pixel centres, no antialias) of n uint8 HWC
  * frames into dst [n][dst_h][dst_w][3] of `dtype`, centred, padded with pad_value, out = px*scale + bias.
  * d_frame_ptrs / d_pitches: device arrays of n frame pointers / row pitches. */

@@ -8,6 +8,7 @@ fallback.
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 from dataclasses import dataclass, field
 from typing import Dict, List, Optional, Sequence, Tuple
@@ -147,7 +148,7 @@ EXPORTS = [
     "octo_executor_create", "octo_executor_serve", "octo_executor_stats", "octo_executor_scale_events", "octo_executor_streams",
     "octo_executor_results", "octo_executor_last_error", "octo_executor_destroy", "octo_profile_layers", "octo_set_layer_timing", "octo_get_layer_info", "octo_set_stage_timing", "octo_get_stage_ms",
     "octo_debug_get_tensor", "octo_debug_tensor_shape", "octo_debug_set_head", "octo_debug_run_model",
-    "octo_debug_get_detections", "octo_debug_get_rois", "octo_debug_get_labels", "octo_letterbox_geometry", "octo_op_letterbox",
+    "octo_debug_get_detections", "octo_debug_get_rois", "octo_debug_get_labels", "octo_letterbox_geometry", "octo_op_frame_table", "octo_op_letterbox",
     "octo_op_crop_resize", "octo_op_decode", "octo_op_topk", "octo_op_nms", "octo_op_nms_scratch_bytes", "octo_op_nms_static", "octo_op_compact", "octo_probe_copy", "octo_probe_mfma",
     "octo_op_conv", "octo_op_conv_packed_bytes", "octo_op_conv_padded_cout", "octo_op_conv_pack", "octo_quantize_e4m3", "octo_dequantize_e4m3",
 ]
@@ -219,6 +220,7 @@ def lib() -> C.CDLL:
         L.octo_debug_get_rois.argtypes = [vp, i32, vp, i32, vp]
         L.octo_debug_get_labels.argtypes = [vp, i32, vp, i32, vp]
         L.octo_letterbox_geometry.argtypes = [i32, i32, i32, i32, vp, vp, vp, vp]
+        L.octo_op_frame_table.argtypes = [vp, vp, i32, vp, vp]
         L.octo_op_letterbox.argtypes = [vp, vp, i32, i32, i32, vp, i32, i32, i32, vp, vp, i32, vp]
         L.octo_op_crop_resize.argtypes = [vp, vp, i32, i32, i32, vp, vp, i32, vp, i32, i32, i32, vp, vp, vp]
         L.octo_op_decode.argtypes = [vp, vp, i32, vp, vp, i32, vp]
@@ -246,9 +248,15 @@ class OctoError(RuntimeError):
         self.status = status
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def torch_dtype(dtype: str):
@@ -267,7 +275,11 @@ def to_device(x_f32: np.ndarray, dtype: str, device="cuda"):
 
 def _stream_ptr(stream) -> int:
     if stream is None:
-        return int(_torch().cuda.current_stream().cuda_stream)
+        t = _torch()
+        try:                              # the raw handle without building a Stream object (5 us a call)
+            return t._C._cuda_getCurrentRawStream(t._C._cuda_getDevice())
+        except AttributeError:
+            return int(t.cuda.current_stream().cuda_stream)
     if isinstance(stream, int):
         return stream
     return int(stream.cuda_stream)
@@ -486,12 +498,28 @@ def _st(st):
         raise OctoError(st, "stage call failed")
 
 
-def frame_tables(frames: Sequence):
-    """Device tables (pointers, pitches) for a list of device uint8 frames."""
+def frame_tables(frames: Sequence, stream=None):
+    """Device tables (pointers, pitches) for a list of device uint8 frames, written on `stream`."""
     t = _torch()
-    ptrs = t.tensor([int(f.data_ptr()) for f in frames], dtype=t.int64, device=frames[0].device)
-    pitches = t.tensor([int(f.stride(0)) for f in frames], dtype=t.int64, device=frames[0].device)
-    return ptrs, pitches
+    n = len(frames)
+    table = t.empty((2, n), dtype=t.int64, device=frames[0].device)
+    ptrs = (C.c_void_p * n)(*[f.data_ptr() for f in frames])
+    pitches = (C.c_size_t * n)(*[f.stride(0) for f in frames])
+    _st(lib().octo_op_frame_table(ptrs, pitches, n, table.data_ptr(), _stream_ptr(stream)))
+    return table[0], table[1]
+
+
+def _zeros(device, *parts):
+    """Zeroed tensors of the given (shape, dtype), views of one buffer: one allocation and one launch for all of them."""
+    t = _torch()
+    sizes = [math.prod(shape) * dtype.itemsize for shape, dtype in parts]
+    buf = t.zeros(sum((n + 255) // 256 * 256 for n in sizes), dtype=t.uint8, device=device)
+    out, at = [], 0
+    for (shape, dtype), n in zip(parts, sizes):
+        v = buf[at:at + n]
+        out.append((v if dtype is t.uint8 else v.view(dtype)).view(shape))
+        at += (n + 255) // 256 * 256
+    return out
 
 
 def letterbox_geometry(src_h: int, src_w: int, dst_h: int, dst_w: int):
@@ -503,7 +531,7 @@ def letterbox_geometry(src_h: int, src_w: int, dst_h: int, dst_w: int):
 
 def op_letterbox(frames: Sequence, dst_h, dst_w, dtype: str, scale=(1 / 255.0,) * 3, bias=(0.0,) * 3, pad_value=114, stream=None):
     t = _torch()
-    ptrs, pitches = frame_tables(frames)
+    ptrs, pitches = frame_tables(frames, stream)
     n, (sh, sw) = len(frames), frames[0].shape[:2]
     out = t.empty((n, dst_h, dst_w, 3), dtype=torch_dtype(dtype), device=frames[0].device)
     sc = (C.c_float * 3)(*scale); bi = (C.c_float * 3)(*bias)
@@ -515,14 +543,18 @@ def op_letterbox(frames: Sequence, dst_h, dst_w, dtype: str, scale=(1 / 255.0,) 
 def op_crop_resize(frames: Sequence, rois: np.ndarray, out_h, out_w, dtype: str, cap=None, scale=(1 / 255.0,) * 3,
                    bias=(0.0,) * 3, stream=None):
     t = _torch()
-    ptrs, pitches = frame_tables(frames)
+    ptrs, pitches = frame_tables(frames, stream)
     sh, sw = frames[0].shape[:2]
     cap = cap or max(1, len(rois))
-    d_rois = t.from_numpy(np.ascontiguousarray(rois).view(np.uint8).reshape(-1)).to(frames[0].device)
-    if len(rois) == 0:
-        d_rois = t.zeros(32, dtype=t.uint8, device=frames[0].device)
-    d_n = t.tensor([len(rois)], dtype=t.int32, device=frames[0].device)
-    out = t.zeros((cap, out_h, out_w, 3), dtype=torch_dtype(dtype), device=frames[0].device)
+    # the ROI records and their count travel in one copy; crops beyond the count are zeros
+    host = np.zeros(32 * len(rois) + 32, np.uint8)
+    host[:32 * len(rois)] = np.ascontiguousarray(rois).view(np.uint8).reshape(-1)
+    host[-32:-28] = np.array([len(rois)], np.int32).view(np.uint8)
+    d = t.from_numpy(host).to(frames[0].device)
+    d_rois, d_n = d, d[32 * len(rois):]
+    out = t.empty((cap, out_h, out_w, 3), dtype=torch_dtype(dtype), device=frames[0].device)
+    if len(rois) < cap:
+        out[len(rois):].zero_()
     sc = (C.c_float * 3)(*scale); bi = (C.c_float * 3)(*bias)
     _st(lib().octo_op_crop_resize(ptrs.data_ptr(), pitches.data_ptr(), len(frames), sh, sw, d_rois.data_ptr(), d_n.data_ptr(), cap,
                                   out.data_ptr(), out_h, out_w, DTYPES[dtype], sc, bi, _stream_ptr(stream)))
@@ -532,16 +564,20 @@ def op_crop_resize(frames: Sequence, rois: np.ndarray, out_h, out_w, dtype: str,
 def op_decode(m: zoo.ModelSpec, heads: Sequence, cap=None, stream=None):
     """heads: device tensors [n][G][G][A*(5+C)] of the model's type.  Returns (cand tensor uint8 view, counts)."""
     t = _torch()
-    keep: list = []
-    hdr = zoo.ModelSpec(name=m.name, dtype=m.dtype, in_h=m.in_h, in_w=m.in_w, kind=m.kind)   # geometry and thresholds only
-    hdr.outputs = list(range(1, len(m.outputs) + 1))
-    hdr.n_classes, hdr.n_anchors, hdr.grids, hdr.strides, hdr.anchors = m.n_classes, m.n_anchors, m.grids, m.strides, m.anchors
-    hdr.score_thr, hdr.iou_thr, hdr.topk, hdr.max_det = m.score_thr, m.iou_thr, m.topk, m.max_det
-    d = model_desc(hdr, keep)
+    d = OctoModelDesc()                                      # geometry and thresholds only
+    d.dtype, d.kind, d.in_h, d.in_w, d.in_c = DTYPES[m.dtype], KINDS[m.kind], m.in_h, m.in_w, m.in_c
+    d.n_outputs, d.n_classes, d.n_anchors = len(m.outputs), m.n_classes, m.n_anchors
+    d.outputs[:len(m.outputs)] = range(1, len(m.outputs) + 1)
+    d.stride[:len(m.strides)] = m.strides
+    if m.anchors is not None:
+        row = 2 * MAX_ANCHORS
+        for l, a in enumerate(m.anchors.tolist()):
+            flat = [v for wh in a for v in wh]
+            d.anchors[l * row:l * row + len(flat)] = flat
+    d.score_thr, d.iou_thr, d.topk, d.max_det = m.score_thr, m.iou_thr, m.topk, m.max_det
     n = int(heads[0].shape[0])
     cap = cap or m.n_cand()
-    cand = t.zeros((n, cap, 32), dtype=t.uint8, device=heads[0].device)
-    count = t.zeros(n, dtype=t.int32, device=heads[0].device)
+    cand, count = _zeros(heads[0].device, ((n, cap, 32), t.uint8), ((n,), t.int32))
     hp = (C.c_void_p * len(heads))(*[int(h.data_ptr()) for h in heads])
     _st(lib().octo_op_decode(C.byref(d), hp, n, cand.data_ptr(), count.data_ptr(), cap, _stream_ptr(stream)))
     return cand, count
@@ -569,8 +605,7 @@ def op_topk(cand, count, k: int, stream=None):
     t = _torch()
     n, in_cap = int(cand.shape[0]), int(cand.shape[1])
     k_cap = (k + 63) // 64 * 64
-    out = t.zeros((n, k_cap, 32), dtype=t.uint8, device=cand.device)
-    oc = t.zeros(n, dtype=t.int32, device=cand.device)
+    out, oc = _zeros(cand.device, ((n, k_cap, 32), t.uint8), ((n,), t.int32))
     _st(lib().octo_op_topk(cand.data_ptr(), count.data_ptr(), in_cap, n, k, out.data_ptr(), oc.data_ptr(), k_cap, _stream_ptr(stream)))
     return out, oc
 
@@ -579,8 +614,7 @@ def op_nms(top, top_count, iou_thr: float, max_det: int, stream=None):
     t = _torch()
     n, k_cap = int(top.shape[0]), int(top.shape[1])
     scratch = t.empty(max(8, lib().octo_op_nms_scratch_bytes(n, k_cap)), dtype=t.uint8, device=top.device)
-    keep = t.zeros((n, max_det), dtype=t.int32, device=top.device)
-    nk = t.zeros(n, dtype=t.int32, device=top.device)
+    keep, nk = _zeros(top.device, ((n, max_det), t.int32), ((n,), t.int32))
     _st(lib().octo_op_nms(top.data_ptr(), top_count.data_ptr(), k_cap, n, iou_thr, max_det, scratch.data_ptr(),
                           keep.data_ptr(), nk.data_ptr(), _stream_ptr(stream)))
     return keep, nk
@@ -599,21 +633,22 @@ def op_nms_static(top, top_count, iou_thr: float, max_det: int, keep, n_keep, st
 def op_compact(top, keep, n_keep, src_hw, in_hw, class_mask: int, cap: int, stream=None):
     t = _torch()
     n, k_cap, max_det = int(top.shape[0]), int(top.shape[1]), int(keep.shape[1])
-    dev = top.device
-    rois = t.zeros((max(cap, 1), 32), dtype=t.uint8, device=dev)
-    n_roi = t.zeros(1, dtype=t.int32, device=dev)
-    roi_of = t.full((n, max_det), -1, dtype=t.int32, device=dev)
-    boxes = t.zeros((n, max_det, 32), dtype=t.uint8, device=dev)
-    flags = t.zeros(n, dtype=t.int32, device=dev)
-    item_counts = t.zeros(n, dtype=t.int32, device=dev)
+    # everything that comes back lies in one buffer and crosses in one copy; the item counters are scratch
+    rows = max(cap, 1)
+    nbytes = [32 * rows, 32 * n * max_det, 4 * n * max_det, 4 * n, 4]                 # rois, boxes, roi_of, flags, number of ROIs
+    at = [sum(nbytes[:k]) for k in range(6)]
+    buf = t.zeros(at[5] + 4 * n, dtype=t.uint8, device=top.device)
+    buf[at[2]:at[3]].fill_(255)                                                       # roi_of: -1
+    base = buf.data_ptr()
     cm = (C.c_uint64 * 2)(class_mask & ((1 << 64) - 1), (class_mask >> 64) & ((1 << 64) - 1))
     _st(lib().octo_op_compact(top.data_ptr(), k_cap, keep.data_ptr(), n_keep.data_ptr(), max_det, n, src_hw[0], src_hw[1],
-                              in_hw[0], in_hw[1], cm, rois.data_ptr(), n_roi.data_ptr(), cap, roi_of.data_ptr(),
-                              item_counts.data_ptr(), boxes.data_ptr(), flags.data_ptr(), _stream_ptr(stream)))
-    nr = int(n_roi.cpu()[0])
-    r = rois.cpu().numpy().reshape(-1).view(ROI_DTYPE)[:nr].copy()
-    b = boxes.cpu().numpy().reshape(n, max_det * 32).view(BOX_DTYPE)
-    return r, roi_of.cpu().numpy(), b, flags.cpu().numpy()
+                              in_hw[0], in_hw[1], cm, base, base + at[4], cap, base + at[2],
+                              base + at[5], base + at[1], base + at[3], _stream_ptr(stream)))
+    h = buf[:at[5]].cpu().numpy()
+    part = lambda k: h[at[k]:at[k + 1]]   # noqa: E731
+    r = part(0).view(ROI_DTYPE)[:int(part(4).view(np.int32)[0])].copy()
+    b = part(1).view(BOX_DTYPE).reshape(n, max_det)
+    return r, part(2).view(np.int32).reshape(n, max_det), b, part(3).view(np.int32)
 
 
 # ---- one convolution layer ------------------------------------------------------

@@ -47,6 +47,19 @@ octo_status octo_letterbox_geometry(int32_t src_h, int32_t src_w, int32_t dst_h,
   return OCTO_OK;
 }
 
+octo_status octo_op_frame_table(const void* const* frames, const size_t* pitches, int32_t n, void* d_table, void* hip_stream) {
+  if (!frames || !pitches || !d_table || n < 0 || ((uintptr_t)d_table & 7)) return OCTO_EINVAL;
+  for (int at = 0; at < n; at += BeginArgs::MAX) {
+    BeginArgs a{};
+    a.n = n - at < BeginArgs::MAX ? n - at : BeginArgs::MAX;
+    a.d_ptr = (const uint8_t**)d_table + at; a.d_pitch = (size_t*)((const uint8_t**)d_table + n) + at;
+    for (int i = 0; i < a.n; ++i) { a.ptr[i] = (const uint8_t*)frames[at + i]; a.pitch[i] = pitches[at + i]; }
+    const hipError_t e = launch_begin(a, (hipStream_t)hip_stream);
+    if (e != hipSuccess) return from_hip(e);
+  }
+  return OCTO_OK;
+}
+
 octo_status octo_op_letterbox(const void* d_frame_ptrs, const void* d_pitches, int32_t n, int32_t src_h, int32_t src_w,
                               void* d_dst, int32_t dst_h, int32_t dst_w, int32_t dtype, const float* scale3, const float* bias3,
                               int32_t pad_value, void* hip_stream) {
