@@ -57,6 +57,8 @@ def conv_name(kid: int, dtype: str) -> str:
     """Template instance behind a conv kernel id (digits 1 BBB PPP K M V), as rocprofv3 prints it."""
     d = kid - 1000000000
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
+    if 500000000 <= d < 600000000:                       # streaming 1x1 kernel: digits BBB KKK (channel tile, input channels)
+        return "octo::conv1x1_stream_kernel<%s, %d>" % (ctype, (d - 500000000) // 1000 // 32)
     if 600000000 <= d < 700000000:                       # split-K kernel: digits S BBB PPP (K split, channel tile, pixel tile)
         ks, bc, bp = (d - 600000000) // 1000000, (d // 1000) % 1000, d % 1000
         return "octo::conv_ksplit_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp // 32, ks, ks)
@@ -112,7 +114,7 @@ TRAFFIC_SOURCE = "profiles/*_hbm_counters.md: rocprofv3 --pmc FETCH_SIZE and --p
 def conv_sources_key() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv.hip", "conv_ksplit.h", "convbig.hip", "conv3x3.hip", "stem.hip", "mfma_common.h"):
+    for f in ("conv.hip", "conv_ksplit.h", "conv1x1.hip", "convbig.hip", "conv3x3.hip", "stem.hip", "mfma_common.h"):
         try:
             h.update(open(os.path.join(ROOT, "paper_2502_01277_amd", "csrc", f), "rb").read())
         except OSError:

@@ -390,7 +390,8 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
  * duration, from events attached to its dispatch; other layers: end of layer i-1 to end of layer i on the stream,
  * which includes the launch gap), kernel_id[i] = which kernel ran it (general convolution: decimal digits
  * 1 BBB PPP K M V = channel tile, pixel tile, 16-byte vectors per K step, workgroups per CU, V = vectorised gather
- * + 2 if operands go straight to LDS; 160S BBB PPP: split-K kernel, K split over S wavefronts, channel tile BBB, pixel tile PPP; 17 0P BBB TTT: wide 3x3 kernel, channel tile BBB, tile width TTT, P = 1 for 512-pixel tiles (else 256);
+ * + 2 if operands go straight to LDS; 15 00 BBB KKK: streaming 1x1 kernel, channel tile BBB, KKK input
+ * channels; 160S BBB PPP: split-K kernel, K split over S wavefronts, channel tile BBB, pixel tile PPP; 17 0P BBB TTT: wide 3x3 kernel, channel tile BBB, tile width TTT, P = 1 for 512-pixel tiles (else 256);
  * 18 00 BBB 0 SS: 3x3 kernel with the input patch in LDS, channel tile BBB and
  * channel slice SS; 19 0F BBB KK P: first-layer kernel, channel tile, kernel height, kernel width in pixel pairs,
  * F = 1 when it also computes the 3x3 / stride-2 max-pool that follows (that layer then reports kernel 0 and 0 ms);

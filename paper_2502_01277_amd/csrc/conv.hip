@@ -584,6 +584,8 @@ hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s,
     const bool ok = (dtype == OCTO_F16 || dtype == OCTO_BF16) && a.y2 && !a.res && !a.out_f32 && !a.pair_view && !a.pool_y && a.split < a.Cout &&
                     ((a.split | a.Cout | a.y_ld | a.y_coff | a.y2_ld | a.y2_coff) & 7) == 0 && ((((uintptr_t)a.y | (uintptr_t)a.y2) & 15) == 0);
     if (!ok) return hipErrorNotSupported;
+    const hipError_t e1 = launch_conv1x1_stream(dtype, a, num_cu, s, kernel_id, tm);
+    if (e1 != hipErrorNotSupported) return e1;
     return dtype == OCTO_F16 ? launch_general_f16(a, num_cu, s, kernel_id, tm) : launch_general_bf16(a, num_cu, s, kernel_id, tm);
   }
   if (a.up_y) {
@@ -597,6 +599,8 @@ hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s,
   }
   const hipError_t es = launch_stem(dtype, a, num_cu, s, kernel_id, tm);
   if (es != hipErrorNotSupported || a.pool_y) return es;      // only the first-layer kernel can pool its own output
+  const hipError_t e1 = launch_conv1x1_stream(dtype, a, num_cu, s, kernel_id, tm);
+  if (e1 != hipErrorNotSupported) return e1;
   // 3x3 layers with at most 64 output channels on wide images: the input patch of a tile lives in LDS (measured
   // +20% on 56x56x64 layers; the 8x32 pixel tile wastes lanes on narrow feature maps, and with more output channels
   // the general kernel's 128-channel tile re-uses the pixel operand enough)

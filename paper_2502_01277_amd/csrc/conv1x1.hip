@@ -1,0 +1,241 @@
+// 1x1 / stride-1 convolution of large maps with short reductions: a stream of pixels past resident weights.
+//
+// Such a layer (96 -> 96 on 32 x 160 x 160) moves as many bytes as a copy and multiplies little.  The general kernel
+// (conv.hip) fetches the weights again for every tile - more bytes than the tile's pixels - and runs fetch, K steps,
+// epilogue and write-out one after the other between barriers: 2.9 TB/s where a copy does 4.7.  Here
+//   * a workgroup keeps the weights of its BC = 32 TC output channels in LDS for its lifetime;
+//   * every wavefront works on its own on blocks of 32 pixels: it fetches a block (and the residual's) with direct-to-LDS
+//     loads, 1 KB of consecutive memory per instruction, multiplies, and requests its next block as soon as the operands
+//     are in registers, so the fetch runs beside the epilogue and the stores.  No barrier after the first;
+//   * weight rows are permuted so that a lane of the matrix instruction's result holds runs of eight consecutive channels
+//     of its pixel: results leave as 16-byte stores, 32 consecutive bytes per pixel and instruction, without a detour
+//     through LDS.
+// LDS rows (a pixel's or an output channel's K values) have an odd pitch in 16-byte vectors: reads of one vector of 32
+// rows hit all banks evenly.
+#include "mfma_common.h"
+#include <hip/hip_ext.h>
+
+namespace octo {
+
+struct StreamGeom {
+  int waves;             // wavefronts per workgroup
+  int kvp, rvp;          // LDS pitch in vectors: a row of K values, a pixel's BC residual values (0: no residual)
+  int x_vecs, r_vecs;    // vectors of a wavefront's pixel block and residual block, whole passes of 64
+  int w_vecs;            // weights, whole passes of all lanes
+  int tiles_c, lanes;    // channel tiles; workgroups per die that share a channel tile
+  FastDiv div_k, div_r;  // by kvp, rvp
+};
+
+// channel (within a block of 32) that row m of the matrix instruction computes: result register 4 q + e of half g of the
+// wavefront is row 8 q + 4 g + e, and shall be channel 16 (q / 2) + 8 g + 4 (q % 2) + e
+__device__ __forceinline__ int row_channel(int m) {
+  const int q = m >> 3, g = (m >> 2) & 1, e = m & 3;
+  return 16 * (q >> 1) + 8 * g + 4 * (q & 1) + e;
+}
+
+template <typename T, int TC>
+__global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, const StreamGeom gm) {
+  using E = Elem<T>;
+  static_assert(sizeof(T) == 2, "16-bit storage types");
+  constexpr int BC = 32 * TC;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char dyn_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  u32x4* sW = (u32x4*)dyn_lds;
+  float* sBias = (float*)(sW + gm.w_vecs);
+  u32x4* sX = (u32x4*)(sBias + BC) + wave * (gm.x_vecs + gm.r_vecs);
+  u32x4* sR = sX + gm.x_vecs;
+
+  int n_items = a.n;
+  if (a.n_dyn) { const int d = *a.n_dyn; n_items = d < a.n ? d : a.n; }
+  const int M = n_items * a.Ho * a.Wo;                   // < 2^31 (host)
+  const int n_blk = (M + 31) >> 5;
+  // workgroup b runs on die b % 8, which owns a contiguous piece of the blocks; the workgroups of the channel tiles of one
+  // pixel range are neighbours on it and advance together, so they meet in its L2
+  const int die = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const int ct = j % gm.tiles_c, pl = j / gm.tiles_c;
+  if (pl >= gm.lanes) return;
+  const int per_die = (n_blk + 7) >> 3;
+  const int end = (die + 1) * per_die < n_blk ? (die + 1) * per_die : n_blk;
+  const int stride = gm.lanes * gm.waves;
+  int blk = die * per_die + pl * gm.waves + wave;
+  const int c0 = ct * BC;
+  const int kv = a.Cin >> 3;                             // vectors per pixel
+
+  // weights, once
+  {
+    const long long w_bytes = (long long)a.w_rows * a.Kp * 2;
+    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, (int)(w_bytes < BUF_MAX ? w_bytes : BUF_MAX), BUF_FLAGS);
+    for (int i = tid; i < gm.w_vecs; i += 64 * gm.waves) {
+      const int m = (int)fast_div((unsigned)i, gm.div_k), v = i - m * gm.kvp;
+      const int c = c0 + (m & ~31) + row_channel(m & 31);
+      sW[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, m < BC && v < kv && c < a.w_rows ? (c * a.Kp + v * 8) * 2 : OOB, 0, 0);
+    }
+    for (int i = tid; i < BC; i += 64 * gm.waves) sBias[i] = c0 + i < a.w_rows ? a.bias[c0 + i] : 0.0f;
+  }
+  // a block's rows into LDS, `vecs` / 64 passes of 1 KB; bytes past the tensor's end and pitch padding read as zeros
+  auto fetch = [&](const T* base, int ld, long long rows_left, int row_vecs, int pitch, const FastDiv& div, u32x4* dst, int vecs) {
+    const long long bytes = rows_left * ld * 2;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)(bytes < BUF_MAX ? bytes : BUF_MAX), BUF_FLAGS);
+    const unsigned lds = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)dst);
+    for (int ps = 0; ps < vecs / 64; ++ps) {
+      const int i = ps * 64 + lane;
+      const int r = (int)fast_div((unsigned)i, div), v = i - r * pitch;
+      const int off = r < 32 && v < row_vecs ? (r * ld + v * 8) * 2 : OOB;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(lds + ps * 1024), "v"(off), "s"(rsrc) : "memory");
+    }
+  };
+  // buffers end where the last row's own channels end (the tensor may be a channel slice of a wider one)
+  const T* xg = (const T*)a.x + a.x_coff;
+  const T* rg = (const T*)a.res + a.res_coff + c0;
+  auto fetch_x = [&](int b) { fetch(xg + (size_t)b * 32 * a.x_ld, a.x_ld, M - b * 32 < 32 ? M - b * 32 : 32, kv, gm.kvp, gm.div_k, sX, gm.x_vecs); };
+  const int res_vecs = a.Cout - c0 < BC ? (a.Cout - c0) >> 3 : BC >> 3;
+  auto fetch_r = [&](int b) { fetch(rg + (size_t)b * 32 * a.res_ld, a.res_ld, M - b * 32 < 32 ? M - b * 32 : 32, res_vecs, gm.rvp, gm.div_r, sR, gm.r_vecs); };
+  const bool has_res = a.res && a.res_mode != OCTO_RES_NONE;
+  if (blk < end) { fetch_x(blk); if (has_res) fetch_r(blk); }
+  __syncthreads();                                       // the weights are in place
+
+  const bool is_silu = a.act == OCTO_ACT_SILU;
+  const float act_lo = a.act == OCTO_ACT_RELU ? 0.0f : -INFINITY;
+  const int nkk = (kv + 1) >> 1;
+  const u32x4* pa = sW + l32 * gm.kvp + g;
+  const u32x4* pb = sX + l32 * gm.kvp + g;
+  const int wstep = 32 * gm.kvp;
+  for (; blk < end; blk += stride) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    floatx16 acc[TC];
+#pragma unroll
+    for (int i = 0; i < TC; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
+    for (int kk = 0; kk < nkk; ++kk) {
+      const u32x4 fb = pb[2 * kk];
+#pragma unroll
+      for (int i = 0; i < TC; ++i) acc[i] = E::mfma(pa[i * wstep + 2 * kk], fb, acc[i]);
+    }
+    const int next = blk + stride;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the block's operands have been read: its buffer takes the next one
+    if (next < end) fetch_x(next);
+
+    const int p = blk * 32 + l32;
+    T* y1p = (T*)a.y + (size_t)p * a.y_ld + a.y_coff;
+    T* y2p = (T*)a.y2 + (size_t)p * a.y2_ld + a.y2_coff - a.split;
+    with_epilogue_mode(has_res ? a.res_mode : OCTO_RES_NONE, is_silu, [&](auto res_c, auto silu_c) __attribute__((always_inline)) {
+      constexpr int RES = decltype(res_c)::value;
+      constexpr bool SILU = decltype(silu_c)::value;
+#pragma unroll
+      for (int i = 0; i < TC; ++i) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int cl = i * 32 + h * 16 + g * 8;        // eight consecutive channels
+          typedef T t8 __attribute__((ext_vector_type(8)));
+          t8 r8 = {};
+          if (RES != OCTO_RES_NONE) r8 = __builtin_bit_cast(t8, sR[l32 * gm.rvp + (cl >> 3)]);
+          t8 o8;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const floatx4 b4 = *(const floatx4*)(sBias + cl + q * 4);
+            floatx4 v, rv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] = acc[i][h * 8 + q * 4 + e]; rv[e] = (float)r8[q * 4 + e]; }
+            v = finish4<RES, SILU>(v, b4, rv, act_lo);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o8[q * 4 + e] = (T)v[e];
+          }
+          const int c = c0 + cl;
+          if (p < M && c < a.Cout) {
+            // two layers in one launch: a vector never straddles the split (a multiple of 8 channels)
+            const bool second = a.split > 0 && c >= a.split;
+            T* yp = second ? y2p + c : y1p + c;
+            if (c + 8 <= a.Cout) {
+              *(u32x4*)yp = __builtin_bit_cast(u32x4, o8);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) if (c + e < a.Cout) yp[e] = o8[e];
+            }
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);               // one block of channels at a time: keeps the register demand low
+      }
+      if (RES != OCTO_RES_NONE) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (next < end) fetch_r(next);
+      }
+    });
+  }
+}
+
+constexpr int STREAM_LDS = 160 * 1024;
+
+// Geometry of a launch with BC = 32 tc channels per workgroup; 0 wavefronts when it does not fit.
+inline StreamGeom stream_geometry(const ConvArgs& a, int tc, int num_cu, size_t* lds) {
+  StreamGeom g{};
+  const int kv = a.Cin / 8, bc = 32 * tc;
+  const bool res = a.res && a.res_mode != OCTO_RES_NONE;
+  g.kvp = ((kv + 1) & ~1) + 1;
+  g.rvp = res ? bc / 8 + 1 : 1;
+  g.x_vecs = (32 * g.kvp + 63) / 64 * 64;
+  g.r_vecs = res ? (32 * g.rvp + 63) / 64 * 64 : 0;
+  g.w_vecs = (bc * g.kvp + 63) / 64 * 64;
+  const int fixed = g.w_vecs * 16 + bc * 4, per_wave = (g.x_vecs + g.r_vecs) * 16;
+  g.waves = (STREAM_LDS - fixed) / per_wave;
+  if (g.waves > 8) g.waves = 8;
+  *lds = (size_t)fixed + (size_t)g.waves * per_wave;
+  g.tiles_c = (a.Cout + bc - 1) / bc;
+  g.div_k = make_fastdiv((unsigned)g.kvp); g.div_r = make_fastdiv((unsigned)g.rvp);
+  return g;
+}
+
+template <typename T, int TC>
+static hipError_t launch_stream_cfg(const ConvArgs& a, long long M, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
+  size_t lds;
+  StreamGeom g = stream_geometry(a, TC, num_cu, &lds);
+  if (g.waves < 3) return hipErrorNotSupported;
+  static const bool ready = [] {
+    (void)hipFuncSetAttribute((const void*)conv1x1_stream_kernel<T, TC>, hipFuncAttributeMaxDynamicSharedMemorySize, STREAM_LDS);
+    (void)hipGetLastError();
+    return true;
+  }();
+  (void)ready;
+  // two workgroups per compute unit while the tensors fit the 256 MB memory-side cache; beyond it one streams better
+  // (48 -> 48 on 32 x 320 x 320, 630 MB: 128 against 144 us)
+  const bool cached = (double)M * (a.Cin + a.Cout * (g.r_vecs ? 2 : 1)) * 2 < 256e6;
+  const int per_cu = lds <= STREAM_LDS / 2 && cached ? 2 : 1;
+  const int per_die = num_cu * per_cu / 8;
+  if (g.tiles_c > per_die) return hipErrorNotSupported;
+  g.lanes = per_die / g.tiles_c;
+  if (kernel_id) *kernel_id = 1500000000 + 32 * TC * 1000 + a.Cin;
+  if (tm.start && tm.stop)
+    hipExtLaunchKernelGGL((conv1x1_stream_kernel<T, TC>), dim3((unsigned)(8 * per_die)), dim3(64 * g.waves), (unsigned)lds, s, tm.start, tm.stop, 0, a, g);
+  else
+    hipLaunchKernelGGL((conv1x1_stream_kernel<T, TC>), dim3((unsigned)(8 * per_die)), dim3(64 * g.waves), (unsigned)lds, s, a, g);
+  return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_stream_typed(const ConvArgs& a, long long M, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
+  if (a.Cout <= 32) return launch_stream_cfg<T, 1>(a, M, num_cu, s, kernel_id, tm);
+  if (a.Cout > 64 && a.Cout % 96 == 0) return launch_stream_cfg<T, 3>(a, M, num_cu, s, kernel_id, tm);
+  if (a.Cout >= 256 && a.Cin <= 64) return launch_stream_cfg<T, 4>(a, M, num_cu, s, kernel_id, tm);
+  return launch_stream_cfg<T, 2>(a, M, num_cu, s, kernel_id, tm);
+}
+
+// 1x1 / stride-1 layers in the 16-bit types with at most 192 input channels and a block of pixels for every other
+// wavefront of the chip; hipErrorNotSupported otherwise.  Longer reductions have work enough per byte for the general
+// kernel's larger tiles (256 channels: even; 384 -> 192 on 80 x 80: 63 us there, 95 here), and so have channel counts that
+// are no multiple of 8 (their last vectors would be written element by element).  The sums are those of the general kernel.
+// Measured, bf16: 96 -> 96 on 32 x 160 x 160 107 -> 81 us (3.9 TB/s), on 32 x 320 x 320 420 -> 301; 64 x 80 x 80 x 128 ->
+// 128 52 -> 42; 119 x 64 x 32 x 64 -> 256 44 -> 31.
+hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm) {
+  if ((dtype != OCTO_F16 && dtype != OCTO_BF16) || a.pair_view || a.pool_y || a.up_y || a.out_f32 || a.kh != 1 || a.kw != 1 || a.stride_h != 1 || a.stride_w != 1 ||
+      a.pad_h || a.pad_w || a.Cin > 192 || a.Cin < 16)
+    return hipErrorNotSupported;
+  if (((a.Cin | a.x_ld | a.x_coff | a.Cout | a.y_ld | a.y_coff) & 7) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return hipErrorNotSupported;
+  if (a.res && (((a.res_ld | a.res_coff) & 7) || ((uintptr_t)a.res & 15))) return hipErrorNotSupported;
+  const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
+  if ((M + 31) / 32 * ((a.Cout + 63) / 64) < 4LL * num_cu) return hipErrorNotSupported;
+  return dtype == OCTO_F16 ? launch_stream_typed<_Float16>(a, M, num_cu, s, kernel_id, tm) : launch_stream_typed<__bf16>(a, M, num_cu, s, kernel_id, tm);
+}
+
+}  // namespace octo

@@ -44,7 +44,7 @@ struct ConvArgs {
   void* pool_y;
   int pool_ho, pool_wo, pool_ld, pool_coff;
   int pool_seg;                   // tiles per segment of a strip (set by launch_stem)
-  // Two layers in one launch (general kernel, 16-bit types, no residual): output channels below `split` go to y as
+  // Two layers in one launch (general, split-K and streaming 1x1 kernels, 16-bit types, no residual): output channels below `split` go to y as
   // usual, channels split .. Cout - 1 to y2 as its channels 0 ..; split is a multiple of 8 and 0 when unused.
   void* y2;
   int y2_ld, y2_coff, split;
@@ -67,6 +67,8 @@ struct ConvTiming { hipEvent_t start = nullptr, stop = nullptr; };
 hipError_t launch_conv(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id = nullptr, ConvTiming tm = ConvTiming());
 // first-layer kernel for pixel-pair layers; hipErrorNotSupported when the layer does not fit it
 hipError_t launch_stem(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
+// 1x1 layers of large maps with resident weights; hipErrorNotSupported when the layer does not fit it
+hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 // 3x3 stride-1 kernel with the input patch in LDS; hipErrorNotSupported when the layer does not fit it
 hipError_t launch_conv3x3_patch(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 // 3x3 stride-1 kernel for wide layers (patch in LDS, 192 / 256-channel tiles); hipErrorNotSupported when the layer does not fit it
