@@ -62,12 +62,11 @@ def conv_name(kid: int, dtype: str) -> str:
     if 600000000 <= d < 700000000:                       # split-K kernel: digits S BBB PPP (K split, channel tile, pixel tile)
         ks, bc, bp = (d - 600000000) // 1000000, (d // 1000) % 1000, d % 1000
         return "octo::conv_ksplit_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp // 32, ks, ks)
-    if 700000000 <= d < 800000000:                       # wide 3x3 kernel: digits P BBB TTT (512-pixel tile, channel tile, tile width)
-        bc = ((d - 700000000) // 1000) % 1000
-        tc, tp, wc = (3, 4, 1) if bc == 96 else (bc // 64, 4, 2)
-        return "octo::conv3x3_big_kernel<%s, %d, %d, %d, 4>" % (ctype, tc, tp, wc)
-    if 800000000 <= d < 900000000:                       # 3x3 kernel with the input patch in LDS: channel slice
-        return "octo::conv3x3_patch_kernel<%s, %d, %d>" % (ctype, (d - 800000000) % 1000, (d - 800000000) // 1000)
+    if 400000000 <= d < 500000000 or 700000000 <= d < 900000000:      # 3x3 kernel with the input patch in LDS: digits Q BBB CCC
+        bp, bc, kv = (128, 256, 64)[(d // 1000000) % 10], (d // 1000) % 1000, d % 1000 // (32 if dtype == "f8" else 16)
+        wc, passes = (2, 4) if bp == 64 else (1, bp * kv * 3 // 512)
+        minb = 2 if kv == 8 or bp == 256 else 3 if bc == 96 else 4
+        return "octo::conv3x3_mid_kernel<%s, %d, %d, %d, %d, 3, %d, %d>" % (ctype, bc, bp, wc, kv, passes, minb)
     if d >= 900000000:                                   # first-layer kernel: digits BBB KK P
         d -= 900000000                                   # F BBB KK P: F = 1 with the following max-pool fused
         return "octo::stem_conv_kernel<%s, %d, %d, %d, %s>" % (ctype, (d // 1000) % 1000, (d // 10) % 100, d % 10, "true" if d >= 1000000 else "false")
@@ -114,7 +113,7 @@ TRAFFIC_SOURCE = "profiles/*_hbm_counters.md: rocprofv3 --pmc FETCH_SIZE and --p
 def conv_sources_key() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv.hip", "conv_ksplit.h", "conv1x1.hip", "convbig.hip", "conv3x3.hip", "stem.hip", "mfma_common.h"):
+    for f in ("conv.hip", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "stem.hip", "mfma_common.h"):
         try:
             h.update(open(os.path.join(ROOT, "paper_2502_01277_amd", "csrc", f), "rb").read())
         except OSError:

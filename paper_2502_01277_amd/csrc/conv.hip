@@ -25,6 +25,7 @@
 #include "octo_internal.h"
 #include "mfma_common.h"
 #include "conv_ksplit.h"
+#include "conv3x3_mid.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -494,6 +495,10 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   // That kernel sums in another order, so the choice is made for a.n_split items where the count is taken on the device:
   // unlike the running average behind n_hint it stays the same from batch to batch, and so do the results.
   const long long M_split = a.n_split > 0 ? (long long)(a.n_split < a.n ? a.n_split : a.n) * a.Ho * a.Wo : M;
+  if constexpr (sizeof(T) == 2) {
+    const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
+    if (em != hipErrorNotSupported) return em;
+  }
   const GeneralTile st = general_tile(a, M_split, num_cu, 1);
   const int ks = ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
   if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
@@ -514,6 +519,12 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   const bool vec = (a.Cin % 16 == 0) && (a.x_ld % 16 == 0) && (a.x_coff % 16 == 0) && (((uintptr_t)a.x & 15) == 0) && a.kh <= 15 && a.kw <= 15;
   if (!vec || !a.scale || a.pair_view) return hipErrorInvalidValue;
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
+  // 3x3 layers with enough tiles for every compute unit: input patch in LDS, slices of 128 channels (256 -> 256 with residual on
+  // 1021 x 14 x 14: 155 us, 161 on the tiles below)
+  if (mid_fits(a) && a.Cout > 32 && a.Cin * 4 >= (a.Cin + 127) / 128 * 128 * 3 && (double)M / 128 * ((a.Cout + 63) / 64) >= 0.8 * num_cu) {
+    const hipError_t em = launch_mid_cfg<f8, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+    if (em != hipErrorNotSupported) return em;
+  }
   const GeneralTile t = general_tile(a, M, num_cu, 2);
   const int ks = ksplit_choose(a, M, 1, t.bc, t.bp, num_cu);
   if (ks >= 0) return launch_ksplit<f8>(ks, a, num_cu, s, kernel_id, tm);
@@ -601,22 +612,6 @@ hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s,
   if (es != hipErrorNotSupported || a.pool_y) return es;      // only the first-layer kernel can pool its own output
   const hipError_t e1 = launch_conv1x1_stream(dtype, a, num_cu, s, kernel_id, tm);
   if (e1 != hipErrorNotSupported) return e1;
-  // 3x3 layers with at most 64 output channels on wide images: the input patch of a tile lives in LDS (measured
-  // +20% on 56x56x64 layers; the 8x32 pixel tile wastes lanes on narrow feature maps, and with more output channels
-  // the general kernel's 128-channel tile re-uses the pixel operand enough)
-  {
-    const long long m_hint = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
-    if (a.Cout <= 64 && a.Wo >= 28 && (a.Wo + 31) / 32 * 32 * 7 <= a.Wo * 8 && m_hint >= 2LL * num_cu * 256) {
-      const hipError_t e3 = launch_conv3x3_patch(dtype, a, num_cu, s, kernel_id, tm);
-      if (e3 != hipErrorNotSupported) return e3;
-    }
-  }
-  // wide 3x3 / stride-1 layers: large tiles with the input patch resident in LDS (the general kernel is paced by its
-  // operand fetch there: every pixel is fetched once per kernel tap)
-  {
-    const hipError_t eb = launch_conv3x3_big(dtype, a, num_cu, s, kernel_id, tm);
-    if (eb != hipErrorNotSupported) return eb;
-  }
   switch (dtype) {
     case OCTO_F8: return launch_general_f8(a, num_cu, s, kernel_id, tm);
     case OCTO_F16: return launch_general_f16(a, num_cu, s, kernel_id, tm);

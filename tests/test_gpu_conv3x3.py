@@ -1,0 +1,65 @@
+"""The 3x3 kernel with the input patch in LDS at its edges: widths that no tile divides, tiles that span several images, images of
+one row or column's width, channel counts below and over a tile, input channels that do not fill the last slice, residuals, unaligned
+and wider output buffers, a device-side item count; against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import nn
+from oracle.rounding import round_storage
+from paper_2502_01277_amd import synth, zoo
+from helpers import TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (n, h, w, cin, cout, act, res_mode, x_extra, y_extra, pixel-tile digit, channel tile, channels in LDS)
+    (3, 57, 83, 48, 64, nn.ACT_SILU, nn.RES_NONE, 16, 0, 2, 64, 128),              # 64 x 64 tiles; ragged columns, 3/4 of a slice
+    (7, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, None, 0, 0),       # too few tiles: split-K
+    (21, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 8, 2, 64, 128),      # 64 x 64 tiles across images
+    (61, 14, 15, 192, 136, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 64, 128),       # slices of 128 bytes, 8 of the last 64 channels
+    (5, 80, 81, 64, 64, nn.ACT_RELU, nn.RES_BEFORE_ACT, 64, 64, 0, 64, 64),        # one slice of each buffer, columns 41 + 40
+    (400, 3, 37, 56, 100, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 1, 0, 64, 64),         # unaligned output, 4 of the last 8 channels
+    (9, 160, 160, 32, 32, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 32, 64),         # 32-channel tiles
+    (3, 160, 111, 96, 96, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 96, 64),         # 96-channel tiles
+    (12, 160, 144, 96, 88, nn.ACT_NONE, nn.RES_NONE, 0, 8, 1, 96, 64),             # 96 channels x 256 pixels
+    (650, 28, 28, 96, 128, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 1, 64, 64),       # 64 channels x 256 pixels
+    (33000, 1, 7, 64, 40, nn.ACT_RELU, nn.RES_NONE, 0, 0, 0, 64, 64),              # one-row images: every tap row but one is outside
+]
+
+
+def reference(x, wt, bias, res, act, res_mode):
+    n, h, w, cin = x.shape
+    xp = np.zeros((n, h + 2, w + 2, cin), np.float32)
+    xp[:, 1:-1, 1:-1] = x
+    y = np.zeros((n * h * w, wt.shape[0]), np.float32)
+    for r in range(3):
+        for s in range(3):
+            y += np.ascontiguousarray(xp[:, r:r + h, s:s + w]).reshape(-1, cin) @ np.ascontiguousarray(wt[:, r, s].T)
+    y = (y + bias).reshape(n, h, w, -1)
+    if res_mode == nn.RES_BEFORE_ACT:
+        return nn.activation(y + res, act)
+    return nn.activation(y, act) + (res if res_mode else 0.0)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", CASES)
+def test_patch_3x3_parity(octo, dtype, case):
+    import torch
+    n, h, w, cin, cout, act, res_mode, xe, ye, q, bc, chan = case
+    rng = np.random.default_rng(43)
+    x = zoo.round_to_dtype(rng.uniform(-1, 1, (n, h, w, cin)).astype(np.float32), dtype)
+    wt = zoo.round_to_dtype((rng.standard_normal((cout, 3, 3, cin)) / np.sqrt(9 * cin)).astype(np.float32), dtype)
+    bias = rng.uniform(-0.1, 0.1, cout).astype(np.float32)
+    layer = octo.ConvOp(synth.to_storage(wt, dtype), bias, dtype, 1, 1, act)
+    res = zoo.round_to_dtype(rng.uniform(-1, 1, (n, h, w, cout)).astype(np.float32), dtype) if res_mode else None
+    dx = torch.full((n, h, w, cin + xe), 5.0, dtype=octo.torch_dtype(dtype), device="cuda")
+    dx[..., :cin] = octo.to_device(x, dtype)
+    dy = torch.full((n, h, w, cout + ye), -7.0, dtype=octo.torch_dtype(dtype), device="cuda")
+    kid = octo.op_conv(layer, dx[..., :cin], dy[..., :cout], octo.to_device(res, dtype) if res_mode else None, res_mode)
+    torch.cuda.synchronize()
+    family = {1400000000, 1700000000, 1800000000}
+    assert (kid // 100000000 * 100000000 in family) == (q is not None), kid
+    if q is not None:
+        assert kid % 100000000 == q * 1000000 + bc * 1000 + chan, kid
+    assert rel_err(dy[..., :cout].float().cpu().numpy(), round_storage(reference(x, wt, bias, res, act, res_mode), dtype)) <= TOL[dtype]
+    assert (dy[..., cout:].float().cpu().numpy() == -7.0).all()
