@@ -63,6 +63,11 @@ def conv_name(kid: int, dtype: str) -> str:
         ks, bc, bp = (d - 600000000) // 1000000, (d // 1000) % 1000, d % 1000
         return "octo::conv_ksplit_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp // 32, ks, ks)
     if 400000000 <= d < 500000000 or 700000000 <= d < 900000000:      # 3x3 kernel with the input patch in LDS: digits Q BBB CCC
+        q, kc = (d // 1000000) % 10, d % 1000 // 16
+        if q == 5:                                                     # its streaming form
+            wc = (d // 1000) % 1000 // 32
+            kv, passes = (4, 6 // wc) if kc == 2 else (8, 6)
+            return "octo::conv3x3_stream_kernel<%s, %d, %d, %d, %d, %d, %d>" % (ctype, wc, kc, kv, passes, 4 if kc == 3 else 3, 3 if wc == 2 and kc == 2 else 2)
         bp, bc, kv = (128, 256, 64)[(d // 1000000) % 10], (d // 1000) % 1000, d % 1000 // (32 if dtype == "f8" else 16)
         wc, passes = (2, 4) if bp == 64 else (1, bp * kv * 3 // 512)
         minb = 2 if kv == 8 or bp == 256 else 3 if bc == 96 else 4
@@ -113,7 +118,7 @@ TRAFFIC_SOURCE = "profiles/*_hbm_counters.md: rocprofv3 --pmc FETCH_SIZE and --p
 def conv_sources_key() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv.hip", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "stem.hip", "mfma_common.h"):
+    for f in ("conv.hip", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "conv3x3_stream.h", "stem.hip", "mfma_common.h"):
         try:
             h.update(open(os.path.join(ROOT, "paper_2502_01277_amd", "csrc", f), "rb").read())
         except OSError:

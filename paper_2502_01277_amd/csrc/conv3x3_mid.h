@@ -9,15 +9,18 @@
 //     once into one of two LDS buffers; only the BC weight rows of a (slice, tap) step stream, through a ring of NST stages.
 //     A 64 x 128 tile then fetches 10.5 KB per 128-byte step instead of 24 KB;
 //   * the pixel operand of every tap is read from the patch with an address that the lane works out once per tile; taps
-//     outside the image point at a row of zeros, so that image borders need no padding rows in LDS;
+//     outside the image point at rows of zeros, so that image borders need no padding rows in LDS;
 //   * the barrier of a step sits before the last group of its MFMAs, with the next step's first fragments read behind it.
 // Several workgroups share a compute unit, so that the prologue and epilogue of one overlap the K loop of another.
 // LDS rows (weights: one output channel; patch: one pixel) are KV vectors of 16 bytes, vector v of row r in slot
-// v ^ ((r / (16 / KV)) % KV): fills and fragment reads are free of bank conflicts.
+// v ^ ((r / (16 / KV)) % KV).  For patch pixels r counts without the halo columns (patch row * TW + column), so that the lanes of
+// consecutive output pixels stay on different banks where a tile row ends (with the halo counted, 64 -> 64 on 56 x 56 maps ran
+// 10 % slower), and a lane outside the image reads zeros from its own bank.
 // vmcnt bookkeeping: every wavefront issues the same number of loads per tap, known at compile time, in program order.
 #pragma once
 #include "octo_internal.h"
 #include "mfma_common.h"
+#include "conv3x3_stream.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
 
@@ -55,7 +58,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   constexpr int ROW = KV * 16, STAGE = LA * RP * ROW, PATCH = MAXP * 4096;
   constexpr int KK = ES == 1 ? KV / 4 : KV / 2;          // groups of MFMAs per step
   constexpr int FV = ES == 1 ? 2 : 1;                    // vectors per operand fragment
-  constexpr int ZROW = MAXP * RP - 1;                    // last row of a patch buffer, kept zero (the host leaves it free)
+  constexpr int ZROW = MAXP * RP - RPW;                  // last rows of a patch buffer, kept zero (the host leaves them free)
   constexpr int NTAP = 9;
   static_assert(BC % 32 == 0 && TC >= 1 && TP >= 1 && KK % 2 == 0 && NST >= 2 && NST <= 4, "tile shape");
   constexpr int OPITCH = BC * ES + 16;
@@ -79,7 +82,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   const T* __restrict__ xg = (const T*)a.x + a.x_coff;
 
   const int ld_row = tid / KV;
-  const int lkv = (tid % KV) ^ ((ld_row / RPW) % KV);
+  const int lkv = (tid % KV) ^ ((ld_row / RPW) % KV);    // logical vector of this lane's slot of a weight row
   const int rsw = (l32 / RPW) % KV;
   const unsigned lds_ring = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)ring + (unsigned)wave * 1024u));
   const unsigned lds_patch = lds_ring + NST * STAGE;
@@ -103,22 +106,28 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
     const long long rem_bytes = (((long long)a.n * H * W - pix0) * a.x_ld - a.x_coff) * ES;
     const int p_len = (int)(rem_bytes < BUF_MAX ? rem_bytes : BUF_MAX);
     void* p_base = (void*)(xg + pix0 * a.x_ld);
-    int poff[MAXP], woff[LA];
+    // (opaque to the compiler, which would otherwise keep the tile-independent part of every address in registers of its own)
+    int poff[MAXP], woff[LA], lrow = ld_row, lpix = wp * (TP * 32) + l32;
+    asm volatile("" : "+v"(lrow), "+v"(lpix));
+    auto patch_offsets = [&](int channels) __attribute__((always_inline)) {      // vectors past that many channels of a slice read as zeros
 #pragma unroll
-    for (int i = 0; i < MAXP; ++i) {
-      const int pp = i * RP + ld_row;
-      const int pr = (int)fast_div((unsigned)pp, gm.div_pw), pc = pp - pr * gm.PW;
-      const int v = v0 - 1 + pr, x = x0 - gm.halo + pc;
-      const bool ok = pr < gm.TH + 2 && (unsigned)v < (unsigned)n_rows && (unsigned)x < (unsigned)W;
-      poff[i] = ok ? ((pr * W + x) * a.x_ld + lkv * VN) * ES : OOB;
-    }
+      for (int i = 0; i < MAXP; ++i) {
+        const int pp = i * RP + lrow;
+        const int pr = (int)fast_div((unsigned)pp, gm.div_pw), pc = pp - pr * gm.PW;
+        const int v = v0 - 1 + pr, x = x0 - gm.halo + pc;
+        const int vec = (tid % KV) ^ ((int)((unsigned)(pr * gm.TW + pc) / RPW) % KV);
+        const bool ok = pr < gm.TH + 2 && (unsigned)v < (unsigned)n_rows && (unsigned)x < (unsigned)W && vec * VN < channels;
+        poff[i] = ok ? ((pr * W + x) * a.x_ld + vec * VN) * ES : OOB;
+      }
+    };
+    patch_offsets(a.Cin);
 #pragma unroll
     for (int i = 0; i < LA; ++i) woff[i] = ld_row + RP * i < BC ? ((c0 + ld_row + RP * i) * a.Kp + lkv * VN) * ES : OOB;
     // byte offset inside a patch buffer of this lane's first vector, per tap and block
     int baddr[NTAP][TP];
 #pragma unroll
     for (int j = 0; j < TP; ++j) {
-      const int q = wp * (TP * 32) + j * 32 + l32;
+      const int q = lpix + j * 32;
       const int ty = (int)fast_div((unsigned)q, gm.div_tw), tx = q - ty * gm.TW;
       const int v = v0 + ty, x = x0 + tx;
       const int yy = v - (int)fast_div((unsigned)v, gm.div_h) * H;
@@ -127,8 +136,8 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
       for (int tap = 0; tap < NTAP; ++tap) {
         const int r = tap / 3, s = tap % 3 - 1;
         const bool in = ok && (unsigned)(yy + r - 1) < (unsigned)H && (unsigned)(x + s) < (unsigned)W;
-        const int px = in ? (ty + r) * gm.PW + tx + s + gm.halo : ZROW;
-        baddr[tap][j] = px * ROW + ((g ^ ((px / RPW) % KV)) << 4);
+        const int px = (ty + r) * gm.PW + tx + s + gm.halo, pos = px - (ty + r) * (gm.PW - gm.TW);
+        baddr[tap][j] = (in ? px : ZROW + (px & (RPW - 1))) * ROW + ((g ^ ((pos >> (RPW == 2 ? 1 : 2)) & (KV - 1))) << 4);
       }
     }
 
@@ -153,15 +162,15 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                      :: "s"(lds_ring + st * STAGE + i * 4096), "v"(woff[i]), "s"(rs), "s"(koff) : "memory");
     };
-    auto issue_p = [&](int sl, int from, int count) __attribute__((always_inline)) {     // passes of slice sl's patch
+    // passes of slice sl's patch
+    auto issue_p = [&](int sl, int from, int count) __attribute__((always_inline)) {
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p_base, 0, sl < n_slices ? p_len : 0, BUF_FLAGS);
       const int koff = sl * BK * ES;
-      const bool past = sl * BK + lkv * VN >= a.Cin;       // channels past the last: zeros (the weights there may be anything finite)
 #pragma unroll
       for (int i = 0; i < MAXP; ++i)
         if (i >= from && i < from + count)
           asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                       :: "s"(lds_patch + (sl & 1) * PATCH + i * 4096), "v"(past ? OOB : poff[i]), "s"(rs), "s"(koff) : "memory");
+                       :: "s"(lds_patch + (sl & 1) * PATCH + i * 4096), "v"(poff[i]), "s"(rs), "s"(koff) : "memory");
     };
     u32x4 fa[2][TC][FV], fb[2][TP][FV];
     const int arow = (wc * (TC * 32) + l32) * ROW;
@@ -214,6 +223,8 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
       rd = nxt;
     };
     for (int sl = 0; sl < n_slices; ++sl) {
+      // the last slice, fetched from here on, may be partial: its missing channels are zeros (the weights there anything finite)
+      if (sl + 2 == n_slices && a.Cin % BK) patch_offsets(a.Cin % BK);
       step(std::integral_constant<int, 0>{}, sl); step(std::integral_constant<int, 1>{}, sl); step(std::integral_constant<int, 2>{}, sl);
       step(std::integral_constant<int, 3>{}, sl); step(std::integral_constant<int, 4>{}, sl); step(std::integral_constant<int, 5>{}, sl);
       step(std::integral_constant<int, 6>{}, sl); step(std::integral_constant<int, 7>{}, sl); step(std::integral_constant<int, 8>{}, sl);
@@ -292,7 +303,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   }
 }
 
-// Tile of at most BP pixels whose patch leaves one of `rows` LDS rows free: the split of the image width into equal columns and
+// Tile of at most BP pixels whose patch leaves four of `rows` LDS rows free: the split of the image width into equal columns and
 // the number of rows that give the most pixels per tile, ties to the smaller patch.  False if no shape fills 3/4 of the tile.
 inline bool mid_geometry(const ConvArgs& a, int BC, int BP, int rows, MidGeom* gm) {
   double best = 0;
@@ -301,7 +312,7 @@ inline bool mid_geometry(const ConvArgs& a, int BC, int BP, int rows, MidGeom* g
     const int tw = (a.W + nx - 1) / nx, pw = nx == 1 ? tw : tw + 2;
     if (tw > BP) continue;
     if (tw < 4) break;
-    const int th = std::min(BP / tw, (rows - 1) / pw - 2);
+    const int th = std::min(BP / tw, (rows - 4) / pw - 2);
     if (th < 1) continue;
     const int tiles_x = (a.W + tw - 1) / tw, patch = (th + 2) * pw;
     const double px = (double)a.W * th / tiles_x;
@@ -350,6 +361,7 @@ inline bool mid_fits(const ConvArgs& a) {
 
 // Tile of a 16-bit layer with M output pixels, or hipErrorNotSupported where the split-K or general kernel is the better one
 // (measured on MI355X).  per_cu: 64 x 128 tiles per compute unit.
+//   * up to 64 channels and many pixels: conv3x3_stream_kernel;
 //   * below 0.35 the split-K kernel spreads the K loop of the few tiles over more wavefronts;
 //   * reductions over at least 192 channels with fewer than six tiles per compute unit are paced by the operand fetch: slices of
 //     128 bytes (whole cache lines), and 64 x 64 tiles while those leave compute units idle.  256 -> 256 on 63 x 14 x 14: 19 us
@@ -364,6 +376,8 @@ inline bool mid_fits(const ConvArgs& a) {
 template <typename T>
 hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (!mid_fits(a)) return hipErrorNotSupported;
+  const hipError_t es = launch_stream3<T>(a, M, num_cu, s, kernel_id, tm);
+  if (es != hipErrorNotSupported) return es;
   const int pad32 = (a.Cin + 31) / 32 * 32, pad64 = (a.Cin + 63) / 64 * 64;
   if (a.Cin * 4 < pad32 * 3) return hipErrorNotSupported;       // more than a quarter of the MFMAs would be padding
   if (a.Cout <= 32) return (double)M / 128 < 0.8 * num_cu ? hipErrorNotSupported : launch_mid_cfg<T, 32, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);

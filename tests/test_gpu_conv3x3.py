@@ -19,7 +19,13 @@ CASES = [
     (61, 14, 15, 192, 136, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 64, 128),       # slices of 128 bytes, 8 of the last 64 channels
     (5, 80, 81, 64, 64, nn.ACT_RELU, nn.RES_BEFORE_ACT, 64, 64, 0, 64, 64),        # one slice of each buffer, columns 41 + 40
     (400, 3, 37, 56, 100, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 1, 0, 64, 64),         # unaligned output, 4 of the last 8 channels
-    (9, 160, 160, 32, 32, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 32, 64),         # 32-channel tiles
+    (8, 83, 80, 32, 32, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 32, 64),           # 32-channel tiles
+    (17, 112, 112, 32, 32, nn.ACT_RELU, nn.RES_BEFORE_ACT, 32, 0, 5, 32, 32),      # resident weights, 16 x 16 tiles
+    (7, 160, 176, 24, 24, nn.ACT_SILU, nn.RES_NONE, 0, 8, 5, 32, 32),              # 8 of the second 16 channels, on both sides
+    (60, 30, 60, 32, 64, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 5, 64, 32),          # 64 output channels over 32 input channels
+    (65, 56, 56, 40, 56, nn.ACT_NONE, nn.RES_AFTER_ACT, 8, 8, 5, 64, 48),          # 4 x 28 tiles, half of the third 16 channels
+    (130, 48, 32, 64, 64, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 64, 5, 64, 64),       # 4 x 32 tiles
+    (5400, 6, 7, 64, 64, nn.ACT_SILU, nn.RES_NONE, 0, 0, 0, 64, 64),               # no tile divides the image
     (3, 160, 111, 96, 96, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 96, 64),         # 96-channel tiles
     (12, 160, 144, 96, 88, nn.ACT_NONE, nn.RES_NONE, 0, 8, 1, 96, 64),             # 96 channels x 256 pixels
     (650, 28, 28, 96, 128, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 1, 64, 64),       # 64 channels x 256 pixels
