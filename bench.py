@@ -70,7 +70,7 @@ def conv_name(kid: int, dtype: str) -> str:
             return "octo::conv3x3_stream_kernel<%s, %d, %d, %d, %d, %d, %d>" % (ctype, wc, kc, kv, passes, 4 if kc == 3 else 3, 3 if wc == 2 and kc == 2 else 2)
         bp, bc, kv = (128, 256, 64)[(d // 1000000) % 10], (d // 1000) % 1000, d % 1000 // (32 if dtype == "f8" else 16)
         wc, passes = (2, 4) if bp == 64 else (1, bp * kv * 3 // 512)
-        minb = 2 if kv == 8 or bp == 256 else 3 if bc == 96 else 4
+        minb = 2 if kv == 8 or bp == 256 else 3 if bc > 64 else 4
         return "octo::conv3x3_mid_kernel<%s, %d, %d, %d, %d, 3, %d, %d>" % (ctype, bc, bp, wc, kv, passes, minb)
     if d >= 900000000:                                   # first-layer kernel: digits BBB KK P
         d -= 900000000                                   # F BBB KK P: F = 1 with the following max-pool fused

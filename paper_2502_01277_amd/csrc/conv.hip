@@ -519,10 +519,15 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   const bool vec = (a.Cin % 16 == 0) && (a.x_ld % 16 == 0) && (a.x_coff % 16 == 0) && (((uintptr_t)a.x & 15) == 0) && a.kh <= 15 && a.kw <= 15;
   if (!vec || !a.scale || a.pair_view) return hipErrorInvalidValue;
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
-  // 3x3 layers with enough tiles for every compute unit: input patch in LDS, slices of 128 channels (256 -> 256 with residual on
-  // 1021 x 14 x 14: 155 us, 161 on the tiles below)
-  if (mid_fits(a) && a.Cout > 32 && a.Cin * 4 >= (a.Cin + 127) / 128 * 128 * 3 && (double)M / 128 * ((a.Cout + 63) / 64) >= 0.8 * num_cu) {
-    const hipError_t em = launch_mid_cfg<f8, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+  // 3x3 layers with enough tiles for every compute unit: input patch in LDS, slices of 64 channels, four workgroups per compute unit
+  // (256 -> 256 on 300 x 14 x 14: 39 us, slices of 128 channels 46); with plenty of tiles 128 channels per tile halve the fetch of
+  // the patch (256 -> 256 with residual on 1021 x 14 x 14: 125 us, 131 on 64 channels, 161 on the tiles below)
+  if (mid_fits(a) && a.Cout > 32 && a.Cin * 4 >= (a.Cin + 63) / 64 * 64 * 3) {
+    const double per_cu = (double)M / 128 * ((a.Cout + 63) / 64) / num_cu;
+    const bool wide = per_cu >= 12 && (a.Cout + 127) / 128 * 2 == (a.Cout + 63) / 64;
+    const hipError_t em = per_cu < 0.8 ? hipErrorNotSupported
+                          : wide      ? launch_mid_cfg<f8, 128, 128, 1, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm)
+                                      : launch_mid_cfg<f8, 64, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);
     if (em != hipErrorNotSupported) return em;
   }
   const GeneralTile t = general_tile(a, M, num_cu, 2);

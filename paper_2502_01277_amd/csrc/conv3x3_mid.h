@@ -60,7 +60,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   constexpr int FV = ES == 1 ? 2 : 1;                    // vectors per operand fragment
   constexpr int ZROW = MAXP * RP - RPW;                  // last rows of a patch buffer, kept zero (the host leaves them free)
   constexpr int NTAP = 9;
-  static_assert(BC % 32 == 0 && TC >= 1 && TP >= 1 && KK % 2 == 0 && NST >= 2 && NST <= 4, "tile shape");
+  static_assert(BC % 32 == 0 && TC >= 1 && TP >= 1 && (KK == 1 || KK % 2 == 0) && NST >= 2 && NST <= 4, "tile shape");
   constexpr int OPITCH = BC * ES + 16;
   constexpr int OPER = NST * STAGE + 2 * PATCH, OSTAGE = BP * OPITCH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[OPER > OSTAGE ? OPER : OSTAGE];
@@ -188,11 +188,14 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
     };
 
     issue_p(0, 0, MAXP);
+    constexpr int AHEAD = KK == 1 ? NST - 1 : NST;         // steps whose weights are requested up front
 #pragma unroll
-    for (int d = 0; d < NST; ++d) issue_w(0, d, d);
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LA) : "memory");
-    __builtin_amdgcn_s_barrier();
-    frags(0, 0, baddr[0], 0, 0);
+    for (int d = 0; d < AHEAD; ++d) issue_w(0, d, d);
+    if constexpr (KK > 1) {
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LA) : "memory");
+      __builtin_amdgcn_s_barrier();
+      frags(0, 0, baddr[0], 0, 0);
+    }
     int rd = 0;                                // ring stage of the current step
     auto step = [&](auto tapc, int sl) __attribute__((always_inline)) {
       constexpr int TAP = decltype(tapc)::value, NEXT = (TAP + 1) % NTAP, LTAP = (TAP + NST) % NTAP;
@@ -200,7 +203,14 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
       const int nxt = NTAP % NST == 0 ? NEXT % NST : (rd + 1 == NST ? 0 : rd + 1);
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
-        if (kk < KK - 1) {
+        if constexpr (KK == 1) {
+          // a single group per step: its fragments are read here, and the loads go to the stage that the previous step has left
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(mid_in_flight(TAP, NST, LA, MAXP)) : "memory");
+          __builtin_amdgcn_s_barrier();
+          frags(0, cur, baddr[TAP], sl & 1, 0);
+          issue_p(sl + 1, TAP * mid_ppt(MAXP), mid_passes(TAP, MAXP));
+          issue_w(TAP + NST - 1 >= NTAP ? sl + 1 : sl, (TAP + NST - 1) % NTAP, NTAP % NST == 0 ? (TAP + NST - 1) % NST : (rd == 0 ? NST - 1 : rd - 1));
+        } else if (kk < KK - 1) {
           frags((kk + 1) & 1, cur, baddr[TAP], sl & 1, kk + 1);
         } else {
           // this wavefront holds all it needs of the stage in registers, and the next step's operands have landed

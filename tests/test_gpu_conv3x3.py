@@ -69,3 +69,29 @@ def test_patch_3x3_parity(octo, dtype, case):
         assert kid % 100000000 == q * 1000000 + bc * 1000 + chan, kid
     assert rel_err(dy[..., :cout].float().cpu().numpy(), round_storage(reference(x, wt, bias, res, act, res_mode), dtype)) <= TOL[dtype]
     assert (dy[..., cout:].float().cpu().numpy() == -7.0).all()
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,res,bc", [
+    (90, 14, 14, 192, 136, True, 64),          # three slices, 8 of the last 64 channels
+    (20, 41, 37, 112, 64, False, 64),          # three quarters of the second slice, ragged columns
+    (1100, 14, 14, 64, 256, True, 128),        # one slice, 128-channel tiles
+])
+def test_patch_3x3_fp8(octo, n, h, w, cin, cout, res, bc):
+    import torch
+    rng = np.random.default_rng(47)
+    f8 = lambda shape, s: torch.from_numpy((rng.standard_normal(shape) * s).astype(np.float32)).to(torch.float8_e4m3fn)
+    x, wt = f8((n, h, w, cin), 1.0), f8((cout, 3, 3, cin), 2.0)
+    r = f8((n, h, w, cout), 1.0) if res else None
+    scale, bias = (0.02 + 0.01 * rng.random(cout)).astype(np.float32), rng.uniform(-0.1, 0.1, cout).astype(np.float32)
+    layer = octo.ConvOp(wt.view(torch.uint8).numpy(), bias, "f8", 1, 1, nn.ACT_RELU, scale=scale)
+    y = torch.zeros((n, h, w, cout), dtype=torch.uint8, device="cuda")
+    kid = octo.op_conv(layer, x.view(torch.uint8).cuda(), y, r.view(torch.uint8).cuda() if res else None, nn.RES_BEFORE_ACT if res else 0, res_scale=0.5, y_inv_scale=2.0)
+    torch.cuda.synchronize()
+    assert kid // 100000000 in (14, 17, 18) and kid % 100000000 == bc * 1000 + 128, kid
+    acc = reference(x.float().numpy(), wt.float().numpy(), np.zeros(cout, np.float32), None, nn.ACT_NONE, nn.RES_NONE)
+    want = np.maximum(acc * scale + bias + (0.5 * r.float().numpy() if res else 0.0), 0.0) * 2.0
+    want = torch.from_numpy(np.minimum(want, 448.0)).to(torch.float8_e4m3fn)
+    got = y.cpu().view(torch.float8_e4m3fn)
+    # one code apart at most, and that only where the fp32 sum lies next to a rounding boundary
+    diff = (got.view(torch.uint8).int() - want.view(torch.uint8).int()).abs()
+    assert int(diff.max()) <= 1 and float((diff != 0).float().mean()) < 1e-3
