@@ -76,11 +76,11 @@ def conv_name(kid: int, dtype: str) -> str:
         d -= 900000000                                   # F BBB KK P: F = 1 with the following max-pool fused
         return "octo::stem_conv_kernel<%s, %d, %d, %d, %s>" % (ctype, (d // 1000) % 1000, (d // 10) % 100, d % 10, "true" if d >= 1000000 else "false")
     bc, bp, kv, minb, v = d // 1000000, (d // 1000) % 1000, (d // 100) % 10, (d // 10) % 10, d % 10
-    vec, dma = v & 1, v >> 1
-    wc, wp = (1, 4) if (bc == 32 or bp == 256) else (2, 2)
-    depth = 1 if dma else 2
-    return "octo::conv_mfma_kernel<%s, %d, %d, %d, %d, %d, %d, %d, %s, %s>" % (
-        ctype, bc, bp, wc, wp, kv, depth, minb, "true" if vec else "false", "true" if dma else "false")
+    vec, dma, pipe = v & 1, (v >> 1) & 1, v >> 2
+    wc, wp = (1, 4) if (bc == 32 or (bp == 256 and bc == 64)) else (2, 2)
+    depth = 2 if pipe or not dma else 1
+    return "octo::conv_mfma_kernel<%s, %d, %d, %d, %d, %d, %d, %d, %s, %s, %s>" % (
+        ctype, bc, bp, wc, wp, kv, depth, minb, "true" if vec else "false", "true" if dma else "false", "true" if pipe else "false")
 
 
 # HBM traffic per launch of the dominant kernel, from `rocprofv3 --pmc FETCH_SIZE` and `--pmc WRITE_SIZE` runs of

@@ -38,7 +38,7 @@ namespace octo {
 // inline assembly (the wave's LDS destination is base M0 + lane * 16), and their completion is awaited with explicit
 // vmcnt waits whose counts rely on every wave issuing the same number of loads per K step.  M0 is reserved by the
 // compiler (it writes M0 immediately before each of its own uses), so setting it inside the asm statement is safe.
-template <typename T, int BC, int BP, int WC, int WP, int KV, int D, int MINB, bool VEC, bool DMA = false>
+template <typename T, int BC, int BP, int WC, int WP, int KV, int D, int MINB, bool VEC, bool DMA = false, bool PIPE = false>
 __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs a) {
   using E = Elem<T>;
   constexpr int VN = E::N;
@@ -54,6 +54,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs
   constexpr int LB = BP / RP;            // (pixels)
   static_assert(DMA || D % 2 == 0, "pipeline depth must be even");
   static_assert(WC * WP == 4 && TC >= 1 && TP >= 1 && LB >= 1 && BP % RP == 0 && BC % 32 == 0, "tile shape");
+  static_assert(!PIPE || DMA, "the pipelined loop loads straight to LDS");
   static_assert(!DMA || (VEC && BC % RP == 0), "direct-to-LDS loads need whole passes of all lanes");
   constexpr int NST = DMA ? D + 1 : 2;   // LDS stages
   constexpr int STAGE_VECS_OP = (BC + BP) * ROWV;
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs
   constexpr int OPITCH = BC * ES + 16;                                    // bytes per staged output row
   constexpr int OPER_VECS = NST * (BC + BP) * ROWV;                       // operand tiles, all stages
   constexpr int STAGE_VECS = BP * OPITCH / 16;                            // output tile
-  constexpr bool STAGED = STAGE_VECS <= 4096;                             // stage outputs of up to 64 KB
+  constexpr bool STAGED = STAGE_VECS <= 4096 || STAGE_VECS <= OPER_VECS;  // stage outputs of up to 64 KB, or what the operands took
   constexpr int SMEM_VECS = STAGED && STAGE_VECS > OPER_VECS ? STAGE_VECS : OPER_VECS;
   __shared__ u32x4 smem[SMEM_VECS];
   __shared__ float sBias[BC];
@@ -175,6 +176,85 @@ __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs
       // LDS byte address of this wave's 1 KB slice of pass 0 of stage 0 (lane l writes at + 16 l)
       const unsigned lds_wave = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)smem + (unsigned)wave * 1024u));
       constexpr unsigned STAGE_BYTES = STAGE_VECS_OP * 16, PASS_BYTES = RP * ROWV * 16, A_BYTES = BC * ROWV * 16;
+      if constexpr (PIPE) {
+      // Pipelined form: a K step is KK groups of matrix instructions.  The fragments of a group are read from LDS while the
+      // group before it is multiplied, the loads of step kb + NST - 1 .. kb + NST go out between the groups, and the barrier sits
+      // before the last group: behind it the next step's operands are complete and the stage of this one is free.
+      constexpr int KK = ES == 1 ? KV / 4 : KV / 2;
+      constexpr int FV = ES == 1 ? 2 : 1;
+      constexpr int P0 = (NL + KK - 1) / KK;       // loads issued with each group
+      unsigned need = 0u; int delta = 0, koff = 0; unsigned sbase = 0;
+#define OCTO_CONV_ADDR(KB, ST)                                                                                      \
+      {                                                                                                             \
+        sbase = lds_wave + (unsigned)(ST) * STAGE_BYTES;                                                            \
+        koff = (KB) * (BK * ES);                                                                                    \
+        const unsigned k = (unsigned)(KB) * BK + lkv * VN;                                                          \
+        const unsigned tap = __umulhi(k, a.magic_cin);                                                              \
+        const int c = (int)(k - tap * a.Cin);                                                                       \
+        const int r = a.kw == 1 ? (int)tap : (int)__umulhi(tap, a.magic_kw);                                        \
+        const int s2 = (int)tap - r * a.kw;                                                                         \
+        delta = ((r * a.W + s2) * a.x_ld + c) * ES;                                                                 \
+        need = k < (unsigned)a.K ? ((1u << r) | (0x10000u << s2)) : 0xFFFFFFFFu;                                    \
+      }
+#define OCTO_CONV_PART(FROM, TO)                                                                                    \
+      _Pragma("unroll") for (int q = (FROM); q < (TO) && q < NL; ++q) {                                             \
+        if (q < LB) {                                                                                               \
+          const int off = (hw_ok[q < LB ? q : 0] & need) == need ? rowoff[q < LB ? q : 0] + delta : OOB;            \
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"                   \
+                       :: "s"(sbase + A_BYTES + q * PASS_BYTES), "v"(off), "s"(rsrc_x) : "memory");                  \
+        } else {                                                                                                    \
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"                  \
+                       :: "s"(sbase + (q - LB) * PASS_BYTES), "v"(woff[q >= LB ? q - LB : 0]), "s"(rsrc_w), "s"(koff) : "memory");             \
+        }                                                                                                           \
+      }
+      u32x4 fa[2][TC][FV], fb[2][TP][FV];
+#define OCTO_CONV_FRAGS(SET, ST, KQ)                                                                                \
+      {                                                                                                             \
+        const u32x4* pa = smem + (ST) * STAGE_VECS_OP;                                                              \
+        const u32x4* pb = pa + BC * ROWV;                                                                           \
+        _Pragma("unroll") for (int h = 0; h < FV; ++h) {                                                            \
+          _Pragma("unroll") for (int i = 0; i < TC; ++i)                                                            \
+            fa[SET][i][h] = pa[(wc * (BC / WC) + i * 32 + l32) * ROWV + ((((KQ) * FV + h) * 2 + g) ^ rsw)];         \
+          _Pragma("unroll") for (int j = 0; j < TP; ++j)                                                            \
+            fb[SET][j][h] = pb[(wp * (BP / WP) + j * 32 + l32) * ROWV + ((((KQ) * FV + h) * 2 + g) ^ rsw)];         \
+        }                                                                                                           \
+      }
+#pragma unroll
+      for (int d = 0; d < NST - 1; ++d) { OCTO_CONV_ADDR(d, d) OCTO_CONV_PART(0, NL) }
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 2) * NL) : "memory");
+      __builtin_amdgcn_s_barrier();
+      OCTO_CONV_ADDR(NST - 1, NST - 1)
+      OCTO_CONV_PART(0, P0)
+      OCTO_CONV_FRAGS(0, 0, 0)
+      int st_rd = 0;
+      for (int kb = 0; kb < nk; ++kb) {
+        const int st_nx = st_rd + 1 == NST ? 0 : st_rd + 1;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+          if (kk < KK - 1) {
+            OCTO_CONV_FRAGS((kk + 1) & 1, st_rd, kk + 1)
+            OCTO_CONV_PART(P0 * (kk + 1), (kk == KK - 2 ? NL : P0 * (kk + 2)))
+          } else {
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NST - 2) * NL) : "memory");
+            __builtin_amdgcn_s_barrier();
+            OCTO_CONV_FRAGS(0, st_nx, 0)
+            OCTO_CONV_ADDR(kb + NST, st_rd)
+            OCTO_CONV_PART(0, P0)
+          }
+#pragma unroll
+          for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int j = 0; j < TP; ++j) {
+              if constexpr (ES == 1) acc[i][j] = E::mfma2(fa[kk & 1][i][0], fa[kk & 1][i][1], fb[kk & 1][j][0], fb[kk & 1][j][1], acc[i][j]);
+              else acc[i][j] = E::mfma(fa[kk & 1][i][0], fb[kk & 1][j][0], acc[i][j]);
+            }
+        }
+        st_rd = st_nx;
+      }
+#undef OCTO_CONV_ADDR
+#undef OCTO_CONV_PART
+#undef OCTO_CONV_FRAGS
+      } else {
 #define OCTO_CONV_DMA(KB, ST)                                                                                       \
       {                                                                                                             \
         const unsigned sbase = lds_wave + (unsigned)(ST) * STAGE_BYTES;                                             \
@@ -240,6 +320,7 @@ __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs
         st_wr = st_wr + 1 == NST ? 0 : st_wr + 1;
       }
 #undef OCTO_CONV_DMA
+      }
       // the loads issued past the last step still write (zeros) into the ring: drain them before the memory is reused
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
@@ -436,9 +517,9 @@ __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs
 // its type behind one entry point (launch_general_<type>).  Compiled as itself it holds no kernel, only the dispatch
 // (launch_conv) and the host helpers.
 #ifndef OCTO_CONV_NO_LAUNCHERS
-template <typename T, int BC, int BP, int WC, int WP, int KV, int D, int MINB, bool VEC, bool DMA = false>
+template <typename T, int BC, int BP, int WC, int WP, int KV, int D, int MINB, bool VEC, bool DMA = false, bool PIPE = false>
 static hipError_t launch_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
-  if (kernel_id) *kernel_id = conv_kernel_id(BC, BP, KV, MINB, VEC, DMA);
+  if (kernel_id) *kernel_id = conv_kernel_id(BC, BP, KV, MINB, VEC, DMA, PIPE);
   const long long M = (long long)a.n * a.Ho * a.Wo;
   const long long tiles = ((M + BP - 1) / BP) * ((a.Cout + BC - 1) / BC);
   if (tiles <= 0) return hipSuccess;
@@ -447,9 +528,9 @@ static hipError_t launch_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* 
   if (grid > cap) grid = cap;
   // with timing events the dispatch itself carries them, so their difference is the kernel's own run time
   if (tm.start && tm.stop)
-    hipExtLaunchKernelGGL((conv_mfma_kernel<T, BC, BP, WC, WP, KV, D, MINB, VEC, DMA>), dim3((unsigned)grid), dim3(THREADS), 0, s, tm.start, tm.stop, 0, a);
+    hipExtLaunchKernelGGL((conv_mfma_kernel<T, BC, BP, WC, WP, KV, D, MINB, VEC, DMA, PIPE>), dim3((unsigned)grid), dim3(THREADS), 0, s, tm.start, tm.stop, 0, a);
   else
-    hipLaunchKernelGGL((conv_mfma_kernel<T, BC, BP, WC, WP, KV, D, MINB, VEC, DMA>), dim3((unsigned)grid), dim3(THREADS), 0, s, a);
+    hipLaunchKernelGGL((conv_mfma_kernel<T, BC, BP, WC, WP, KV, D, MINB, VEC, DMA, PIPE>), dim3((unsigned)grid), dim3(THREADS), 0, s, a);
   return hipGetLastError();
 }
 
@@ -467,12 +548,26 @@ static hipError_t launch_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* 
 // traffic - whose channel count the 128-channel tile would pad (192 = 3 x 64): 192 -> 192 on 32 x 160 x 160 runs 11 %
 // faster than on 64x128 tiles; beyond K = 384 the larger K step wins.
 // k_scale: values per 2 bytes of K (2 for 8-bit storage, whose reductions are half as long in bytes).
-struct GeneralTile { int bc, bp; };
-static GeneralTile general_tile(const ConvArgs& a, long long M, int num_cu, int k_scale) {
+// 16-bit layers also have three shapes of the pipelined form, whose deeper ring leaves room for two workgroups per compute unit (three
+// with 64x64): 128x64 (64x128 where 128 channels would pad) where their tiles fill one round of those and not more - 128 -> 256,
+// stride 2 on 8 x 80 x 80 15.6 us (128x128: 19.6), 1024 -> 512 on 60 x 16 x 8 14.7 (18.2); one tile more than a round and the
+// others win again -, 64x64 in the same way for fewer pixels and a reduction of at least 1 KB (256 -> 512, stride 2 on
+// 63 x 14 x 14 16.4 us, split-K 18.2), and 128x256 with 64-byte K steps for long reductions over enough pixels to keep its
+// rounds three quarters full (256 -> 512, stride 2 on 64 x 40 x 40 76 us, 128x128: 88).
+struct GeneralTile { int bc, bp; bool pipe = false; };
+static GeneralTile general_tile(const ConvArgs& a, long long M, int num_cu, int k_scale, bool pipe_ok = false) {
   auto tiles = [&](int bc, int bp) { return ((M + bp - 1) / bp) * ((a.Cout + bc - 1) / bc); };
   if (a.Cout <= 32 && k_scale == 1) return {32, 128};
   const bool fits128 = a.Cout >= 96 && (a.Cout + 127) / 128 * 128 == (a.Cout + 63) / 64 * 64;
   if (tiles(64, 256) >= 4 * num_cu && (a.Cout <= 64 || (k_scale == 1 && !fits128 && a.Kp <= 384))) return {64, 256};
+  if (pipe_ok) {
+    const long long big = tiles(128, 256), rounds = (big + 2 * num_cu - 1) / (2 * num_cu);
+    if (fits128 && a.Kp >= 512 && big * 4 >= rounds * 2 * num_cu * 3) return {128, 256, true};
+    auto one_round = [&](long long t, int per_cu) { return t > num_cu && t <= (long long)per_cu * num_cu; };
+    if (fits128 && one_round(tiles(128, 64), 2)) return {128, 64, true};
+    if (!fits128 && a.Cout > 64 && one_round(tiles(64, 128), 2) && tiles(64, 128) * 10 >= 13 * num_cu) return {64, 128, true};
+    if (a.Kp >= 512 && one_round(tiles(64, 64), fits128 ? 2 : 3)) return {64, 64, true};
+  }
   if (fits128 && tiles(128, 128) >= (a.Kp >= 1024 * k_scale ? num_cu / 4 : 5 * num_cu / 4)) return {128, 128};
   if (tiles(64, 128) >= (a.Kp >= 512 * k_scale ? num_cu / 4 : 9 * num_cu / 8)) return {64, 128};
   return {64, 64};
@@ -499,11 +594,18 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
     if (em != hipErrorNotSupported) return em;
   }
-  const GeneralTile st = general_tile(a, M_split, num_cu, 1);
-  const int ks = ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
+  const bool pipe_ok = sizeof(T) == 2 && !a.up_y;      // (only the split-K kernel writes an upsampled copy)
+  const GeneralTile st = general_tile(a, M_split, num_cu, 1, pipe_ok);
+  const int ks = st.pipe ? -1 : ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
   if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
   if (a.up_y) return hipErrorNotSupported;
-  const GeneralTile t = general_tile(a, M, num_cu, 1);
+  const GeneralTile t = general_tile(a, M, num_cu, 1, pipe_ok);
+  if constexpr (sizeof(T) == 2) {
+    if (t.pipe && t.bp == 256) return launch_cfg<T, 128, 256, 2, 2, 4, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);
+    if (t.pipe && t.bc == 128) return launch_cfg<T, 128, 64, 2, 2, 8, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);
+    if (t.pipe && t.bp == 128) return launch_cfg<T, 64, 128, 2, 2, 8, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);
+    if (t.pipe) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
+  }
   if (t.bc == 32) return launch_cfg<T, 32, 128, 1, 4, 4, 2, 4, true>(a, num_cu, s, kernel_id, tm);
   if (t.bp == 256) return launch_cfg<T, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
   if (t.bc == 128) return launch_cfg<T, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
@@ -556,7 +658,7 @@ hipError_t launch_general_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* 
 
 // kernel id of a conv tile configuration, decimal digits 1 BBB PPP K M V: channel tile, pixel tile, 16-byte vectors per
 // K step, workgroups per CU the registers are sized for, vectorised gather
-int conv_kernel_id(int bc, int bp, int kv, int minb, bool vec, bool dma) { return 1000000000 + bc * 1000000 + bp * 1000 + kv * 100 + minb * 10 + (vec ? 1 : 0) + (dma ? 2 : 0); }
+int conv_kernel_id(int bc, int bp, int kv, int minb, bool vec, bool dma, bool pipe) { return 1000000000 + bc * 1000000 + bp * 1000 + kv * 100 + minb * 10 + (vec ? 1 : 0) + (dma ? 2 : 0) + (pipe ? 4 : 0); }
 
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out) {
   const int vn = 16 / dtype_size(dtype);
