@@ -166,19 +166,22 @@ __global__ void crop_resize_kernel(const ResizeArgs a) {
   }
 }
 
-// Crop-resize with the source rows staged in LDS.  One wavefront (a 64-thread workgroup) produces one output row of
-// one ROI, 4 pixels per lane.  The two source rows it taps are first copied into LDS - only the span of pixels this
-// part of the row needs, with aligned 16-byte loads - and every lane then picks its taps from there.  Sampling
-// straight from global memory costs two 12-byte loads at arbitrary addresses per output pixel; for crops that are
-// enlarged or mildly reduced (the usual case: objects of 24-360 pixels to 224) neighbouring lanes hit the same few
-// cache lines over and over, and the kernel runs at the rate the L1 can look lines up, not at memory bandwidth.
+// Crop-resize with the source rows staged in LDS.  One wavefront (a 64-thread workgroup) produces a few consecutive output rows of
+// one ROI, 4 pixels per lane.  A source row is copied into LDS - only the span of pixels this part of the output row needs, with
+// aligned 16-byte loads -, every lane picks its taps from there and keeps the 12 horizontally interpolated values in registers
+// for as long as output rows tap that source row.  Sampling straight from global memory costs two 12-byte loads at arbitrary
+// addresses per output pixel; for crops that are enlarged or mildly reduced (the usual case: objects of 24-360 pixels to 224)
+// neighbouring lanes hit the same few cache lines over and over, and the kernel runs at the rate the L1 can look lines up.  With
+// the rows in LDS it is bound by vector arithmetic, about 100 instructions per pixel with both source rows of every output row
+// interpolated anew; an enlarged crop needs less than one new source row per output row (3617 crops to 224 x 224: 776 -> 449 us).
 // A span too long for the buffer (strong reduction: taps of neighbouring pixels share no lines anyway) is sampled
 // directly, as in the kernel above.  Same arithmetic, so the results are identical.
-constexpr int CROP_ROWBUF = 2048;     // bytes of LDS per staged source row
+constexpr int CROP_ROWBUF = 2048;     // bytes of LDS for the staged source row
+constexpr int CROP_ROWS = 8;          // most output rows of one ROI per wavefront
 
 template <typename T, bool C4>
 __global__ __launch_bounds__(64) void crop_resize_rows_kernel(const ResizeArgs a) {
-  __shared__ __attribute__((aligned(16))) uint8_t srow[2][CROP_ROWBUF];
+  __shared__ __attribute__((aligned(16))) uint8_t srow[CROP_ROWBUF];
   const int wq = a.dst_w / 4;
   int n_items = a.n;
   if (a.n_dyn) { int d = *a.n_dyn; n_items = d < a.n ? (d < 0 ? 0 : d) : a.n; }
@@ -190,21 +193,19 @@ __global__ __launch_bounds__(64) void crop_resize_rows_kernel(const ResizeArgs a
   // workgroups take consecutive rows, so the rows of one ROI are in flight together.  The grid is a multiple of 8.
   const unsigned die = blockIdx.x & 7u, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
   const unsigned die_rois = (unsigned)n_items > die ? ((unsigned)n_items - die + 7u) >> 3 : 0u;
-  const unsigned die_rows = die_rois * (unsigned)a.dst_h;                  // < 2^31 (checked by the launcher)
-  for (unsigned row = slot; row < die_rows; row += slots) {
-    const unsigned nth = fast_div(row, a.div_h);
+  // rows per wavefront: as many as leave every workgroup something to do
+  unsigned rows = die_rois * (unsigned)a.dst_h / slots;                    // < 2^31 (checked by the launcher)
+  rows = rows < 1u ? 1u : (rows > (unsigned)CROP_ROWS ? (unsigned)CROP_ROWS : rows);
+  const unsigned per_roi = ((unsigned)a.dst_h + rows - 1u) / rows;
+  for (unsigned u = slot; u < die_rois * per_roi; u += slots) {
+    const unsigned nth = u / per_roi;
     const int roi = (int)(die + 8u * nth);
-    const int y = (int)(row - nth * (unsigned)a.dst_h);
+    const int y0 = (int)((u - nth * per_roi) * rows), y1 = y0 + (int)rows < a.dst_h ? y0 + (int)rows : a.dst_h;
     const octo_roi r = a.rois[roi];
     const int fr = clampi(r.frame, 0, a.n_frames - 1);
     const uint8_t* base = a.frames[fr];
     const size_t pitch = a.pitches[fr];
-    const float sy = r.y1 + ((float)y + 0.5f) * ((r.y2 - r.y1) / (float)a.dst_h) - 0.5f;
-    const float y0f = floorf(sy);
-    const float fy = sy - y0f;
-    const int ya = clampi((int)y0f, 0, a.src_h - 1), yb = clampi((int)y0f + 1, 0, a.src_h - 1);
-    const uint8_t* rowp[2] = {base + (size_t)ya * pitch, base + (size_t)yb * pitch};
-    const float step = (r.x2 - r.x1) / (float)a.dst_w;
+    const float ystep = (r.y2 - r.y1) / (float)a.dst_h, step = (r.x2 - r.x1) / (float)a.dst_w;
     for (int xq0 = 0; xq0 < wq; xq0 += 64) {
       // source pixels this chunk of the row taps: the coordinate is monotonic in the output pixel, so the ends bound it
       const int pa = xq0 * 4, pb = (xq0 + 64 < wq ? xq0 + 64 : wq) * 4 - 1;
@@ -213,66 +214,88 @@ __global__ __launch_bounds__(64) void crop_resize_rows_kernel(const ResizeArgs a
       const int xhi = clampi((int)floorf(fmaxf(sa, sb)) + 1, 0, a.src_w - 1);
       const int span = (xhi - xlo + 1) * 3;
       const bool staged = span > 0 && span + 32 <= CROP_ROWBUF;
-      int koff[2] = {0, 0};                // LDS byte index of source pixel x in row rr: koff[rr] + 3 * x
-      if (staged) {
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-          const uint8_t* p0 = rowp[rr] + 3 * xlo;
-          const uint8_t* a0 = (const uint8_t*)((uintptr_t)p0 & ~(uintptr_t)15);
-          const int nvec = (int)((p0 + span - a0 + 15) >> 4);
-          const uint8_t* row_end = rowp[rr] + (size_t)a.src_w * 3;
-          for (int v = lane; v < nvec; v += 64) {
-            const uint8_t* va = a0 + 16 * v;
-            uint4 q;
-            if (va >= rowp[rr] && va + 16 <= row_end) {
-              q = *(const uint4*)va;
-            } else {
-              // first or last vector of the row: never touch bytes outside the row
-              alignas(16) uint8_t b[16];
-#pragma unroll
-              for (int e = 0; e < 16; ++e) b[e] = (va + e >= rowp[rr] && va + e < row_end) ? va[e] : (uint8_t)0;
-              q = *(const uint4*)b;
-            }
-            *(uint4*)&srow[rr][16 * v] = q;
-          }
-          koff[rr] = (int)(p0 - a0) - 3 * xlo;
-        }
-      }
-      __syncthreads();
       const int xq = xq0 + lane;
-      if (xq < wq) {
-        float v[12];
+      int xa[4], xb[4];
+      float fx[4];
+#pragma unroll
+      for (int px = 0; px < 4; ++px) {
+        const float sx = r.x1 + ((float)(xq * 4 + px) + 0.5f) * step - 0.5f;
+        const float x0f = floorf(sx);
+        fx[px] = sx - x0f;
+        xa[px] = clampi((int)x0f, 0, a.src_w - 1); xb[px] = clampi((int)x0f + 1, 0, a.src_w - 1);
+      }
+      // source row ys: staged, and interpolated at this lane's four pixels
+      auto interpolate = [&](int ys, float (&h)[12]) __attribute__((always_inline)) {
+        const uint8_t* rowp = base + (size_t)ys * pitch;
+        const uint8_t* p0 = rowp + 3 * xlo;
+        const uint8_t* a0 = (const uint8_t*)((uintptr_t)p0 & ~(uintptr_t)15);
+        const int nvec = (int)((p0 + span - a0 + 15) >> 4);
+        const uint8_t* row_end = rowp + (size_t)a.src_w * 3;
+        __syncthreads();                   // the row before has been read
+        for (int v = lane; v < nvec; v += 64) {
+          const uint8_t* va = a0 + 16 * v;
+          uint4 q;
+          if (va >= rowp && va + 16 <= row_end) {
+            q = *(const uint4*)va;
+          } else {
+            // first or last vector of the row: never touch bytes outside the row
+            alignas(16) uint8_t b[16];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) b[e] = (va + e >= rowp && va + e < row_end) ? va[e] : (uint8_t)0;
+            q = *(const uint4*)b;
+          }
+          *(uint4*)&srow[16 * v] = q;
+        }
+        __syncthreads();
+        const int koff = (int)(p0 - a0) - 3 * xlo;     // LDS byte index of source pixel x: koff + 3 * x
 #pragma unroll
         for (int px = 0; px < 4; ++px) {
-          const float sx = r.x1 + ((float)(xq * 4 + px) + 0.5f) * step - 0.5f;
-          const float x0f = floorf(sx);
-          const float fx = sx - x0f;
-          const int xa = clampi((int)x0f, 0, a.src_w - 1), xb = clampi((int)x0f + 1, 0, a.src_w - 1);
-          if (staged) {
-            float t[2][2][3];
+          int k = koff + 3 * xa[px];
+          k = k < 0 ? 0 : (k > CROP_ROWBUF - 12 ? CROP_ROWBUF - 12 : k);      // taps lie inside the span; non-finite boxes must not index outside the buffer
+          const uint32_t* w = (const uint32_t*)&srow[k & ~3];
+          const unsigned lo = __builtin_amdgcn_alignbyte(w[1], w[0], k & 3), hi = __builtin_amdgcn_alignbyte(w[2], w[1], k & 3);
+          const unsigned nx = xb[px] == xa[px] ? lo : __builtin_amdgcn_alignbyte(hi, lo, 3);
 #pragma unroll
-            for (int rr = 0; rr < 2; ++rr)
-#pragma unroll
-              for (int tp = 0; tp < 2; ++tp) {
-                int k = koff[rr] + 3 * (tp ? xb : xa);
-                k = k < 0 ? 0 : (k > CROP_ROWBUF - 8 ? CROP_ROWBUF - 8 : k);      // taps lie inside the span; non-finite boxes must not index outside the buffer
-                const uint32_t* w = (const uint32_t*)&srow[rr][k & ~3];
-                const unsigned u = (unsigned)((((unsigned long long)w[1] << 32) | w[0]) >> (8 * (k & 3)));
-                t[rr][tp][0] = (float)(u & 0xFFu); t[rr][tp][1] = (float)((u >> 8) & 0xFFu); t[rr][tp][2] = (float)((u >> 16) & 0xFFu);
-              }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              float top = (1.0f - fx) * t[0][0][c] + fx * t[0][1][c];
-              float bot = (1.0f - fx) * t[1][0][c] + fx * t[1][1][c];
-              v[3 * px + c] = ((1.0f - fy) * top + fy * bot) * a.scale[c] + a.bias[c];
-            }
-          } else {
-            bilinear_rgb(rowp[0], rowp[1], xa, xb, a.src_w, fx, fy, a.scale, a.bias, v + 3 * px);
-          }
+          for (int c = 0; c < 3; ++c)
+            h[3 * px + c] = (1.0f - fx[px]) * (float)((lo >> (8 * c)) & 0xFFu) + fx[px] * (float)((nx >> (8 * c)) & 0xFFu);
         }
-        store_pixels<T, 4, C4>(dst + (((size_t)roi * a.dst_h + y) * a.dst_w + (size_t)xq * 4) * (C4 ? 4 : 3), v);
+      };
+      int ra = -1, rb = -1;                // source rows behind ha and hb
+      float ha[12], hb[12];
+      for (int y = y0; y < y1; ++y) {
+        const float sy = r.y1 + ((float)y + 0.5f) * ystep - 0.5f;
+        const float y0f = floorf(sy);
+        const float fy = sy - y0f;
+        const int ya = clampi((int)y0f, 0, a.src_h - 1), yb = clampi((int)y0f + 1, 0, a.src_h - 1);
+        float v[12];
+        if (staged) {
+          if (ya != ra) {
+            if (ya == rb) {
+#pragma unroll
+              for (int i = 0; i < 12; ++i) ha[i] = hb[i];
+            } else {
+              interpolate(ya, ha);
+            }
+            ra = ya;
+          }
+          if (yb != rb) {
+            if (yb == ra) {
+#pragma unroll
+              for (int i = 0; i < 12; ++i) hb[i] = ha[i];
+            } else {
+              interpolate(yb, hb);
+            }
+            rb = yb;
+          }
+#pragma unroll
+          for (int i = 0; i < 12; ++i) v[i] = ((1.0f - fy) * ha[i] + fy * hb[i]) * a.scale[i % 3] + a.bias[i % 3];
+        } else if (xq < wq) {
+#pragma unroll
+          for (int px = 0; px < 4; ++px)
+            bilinear_rgb(base + (size_t)ya * pitch, base + (size_t)yb * pitch, xa[px], xb[px], a.src_w, fx[px], fy, a.scale, a.bias, v + 3 * px);
+        }
+        if (xq < wq) store_pixels<T, 4, C4>(dst + (((size_t)roi * a.dst_h + y) * a.dst_w + (size_t)xq * 4) * (C4 ? 4 : 3), v);
       }
-      __syncthreads();                   // the next chunk overwrites the staged rows
     }
   }
 }
