@@ -393,7 +393,7 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
  * + 2 if operands go straight to LDS, + 4 in the pipelined form; 15 00 BBB KKK: streaming 1x1 kernel, channel tile BBB, KKK input
  * channels; 160S BBB PPP: split-K kernel, K split over S wavefronts, channel tile BBB, pixel tile PPP; 14, 17 or 18
  * 0Q BBB CCC: 3x3 kernel with the input patch in LDS (17: more than 64 output channels, 18: up to 64, 14: input channels
- * not in whole slices), Q = 0 / 1 / 2 for tiles of 128 / 256 / 64 pixels, channel tile BBB, patch of CCC channels in LDS
+ * not in whole slices), Q = 0 / 1 / 2 / 3 for tiles of 128 / 256 / 64 / 128 pixels, channel tile BBB, patch of CCC channels in LDS
  * (two slices), Q = 5 for the form with resident weights; 19 0F BBB KK P: first-layer kernel, channel tile, kernel height, kernel width in pixel pairs,
  * F = 1 when it also computes the 3x3 / stride-2 max-pool that follows (that layer then reports kernel 0 and 0 ms);
  * 1 max-pool, 2 upsample, 3 channel copy, 4 add, 5 global average pool, 0 none), per ITEM dense FLOPs and activation

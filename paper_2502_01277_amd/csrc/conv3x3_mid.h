@@ -349,9 +349,9 @@ hipError_t launch_mid_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* ker
   if (tiles >= 0x7FFFFFF0LL || n_rows * a.W >= 0x7FFFFFFFLL) return hipErrorNotSupported;
   if ((long long)(gm.TH + 2) * a.W * a.x_ld * (int)sizeof(T) > 0x7FFFFFF0LL) return hipErrorNotSupported;     // 32-bit offsets inside a patch
   // digits FF Q BBB CCC: family (17: more than 64 output channels, 18: up to 64, 14: input channels not in whole slices), pixel tile
-  // (0: 128, 1: 256, 2: 64), channel tile, input channels whose patch the two buffers hold
+  // (0: 128, 1: 256, 2: 64, 3: 128 with a patch of five passes), channel tile, input channels whose patch the two buffers hold
   if (kernel_id)
-    *kernel_id = (a.Cin % (KV * Elem<T>::N) ? 1400000000 : (a.Cout > 64 ? 1700000000 : 1800000000)) + (BP == 128 ? 0 : (BP == 256 ? 1 : 2)) * 1000000 + BC * 1000 +
+    *kernel_id = (a.Cin % (KV * Elem<T>::N) ? 1400000000 : (a.Cout > 64 ? 1700000000 : 1800000000)) + (BP == 128 ? (MAXP == 5 ? 3 : 0) : (BP == 256 ? 1 : 2)) * 1000000 + BC * 1000 +
                  2 * KV * Elem<T>::N;
   long long grid = (tiles + 7) / 8 * 8;
   const long long cap = ((long long)num_cu * MINB + 7) / 8 * 8;
@@ -395,7 +395,17 @@ hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s,
   if (per_cu < 0.35) return hipErrorNotSupported;
   if (pad32 == pad64) {
     if (per_cu < 0.8) return launch_mid_cfg<T, 64, 64, 2, 8, 3, 4, 2>(a, num_cu, s, kernel_id, tm);
-    if (a.Cin >= 192 && per_cu < 6) return launch_mid_cfg<T, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+    if (a.Cin >= 192 && per_cu < 6) {
+      // tiles whose patch fits five passes of the loader (whole images of up to 14 columns) save the sixth, which would fetch
+      // nothing: 512 -> 512 on 200 x 7 x 7 51 us (56).  Same slices, so a running count may choose: 128 channels with plenty of
+      // tiles after all (512 -> 512 on 3600 x 7 x 7 729 us, 765)
+      MidGeom g5{}, g6{};
+      const bool five = mid_geometry(a, 64, 128, 160, &g5) && mid_geometry(a, 64, 128, 192, &g6) && g5.TH * g5.TW == g6.TH * g6.TW;
+      const double now = (double)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo / 128 * ((a.Cout + 63) / 64) / num_cu;
+      if (five && now >= 24 && a.Cout % 128 == 0) return launch_mid_cfg<T, 128, 128, 2, 8, 2, 5, 2>(a, num_cu, s, kernel_id, tm);
+      if (five) return launch_mid_cfg<T, 64, 128, 1, 8, 3, 5, 2>(a, num_cu, s, kernel_id, tm);
+      return launch_mid_cfg<T, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+    }
   }
   if ((a.Cout + 95) / 96 * 96 < (a.Cout + 63) / 64 * 64)
     return M / 256 * ((a.Cout + 95) / 96) >= 4 * num_cu ? launch_mid_cfg<T, 96, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm)
