@@ -53,27 +53,35 @@ def make_workload(name: str):
     return spec, scene, heads, desc
 
 
+# Template arguments of the 3x3 patch kernels that their id does not spell out.  By (pixel-tile digit, channel tile, vectors per LDS
+# row): wavefronts along the channels, stages of the weight ring, loader passes, workgroups per compute unit.
+MID = {(0, 32, 4): (1, 3, 3, 4), (0, 64, 4): (1, 3, 3, 4), (0, 64, 8): (1, 3, 6, 2), (0, 96, 4): (1, 3, 3, 3), (0, 128, 4): (1, 3, 3, 3),
+       (1, 64, 4): (1, 3, 6, 2), (1, 96, 4): (1, 3, 6, 2), (2, 64, 8): (2, 3, 4, 2), (3, 64, 8): (1, 3, 5, 2), (3, 128, 8): (2, 2, 5, 2)}
+# By (blocks of 32 channels, groups of 16 input channels): vectors per LDS row, loader passes, prefetch depth, workgroups per compute unit.
+STREAM3 = {(1, 2): (4, 6, 3, 2), (2, 2): (4, 3, 3, 3), (2, 3): (8, 6, 4, 2), (2, 4): (8, 6, 3, 2)}
+
+
 def conv_name(kid: int, dtype: str) -> str:
-    """Template instance behind a conv kernel id (digits 1 BBB PPP K M V), as rocprofv3 prints it."""
+    """Template instance behind a conv kernel id (csrc/kernel_ids.h), as rocprofv3 prints it; an id that is none of the library's is
+    named as such."""
     d = kid - 1000000000
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
-    if 500000000 <= d < 600000000:                       # streaming 1x1 kernel: digits BBB KKK (channel tile, input channels)
+    if 500000000 <= d < 600000000:                       # streaming 1x1 kernel
         return "octo::conv1x1_stream_kernel<%s, %d>" % (ctype, (d - 500000000) // 1000 // 32)
-    if 600000000 <= d < 700000000:                       # split-K kernel: digits S BBB PPP (K split, channel tile, pixel tile)
+    if 600000000 <= d < 700000000:                       # split-K kernel
         ks, bc, bp = (d - 600000000) // 1000000, (d // 1000) % 1000, d % 1000
         return "octo::conv_ksplit_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp // 32, ks, ks)
-    if 400000000 <= d < 500000000 or 700000000 <= d < 900000000:      # 3x3 kernel with the input patch in LDS: digits Q BBB CCC
-        q, kc = (d // 1000000) % 10, d % 1000 // 16
-        if q == 5:                                                     # its streaming form
-            wc = (d // 1000) % 1000 // 32
-            kv, passes = (4, 6 // wc) if kc == 2 else (8, 6)
-            return "octo::conv3x3_stream_kernel<%s, %d, %d, %d, %d, %d, %d>" % (ctype, wc, kc, kv, passes, 4 if kc == 3 else 3, 3 if wc == 2 and kc == 2 else 2)
-        bp, bc, kv = (128, 256, 64)[(d // 1000000) % 10], (d // 1000) % 1000, d % 1000 // (32 if dtype == "f8" else 16)
-        wc, passes = (2, 4) if bp == 64 else (1, bp * kv * 3 // 512)
-        minb = 2 if kv == 8 or bp == 256 else 3 if bc > 64 else 4
-        return "octo::conv3x3_mid_kernel<%s, %d, %d, %d, %d, 3, %d, %d>" % (ctype, bc, bp, wc, kv, passes, minb)
-    if d >= 900000000:                                   # first-layer kernel: digits BBB KK P
-        d -= 900000000                                   # F BBB KK P: F = 1 with the following max-pool fused
+    if 400000000 <= d < 500000000 or 700000000 <= d < 900000000:      # 3x3 kernels with the input patch in LDS: digits Q BBB CCC
+        q, bc, chan = (d // 1000000) % 100, (d // 1000) % 1000, d % 1000
+        rest = STREAM3.get((bc // 32, chan // 16)) if q == 5 else MID.get((q, bc, chan // (32 if dtype == "f8" else 16)))
+        if rest is None:
+            return "convolution kernel %d" % kid
+        if q == 5:                                       # its streaming form
+            return "octo::conv3x3_stream_kernel<%s, %d, %d, %d, %d, %d, %d>" % ((ctype, bc // 32, chan // 16) + rest)
+        return "octo::conv3x3_mid_kernel<%s, %d, %d, %d, %d, %d, %d, %d>" % (
+            (ctype, bc, (128, 256, 64, 128)[q], rest[0], chan // (32 if dtype == "f8" else 16)) + rest[1:])
+    if d >= 900000000:                                   # first-layer kernel
+        d -= 900000000                                   # F = 1 with the following max-pool fused
         return "octo::stem_conv_kernel<%s, %d, %d, %d, %s>" % (ctype, (d // 1000) % 1000, (d // 10) % 100, d % 10, "true" if d >= 1000000 else "false")
     bc, bp, kv, minb, v = d // 1000000, (d // 1000) % 1000, (d // 100) % 10, (d // 10) % 10, d % 10
     vec, dma, pipe = v & 1, (v >> 1) & 1, v >> 2

@@ -656,10 +656,6 @@ hipError_t launch_general_bf16(const ConvArgs& a, int num_cu, hipStream_t s, int
 hipError_t launch_general_f32(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 hipError_t launch_general_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 
-// kernel id of a conv tile configuration, decimal digits 1 BBB PPP K M V: channel tile, pixel tile, 16-byte vectors per
-// K step, workgroups per CU the registers are sized for, vectorised gather
-int conv_kernel_id(int bc, int bp, int kv, int minb, bool vec, bool dma, bool pipe) { return 1000000000 + bc * 1000000 + bp * 1000 + kv * 100 + minb * 10 + (vec ? 1 : 0) + (dma ? 2 : 0) + (pipe ? 4 : 0); }
-
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out) {
   const int vn = 16 / dtype_size(dtype);
   const int bk = 8 * vn;   // largest K step of any tile configuration

@@ -205,7 +205,7 @@ static hipError_t launch_stream_cfg(const ConvArgs& a, long long M, int num_cu, 
   const int per_die = num_cu * per_cu / 8;
   if (g.tiles_c > per_die) return hipErrorNotSupported;
   g.lanes = per_die / g.tiles_c;
-  if (kernel_id) *kernel_id = 1500000000 + 32 * TC * 1000 + a.Cin;
+  if (kernel_id) *kernel_id = stream1_kernel_id(TC, a.Cin);
   if (tm.start && tm.stop)
     hipExtLaunchKernelGGL((conv1x1_stream_kernel<T, TC>), dim3((unsigned)(8 * per_die)), dim3(64 * g.waves), (unsigned)lds, s, tm.start, tm.stop, 0, a, g);
   else

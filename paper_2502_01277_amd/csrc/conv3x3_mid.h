@@ -348,11 +348,7 @@ hipError_t launch_mid_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* ker
   if (tiles <= 0) return hipSuccess;
   if (tiles >= 0x7FFFFFF0LL || n_rows * a.W >= 0x7FFFFFFFLL) return hipErrorNotSupported;
   if ((long long)(gm.TH + 2) * a.W * a.x_ld * (int)sizeof(T) > 0x7FFFFFF0LL) return hipErrorNotSupported;     // 32-bit offsets inside a patch
-  // digits FF Q BBB CCC: family (17: more than 64 output channels, 18: up to 64, 14: input channels not in whole slices), pixel tile
-  // (0: 128, 1: 256, 2: 64, 3: 128 with a patch of five passes), channel tile, input channels whose patch the two buffers hold
-  if (kernel_id)
-    *kernel_id = (a.Cin % (KV * Elem<T>::N) ? 1400000000 : (a.Cout > 64 ? 1700000000 : 1800000000)) + (BP == 128 ? (MAXP == 5 ? 3 : 0) : (BP == 256 ? 1 : 2)) * 1000000 + BC * 1000 +
-                 2 * KV * Elem<T>::N;
+  if (kernel_id) *kernel_id = mid_kernel_id(BC, BP, KV, Elem<T>::N, MAXP, a.Cin, a.Cout);
   long long grid = (tiles + 7) / 8 * 8;
   const long long cap = ((long long)num_cu * MINB + 7) / 8 * 8;
   if (grid > cap) grid = cap;

@@ -239,8 +239,7 @@ hipError_t launch_stream3_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int*
   if (tiles >= 0x3FFFFFF0LL) return hipErrorNotSupported;
   // 32-bit offsets inside a tile
   if ((long long)(gm.TH + 2) * a.W * std::max(a.x_ld, std::max(a.y_ld, a.res ? a.res_ld : 0)) * 2 > 0x7FFFFFF0LL) return hipErrorNotSupported;
-  // digits as conv3x3_mid_kernel's, Q = 5
-  if (kernel_id) *kernel_id = (a.Cin % (KV * 8) ? 1400000000 : 1800000000) + 5000000 + WC * 32000 + KC * 16;
+  if (kernel_id) *kernel_id = stream3_kernel_id(WC, KC, KV, a.Cin);
   long long grid = (tiles + 7) / 8 * 8;
   const long long cap = ((long long)num_cu * MINB + 7) / 8 * 8;
   if (grid > cap) grid = cap;

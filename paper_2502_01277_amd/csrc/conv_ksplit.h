@@ -331,8 +331,6 @@ inline int ksplit_choose(const ConvArgs& a, long long M, int es, int bc, int bp,
   return pick;
 }
 
-inline int ksplit_kernel_id(int bc, int bp, int ks) { return 1600000000 + ks * 1000000 + bc * 1000 + bp; }
-
 template <typename T, int TC, int TP, int NW, int KS>
 static hipError_t launch_ksplit_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   constexpr int BC = 32 * TC, BP = 32 * TP * (NW / KS);

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/octo.h"
+#include "kernel_ids.h"
 
 namespace octo {
 
@@ -69,7 +70,6 @@ hipError_t launch_conv(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, 
 hipError_t launch_stem(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 // 1x1 layers of large maps with resident weights; hipErrorNotSupported when the layer does not fit it
 hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
-int conv_kernel_id(int bc, int bp, int kv, int minb, bool vec, bool dma = false, bool pipe = false);
 enum { KID_NONE = 0, KID_MAXPOOL = 1, KID_UPSAMPLE = 2, KID_COPY = 3, KID_ADD = 4, KID_GAP = 5 };
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out);
 

@@ -265,7 +265,6 @@ __global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a)
   }
 }
 
-int stem_kernel_id(int bc, int kh, int pkw, bool pool) { return 1900000000 + (pool ? 1000000 : 0) + bc * 1000 + kh * 10 + pkw; }
 
 template <typename T, int BC, int KH, int PKW, bool POOL>
 static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
