@@ -124,17 +124,21 @@ __global__ __launch_bounds__(256) void maxpool_rows_kernel(const PoolArgs a, int
 // taken in, so the results are those of three separate pools.  Bound by vector arithmetic and LDS: values of 16-bit types are
 // held as integers of the same order, so that a vector of eight takes four packed instructions per maximum (with
 // conversions to and from fp32 64 x 20 x 20 x 256 took 40 us).
-// Order-preserving integer of a 16-bit float: the magnitude bits of negative values are inverted.  NaN, which fmax ignores,
-// becomes the smallest integer; the inverse is the same function (and gives a NaN for it).
+// Order-preserving integer of a 16-bit float: the magnitude bits of negative values are inverted; the inverse is the same
+// function.  NaN takes the place of -inf (whose integer is ~inf) in all types, as in the separate pools, whose running maximum
+// starts at -inf and ignores NaN: a window of nothing but NaN gives -inf.
 typedef short short8v __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ short8v order_flip(short8v x) { return x ^ ((x >> 15) & (short)0x7FFF); }
 template <typename T> __device__ __forceinline__ uint4 pool_key(uint4 q) {
-  if constexpr (sizeof(T) == 4) return q;
+  if constexpr (sizeof(T) == 4) {
+    const float4 x = __builtin_bit_cast(float4, q);
+    return __builtin_bit_cast(uint4, make_float4(fmaxf(x.x, -INFINITY), fmaxf(x.y, -INFINITY), fmaxf(x.z, -INFINITY), fmaxf(x.w, -INFINITY)));
+  }
   const short inf = std::is_same<T, _Float16>::value ? 0x7C00 : 0x7F80;
   short8v x = __builtin_bit_cast(short8v, q);
   const short8v k = order_flip(x);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = (short)(x[e] & 0x7FFF) > inf ? (short)-32768 : k[e];
+  for (int e = 0; e < 8; ++e) x[e] = (short)(x[e] & 0x7FFF) > inf ? (short)~inf : k[e];
   return __builtin_bit_cast(uint4, x);
 }
 template <typename T> __device__ __forceinline__ uint4 pool_value(uint4 q) {

@@ -237,6 +237,47 @@ def test_stride_1_max_pools_walk_down_the_rows(octo, dtype, case):
     assert rel_err(got[-1], ref[-1]) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("h,w,c,k,n", [(20, 20, 256, 5, 64), (9, 31, 48, 3, 180), (13, 7, 24, 5, 3), (1, 5, 8, 5, 2), (31, 33, 8, 7, 2), (6, 1, 16, 3, 1), (50, 42, 8, 5, 2)])
+def test_three_chained_max_pools_in_one_launch(octo, dtype, h, w, c, k, n):
+    """Three chained stride-1 pools of one size run as one launch, each stage equal to the oracle's window maximum and to
+    the three separate launches bit for bit.  Sizes: one, two and four channel vectors per workgroup (the 16-bit types; fp32
+    has twice as many vectors), odd maps, one row or column, a window of 7 on a map that nearly fills the LDS, and a map that
+    does not fit it (separate launches).  Infinities and NaN are in the input, among them NaN over whole windows: NaN is
+    ignored, and a window of nothing else gives -inf."""
+    import torch
+
+    def build(B):
+        p1 = B.maxpool(0, k, 1, k // 2)
+        p2 = B.maxpool(p1, k, 1, k // 2)
+        p3 = B.maxpool(p2, k, 1, k // 2)
+        return B.conv(B.cat([p1, p2, p3]), 16, 1, 1, 0)
+    m = _model(dtype, (h, w), c, build, n)
+    rng = np.random.default_rng(31)
+    x = zoo.round_to_dtype(rng.uniform(-1, 1, (n, h, w, c)).astype(np.float32), dtype)
+    special = rng.random(x.shape)
+    x[special < 0.002] = np.inf
+    x[(special >= 0.002) & (special < 0.2)] = -np.inf
+    x[special > 0.8] = np.nan
+    x[:, :, :, 1] = np.nan                        # nothing but NaN in every window
+    x[0, :k, :k, 2] = np.nan                      # in some windows
+    dx = torch.from_numpy(x).to(octo.torch_dtype(dtype)).cuda()
+    spec = zoo.PipelineSpec("t", [small_root(dtype), m], [], 200.0, 32, 32, 1, 1)
+    got = {}
+    for keep in (1, 2):                           # every layer on its own; fused, with every buffer kept
+        P = octo.Pipeline(spec, keep_all_tensors=keep)
+        P.run_model_on(1, dx)
+        got[keep] = [P.get_tensor(1, t, n) for t in (1, 2, 3)]
+        fused = [int(v) for v in P.layer_info(1)[1][:3]]
+        assert fused == ([1, 0, 0] if keep == 2 and h * w * 32 <= 64 * 1024 else [1, 1, 1]), fused
+        P.close()
+    ref = np.where(np.isnan(x), -np.inf, x)
+    for st in range(3):
+        ref = nn.maxpool(ref, k, 1, k // 2).astype(np.float32)
+        assert np.array_equal(got[1][st], ref), st
+        assert np.array_equal(got[2][st], ref), st
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("case", [(40, 40, 96, 48, 48, 6), (23, 17, 64, 32, 96, 5), (80, 80, 192, 96, 96, 4), (9, 9, 384, 192, 192, 3), (12, 12, 48, 40, 24, 2)])
 def test_two_1x1_layers_of_one_input_in_one_launch(octo, dtype, case):
