@@ -498,13 +498,35 @@ def _st(st):
         raise OctoError(st, "stage call failed")
 
 
+def _order(stream, *scratch):
+    """Before a stage call on a stream that is not the current one: tensors come from the current stream's allocator, so the call
+    waits for what that stream has been given so far (fills of its outputs, earlier users of their memory), and memory of the
+    call's own scratch tensors is not handed out again before the call is done.  Returns the stream as a torch object, or None
+    where it is the current one.  Under capture of either stream the order is the caller's: a wait would join the two."""
+    if stream is None or _stream_ptr(stream) == _stream_ptr(None):
+        return None
+    t = _torch()
+    side = stream if isinstance(stream, t.cuda.Stream) else t.cuda.ExternalStream(_stream_ptr(stream))
+    here = t.cuda.current_stream()
+    if t.cuda.is_current_stream_capturing():
+        return None
+    with t.cuda.stream(side):
+        if t.cuda.is_current_stream_capturing():
+            return None
+    side.wait_stream(here)
+    for x in scratch:
+        x.record_stream(side)
+    return side
+
+
 def frame_tables(frames: Sequence, stream=None):
-    """Device tables (pointers, pitches) for a list of device uint8 frames, written on `stream`."""
+    """Device tables (pointers, pitches) for a list of device uint8 frames, written on `stream` for calls on that stream."""
     t = _torch()
     n = len(frames)
     table = t.empty((2, n), dtype=t.int64, device=frames[0].device)
     ptrs = (C.c_void_p * n)(*[f.data_ptr() for f in frames])
     pitches = (C.c_size_t * n)(*[f.stride(0) for f in frames])
+    _order(stream, table)
     _st(lib().octo_op_frame_table(ptrs, pitches, n, table.data_ptr(), _stream_ptr(stream)))
     return table[0], table[1]
 
@@ -535,6 +557,7 @@ def op_letterbox(frames: Sequence, dst_h, dst_w, dtype: str, scale=(1 / 255.0,) 
     n, (sh, sw) = len(frames), frames[0].shape[:2]
     out = t.empty((n, dst_h, dst_w, 3), dtype=torch_dtype(dtype), device=frames[0].device)
     sc = (C.c_float * 3)(*scale); bi = (C.c_float * 3)(*bias)
+    _order(stream)
     _st(lib().octo_op_letterbox(ptrs.data_ptr(), pitches.data_ptr(), n, sh, sw, out.data_ptr(), dst_h, dst_w, DTYPES[dtype],
                                 sc, bi, pad_value, _stream_ptr(stream)))
     return out
@@ -556,6 +579,7 @@ def op_crop_resize(frames: Sequence, rois: np.ndarray, out_h, out_w, dtype: str,
     if len(rois) < cap:
         out[len(rois):].zero_()
     sc = (C.c_float * 3)(*scale); bi = (C.c_float * 3)(*bias)
+    _order(stream, d)
     _st(lib().octo_op_crop_resize(ptrs.data_ptr(), pitches.data_ptr(), len(frames), sh, sw, d_rois.data_ptr(), d_n.data_ptr(), cap,
                                   out.data_ptr(), out_h, out_w, DTYPES[dtype], sc, bi, _stream_ptr(stream)))
     return out
@@ -579,6 +603,7 @@ def op_decode(m: zoo.ModelSpec, heads: Sequence, cap=None, stream=None):
     cap = cap or m.n_cand()
     cand, count = _zeros(heads[0].device, ((n, cap, 32), t.uint8), ((n,), t.int32))
     hp = (C.c_void_p * len(heads))(*[int(h.data_ptr()) for h in heads])
+    _order(stream)
     _st(lib().octo_op_decode(C.byref(d), hp, n, cand.data_ptr(), count.data_ptr(), cap, _stream_ptr(stream)))
     return cand, count
 
@@ -606,6 +631,7 @@ def op_topk(cand, count, k: int, stream=None):
     n, in_cap = int(cand.shape[0]), int(cand.shape[1])
     k_cap = (k + 63) // 64 * 64
     out, oc = _zeros(cand.device, ((n, k_cap, 32), t.uint8), ((n,), t.int32))
+    _order(stream)
     _st(lib().octo_op_topk(cand.data_ptr(), count.data_ptr(), in_cap, n, k, out.data_ptr(), oc.data_ptr(), k_cap, _stream_ptr(stream)))
     return out, oc
 
@@ -615,6 +641,7 @@ def op_nms(top, top_count, iou_thr: float, max_det: int, stream=None):
     n, k_cap = int(top.shape[0]), int(top.shape[1])
     scratch = t.empty(max(8, lib().octo_op_nms_scratch_bytes(n, k_cap)), dtype=t.uint8, device=top.device)
     keep, nk = _zeros(top.device, ((n, max_det), t.int32), ((n,), t.int32))
+    _order(stream, scratch)
     _st(lib().octo_op_nms(top.data_ptr(), top_count.data_ptr(), k_cap, n, iou_thr, max_det, scratch.data_ptr(),
                           keep.data_ptr(), nk.data_ptr(), _stream_ptr(stream)))
     return keep, nk
@@ -641,9 +668,12 @@ def op_compact(top, keep, n_keep, src_hw, in_hw, class_mask: int, cap: int, stre
     buf[at[2]:at[3]].fill_(255)                                                       # roi_of: -1
     base = buf.data_ptr()
     cm = (C.c_uint64 * 2)(class_mask & ((1 << 64) - 1), (class_mask >> 64) & ((1 << 64) - 1))
+    side = _order(stream, buf)
     _st(lib().octo_op_compact(top.data_ptr(), k_cap, keep.data_ptr(), n_keep.data_ptr(), max_det, n, src_hw[0], src_hw[1],
                               in_hw[0], in_hw[1], cm, base, base + at[4], cap, base + at[2],
                               base + at[5], base + at[1], base + at[3], _stream_ptr(stream)))
+    if side is not None:
+        t.cuda.current_stream().wait_stream(side)
     h = buf[:at[5]].cpu().numpy()
     part = lambda k: h[at[k]:at[k + 1]]   # noqa: E731
     r = part(0).view(ROI_DTYPE)[:int(part(4).view(np.int32)[0])].copy()
