@@ -147,7 +147,7 @@ EXPORTS = [
     "octo_plan_pipeline", "octo_to_edge", "octo_scaler_create", "octo_scaler_observe", "octo_scaler_destroy", "octo_run_model",
     "octo_executor_create", "octo_executor_serve", "octo_executor_stats", "octo_executor_scale_events", "octo_executor_streams",
     "octo_executor_results", "octo_executor_last_error", "octo_executor_destroy", "octo_profile_layers", "octo_set_layer_timing", "octo_get_layer_info", "octo_set_stage_timing", "octo_get_stage_ms",
-    "octo_debug_get_tensor", "octo_debug_tensor_shape", "octo_debug_set_head", "octo_debug_run_model",
+    "octo_debug_get_tensor", "octo_debug_tensor_shape", "octo_debug_set_head", "octo_debug_get_launch_counts", "octo_debug_run_model",
     "octo_debug_get_detections", "octo_debug_get_rois", "octo_debug_get_labels", "octo_letterbox_geometry", "octo_op_frame_table", "octo_op_letterbox",
     "octo_op_crop_resize", "octo_op_decode", "octo_op_topk", "octo_op_nms", "octo_op_nms_scratch_bytes", "octo_op_nms_static", "octo_op_compact", "octo_probe_copy", "octo_probe_mfma",
     "octo_op_conv", "octo_op_conv_packed_bytes", "octo_op_conv_padded_cout", "octo_op_conv_pack", "octo_quantize_e4m3", "octo_dequantize_e4m3",
@@ -215,6 +215,7 @@ def lib() -> C.CDLL:
         L.octo_debug_get_tensor.argtypes = [vp, i32, i32, i32, i32, vp, C.c_size_t]
         L.octo_debug_tensor_shape.argtypes = [vp, i32, i32, vp, vp, vp]
         L.octo_debug_set_head.argtypes = [vp, i32, i32, vp]
+        L.octo_debug_get_launch_counts.argtypes = [vp, vp, vp, vp]
         L.octo_debug_run_model.argtypes = [vp, i32, vp, i32, vp]
         L.octo_debug_get_detections.argtypes = [vp, i32, i32, vp, vp, i32, vp, vp, i32, vp]
         L.octo_debug_get_rois.argtypes = [vp, i32, vp, i32, vp]
@@ -435,6 +436,12 @@ class Pipeline:
 
     def set_head(self, model: int, level: int, tensor):
         self._check(self.L.octo_debug_set_head(self.h, model, level, None if tensor is None else int(tensor.data_ptr())))
+
+    def launch_counts(self):
+        """(enqueued, replayed, recorded): executions of models by run(), and recordings made."""
+        v = [C.c_int64() for _ in range(3)]
+        self._check(self.L.octo_debug_get_launch_counts(self.h, *[C.byref(x) for x in v]))
+        return tuple(int(x.value) for x in v)
 
     def run_model_on(self, model: int, x, stream=None):
         self._check(self.L.octo_debug_run_model(self.h, model, int(x.data_ptr()), int(x.shape[0]), _stream_ptr(stream)))

@@ -191,6 +191,7 @@ struct PublishArgs {
   const char* src; char* dst;              // result block on the device, its mirror in host memory
   int header_bytes;                        // counters in front of the boxes (a multiple of 16)
   const int* n_keep; int max_det; int n;
+  unsigned* done; unsigned number;         // host memory: the number of the batch is written there
 };
 hipError_t launch_publish(const PublishArgs& a, hipStream_t s);
 

@@ -10,6 +10,8 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -20,7 +22,25 @@ using namespace octo;
 namespace {
 
 thread_local std::string g_create_error;
-std::atomic<int> g_busy_pipelines{0};     // pipelines of this process with a batch in flight
+
+// What a pipeline has running on its GPU, for the other pipelines of the process to see (gpu_is_shared): batches whose last
+// launch has been enqueued, and the last of them that has run, which the publish kernel writes to pinned host memory.  A batch
+// that has run but was not collected yet does not count, nor does one on another GPU.
+struct Presence {
+  int device = -1;
+  std::atomic<unsigned> launched{0};
+  volatile unsigned* done = nullptr;       // host address
+  unsigned* done_dev = nullptr;            // the address kernels write to
+};
+std::mutex g_presence_mutex;
+std::vector<const Presence*> g_presence;
+
+bool gpu_is_shared(const Presence& me) {
+  std::lock_guard<std::mutex> lock(g_presence_mutex);
+  for (const Presence* q : g_presence)
+    if (q != &me && q->device == me.device && (int)(q->launched.load(std::memory_order_relaxed) - *q->done) > 0) return true;
+  return false;
+}
 
 struct Arena {
   char* base = nullptr;   // nullptr: sizing pass
@@ -170,9 +190,10 @@ struct octo_pipeline {
   hipStream_t capture_stream = nullptr;
   unsigned long long graph_clock = 0;
   int heads_version = 0;
-  bool counted_busy = false;       // counted in g_busy_pipelines: a batch is in flight
-  bool overlapped = false;         // another pipeline had a batch in flight beside this one's last batch
+  Presence presence;
+  bool overlapped = false;         // another pipeline was using the GPU when this one's last batch was collected
   bool graphs_off = false;
+  long long n_enqueued = 0, n_replayed = 0, n_recorded = 0;      // executions of models by octo_run; recordings made
   int next_slot = 0;
   bool stage_timing = false, layer_timing = false;
   std::vector<float> last_stage_ms;
@@ -768,13 +789,6 @@ hipEvent_t get_event(octo_pipeline* p) {
   return e;
 }
 
-// keeps g_busy_pipelines right after the list of batches in flight has changed
-void note_busy(octo_pipeline* p) {
-  const bool busy = !p->inflight.empty();
-  if (busy != p->counted_busy) g_busy_pipelines.fetch_add(busy ? 1 : -1, std::memory_order_relaxed);
-  p->counted_busy = busy;
-}
-
 // an event that marks the end of a batch: no timing, so that recording it costs the stream nothing but the signal
 hipEvent_t get_done_event(octo_pipeline* p) {
   if (!p->done_pool.empty()) { hipEvent_t e = p->done_pool.back(); p->done_pool.pop_back(); return e; }
@@ -824,14 +838,12 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched, bool who
   b.t_launch = octo_now_ms();
   b.model_ran.assign(p->models.size(), false);
   p->inflight.push_back(std::move(b));
-  note_busy(p);
   // If enqueueing fails half-way, the batch is withdrawn again: its frames stay queued (a later run forms the batch anew;
   // whatever part was enqueued only wrote this pipeline's own buffers), and the handle stays usable.
   const octo_status st = enqueue_batch(p, s, n, whole);
   if (st != OCTO_OK) {
     give_back(p->inflight.back());
     p->inflight.pop_back();
-    note_busy(p);
     *launched = 0;
     return st;
   }
@@ -855,13 +867,12 @@ octo_status enqueue_models(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
 // the GPU - while one batch's 110 launches are enqueued, the GPU waits for the next pipeline's (four instances of the
 // traffic cascade: 3.52 -> 3.21 ms for a batch of each).  A pipeline alone on the GPU is faster without (2 % here): its
 // launches are enqueued faster than they run, and nothing of a graph runs before all of it has been handed over.  So a
-// graph is used while another pipeline has a batch in flight, or had one beside this pipeline's previous batch.  A
+// graph is used while another pipeline has work on the same GPU, or had when this pipeline's previous batch was collected.  A
 // sequence is recorded the second time it is needed; whatever goes wrong while recording only switches recording off.
 // False: not available, nothing was enqueued.
 bool launch_graph(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
   const int exec_bz = p->models[0].exec_bz;
-  const bool shared = p->overlapped || g_busy_pipelines.load(std::memory_order_relaxed) > (p->counted_busy ? 1 : 0);
-  if (!shared || p->graphs_off || p->stage_timing || p->layer_timing || (exec_bz > 0 && exec_bz < n)) return false;
+  if (!(p->overlapped || gpu_is_shared(p->presence)) || p->graphs_off || p->stage_timing || p->layer_timing || (exec_bz > 0 && exec_bz < n)) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return false; }
   GraphKey key;
@@ -893,6 +904,7 @@ bool launch_graph(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
     }
     if (graph) hipGraphDestroy(graph);
     if (!ok) { g->exec = nullptr; p->graphs_off = true; (void)hipGetLastError(); return false; }
+    ++p->n_recorded;
   }
   if (hipGraphLaunch(g->exec, s) != hipSuccess) { p->graphs_off = true; (void)hipGetLastError(); return false; }
   return true;
@@ -935,7 +947,8 @@ octo_status enqueue_batch(octo_pipeline* p, hipStream_t s, int n, bool whole) {
   }
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
   if (whole) {
-    if (launch_graph(p, B, s, n)) return OCTO_OK;
+    if (launch_graph(p, B, s, n)) { p->n_replayed += 1 + (long long)p->edges.size(); return OCTO_OK; }
+    p->n_enqueued += 1 + (long long)p->edges.size();
     return enqueue_models(p, B, s, n);
   }
   const octo_status st = enqueue_root(p, B, s, n);
@@ -1017,8 +1030,10 @@ octo_status finalize_batch(octo_pipeline* p, Batch& B, hipStream_t s, bool cross
     HIPCHK(p, hipStreamWaitEvent(s, p->ev_det, 0));
     for (int e = 0; e < (int)p->edges.size(); ++e) HIPCHK(p, hipStreamWaitEvent(s, p->ev_child[e], 0));
   }
-  PublishArgs pa{p->d_result, p->h_result_dev[B.slot], (int)p->off_boxes, root.n_keep, root.d.max_det, B.n};
+  const unsigned number = p->presence.launched.load(std::memory_order_relaxed) + 1;
+  PublishArgs pa{p->d_result, p->h_result_dev[B.slot], (int)p->off_boxes, root.n_keep, root.d.max_det, B.n, p->presence.done_dev, number};
   HIPCHK(p, launch_publish(pa, s));
+  p->presence.launched.store(number, std::memory_order_relaxed);
   HIPCHK(p, hipEventRecord(B.done, s));
   B.finalized = true;
   return OCTO_OK;
@@ -1055,6 +1070,13 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
   if (st == OCTO_OK) {
     int dev = 0; hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) p->num_cu = prop.multiProcessorCount;
+    p->presence.device = dev;
+    void* word = nullptr;
+    if (hipHostMalloc(&word, 64, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+        hipHostGetDevicePointer((void**)&p->presence.done_dev, word, 0) != hipSuccess)
+      st = fail(p, OCTO_ENOMEM, "pinned host allocation failed");
+    p->presence.done = (volatile unsigned*)word;
+    if (word) *p->presence.done = 0;
     for (int r = 0; r < RING && st == OCTO_OK; ++r) {
       if (hipHostMalloc((void**)&p->h_result[r], p->result_bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
           hipHostGetDevicePointer((void**)&p->h_result_dev[r], p->h_result[r], 0) != hipSuccess)
@@ -1066,6 +1088,14 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
       if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) st = fail(p, OCTO_EHIP, "hipEventCreate failed");
       else p->ev_child.push_back(ev);
     }
+    if (st == OCTO_OK) {
+      try {
+        std::lock_guard<std::mutex> lock(g_presence_mutex);
+        g_presence.push_back(&p->presence);
+      } catch (const std::bad_alloc&) {
+        st = fail(p, OCTO_ENOMEM, "host allocation failed");
+      }
+    }
   }
   if (st != OCTO_OK) { g_create_error = p->err; octo_pipeline_destroy(p); return st; }
   *out = p;
@@ -1074,7 +1104,10 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
 
 octo_status octo_pipeline_destroy(octo_pipeline* p) {
   if (!p) return OCTO_EINVAL;
-  if (p->counted_busy) g_busy_pipelines.fetch_add(-1, std::memory_order_relaxed);
+  {
+    std::lock_guard<std::mutex> lock(g_presence_mutex);
+    g_presence.erase(std::remove(g_presence.begin(), g_presence.end(), &p->presence), g_presence.end());
+  }
   for (Batch& b : p->inflight) {
     if (b.done) { hipEventSynchronize(b.done); hipEventDestroy(b.done); }
     for (hipEvent_t e : b.stage_ev) hipEventDestroy(e);
@@ -1088,6 +1121,7 @@ octo_status octo_pipeline_destroy(octo_pipeline* p) {
   if (p->ev_det) hipEventDestroy(p->ev_det);
   for (hipEvent_t e : p->ev_child) hipEventDestroy(e);
   for (int r = 0; r < RING; ++r) if (p->h_result[r]) hipHostFree(p->h_result[r]);
+  if (p->presence.done) hipHostFree((void*)p->presence.done);
   delete p;
   return OCTO_OK;
 }
@@ -1239,9 +1273,8 @@ octo_status octo_collect(octo_pipeline* p, octo_frame_result* frames, int32_t fr
       for (hipEvent_t e : le) p->event_pool.push_back(e);
     }
     p->done_pool.push_back(B.done);
-    p->overlapped = g_busy_pipelines.load(std::memory_order_relaxed) > 1;
+    p->overlapped = gpu_is_shared(p->presence);
     p->inflight.pop_front();
-    note_busy(p);
   }
   if (p->inflight.empty()) {
     for (hipGraphExec_t g : p->retired) hipGraphExecDestroy(g);
@@ -1386,6 +1419,13 @@ octo_status octo_debug_set_head(octo_pipeline* p, int32_t model, int32_t level, 
     return fail(p, OCTO_EINVAL, "bad model or level");
   p->models[model].head_override[level] = d_head;
   ++p->heads_version;
+  return OCTO_OK;
+}
+
+octo_status octo_debug_get_launch_counts(octo_pipeline* p, int64_t* enqueued, int64_t* replayed, int64_t* recorded) {
+  if (!p) return OCTO_EINVAL;
+  if (!enqueued || !replayed || !recorded) return fail(p, OCTO_EINVAL, "bad arguments");
+  *enqueued = p->n_enqueued; *replayed = p->n_replayed; *recorded = p->n_recorded;
   return OCTO_OK;
 }
 

@@ -604,6 +604,7 @@ __global__ __launch_bounds__(256) void publish_kernel(const PublishArgs a) {
   const uint4* s = (const uint4*)(a.src + off);
   uint4* d = (uint4*)(a.dst + off);
   for (int i = threadIdx.x; i < nk * (int)(sizeof(octo_box) / 16); i += blockDim.x) d[i] = s[i];
+  if (item == 0 && threadIdx.x == 0) *a.done = a.number;
 }
 
 hipError_t launch_publish(const PublishArgs& a, hipStream_t s) {

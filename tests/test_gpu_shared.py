@@ -8,6 +8,45 @@ from paper_2502_01277_amd import synth, zoo
 pytestmark = pytest.mark.gpu
 
 
+def _spec_and_batches(octo, frames, counts, seed, size=(1080, 1920)):
+    """The traffic cascade for up to `frames` frames, and per entry of `counts` (objects per frame) a batch's frames and heads."""
+    import torch
+    spec = zoo.traffic_cascade("f16", det_batch=frames, max_rois_per_frame=24)
+    spec.src_h, spec.src_w = size
+    det = spec.models[0]
+    rng = np.random.default_rng(zoo.SEED0 + seed)
+    sets = []
+    for c in counts:
+        scene = synth.make_scene(rng, frames, *size, c, 24, 360, log_uniform=True)
+        heads = synth.planted_heads(rng, det, scene, *size, octo.letterbox_geometry(*size, det.in_h, det.in_w))
+        sets.append(([torch.from_numpy(f).cuda() for f in scene.frames], [octo.to_device(h, det.dtype) for h in heads]))
+    return spec, sets
+
+
+def _plant(P, heads):
+    for l, h in enumerate(heads):
+        P.set_head(0, l, h)
+
+
+def test_an_uncollected_batch_elsewhere_is_no_work_on_the_gpu(octo):
+    import torch
+    spec, [(frames, heads)] = _spec_and_batches(octo, 2, [[3, 5]], 79)
+    idle, P = octo.Pipeline(spec), octo.Pipeline(spec)
+    for q in (idle, P):
+        _plant(q, heads)
+    idle.submit(frames)
+    idle.run()
+    torch.cuda.synchronize()
+    for _ in range(6):
+        P.submit(frames)
+        P.run()
+        want = P.collect()[1].tobytes()
+    assert P.launch_counts() == (18, 0, 0)
+    assert idle.collect()[1].tobytes() == want
+    idle.close()
+    P.close()
+
+
 def test_replayed_batches_equal_batches_alone(octo):
     import torch
     spec = zoo.traffic_cascade("f16", det_batch=4, max_rois_per_frame=12)
