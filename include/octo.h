@@ -430,7 +430,7 @@ octo_status octo_debug_tensor_shape(octo_pipeline* p, int32_t model, int32_t ten
 octo_status octo_debug_set_head(octo_pipeline* p, int32_t model, int32_t level, const void* d_head);
 /* How octo_run has started the models of its batches since create: *enqueued launch by launch, *replayed from a recording of
  * those launches; *recorded counts the recordings made.  (While pipelines share a GPU, launches that come up again are recorded
- * and replayed.  Results are the same.) */
+ * in octo_collect's waits and replayed.  Results are the same.) */
 octo_status octo_debug_get_launch_counts(octo_pipeline* p, int64_t* enqueued, int64_t* replayed, int64_t* recorded);
 /* Run one model on a caller-provided dense input [n][in_h][in_w][in_c] (device, model's type). */
 octo_status octo_debug_run_model(octo_pipeline* p, int32_t model, const void* d_input, int32_t n, void* hip_stream);

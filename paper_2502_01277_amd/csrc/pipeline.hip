@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
@@ -101,6 +102,14 @@ struct TensorPlan {
   void* ptr = nullptr;     // root buffer base
 };
 
+// The launches of one model in a batch, recorded as a graph.  They depend on one number, the key of the map that holds the
+// recordings (root model: frames of the batch; child: items_hint), and on settings whose change drops the recordings.
+struct Recording {
+  int seen = 0;                            // batches that would have used it before it was made
+  hipGraphExec_t exec = nullptr;
+  unsigned used = 0;                       // number of the last batch that used it
+};
+
 struct ModelPlan {
   octo_model_desc d{};
   std::string name;
@@ -127,6 +136,9 @@ struct ModelPlan {
   // classifier
   int* labels = nullptr;   // also used by detector children (label = number of kept boxes)
   int n_logits = 0;
+  // recorded launches (replay)
+  std::map<int, Recording> recordings;
+  int record_key = -1;                     // the recording to make when the host next waits (-1: none)
 };
 
 struct Batch {
@@ -142,22 +154,11 @@ struct Batch {
   std::vector<bool> model_ran;
 };
 
-// The launches of one whole batch between the frame table and the results, recorded once and replayed as a graph: the
-// sequence depends only on this key.
-struct GraphKey {
-  int n = 0, heads = 0, hint[OCTO_MAX_EDGES]{};
-  bool operator==(const GraphKey& o) const {
-    bool same = n == o.n && heads == o.heads;
-    for (int e = 0; e < OCTO_MAX_EDGES; ++e) same = same && hint[e] == o.hint[e];
-    return same;
-  }
-};
-struct GraphEntry { GraphKey key; hipGraphExec_t exec = nullptr; unsigned long long used = 0; };
-
 struct QueuedFrame { const void* ptr; size_t pitch; double arrival; int64_t id; };
 
 constexpr int RING = 8;
-constexpr size_t MAX_GRAPHS = 8;
+constexpr int MAX_GRAPHS = 16;              // recordings of a model
+constexpr unsigned GRAPH_IDLE = 256;        // batches after which an unused recording may make room for another
 constexpr int CNT_STRIDE = 32;   // candidate counters sit 128 bytes apart: same-line atomics serialise in L2
 
 }  // namespace
@@ -183,14 +184,11 @@ struct octo_pipeline {
   std::deque<QueuedFrame> queue;
   std::deque<Batch> inflight;
   std::vector<hipEvent_t> event_pool, done_pool;      // with timing; without
-  // recorded launch sequences: at most MAX_GRAPHS, the least recently used one makes room; one that may still be running
-  // waits in `retired` until nothing is in flight
-  std::vector<GraphEntry> graphs;
-  std::vector<hipGraphExec_t> retired;
+  // recorded launches: dropped recordings may still be running and are destroyed once the batches up to a number are collected
+  std::vector<std::pair<unsigned, hipGraphExec_t>> retired;
   hipStream_t capture_stream = nullptr;
-  unsigned long long graph_clock = 0;
-  int heads_version = 0;
   Presence presence;
+  unsigned collected = 0;          // batches collected
   bool overlapped = false;         // another pipeline was using the GPU when this one's last batch was collected
   bool graphs_off = false;
   long long n_enqueued = 0, n_replayed = 0, n_recorded = 0;      // executions of models by octo_run; recordings made
@@ -856,58 +854,117 @@ octo_status start_batch(octo_pipeline* p, hipStream_t s, int* launched, bool who
 octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool own_stream);
 octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n);
 
-// All launches of a whole batch after the frame table, one after the other on `s`.
-octo_status enqueue_models(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
-  octo_status st = enqueue_root(p, B, s, n);
-  for (int e = 0; e < (int)p->edges.size() && st == OCTO_OK; ++e) st = run_child(p, B, e, s, false);
-  return st;
-}
-
-// The same from a recorded graph: 0.9 us of host time per launch instead of 2.6.  That pays where several pipelines share
-// the GPU - while one batch's 110 launches are enqueued, the GPU waits for the next pipeline's (four instances of the
-// traffic cascade: 3.52 -> 3.21 ms for a batch of each).  A pipeline alone on the GPU is faster without (2 % here): its
-// launches are enqueued faster than they run, and nothing of a graph runs before all of it has been handed over.  So a
-// graph is used while another pipeline has work on the same GPU, or had when this pipeline's previous batch was collected.  A
-// sequence is recorded the second time it is needed; whatever goes wrong while recording only switches recording off.
-// False: not available, nothing was enqueued.
-bool launch_graph(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
+// ---- recorded launches ---------------------------------------------------------
+// Replaying a model's launches from a graph takes 0.9 us of host time per launch instead of 2.6.  That pays where several
+// pipelines share the GPU and the host is behind: while one batch's 110 launches are enqueued, the GPU waits for the next
+// pipeline's (traffic cascade, 8 frames, four instances, a batch of each and then the results: 3.44 -> 3.12 ms; with two batches of
+// each in flight 0.72 ms a batch either way, with 1 .. 8 frames a batch 0.50).  A pipeline alone on the GPU is faster without
+// (2 % here): its launches are enqueued faster than they run, and nothing of a graph runs before all of it has been handed
+// over.  So recordings are used while another pipeline has work on the same GPU, or had when this pipeline's previous
+// batch was collected.
+// A recording is made once its key has come up twice, and not in the call that serves a batch but while octo_collect waits for
+// one (a caller that only polls keeps enqueueing).  One graph per model: with one per batch, twelve batch sizes times a few item
+// counts of each child were more sequences than could be kept.
+bool replay_wanted(octo_pipeline* p, hipStream_t s, int n) {
   const int exec_bz = p->models[0].exec_bz;
-  if (!(p->overlapped || gpu_is_shared(p->presence)) || p->graphs_off || p->stage_timing || p->layer_timing || (exec_bz > 0 && exec_bz < n)) return false;
+  if (p->graphs_off || p->stage_timing || p->layer_timing || (exec_bz > 0 && exec_bz < n)) return false;
+  if (!p->overlapped && !gpu_is_shared(p->presence)) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return false; }
-  GraphKey key;
-  key.n = n; key.heads = p->heads_version;
-  for (size_t e = 0; e < p->edges.size(); ++e) key.hint[e] = p->models[p->edges[e].child].items_hint;
-  GraphEntry* g = nullptr;
-  for (GraphEntry& x : p->graphs) if (x.key == key) g = &x;
-  if (!g) {
-    if (p->graphs.size() >= MAX_GRAPHS) {
-      auto old = std::min_element(p->graphs.begin(), p->graphs.end(), [](const GraphEntry& a, const GraphEntry& b) { return a.used < b.used; });
-      if (old->exec) p->retired.push_back(old->exec);
-      p->graphs.erase(old);
-    }
-    GraphEntry x;
-    x.key = key; x.used = ++p->graph_clock;
-    p->graphs.push_back(x);
+  return true;
+}
+
+// False: there is no recording for the key (yet), nothing was enqueued.
+bool replay(octo_pipeline* p, ModelPlan& m, int key, hipStream_t s) {
+  Recording& r = m.recordings[key];
+  r.used = p->presence.launched.load(std::memory_order_relaxed);
+  if (!r.exec) {
+    if (++r.seen >= 2) m.record_key = key;
     return false;
   }
-  g->used = ++p->graph_clock;
-  if (!g->exec) {
-    hipGraph_t graph = nullptr;
-    bool ok = p->capture_stream || hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking) == hipSuccess;
-    if (ok && hipStreamBeginCapture(p->capture_stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-      ok = enqueue_models(p, B, p->capture_stream, n) == OCTO_OK;
-      ok = hipStreamEndCapture(p->capture_stream, &graph) == hipSuccess && ok && graph;
-      ok = ok && hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0) == hipSuccess;
-    } else {
-      ok = false;
-    }
-    if (graph) hipGraphDestroy(graph);
-    if (!ok) { g->exec = nullptr; p->graphs_off = true; (void)hipGetLastError(); return false; }
-    ++p->n_recorded;
-  }
-  if (hipGraphLaunch(g->exec, s) != hipSuccess) { p->graphs_off = true; (void)hipGetLastError(); return false; }
+  if (hipGraphLaunch(r.exec, s) != hipSuccess) { p->graphs_off = true; (void)hipGetLastError(); return false; }
+  ++p->n_replayed;
   return true;
+}
+
+void retire(octo_pipeline* p, Recording& r) {
+  if (r.exec) p->retired.push_back({p->presence.launched.load(std::memory_order_relaxed), r.exec});
+  r.exec = nullptr;
+  r.seen = 0;
+}
+
+// after a change of anything but the key that the launches depend on
+void drop_recordings(octo_pipeline* p, ModelPlan& m) {
+  for (auto& kr : m.recordings) retire(p, kr.second);
+  m.recordings.clear();
+  m.record_key = -1;
+}
+
+// Whatever goes wrong while recording only switches recording off.
+void record(octo_pipeline* p, int model, int key) {
+  ModelPlan& m = p->models[model];
+  int held = 0;
+  Recording* oldest = nullptr;
+  for (auto& kr : m.recordings)
+    if (kr.second.exec) {
+      ++held;
+      if (!oldest || (int)(kr.second.used - oldest->used) < 0) oldest = &kr.second;
+    }
+  if (held >= MAX_GRAPHS) {
+    if (p->presence.launched.load(std::memory_order_relaxed) - oldest->used < GRAPH_IDLE) return;
+    retire(p, *oldest);
+  }
+  Batch b;
+  b.n = model == 0 ? key : p->max_frames;
+  b.model_ran.assign(p->models.size(), false);
+  b.layer_ev.resize(p->models.size());
+  const int hint = m.items_hint;
+  Recording r;
+  hipGraph_t graph = nullptr;
+  bool ok = p->capture_stream || hipStreamCreateWithFlags(&p->capture_stream, hipStreamNonBlocking) == hipSuccess;
+  if (ok && hipStreamBeginCapture(p->capture_stream, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+    if (model == 0) {
+      ok = enqueue_root(p, b, p->capture_stream, key) == OCTO_OK;
+    } else {
+      m.items_hint = key;
+      ok = run_child(p, b, p->edge_of_model[model], p->capture_stream, false) == OCTO_OK;
+      m.items_hint = hint;
+    }
+    ok = hipStreamEndCapture(p->capture_stream, &graph) == hipSuccess && ok && graph;
+    ok = ok && hipGraphInstantiate(&r.exec, graph, nullptr, nullptr, 0) == hipSuccess;
+  } else {
+    ok = false;
+  }
+  if (graph) hipGraphDestroy(graph);
+  if (!ok) { p->graphs_off = true; (void)hipGetLastError(); return; }
+  r.used = p->presence.launched.load(std::memory_order_relaxed);
+  m.recordings[key] = r;
+  ++p->n_recorded;
+}
+
+// Makes the recordings that are due, as long as `until` has not happened.
+void record_while_waiting(octo_pipeline* p, hipEvent_t until) {
+  int dev = -1;
+  if (p->stage_timing || p->layer_timing || hipGetDevice(&dev) != hipSuccess || dev != p->presence.device) return;
+  for (size_t k = 0; k < p->models.size(); ++k) {
+    const int key = p->models[k].record_key;
+    if (key < 0 || p->graphs_off) continue;
+    if (hipEventQuery(until) != hipErrorNotReady) return;
+    p->models[k].record_key = -1;
+    record(p, (int)k, key);
+  }
+}
+
+// All launches of a whole batch after the frame table, one after the other on `s`.
+octo_status enqueue_models(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
+  const bool use = replay_wanted(p, s, n);
+  octo_status st = OCTO_OK;
+  if (!use || !replay(p, p->models[0], n, s)) { st = enqueue_root(p, B, s, n); ++p->n_enqueued; }
+  for (int e = 0; e < (int)p->edges.size() && st == OCTO_OK; ++e) {
+    ModelPlan& c = p->models[p->edges[e].child];
+    if (!use || p->graphs_off || !replay(p, c, c.items_hint, s)) { st = run_child(p, B, e, s, false); ++p->n_enqueued; }
+  }
+  return st;
 }
 
 // Enqueues the newest batch in flight on `s`: copy of the frame table, then the root model (letterbox, detector, decode,
@@ -946,11 +1003,7 @@ octo_status enqueue_batch(octo_pipeline* p, hipStream_t s, int n, bool whole) {
     } while (at < n);
   }
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
-  if (whole) {
-    if (launch_graph(p, B, s, n)) { p->n_replayed += 1 + (long long)p->edges.size(); return OCTO_OK; }
-    p->n_enqueued += 1 + (long long)p->edges.size();
-    return enqueue_models(p, B, s, n);
-  }
+  if (whole) return enqueue_models(p, B, s, n);
   const octo_status st = enqueue_root(p, B, s, n);
   if (st == OCTO_OK) HIPCHK(p, hipEventRecord(p->ev_det, s));       // the children may run on streams of their own
   return st;
@@ -1004,7 +1057,7 @@ octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool own
   ra.frames = p->d_frames; ra.pitches = p->d_pitch; ra.src_h = p->d.src_h; ra.src_w = p->d.src_w;
   ra.dst = view_of(c, 0).ptr; ra.dst_h = c.d.in_h; ra.dst_w = c.d.in_w; ra.dst_c = c.input_c4 ? 4 : 3;
   for (int k = 0; k < 3; ++k) { ra.scale[k] = c.d.norm_scale[k]; ra.bias[k] = c.d.norm_bias[k]; }
-  ra.n = c.cap; ra.n_dyn = c.n_dyn; ra.rois = p->rois[e]; ra.n_frames = B.n;
+  ra.n = c.cap; ra.n_dyn = c.n_dyn; ra.rois = p->rois[e]; ra.n_frames = p->max_frames;      // ROIs name frames of the batch only
   HIPCHK(p, launch_crop_resize(c.d.dtype, ra, s));
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
   HIPCHK(p, run_layers(p, c, c.cap, c.n_dyn, s, p->layer_timing ? &B.layer_ev[p->edges[e].child] : nullptr));
@@ -1115,8 +1168,8 @@ octo_status octo_pipeline_destroy(octo_pipeline* p) {
   }
   for (hipEvent_t e : p->event_pool) hipEventDestroy(e);
   for (hipEvent_t e : p->done_pool) hipEventDestroy(e);
-  for (const GraphEntry& g : p->graphs) if (g.exec) hipGraphExecDestroy(g.exec);
-  for (hipGraphExec_t g : p->retired) hipGraphExecDestroy(g);
+  for (ModelPlan& m : p->models) drop_recordings(p, m);
+  for (const auto& g : p->retired) hipGraphExecDestroy(g.second);
   if (p->capture_stream) hipStreamDestroy(p->capture_stream);
   if (p->ev_det) hipEventDestroy(p->ev_det);
   for (hipEvent_t e : p->ev_child) hipEventDestroy(e);
@@ -1152,6 +1205,7 @@ octo_status octo_set_batch_size(octo_pipeline* p, int32_t model, int32_t bz) {
 octo_status octo_set_detector_batch(octo_pipeline* p, int32_t frames_per_execution) {
   if (!p) return OCTO_EINVAL;
   if (frames_per_execution < 0 || frames_per_execution > p->models[0].cap) return fail(p, OCTO_EINVAL, "bad detector batch size");
+  if (frames_per_execution != p->models[0].exec_bz) drop_recordings(p, p->models[0]);
   p->models[0].exec_bz = frames_per_execution;
   return OCTO_OK;
 }
@@ -1206,7 +1260,10 @@ octo_status octo_collect(octo_pipeline* p, octo_frame_result* frames, int32_t fr
   while (!p->inflight.empty()) {
     Batch& B = p->inflight.front();
     if (!B.finalized) break;
-    if (blocking && *n_frames == 0) HIPCHK(p, hipEventSynchronize(B.done));
+    if (blocking && *n_frames == 0) {
+      record_while_waiting(p, B.done);
+      HIPCHK(p, hipEventSynchronize(B.done));
+    }
     else {
       hipError_t q = hipEventQuery(B.done);
       if (q == hipErrorNotReady) break;
@@ -1275,10 +1332,11 @@ octo_status octo_collect(octo_pipeline* p, octo_frame_result* frames, int32_t fr
     p->done_pool.push_back(B.done);
     p->overlapped = gpu_is_shared(p->presence);
     p->inflight.pop_front();
+    ++p->collected;
   }
-  if (p->inflight.empty()) {
-    for (hipGraphExec_t g : p->retired) hipGraphExecDestroy(g);
-    p->retired.clear();
+  while (!p->retired.empty() && (int)(p->collected - p->retired.front().first) >= 0) {
+    hipGraphExecDestroy(p->retired.front().second);
+    p->retired.erase(p->retired.begin());
   }
   if (*n_frames == 0) return blocking ? fail(p, OCTO_ESTATE, "nothing in flight") : OCTO_ENOTREADY;
   return overflow ? OCTO_ECAP : OCTO_OK;
@@ -1417,8 +1475,9 @@ octo_status octo_debug_set_head(octo_pipeline* p, int32_t model, int32_t level, 
   if (!p) return OCTO_EINVAL;
   if (model < 0 || model >= (int)p->models.size() || p->models[model].d.kind != OCTO_DETECTOR || level < 0 || level >= p->models[model].d.n_outputs)
     return fail(p, OCTO_EINVAL, "bad model or level");
-  p->models[model].head_override[level] = d_head;
-  ++p->heads_version;
+  ModelPlan& m = p->models[model];
+  if (m.head_override[level] != d_head) drop_recordings(p, m);
+  m.head_override[level] = d_head;
   return OCTO_OK;
 }
 

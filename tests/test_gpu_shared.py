@@ -28,6 +28,40 @@ def _plant(P, heads):
         P.set_head(0, l, h)
 
 
+def test_batches_of_every_size_are_replayed(octo):
+    """Batch sizes and object counts that change from batch to batch, as a server's do: after a warm-up nine executions of a model
+    in ten are replays, recordings stay few, and every batch gives what it gives alone."""
+    spec, [(frames, heads)] = _spec_and_batches(octo, 12, [[0, 9, 1, 4, 14, 2, 7, 0, 3, 20, 6, 5]], 78)
+    solo = octo.Pipeline(spec)
+    _plant(solo, heads)
+    want = {}
+    for n in range(1, 13):
+        solo.submit(frames[:n])
+        assert solo.run() == n
+        want[n] = solo.collect()[1].tobytes()
+    assert solo.launch_counts() == (12 * 3, 0, 0)          # alone on the GPU: never
+    solo.close()
+    pipes = [octo.Pipeline(spec) for _ in range(3)]
+    for P in pipes:
+        _plant(P, heads)
+    rng = np.random.default_rng(1)
+    before = [None] * 3
+    for r in range(150):
+        sizes = rng.integers(1, 13, 3)
+        if r == 90:
+            before = [P.launch_counts() for P in pipes]
+        for P, n in zip(pipes, sizes):
+            P.submit(frames[:n])
+            assert P.run() == n
+        for P, n in zip(pipes, sizes):
+            assert P.collect()[1].tobytes() == want[n], (r, n)
+    for P, (e0, r0, _) in zip(pipes, before):
+        e1, r1, rec = P.launch_counts()
+        assert e1 - e0 + r1 - r0 == 60 * 3 and r1 - r0 >= 0.9 * 60 * 3, (e1 - e0, r1 - r0)
+        assert 12 <= rec <= 12 + 2 * 10, rec                # twelve batch sizes; item counts of two children, rounded
+        P.close()
+
+
 def test_an_uncollected_batch_elsewhere_is_no_work_on_the_gpu(octo):
     import torch
     spec, [(frames, heads)] = _spec_and_batches(octo, 2, [[3, 5]], 79)
