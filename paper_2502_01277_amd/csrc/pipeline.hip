@@ -108,6 +108,7 @@ struct Recording {
   int seen = 0;                            // batches that would have used it before it was made
   hipGraphExec_t exec = nullptr;
   unsigned used = 0;                       // number of the last batch that used it
+  std::vector<int> kernel_ids;             // per layer, as if it had been enqueued launch by launch
 };
 
 struct ModelPlan {
@@ -883,6 +884,7 @@ bool replay(octo_pipeline* p, ModelPlan& m, int key, hipStream_t s) {
     return false;
   }
   if (hipGraphLaunch(r.exec, s) != hipSuccess) { p->graphs_off = true; (void)hipGetLastError(); return false; }
+  for (size_t i = 0; i < m.layers.size(); ++i) m.layers[i].kernel_id = r.kernel_ids[i];
   ++p->n_replayed;
   return true;
 }
@@ -914,6 +916,8 @@ void record(octo_pipeline* p, int model, int key) {
     if (p->presence.launched.load(std::memory_order_relaxed) - oldest->used < GRAPH_IDLE) return;
     retire(p, *oldest);
   }
+  std::vector<int> ids(m.layers.size());
+  for (size_t i = 0; i < ids.size(); ++i) ids[i] = m.layers[i].kernel_id;
   Batch b;
   b.n = model == 0 ? key : p->max_frames;
   b.model_ran.assign(p->models.size(), false);
@@ -936,6 +940,7 @@ void record(octo_pipeline* p, int model, int key) {
     ok = false;
   }
   if (graph) hipGraphDestroy(graph);
+  for (size_t i = 0; i < ids.size(); ++i) { r.kernel_ids.push_back(m.layers[i].kernel_id); m.layers[i].kernel_id = ids[i]; }
   if (!ok) { p->graphs_off = true; (void)hipGetLastError(); return; }
   r.used = p->presence.launched.load(std::memory_order_relaxed);
   m.recordings[key] = r;

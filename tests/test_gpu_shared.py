@@ -81,6 +81,39 @@ def test_an_uncollected_batch_elsewhere_is_no_work_on_the_gpu(octo):
     P.close()
 
 
+def test_layer_info_names_the_kernels_of_a_replayed_batch(octo):
+    """A replay enqueues nothing itself; the kernels reported are still those of the batch that ran last."""
+    spec, [(frames, heads)] = _spec_and_batches(octo, 16, [[4] * 16], 80)
+
+    def kernels(P):
+        return [[int(k) for k in P.layer_info(m)[1]] for m in range(3)]
+    solo = octo.Pipeline(spec)
+    _plant(solo, heads)
+    want = {}
+    for n in (16, 1):
+        solo.submit(frames[:n])
+        solo.run()
+        solo.collect()
+        want[n] = kernels(solo)[0]
+    assert want[16] != want[1]
+    solo.close()
+    pipes = [octo.Pipeline(spec) for _ in range(2)]
+    for P in pipes:
+        _plant(P, heads)
+    for r in range(12):
+        n = (16, 1)[r % 2]
+        counts = [P.launch_counts() for P in pipes]
+        for P in pipes:
+            P.submit(frames[:n])
+            P.run()
+        for P in pipes:
+            P.collect()
+            assert kernels(P)[0] == want[n], (r, n)
+    assert all(P.launch_counts()[1] >= c[1] + 1 for P, c in zip(pipes, counts))       # the last batches were replays
+    for P in pipes:
+        P.close()
+
+
 def test_replayed_batches_equal_batches_alone(octo):
     import torch
     spec = zoo.traffic_cascade("f16", det_batch=4, max_rois_per_frame=12)
