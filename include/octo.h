@@ -174,6 +174,11 @@ octo_status octo_set_batch_size(octo_pipeline* p, int32_t model, int32_t bz);
  * identical either way.  Layer tensors read back with octo_debug_get_tensor, and the per-layer times, are those of
  * the last execution.  0 <= b <= max_frames. */
 octo_status octo_set_detector_batch(octo_pipeline* p, int32_t frames_per_execution);
+/* About how many ROIs a batch gives a downstream model; 0 (the default): eight per frame of max_frames.  Layers whose launch
+ * is small take kernels that sum in another order (the reduction is split), and so that the results for an ROI do not change with
+ * the number of ROIs beside it, that choice is made for this count and not for the one a batch turns out to have; any count
+ * runs correctly.  1 <= items <= the model's capacity. */
+octo_status octo_set_expected_items(octo_pipeline* p, int32_t model, int32_t items);
 const char* octo_last_error(const octo_pipeline* p);    /* library-owned text, valid until the next call on p (NULL p: last create error) */
 double octo_now_ms(void);                               /* monotonic host clock used for arrival / completion times */
 

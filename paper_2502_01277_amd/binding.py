@@ -147,7 +147,7 @@ EXPORTS = [
     "octo_plan_pipeline", "octo_to_edge", "octo_scaler_create", "octo_scaler_observe", "octo_scaler_destroy", "octo_run_model",
     "octo_executor_create", "octo_executor_serve", "octo_executor_stats", "octo_executor_scale_events", "octo_executor_streams",
     "octo_executor_results", "octo_executor_last_error", "octo_executor_destroy", "octo_profile_layers", "octo_set_layer_timing", "octo_get_layer_info", "octo_set_stage_timing", "octo_get_stage_ms",
-    "octo_debug_get_tensor", "octo_debug_tensor_shape", "octo_debug_set_head", "octo_debug_get_launch_counts", "octo_debug_run_model",
+    "octo_debug_get_tensor", "octo_debug_tensor_shape", "octo_debug_set_head", "octo_set_expected_items", "octo_debug_get_launch_counts", "octo_debug_run_model",
     "octo_debug_get_detections", "octo_debug_get_rois", "octo_debug_get_labels", "octo_letterbox_geometry", "octo_op_frame_table", "octo_op_letterbox",
     "octo_op_crop_resize", "octo_op_decode", "octo_op_topk", "octo_op_nms", "octo_op_nms_scratch_bytes", "octo_op_nms_static", "octo_op_compact", "octo_probe_copy", "octo_probe_mfma",
     "octo_op_conv", "octo_op_conv_packed_bytes", "octo_op_conv_padded_cout", "octo_op_conv_pack", "octo_quantize_e4m3", "octo_dequantize_e4m3",
@@ -215,6 +215,7 @@ def lib() -> C.CDLL:
         L.octo_debug_get_tensor.argtypes = [vp, i32, i32, i32, i32, vp, C.c_size_t]
         L.octo_debug_tensor_shape.argtypes = [vp, i32, i32, vp, vp, vp]
         L.octo_debug_set_head.argtypes = [vp, i32, i32, vp]
+        L.octo_set_expected_items.argtypes = [vp, i32, i32]
         L.octo_debug_get_launch_counts.argtypes = [vp, vp, vp, vp]
         L.octo_debug_run_model.argtypes = [vp, i32, vp, i32, vp]
         L.octo_debug_get_detections.argtypes = [vp, i32, i32, vp, vp, i32, vp, vp, i32, vp]
@@ -416,6 +417,10 @@ class Pipeline:
 
     def set_detector_batch(self, frames_per_execution: int):
         self._check(self.L.octo_set_detector_batch(self.h, frames_per_execution))
+
+    def set_expected_items(self, model: int, items: int):
+        """About how many ROIs a batch gives a downstream model (0: eight per frame of the capacity)."""
+        self._check(self.L.octo_set_expected_items(self.h, model, items))
 
     # ---- hooks ----
     def tensor_shape(self, model: int, tid: int):

@@ -393,3 +393,43 @@ def test_detector_batch_smaller_than_the_frame_batch(octo):
         assert rel_err(lb, l0) <= 1e-6                                  # same crops, same kernels
         for l, t in enumerate(det.outputs):                           # the activation buffers hold the last execution
             assert rel_err(hb[l], ref.heads[l][last:]) <= TOL[dtype], (b, l)
+
+
+def test_stated_item_count_decides_the_kernels_and_nothing_else(octo):
+    """octo_set_expected_items: the count that the order of summation is chosen for.  Kernels change with it, results stay within
+    the tolerance of each other, an ROI's results are the same whatever the number of ROIs beside it, and counts outside the
+    model's capacity, the detector and unknown models are refused."""
+    from paper_2502_01277_amd import binding
+    spec = zoo.traffic_cascade("f16", det_batch=4, max_rois_per_frame=40)
+    det = spec.models[0]
+    rng = np.random.default_rng(zoo.SEED0 + 12)
+    scene = synth.make_scene(rng, 4, 1080, 1920, [3, 0, 2, 4], 24, 360, log_uniform=True)
+    planted = synth.planted_heads(rng, det, scene, 1080, 1920, pre.letterbox_geometry(1080, 1920, det.in_h, det.in_w)[1:])
+    dev, d_heads = _frames_dev(scene.frames), [octo.to_device(h, "f16") for h in planted]
+    P = octo.Pipeline(spec)
+    for l, h in enumerate(d_heads):
+        P.set_head(0, l, h)
+    for model, items in ((0, 8), (3, 8), (1, -1), (1, 161), (2, 161)):
+        with pytest.raises(binding.OctoError) as e:
+            P.set_expected_items(model, items)
+        assert e.value.status == binding.EINVAL
+    logits, kernels = {}, {}
+    for items in (0, 1, 160, 0):
+        for model in (1, 2):
+            P.set_expected_items(model, items)
+        for n in (1, 4):                            # the first frame's ROIs alone, then with the others behind them
+            P.submit(dev[:n])
+            P.run()
+            P.collect()
+            rois = len(P.get_rois(0))
+            out = P.get_tensor(1, spec.models[1].outputs[0], rois).reshape(rois, -1)
+            if n == 1:
+                first = out
+        assert len(first) >= 3 and np.array_equal(out[:len(first)], first)
+        if items in logits:
+            assert np.array_equal(logits[items], out)
+        logits[items], kernels[items] = out, [int(k) for k in P.layer_info(1)[1]]
+    P.close()
+    assert kernels[1] != kernels[160]
+    for items in (1, 160):
+        assert rel_err(logits[items], logits[0]) <= TOL["f16"]

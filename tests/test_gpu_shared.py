@@ -100,16 +100,18 @@ def test_layer_info_names_the_kernels_of_a_replayed_batch(octo):
     pipes = [octo.Pipeline(spec) for _ in range(2)]
     for P in pipes:
         _plant(P, heads)
+    most = [0, 0]                                          # models replayed in one batch
     for r in range(12):
         n = (16, 1)[r % 2]
-        counts = [P.launch_counts() for P in pipes]
+        counts = [P.launch_counts()[1] for P in pipes]
         for P in pipes:
             P.submit(frames[:n])
             P.run()
         for P in pipes:
             P.collect()
             assert kernels(P)[0] == want[n], (r, n)
-    assert all(P.launch_counts()[1] >= c[1] + 1 for P, c in zip(pipes, counts))       # the last batches were replays
+        most = [max(m, P.launch_counts()[1] - c) for m, P, c in zip(most, pipes, counts)]
+    assert most == [3, 3]                                  # the detector's too
     for P in pipes:
         P.close()
 
