@@ -552,7 +552,9 @@ static hipError_t launch_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* 
 // with 64x64): 128x64 (64x128 where 128 channels would pad) where their tiles fill one round of those and not more - 128 -> 256,
 // stride 2 on 8 x 80 x 80 15.6 us (128x128: 19.6), 1024 -> 512 on 60 x 16 x 8 14.7 (18.2); one tile more than a round and the
 // others win again -, 64x64 in the same way for fewer pixels and a reduction of at least 1 KB (256 -> 512, stride 2 on
-// 63 x 14 x 14 16.4 us, split-K 18.2), and 128x256 with 64-byte K steps for long reductions over enough pixels to keep its
+// 63 x 14 x 14 16.4 us, split-K 18.2; where 64x128 would do too, up to 1.3 of those per compute unit, beyond which the three
+// per unit that 64x64 tiles fit run out: 192 -> 192, stride 2 on 56 x 56, 64x64 : 64x128 at 1.08 17.0 : 17.1, at 1.29 17.7 : 17.6, at
+// 1.58 23.8 : 18.9; 128 -> 192, stride 2 on 57 x 57 at 1.15 13.1 : 13.5, at 1.31 13.3 : 13.7, at 1.54 17.3 : 14.0), and 128x256 with 64-byte K steps for long reductions over enough pixels to keep its
 // rounds three quarters full (256 -> 512, stride 2 on 64 x 40 x 40 76 us, 128x128: 88).
 struct GeneralTile { int bc, bp; bool pipe = false; };
 static GeneralTile general_tile(const ConvArgs& a, long long M, int num_cu, int k_scale, bool pipe_ok = false) {
@@ -623,7 +625,9 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
   // 3x3 layers with enough tiles for every compute unit: input patch in LDS, slices of 64 channels, four workgroups per compute unit
   // (256 -> 256 on 300 x 14 x 14: 39 us, slices of 128 channels 46); with plenty of tiles 128 channels per tile halve the fetch of
-  // the patch (256 -> 256 with residual on 1021 x 14 x 14: 125 us, 131 on 64 channels, 161 on the tiles below)
+  // the patch (256 -> 256 with residual on 1021 x 14 x 14: 125 us, 131 on 64 channels, 161 on the tiles below).  The lines, by 64 x 128
+  // tiles per compute unit: split-K : patch 14 x 14 x 256 at 0.48 8.8 : 9.0, at 0.81 11.4 : 9.2 (7 x 7 x 512 turns below 0.6:
+  // 16.3 : 13.1); 64 : 128 channels at 6 31.7 : 34.4, at 9.6 45.2 : 44.4, at 12 57.0 : 56.6, at 24 110 : 106
   if (mid_fits(a) && a.Cout > 32 && a.Cin * 4 >= (a.Cin + 63) / 64 * 64 * 3) {
     const double per_cu = (double)M / 128 * ((a.Cout + 63) / 64) / num_cu;
     const bool wide = per_cu >= 12 && (a.Cout + 127) / 128 * 2 == (a.Cout + 63) / 64;
@@ -694,7 +698,7 @@ hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s,
   ConvArgs a = a0;
   if (!conv_prepare(a, dtype)) return hipErrorInvalidValue;
   if (a.split > 0) {
-    // two layers in one launch: only the general kernel's staged epilogue knows the second output tensor
+    // two layers in one launch: the streaming 1x1 kernel, the split-K kernel and the general kernel's staged epilogue write two tensors
     const bool ok = (dtype == OCTO_F16 || dtype == OCTO_BF16) && a.y2 && !a.res && !a.out_f32 && !a.pair_view && !a.pool_y && a.split < a.Cout &&
                     ((a.split | a.Cout | a.y_ld | a.y_coff | a.y2_ld | a.y2_coff) & 7) == 0 && ((((uintptr_t)a.y | (uintptr_t)a.y2) & 15) == 0);
     if (!ok) return hipErrorNotSupported;

@@ -366,17 +366,27 @@ inline bool mid_fits(const ConvArgs& a) {
 }
 
 // Tile of a 16-bit layer with M output pixels, or hipErrorNotSupported where the split-K or general kernel is the better one
-// (measured on MI355X).  per_cu: 64 x 128 tiles per compute unit.
+// (measured on MI355X, bf16, us; layers of H x W x C -> C, by the number of images).  per_cu: 64 x 128 tiles per compute unit.
 //   * up to 64 channels and many pixels: conv3x3_stream_kernel;
-//   * below 0.35 the split-K kernel spreads the K loop of the few tiles over more wavefronts;
+//   * below 0.35 the split-K kernel spreads the K loop of the few tiles over more wavefronts.  Against 64 x 64 tiles: 14 x 14 x 256 at
+//     0.22 9.0 : 9.5, at 0.36 11.0 : 9.7; 20 x 20 x 64 at 0.24 5.7 : 6.1, at 0.34 7.2 : 6.2; 40 x 40 x 128 at 0.20 6.7 : 7.2, at 0.29
+//     8.4 : 7.3; the long reduction of 7 x 7 x 512 turns later, at 0.43 16.5 : 19.2, at 0.60 24.7 : 19.9;
+//   * 64 x 64 tiles up to 0.8.  Against 64 x 128: 14 x 14 x 256 at 0.72 12.0 : 12.3, at 0.96 12.8 : 12.8, at 1.2 18.9 : 17.2;
+//     7 x 7 x 512 at 0.72 20.4 : 20.8, at 0.96 23.1 : 21.7;
 //   * reductions over at least 192 channels with fewer than six tiles per compute unit are paced by the operand fetch: slices of
 //     128 bytes (whole cache lines), and 64 x 64 tiles while those leave compute units idle.  256 -> 256 on 63 x 14 x 14: 19 us
 //     on 64 x 128 (general kernel 27), 512 -> 512 on 63 x 7 x 7: 22 us on 64 x 64 (split-K 29);
 //   * otherwise slices of 64 bytes, half the LDS and up to four workgroups per compute unit, which hide each other's prologue
 //     and epilogue: 64 -> 64 with residual on 64 x 80 x 80 46 us (general kernel 74).  Tiles of 256 pixels fetch the weights half
 //     as often and pay once there are plenty of them: 384 -> 384 on 32 x 40 x 40 116 us (64 x 128: 136, general kernel 156).
-//   * tiles of 32 channels for layers with no more: 32 -> 32 with residual on 16 x 160 x 160 24 us (33);
-//   * tiles of 96 channels where those of 64 would pad: 96 -> 96 on 32 x 160 x 160 156 us (187).
+//     From 96 channels that is at 12 (64 x 128 : 64 x 256): 28 x 28 x 128 at 8 43.7 : 44.6, at 12 61.8 : 60.3, at 20 99.7 : 93.9;
+//     56 x 56 x 96 -> 64 at 8.6 37.7 : 39.4, at 19 77.9 : 74.9.  From 192 channels it is a matter of rounds: 14 x 14 x 256, slices of 128
+//     bytes : 64 x 256, at 2.0 27.3 : 28.9, at 3.8 37.1 : 35.2, at 5.0 52.4 : 47.5, at 6.0 59.2 : 61.5, at 7.2 70.2 : 63.1, at 14
+//     128 : 127; the line at 6 is right on both sides of itself and 10 % off in the last third of a round below it;
+//   * tiles of 32 channels for layers with no more: 32 -> 32 with residual on 16 x 160 x 160 24 us (33).  From 0.8: 80 x 80 x 32 at 0.59 5.8
+//     on either, at 0.78 5.7 (general kernel 7.0);
+//   * tiles of 96 channels where those of 64 would pad: 96 -> 96 on 32 x 160 x 160 156 us (187), of 256 pixels from four per compute
+//     unit on (80 x 80 x 96, 128 : 256 pixels, 15.2 : 17.9 for 10 images, 36.6 : 37.4 for 30, 46.9 : 46.3 for 40, 89.4 : 86.2 for 80).
 // The two slice widths sum in different orders; M is taken for a count that stays the same from batch to batch (a.n_split), and
 // so do the results.
 template <typename T>
@@ -394,7 +404,8 @@ hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s,
     if (a.Cin >= 192 && per_cu < 6) {
       // tiles whose patch fits five passes of the loader (whole images of up to 14 columns) save the sixth, which would fetch
       // nothing: 512 -> 512 on 200 x 7 x 7 51 us (56).  Same slices, so a running count may choose: 128 channels with plenty of
-      // tiles after all (512 -> 512 on 3600 x 7 x 7 729 us, 765)
+      // tiles after all (64 : 128 channels, 7 x 7 x 512 at 18 300 : 313 us, at 24 397 : 389, at 30 497 : 502, at 48 814 : 780;
+      // 14 x 14 x 256 at 24 212 : 206, at 36 328 : 312)
       MidGeom g5{}, g6{};
       const bool five = mid_geometry(a, 64, 128, 160, &g5) && mid_geometry(a, 64, 128, 192, &g6) && g5.TH * g5.TW == g6.TH * g6.TW;
       const double now = (double)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo / 128 * ((a.Cout + 63) / 64) / num_cu;

@@ -303,7 +303,8 @@ __global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(const ConvArgs a, 
 // error 6 - 8 %): a constant (start, first trip to memory, drain), plus what the busiest compute unit does: per tile the
 // bytes of its operands at the rate one unit fetches them from its L2 (130 GB/s = 55 bytes per clock here, half of that in
 // the general kernel) and an epilogue, plus a latency per K step.  The smallest estimate wins; over those layers the
-// choice is within 1 % of always taking the fastest kernel.
+// choice is within 1 % of always taking the fastest kernel.  The general kernel's pipelined tiles and its 64 x 256 one have no entry: the
+// former are taken before this comparison where they win (general_tile), the latter only for launches far too large to split.
 struct ConvCost { int bc, bp, ks; double start, per_100kb, per_tile, per_step; };
 inline double conv_cost_us(const ConvCost& c, long long M, int cout, int kp_bytes, int num_cu) {
   const double tiles = (double)((M + c.bp - 1) / c.bp) * ((cout + c.bc - 1) / c.bc);
