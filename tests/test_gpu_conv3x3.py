@@ -1,6 +1,6 @@
 """The 3x3 kernel with the input patch in LDS at its edges: widths that no tile divides, tiles that span several images, images of
 one row or column's width, channel counts below and over a tile, input channels that do not fill the last slice, residuals, unaligned
-and wider output buffers, a device-side item count; against the oracle."""
+and wider output buffers, an item count taken on the device; against the oracle."""
 import numpy as np
 import pytest
 
@@ -96,3 +96,53 @@ def test_patch_3x3_fp8(octo, n, h, w, cin, cout, res, bc):
     # one code apart at most, and that only where the fp32 sum lies next to a rounding boundary
     diff = (got.view(torch.uint8).int() - want.view(torch.uint8).int()).abs()
     assert int(diff.max()) <= 1 and float((diff != 0).float().mean()) < 1e-3
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_patch_3x3_with_the_item_count_on_the_device(octo, dtype):
+    """3x3 layers of a downstream model, whose item count stays on the device: a batch with a few hundred ROIs, then one with a few
+    dozen, on kernels chosen for 400, 60 and 3 items.  Every tensor of the first, last and some other ROIs against the oracle on the
+    GPU's own crops; what the larger batch left beyond the smaller one's items is untouched."""
+    import torch
+    det = zoo.traffic_cascade(dtype).models[0]
+    det.batch_size = 4
+    B = zoo._Builder("child", dtype, 56, 56, "classifier", np.random.default_rng(17))
+    a = B.conv(B.conv(0, 64, 3, 2, act=zoo.ACT_RELU), 64, 3, act=zoo.ACT_NONE)
+    a = B.conv(a, 64, 3, act=zoo.ACT_RELU, res=1, res_mode=zoo.RES_BEFORE_ACT)
+    b = B.conv(B.conv(a, 96, 3, act=zoo.ACT_SILU), 192, 3, 2, act=zoo.ACT_RELU)
+    c = B.conv(B.conv(b, 192, 3, act=zoo.ACT_RELU), 40, 3, act=zoo.ACT_SILU)
+    B.m.outputs = [B.fc(B.gap(c), 10)]
+    B.m.batch_size = 400
+    spec = zoo.PipelineSpec("items", [det, B.m], [zoo.Edge(0, 1)], 1000.0, 540, 960, 4, 100)
+    rng = np.random.default_rng(zoo.SEED0 + 91)
+    geo = octo.letterbox_geometry(540, 960, det.in_h, det.in_w)
+    scenes = [synth.make_scene(rng, 4, 540, 960, counts, 16, 200, log_uniform=True) for counts in ([120] * 4, [5, 0, 17, 9])]
+    heads = [[octo.to_device(v, dtype) for v in synth.planted_heads(rng, det, s, 540, 960, geo)] for s in scenes]
+    frames = [[torch.from_numpy(f).cuda() for f in s.frames] for s in scenes]
+    n_t = len(B.m.layers)
+    P = octo.Pipeline(spec, keep_all_tensors=1)
+    families, refs = set(), {}
+    for expected in (400, 60, 3):
+        P.set_expected_items(1, expected)
+        before = None
+        for k in (0, 1):
+            for l, v in enumerate(heads[k]):
+                P.set_head(0, l, v)
+            P.submit(frames[k])
+            P.run()
+            P.collect()
+            n = len(P.get_rois(0))
+            assert n > 200 if k == 0 else 20 < n < 60
+            at = [0, n // 2, n - 1]
+            got = [np.concatenate([P.get_tensor(1, t, 1, first=i) for i in at]) for t in range(n_t + 1)]
+            beyond = [np.concatenate([P.get_tensor(1, t, 1, first=i) for i in (60, 120, 199)]) for t in range(n_t + 1)]
+            if k not in refs:
+                refs[k] = nn.run_model(B.m, got[0], keep_all=True)
+            for t in range(1, n_t + 1):
+                assert rel_err(got[t].reshape(refs[k][t].shape), refs[k][t]) <= TOL[dtype], (expected, k, t)
+                if before is not None:
+                    assert np.array_equal(beyond[t], before[t]), (expected, t)
+            before = beyond
+        families |= {int(v) // 100000000 for v in P.layer_info(1)[1][1:7]}
+    P.close()
+    assert {16, 17, 18} <= families, families             # split-K, patch kernels of more and of up to 64 channels

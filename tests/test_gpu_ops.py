@@ -212,6 +212,90 @@ def test_first_layer_with_fused_max_pool(octo, dtype, case):
     assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[2][1], got[1][1])
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("h,w,cout,n", [(224, 224, 64, 25), (70, 90, 40, 60), (134, 60, 64, 110)])
+def test_fused_max_pool_on_segments_of_a_strip(octo, dtype, h, w, cout, n):
+    """The same with strips cut into segments of several tiles, the last one shorter (5 x 3 of 14 tiles, 3 x 2 of 5, 3 x 3 of 9): a
+    segment computes the tile above it once more for the row its first windows need."""
+    def build(B):
+        a = B.conv(0, cout, 7, 2, 3, act=zoo.ACT_SILU)
+        return B.conv(B.maxpool(a, 3, 2, 1), 16, 1, 1)
+    m = _model(dtype, (h, w), 3, build, n)
+    x = zoo.round_to_dtype(np.random.default_rng(22).uniform(-1, 1, (n, h, w, 3)).astype(np.float32), dtype)
+    spec = zoo.PipelineSpec("t", [small_root(dtype), m], [], 200.0, 32, 32, 1, 1)
+    got = {}
+    for keep in (1, 2):
+        P = octo.Pipeline(spec, keep_all_tensors=keep)
+        P.run_model_on(1, octo.to_device(x, dtype))
+        got[keep] = P.get_tensor(1, 2, n)
+        if keep == 1:
+            conv = P.get_tensor(1, 1, n)
+        else:
+            assert int(P.layer_info(1)[1][0]) == 1901064074
+        P.close()
+    want = nn.maxpool(conv, 3, 2, 1).astype(np.float32)
+    assert np.array_equal(got[1], want) and np.array_equal(got[2], want)
+    assert rel_err(conv[-1:], nn.run_model(m, x[-1:], keep_all=True)[1]) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("h,w,c,n", [(7, 7, 512, 3), (1, 1, 8, 5), (9, 7, 24, 2), (17, 13, 520, 4), (2, 3, 1000, 300), (5, 5, 12, 3), (4, 8, 2048, 70)])
+def test_global_average_pool_at_ragged_channels(octo, dtype, h, w, c, n):
+    """Channel vectors that fill a workgroup's lanes, a few of them, several chunks with a ragged last one (520 = 65 vectors of 8,
+    1000 = 125), more units than workgroups, one pixel, fewer pixels than lane groups, and a count that is no whole vector in
+    the 16-bit types (12).  Bar: the mean is summed in fp32 (n terms of magnitude <= 1) and rounded once."""
+    rng = np.random.default_rng(37)
+    B = zoo._Builder("t", dtype, h, w, "classifier", rng)
+    B.ch = [c]
+    B.m.in_c = c
+    B.m.outputs = [B.fc(B.gap(0), 10)]
+    B.m.batch_size = n
+    x = zoo.round_to_dtype(rng.uniform(-1, 1, (n, h, w, c)).astype(np.float32), dtype)
+    got = _run_detached(octo, B.m, x)[1].reshape(n, c)
+    ref = x.astype(np.float64).mean((1, 2))
+    bar = {"f32": 2.0 ** -24, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype] * np.abs(ref) + h * w * 2.0 ** -24 + (2.0 ** -25 if dtype == "f16" else 0.0)
+    assert (np.abs(got - ref) <= bar).all()
+
+
+UPSAMPLE_CASES = [
+    # (n, h, w, cin, channels of the two upsampled layers): of each, the split-K shape (None: not one, the upsampling is a launch)
+    (1, 20, 20, 256, ((128, 4032032), (64, 4032032))),
+    (1, 13, 7, 72, ((40, 4032032), (8, 4032032))),         # ragged pixels, reductions shorter than the split
+    (1, 1, 1, 64, ((24, 4032032), (16, 4032032))),
+    (8, 20, 20, 512, ((256, 4064064), (72, 4064032))),
+    (3, 23, 19, 264, ((200, 4064032), (136, 4032032))),    # images that end inside a tile, ragged channel tiles
+    (9, 40, 40, 256, ((512, None), (128, None))),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("n,h,w,cin,layers", UPSAMPLE_CASES)
+def test_1x1_layer_that_writes_its_upsampled_copy(octo, dtype, n, h, w, cin, layers):
+    """A 1x1 layer followed by the nearest upsampling of its output writes both tensors, the copy into a slice of a
+    concatenation, with 16-byte or (32-channel shapes) 8-byte stores.  The copy must repeat the layer's own output exactly, and
+    both equal the path of separate launches bit for bit."""
+    def build(B):
+        up = [B.up(B.conv(0, c, 1, 1, 0, act=zoo.ACT_SILU)) for c, _ in layers]
+        return B.conv(B.cat(up), 16, 1, 1, 0)
+    m = _model(dtype, (h, w), cin, build, n)
+    x = zoo.round_to_dtype(np.random.default_rng(41).uniform(-1, 1, (n, h, w, cin)).astype(np.float32), dtype)
+    spec = zoo.PipelineSpec("t", [small_root(dtype), m], [], 200.0, 32, 32, 1, 1)
+    got, kids = {}, {}
+    for keep in (1, 2):
+        P = octo.Pipeline(spec, keep_all_tensors=keep)
+        P.run_model_on(1, octo.to_device(x, dtype))
+        got[keep] = [P.get_tensor(1, t, n) for t in (1, 2, 3, 4)]
+        kids[keep] = [int(k) for k in P.layer_info(1)[1][:4]]
+        P.close()
+    for j, (c, shape) in enumerate(layers):
+        assert kids[1][2 * j + 1] == 2 and kids[2][2 * j + 1] == (2 if shape is None else 0), kids
+        assert shape is None or kids[2][2 * j] == kids[1][2 * j] == 1600000000 + shape, kids
+        y, u = got[2][2 * j], got[2][2 * j + 1]
+        assert np.array_equal(u, y.repeat(2, 1).repeat(2, 2))
+        assert np.array_equal(y, got[1][2 * j]) and np.array_equal(u, got[1][2 * j + 1])
+        assert rel_err(y, nn.run_model(m, x, keep_all=True)[2 * j + 1]) <= TOL[dtype]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("case", [(40, 40, 384, 5, 9), (23, 3, 512, 5, 176), (64, 9, 256, 3, 24), (11, 50, 256, 5, 48), (9, 9, 40, 5, 2), (40, 40, 64, 5, 4)])
 def test_stride_1_max_pools_walk_down_the_rows(octo, dtype, case):
