@@ -96,25 +96,41 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "93d07c228e907e2c": {
-        "octo::conv_mfma_kernel<__bf16, 128, 128, 2, 2, 8, 1, 2, true, true>": 624532799,
-        "octo::conv3x3_patch_kernel<__bf16, 64, 64>": 4275894878,
-        "octo::conv_mfma_kernel<__bf16, 64, 256, 1, 4, 4, 1, 3, true, true>": 412985885,
-        "octo::conv3x3_big_kernel<__bf16, 4, 4, 2, 4>": 1153790470,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3409215376,
-        "octo::conv3x3_big_kernel<__bf16, 3, 4, 1, 4>": 526039832,
-        "octo::conv3x3_big_kernel<__bf16, 3, 4, 2, 4>": 244944910,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1753120816,
-        "octo::conv_mfma_kernel<__bf16, 64, 128, 2, 2, 8, 1, 3, true, true>": 541911139,
-        "octo::conv_mfma_kernel<_Float16, 128, 128, 2, 2, 8, 1, 2, true, true>": 29254610,
-        "octo::conv_mfma_kernel<_Float16, 64, 128, 2, 2, 8, 1, 3, true, true>": 18779512,
-        "octo::conv3x3_patch_kernel<_Float16, 64, 64>": 69226266,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 78867677,
-        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 1, 4, true, true>": 6645295,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 55154702,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false>": 13644829,
-        "octo::conv3x3_patch_kernel<_Float16, 32, 64>": 39928727,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18000958,
+    "58d285fd05ad921d": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4365782990,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 667333861,
+        "octo::conv_mfma_kernel<__bf16, 128, 256, 2, 2, 4, 2, 2, true, true, true>": 819593349,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 379802638,
+        "octo::conv_mfma_kernel<__bf16, 128, 128, 2, 2, 8, 1, 2, true, true, false>": 430804795,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 128, 2, 8, 2, 5, 2>": 1317601096,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3373198559,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 432433494,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 990130530,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1745473789,
+        "octo::conv_mfma_kernel<__bf16, 64, 128, 2, 2, 8, 1, 3, true, true, false>": 778511646,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629394498,
+        "octo::conv_mfma_kernel<__bf16, 64, 256, 1, 4, 4, 1, 3, true, true, false>": 597296768,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838286,
+        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69117604,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22741543,
+        "octo::conv1x1_stream_kernel<_Float16, 2>": 28251951,
+        "octo::conv_mfma_kernel<_Float16, 128, 128, 2, 2, 8, 1, 2, true, true, false>": 34952964,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28762121,
+        "octo::conv_mfma_kernel<_Float16, 128, 64, 2, 2, 8, 2, 2, true, true, true>": 17086574,
+        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 16199256,
+        "octo::conv_mfma_kernel<_Float16, 64, 128, 2, 2, 8, 1, 3, true, true, false>": 45310226,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28383205,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 78880963,
+        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 1, 4, true, true, false>": 6910103,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 55174108,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 12093732,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39719055,
+        "octo::conv1x1_stream_kernel<_Float16, 1>": 26389040,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18000938,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644794,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3224504,
+        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4732523,
+        "octo::conv_mfma_kernel<_Float16, 128, 256, 2, 2, 4, 2, 2, true, true, true>": 33767946,
     },
 }
 
