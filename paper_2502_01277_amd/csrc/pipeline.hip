@@ -1134,14 +1134,9 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
     int dev = 0; hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) p->num_cu = prop.multiProcessorCount;
     p->presence.device = dev;
-    void* word = nullptr;
-    if (hipHostMalloc(&word, 64, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&p->presence.done_dev, word, 0) != hipSuccess)
-      st = fail(p, OCTO_ENOMEM, "pinned host allocation failed");
-    p->presence.done = (volatile unsigned*)word;
-    if (word) *p->presence.done = 0;
+    const size_t word = (p->result_bytes + 63) & ~(size_t)63;      // where the first block holds the number of the last batch that has run
     for (int r = 0; r < RING && st == OCTO_OK; ++r) {
-      if (hipHostMalloc((void**)&p->h_result[r], p->result_bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+      if (hipHostMalloc((void**)&p->h_result[r], r == 0 ? word + 64 : p->result_bytes, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
           hipHostGetDevicePointer((void**)&p->h_result_dev[r], p->h_result[r], 0) != hipSuccess)
         st = fail(p, OCTO_ENOMEM, "pinned host allocation failed");
     }
@@ -1152,6 +1147,9 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
       else p->ev_child.push_back(ev);
     }
     if (st == OCTO_OK) {
+      p->presence.done = (volatile unsigned*)(p->h_result[0] + word);
+      p->presence.done_dev = (unsigned*)(p->h_result_dev[0] + word);
+      *p->presence.done = 0;
       try {
         std::lock_guard<std::mutex> lock(g_presence_mutex);
         g_presence.push_back(&p->presence);
@@ -1184,7 +1182,6 @@ octo_status octo_pipeline_destroy(octo_pipeline* p) {
   if (p->ev_det) hipEventDestroy(p->ev_det);
   for (hipEvent_t e : p->ev_child) hipEventDestroy(e);
   for (int r = 0; r < RING; ++r) if (p->h_result[r]) hipHostFree(p->h_result[r]);
-  if (p->presence.done) hipHostFree((void*)p->presence.done);
   delete p;
   return OCTO_OK;
 }
