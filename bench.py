@@ -362,8 +362,8 @@ def run_conv8(args):
     """The 8-bit floating-point (E4M3) variant of the convolution kernel against the bf16 kernels, layer by layer: every
     convolution of the high-resolution cascade's two models whose input channels come in 16s (all but the two first
     layers), at the batch the cascade serves (32 frames, 4170 ROIs), each run alone through octo_op_conv on random
-    tensors of identical shape.  bf16 takes whichever kernel the pipeline would (patch, wide or general); E4M3 has the
-    general kernel only."""
+    tensors of identical shape.  Both types take whichever kernel the library picks; the streaming 1x1 and 3x3 kernels exist for
+    the 16-bit types only."""
     import torch
     from paper_2502_01277_amd import binding, zoo
     spec = zoo.hires_cascade()

@@ -862,7 +862,7 @@ octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n);
 
 // ---- recorded launches ---------------------------------------------------------
 // Replaying a model's launches from a graph takes 0.9 us of host time per launch instead of 2.6.  That pays where several
-// pipelines share the GPU and the host is behind: while one batch's 110 launches are enqueued, the GPU waits for the next
+// pipelines share the GPU and the host is behind: while one batch's hundred launches are enqueued, the GPU waits for the next
 // pipeline's (traffic cascade, 8 frames, four instances, a batch of each and then the results: 3.44 -> 3.12 ms; with two batches of
 // each in flight 0.72 ms a batch either way, with 1 .. 8 frames a batch 0.50).  A pipeline alone on the GPU is faster without
 // (2 % here): its launches are enqueued faster than they run, and nothing of a graph runs before all of it has been handed
