@@ -62,6 +62,48 @@ def test_batches_of_every_size_are_replayed(octo):
         P.close()
 
 
+def test_pipelines_of_several_threads(octo):
+    """Each pipeline driven by a thread of its own, on its own stream: one records while the others enqueue and replay."""
+    import threading
+    import torch
+    spec, [(frames, heads)] = _spec_and_batches(octo, 6, [[4, 9, 0, 13, 2, 6]], 82)
+    solo = octo.Pipeline(spec)
+    _plant(solo, heads)
+    want = {}
+    for n in range(1, 7):
+        solo.submit(frames[:n])
+        solo.run()
+        want[n] = solo.collect()[1].tobytes()
+    solo.close()
+    n_cu = octo.device_cu_count()
+    streams = [octo.stream_create_range(0, n_cu) for _ in range(3)]
+    pipes = [octo.Pipeline(spec) for _ in range(3)]
+    for P in pipes:
+        _plant(P, heads)
+    torch.cuda.synchronize()
+    wrong = []
+
+    def drive(k):
+        rng = np.random.default_rng(k)
+        for r in range(40):
+            n = int(rng.integers(1, 7))
+            pipes[k].submit(frames[:n])
+            pipes[k].run(streams[k])
+            if pipes[k].collect()[1].tobytes() != want[n]:
+                wrong.append((k, r, n))
+    threads = [threading.Thread(target=drive, args=(k,)) for k in range(3)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not wrong
+    assert all(P.launch_counts()[1] > 0 for P in pipes)
+    for P in pipes:
+        P.close()
+    for s in streams:
+        octo.stream_destroy(s)
+
+
 def test_an_uncollected_batch_elsewhere_is_no_work_on_the_gpu(octo):
     import torch
     spec, [(frames, heads)] = _spec_and_batches(octo, 2, [[3, 5]], 79)
