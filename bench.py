@@ -56,7 +56,7 @@ def make_workload(name: str):
 # Template arguments of the 3x3 patch kernels that their id does not spell out.  By (pixel-tile digit, channel tile, vectors per LDS
 # row): wavefronts along the channels, stages of the weight ring, loader passes, workgroups per compute unit.
 MID = {(0, 32, 4): (1, 3, 3, 4), (0, 64, 4): (1, 3, 3, 4), (0, 64, 8): (1, 3, 6, 2), (0, 96, 4): (1, 3, 3, 3), (0, 128, 4): (1, 3, 3, 3),
-       (1, 64, 4): (1, 3, 6, 2), (1, 96, 4): (1, 3, 6, 2), (2, 64, 8): (2, 3, 4, 2), (3, 64, 8): (1, 3, 5, 2), (3, 128, 8): (2, 2, 5, 2)}
+       (1, 64, 4): (1, 3, 6, 2), (1, 96, 4): (1, 3, 6, 2), (1, 128, 4): (1, 3, 6, 2), (2, 64, 8): (2, 3, 4, 2), (3, 64, 8): (1, 3, 5, 2), (3, 128, 8): (2, 2, 5, 2)}
 # By (blocks of 32 channels, groups of 16 input channels): vectors per LDS row, loader passes, prefetch depth, workgroups per compute unit.
 STREAM3 = {(1, 2): (4, 6, 3, 2), (2, 2): (4, 3, 3, 3), (2, 3): (8, 6, 4, 2), (2, 4): (8, 6, 3, 2)}
 

@@ -624,16 +624,19 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   if (!vec || !a.scale || a.pair_view) return hipErrorInvalidValue;
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
   // 3x3 layers with enough tiles for every compute unit: input patch in LDS, slices of 64 channels, four workgroups per compute unit
-  // (256 -> 256 on 300 x 14 x 14: 39 us, slices of 128 channels 46); with plenty of tiles 128 channels per tile halve the fetch of
-  // the patch (256 -> 256 with residual on 1021 x 14 x 14: 125 us, 131 on 64 channels, 161 on the tiles below).  The lines, by 64 x 128
-  // tiles per compute unit: split-K : patch 14 x 14 x 256 at 0.48 8.8 : 9.0, at 0.81 11.4 : 9.2 (7 x 7 x 512 turns below 0.6:
-  // 16.3 : 13.1); 64 : 128 channels at 6 31.7 : 34.4, at 9.6 45.2 : 44.4, at 12 57.0 : 56.6, at 24 110 : 106
+  // (256 -> 256 on 300 x 14 x 14: 39 us, slices of 128 channels 46).  The lines, by 64 x 128 tiles per compute unit: split-K : patch
+  // 14 x 14 x 256 at 0.48 8.8 : 9.0, at 0.81 11.4 : 9.2 (7 x 7 x 512 turns below 0.6: 16.3 : 13.1).  128 x 256 tiles where they are the
+  // cheaper by whole tiles per compute unit, as in launch_mid (256 -> 256 with residual, 64 x 128 : 128 x 128 : 128 x 256, on 250 x 14 x 14
+  // 34.6 : 37.4 : 35.8, on 420 52.9 : 54.5 : 50.6, on 1021 119 : 115 : 113, on 4170 503 : 485 : 454); else 128 channels per tile
+  // (and for a single slice, which leaves a large tile mostly epilogue) halve the fetch of the patch from 12 on (at 6 34.6 : 37.4, at 12 112 : 110 (7 x 7 x 512), at 24 119 : 115)
   if (mid_fits(a) && a.Cout > 32 && a.Cin * 4 >= (a.Cin + 63) / 64 * 64 * 3) {
     const double per_cu = (double)M / 128 * ((a.Cout + 63) / 64) / num_cu;
-    const bool wide = per_cu >= 12 && (a.Cout + 127) / 128 * 2 == (a.Cout + 63) / 64;
+    const bool fits128 = (a.Cout + 127) / 128 * 2 == (a.Cout + 63) / 64;
+    const long long items = M / ((long long)a.Ho * a.Wo), huge = fits128 && a.Cin >= 128 ? mid_rounds(a, items, 128, 256, 384, num_cu) : 0;
     const hipError_t em = per_cu < 0.8 ? hipErrorNotSupported
-                          : wide      ? launch_mid_cfg<f8, 128, 128, 1, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm)
-                                      : launch_mid_cfg<f8, 64, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);
+                          : huge >= 2 && 3.5 * huge < mid_rounds(a, items, 64, 128, 192, num_cu) ? launch_mid_cfg<f8, 128, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm)
+                          : per_cu >= 12 && fits128 ? launch_mid_cfg<f8, 128, 128, 1, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm)
+                                                    : launch_mid_cfg<f8, 64, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);
     if (em != hipErrorNotSupported) return em;
   }
   const GeneralTile t = general_tile(a, M, num_cu, 2);

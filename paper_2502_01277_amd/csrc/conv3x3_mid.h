@@ -1,4 +1,4 @@
-// 3x3 / stride-1 / pad-1 convolution with the input patch of a tile in LDS, for tiles of 64 or 128 channels x 128 or 256 pixels.
+// 3x3 / stride-1 / pad-1 convolution with the input patch of a tile in LDS, for tiles of 32 to 128 channels x 64 to 256 pixels.
 //
 // What paces the general kernel (conv.hip) on these layers is the operand fetch from the L2s: every input pixel is
 // fetched once per kernel tap, and a workgroup that is alone on its compute unit gets 18 .. 25 bytes per clock.  Here
@@ -10,8 +10,16 @@
 //     A 64 x 128 tile then fetches 10.5 KB per 128-byte step instead of 24 KB;
 //   * the pixel operand of every tap is read from the patch with an address that the lane works out once per tile; taps
 //     outside the image point at rows of zeros, so that image borders need no padding rows in LDS;
-//   * the barrier of a step sits before the last group of its MFMAs, with the next step's first fragments read behind it.
-// Several workgroups share a compute unit, so that the prologue and epilogue of one overlap the K loop of another.
+//   * the barrier of a step sits before the last group of its MFMAs, with the next step's first fragments read behind it;
+//   * the stream of loads runs on across tiles: the last slice of a tile requests the first patch, weights and bias of the next one, and
+//     the residual two taps before the end.  Weight rows are taken in an order that leaves 16 consecutive channels of a pixel in one
+//     lane, so that results leave as 16-byte stores straight from registers, LDS stays the next tile's, and the stores drain beside
+//     its K loop.
+// What bounds it: the matrix pipe and the clock that the power leaves it (1.65 .. 2.1 GHz on random data), and on 28 x 28 maps the memory
+// traffic.  By cycle counts of 128 -> 128 on 4170 x 28 x 28 (64 x 256 tiles) with the epilogue through LDS and a prologue of its own
+// per tile, the K loop took 64 % of the time, addresses and prologue 20 %, the way out 16 %, and waiting for the residual as much as
+// a quarter of it all.  Before and after, us: that layer 1022 -> 863 without and 1227 -> 989 with residual, 256 -> 256 on 4170 x 14 x 14
+// 969 -> 813, 512 -> 512 on 4170 x 7 x 7 865 -> 743 (0.96 -> 1.30 PFLOP/s), 96 -> 96 on 32 x 160 x 160 214 -> 177.
 // LDS rows (weights: one output channel; patch: one pixel) are KV vectors of 16 bytes, vector v of row r in slot
 // v ^ ((r / (16 / KV)) % KV).  For patch pixels r counts without the halo columns (patch row * TW + column), so that the lanes of
 // consecutive output pixels stay on different banks where a tile row ends (with the halo counted, 64 -> 64 on 56 x 56 maps ran
@@ -35,16 +43,57 @@ struct MidGeom {
 };
 
 // Passes of the next slice's patch that are issued at tap t of a slice (all within the first six taps), and the loads that may
-// still be in flight when the operands of the step after tap t must have landed: those issued at the NST - 2 taps before t.
+// still be in flight when the operands of the step after tap t must have landed: those issued at the NST - 2 taps before t.  The
+// last slice of a tile also fetches `extra` vectors (bias, scales) of the next tile at tap 0.
 constexpr int mid_ppt(int maxp) { return (maxp + 5) / 6; }
 constexpr int mid_passes(int t, int maxp) {
   const int left = maxp - (t + 9) % 9 * mid_ppt(maxp);
   return left < 0 ? 0 : (left < mid_ppt(maxp) ? left : mid_ppt(maxp));
 }
-constexpr int mid_in_flight(int t, int nst, int la, int maxp) {
+constexpr int mid_in_flight(int t, int nst, int la, int maxp, int extra) {
   int n = 0;
-  for (int i = t + 2 - nst; i < t; ++i) n += la + mid_passes(i, maxp);
+  for (int i = t + 2 - nst; i < t; ++i) n += la + mid_passes(i, maxp) + (i == 0 ? extra : 0);
   return n;
+}
+
+// The first n of a vector's values to or from memory of any alignment.
+template <typename T>
+__device__ __forceinline__ void mid_store_pieces(T* p, u32x4 v, int n) {
+  constexpr int HN = 8 / (int)sizeof(T);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (n >= (h + 1) * HN && ((uintptr_t)p & 7) == 0) { *(u32x2*)(p + h * HN) = u32x2{v[2 * h], v[2 * h + 1]}; continue; }
+#pragma unroll
+    for (int e = 0; e < HN; ++e) {
+      const uint32_t w = v[2 * h + e * (int)sizeof(T) / 4] >> (e * (int)sizeof(T) % 4 * 8);
+      if (h * HN + e >= n) continue;
+      if constexpr (sizeof(T) == 1) p[h * HN + e].bits = (uint8_t)w;
+      else p[h * HN + e] = __builtin_bit_cast(T, (uint16_t)w);
+    }
+  }
+}
+template <typename T>
+__device__ __forceinline__ u32x4 mid_load_pieces(const T* p, int n) {
+  constexpr int HN = 8 / (int)sizeof(T);
+  u32x4 v = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (n >= (h + 1) * HN && ((uintptr_t)p & 7) == 0) {
+      const u32x2 w = *(const u32x2*)(p + h * HN);
+      v[2 * h] = w[0]; v[2 * h + 1] = w[1];
+      continue;
+    }
+#pragma unroll
+    for (int e = 0; e < HN; ++e) {
+      uint32_t w = 0u;
+      if (h * HN + e < n) {
+        if constexpr (sizeof(T) == 1) w = p[h * HN + e].bits;
+        else w = __builtin_bit_cast(uint16_t, p[h * HN + e]);
+      }
+      v[2 * h + e * (int)sizeof(T) / 4] |= w << (e * (int)sizeof(T) % 4 * 8);
+    }
+  }
+  return v;
 }
 
 // BC x BP: tile; WC: wavefronts along the channels (4 / WC along the pixels); KV: vectors of 16 bytes per LDS row; NST: stages
@@ -60,12 +109,16 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   constexpr int FV = ES == 1 ? 2 : 1;                    // vectors per operand fragment
   constexpr int ZROW = MAXP * RP - RPW;                  // last rows of a patch buffer, kept zero (the host leaves them free)
   constexpr int NTAP = 9;
+  constexpr int HV = 16 / VN;                            // vectors of a lane's 16 consecutive output channels of a 32-channel block
+  constexpr int PJ = TC * TP * HV <= 8 ? TP : 1;         // pixel blocks whose residual is requested before the K loop ends
+  constexpr int NSTO = TC * TP * HV, NRES = TC * PJ * HV, NB = ES == 1 ? 2 : 1;
+  constexpr bool PACKED = TC * TP >= 8;                  // two patch offsets per register where accumulators leave few
+  constexpr int BW = PACKED ? (TP + 1) / 2 : TP;
+  constexpr int RTAP = NTAP - NST;                       // tap of the last slice that requests the residual
   static_assert(BC % 32 == 0 && TC >= 1 && TP >= 1 && (KK == 1 || KK % 2 == 0) && NST >= 2 && NST <= 4, "tile shape");
-  constexpr int OPITCH = BC * ES + 16;
-  constexpr int OPER = NST * STAGE + 2 * PATCH, OSTAGE = BP * OPITCH;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[OPER > OSTAGE ? OPER : OSTAGE];
-  __shared__ float sBias[BC];
-  __shared__ float sScale[ES == 1 ? BC : 1];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE + 2 * PATCH];
+  __shared__ __attribute__((aligned(16))) float sBias[2][THREADS];               // of this tile and the next
+  __shared__ __attribute__((aligned(16))) float sScale[2][ES == 1 ? THREADS : 1];
   unsigned char* ring = smem;
   unsigned char* patch = smem + NST * STAGE;
 
@@ -86,45 +139,107 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   const int rsw = (l32 / RPW) % KV;
   const unsigned lds_ring = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)ring + (unsigned)wave * 1024u));
   const unsigned lds_patch = lds_ring + NST * STAGE;
+  const unsigned lds_bias = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)&sBias[0][0] + (unsigned)wave * 256u));
+  const unsigned lds_scale = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)&sScale[0][0] + (unsigned)wave * 256u));
   const long long w_bytes = (long long)a.w_rows * a.Kp * ES;
   const int w_len = (int)(w_bytes < BUF_MAX ? w_bytes : BUF_MAX);
   const bool is_silu = a.act == OCTO_ACT_SILU;
   const float act_lo = a.act == OCTO_ACT_RELU ? 0.0f : -INFINITY;
+  // outputs and residuals in whole aligned vectors; anything else is written and read in pieces
+  const bool vec_out = ((a.Cout | a.y_ld | a.y_coff) % VN) == 0 && ((uintptr_t)a.y & 15) == 0;
+  const bool vec_res = a.res && ((a.Cout | a.res_ld | a.res_coff) % VN) == 0 && ((uintptr_t)a.res & 15) == 0;
 
   const int per_die = (n_tiles + 7) >> 3;      // see conv_mfma_kernel: one contiguous chunk of the tile list per die
-  for (int t = blockIdx.x; t < per_die * 8; t += gridDim.x) {
-    const int tile = (t & 7) * per_die + (t >> 3);
-    if (tile >= n_tiles) continue;
-    const unsigned tpx = fast_div((unsigned)tile, gm.div_tc);
-    const int c0 = (int)((unsigned)tile - tpx * (unsigned)tiles_c) * BC;
-    const unsigned tv = fast_div(tpx, gm.div_tx);
-    const int x0 = (int)(tpx - tv * (unsigned)gm.tiles_x) * gm.TW;
-    const int v0 = (int)tv * gm.TH;
+  const int t_end = per_die * 8;
+  auto next_valid = [&](int t) -> int {
+    while (t < t_end && (t & 7) * per_die + (t >> 3) >= n_tiles) t += gridDim.x;
+    return t;
+  };
+  auto locate = [&](int t, int& v0, int& x0, int& c0) __attribute__((always_inline)) {
+    const unsigned tile = (unsigned)((t & 7) * per_die + (t >> 3));
+    const unsigned tpx = fast_div(tile, gm.div_tc), tv = fast_div(tpx, gm.div_tx);
+    c0 = (int)(tile - tpx * (unsigned)tiles_c) * BC;
+    x0 = (int)(tpx - tv * (unsigned)gm.tiles_x) * gm.TW;
+    v0 = (int)tv * gm.TH;
+  };
 
-    // loaders: this lane's vector of every pass of the patch (relative to the first patch row) and of the weight rows
+  // Loaders.  Patch: this lane's vector of every pass, relative to the first patch row of a tile; vectors past `channels` of a slice
+  // read as zeros.  (Lane values are opaque to the compiler, which would otherwise keep the tile-independent part of every
+  // address in registers of its own.)
+  int poff[MAXP], woff[LA], p_len = 0;
+  void* p_base = nullptr;
+  auto patch_of = [&](int v0, int x0, int channels) __attribute__((always_inline)) {
     const long long pix0 = (long long)(v0 - 1) * W;                  // may be -W: lanes of that row are out of range
     const long long rem_bytes = (((long long)a.n * H * W - pix0) * a.x_ld - a.x_coff) * ES;
-    const int p_len = (int)(rem_bytes < BUF_MAX ? rem_bytes : BUF_MAX);
-    void* p_base = (void*)(xg + pix0 * a.x_ld);
-    // (opaque to the compiler, which would otherwise keep the tile-independent part of every address in registers of its own)
-    int poff[MAXP], woff[LA], lrow = ld_row, lpix = wp * (TP * 32) + l32;
-    asm volatile("" : "+v"(lrow), "+v"(lpix));
-    auto patch_offsets = [&](int channels) __attribute__((always_inline)) {      // vectors past that many channels of a slice read as zeros
+    p_len = (int)(rem_bytes < BUF_MAX ? rem_bytes : BUF_MAX);
+    p_base = (void*)(xg + pix0 * a.x_ld);
+    int lrow = ld_row;
+    asm volatile("" : "+v"(lrow));
 #pragma unroll
-      for (int i = 0; i < MAXP; ++i) {
-        const int pp = i * RP + lrow;
-        const int pr = (int)fast_div((unsigned)pp, gm.div_pw), pc = pp - pr * gm.PW;
-        const int v = v0 - 1 + pr, x = x0 - gm.halo + pc;
-        const int vec = (tid % KV) ^ ((int)((unsigned)(pr * gm.TW + pc) / RPW) % KV);
-        const bool ok = pr < gm.TH + 2 && (unsigned)v < (unsigned)n_rows && (unsigned)x < (unsigned)W && vec * VN < channels;
-        poff[i] = ok ? ((pr * W + x) * a.x_ld + vec * VN) * ES : OOB;
-      }
-    };
-    patch_offsets(a.Cin);
+    for (int i = 0; i < MAXP; ++i) {
+      const int pp = i * RP + lrow;
+      const int pr = (int)fast_div((unsigned)pp, gm.div_pw), pc = pp - pr * gm.PW;
+      const int v = v0 - 1 + pr, x = x0 - gm.halo + pc;
+      const int vec = (tid % KV) ^ ((int)((unsigned)(pr * gm.TW + pc) / RPW) % KV);
+      const bool ok = pr < gm.TH + 2 && (unsigned)v < (unsigned)n_rows && (unsigned)x < (unsigned)W && vec * VN < channels;
+      poff[i] = ok ? ((pr * W + x) * a.x_ld + vec * VN) * ES : OOB;
+    }
+  };
+  // Weights: LDS row m of a 32-row block holds channel 16 ((m / 4) % 2) + 4 (m / 8) + m % 4 of the block: register 4 q + e of half g of
+  // a wavefront's result is row 8 q + 4 g + e, so a lane gets 16 consecutive channels of its pixel
+  {
+    const int m = ld_row & 31, ch = (ld_row & ~31) + 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3);
 #pragma unroll
-    for (int i = 0; i < LA; ++i) woff[i] = ld_row + RP * i < BC ? ((c0 + ld_row + RP * i) * a.Kp + lkv * VN) * ES : OOB;
+    for (int i = 0; i < LA; ++i) woff[i] = ld_row + RP * i < BC ? ((ch + RP * i) * a.Kp + lkv * VN) * ES : OOB;
+  }
+  // weights of the channels from c0 on, (slice, tap), into ring stage st; nothing is fetched if !any
+  auto issue_w = [&](int c0, int sl, int tap, int st, bool any) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, any ? w_len : 0, BUF_FLAGS);
+    const int koff = any ? (c0 * a.Kp + tap * a.Cin + sl * BK) * ES : 0;
+#pragma unroll
+    for (int i = 0; i < LA; ++i)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                   :: "s"(lds_ring + st * STAGE + i * 4096), "v"(woff[i]), "s"(rs), "s"(koff) : "memory");
+  };
+  // passes of a slice's patch into buffer buf
+  auto issue_p = [&](int buf, int sl, int from, int count, bool any) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p_base, 0, any ? p_len : 0, BUF_FLAGS);
+    const int koff = any ? sl * BK * ES : 0;
+#pragma unroll
+    for (int i = 0; i < MAXP; ++i)
+      if (i >= from && i < from + count)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :: "s"(lds_patch + buf * PATCH + i * 4096), "v"(poff[i]), "s"(rs), "s"(koff) : "memory");
+  };
+  auto issue_bias = [&](int c0, int buf, bool any) __attribute__((always_inline)) {       // (and scales); padded to whole tiles like the weights
+    const int off = tid < BC ? (c0 + tid) * 4 : OOB, len = any ? a.w_rows * 4 : 0;
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, len, BUF_FLAGS);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_bias + buf * (THREADS * 4)), "v"(off), "s"(rb) : "memory");
+    if constexpr (ES == 1) {
+      const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((void*)a.scale, 0, len, BUF_FLAGS);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_scale + buf * (THREADS * 4)), "v"(off), "s"(rc) : "memory");
+    }
+  };
+
+  int t = next_valid(blockIdx.x);
+  if (t >= t_end) return;
+  int v0, x0, c0;
+  locate(t, v0, x0, c0);
+  patch_of(v0, x0, a.Cin);
+  issue_p(0, 0, 0, MAXP, true);
+  constexpr int AHEAD = KK == 1 ? NST - 1 : NST;         // steps whose weights are requested ahead
+#pragma unroll
+  for (int d = 0; d < AHEAD; ++d) issue_w(c0, 0, d, d, true);
+  issue_bias(c0, 0, true);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+
+  int rd = 0, pbuf = 0, bbuf = 0;                        // ring stage of the current step, patch buffer of the current slice, bias buffer
+  bool stored = false;                                   // the vmcnt of the first steps counts the stores of the tile before
+  for (;;) {
     // byte offset inside a patch buffer of this lane's first vector, per tap and block
-    int baddr[NTAP][TP];
+    int baddr[NTAP][BW], lpix = wp * (TP * 32) + l32;
+    asm volatile("" : "+v"(lpix));
 #pragma unroll
     for (int j = 0; j < TP; ++j) {
       const int q = lpix + j * 32;
@@ -137,7 +252,9 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
         const int r = tap / 3, s = tap % 3 - 1;
         const bool in = ok && (unsigned)(yy + r - 1) < (unsigned)H && (unsigned)(x + s) < (unsigned)W;
         const int px = (ty + r) * gm.PW + tx + s + gm.halo, pos = px - (ty + r) * (gm.PW - gm.TW);
-        baddr[tap][j] = (in ? px : ZROW + (px & (RPW - 1))) * ROW + ((g ^ ((pos >> (RPW == 2 ? 1 : 2)) & (KV - 1))) << 4);
+        const int off = (in ? px : ZROW + (px & (RPW - 1))) * ROW + ((g ^ ((pos >> (RPW == 2 ? 1 : 2)) & (KV - 1))) << 4);
+        if (!PACKED) baddr[tap][j] = off;
+        else baddr[tap][j / 2] = j % 2 ? baddr[tap][j / 2] | off << 16 : off;
       }
     }
 
@@ -149,76 +266,89 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    __syncthreads();   // the previous tile's LDS reads are done
-    if (tid < BC) sBias[tid] = a.bias[c0 + tid];
-    if constexpr (ES == 1) { if (tid < BC) sScale[tid] = a.scale[c0 + tid]; }
-
-    // weights of (slice SL, tap TAP) into ring stage ST; nothing is fetched past the last slice
-    auto issue_w = [&](int sl, int tap, int st) __attribute__((always_inline)) {
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, sl < n_slices ? w_len : 0, BUF_FLAGS);
-      const int koff = (tap * a.Cin + sl * BK) * ES;
-#pragma unroll
-      for (int i = 0; i < LA; ++i)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     :: "s"(lds_ring + st * STAGE + i * 4096), "v"(woff[i]), "s"(rs), "s"(koff) : "memory");
-    };
-    // passes of slice sl's patch
-    auto issue_p = [&](int sl, int from, int count) __attribute__((always_inline)) {
-      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p_base, 0, sl < n_slices ? p_len : 0, BUF_FLAGS);
-      const int koff = sl * BK * ES;
-#pragma unroll
-      for (int i = 0; i < MAXP; ++i)
-        if (i >= from && i < from + count)
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                       :: "s"(lds_patch + (sl & 1) * PATCH + i * 4096), "v"(poff[i]), "s"(rs), "s"(koff) : "memory");
-    };
     u32x4 fa[2][TC][FV], fb[2][TP][FV];
     const int arow = (wc * (TC * 32) + l32) * ROW;
-    auto frags = [&](int set, int st, const int (&ba)[TP], int pbuf, int kq) __attribute__((always_inline)) {
+    auto frags = [&](int set, int st, const int (&ba)[BW], int buf, int kq) __attribute__((always_inline)) {
       const unsigned char* pa = ring + st * STAGE + arow;
-      const unsigned char* pb = patch + pbuf * PATCH;
+      const unsigned char* pb = patch + buf * PATCH;
 #pragma unroll
       for (int h = 0; h < FV; ++h) {
         const int v = (kq * FV + h) * 2;
 #pragma unroll
         for (int i = 0; i < TC; ++i) fa[set][i][h] = *(const u32x4*)(pa + i * (32 * ROW) + (((v + g) ^ rsw) << 4));
 #pragma unroll
-        for (int j = 0; j < TP; ++j) fb[set][j][h] = *(const u32x4*)(pb + (ba[j] ^ (v << 4)));
+        for (int j = 0; j < TP; ++j) fb[set][j][h] = *(const u32x4*)(pb + ((PACKED ? (j % 2 ? (int)((unsigned)ba[j / 2] >> 16) : ba[j / 2] & 0xFFFF) : ba[j]) ^ (v << 4)));
+      }
+    };
+    // output and residual: offset of this lane's first channel from the tile's first pixel, per pixel block
+    const int cw = c0 + wc * (TC * 32) + g * 16;
+    const long long pix0 = (long long)v0 * W + x0;
+    auto pixel_off = [&](int j, int ld) __attribute__((always_inline)) -> int {
+      const int q = lpix + j * 32;
+      const int ty = (int)fast_div((unsigned)q, gm.div_tw), tx = q - ty * gm.TW;
+      return ty < gm.TH && v0 + ty < n_rows && x0 + tx < W ? ((ty * W + tx) * ld + cw) * ES : OOB;
+    };
+    u32x4 rv[TP][TC][HV];
+    auto load_res = [&](int from, int to) __attribute__((always_inline)) {
+      const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc((void*)((const T*)a.res + a.res_coff + pix0 * a.res_ld), 0, (int)BUF_MAX, BUF_FLAGS);
+#pragma unroll
+      for (int j = 0; j < TP; ++j) {
+        if (j < from || j >= to) continue;
+        const int off = pixel_off(j, a.res_ld);
+#pragma unroll
+        for (int i = 0; i < TC; ++i)
+#pragma unroll
+          for (int h = 0; h < HV; ++h)
+            rv[j][i][h] = __builtin_amdgcn_raw_buffer_load_b128(rr, cw + i * 32 + h * VN < a.Cout ? off + i * 32 * ES + h * 16 : OOB, 0, 0);
       }
     };
 
-    issue_p(0, 0, MAXP);
-    constexpr int AHEAD = KK == 1 ? NST - 1 : NST;         // steps whose weights are requested up front
-#pragma unroll
-    for (int d = 0; d < AHEAD; ++d) issue_w(0, d, d);
-    if constexpr (KK > 1) {
-      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NST - 1) * LA) : "memory");
-      __builtin_amdgcn_s_barrier();
-      frags(0, 0, baddr[0], 0, 0);
-    }
-    int rd = 0;                                // ring stage of the current step
-    auto step = [&](auto tapc, int sl) __attribute__((always_inline)) {
-      constexpr int TAP = decltype(tapc)::value, NEXT = (TAP + 1) % NTAP, LTAP = (TAP + NST) % NTAP;
+    int vn0 = 0, xn0 = 0, cn0 = 0;                       // the next tile, whose operands are requested during the last slice
+    bool more = false;
+    // Waits until the operands of the step after tap TAP of a slice have landed.  In program order later than those: the loads of
+    // the NST - 2 taps before, the residual's after tap RTAP of the last slice, and, in the first steps, the stores of the tile before
+    auto landed = [&](auto tapc, auto lastc, bool first) __attribute__((always_inline)) {
+      constexpr int TAP = decltype(tapc)::value;
+      constexpr bool LAST = decltype(lastc)::value;
+      constexpr int N = mid_in_flight(TAP, NST, LA, MAXP, LAST ? NB : 0);
+      constexpr bool AFTER_RES = LAST && TAP > RTAP, AFTER_STORES = TAP < NST - 1;
+      if constexpr (AFTER_STORES) {
+        if (first) { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N + NSTO) : "memory"); return; }
+      }
+      if constexpr (AFTER_RES) {
+        if (vec_res) { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N + NRES) : "memory"); return; }
+      }
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory");
+    };
+    auto step = [&](auto tapc, auto lastc, int sl) __attribute__((always_inline)) {
+      constexpr int TAP = decltype(tapc)::value, NEXT = (TAP + 1) % NTAP;
+      constexpr bool LAST = decltype(lastc)::value;
       const int cur = NTAP % NST == 0 ? TAP % NST : rd;
       const int nxt = NTAP % NST == 0 ? NEXT % NST : (rd + 1 == NST ? 0 : rd + 1);
+      // loads that go out at this tap: the next slice's patch, weights AHEAD steps on, both of the next tile after the last slice
+      auto issue = [&](int st) __attribute__((always_inline)) {
+        issue_p(pbuf ^ 1, LAST ? 0 : sl + 1, TAP * mid_ppt(MAXP), mid_passes(TAP, MAXP), !LAST || more);
+        constexpr bool WRAP = TAP + AHEAD >= NTAP;
+        issue_w(LAST && WRAP ? cn0 : c0, WRAP ? (LAST ? 0 : sl + 1) : sl, (TAP + AHEAD) % NTAP, st, !(LAST && WRAP) || more);
+        if constexpr (LAST && TAP == 0) issue_bias(cn0, bbuf ^ 1, more);
+        if constexpr (LAST && TAP == RTAP) { if (vec_res) load_res(0, PJ); }
+      };
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {
         if constexpr (KK == 1) {
           // a single group per step: its fragments are read here, and the loads go to the stage that the previous step has left
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(mid_in_flight(TAP, NST, LA, MAXP)) : "memory");
+          landed(tapc, lastc, stored && sl == 0);
           __builtin_amdgcn_s_barrier();
-          frags(0, cur, baddr[TAP], sl & 1, 0);
-          issue_p(sl + 1, TAP * mid_ppt(MAXP), mid_passes(TAP, MAXP));
-          issue_w(TAP + NST - 1 >= NTAP ? sl + 1 : sl, (TAP + NST - 1) % NTAP, NTAP % NST == 0 ? (TAP + NST - 1) % NST : (rd == 0 ? NST - 1 : rd - 1));
+          frags(0, cur, baddr[TAP], pbuf, 0);
+          issue(NTAP % NST == 0 ? (TAP + NST - 1) % NST : (rd == 0 ? NST - 1 : rd - 1));
         } else if (kk < KK - 1) {
-          frags((kk + 1) & 1, cur, baddr[TAP], sl & 1, kk + 1);
+          frags((kk + 1) & 1, cur, baddr[TAP], pbuf, kk + 1);
         } else {
           // this wavefront holds all it needs of the stage in registers, and the next step's operands have landed
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(mid_in_flight(TAP, NST, LA, MAXP)) : "memory");
+          landed(tapc, lastc, stored && sl == 0);
           __builtin_amdgcn_s_barrier();
-          frags(0, nxt, baddr[NEXT], TAP == NTAP - 1 ? (sl + 1) & 1 : sl & 1, 0);
-          issue_p(sl + 1, TAP * mid_ppt(MAXP), mid_passes(TAP, MAXP));
-          issue_w(TAP + NST >= NTAP ? sl + 1 : sl, LTAP, cur);
+          if constexpr (!(LAST && TAP == NTAP - 1)) frags(0, nxt, baddr[NEXT], TAP == NTAP - 1 ? pbuf ^ 1 : pbuf, 0);
+          issue(cur);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -232,85 +362,81 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
       }
       rd = nxt;
     };
-    for (int sl = 0; sl < n_slices; ++sl) {
-      // the last slice, fetched from here on, may be partial: its missing channels are zeros (the weights there anything finite)
-      if (sl + 2 == n_slices && a.Cin % BK) patch_offsets(a.Cin % BK);
-      step(std::integral_constant<int, 0>{}, sl); step(std::integral_constant<int, 1>{}, sl); step(std::integral_constant<int, 2>{}, sl);
-      step(std::integral_constant<int, 3>{}, sl); step(std::integral_constant<int, 4>{}, sl); step(std::integral_constant<int, 5>{}, sl);
-      step(std::integral_constant<int, 6>{}, sl); step(std::integral_constant<int, 7>{}, sl); step(std::integral_constant<int, 8>{}, sl);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // loads issued past the last step wrote zeros into the ring
-    __syncthreads();
-
-    // epilogue: through LDS as [pixel][channel], so that residual and output move in 16-byte pieces of whole rows
-    constexpr int VPR = BC / VN, PPP = THREADS / VPR;      // vectors per pixel, pixels per pass
-    constexpr int NPASS = (BP + PPP - 1) / PPP;
-    const int ov = tid % VPR, opr = tid / VPR;
-    const int oc = c0 + ov * VN;
-    auto out_pixel = [&](int pl) -> int {                  // pixel of the batch, or -1
-      const int ty = (int)fast_div((unsigned)pl, gm.div_tw), tx = pl - ty * gm.TW;
-      return ty < gm.TH && v0 + ty < n_rows && x0 + tx < W && oc < a.Cout && (THREADS % VPR == 0 || opr < PPP) ? (v0 + ty) * W + x0 + tx : -1;
-    };
-    const bool whole = oc + VN <= a.Cout;
-    const bool vec_out = whole && ((a.y_ld | a.y_coff) % VN) == 0 && ((uintptr_t)a.y & 15) == 0;
-    const bool vec_res = whole && ((a.res_ld | a.res_coff) % VN) == 0 && ((uintptr_t)a.res & 15) == 0;
-    if (a.res) {
+    auto slice = [&](auto lastc, int sl) __attribute__((always_inline)) {
+      if constexpr (PACKED) {        // opaque: the unpacked offsets would otherwise be kept in registers of their own
 #pragma unroll
-      for (int ps = 0; ps < NPASS; ++ps) {
-        const int pl = ps * PPP + opr, p = out_pixel(pl);
-        if (p < 0) continue;
-        const T* r = (const T*)a.res + (size_t)p * a.res_ld + a.res_coff + oc;
-        T* o = (T*)(smem + pl * OPITCH + ov * 16);
-        if (vec_res) *(u32x4*)o = *(const u32x4*)r;
-        else
-#pragma unroll 1
-          for (int e = 0; e < VN && oc + e < a.Cout; ++e) o[e] = r[e];
+        for (int tap = 0; tap < NTAP; ++tap)
+#pragma unroll
+          for (int j = 0; j < BW; ++j) asm volatile("" : "+v"(baddr[tap][j]));
       }
-      __syncthreads();
+      step(std::integral_constant<int, 0>{}, lastc, sl); step(std::integral_constant<int, 1>{}, lastc, sl); step(std::integral_constant<int, 2>{}, lastc, sl);
+      step(std::integral_constant<int, 3>{}, lastc, sl); step(std::integral_constant<int, 4>{}, lastc, sl); step(std::integral_constant<int, 5>{}, lastc, sl);
+      step(std::integral_constant<int, 6>{}, lastc, sl); step(std::integral_constant<int, 7>{}, lastc, sl); step(std::integral_constant<int, 8>{}, lastc, sl);
+      pbuf ^= 1;
+    };
+    if constexpr (KK > 1) frags(0, rd, baddr[0], pbuf, 0);
+    for (int sl = 0; sl + 1 < n_slices; ++sl) {
+      // the last slice, fetched from here on, may be partial: its missing channels are zeros (the weights there anything finite)
+      if (sl + 2 == n_slices && a.Cin % BK) patch_of(v0, x0, a.Cin % BK);
+      slice(std::false_type{}, sl);
     }
+    t = next_valid(t + gridDim.x);
+    more = t < t_end;
+    if (more) { locate(t, vn0, xn0, cn0); patch_of(vn0, xn0, a.Cin); }
+    slice(std::true_type{}, n_slices - 1);
+
+    // epilogue, from registers: lane (l32, g) holds channels 16 g + 4 q + e of each 32-channel block of its pixel
+    if constexpr (PJ < TP) { if (vec_res) load_res(PJ, TP); }
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)((T*)a.y + a.y_coff + pix0 * a.y_ld), 0, (int)BUF_MAX, BUF_FLAGS);
+    const int cl = wc * (TC * 32) + g * 16;
     with_epilogue_mode(a.res ? a.res_mode : OCTO_RES_NONE, is_silu, [&](auto res_c, auto silu_c) __attribute__((always_inline)) {
     constexpr int RES = decltype(res_c)::value;
     constexpr bool SILU = decltype(silu_c)::value;
 #pragma unroll
     for (int j = 0; j < TP; ++j) {
-      const int pl = wp * (BP / WP) + j * 32 + l32;
+      const int yo = pixel_off(j, a.y_ld);
 #pragma unroll
-      for (int i = 0; i < TC; ++i) {
-        const int cblk = wc * (BC / WC) + i * 32 + g * 4;
+      for (int i = 0; i < TC; ++i)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          T* o = (T*)(smem + pl * OPITCH) + cblk + q * 8;
-          floatx4 rv = floatx4{0.f, 0.f, 0.f, 0.f}, v;
-          if (RES != OCTO_RES_NONE) rv = load4<T>(o);
-          const floatx4 b4 = *(const floatx4*)&sBias[cblk + q * 8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = ES == 1 ? acc[i][j][q * 4 + e] * sScale[cblk + q * 8 + e] : acc[i][j][q * 4 + e];
-            if (ES == 1) rv[e] *= a.res_scale;
+        for (int h = 0; h < HV; ++h) {
+          const int c = cw + i * 32 + h * VN;              // first channel of the vector
+          u32x4 rvec = {0u, 0u, 0u, 0u}, out;
+          if constexpr (RES != OCTO_RES_NONE) {
+            if (vec_res) rvec = rv[j][i][h];
+            else if (yo != OOB) rvec = mid_load_pieces<T>((const T*)a.res + a.res_coff + pix0 * a.res_ld + (pixel_off(j, a.res_ld) / ES - cw + c), a.Cout - c);
           }
-          v = finish4<RES, SILU>(v, b4, rv, act_lo);
-          if constexpr (ES == 1) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= a.y_inv_scale;
+          for (int q = 0; q < VN / 4; ++q) {
+            const int cq = cl + i * 32 + h * VN + q * 4;
+            const floatx4 b4 = *(const floatx4*)&sBias[bbuf][cq];
+            floatx4 v, r4 = floatx4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (RES != OCTO_RES_NONE) r4 = load4<T>((const T*)&rvec + q * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float av = acc[i][j][h * VN + q * 4 + e];
+              v[e] = ES == 1 ? av * sScale[bbuf][cq + e] : av;
+              if (ES == 1) r4[e] *= a.res_scale;
+            }
+            v = finish4<RES, SILU>(v, b4, r4, act_lo);
+            if constexpr (ES == 1) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] *= a.y_inv_scale;
+            }
+            store4<T>((T*)&out + q * 4, v);
           }
-          store4<T>(o, v);
+          if (vec_out) __builtin_amdgcn_raw_buffer_store_b128(out, ry, c < a.Cout ? yo + i * 32 * ES + h * 16 : OOB, 0, 0);
+          else if (yo != OOB) mid_store_pieces<T>((T*)a.y + a.y_coff + pix0 * a.y_ld + (yo / ES - cw + c), out, a.Cout - c);
+          __builtin_amdgcn_sched_barrier(0);               // one vector at a time: keeps the register demand low
         }
-      }
     }
     });
-    __syncthreads();
-#pragma unroll
-    for (int ps = 0; ps < NPASS; ++ps) {
-      const int pl = ps * PPP + opr, p = out_pixel(pl);
-      if (p < 0) continue;
-      T* y = (T*)a.y + (size_t)p * a.y_ld + a.y_coff + oc;
-      const T* o = (const T*)(smem + pl * OPITCH + ov * 16);
-      if (vec_out) *(u32x4*)y = *(const u32x4*)o;
-      else
-#pragma unroll 1
-        for (int e = 0; e < VN && oc + e < a.Cout; ++e) y[e] = o[e];
-    }
+    if (!more) break;
+    stored = vec_out;
+    if (!vec_out || (a.res && !vec_res)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); stored = false; }     // a number of accesses that is not known here
+    v0 = vn0; x0 = xn0; c0 = cn0;
+    bbuf ^= 1;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // loads issued past the last step write zeros into LDS
 }
 
 // Tile of at most BP pixels whose patch leaves four of `rows` LDS rows free: the split of the image width into equal columns and
@@ -347,7 +473,7 @@ hipError_t launch_mid_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* ker
   const long long tiles = ((n_rows + gm.TH - 1) / gm.TH) * gm.tiles_x * ((a.Cout + BC - 1) / BC);
   if (tiles <= 0) return hipSuccess;
   if (tiles >= 0x7FFFFFF0LL || n_rows * a.W >= 0x7FFFFFFFLL) return hipErrorNotSupported;
-  if ((long long)(gm.TH + 2) * a.W * a.x_ld * (int)sizeof(T) > 0x7FFFFFF0LL) return hipErrorNotSupported;     // 32-bit offsets inside a patch
+  if ((long long)(gm.TH + 2) * a.W * std::max(a.x_ld, std::max(a.y_ld, a.res ? a.res_ld : 0)) * (int)sizeof(T) > 0x7FFFFFF0LL) return hipErrorNotSupported;     // 32-bit offsets inside a tile
   if (kernel_id) *kernel_id = mid_kernel_id(BC, BP, KV, Elem<T>::N, MAXP, a.Cin, a.Cout);
   long long grid = (tiles + 7) / 8 * 8;
   const long long cap = ((long long)num_cu * MINB + 7) / 8 * 8;
@@ -365,30 +491,38 @@ inline bool mid_fits(const ConvArgs& a) {
          !a.pool_y && !a.up_y && a.split == 0;
 }
 
+// Tiles of one configuration for a layer with that many items, per compute unit and rounded up; 0 where no tile shape fits.
+inline long long mid_rounds(const ConvArgs& a, long long items, int BC, int BP, int rows, int num_cu) {
+  MidGeom gm{};
+  if (!mid_geometry(a, BC, BP, rows, &gm)) return 0;
+  const long long tiles = (items * a.H + gm.TH - 1) / gm.TH * gm.tiles_x * ((a.Cout + BC - 1) / BC);
+  return (tiles + num_cu - 1) / num_cu;
+}
+
 // Tile of a 16-bit layer with M output pixels, or hipErrorNotSupported where the split-K or general kernel is the better one
 // (measured on MI355X, bf16, us; layers of H x W x C -> C, by the number of images).  per_cu: 64 x 128 tiles per compute unit.
 //   * up to 64 channels and many pixels: conv3x3_stream_kernel;
 //   * below 0.35 the split-K kernel spreads the K loop of the few tiles over more wavefronts.  Against 64 x 64 tiles: 14 x 14 x 256 at
 //     0.22 9.0 : 9.5, at 0.36 11.0 : 9.7; 20 x 20 x 64 at 0.24 5.7 : 6.1, at 0.34 7.2 : 6.2; 40 x 40 x 128 at 0.20 6.7 : 7.2, at 0.29
 //     8.4 : 7.3; the long reduction of 7 x 7 x 512 turns later, at 0.43 16.5 : 19.2, at 0.60 24.7 : 19.9;
-//   * 64 x 64 tiles up to 0.8.  Against 64 x 128: 14 x 14 x 256 at 0.72 12.0 : 12.3, at 0.96 12.8 : 12.8, at 1.2 18.9 : 17.2;
-//     7 x 7 x 512 at 0.72 20.4 : 20.8, at 0.96 23.1 : 21.7;
-//   * reductions over at least 192 channels with fewer than six tiles per compute unit are paced by the operand fetch: slices of
-//     128 bytes (whole cache lines), and 64 x 64 tiles while those leave compute units idle.  256 -> 256 on 63 x 14 x 14: 19 us
-//     on 64 x 128 (general kernel 27), 512 -> 512 on 63 x 7 x 7: 22 us on 64 x 64 (split-K 29);
-//   * otherwise slices of 64 bytes, half the LDS and up to four workgroups per compute unit, which hide each other's prologue
-//     and epilogue: 64 -> 64 with residual on 64 x 80 x 80 46 us (general kernel 74).  Tiles of 256 pixels fetch the weights half
-//     as often and pay once there are plenty of them: 384 -> 384 on 32 x 40 x 40 116 us (64 x 128: 136, general kernel 156).
-//     From 96 channels that is at 12 (64 x 128 : 64 x 256): 28 x 28 x 128 at 8 43.7 : 44.6, at 12 61.8 : 60.3, at 20 99.7 : 93.9;
-//     56 x 56 x 96 -> 64 at 8.6 37.7 : 39.4, at 19 77.9 : 74.9.  From 192 channels it is a matter of rounds: 14 x 14 x 256, slices of 128
-//     bytes : 64 x 256, at 2.0 27.3 : 28.9, at 3.8 37.1 : 35.2, at 5.0 52.4 : 47.5, at 6.0 59.2 : 61.5, at 7.2 70.2 : 63.1, at 14
-//     128 : 127; the line at 6 is right on both sides of itself and 10 % off in the last third of a round below it;
+//   * 64 x 64 tiles up to 0.8.  Against 64 x 128: 14 x 14 x 256 at 0.79 13.0 : 13.4, at 1.0 19.8 : 18.1; 7 x 7 x 512 at 0.6 20.7 : 21.3, at 1.0
+//     36.2 : 30.1; 28 x 28 x 128 at 0.81 9.3 : 9.9, at 1.0 13.3 : 12.2;
 //   * tiles of 32 channels for layers with no more: 32 -> 32 with residual on 16 x 160 x 160 24 us (33).  From 0.8: 80 x 80 x 32 at 0.59 5.8
 //     on either, at 0.78 5.7 (general kernel 7.0);
-//   * tiles of 96 channels where those of 64 would pad: 96 -> 96 on 32 x 160 x 160 156 us (187), of 256 pixels from four per compute
-//     unit on (80 x 80 x 96, 128 : 256 pixels, 15.2 : 17.9 for 10 images, 36.6 : 37.4 for 30, 46.9 : 46.3 for 40, 89.4 : 86.2 for 80).
-// The two slice widths sum in different orders; M is taken for a count that stays the same from batch to batch (a.n_split), and
-// so do the results.
+//   * tiles of 96 channels where those of 64 would pad: 96 -> 96 on 32 x 160 x 160 177 us (64 x 256 218), of 256 pixels from four per
+//     compute unit on (80 x 80 x 96, 128 : 256 pixels, 15.2 : 17.9 for 10 images, 36.6 : 37.4 for 30, 46.9 : 46.3 for 40);
+//   * otherwise by estimated time: tiles per compute unit, rounded up, times what a tile costs beside a 64 x 128 one.  A launch whose
+//     compute units have to do one tile more takes that much longer, and large tiles are cheaper by the pixel (128 x 256: four
+//     wavefronts that hold all 128 channels read the weights half as often from LDS and the patch half as often from memory).
+//     14 x 14 x 256, 64 x 128 (128-byte slices) : 64 x 256 : 128 x 256, at 3.0 34.7 : 33.6 : 35.8, at 4.0 43.6 : 50.0 : 54.7, at 5.0 52.2 :
+//     50.4 : 55.9, at 6.0 59.8 : 64.2 : 59.0, at 8.0 78.2 : 77.7 : 85.3, at 10 94.1 : 98.7 : 87.6, at 24 227 : 221 : 211, at 40 383 : 363 :
+//     342; 7 x 7 x 512 at 10 175 : 184 : 159, at 40 696 : 669 : 623; 28 x 28 x 128 at 8 46.0 : 48.4 : 53.1, at 10 56.1 : 57.2 : 54.8, at 40 242 : 221 :
+//     209.  With less than two tiles per compute unit nothing overlaps a large tile's prologue and epilogue: 64 x 128 then.
+//     96 x 256 tiles where 128 would pad but 96 do not: 192 -> 192 on 32 x 80 x 80 123 us (64 x 256 134).
+// Reductions over at least 192 channels are paced by the operand fetch: 64 x 128 tiles take slices of 128 bytes (whole cache lines)
+// there, and of 64 bytes, half the LDS and up to four workgroups per compute unit elsewhere (28 x 28 x 128 at 2.0 16.0 : 18.8).
+// The two slice widths sum in different orders; the choice between them is made for a count that stays the same from batch to
+// batch (M, from a.n_split), and so the results do.
 template <typename T>
 hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (!mid_fits(a)) return hipErrorNotSupported;
@@ -399,25 +533,46 @@ hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s,
   if (a.Cout <= 32) return (double)M / 128 < 0.8 * num_cu ? hipErrorNotSupported : launch_mid_cfg<T, 32, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);
   const double per_cu = (double)M / 128 * ((a.Cout + 63) / 64) / num_cu;
   if (per_cu < 0.35) return hipErrorNotSupported;
-  if (pad32 == pad64) {
-    if (per_cu < 0.8) return launch_mid_cfg<T, 64, 64, 2, 8, 3, 4, 2>(a, num_cu, s, kernel_id, tm);
-    if (a.Cin >= 192 && per_cu < 6) {
+  const bool k8 = pad32 == pad64;
+  if (k8 && per_cu < 0.8) return launch_mid_cfg<T, 64, 64, 2, 8, 3, 4, 2>(a, num_cu, s, kernel_id, tm);
+  if ((a.Cout + 95) / 96 * 96 < (a.Cout + 63) / 64 * 64 && !(k8 && a.Cin >= 192 && per_cu < 6))
+    return M / 256 * ((a.Cout + 95) / 96) >= 4 * num_cu ? launch_mid_cfg<T, 96, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm)
+                                                        : launch_mid_cfg<T, 96, 128, 1, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm);
+  const bool fits128 = (a.Cout + 127) / 128 * 2 == (a.Cout + 63) / 64, long_k = a.Cin >= 192;
+  // the cheapest of the large tiles for that many items: 0 none, 1 64 x 256, 2 96 x 256, 3 128 x 256
+  auto large = [&](long long items, double* cost) -> int {
+    int best = 0;
+    auto offer = [&](int which, int bc, double c) {
+      const long long r = mid_rounds(a, items, bc, 256, 384, num_cu);
+      if (r >= 2 && c * r < *cost) { *cost = c * r; best = which; }
+    };
+    if (a.Cin >= 96) offer(1, 64, long_k ? 1.83 : 1.9);
+    if (long_k && !fits128 && a.Cout % 96 == 0) offer(2, 96, 2.56);
+    if (a.Cin >= 128 && fits128) offer(3, 128, long_k ? 3.26 : 3.5);
+    return best;
+  };
+  const long long hw = (long long)a.Ho * a.Wo, now = a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n;
+  if (k8 && long_k) {
+    double cost = (double)mid_rounds(a, M / hw, 64, 128, 192, num_cu);
+    if (!large(M / hw, &cost)) {
       // tiles whose patch fits five passes of the loader (whole images of up to 14 columns) save the sixth, which would fetch
       // nothing: 512 -> 512 on 200 x 7 x 7 51 us (56).  Same slices, so a running count may choose: 128 channels with plenty of
-      // tiles after all (64 : 128 channels, 7 x 7 x 512 at 18 300 : 313 us, at 24 397 : 389, at 30 497 : 502, at 48 814 : 780;
-      // 14 x 14 x 256 at 24 212 : 206, at 36 328 : 312)
+      // tiles after all (64 : 128 channels, 7 x 7 x 512 at 12 208 : 210, at 16 276 : 271, at 24 415 : 408, at 40 696 : 674)
       MidGeom g5{}, g6{};
       const bool five = mid_geometry(a, 64, 128, 160, &g5) && mid_geometry(a, 64, 128, 192, &g6) && g5.TH * g5.TW == g6.TH * g6.TW;
-      const double now = (double)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo / 128 * ((a.Cout + 63) / 64) / num_cu;
-      if (five && now >= 24 && a.Cout % 128 == 0) return launch_mid_cfg<T, 128, 128, 2, 8, 2, 5, 2>(a, num_cu, s, kernel_id, tm);
+      if (five && fits128 && (double)now * hw / 128 * ((a.Cout + 63) / 64) / num_cu >= 24)
+        return launch_mid_cfg<T, 128, 128, 2, 8, 2, 5, 2>(a, num_cu, s, kernel_id, tm);
       if (five) return launch_mid_cfg<T, 64, 128, 1, 8, 3, 5, 2>(a, num_cu, s, kernel_id, tm);
       return launch_mid_cfg<T, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
     }
   }
-  if ((a.Cout + 95) / 96 * 96 < (a.Cout + 63) / 64 * 64)
-    return M / 256 * ((a.Cout + 95) / 96) >= 4 * num_cu ? launch_mid_cfg<T, 96, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm)
-                                                        : launch_mid_cfg<T, 96, 128, 1, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm);
-  if (a.Cin >= 192 || (a.Cin >= 96 && per_cu >= 12)) return launch_mid_cfg<T, 64, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+  double cost = (double)mid_rounds(a, now, 64, 128, 192, num_cu) * (long_k ? 1.08 : 1.0);
+  if (cost == 0) cost = 1e30;
+  switch (large(now, &cost)) {
+    case 1: return launch_mid_cfg<T, 64, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+    case 2: return launch_mid_cfg<T, 96, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+    case 3: return launch_mid_cfg<T, 128, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+  }
   return launch_mid_cfg<T, 64, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);
 }
 

@@ -98,6 +98,25 @@ def test_patch_3x3_fp8(octo, n, h, w, cin, cout, res, bc):
     assert int(diff.max()) <= 1 and float((diff != 0).float().mean()) < 1e-3
 
 
+# Several tiles per workgroup, so that one tile's K loop runs into the next one's: large tiles, outputs and residuals in whole vectors
+# and in pieces.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", [
+    (860, 14, 14, 136, 120, nn.ACT_RELU, nn.RES_BEFORE_ACT, 8, 8, 1, 128, 64),     # 128 x 256, a quarter of the last slice, 8 channels short
+    (860, 14, 14, 128, 128, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 1, 1, 128, 64),      # the same, output rows of odd pitch
+    (860, 14, 14, 128, 124, nn.ACT_NONE, nn.RES_NONE, 0, 0, 1, 128, 64),           # half a vector at the end of a row
+    (14, 80, 80, 192, 192, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 1, 96, 64),        # 96 x 256 where 128 channels would pad
+    (1300, 3, 37, 56, 100, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 1, 0, 64, 64),       # 64 x 128 in pieces
+])
+def test_patch_3x3_tile_after_tile(octo, dtype, case):
+    test_patch_3x3_parity(octo, dtype, case)
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,res", [(430, 14, 14, 128, 256, True), (420, 14, 14, 144, 248, True), (860, 14, 14, 128, 128, False)])
+def test_patch_3x3_fp8_large_tiles(octo, n, h, w, cin, cout, res):
+    test_patch_3x3_fp8(octo, n, h, w, cin, cout, res, 1128)      # 128 channels x 256 pixels (digit 1); 248 channels leave in pieces of 8
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_patch_3x3_with_the_item_count_on_the_device(octo, dtype):
     """3x3 layers of a downstream model, whose item count stays on the device: a batch with a few hundred ROIs, then one with a few
