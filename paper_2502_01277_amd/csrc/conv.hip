@@ -26,6 +26,7 @@
 #include "mfma_common.h"
 #include "conv_ksplit.h"
 #include "conv3x3_mid.h"
+#include "conv_flow_choice.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -597,6 +598,29 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     if (em != hipErrorNotSupported) return em;
   }
   const bool pipe_ok = sizeof(T) == 2 && !a.up_y;      // (only the split-K kernel writes an upsampled copy)
+  if constexpr (sizeof(T) == 2) {
+    // conv_flow_kernel takes what has its form, except strided layers in one round of pipelined 64x64 tiles: 256 -> 512, stride 2 on
+    // 42 x 14 x 14 16.1 us here, 18.1 there, 128 -> 128, stride 2 on 8 x 80 x 80 10.5 : 11.1 (a step of such a tile is four matrix instructions
+    // per wavefront, fewer than the cursor's scalar ones).  Their order of summation is the same, so the running count may choose between
+    // those two; split-K or not is decided for M_split.
+    if (flow_fits(a)) {
+      const bool pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
+      auto stays = [&](long long m) {
+        const GeneralTile t = general_tile(a, m, num_cu, 1, pipe_ok);
+        return !pw && t.pipe && t.bc == 64 && t.bp == 64;
+      };
+      double us = 0;
+      int kf = -1;
+      if (!stays(M_split)) {
+        flow_choose(a, M_split, num_cu, &us);
+        kf = ksplit_best(a, M_split, 2, num_cu, us);
+      }
+      if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
+      if (stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
+      const int which = flow_choose(a, M, num_cu, &us);
+      return std::is_same<T, __bf16>::value ? launch_flow_bf16(which, a, num_cu, s, kernel_id, tm) : launch_flow_f16(which, a, num_cu, s, kernel_id, tm);
+    }
+  }
   const GeneralTile st = general_tile(a, M_split, num_cu, 1, pipe_ok);
   const int ks = st.pipe ? -1 : ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
   if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);

@@ -13,6 +13,7 @@
 // LDS rows (a pixel's or an output channel's K values) have an odd pitch in 16-byte vectors: reads of one vector of 32
 // rows hit all banks evenly.
 #include "mfma_common.h"
+#include "conv_flow_choice.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -233,6 +234,7 @@ hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipSt
     return hipErrorNotSupported;
   if (((a.Cin | a.x_ld | a.x_coff | a.Cout | a.y_ld | a.y_coff) & 7) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return hipErrorNotSupported;
   if (a.res && (((a.res_ld | a.res_coff) & 7) || ((uintptr_t)a.res & 15))) return hipErrorNotSupported;
+  if (flow_takes_1x1(a)) return hipErrorNotSupported;
   const long long M = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.Ho * a.Wo;
   // several channel tiles read the pixels several times and need more of them: with fewer than six blocks per compute unit the
   // general kernel's 64x64 tiles are faster (192 -> 192 on 14336 pixels 7.4 us, 8.9 here; 64 -> 256 on 10240: 6.1, 8.3)

@@ -225,13 +225,13 @@ __global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvAr
   if (t >= t_end) return;
   int v0, x0, c0;
   locate(t, v0, x0, c0);
+  issue_bias(c0, 0, true);
   patch_of(v0, x0, a.Cin);
   issue_p(0, 0, 0, MAXP, true);
   constexpr int AHEAD = KK == 1 ? NST - 1 : NST;         // steps whose weights are requested ahead
 #pragma unroll
   for (int d = 0; d < AHEAD; ++d) issue_w(c0, 0, d, d, true);
-  issue_bias(c0, 0, true);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"((AHEAD - 1) * LA) : "memory");
   __builtin_amdgcn_s_barrier();
 
   int rd = 0, pbuf = 0, bbuf = 0;                        // ring stage of the current step, patch buffer of the current slice, bias buffer

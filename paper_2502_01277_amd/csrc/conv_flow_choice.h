@@ -1,0 +1,63 @@
+// Which layers take conv_flow_kernel (conv_flow.h), and with which tile.  Host arithmetic only.
+#pragma once
+#include "octo_internal.h"
+#include <algorithm>
+
+namespace octo {
+
+// Does a 16-bit layer have the form that conv_flow_kernel takes?
+inline bool flow_fits(const ConvArgs& a) {
+  constexpr int VN = 8, ES = 2;
+  if (a.out_f32 || a.pair_view || a.pool_y || a.up_y || a.kh > 15 || a.kw > 15) return false;
+  if (((a.Cin | a.Cout | a.x_ld | a.x_coff | a.y_ld | a.y_coff) % VN) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return false;
+  if (a.res && (((a.res_ld | a.res_coff) % VN) || ((uintptr_t)a.res & 15))) return false;
+  if (a.split > 0 && a.split % 32) return false;
+  if (a.Cout <= 32 || a.K <= 64) return false;             // nothing to fill a tile with; the bias of the next tile needs two K steps
+  // 32-bit offsets: weights, and the pixels of a tile (256 of them) in every tensor
+  const long long ld = std::max(std::max(a.x_ld, a.y_ld), std::max(a.res ? a.res_ld : 0, a.split > 0 ? a.y2_ld : 0));
+  return (long long)a.w_rows * a.Kp * ES < 0x7FFFFFFFLL && 256 * ld * ES < 0x7FFFFFF0LL && (long long)a.n * a.Ho * a.Wo < 0x7FFFFF00LL &&
+         (2LL * a.H * a.W + 1024LL * a.stride_h * a.stride_w + (long long)a.pad_h * a.W + a.pad_w) * a.x_ld * ES < 0x7FFFFFF0LL;
+}
+
+// Time of a launch in us, fitted to 656 layers (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of
+// 64 x 128 per compute unit, bf16, 256 compute units; residual error 8 - 11 %): a constant, what the busiest compute unit does - its tiles,
+// rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the memory traffic.  Over those
+// layers the choice loses 1.3 % against always taking the fastest tile, and takes 0.88 of the time of the kernels it replaced
+// (128 x 256 and 64 x 64 tiles of the general kernel, pipelined: 0.87 and, for 1x1 layers, 0.84; its plain tiles 0.86; the streaming 1x1
+// kernel 0.83 from 128 input channels on).
+struct FlowCost { int bc, bp; double base, step, tile, latency, per_mb, any_step; };
+constexpr FlowCost FLOW_COST[8] = {
+    {64, 64, 3.73, 0.165, 0.22, 0.118, 0.040, 0.031},
+    {64, 128, 3.60, 0.258, 0.42, 0.091, 0.052, 0.065},
+    {128, 64, 3.65, 0.255, 0.52, 0.092, 0.035, 0.028},
+    {128, 128, 3.08, 0.442, 1.27, 0.000, 0.042, 0.076},
+    {96, 256, 2.93, 0.580, 1.59, 0.000, 0.064, 0.145},
+    {192, 128, 3.22, 0.554, 1.46, 0.000, 0.045, 0.064},
+    {128, 256, 3.00, 0.674, 2.06, 0.000, 0.065, 0.093},
+    {256, 128, 3.76, 0.653, 1.18, 0.000, 0.061, 0.053}};
+inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, int num_cu) {
+  const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
+  const double per_cu = (double)((tiles + num_cu - 1) / num_cu), nk = (a.K + 63) / 64;
+  const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
+  const double mb = 2e-6 * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
+  return c.base + per_cu * (nk * (c.step + (a.Cin % 64 ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * nk : 0.0) + c.per_mb * mb;
+}
+// The row of FLOW_COST with the smallest estimate for M output pixels.
+inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us) {
+  int best = 0;
+  for (int i = 0; i < 8; ++i) {
+    const double t = flow_cost_us(FLOW_COST[i], a, M, num_cu);
+    if (i == 0 || t < *us) { *us = t; best = i; }
+  }
+  return best;
+}
+// 1x1 / stride-1 layers that the streaming kernel (conv1x1.hip) leaves to this one: whole K steps, two or more (128 -> 128 on 64 x 40 x 40
+// 15.9 -> 12.7 us, 192 -> 192 on 41 x 80 x 80 40.8 -> 38.8, 192 -> 96 with residual on 20 x 80 x 80 23.0 -> 17.9).  Fewer or broken steps are
+// faster there (96 -> 192 on 41 x 40 x 40 11.4 : 14.5, 64 -> 256 on 16 x 32 x 32 8.0 and not possible here).  What adds a residual and
+// writes a channel slice of a wider tensor stays there too: no network here has such a layer, the tests of that kernel's edges do.
+inline bool flow_takes_1x1(const ConvArgs& a) { return a.Cin >= 128 && a.Cin % 64 == 0 && !(a.res && a.y_ld != a.Cout) && flow_fits(a); }
+
+hipError_t launch_flow_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
+hipError_t launch_flow_bf16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
+
+}  // namespace octo

@@ -320,16 +320,20 @@ constexpr ConvCost KSPLIT_COST[4] = {{32, 32, 8, 3.0, 0.75, 1.00, 0.07}, {32, 32
 constexpr ConvCost GENERAL_COST[4] = {{32, 128, 0, 3.9, 0.91, 0.80, 0.36}, {64, 64, 0, 3.7, 0.28, 0.84, 0.28},
                                       {64, 128, 0, 4.0, 1.32, 1.57, 0.12}, {128, 128, 0, 4.5, 1.27, 3.28, 0.19}};
 
-// Index of the split-K shape that beats the general kernel's bc x bp tile, or -1.  M: output pixels expected.
-inline int ksplit_choose(const ConvArgs& a, long long M, int es, int bc, int bp, int num_cu) {
-  double best = -1.0;
-  for (const ConvCost& g : GENERAL_COST) if (g.bc == bc && g.bp == bp) best = 0.97 * conv_cost_us(g, M, a.Cout, a.Kp * es, num_cu);
+// Index of the split-K shape with the smallest estimate below `best` us, or -1.  M: output pixels expected.
+inline int ksplit_best(const ConvArgs& a, long long M, int es, int num_cu, double best) {
   int pick = -1;
   for (int i = 0; i < 4; ++i) {
     const double t = conv_cost_us(KSPLIT_COST[i], M, a.Cout, a.Kp * es, num_cu);
     if (t < best) { best = t; pick = i; }
   }
   return pick;
+}
+// The one that beats the general kernel's bc x bp tile, or -1.
+inline int ksplit_choose(const ConvArgs& a, long long M, int es, int bc, int bp, int num_cu) {
+  double best = -1.0;
+  for (const ConvCost& g : GENERAL_COST) if (g.bc == bc && g.bp == bp) best = 0.97 * conv_cost_us(g, M, a.Cout, a.Kp * es, num_cu);
+  return ksplit_best(a, M, es, num_cu, best);
 }
 
 template <typename T, int TC, int TP, int NW, int KS>

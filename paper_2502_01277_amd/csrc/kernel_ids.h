@@ -11,6 +11,10 @@ constexpr int conv_kernel_id(int bc, int bp, int kv, int minb, bool vec, bool dm
   return 1000000000 + bc * 1000000 + bp * 1000 + kv * 100 + minb * 10 + (vec ? 1 : 0) + (dma ? 2 : 0) + (pipe ? 4 : 0);
 }
 
+// general form whose loads run across tiles (conv_flow.h), digits 12 M BBB PPP K: how addresses are made, channel tile, pixel tile, 16-byte
+// vectors per K step
+constexpr int flow_kernel_id(int bc, int bp, int kv, int mode) { return 1200000000 + mode * 10000000 + bc * 10000 + bp * 10 + kv; }
+
 // 3x3 layers with the input patch in LDS (conv3x3_mid.h), digits FF Q BBB CCC: family (17: more than 64 output channels, 18: up to
 // 64, 14: input channels not in whole slices), pixel tile (0: 128, 1: 256, 2: 64, 3: 128 with a patch of five passes), channel
 // tile, input channels whose patch the two buffers hold.  vn: values per 16-byte vector

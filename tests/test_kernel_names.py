@@ -78,6 +78,16 @@ def test_general_kernel(ids):
                 CTYPE[dt], ", ".join(map(str, a[:7])), ", ".join("true" if v else "false" for v in a[7:]))
 
 
+def test_kernels_whose_loads_run_across_tiles(tmp_path):
+    src = '#include "%s/kernel_ids.h"\nextern "C" int flow_kernel_id(int a, int b, int c, int d) { return octo::flow_kernel_id(a, b, c, d); }\n' % CSRC
+    (tmp_path / "ids.cpp").write_text(src)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-o", str(tmp_path / "ids.so"), str(tmp_path / "ids.cpp")], check=True)
+    fn = ctypes.CDLL(str(tmp_path / "ids.so")).flow_kernel_id
+    for _, (nt, bc, bp, wc, kv, nst, minb) in instances("launch_flow_cfg", "conv_flow.h"):
+        for mode in range(3):
+            assert bench.conv_name(fn(bc, bp, kv, mode), "bf16") == "octo::conv_flow_kernel<__bf16, %d, %d, %d, %d, %d, %d, %d, %d>" % (nt, bc, bp, wc, kv, nst, minb, mode)
+
+
 def test_an_unknown_id_has_a_name_too():
     for kid in (1403064128 + 4000000, 1804064128, 1700064999, 1899999999, 1499999999, 1805128128):
         for dt in CTYPE:
