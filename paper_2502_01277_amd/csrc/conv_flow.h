@@ -47,7 +47,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
   constexpr int NSTO = TC * TP * HV, NRES = TC * PJ * HV;
   static_assert(ES == 2 && KK >= 2 && KK % 2 == 0 && BP % RP == 0 && TC >= 1 && TP >= 1, "tile shape");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE];
-  __shared__ __attribute__((aligned(16))) float sBias[2][NT];               // of this tile and the next
+  __shared__ __attribute__((aligned(16))) float sBias[3][NT];               // of this tile and the next; with one channel tile of all, and a dump
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave % WC, wp = wave / WC;
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
   issue(0, P0);
   frags(0, 0, 0);
 
-  const bool has_res = a.res && a.res_mode != OCTO_RES_NONE;
+  const bool has_res = a.res && a.res_mode != OCTO_RES_NONE, tail = a.Cout % VN != 0;
   int st_rd = 0, bbuf = 0;
   bool stored = false;                                     // the first wait of a tile counts the stores of the one before
   for (;;) {
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
       constexpr bool LAST = decltype(lastc)::value;
       const int nxt = st_rd + 1 == NST ? 0 : st_rd + 1;
       if constexpr (LAST) {
-        issue_bias(cn0, bbuf ^ 1, more);
+        issue_bias(cn0, tiles_c == 1 ? 2 : bbuf ^ 1, more);
         if (PJ > 0 && has_res) load_res(0, PJ);
       }
 #pragma unroll
@@ -322,7 +322,16 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
             const u32x2 ob = __builtin_bit_cast(u32x2, o);
             out[2 * q] = ob[0]; out[2 * q + 1] = ob[1];
           }
-          const bool ok = cw + i * 32 + h * VN < a.Cout;
+          const bool ok = cw + i * 32 + h * VN + VN <= a.Cout;
+          const int left = a.Cout - (c0 + wc * (TC * 32) + i * 32);
+          if (tail && left > 0 && left < 32 && (left / VN) % 2 == h) {    // the vector that ends past the last channel: its values in pairs
+            const int to = !ok && cw + i * 32 + h * VN < a.Cout ? yo + i * 32 * ES + h * 16 : OOB;
+#pragma unroll
+            for (int e = 0; e < VN / 2; ++e) {
+              if (2 * e + 2 <= left % VN) __builtin_amdgcn_raw_buffer_store_b32(out[e], ry, to + e * 4, 0, 0);
+              else if (2 * e + 1 == left % VN) __builtin_amdgcn_raw_buffer_store_b16((short)out[e], ry, to + e * 4, 0, 0);
+            }
+          }
           if (second) __builtin_amdgcn_raw_buffer_store_b128(out, ry2, ok ? yo2 + i * 32 * ES + h * 16 : OOB, 0, 0);
           else __builtin_amdgcn_raw_buffer_store_b128(out, ry, ok ? yo + i * 32 * ES + h * 16 : OOB, 0, 0);
           __builtin_amdgcn_sched_barrier(0);               // one vector at a time: keeps the register demand low
@@ -333,7 +342,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
     if (!more) break;
     stored = true;
     t = tn; p0 = pn0; c0 = cn0;
-    bbuf ^= 1;
+    if (tiles_c > 1) bbuf ^= 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // loads issued past the last step write zeros into LDS
 }
@@ -354,8 +363,9 @@ template <typename T, int NT, int BC, int BP, int WC, int KV, int NST, int MINB>
 static hipError_t launch_flow_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   constexpr int BK = KV * Elem<T>::N;
   // The bias of a tile is requested at the last step of the one before: its place must be free (a barrier since the epilogue before),
-  // and it must have landed by the epilogue (older than the operands of step NST - 2)
+  // and it must have landed by the epilogue (older than the operands of step NST - 2).  With a single step there must be one channel tile.
   static_assert(KV == 8 && NST <= 4, "two K steps suffice: a.K > 64");
+  if (a.K <= BK && a.Cout > BC) return hipErrorNotSupported;
   const long long M = (long long)a.n * a.Ho * a.Wo, tiles_c = (a.Cout + BC - 1) / BC, tiles = (M + BP - 1) / BP * tiles_c;
   if (tiles <= 0) return hipSuccess;
   if (tiles >= 0x3FFFFFF0LL) return hipErrorNotSupported;

@@ -9,10 +9,11 @@ namespace octo {
 inline bool flow_fits(const ConvArgs& a) {
   constexpr int VN = 8, ES = 2;
   if (a.out_f32 || a.pair_view || a.pool_y || a.up_y || a.kh > 15 || a.kw > 15) return false;
-  if (((a.Cin | a.Cout | a.x_ld | a.x_coff | a.y_ld | a.y_coff) % VN) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return false;
+  if (a.Cout % VN && (a.res || a.split > 0)) return false;
+  if (((a.Cin | a.x_ld | a.x_coff | a.y_ld | a.y_coff) % VN) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return false;
   if (a.res && (((a.res_ld | a.res_coff) % VN) || ((uintptr_t)a.res & 15))) return false;
   if (a.split > 0 && a.split % 32) return false;
-  if (a.Cout <= 32 || a.K <= 64) return false;             // nothing to fill a tile with; the bias of the next tile needs two K steps
+  if (a.Cout <= 32 || (a.K <= 64 && a.Cout > 256)) return false;      // nothing to fill a tile with; one K step: one channel tile (launch_flow_cfg)
   // 32-bit offsets: weights, and the pixels of a tile (256 of them) in every tensor
   const long long ld = std::max(std::max(a.x_ld, a.y_ld), std::max(a.res ? a.res_ld : 0, a.split > 0 ? a.y2_ld : 0));
   return (long long)a.w_rows * a.Kp * ES < 0x7FFFFFFFLL && 256 * ld * ES < 0x7FFFFFF0LL && (long long)a.n * a.Ho * a.Wo < 0x7FFFFF00LL &&
@@ -44,13 +45,17 @@ inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, in
 }
 // The row of FLOW_COST with the smallest estimate for M output pixels.
 inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us) {
-  int best = 0;
+  int best = -1;
   for (int i = 0; i < 8; ++i) {
+    if (a.K <= 64 && a.Cout > FLOW_COST[i].bc) continue;
     const double t = flow_cost_us(FLOW_COST[i], a, M, num_cu);
-    if (i == 0 || t < *us) { *us = t; best = i; }
+    if (best < 0 || t < *us) { *us = t; best = i; }
   }
   return best;
 }
+// Output channels that are no whole vectors (detector heads: 255 in rows of 256) cost a few stores more: 192 -> 255 on 32 x 160 x 160
+// 246 us on the general kernel's plain 128x128 tiles, 191 here, 128 -> 255 on 64 x 80 x 80 112 : 82.  A single K step needs its channels in
+// one tile (64 -> 128, stride 2 on 4170 x 56 x 56 341 : 316).
 // 1x1 / stride-1 layers that the streaming kernel (conv1x1.hip) leaves to this one: whole K steps, two or more (128 -> 128 on 64 x 40 x 40
 // 15.9 -> 12.7 us, 192 -> 192 on 41 x 80 x 80 40.8 -> 38.8, 192 -> 96 with residual on 20 x 80 x 80 23.0 -> 17.9).  Fewer or broken steps are
 // faster there (96 -> 192 on 41 x 40 x 40 11.4 : 14.5, 64 -> 256 on 16 x 32 x 32 8.0 and not possible here).  What adds a residual and

@@ -19,6 +19,12 @@ CASES = [
     (60, 40, 41, 192, 96, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 1200962568),
     (9, 41, 39, 256, 72, 1, 1, nn.ACT_NONE, nn.RES_NONE, 0, 64, 1200640648),
     (33, 40, 40, 384, 384, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 0, 1201921288),
+    (9, 41, 40, 192, 255, 1, 1, nn.ACT_NONE, nn.RES_NONE, 0, 1, 1201281288),
+    (9, 41, 40, 192, 253, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 3, 1201281288),
+    (31, 80, 79, 64, 250, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 6, 1212561288),
+    (7, 33, 31, 520, 172, 1, 1, nn.ACT_RELU, nn.RES_NONE, 0, 4, 1221280648),
+    (40, 57, 55, 64, 128, 1, 2, nn.ACT_NONE, nn.RES_NONE, 0, 0, 1211281288),             # one K step
+    (40, 57, 55, 56, 190, 1, 2, nn.ACT_RELU, nn.RES_NONE, 0, 2, 1221921288),             # three quarters of one
     (33, 40, 41, 256, 64, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 0, 1200641288),
     (9, 159, 157, 128, 120, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 1211282568),
     (25, 61, 63, 64, 128, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 1211281288),
