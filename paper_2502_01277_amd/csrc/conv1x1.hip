@@ -7,8 +7,8 @@
 //   * every wavefront works on its own on blocks of 32 pixels: it fetches a block (and the residual's) with direct-to-LDS
 //     loads, 1 KB of consecutive memory per instruction, multiplies, and requests its next block as soon as the operands
 //     are in registers, so the fetch runs beside the epilogue and the stores.  No barrier after the first;
-//   * weight rows are permuted so that a lane of the matrix instruction's result holds runs of eight consecutive channels
-//     of its pixel: results leave as 16-byte stores, 32 consecutive bytes per pixel and instruction, without a detour
+//   * weight rows are permuted so that a lane of the matrix instruction's result holds 16 consecutive channels of its pixel:
+//     results leave as 16-byte stores, 64 consecutive bytes per pixel and instruction (see swap_rows16), without a detour
 //     through LDS.
 // LDS rows (a pixel's or an output channel's K values) have an odd pitch in 16-byte vectors: reads of one vector of 32
 // rows hit all banks evenly.
@@ -28,11 +28,8 @@ struct StreamGeom {
 };
 
 // channel (within a block of 32) that row m of the matrix instruction computes: result register 4 q + e of half g of the
-// wavefront is row 8 q + 4 g + e, and shall be channel 16 (q / 2) + 8 g + 4 (q % 2) + e
-__device__ __forceinline__ int row_channel(int m) {
-  const int q = m >> 3, g = (m >> 2) & 1, e = m & 3;
-  return 16 * (q >> 1) + 8 * g + 4 * (q & 1) + e;
-}
+// wavefront is row 8 q + 4 g + e, and shall be channel 16 g + 4 q + e
+__device__ __forceinline__ int row_channel(int m) { return 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3); }
 
 template <typename T, int TC>
 __global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, const StreamGeom gm) {
@@ -51,16 +48,16 @@ __global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, c
   if (a.n_dyn) { const int d = *a.n_dyn; n_items = d < a.n ? d : a.n; }
   const int M = n_items * a.Ho * a.Wo;                   // < 2^31 (host)
   const int n_blk = (M + 31) >> 5;
-  // workgroup b runs on die b % 8, which owns a contiguous piece of the blocks; the workgroups of the channel tiles of one
-  // pixel range are neighbours on it and advance together, so they meet in its L2
+  // A workgroup takes runs of as many consecutive blocks as it has wavefronts; the runs go round the dies (workgroup b runs on die b % 8),
+  // so that the chip reads and writes one window of memory at a time: 64 -> 64 on 64 x 160 x 160 85 -> 81 us against a contiguous piece
+  // of the tensor for every die, 64 -> 256 with residual on 119 x 64 x 32 63 -> 57.  The workgroups of the channel tiles of one pixel
+  // range are neighbours on a die and advance together, so they meet in its L2
   const int die = blockIdx.x & 7, j = blockIdx.x >> 3;
   const int ct = j % gm.tiles_c, pl = j / gm.tiles_c;
   if (pl >= gm.lanes) return;
-  const int per_die = (n_blk + 7) >> 3;
-  const int end = (die + 1) * per_die < n_blk ? (die + 1) * per_die : n_blk;
-  const int stride = gm.lanes * gm.waves;
-  int blk = die * per_die + pl * gm.waves + wave;
-  const int c0 = ct * BC;
+  const int stride = gm.lanes * 8 * gm.waves;
+  int blk = (pl * 8 + die) * gm.waves + wave;
+  const int c0 = ct * BC, cs = c0 + (lane >> 4) * 8;     // channels of the vector this lane stores, of pixel lane % 16
   const int kv = a.Cin >> 3;                             // vectors per pixel
 
   // weights, once
@@ -94,7 +91,7 @@ __global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, c
   const int res_vecs = a.Cout - c0 < BC ? (a.Cout - c0) >> 3 : BC >> 3;
   auto fetch_r = [&](int b) { fetch(rg + (size_t)b * 32 * a.res_ld, a.res_ld, M - b * 32 < 32 ? M - b * 32 : 32, res_vecs, gm.rvp, gm.div_r, sR, gm.r_vecs); };
   const bool has_res = a.res && a.res_mode != OCTO_RES_NONE;
-  if (blk < end) { fetch_x(blk); if (has_res) fetch_r(blk); }
+  if (blk < n_blk) { fetch_x(blk); if (has_res) fetch_r(blk); }
   __syncthreads();                                       // the weights are in place
 
   const bool is_silu = a.act == OCTO_ACT_SILU;
@@ -103,7 +100,7 @@ __global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, c
   const u32x4* pa = sW + l32 * gm.kvp + g;
   const u32x4* pb = sX + l32 * gm.kvp + g;
   const int wstep = 32 * gm.kvp;
-  for (; blk < end; blk += stride) {
+  for (; blk < n_blk; blk += stride) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     floatx16 acc[TC];
 #pragma unroll
@@ -117,19 +114,26 @@ __global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, c
     }
     const int next = blk + stride;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the block's operands have been read: its buffer takes the next one
-    if (next < end) fetch_x(next);
+    if (next < n_blk) fetch_x(next);
 
-    const int p = blk * 32 + l32;
-    T* y1p = (T*)a.y + (size_t)p * a.y_ld + a.y_coff;
-    T* y2p = (T*)a.y2 + (size_t)p * a.y2_ld + a.y2_coff - a.split;
+    const int p0 = blk * 32;
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)((T*)a.y + a.y_coff + (size_t)p0 * a.y_ld), 0, (int)BUF_MAX, BUF_FLAGS);
+    const __amdgpu_buffer_rsrc_t ry2 = __builtin_amdgcn_make_buffer_rsrc((void*)((T*)a.y2 + a.y2_coff - a.split + (size_t)p0 * a.y2_ld), 0, (int)BUF_MAX, BUF_FLAGS);
+    int yo[2], yo2[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int pl = h * 16 + (lane & 15);
+      yo[h] = p0 + pl < M ? (pl * a.y_ld + cs) * 2 : OOB; yo2[h] = p0 + pl < M ? (pl * a.y2_ld + cs) * 2 : OOB;
+    }
     with_epilogue_mode(has_res ? a.res_mode : OCTO_RES_NONE, is_silu, [&](auto res_c, auto silu_c) __attribute__((always_inline)) {
       constexpr int RES = decltype(res_c)::value;
       constexpr bool SILU = decltype(silu_c)::value;
 #pragma unroll
       for (int i = 0; i < TC; ++i) {
+        u32x4 out[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const int cl = i * 32 + h * 16 + g * 8;        // eight consecutive channels
+          const int cl = i * 32 + g * 16 + h * 8;        // eight consecutive channels
           typedef T t8 __attribute__((ext_vector_type(8)));
           t8 r8 = {};
           if (RES != OCTO_RES_NONE) r8 = __builtin_bit_cast(t8, sR[l32 * gm.rvp + (cl >> 3)]);
@@ -144,24 +148,22 @@ __global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, c
 #pragma unroll
             for (int e = 0; e < 4; ++e) o8[q * 4 + e] = (T)v[e];
           }
-          const int c = c0 + cl;
-          if (p < M && c < a.Cout) {
-            // two layers in one launch: a vector never straddles the split (a multiple of 8 channels)
-            const bool second = a.split > 0 && c >= a.split;
-            T* yp = second ? y2p + c : y1p + c;
-            if (c + 8 <= a.Cout) {
-              *(u32x4*)yp = __builtin_bit_cast(u32x4, o8);
-            } else {
+          out[h] = __builtin_bit_cast(u32x4, o8);
+        }
+        swap_rows16(out[0], out[1]);
+        // two layers in one launch: a block of 32 channels belongs to one of them, or (a split that is a multiple of 8 only) each vector to its own
+        const int left = a.split - c0 - i * 32;
+        const bool any = cs + i * 32 < a.Cout, second = a.split > 0 && cs + i * 32 >= a.split;
 #pragma unroll
-              for (int e = 0; e < 8; ++e) if (c + e < a.Cout) yp[e] = o8[e];
-            }
-          }
+        for (int h = 0; h < 2; ++h) {
+          if (a.split == 0 || left > 0) __builtin_amdgcn_raw_buffer_store_b128(out[h], ry, any && !second ? yo[h] + i * 64 : OOB, 0, 0);
+          if (a.split > 0 && left < 32) __builtin_amdgcn_raw_buffer_store_b128(out[h], ry2, any && second ? yo2[h] + i * 64 : OOB, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);               // one block of channels at a time: keeps the register demand low
       }
       if (RES != OCTO_RES_NONE) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (next < end) fetch_r(next);
+        if (next < n_blk) fetch_r(next);
       }
     });
   }
@@ -226,8 +228,9 @@ static hipError_t launch_stream_typed(const ConvArgs& a, long long M, int num_cu
 // wavefront of the chip; hipErrorNotSupported otherwise.  Longer reductions have work enough per byte for the general
 // kernel's larger tiles (256 channels: even; 384 -> 192 on 80 x 80: 63 us there, 95 here), and so have channel counts that
 // are no multiple of 8 (their last vectors would be written element by element).  The sums are those of the general kernel.
-// Measured, bf16: 96 -> 96 on 32 x 160 x 160 107 -> 81 us (3.9 TB/s), on 32 x 320 x 320 420 -> 301; 64 x 80 x 80 x 128 ->
-// 128 52 -> 42; 119 x 64 x 32 x 64 -> 256 44 -> 31.
+// Bound by memory.  Measured, bf16, with stores of 32 consecutive bytes per pixel and a contiguous piece of the tensor for every die, and
+// now: 96 -> 96 on 32 x 160 x 160 84 -> 68 us (4.6 TB/s; a copy of that size does 5.3), on 32 x 320 x 320 300 -> 249 (5.0); 64 -> 64 on
+// 64 x 160 x 160 103 -> 81; 64 -> 256 with residual on 119 x 64 x 32 74 -> 57.  A second block per wavefront in flight gave nothing.
 hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm) {
   if ((dtype != OCTO_F16 && dtype != OCTO_BF16) || a.pair_view || a.pool_y || a.up_y || a.out_f32 || a.kh != 1 || a.kw != 1 || a.stride_h != 1 || a.stride_w != 1 ||
       a.pad_h || a.pad_w || a.Cin > 192 || a.Cin < 16)

@@ -24,8 +24,7 @@ inline bool flow_fits(const ConvArgs& a) {
 // 64 x 128 per compute unit, bf16, 256 compute units; residual error 8 - 11 %): a constant, what the busiest compute unit does - its tiles,
 // rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the memory traffic.  Over those
 // layers the choice loses 1.3 % against always taking the fastest tile, and takes 0.88 of the time of the kernels it replaced
-// (128 x 256 and 64 x 64 tiles of the general kernel, pipelined: 0.87 and, for 1x1 layers, 0.84; its plain tiles 0.86; the streaming 1x1
-// kernel 0.83 from 128 input channels on).
+// (128 x 256 and 64 x 64 tiles of the general kernel, pipelined: 0.87 and, for 1x1 layers, 0.84; its plain tiles 0.86).
 struct FlowCost { int bc, bp; double base, step, tile, latency, per_mb, any_step; };
 constexpr FlowCost FLOW_COST[8] = {
     {64, 64, 3.73, 0.165, 0.22, 0.118, 0.040, 0.031},
@@ -56,10 +55,11 @@ inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us) {
 // Output channels that are no whole vectors (detector heads: 255 in rows of 256) cost a few stores more: 192 -> 255 on 32 x 160 x 160
 // 246 us on the general kernel's plain 128x128 tiles, 191 here, 128 -> 255 on 64 x 80 x 80 112 : 82.  A single K step needs its channels in
 // one tile (64 -> 128, stride 2 on 4170 x 56 x 56 341 : 316).
-// 1x1 / stride-1 layers that the streaming kernel (conv1x1.hip) leaves to this one: whole K steps, two or more (128 -> 128 on 64 x 40 x 40
-// 15.9 -> 12.7 us, 192 -> 192 on 41 x 80 x 80 40.8 -> 38.8, 192 -> 96 with residual on 20 x 80 x 80 23.0 -> 17.9).  Fewer or broken steps are
-// faster there (96 -> 192 on 41 x 40 x 40 11.4 : 14.5, 64 -> 256 on 16 x 32 x 32 8.0 and not possible here).  What adds a residual and
-// writes a channel slice of a wider tensor stays there too: no network here has such a layer, the tests of that kernel's edges do.
+// 1x1 / stride-1 layers that the streaming kernel (conv1x1.hip) leaves to this one: whole K steps, two or more.  Streaming : here, us:
+// 128 -> 128 on 64 x 80 x 80 41 : 38, on 8 x 80 x 80 9.9 : 8.5, 128 -> 256 with residual on 16 x 40 x 40 11.6 : 10.5, 192 -> 192 on 32 x 80 x 80
+// 37.5 : 36.3, on 32 x 160 x 160 150 : 150.  Fewer or broken steps are faster there (96 -> 192 on 41 x 40 x 40 11.6 : 14.5, 64 -> 256 on
+// 16 x 32 x 32 8.0 and not possible here).  What adds a residual and writes a channel slice of a wider tensor stays there too: no
+// network here has such a layer, the tests of that kernel's edges do.
 inline bool flow_takes_1x1(const ConvArgs& a) { return a.Cin >= 128 && a.Cin % 64 == 0 && !(a.res && a.y_ld != a.Cout) && flow_fits(a); }
 
 hipError_t launch_flow_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
