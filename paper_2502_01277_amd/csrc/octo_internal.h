@@ -174,7 +174,11 @@ struct CompactArgs {
   octo_box* boxes;                         // [n][max_det] final boxes in source pixels
   int* flags;                              // [n]
 };
-hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
+hipError_t launch_compact(const CompactArgs& a, hipStream_t s, bool counted = false);     // counted: step 1 has run (launch_select)
+// Top-k, NMS and (with ca) step 1 of the compaction in one launch; m.mask is not used.
+constexpr int SELECT_MAX = 1024;           // boxes per item, at most
+bool select_fits(const TopkArgs& a);
+hipError_t launch_select(const TopkArgs& a, const NmsArgs& m, const CompactArgs* ca, hipStream_t s);
 
 // First launch of a batch: the frame table (passed by value, at most MAX frames per launch) and cleared counters.
 struct BeginArgs {

@@ -655,7 +655,9 @@ hipError_t run_layers(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, h
 // decode -> top-k -> NMS of a detector (root or child) for n items.  The head tensors hold items 0 .. n-1 of this
 // execution; their results go to slots item0 .. item0 + n - 1 of the model's per-item arrays (item0 > 0 when the
 // detector of one batch runs in several executions).  The candidate counters must have been cleared.
-hipError_t run_detect_tail(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, hipStream_t s, hipEvent_t* evs, int item0 = 0, LabelDest dest = LabelDest()) {
+// ca: also step 1 of the compaction of these items, if that rides on the selection (*counted)
+hipError_t run_detect_tail(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, hipStream_t s, hipEvent_t* evs, int item0 = 0, LabelDest dest = LabelDest(),
+                           const CompactArgs* ca = nullptr, bool* counted = nullptr) {
   hipError_t e;
   DecodeArgs da{};
   da.n_levels = m.d.n_outputs;
@@ -673,6 +675,13 @@ hipError_t run_detect_tail(octo_pipeline* p, ModelPlan& m, int n, const int* n_d
   if ((e = launch_decode(m.d.dtype, da, s)) != hipSuccess) return e;
   if (evs) hipEventRecord(evs[0], s);
   TopkArgs ta{da.cand, da.count, m.n_cand, CNT_STRIDE, m.top + (size_t)item0 * m.k_cap, m.top_count + item0, std::min(m.d.topk, m.n_cand), m.k_cap, n, n_dyn};
+  const NmsArgs one{ta.out, ta.out_count, m.k_cap, m.d.iou_thr, m.d.max_det, nullptr, m.keep + (size_t)item0 * m.d.max_det, m.n_keep + item0, n, n_dyn, dest};
+  if (select_fits(ta)) {               // one launch; the NMS stage then takes no time of its own
+    if ((e = launch_select(ta, one, ca, s)) != hipSuccess) return e;
+    if (counted) *counted = ca != nullptr;
+    if (evs) { hipEventRecord(evs[1], s); hipEventRecord(evs[2], s); }
+    return hipSuccess;
+  }
   if ((e = launch_topk(ta, s)) != hipSuccess) return e;
   if (evs) hipEventRecord(evs[1], s);
   // the suppression bit mask is scratch of one execution: every execution uses the first n items' worth of it
@@ -740,7 +749,7 @@ octo_status build(octo_pipeline* p, const octo_pipeline_desc* desc, Arena& ar) {
       m.cand_count = (int*)ar.alloc((size_t)m.cap * CNT_STRIDE * sizeof(int));
       m.top = (octo_cand*)ar.alloc((size_t)m.cap * m.k_cap * sizeof(octo_cand));
       m.top_count = (int*)ar.alloc((size_t)m.cap * sizeof(int));
-      m.mask = (unsigned long long*)ar.alloc(nms_mask_bytes(m.cap, m.k_cap));
+      if (std::min(m.d.topk, m.n_cand) > SELECT_MAX) m.mask = (unsigned long long*)ar.alloc(nms_mask_bytes(m.cap, m.k_cap));      // else one launch selects, without it
       if (k > 0) {
         m.keep = (int*)ar.alloc((size_t)m.cap * m.d.max_det * sizeof(int));
         m.flags = (int*)ar.alloc((size_t)m.cap * sizeof(int));
@@ -1027,6 +1036,18 @@ octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
   ra.dst = view_of(root, 0).ptr; ra.dst_h = root.d.in_h; ra.dst_w = root.d.in_w; ra.dst_c = root.input_c4 ? 4 : 3;
   for (int c = 0; c < 3; ++c) { ra.scale[c] = root.d.norm_scale[c]; ra.bias[c] = root.d.norm_bias[c]; }
   ra.pad_value = root.d.pad_value;
+  CompactArgs ca{};
+  ca.top = root.top; ca.k_cap = root.k_cap; ca.keep = root.keep; ca.n_keep = root.n_keep; ca.max_det = root.d.max_det; ca.n = n;
+  ca.left = (float)p->left; ca.top_pad = (float)p->top;
+  ca.rx = (float)p->nw / (float)p->d.src_w; ca.ry = (float)p->nh / (float)p->d.src_h;
+  ca.src_w = (float)p->d.src_w; ca.src_h = (float)p->d.src_h;
+  ca.n_edges = (int)p->edges.size();
+  for (int e = 0; e < ca.n_edges; ++e) {
+    ca.class_mask[e][0] = p->edges[e].class_mask[0]; ca.class_mask[e][1] = p->edges[e].class_mask[1];
+    ca.rois[e] = p->rois[e]; ca.n_roi[e] = p->n_roi[e]; ca.roi_cap[e] = p->roi_cap[e]; ca.roi_of[e] = p->roi_of[e]; ca.roi_cnt[e] = p->roi_cnt[e];
+  }
+  ca.boxes = (octo_box*)(p->d_result + p->off_boxes); ca.flags = root.flags;
+  bool counted = false;
   // The detector runs on exec_bz frames at a time (its own batch size; by default the whole batch), every execution
   // through the same activation buffers; candidates, top-k lists and keep lists are per frame and collect in place.
   // Stage events (when enabled) bracket the last execution's stages; the letterbox and layer stages of the earlier
@@ -1040,20 +1061,9 @@ octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
     if (ev && last) HIPCHK(p, hipEventRecord(ev[1 + ST_LETTERBOX], s));
     HIPCHK(p, run_layers(p, root, cn, nullptr, s, p->layer_timing && last ? &B.layer_ev[0] : nullptr));
     if (ev && last) HIPCHK(p, hipEventRecord(ev[1 + ST_DET_LAYERS], s));
-    HIPCHK(p, run_detect_tail(p, root, cn, nullptr, s, ev && last ? ev + 1 + ST_DECODE : nullptr, c0));
+    HIPCHK(p, run_detect_tail(p, root, cn, nullptr, s, ev && last ? ev + 1 + ST_DECODE : nullptr, c0, LabelDest(), cn == n ? &ca : nullptr, &counted));
   }
-  CompactArgs ca{};
-  ca.top = root.top; ca.k_cap = root.k_cap; ca.keep = root.keep; ca.n_keep = root.n_keep; ca.max_det = root.d.max_det; ca.n = n;
-  ca.left = (float)p->left; ca.top_pad = (float)p->top;
-  ca.rx = (float)p->nw / (float)p->d.src_w; ca.ry = (float)p->nh / (float)p->d.src_h;
-  ca.src_w = (float)p->d.src_w; ca.src_h = (float)p->d.src_h;
-  ca.n_edges = (int)p->edges.size();
-  for (int e = 0; e < ca.n_edges; ++e) {
-    ca.class_mask[e][0] = p->edges[e].class_mask[0]; ca.class_mask[e][1] = p->edges[e].class_mask[1];
-    ca.rois[e] = p->rois[e]; ca.n_roi[e] = p->n_roi[e]; ca.roi_cap[e] = p->roi_cap[e]; ca.roi_of[e] = p->roi_of[e]; ca.roi_cnt[e] = p->roi_cnt[e];
-  }
-  ca.boxes = (octo_box*)(p->d_result + p->off_boxes); ca.flags = root.flags;
-  HIPCHK(p, launch_compact(ca, s));
+  HIPCHK(p, launch_compact(ca, s, counted));
   if (ev) HIPCHK(p, hipEventRecord(ev[1 + ST_COMPACT], s));
   return OCTO_OK;
 }

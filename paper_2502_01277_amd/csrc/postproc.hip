@@ -304,39 +304,60 @@ __device__ __forceinline__ void bitonic_desc(unsigned long long* key, unsigned* 
   __syncthreads();
 }
 
+// Leaves the slots in `in` of the k best of an item's candidates, best first, in val[0 .. kk); returns kk.  All threads of the workgroup.
+__device__ __forceinline__ int sort_best(const TopkArgs& a, int item, unsigned long long* key, unsigned* val) {
+  int count = a.in_count[(size_t)item * a.in_count_stride];
+  if (count > a.in_cap) count = a.in_cap;
+  if (count < 0) count = 0;
+  const octo_cand* in = a.in + (size_t)item * a.in_cap;
+  const int kk = count < a.k ? count : a.k;
+  auto key_of = [&](int slot) -> unsigned long long {
+    const octo_cand c = in[slot];
+    return ((unsigned long long)__float_as_uint(c.score) << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)c.idx);
+  };
+  __syncthreads();
+  if (count <= 256) {
+    // few candidates: a candidate's place is the number of larger keys (equal ones, which only a caller's own list can hold, by slot);
+    // the network's 21 barriers and more take 2 us longer for 20 candidates
+    const int t = threadIdx.x;
+    const unsigned long long mine = t < count ? key_of(t) : 0ull;
+    if (t < count) key[t] = mine;
+    __syncthreads();
+    if (t < count) {
+      int before = 0;
+      for (int q = 0; q < count; ++q) before += key[q] > mine || (key[q] == mine && q < t) ? 1 : 0;
+      if (before < kk) val[before] = (unsigned)t;
+    }
+    __syncthreads();
+    return kk;
+  }
+  int consumed = 0;
+  int have = 0;                       // entries carried over from the previous fold (already in slots [0, have))
+  while (true) {
+    int take = count - consumed;
+    if (take > TOPK_P - have) take = TOPK_P - have;
+    const int filled = have + take;
+    int P = 64;
+    while (P < filled) P <<= 1;
+    for (int t = threadIdx.x; t < P - have; t += blockDim.x) {
+      key[have + t] = t < take ? key_of(consumed + t) : 0ull;
+      val[have + t] = t < take ? (unsigned)(consumed + t) : 0u;
+    }
+    bitonic_desc(key, val, P);
+    consumed += take;
+    if (consumed >= count) break;
+    have = kk;                        // count > TOPK_P here, so kk == k <= TOPK_P / 2
+  }
+  return kk;
+}
+
 __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const TopkArgs a) {
   __shared__ unsigned long long key[TOPK_P];
   __shared__ unsigned val[TOPK_P];
   const int n_items = dyn_n(a.n_dyn, a.n);
   for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-    int count = a.in_count[(size_t)item * a.in_count_stride];
-    if (count > a.in_cap) count = a.in_cap;
-    if (count < 0) count = 0;
+    const int kk = sort_best(a, item, key, val);
     const octo_cand* in = a.in + (size_t)item * a.in_cap;
-    const int kk = count < a.k ? count : a.k;
-    int consumed = 0;
-    int have = 0;                       // entries carried over from the previous fold (already in slots [0, have))
-    __syncthreads();
-    while (true) {
-      int take = count - consumed;
-      if (take > TOPK_P - have) take = TOPK_P - have;
-      const int filled = have + take;
-      int P = 64;
-      while (P < filled) P <<= 1;
-      for (int t = threadIdx.x; t < P - have; t += blockDim.x) {
-        unsigned long long k = 0ull; unsigned v = 0u;
-        if (t < take) {
-          const octo_cand c = in[consumed + t];
-          k = ((unsigned long long)__float_as_uint(c.score) << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)c.idx);
-          v = (unsigned)(consumed + t);
-        }
-        key[have + t] = k; val[have + t] = v;
-      }
-      bitonic_desc(key, val, P);
-      consumed += take;
-      if (consumed >= count) break;
-      have = kk;                        // count > TOPK_P here, so kk == k <= TOPK_P / 2
-    }
     octo_cand* out = a.out + (size_t)item * a.k_cap;
     for (int t = threadIdx.x; t < kk; t += blockDim.x) out[t] = in[val[t]];
     if (threadIdx.x == 0) a.out_count[item] = kk;
@@ -474,6 +495,120 @@ __device__ __forceinline__ float to_src(float v, float off, float r, float hi) {
   return fminf(fmaxf(s, 0.0f), hi);
 }
 
+// A kept box in source pixels, no child labels yet; and whether a class is routed along edge e.
+__device__ __forceinline__ octo_box final_box(const CompactArgs& a, const octo_cand& c) {
+  octo_box b;
+  b.x1 = to_src(c.x1, a.left, a.rx, a.src_w); b.x2 = to_src(c.x2, a.left, a.rx, a.src_w);
+  b.y1 = to_src(c.y1, a.top_pad, a.ry, a.src_h); b.y2 = to_src(c.y2, a.top_pad, a.ry, a.src_h);
+  b.score = c.score; b.cls = c.cls;
+  for (int k = 0; k < OCTO_MAX_CHILD_LABELS; ++k) b.child_label[k] = -1;
+  return b;
+}
+__device__ __forceinline__ bool routed(const CompactArgs& a, int e, int cls) {
+  return cls >= 0 && cls < 128 && ((a.class_mask[e][cls < 64 ? 0 : 1] >> (cls & 63)) & 1ull);
+}
+
+// Top-k, NMS and step 1 of the compaction (below) of an item in one workgroup, for up to 1024 boxes: thread t holds box t of the order.
+// The wavefront that owns a block of 64 boxes walks its survivors one by one (the first one left is kept and removes its like among the
+// lanes) and leaves them in LDS; the later wavefronts test their boxes against those, and so on: what is compared is (kept boxes) x
+// (later boxes), not every pair, and a launch of 4 - 6 us each is saved for the mask, its reduction and the counts.  Same predicate,
+// same order, same boxes as nms_mask_kernel + nms_reduce_kernel.  Bound by latency.  Measured, us: 8 frames of about 20 candidates 6.6 + 4.8 + 5.3 +
+// 4.6 -> 8.1; 32 frames of 1000 candidates crowded around 40 spots 29 + 23 + 81 + 4.8 -> 117.
+static_assert(SELECT_MAX == TOPK_THREADS, "a thread per box");
+__global__ __launch_bounds__(TOPK_THREADS) void select_kernel(const TopkArgs a, const NmsArgs m, const CompactArgs ca, const int compact) {
+  __shared__ unsigned long long key[TOPK_P];
+  __shared__ unsigned val[TOPK_P];
+  __shared__ float4 kept[2][64];             // corners of the boxes kept in a block; area and class
+  __shared__ float2 kept_ac[2][64];
+  __shared__ int s_nk[2], s_keep[SELECT_MAX], s_wave[SELECT_MAX / 64];
+  const int n_items = dyn_n(a.n_dyn, a.n);
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+    const int kk = sort_best(a, item, key, val);
+    const octo_cand* in = a.in + (size_t)item * a.in_cap;
+    octo_cand c{};
+    if (t < kk) { c = in[val[t]]; a.out[(size_t)item * a.k_cap + t] = c; }
+    if (t == 0) a.out_count[item] = kk;
+    const float area = __fmul_rn(__fsub_rn(c.x2, c.x1), __fsub_rn(c.y2, c.y1));
+    bool alive = t < kk;
+    int total = 0;
+    for (int b = 0; b * 64 < kk && total < m.max_det; ++b) {
+      const int buf = b & 1;
+      if (wave == b) {
+        unsigned long long left = __ballot(alive);
+        int nk = 0;
+        while (left && total + nk < m.max_det) {
+          const int src = __ffsll((long long)left) - 1;
+          auto of_src = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src)); };
+          const float x1 = of_src(c.x1), y1 = of_src(c.y1), x2 = of_src(c.x2), y2 = of_src(c.y2), ar = of_src(area);
+          const int cls = __builtin_amdgcn_readlane(c.cls, src);
+          const bool gone = lane == src || (lane > src && c.cls == cls && suppresses(x1, y1, x2, y2, ar, c.x1, c.y1, c.x2, c.y2, area, m.iou_thr));
+          left &= ~__ballot(gone);
+          if (lane == src) {
+            kept[buf][nk] = make_float4(x1, y1, x2, y2); kept_ac[buf][nk] = make_float2(ar, __int_as_float(cls));
+            s_keep[total + nk] = t;
+          }
+          ++nk;
+        }
+        if (lane == 0) s_nk[buf] = nk;
+        if (lane < 3 && nk + lane < 64) kept_ac[buf][nk + lane] = make_float2(0.0f, __int_as_float(-1));      // no class: groups of four may be read
+      }
+      __syncthreads();
+      const int nk = s_nk[buf];
+      total += nk;
+      if (wave > b && __ballot(alive)) {
+        bool gone = false;
+        for (int q = 0; q < nk; q += 4)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 o = kept[buf][q + i];
+            const float2 ac = kept_ac[buf][q + i];
+            gone |= __float_as_int(ac.y) == c.cls && suppresses(o.x, o.y, o.z, o.w, ac.x, c.x1, c.y1, c.x2, c.y2, area, m.iou_thr);
+          }
+        if (gone) alive = false;
+      }
+      // (the buffer is written again two blocks on, behind the barrier of the next)
+    }
+    __syncthreads();
+    octo_cand k{};
+    const bool mine = t < total;             // thread t now stands for kept box t
+    if (mine) {
+      const int at = s_keep[t];
+      m.keep[(size_t)item * m.max_det + t] = at;
+      k = in[val[at]];
+    }
+    if (t == 0) {
+      m.n_keep[item] = total;
+      if (m.dest.boxes) m.dest.boxes[(size_t)m.dest.rois[item].frame * m.dest.max_det + m.dest.rois[item].rank].child_label[m.dest.slot] = total;
+    }
+    if (compact) {
+      if (mine) ca.boxes[(size_t)item * ca.max_det + t] = final_box(ca, k);
+      for (int e = 0; e < ca.n_edges; ++e) {
+        const bool hit = mine && routed(ca, e, k.cls);
+        const unsigned long long bal = __ballot(hit);
+        if (lane == 0) s_wave[wave] = __popcll(bal);
+        __syncthreads();
+        int before = 0, all = 0;
+        for (int w = 0; w < SELECT_MAX / 64; ++w) { if (w < wave) before += s_wave[w]; all += s_wave[w]; }
+        if (mine) ca.roi_of[e][(size_t)item * ca.max_det + t] = hit ? before + __popcll(bal & ((1ull << lane) - 1ull)) : -1;      // rank inside the item for now
+        if (t == 0) ca.roi_cnt[e][item] = all;
+        __syncthreads();
+      }
+    }
+    __syncthreads();                         // val and s_keep have been read
+  }
+}
+
+bool select_fits(const TopkArgs& a) { return a.k <= SELECT_MAX && a.k <= a.k_cap && !(a.in_cap > TOPK_P && a.k > TOPK_P / 2); }
+
+hipError_t launch_select(const TopkArgs& a, const NmsArgs& m, const CompactArgs* ca, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
+  if (!select_fits(a)) return hipErrorInvalidValue;
+  if (ca) for (int e = 0; e < ca->n_edges; ++e) if (!ca->roi_of[e] || !ca->roi_cnt[e]) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(select_kernel, dim3(a.n > 1024 ? 1024 : a.n), dim3(TOPK_THREADS), 0, s, a, m, ca ? *ca : CompactArgs{}, ca ? 1 : 0);
+  return hipGetLastError();
+}
+
 // Step 1, one workgroup per (item, edge) [and one extra grid row for the final box table]: flag the kept boxes whose
 // class is routed along the edge, give each its rank among the item's flagged boxes (workgroup scan) and leave the
 // item's count in roi_cnt.  Step 2, same grid: the item's first ROI id is the sum of the counts of the items before
@@ -491,24 +626,17 @@ __global__ __launch_bounds__(256) void compact_count_kernel(const CompactArgs a)
     // final boxes of the item, in keep order, in source pixels
     for (int r = t; r < nk; r += blockDim.x) {
       const octo_cand c = a.top[(size_t)item * a.k_cap + a.keep[(size_t)item * a.max_det + r]];
-      octo_box b;
-      b.x1 = to_src(c.x1, a.left, a.rx, a.src_w); b.x2 = to_src(c.x2, a.left, a.rx, a.src_w);
-      b.y1 = to_src(c.y1, a.top_pad, a.ry, a.src_h); b.y2 = to_src(c.y2, a.top_pad, a.ry, a.src_h);
-      b.score = c.score; b.cls = c.cls;
-      for (int k = 0; k < OCTO_MAX_CHILD_LABELS; ++k) b.child_label[k] = -1;
-      a.boxes[(size_t)item * a.max_det + r] = b;
+      a.boxes[(size_t)item * a.max_det + r] = final_box(a, c);
     }
     return;
   }
-  const uint64_t m0 = a.class_mask[e][0], m1 = a.class_mask[e][1];
   if (t == 0) s_run = 0;
   __syncthreads();
   for (int r0 = 0; r0 < nk; r0 += blockDim.x) {
     const int r = r0 + t;
     bool hit = false;
     if (r < nk) {
-      const int cls = a.top[(size_t)item * a.k_cap + a.keep[(size_t)item * a.max_det + r]].cls;
-      hit = cls >= 0 && cls < 128 && (((cls < 64 ? m0 : m1) >> (cls & 63)) & 1ull);
+      hit = routed(a, e, a.top[(size_t)item * a.k_cap + a.keep[(size_t)item * a.max_det + r]].cls);
     }
     const unsigned long long bal = __ballot(hit);
     if (lane == 0) s_wave[wave] = __popcll(bal);
@@ -565,13 +693,16 @@ __global__ __launch_bounds__(256) void compact_write_kernel(const CompactArgs a)
   }
 }
 
-hipError_t launch_compact(const CompactArgs& a, hipStream_t s) {
+hipError_t launch_compact(const CompactArgs& a, hipStream_t s, bool counted) {
   if (a.n <= 0) return hipSuccess;
   if (a.n > 65535) return hipErrorInvalidValue;
   for (int e = 0; e < a.n_edges; ++e) if (!a.roi_of[e] || !a.roi_cnt[e]) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(compact_count_kernel, dim3(a.n, a.n_edges + (a.boxes ? 1 : 0)), dim3(256), 0, s, a);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess || a.n_edges == 0) return err;
+  if (!counted) {
+    hipLaunchKernelGGL(compact_count_kernel, dim3(a.n, a.n_edges + (a.boxes ? 1 : 0)), dim3(256), 0, s, a);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  if (a.n_edges == 0) return hipSuccess;
   hipLaunchKernelGGL(compact_write_kernel, dim3(a.n, a.n_edges), dim3(256), 0, s, a);
   return hipGetLastError();
 }
