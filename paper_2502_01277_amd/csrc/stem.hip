@@ -1,284 +1,321 @@
-// First-layer convolution (3 input channels, stride 2) on the matrix cores.
+// First-layer convolution (3 input channels, stride 2) on the matrix cores, and the 3x3 / stride-2 / pad-1 max-pool behind it where the
+// layer's output feeds nothing else (only the pooled tensor is written then).
 //
 // The input is stored with 4 channels, so two neighbouring pixels form one 16-byte vector of 8 values, and a
 // stride-2 convolution becomes a stride-1 convolution over pixel pairs with a kernel of KH x PKW pairs (see
 // pipeline.hip, which also re-packs the weights as [Cout][(row, pair, 8 values)]).  The general implicit-GEMM kernel
 // gathers every K vector of every output pixel from global memory: for a 7x7 kernel that is 28 loads of 16 bytes per
-// output pixel, almost all of them re-reads.  Here a workgroup instead
-//   - keeps the weight matrix in registers for its lifetime (it is persistent over tiles): every lane holds the
-//     MFMA A fragments of its row of each 32-channel block, all K steps of them (112 registers for 64 channels x 7x7).
-//     Out of LDS they cost as many bytes per MFMA as the pixel operand, and the two together are exactly what a
-//     compute unit's LDS delivers at the full MFMA rate - with two workgroups per unit the loop ran at half of it,
-//   - loads the input patch of an 8 x 32 output tile once (21 x 35 pair vectors for 7x7), zero-filled outside the image,
-//   - feeds the MFMA B operand straight from the patch: for kernel tap (r, s) output pixel (y, x) needs patch vector
-//     (2y + r, x + s), so the 32 lanes of a block read 32 consecutive vectors (bank-conflict free),
-//   - stages the output tile in LDS (over the patch) and writes it with 16-byte stores along the channels.
-// One K step of the MFMA (16 values) is two pair vectors; with an odd number of vectors the last half step multiplies
-// a zero weight column.
+// output pixel, almost all of them re-reads.  Here
+//   * the weights live in registers for the lifetime of a wavefront (112 registers for 64 channels x 7x7).  Out of LDS they cost as many
+//     bytes per MFMA as the pixel operand, and the two together are exactly what a compute unit's LDS delivers at the full MFMA rate;
+//   * a wavefront works on its own: it walks down a segment of a strip of 64 convolution columns, one row at a time, with the input rows
+//     in a ring of eight row pairs in LDS, fetched four rows ahead straight from memory.  No barrier after the weights.  (A workgroup that
+//     loaded a patch, computed a tile, staged it in LDS and wrote or pooled it took turns at each: matrix pipe 29 % busy with the pool.)
+//   * the 16 channels that a lane gets of a pixel are consecutive (rows of the weight operand are permuted to that end), and results leave
+//     from the registers, 64 bytes of a pixel at a time;
+//   * for the pool, one block of 32 pixels is the even columns of a row and the other the odd ones, so that the two or three columns of a
+//     window lie in one lane and its neighbour: the horizontal maximum is two instructions per accumulator, the vertical one another, on
+//     registers that the wavefront carries from row to row.  Bias and activation come after the maximum (before it for SiLU, which is not
+//     monotonous), on a quarter of the values.  Rounding keeps the order, so the result is that of the separate kernels bit for bit.  The
+//     ring then stores the even and the odd pixel pairs of a row apart: either way an operand read is 32 consecutive vectors.
+// Bound by the matrix pipe with the pool (28 vectors of 8 products, of which 147 are real), without it by memory and SiLU.
+// Measured against tiles staged in LDS, us: 7x7 with the pool, bf16, 4170 crops of 224 x 224 2146 -> 1300, some 380 crops 232 -> 148, some 6
+// crops 23 -> 18; 6x6 on 32 frames of 1280 x 1280 to 64 channels 496 -> 434, on 64 of 640 x 640 to 32 channels 170 -> 127 (5 TB/s).
 #include "mfma_common.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
 
-constexpr int STEM_TH = 8, STEM_TW = 32;   // output tile: rows x columns
-constexpr int STEM_POOL_COLS = 15;          // pooled columns per strip (their windows span 31 of the tile's 32 columns)
-
-// 16-bit floating-point patterns (two per word) <-> signed 16-bit integers of the same order; its own inverse
-__device__ __forceinline__ unsigned order_key16x2(unsigned x) {
-  typedef short s16x2 __attribute__((ext_vector_type(2)));
-  return x ^ (__builtin_bit_cast(unsigned, __builtin_bit_cast(s16x2, x) >> 15) & 0x7FFF7FFFu);     // negative: magnitude bits flipped
+// A maximum of accumulators ignores NaN (as bias and activation by fmaxf do one by one), one of SiLU's results keeps it.  In assembly:
+// fmaxf would quiet both operands first, three instructions for one.
+template <bool KEEP_NAN>
+__device__ __forceinline__ float max3_raw(float a, float b, float c) {
+  float r;
+  if constexpr (KEEP_NAN) asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  else asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
-__device__ __forceinline__ unsigned max_i16x2(unsigned a, unsigned b) {
-  typedef short s16x2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(s16x2, a), __builtin_bit_cast(s16x2, b)));
-}
+constexpr int SP_STRIP = 64, SP_POOLED = 31; // convolution columns per strip; pooled ones: windows 2 l .. 2 l + 2
+constexpr int SP_PAIRS = 8, SP_ROW = 68, SP_PAIR = 2 * SP_ROW * 16;      // ring of row pairs; vectors of a row (a half: even, odd); bytes of a pair
 
-// POOL: the layer's output feeds nothing but a 3x3 / stride-2 / pad-1 max-pool, and only the pooled tensor is written
-// (a.pool_y).  A workgroup then owns a strip of the image - 15 pooled columns, i.e. convolution columns 30 sx - 1 ..
-// 30 sx + 30 - and walks down it tile by tile: the tile staged in LDS plus its predecessor's last row (kept in a
-// second LDS buffer) hold every window of four pooled rows, so no convolution row is computed twice; along the
-// columns neighbouring strips overlap by two columns of 32.  The maximum is taken on the rounded 16-bit values, as an
-// integer maximum of order-preserving keys.
-template <typename T, int BC, int KH, int PKW, bool POOL>
-__global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a) {
+// PLAIN: no SiLU and a multiple of 8 channels; with the pool the other code would cost the row loop registers that it has not got
+template <typename T, int BC, int KH, int PKW, bool POOL, bool PLAIN>
+__device__ __forceinline__ void stem_walk(const ConvArgs& a) {
   using E = Elem<T>;
   static_assert(sizeof(T) == 2 && E::N == 8, "pixel pairs are 16-byte vectors of 8 values");
-  constexpr int TH = STEM_TH, TW = STEM_TW, BP = TH * TW;
-  constexpr int NV = KH * PKW;                 // K vectors
-  constexpr int NJ = (NV + 1) / 2;             // MFMA steps
-  constexpr int PH = (TH - 1) * 2 + KH, PW = TW + PKW - 1, PVEC = PH * PW;
-  constexpr int PLOADS = (PVEC + THREADS - 1) / THREADS;
-  constexpr int TC = BC / 32;
-  constexpr int OPITCH = BC * 2 + 16;          // bytes per staged output pixel
-  constexpr int REGION_VECS = (PLOADS * THREADS > BP * OPITCH / 16) ? PLOADS * THREADS : BP * OPITCH / 16;
-  __shared__ u32x4 sR[REGION_VECS];            // input patch, then the staged output tile
-  __shared__ u32x4 sCarry[POOL ? 2 * TW * OPITCH / 16 : 1];   // last row of the previous tile of the strip (two buffers, alternating)
-  __shared__ float sBias[BC];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
+  constexpr int TC = BC / 32, NV = KH * PKW, NJ = NV / 2, PD = 3, NP = (KH + 1) / 2;
+  constexpr bool BY_ROWS = PKW % 2 != 0;     // the two vectors of an MFMA step: of two rows of a pair, or neighbours in a row
+  static_assert(BY_ROWS ? KH % 2 == 0 : true, "an even number of vectors");
+  constexpr int AHEAD = SP_PAIRS - NP;       // rows between a pair's fetch and its first use
+  constexpr int STORES = POOL ? AHEAD / 2 * 2 * TC : AHEAD * 4 * TC;      // stores of that many rows
+  static_assert(AHEAD * 3 + STORES < 64, "counter");
+  __shared__ __attribute__((aligned(1024))) unsigned char ring_all[4 * SP_PAIRS * SP_PAIR];
+  __shared__ __attribute__((aligned(16))) float sBias[BC];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
   int n_items = a.n;
-  if (a.n_dyn) { int d = *a.n_dyn; n_items = d < a.n ? d : a.n; }
-  const int tiles_y = (a.Ho + TH - 1) / TH;
-  const int tiles_x = POOL ? (a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS : (a.Wo + TW - 1) / TW;
-  // unit of work: a tile, or (POOL) a segment of pool_seg tiles of a strip
-  const int seg = POOL ? a.pool_seg : 1;
-  const int per_img = tiles_x * ((tiles_y + seg - 1) / seg);
-  const long long n_units = (long long)n_items * per_img;
-  const T* __restrict__ xg = (const T*)a.x + a.x_coff;
-  const long long img_elems = (long long)a.H * a.W * a.x_ld;
-  const bool is_silu = a.act == OCTO_ACT_SILU;
+  if (a.n_dyn) { const int d = *a.n_dyn; n_items = d < a.n ? d : a.n; }
+  constexpr int WIDTH = POOL ? SP_POOLED : SP_STRIP;         // of a strip, and the size it is cut from
+  const int out_w = POOL ? a.pool_wo : a.Wo, out_h = POOL ? a.pool_ho : a.Ho;
+  const int strips = (out_w + WIDTH - 1) / WIDTH, seg = a.stem_seg, segs = (out_h + seg - 1) / seg, per_img = strips * segs;
+  const int n_units = n_items * per_img;     // < 2^31 (host)
+  const bool is_silu = !(POOL && PLAIN) && a.act == OCTO_ACT_SILU;
   const float act_lo = a.act == OCTO_ACT_RELU ? 0.0f : -INFINITY;
+  unsigned char* ring = ring_all + wave * (SP_PAIRS * SP_PAIR);
+  const unsigned lds = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(uintptr_t)ring);
 
-  // weights -> registers, once: row i * 32 + l32 of the packed matrix, K vector 2 j + g of step j (rows beyond Cout
-  // are zero in the packed matrix; the half step past an odd number of vectors multiplies zeros)
+  // weights -> registers, once; row m of a 32-channel operand is channel 16 ((m / 4) % 2) + 4 (m / 8) + m % 4: register 4 q + e of half g
+  // of a lane is channel 16 g + 4 q + e of the block (rows beyond Cout are zero in the packed matrix)
   u32x4 wreg[TC][NJ];
   {
     const long long w_bytes = (long long)a.w_rows * a.Kp * 2;
-    const __amdgpu_buffer_rsrc_t rsrc_w = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, (int)(w_bytes < BUF_MAX ? w_bytes : BUF_MAX), BUF_FLAGS);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, (int)(w_bytes < BUF_MAX ? w_bytes : BUF_MAX), BUF_FLAGS);
+    const int row = 16 * ((l32 >> 2) & 1) + 4 * (l32 >> 3) + (l32 & 3);
 #pragma unroll
     for (int i = 0; i < TC; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        const int v = 2 * j + g;
-        wreg[i][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_w, v < NV ? ((i * 32 + l32) * a.Kp + v * 8) * 2 : OOB, 0, 0);
+        const int v = BY_ROWS ? (2 * (j / PKW) + g) * PKW + j % PKW : 2 * j + g;
+        wreg[i][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, ((i * 32 + row) * a.Kp + v * 8) * 2, 0, 0);
       }
     if (tid < BC) sBias[tid] = a.bias[tid];
   }
+  __syncthreads();
 
-  const long long per_die = (n_units + 7) >> 3;      // contiguous chunk of the unit list per die (see conv.hip)
-  const long long t_end = per_die * 8;
-  auto unit_of = [&](long long t) -> long long { return (t & 7) * per_die + (t >> 3); };
-  auto next_valid = [&](long long t) -> long long {
-    while (t < t_end && unit_of(t) >= n_units) t += gridDim.x;
-    return t;
-  };
-  // (position in the unit list, tile of the unit) -> image, tile row and column.  Tile -1 of a segment that does not start
-  // at the top of its strip is the last tile of the segment above, computed once more for the row it carries over.
-  auto locate = [&](long long t, int k, int& img, int& ty, int& tx) {
-    const long long unit = unit_of(t);
-    img = (int)(unit / per_img);
-    const int rem = (int)(unit - (long long)img * per_img);
-    const int row = rem / tiles_x;
-    ty = row * seg + k;
-    tx = rem - row * tiles_x;
-  };
-  auto first_tile = [&](long long t) -> int { return POOL && unit_of(t) % per_img >= tiles_x ? -1 : 0; };
-  // global loads of a tile's input patch (zeros outside the image); one image per buffer: 32-bit offsets suffice
-  u32x4 pv[PLOADS];
-  auto load_patch = [&](long long t, int k) {
-    int img, ty, tx;
-    locate(t, k, img, ty, tx);
-    const int iy0 = ty * TH * 2 - a.pad_h, ix0 = (POOL ? tx * (2 * STEM_POOL_COLS) - 1 : tx * TW) - a.pad_w;   // patch origin in input rows / pairs
-    const long long img_bytes = img_elems * 2;
-    const __amdgpu_buffer_rsrc_t rsrc_x =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(xg + (long long)img * img_elems), 0, (int)(img_bytes < BUF_MAX ? img_bytes : BUF_MAX), BUF_FLAGS);
+  // operand reads; with the pool column 2 l + tp + s of a row is vector l + (tp + s) / 2 of its even or odd half, and s = 2 (j % 2) + g
+  int bbase[2];
 #pragma unroll
-    for (int i = 0; i < PLOADS; ++i) {
-      const int q = i * THREADS + tid;
-      const int prow = q / PW, pcol = q - prow * PW;
-      const int iy = iy0 + prow, ix = ix0 + pcol;
-      const bool ok = q < PVEC && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-      pv[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, ok ? (iy * a.W + ix) * a.x_ld * 2 : OOB, 0, 0);
+  for (int tp = 0; tp < 2; ++tp)
+    bbase[tp] = (POOL ? ((tp + g) & 1) * (SP_ROW / 2) + l32 + ((tp + g) >> 1) : tp * 32 + l32 + g * (BY_ROWS ? SP_ROW : 1)) * 16;
+  const long long img_elems = (long long)a.H * a.W * 8;
+  const int img_bytes = (int)(img_elems * 2), row_bytes = a.W * 16;          // fits (host)
+  const bool tail = !(POOL && PLAIN) && a.Cout % 8 != 0;
+  const int cs = (lane >> 4) * 8;            // channels of the vector this lane stores, of pixel lane % 16 (see swap_rows16)
+
+  // 32 pixels x 32 channels, two vectors of consecutive channels per lane, to row y0 of the output
+  auto store_block = [&](const __amdgpu_buffer_rsrc_t& ry, u32x4 (&out)[2], int i, int col0, int cols, int ld) __attribute__((always_inline)) {
+    swap_rows16(out[0], out[1]);
+    const int c = i * 32 + cs;
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int pc = col0 + v * 16 + (lane & 15);
+      const int yo = pc < cols ? (pc * ld + c) * 2 : OOB;
+      __builtin_amdgcn_raw_buffer_store_b128(out[v], ry, c + 8 <= a.Cout ? yo : OOB, 0, 0);
+      if (tail && a.Cout > i * 32 && a.Cout < i * 32 + 32) {           // the vector that ends past the last channel: value by value
+        const int to = c < a.Cout && c + 8 > a.Cout ? yo : OOB;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (e < a.Cout % 8) __builtin_amdgcn_raw_buffer_store_b16((short)(out[v][e / 2] >> (e % 2 * 16)), ry, to + e * 2, 0, 0);
+      }
     }
   };
 
-  long long t = next_valid(blockIdx.x);
-  int k = 0;
-  if (t < t_end) { k = first_tile(t); load_patch(t, k); }
-  while (t < t_end) {
-    int img, ty, tx;
-    locate(t, k, img, ty, tx);
-    const int oy0 = ty * TH, ox0 = POOL ? tx * (2 * STEM_POOL_COLS) - 1 : tx * TW;
-    __syncthreads();                     // the previous tile's staged output has been written out / pooled
+  // runs of four units (one per wavefront) go round the dies
+  for (int unit = blockIdx.x * 4 + wave; unit < n_units; unit += gridDim.x * 4) {
+    const int img = unit / per_img, rem = unit - img * per_img, sx = rem / segs, sy = rem - sx * segs;
+    const int px0 = sx * WIDTH, py0 = sy * seg, py1 = py0 + seg < out_h ? py0 + seg : out_h;
+    // convolution columns and rows; with the pool a segment also computes the row that its first windows share with the segment above,
+    // and its last row may lie outside
+    const int ox0 = POOL ? 2 * px0 - 1 : px0, ys = POOL ? (py0 > 0 ? 2 * py0 - 1 : 0) : py0, ye = POOL ? 2 * py1 - 1 : py1 - 1;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)((const T*)a.x + a.x_coff + (long long)img * img_elems), 0, img_bytes, BUF_FLAGS);
+    // loader: vector p = 64 k + lane of a pair; columns outside the image read as zeros, and so do rows, whose offsets lie outside the buffer
+    int loff[3];
 #pragma unroll
-    for (int i = 0; i < PLOADS; ++i) sR[i * THREADS + tid] = pv[i];
-    __syncthreads();
+    for (int k = 0; k < 3; ++k) {
+      const int p = k * 64 + lane, sub = p >= SP_ROW ? 1 : 0, pos = p - sub * SP_ROW;
+      const int col = !POOL ? pos : pos < SP_ROW / 2 ? 2 * pos : 2 * (pos - SP_ROW / 2) + 1, ix = ox0 - a.pad_w + col;
+      loff[k] = col < SP_STRIP + PKW - 1 && (unsigned)ix < (unsigned)a.W ? (sub * a.W + ix) * 16 : OOB;
+    }
+    const int last_pair = ye + NP - 1;
+    auto load_pair = [&](int q) __attribute__((always_inline)) {       // input rows 2 q - pad, 2 q + 1 - pad
+      const int base = (2 * q - a.pad_h) * row_bytes;
+      const unsigned at = lds + (unsigned)(q & (SP_PAIRS - 1)) * SP_PAIR;
+      const bool any = q <= last_pair;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const int off = any && loff[k] != OOB ? loff[k] + base : OOB;
+        if (k < 2 || lane < 2 * SP_ROW - 128)
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" :: "s"(at + k * 1024), "v"(off), "s"(rx) : "memory");
+      }
+    };
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 1
+    for (int q = ys; q < ys + SP_PAIRS - 1; ++q) load_pair(q);
 
-    floatx16 acc[TC][2];
-#pragma unroll
-    for (int i = 0; i < TC; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    const int prow0 = (wave * 2) * 2 * PW + l32;       // patch vector of tap (0, 0) for this lane's pixel of block 0
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int v0 = 2 * j, v1 = 2 * j + 1 < NV ? 2 * j + 1 : NV - 1;   // a half step past the end re-reads a valid vector: its weights are zero
-      const int off0 = (v0 / PKW) * PW + (v0 % PKW), off1 = (v1 / PKW) * PW + (v1 % PKW);
-      const int boff = prow0 + (g ? off1 : off0);
-      u32x4 fb[2];
-#pragma unroll
-      for (int tp = 0; tp < 2; ++tp) fb[tp] = sR[boff + tp * 2 * PW];
+    // pool: columns outside the image do not take part - convolution column -1, and the last one plus 1 of an odd width
+    const bool edge = px0 == 0 || 2 * (px0 + SP_POOLED) > a.Wo, col_in = (unsigned)(ox0 + 2 * l32) < (unsigned)a.Wo;
+    float run[POOL ? TC : 1][16];            // maximum over the window's rows so far
+    if constexpr (POOL) {
 #pragma unroll
       for (int i = 0; i < TC; ++i)
 #pragma unroll
-        for (int tp = 0; tp < 2; ++tp) acc[i][tp] = E::mfma(wreg[i][j], fb[tp], acc[i][tp]);
+        for (int k = 0; k < 16; ++k) run[i][k] = -INFINITY;
     }
-
-    // the next tile's patch is fetched while this one is staged and written (or pooled)
-    long long nt = t;
-    int nk = k + 1;
-    if (nk == seg || ty + 1 == tiles_y || !POOL) {
-      nt = next_valid(t + gridDim.x);
-      if (nt < t_end) nk = first_tile(nt);
-    }
-    if (nt < t_end) load_patch(nt, nk);
-
-    __syncthreads();                     // everyone is done with the patch: the region now stages the output
+    for (int y = ys; y <= ye; ++y) {
+      load_pair(y + SP_PAIRS - 1);           // into the place of the pair that the row before used last
+      // Younger than this row's last pair: the loads of the AHEAD pairs after it, and the stores of the AHEAD rows before this one, if there
+      // were that many (with the pool those of a second row each: AHEAD rows are sure to hold that many from row AHEAD + 1 on)
+      if (y - ys >= AHEAD + (POOL ? 1 : 0)) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * AHEAD + STORES) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * AHEAD) : "memory");
+      floatx16 acc[TC][2];
 #pragma unroll
-    for (int tp = 0; tp < 2; ++tp) {
-      const int pl = (wave * 2 + tp) * TW + l32;
-      // the tile's last row also goes to the carry buffer that the strip's next tile reads
-      char* carry = POOL && wave * 2 + tp == TH - 1 ? (char*)sCarry + (size_t)(((k + 1) & 1) * TW + l32) * OPITCH : nullptr;
+      for (int i = 0; i < TC; ++i)
 #pragma unroll
-      for (int i = 0; i < TC; ++i) {
-        const int cblk = i * 32 + g * 4;
+        for (int tp = 0; tp < 2; ++tp)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const floatx4 b4 = *(const floatx4*)&sBias[cblk + q * 8];
-          floatx4 v;
+          for (int r = 0; r < 16; ++r) acc[i][tp][r] = 0.0f;
+      u32x4 fb[PD][2];
+      auto read = [&](int j) __attribute__((always_inline)) {
+        const int row = BY_ROWS ? 2 * (j / PKW) : 2 * j / PKW, s = BY_ROWS ? j % PKW : 2 * j % PKW;      // of half 0
+        const unsigned char* p = ring + ((y + row / 2) & (SP_PAIRS - 1)) * SP_PAIR;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = fmaxf(acc[i][tp][q * 4 + e] + b4[e], act_lo);
-          if (is_silu) {
+        for (int tp = 0; tp < 2; ++tp) fb[j % PD][tp] = *(const u32x4*)(p + bbase[tp] + (row & 1) * (SP_ROW * 16) + (POOL ? s / 2 : s) * 16);
+      };
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = silu(v[e]);
+      for (int j = 0; j < PD - 1; ++j) read(j);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (j + PD - 1 < NJ) read(j + PD - 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TC; ++i)
+#pragma unroll
+          for (int tp = 0; tp < 2; ++tp) acc[i][tp] = E::mfma(wreg[i][j], fb[j % PD][tp], acc[i][tp]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      typedef T t4 __attribute__((ext_vector_type(4)));
+      if constexpr (!POOL) {
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void*)((T*)a.y + (((size_t)img * a.Ho + y) * a.Wo + px0) * a.y_ld + a.y_coff), 0, (int)BUF_MAX, BUF_FLAGS);
+#pragma unroll
+        for (int i = 0; i < TC; ++i)
+#pragma unroll
+          for (int tp = 0; tp < 2; ++tp) {
+            u32x4 out[2];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const floatx4 b4 = *(const floatx4*)&sBias[i * 32 + g * 16 + q * 4];
+              t4 o;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float v = fmaxf(acc[i][tp][q * 4 + e] + b4[e], act_lo);
+                o[e] = (T)(is_silu ? silu(v) : v);
+              }
+              const u32x2 ob = __builtin_bit_cast(u32x2, o);
+              out[q / 2][q % 2 * 2] = ob[0]; out[q / 2][q % 2 * 2 + 1] = ob[1];
+            }
+            store_block(ry, out, i, tp * 32, a.Wo - px0, a.y_ld);
           }
-          if constexpr (POOL) {              // staged as order keys: the pooling pass is then a plain integer maximum
-            typedef T t4 __attribute__((ext_vector_type(4)));
-            const t4 h = {(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-            u32x2 kk = __builtin_bit_cast(u32x2, h);
-            kk[0] = order_key16x2(kk[0]); kk[1] = order_key16x2(kk[1]);
-            *(u32x2*)((char*)sR + (size_t)pl * OPITCH + (size_t)(cblk + q * 8) * 2) = kk;
-            if (carry) *(u32x2*)(carry + (size_t)(cblk + q * 8) * 2) = kk;
-          } else {
-            store4<T>((T*)((char*)sR + (size_t)pl * OPITCH) + cblk + q * 8, v);
+      } else {
+        // the matrix results are read by inline assembly below: wait states that the compiler would insert for its own instructions
+#pragma unroll
+        for (int i = TC - 1; i >= 0; --i) {
+          if (i == TC - 1) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acc[i][0]), "+v"(acc[i][1]));
+          else asm volatile("" : "+v"(acc[i][0]), "+v"(acc[i][1]));
+        }
+        if (is_silu) {
+#pragma unroll
+          for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const floatx4 b4 = *(const floatx4*)&sBias[i * 32 + g * 16 + q * 4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i][tp][q * 4 + e] = silu(fmaxf(acc[i][tp][q * 4 + e] + b4[e], -INFINITY));
+              }
+        }
+        if (edge) {
+#pragma unroll
+          for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc[i][0][k] = col_in ? acc[i][0][k] : -INFINITY;
+        }
+        // horizontal maximum of columns 2 l, 2 l + 1 and the next lane's 2 l (lane 31 of a half has no next one, and no pooled column)
+        auto across = [&](auto keep_nan) __attribute__((always_inline)) {
+#pragma unroll
+          for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+              const float c0 = acc[i][0][k];
+              const float next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c0), 0x130, 0xF, 0xF, true));
+              acc[i][0][k] = max3_raw<keep_nan.value>(c0, acc[i][1][k], next);
+            }
+        };
+        if (is_silu) across(std::true_type{});
+        else across(std::false_type{});
+        if (y >= a.Ho) {                     // the last row of an odd height is missing
+#pragma unroll
+          for (int i = 0; i < TC; ++i) acc[i][0] = -INFINITY;
+        }
+        // the window's rows so far
+        auto down = [&](auto keep_nan) __attribute__((always_inline)) {
+#pragma unroll
+          for (int i = 0; i < TC; ++i)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) run[i][k] = max3_raw<keep_nan.value>(run[i][k], acc[i][0][k], acc[i][0][k]);
+        };
+        if (is_silu) down(std::true_type{});
+        else down(std::false_type{});
+        if (!(y & 1) || (y == ys && py0 > 0)) continue;    // the first row of a pair, or the row shared with the segment above
+        // row y ends the windows of pooled row y / 2 and begins those of the next
+        const int cols = px0 + SP_POOLED < a.pool_wo ? SP_POOLED : a.pool_wo - px0;
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+            (void*)((T*)a.pool_y + (((size_t)img * a.pool_ho + (y >> 1)) * a.pool_wo + px0) * a.pool_ld + a.pool_coff), 0, (int)BUF_MAX, BUF_FLAGS);
+#pragma unroll
+        for (int i = 0; i < TC; ++i) {
+          u32x4 out[2];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const floatx4 b4 = *(const floatx4*)&sBias[i * 32 + g * 16 + q * 4];
+            t4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int k = q * 4 + e;
+              o[e] = (T)(is_silu ? run[i][k] : fmaxf(run[i][k] + b4[e], act_lo));
+              run[i][k] = acc[i][0][k];
+            }
+            const u32x2 ob = __builtin_bit_cast(u32x2, o);
+            out[q / 2][q % 2 * 2] = ob[0]; out[q / 2][q % 2 * 2 + 1] = ob[1];
           }
+          store_block(ry, out, i, 0, cols, a.pool_ld);
         }
       }
     }
-    __syncthreads();
-    constexpr int VPR = BC / 8;                  // 16-byte vectors per pixel
-    if constexpr (POOL) {
-      if (k < 0) { t = nt; k = nk; continue; }
-      // pooled rows 4 ty .. 4 ty + 3: window rows 2 py - 1 .. 2 py + 1 = staged rows -1 (the carry) .. 7; window columns
-      // 2 pc .. 2 pc + 2 of the tile (convolution column = ox0 + tile column)
-      constexpr int POOL_ROWS = TH / 2;
-      for (int item = tid; item < POOL_ROWS * STEM_POOL_COLS * VPR; item += THREADS) {
-        const int v = item % VPR, pp = item / VPR;
-        const int pr = pp / STEM_POOL_COLS, pc = pp - pr * STEM_POOL_COLS;
-        const int py = ty * POOL_ROWS + pr, px = tx * STEM_POOL_COLS + pc;
-        if (py >= a.pool_ho || px >= a.pool_wo || v * 8 >= a.Cout) continue;
-        u32x4 best = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};      // smallest key
-#pragma unroll
-        for (int dr = 0; dr < 3; ++dr) {
-          const int r = 2 * pr + dr - 1;         // staged row, -1: the carry
-          const int oy = oy0 + r;
-          if (oy < 0 || oy >= a.Ho) continue;
-          const char* row = r < 0 ? (const char*)sCarry + (size_t)((k & 1) * TW) * OPITCH : (const char*)sR + (size_t)(r * TW) * OPITCH;
-#pragma unroll
-          for (int dc = 0; dc < 3; ++dc) {
-            const int col = 2 * pc + dc;
-            const int ox = ox0 + col;
-            if (ox < 0 || ox >= a.Wo) continue;
-            const u32x4 val = *(const u32x4*)(row + (size_t)col * OPITCH + (size_t)v * 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) best[e] = max_i16x2(best[e], val[e]);
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) best[e] = order_key16x2(best[e]);
-        T* yp = (T*)a.pool_y + (((size_t)img * a.pool_ho + py) * a.pool_wo + px) * a.pool_ld + a.pool_coff + v * 8;
-        if (v * 8 + 8 <= a.Cout) {
-          *(u32x4*)yp = best;
-        } else {
-          typedef T tv __attribute__((ext_vector_type(8)));
-          const tv tvv = __builtin_bit_cast(tv, best);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) if (v * 8 + e < a.Cout) yp[e] = tvv[e];
-        }
-      }
-    } else {
-    constexpr int PPP = THREADS / VPR;           // pixels per pass
-    const int v = tid % VPR, pr = tid / VPR;
-    const int c = v * 8;
-#pragma unroll
-    for (int ps = 0; ps < BP / PPP; ++ps) {
-      const int pl = ps * PPP + pr;
-      const int oy = oy0 + pl / TW, ox = ox0 + pl % TW;
-      if (oy < a.Ho && ox < a.Wo && c < a.Cout) {
-        const u32x4 val = *(const u32x4*)((const char*)sR + (size_t)pl * OPITCH + (size_t)v * 16);
-        T* yp = (T*)a.y + (((size_t)img * a.Ho + oy) * a.Wo + ox) * a.y_ld + a.y_coff + c;
-        if (c + 8 <= a.Cout) {
-          *(u32x4*)yp = val;
-        } else {
-          typedef T tv __attribute__((ext_vector_type(8)));
-          const tv tvv = __builtin_bit_cast(tv, val);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) if (c + e < a.Cout) yp[e] = tvv[e];
-        }
-      }
-    }
-    }
-    t = nt; k = nk;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the last loads write into LDS
 }
 
+template <typename T, int BC, int KH, int PKW, bool POOL>
+__global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a) { stem_walk<T, BC, KH, PKW, POOL, true>(a); }
+template <typename T, int BC, int KH, int PKW>
+__global__ __launch_bounds__(THREADS, 2) void stem_pool_any_kernel(const ConvArgs a) { stem_walk<T, BC, KH, PKW, true, false>(a); }
 
 template <typename T, int BC, int KH, int PKW, bool POOL>
 static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (kernel_id) *kernel_id = stem_kernel_id(BC, KH, PKW, POOL);
-  const long long units = POOL ? (long long)a.n * ((a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS) * (((a.Ho + STEM_TH - 1) / STEM_TH + a.pool_seg - 1) / a.pool_seg)
-                               : (long long)a.n * ((a.Wo + STEM_TW - 1) / STEM_TW) * ((a.Ho + STEM_TH - 1) / STEM_TH);
+  // Output rows per segment: a strip walked by one wavefront is a serial chain (11 crops of 224 x 224 have 22 strips of 112 rows, the chip has
+  // 2048 wavefronts).  Cut into segments it costs, with the pool, one more convolution row for each cut, and about two rows' time to start;
+  // the length with the shortest busiest wavefront is taken, for the expected number of items.
+  ConvArgs b = a;
+  const int out_w = POOL ? a.pool_wo : a.Wo, out_h = POOL ? a.pool_ho : a.Ho, width = POOL ? SP_POOLED : SP_STRIP;
+  const long long strips = (out_w + width - 1) / width, waves = 8LL * num_cu;
+  const long long items = a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n;
+  long long best = 0;
+  for (int seg = out_h; seg >= 1; --seg) {
+    const long long units = items * strips * ((out_h + seg - 1) / seg), rounds = (units + waves - 1) / waves;
+    const long long rows = rounds * (POOL ? 2 * seg + 3 : seg + 2);
+    if (seg == out_h || rows < best) { best = rows; b.stem_seg = seg; }
+  }
+  const long long units = out_h > 0 ? (long long)a.n * strips * ((out_h + b.stem_seg - 1) / b.stem_seg) : 0;
   if (units <= 0) return hipSuccess;
-  long long grid = (units + 7) / 8 * 8;
-  const long long cap = (long long)num_cu * 2;
-  if (grid > cap) grid = cap;
-  if (tm.start && tm.stop)
-    hipExtLaunchKernelGGL((stem_conv_kernel<T, BC, KH, PKW, POOL>), dim3((unsigned)grid), dim3(THREADS), 0, s, tm.start, tm.stop, 0, a);
-  else
-    hipLaunchKernelGGL((stem_conv_kernel<T, BC, KH, PKW, POOL>), dim3((unsigned)grid), dim3(THREADS), 0, s, a);
+  if (units >= 0x7FFF0000LL) return hipErrorNotSupported;
+  long long grid = ((units + 3) / 4 + 7) / 8 * 8;
+  if (grid > 2LL * num_cu) grid = 2LL * num_cu;
+  void (*kernel)(ConvArgs) = stem_conv_kernel<T, BC, KH, PKW, POOL>;
+  if constexpr (POOL) {
+    if (a.act == OCTO_ACT_SILU || a.Cout % 8 != 0) kernel = stem_pool_any_kernel<T, BC, KH, PKW>;
+  }
+  if (tm.start && tm.stop) hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(THREADS), 0, s, tm.start, tm.stop, 0, b);
+  else hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(THREADS), 0, s, b);
   return hipGetLastError();
 }
 
@@ -286,19 +323,7 @@ template <typename T>
 static hipError_t launch_stem_typed(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (a.pool_y) {
     if (a.kh != 7 || a.kw != 4 || a.Cout > 64) return hipErrorNotSupported;
-    // Tiles per segment: a strip walked by one workgroup is a serial chain (11 crops of 224 x 224 have 44 strips of 14
-    // tiles: 68 us on 44 of the chip's 512 workgroup slots).  Cut into segments it costs one more tile for each cut; the
-    // length with the shortest busiest slot is taken, for the expected number of items.
-    ConvArgs b = a;
-    const int tiles_y = (a.Ho + STEM_TH - 1) / STEM_TH;
-    const long long strips = (long long)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * ((a.pool_wo + STEM_POOL_COLS - 1) / STEM_POOL_COLS);
-    long long best = 0;
-    for (int seg = tiles_y; seg >= 1; --seg) {
-      const long long units = strips * ((tiles_y + seg - 1) / seg), rounds = (units + 2 * num_cu - 1) / (2 * num_cu);
-      const long long tiles = rounds * (seg == tiles_y ? seg : seg + 1);
-      if (seg == tiles_y || tiles < best) { best = tiles; b.pool_seg = seg; }
-    }
-    return launch_stem_cfg<T, 64, 7, 4, true>(b, num_cu, s, kernel_id, tm);
+    return launch_stem_cfg<T, 64, 7, 4, true>(a, num_cu, s, kernel_id, tm);
   }
   if (a.kh == 7 && a.kw == 4 && a.Cout <= 64) return launch_stem_cfg<T, 64, 7, 4, false>(a, num_cu, s, kernel_id, tm);
   if (a.kh == 6 && a.kw == 3 && a.Cout <= 32) return launch_stem_cfg<T, 32, 6, 3, false>(a, num_cu, s, kernel_id, tm);
