@@ -597,7 +597,15 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
     if (em != hipErrorNotSupported) return em;
   }
-  const bool pipe_ok = sizeof(T) == 2 && !a.up_y;      // (only the split-K kernel writes an upsampled copy)
+  // Only the split-K kernel writes an upsampled copy.  Where it is worth that, the same layer on its own takes it too (8 x 20 x 20, 512 -> 256:
+  // 6.5 us estimated, 6.4 for the best other one), so that fused and separate launches sum in one order.
+  if (sizeof(T) == 2 && (a.up_y || a.up_next)) {
+    const GeneralTile st = general_tile(a, M_split, num_cu, 1, false);
+    const int ks = ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
+    if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
+  }
+  if (a.up_y) return hipErrorNotSupported;
+  const bool pipe_ok = sizeof(T) == 2;
   if constexpr (sizeof(T) == 2) {
     // conv_flow_kernel takes what has its form, except strided layers in one round of pipelined 64x64 tiles: 256 -> 512, stride 2 on
     // 42 x 14 x 14 16.1 us here, 18.1 there, 128 -> 128, stride 2 on 8 x 80 x 80 10.5 : 11.1 (a step of such a tile is four matrix instructions
@@ -624,7 +632,6 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   const GeneralTile st = general_tile(a, M_split, num_cu, 1, pipe_ok);
   const int ks = st.pipe ? -1 : ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
   if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
-  if (a.up_y) return hipErrorNotSupported;
   const GeneralTile t = general_tile(a, M, num_cu, 1, pipe_ok);
   if constexpr (sizeof(T) == 2) {
     if (t.pipe && t.bp == 256) return launch_cfg<T, 128, 256, 2, 2, 4, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);

@@ -52,6 +52,7 @@ struct ConvArgs {
   // Nearest 2x upsampling of the output, written beside y (16-bit types, whole 16-byte vectors, no second output): pixel
   // (i, j) also goes to pixels (2 i .. 2 i + 1, 2 j .. 2 j + 1) of up_y.  Unused when null.
   void* up_y;
+  int up_next;                    // host only: an upsampling of the output follows; the split-K kernel is chosen as if it were to write it
   int up_ld, up_coff;
   // 8-bit floating point storage only: y = act(acc * scale[c] + bias[c] (+ res * res_scale)), stored as
   // E4M3(y * y_inv_scale) unless out_f32.  scale: device, one factor per output channel, padded like the bias.

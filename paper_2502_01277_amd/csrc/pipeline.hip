@@ -78,7 +78,7 @@ struct LayerPlan {
   bool fuse_pool = false;
   // The next layer is a nearest 2x upsampling of this convolution's output.  Where the kernel chosen for the launch can
   // write both tensors it does (up_done) and the next layer does nothing.
-  bool fuse_up = false, up_done = false;
+  bool up_next = false, fuse_up = false, up_done = false;      // (such a next layer; it may be fused; it was)
   // This and the next two layers are chained stride-1 max-pools of one size (a spatial-pyramid block): one launch does all
   // three; the next two layers then do nothing.  Cleared for good the first time no kernel accepts the chain.
   bool fuse_chain = false;
@@ -387,8 +387,9 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
   for (int i = 0; i + 1 < (int)m.layers.size(); ++i) {
     LayerPlan& lp = m.layers[i];
     const octo_layer& U = m.layers[i + 1].L;
-    lp.fuse_up = allow_fusion && dtype_size(m.d.dtype) == 2 && lp.L.op == OCTO_CONV && lp.L.kh == 1 && lp.L.kw == 1 && !lp.pair_view && !lp.fuse_pool &&
+    lp.up_next = dtype_size(m.d.dtype) == 2 && lp.L.op == OCTO_CONV && lp.L.kh == 1 && lp.L.kw == 1 && !lp.pair_view && !lp.fuse_pool &&
                  U.op == OCTO_UPSAMPLE2X && U.in[0] == i + 1;
+    lp.fuse_up = allow_fusion && lp.up_next;
   }
   // three chained stride-1 max-pools of one size
   for (int i = 0; i + 2 < (int)m.layers.size(); ++i) {
@@ -561,6 +562,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (L.n_in == 2) { const TensorView r = view_of(m, L.in[1]); a.res = r.ptr; a.res_ld = r.ld; a.res_coff = r.coff; }
       if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
+      a.up_next = lp.up_next;
       if (i > 0 && m.layers[i - 1].fuse_twin) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (lp.fuse_twin) {
         const TensorView y2 = view_of(m, i + 2);
