@@ -242,41 +242,45 @@ __global__ void add_kernel(const AddArgs a) {
 // Global average pool, one workgroup per (item, 64 V channels): VL lanes take neighbouring 16-byte channel vectors of a
 // pixel, the workgroup's 256 / VL lane groups every (256 / VL)-th pixel, and the groups' sums meet in LDS.  A thread per
 // channel that walked all pixels alone was one chain of loads: 14 us for 11 items of 7 x 7 x 512 and 2.0 TB/s for 3617.
+template <typename T, typename Out>
+__device__ __forceinline__ void gap_chunk(const PoolArgs& a, int img, int chunk, int vl, float (*part)[16 / sizeof(T) + 1], Out&& out) {
+  constexpr int V = 16 / (int)sizeof(T);
+  const int cv = a.C / V, hw = a.H * a.W;
+  const int lane = threadIdx.x & (vl - 1), group = threadIdx.x / vl, groups = 256 / vl, v = chunk * vl + lane;
+  float s[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) s[e] = 0.0f;
+  if (v < cv) {
+    const T* p = (const T*)a.x + (size_t)img * hw * a.x_ld + a.x_coff + v * V;
+#pragma unroll 4
+    for (int j = group; j < hw; j += groups) {
+      alignas(16) T q[V];
+      *(uint4*)q = *(const uint4*)(p + (size_t)j * a.x_ld);
+#pragma unroll
+      for (int e = 0; e < V; ++e) s[e] += (float)q[e];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < V; ++e) part[threadIdx.x][e] = s[e];
+  __syncthreads();
+  for (int o = threadIdx.x; o < vl * V; o += 256) {
+    const int l = o / V, e = o - l * V, c = (chunk * vl + l) * V + e;
+    if (c < a.C) {
+      float t = 0.0f;
+      for (int g = 0; g < groups; ++g) t += part[g * vl + l][e];
+      out(c, (T)(t / (float)hw));
+    }
+  }
+  __syncthreads();
+}
 template <typename T>
 __global__ __launch_bounds__(256) void gap_kernel(const PoolArgs a, int vl) {
   constexpr int V = 16 / (int)sizeof(T);
   __shared__ float part[256][V + 1];
-  const int items = dyn_items(a.n_dyn, a.n);
-  const int cv = a.C / V, chunks = (cv + vl - 1) / vl;
-  const int lane = threadIdx.x & (vl - 1), group = threadIdx.x / vl, groups = 256 / vl;
-  const int hw = a.H * a.W;
+  const int items = dyn_items(a.n_dyn, a.n), chunks = (a.C / V + vl - 1) / vl;
   for (int u = blockIdx.x; u < items * chunks; u += gridDim.x) {
-    const int img = u / chunks, v = (u - img * chunks) * vl + lane;
-    float s[V];
-#pragma unroll
-    for (int e = 0; e < V; ++e) s[e] = 0.0f;
-    if (v < cv) {
-      const T* p = (const T*)a.x + (size_t)img * hw * a.x_ld + a.x_coff + v * V;
-#pragma unroll 4
-      for (int j = group; j < hw; j += groups) {
-        alignas(16) T q[V];
-        *(uint4*)q = *(const uint4*)(p + (size_t)j * a.x_ld);
-#pragma unroll
-        for (int e = 0; e < V; ++e) s[e] += (float)q[e];
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < V; ++e) part[threadIdx.x][e] = s[e];
-    __syncthreads();
-    for (int o = threadIdx.x; o < vl * V; o += 256) {
-      const int l = o / V, e = o - l * V, c = ((u - img * chunks) * vl + l) * V + e;
-      if (c < a.C) {
-        float t = 0.0f;
-        for (int g = 0; g < groups; ++g) t += part[g * vl + l][e];
-        ((T*)a.y)[(size_t)img * a.y_ld + a.y_coff + c] = (T)(t / (float)hw);
-      }
-    }
-    __syncthreads();
+    const int img = u / chunks;
+    gap_chunk<T>(a, img, u - img * chunks, vl, part, [&](int c, T m) { ((T*)a.y)[(size_t)img * a.y_ld + a.y_coff + c] = m; });
   }
 }
 // channel counts or pitches that are no whole vectors: one thread per (item, channel)
@@ -296,36 +300,96 @@ __global__ void gap_scalar_kernel(const PoolArgs a) {
   }
 }
 
-// one wavefront per row; ties resolve to the lowest index.  Eight loads per lane are in flight at a time.  With
-// d.boxes, the label is also written to the result record of the box the row was cropped from.
+// Index of the largest of a row's values for a wavefront; ties resolve to the lowest index, 0 if there is no number.  Eight loads per lane
+// are in flight at a time.
+__device__ __forceinline__ int wave_argmax(const float* row, int n_out, int lane) {
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+  for (int j0 = lane; j0 < n_out; j0 += 512) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = j0 + 64 * q < n_out ? row[j0 + 64 * q] : -INFINITY;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (j0 + 64 * q < n_out && (v[q] > best || (v[q] == best && j0 + 64 * q < bi))) { best = v[q]; bi = j0 + 64 * q; }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    float ob = __shfl_xor(best, off);
+    int oi = __shfl_xor(bi, off);
+    if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+  }
+  return bi == 0x7fffffff ? 0 : bi;
+}
+// The label of a row; with d.boxes it is also written to the result record of the box the row was cropped from.
+__device__ __forceinline__ void put_label(int* labels, const LabelDest& d, int r, int label) {
+  labels[r] = label;
+  if (d.boxes) d.boxes[(size_t)d.rois[r].frame * d.max_det + d.rois[r].rank].child_label[d.slot] = label;
+}
+// one wavefront per row
 __global__ __launch_bounds__(256) void argmax_kernel(const float* logits, int ld, int n_out, const int* n_dyn, int n, int* labels, const LabelDest d) {
   const int rows = dyn_items(n_dyn, n);
   const int lane = threadIdx.x & 63;
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int n_waves = (gridDim.x * blockDim.x) >> 6;
   for (int r = wave; r < rows; r += n_waves) {
-    float best = -INFINITY;
-    int bi = 0x7fffffff;
-    const float* row = logits + (size_t)r * ld;
-    for (int j0 = lane; j0 < n_out; j0 += 512) {
-      float v[8];
+    const int label = wave_argmax(logits + (size_t)r * ld, n_out, lane);
+    if (lane == 0) put_label(labels, d, r, label);
+  }
+}
+
+// The end of a classifier - global average pool, fully connected layer, label - with a workgroup per item, which keeps the means in LDS and
+// reads the whole weight matrix: three launches of a chain in one.  The means are rounded to the tensor's type as the pool kernel does; a logit
+// is summed in fp32, 64 lanes' parts and then their sum.  Bound by latency, for many items by reading the map.  Measured in us with a copy of
+// the input, separate : fused, 16-bit: 64 channels to 10 outputs 13.2 : 7.6 for 2 items, 19.0 : 18.0 for 2048; 512 channels to 16 outputs
+// (16 KB of weights) 15.5 : 10.6 and 54.9 : 53.3; to 32 15.2 : 11.7 and 54.9 : 56.9; to 128 16.0 : 18.6; 2048 channels to 8 15.8 : 20.6 (a workgroup
+// takes them in four turns).  Hence the lines: one turn of 64 channel vectors, 16 KB.
+constexpr int CLASSIFY_W_BYTES = 16 * 1024, CLASSIFY_OUT = CLASSIFY_W_BYTES / 128;       // (rows are padded to 128 bytes)
+template <typename T>
+__global__ __launch_bounds__(256) void classify_kernel(const ClassifyArgs a, int vl) {
+  constexpr int V = 16 / (int)sizeof(T), OUTS = 4;     // outputs that a wavefront sums at a time
+  __shared__ float part[256][V + 1];
+  __shared__ __attribute__((aligned(16))) float mean[64 * V];
+  __shared__ float logit[CLASSIFY_OUT];
+  const PoolArgs& g = a.pool;
+  const int items = dyn_items(g.n_dyn, g.n);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int img = blockIdx.x; img < items; img += gridDim.x) {
+    gap_chunk<T>(g, img, 0, vl, part, [&](int c, T m) { ((T*)g.y)[(size_t)img * g.y_ld + g.y_coff + c] = m; mean[c] = (float)m; });
+    for (int o0 = wave * OUTS; o0 < a.n_out; o0 += 4 * OUTS) {
+      float s[OUTS];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = j0 + 64 * q < n_out ? row[j0 + 64 * q] : -INFINITY;
+      for (int q = 0; q < OUTS; ++q) s[q] = 0.0f;
+      if (const int k = lane * V; k < g.C) {
+        alignas(16) T w[OUTS][V];
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        if (j0 + 64 * q < n_out && (v[q] > best || (v[q] == best && j0 + 64 * q < bi))) { best = v[q]; bi = j0 + 64 * q; }
-    }
+        for (int q = 0; q < OUTS; ++q)       // (an output past the last one repeats it)
+          *(uint4*)w[q] = *(const uint4*)((const T*)a.w + (size_t)(o0 + q < a.n_out ? o0 + q : a.n_out - 1) * a.kp + k);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      float ob = __shfl_xor(best, off);
-      int oi = __shfl_xor(bi, off);
-      if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+        for (int e = 0; e < V; ++e) {
+          const float m = mean[k + e];
+#pragma unroll
+          for (int q = 0; q < OUTS; ++q) s[q] = fmaf((float)w[q][e], m, s[q]);
+        }
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < OUTS; ++q) s[q] += __shfl_xor(s[q], off);
+#pragma unroll
+      for (int q = 0; q < OUTS; ++q)
+        if (lane == q && o0 + q < a.n_out) {
+          const float v = s[q] + a.bias[o0 + q];
+          logit[o0 + q] = v;
+          a.logits[(size_t)img * a.ld + o0 + q] = v;
+        }
     }
-    if (lane == 0) {
-      const int label = bi == 0x7fffffff ? 0 : bi;
-      labels[r] = label;
-      if (d.boxes) d.boxes[(size_t)d.rois[r].frame * d.max_det + d.rois[r].rank].child_label[d.slot] = label;
+    __syncthreads();
+    if (wave == 0) {
+      const int label = wave_argmax(logit, a.n_out, lane);
+      if (lane == 0) put_label(a.labels, a.dest, img, label);
     }
+    __syncthreads();                         // the logits have been read
   }
 }
 
@@ -416,11 +480,17 @@ template <typename T> static hipError_t add_t(const AddArgs& a, hipStream_t s) {
 hipError_t launch_add(int dtype, const AddArgs& a, hipStream_t s) {
   DISPATCH_T(dtype, add_t<float>(a, s), add_t<_Float16>(a, s), add_t<__bf16>(a, s))
 }
+// lanes over channel vectors in a workgroup of the pool kernel; 0: no whole vectors
+template <typename T> static int gap_lanes(const PoolArgs& a) {
+  constexpr int V = 16 / sizeof(T);
+  if (a.C % V != 0 || a.x_ld % V != 0 || a.x_coff % V != 0 || ((uintptr_t)a.x & 15) != 0) return 0;
+  int vl = 4;
+  while (vl < 64 && vl < a.C / V) vl *= 2;
+  return vl;
+}
 template <typename T> static hipError_t gap_t(const PoolArgs& a, hipStream_t s) {
   constexpr int V = 16 / sizeof(T);
-  if (a.C % V == 0 && a.x_ld % V == 0 && a.x_coff % V == 0 && ((uintptr_t)a.x & 15) == 0) {
-    int vl = 4;
-    while (vl < 64 && vl < a.C / V) vl *= 2;
+  if (const int vl = gap_lanes<T>(a)) {
     const long long units = (long long)a.n * ((a.C / V + vl - 1) / vl);
     if (units < 0x7FFFFFFFLL) {
       hipLaunchKernelGGL((gap_kernel<T>), dim3((unsigned)(units < 256 * 8 ? units : 256 * 8)), dim3(256), 0, s, a, vl);
@@ -432,6 +502,18 @@ template <typename T> static hipError_t gap_t(const PoolArgs& a, hipStream_t s) 
 }
 hipError_t launch_gap(int dtype, const PoolArgs& a, hipStream_t s) {
   DISPATCH_T(dtype, gap_t<float>(a, s), gap_t<_Float16>(a, s), gap_t<__bf16>(a, s))
+}
+template <typename T> static hipError_t classify_t(const ClassifyArgs& a, hipStream_t s) {
+  const int vl = gap_lanes<T>(a.pool);
+  if (!vl || a.pool.C > 1024 / (int)sizeof(T) || a.n_out < 1 || a.n_out > CLASSIFY_OUT || (long long)a.n_out * a.kp * (int)sizeof(T) > CLASSIFY_W_BYTES ||
+      a.kp < a.pool.C || a.kp * sizeof(T) % 16 != 0 || ((uintptr_t)a.w & 15) != 0)
+    return hipErrorNotSupported;
+  if (a.pool.n <= 0) return hipSuccess;
+  hipLaunchKernelGGL((classify_kernel<T>), dim3((unsigned)(a.pool.n < 256 * 8 ? a.pool.n : 256 * 8)), dim3(256), 0, s, a, vl);
+  return hipGetLastError();
+}
+hipError_t launch_classify(int dtype, const ClassifyArgs& a, hipStream_t s) {
+  DISPATCH_T(dtype, classify_t<float>(a, s), classify_t<_Float16>(a, s), classify_t<__bf16>(a, s))
 }
 hipError_t launch_argmax(const float* logits, int ld, int n_out, const int* n_dyn, int n, int* labels, const LabelDest& d, hipStream_t s) {
   if (n <= 0) return hipSuccess;

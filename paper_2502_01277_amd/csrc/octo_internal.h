@@ -94,6 +94,10 @@ hipError_t launch_gap(int dtype, const PoolArgs& a, hipStream_t s);             
 // Where the labels of a child's items go besides its own label array: child_label[slot] of the box that item r was cropped
 // from (rois[r]: frame, rank).  boxes == nullptr: nowhere.
 struct LabelDest { octo_box* boxes = nullptr; const octo_roi* rois = nullptr; int max_det = 0, slot = 0; };
+// Global average pool, fully connected layer without activation and label in one launch; every tensor is written.  kp: values per row of w.
+// hipErrorNotSupported: the matrix is too large for a workgroup per item, or the pool's input is not in whole 16-byte vectors.
+struct ClassifyArgs { PoolArgs pool; const void* w; const float* bias; int kp, n_out; float* logits; int ld; int* labels; LabelDest dest; };
+hipError_t launch_classify(int dtype, const ClassifyArgs& a, hipStream_t s);
 hipError_t launch_argmax(const float* logits, int ld, int n_out, const int* n_dyn, int n, int* labels, const LabelDest& d, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int value, int count, hipStream_t s);
 

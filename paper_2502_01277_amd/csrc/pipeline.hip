@@ -82,6 +82,9 @@ struct LayerPlan {
   // This and the next two layers are chained stride-1 max-pools of one size (a spatial-pyramid block): one launch does all
   // three; the next two layers then do nothing.  Cleared for good the first time no kernel accepts the chain.
   bool fuse_chain = false;
+  // A classifier's global average pool, whose reader is the next and last layer, a fully connected one without activation: one launch does both
+  // and finds the labels.  The next layer then does nothing.  Cleared for good the first time no kernel accepts it.
+  bool fuse_label = false;
   // The next layer is a 1x1 convolution of the same input with the same activation (the two entry convolutions of a
   // cross-stage block): one launch computes both - the weight matrices stacked, the second layer's channels written to
   // its own tensor - so the input is read once.  The next layer then does nothing (kernel id KID_NONE).  Cleared for
@@ -138,6 +141,7 @@ struct ModelPlan {
   // classifier
   int* labels = nullptr;   // also used by detector children (label = number of kept boxes)
   int n_logits = 0;
+  LabelDest label_dest{};  // classifiers: where the labels of the execution being enqueued go
   // recorded launches (replay)
   std::map<int, Recording> recordings;
   int record_key = -1;                     // the recording to make when the host next waits (-1: none)
@@ -411,6 +415,12 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     if (ta.f32 || tb.f32 || ((a.L.cout | b.L.cout | ta.ld | ta.coff | tb.ld | tb.coff) & 7)) continue;
     a.fuse_twin = true;
   }
+  // the end of a classifier (also with every layer on its own: the launch writes every tensor, and a logit's order of summation stays the same)
+  for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_label = false;
+  if (const int i = (int)m.layers.size() - 2; m.d.kind == OCTO_CLASSIFIER && i >= 0 && m.d.outputs[0] == i + 2) {
+    const octo_layer &G = m.layers[i].L, &F = m.layers[i + 1].L;
+    m.layers[i].fuse_label = G.op == OCTO_GAP && F.op == OCTO_FC && F.in[0] == i + 1 && F.n_in == 1 && F.act == OCTO_ACT_NONE;
+  }
   // lifetimes of root buffers in layer steps: tensor t is written at step t-1 (input: -1)
   std::vector<int> birth(nt, 1 << 30), death(nt, -2);
   for (int t = 0; t < nt; ++t) {
@@ -419,7 +429,7 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     death[r] = std::max(death[r], t - 1);
   }
   for (int i = 0; i < (int)m.layers.size(); ++i)
-    if (m.layers[i].fuse_pool || m.layers[i].fuse_twin || m.layers[i].fuse_up) {      // the next layer's output is written one step early, by this layer
+    if (m.layers[i].fuse_pool || m.layers[i].fuse_twin || m.layers[i].fuse_up || m.layers[i].fuse_label) {      // the next layer's output is written one step early, by this layer
       const int r = m.tensors[i + 2].root;
       birth[r] = std::min(birth[r], i);
     }
@@ -563,7 +573,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
       a.up_next = lp.up_next;
-      if (i > 0 && m.layers[i - 1].fuse_twin) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
+      if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (lp.fuse_twin) {
         const TensorView y2 = view_of(m, i + 2);
         ConvArgs f = a;
@@ -634,10 +644,26 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
     case OCTO_GAP: {
       PoolArgs a{x.ptr, y.ptr, n_dyn, n, x.h, x.w, x.c, x.ld, x.coff, 1, 1, y.ld, y.coff, 1, 1, 0};
       lp.kernel_id = KID_GAP;
+      if (lp.fuse_label) {
+        const LayerPlan& fc = m.layers[i + 1];
+        const TensorView lg = view_of(m, i + 2);
+        const ClassifyArgs f{a, fc.d_weight, fc.d_bias, fc.Kp, fc.L.cout, (float*)lg.ptr + lg.coff, lg.ld, m.labels, m.label_dest};
+        const hipError_t e = launch_classify(m.d.dtype, f, s);
+        if (e != hipErrorNotSupported) return e;
+        lp.fuse_label = false;
+      }
       return launch_gap(m.d.dtype, a, s);
     }
   }
   return hipErrorInvalidValue;
+}
+
+// Labels of a classifier whose layers have run, unless the last launch of those found them.
+hipError_t run_labels(ModelPlan& m, int n, const int* n_dyn, hipStream_t s) {
+  const int L = (int)m.layers.size();
+  if (L >= 2 && m.layers[L - 2].fuse_label) return hipSuccess;
+  const TensorView lg = view_of(m, m.d.outputs[0]);
+  return launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, m.n_logits, n_dyn, n, m.labels, m.label_dest, s);
 }
 
 hipError_t run_layers(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, hipStream_t s, std::vector<hipEvent_t>* evs = nullptr) {
@@ -1082,15 +1108,14 @@ octo_status run_child(octo_pipeline* p, Batch& B, int e, hipStream_t s, bool own
   ra.n = c.cap; ra.n_dyn = c.n_dyn; ra.rois = p->rois[e]; ra.n_frames = p->max_frames;      // ROIs name frames of the batch only
   HIPCHK(p, launch_crop_resize(c.d.dtype, ra, s));
   if (ev) HIPCHK(p, hipEventRecord(ev[0], s));
+  c.label_dest = LabelDest();            // the results of the first edges go into the boxes the items came from
+  if (e < OCTO_MAX_CHILD_LABELS) c.label_dest = LabelDest{(octo_box*)(p->d_result + p->off_boxes), p->rois[e], p->models[0].d.max_det, e};
   HIPCHK(p, run_layers(p, c, c.cap, c.n_dyn, s, p->layer_timing ? &B.layer_ev[p->edges[e].child] : nullptr));
   if (ev) HIPCHK(p, hipEventRecord(ev[1], s));
-  LabelDest dest;                        // the results of the first edges go into the boxes the items came from
-  if (e < OCTO_MAX_CHILD_LABELS) dest = LabelDest{(octo_box*)(p->d_result + p->off_boxes), p->rois[e], p->models[0].d.max_det, e};
   if (c.d.kind == OCTO_CLASSIFIER) {
-    const TensorView lg = view_of(c, c.d.outputs[0]);
-    HIPCHK(p, launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, c.n_logits, c.n_dyn, c.cap, c.labels, dest, s));
+    HIPCHK(p, run_labels(c, c.cap, c.n_dyn, s));
   } else {
-    HIPCHK(p, run_detect_tail(p, c, c.cap, c.n_dyn, s, nullptr, 0, dest));
+    HIPCHK(p, run_detect_tail(p, c, c.cap, c.n_dyn, s, nullptr, 0, c.label_dest));
   }
   if (ev) HIPCHK(p, hipEventRecord(ev[2], s));
   if (own_stream) HIPCHK(p, hipEventRecord(p->ev_child[e], s));
@@ -1533,14 +1558,14 @@ octo_status octo_debug_run_model(octo_pipeline* p, int32_t model, const void* d_
   } else {
     HIPCHK(p, hipMemcpyAsync(view_of(m, 0).ptr, d_input, bytes, hipMemcpyDeviceToDevice, s));
   }
+  m.label_dest = LabelDest();
   HIPCHK(p, run_layers(p, m, n, nullptr, s));
   if (m.d.kind == OCTO_DETECTOR) {
     if (m.flags) HIPCHK(p, launch_fill_i32(m.flags, 0, m.cap, s));
     HIPCHK(p, launch_fill_i32(m.cand_count, 0, n * CNT_STRIDE, s));
     HIPCHK(p, run_detect_tail(p, m, n, nullptr, s, nullptr));
   } else if (m.labels) {
-    const TensorView lg = view_of(m, m.d.outputs[0]);
-    HIPCHK(p, launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, m.n_logits, nullptr, n, m.labels, LabelDest(), s));
+    HIPCHK(p, run_labels(m, n, nullptr, s));
   }
   return OCTO_OK;
 }
