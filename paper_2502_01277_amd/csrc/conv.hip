@@ -607,21 +607,27 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   if (a.up_y) return hipErrorNotSupported;
   const bool pipe_ok = sizeof(T) == 2;
   if constexpr (sizeof(T) == 2) {
-    // conv_flow_kernel takes what has its form, except strided layers in one round of pipelined 64x64 tiles: 256 -> 512, stride 2 on
-    // 42 x 14 x 14 16.1 us here, 18.1 there, 128 -> 128, stride 2 on 8 x 80 x 80 10.5 : 11.1 (a step of such a tile is four matrix instructions
-    // per wavefront, fewer than the cursor's scalar ones).  Their order of summation is the same, so the running count may choose between
-    // those two; split-K or not is decided for M_split.
+    // conv_flow_kernel takes what has its form, except strided layers of up to two pipelined 64x64 tiles per compute unit: 256 -> 512,
+    // stride 2 on 42 x 14 x 14 16.1 us here, 18.1 there, 128 -> 128, stride 2 on 8 x 80 x 80 10.5 : 11.1 (a step of such a tile is four matrix
+    // instructions per wavefront, fewer than the cursor's scalar ones).  By tiles per compute unit: 256 -> 256 on 20 x 40 x 40 at 1.95 17.1 :
+    // 18.4, 128 -> 64 on 82 x 40 x 40 at 2.0 (513 tiles) 14.6 : 13.9, 96 -> 192 on 9 x 57 x 83 at 2.02 13.4 : 12.5, 192 -> 192 on 7 x 80 x 80 at
+    // 2.05 18.0 : 17.2.  Their order of summation is the same, so the running count may choose between those two; split-K or not is
+    // decided for M_split.
     if (flow_fits(a)) {
       const bool pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
       auto stays = [&](long long m) {
         const GeneralTile t = general_tile(a, m, num_cu, 1, pipe_ok);
-        return !pw && t.pipe && t.bc == 64 && t.bp == 64;
+        return !pw && t.pipe && t.bc == 64 && t.bp == 64 && (m + 63) / 64 * ((a.Cout + 63) / 64) <= 2LL * num_cu;
       };
       double us = 0;
       int kf = -1;
       if (!stays(M_split)) {
         flow_choose(a, M_split, num_cu, &us);
-        kf = ksplit_best(a, M_split, 2, num_cu, us);
+        // Against this kernel split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
+        // on 7 x 40 x 40 at 4.1 38.0 : 28.0, 512 -> 64 1x1 on 82 x 20 x 20 at 4.0 11.1 : 8.2).  Its 64 x 64 tiles serve long reductions (256 -> 256,
+        // stride 2 on 6 x 40 x 40 11.0 : 13.8), not 1x1 layers (512 -> 512 on 5 x 20 x 20 7.3 : 5.8, 1024 -> 512 8.7 : 7.3), where this kernel's
+        // estimate is 15 % high while it has few tiles.
+        kf = ksplit_best(a, M_split, 2, num_cu, pw ? 0.85 * us : us, pw ? 3 : 4, 4.0);
       }
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
       if (stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);

@@ -320,10 +320,13 @@ constexpr ConvCost KSPLIT_COST[4] = {{32, 32, 8, 3.0, 0.75, 1.00, 0.07}, {32, 32
 constexpr ConvCost GENERAL_COST[4] = {{32, 128, 0, 3.9, 0.91, 0.80, 0.36}, {64, 64, 0, 3.7, 0.28, 0.84, 0.28},
                                       {64, 128, 0, 4.0, 1.32, 1.57, 0.12}, {128, 128, 0, 4.5, 1.27, 3.28, 0.19}};
 
-// Index of the split-K shape with the smallest estimate below `best` us, or -1.  M: output pixels expected.
-inline int ksplit_best(const ConvArgs& a, long long M, int es, int num_cu, double best) {
+// Index of the split-K shape with the smallest estimate below `best` us, or -1.  M: output pixels expected; shapes: the first so many of
+// KSPLIT_COST; most: a shape needs fewer tiles per compute unit than this.
+inline int ksplit_best(const ConvArgs& a, long long M, int es, int num_cu, double best, int shapes = 4, double most = 1e30) {
   int pick = -1;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < shapes; ++i) {
+    const ConvCost& c = KSPLIT_COST[i];
+    if ((double)((M + c.bp - 1) / c.bp) * ((a.Cout + c.bc - 1) / c.bc) >= most * num_cu) continue;
     const double t = conv_cost_us(KSPLIT_COST[i], M, a.Cout, a.Kp * es, num_cu);
     if (t < best) { best = t; pick = i; }
   }

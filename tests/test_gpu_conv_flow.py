@@ -34,6 +34,8 @@ CASES = [
     (31, 59, 51, 168, 392, 1, 2, nn.ACT_SILU, nn.RES_NONE, 0, 0, 1222561288),
     (17, 54, 34, 184, 376, 5, 1, nn.ACT_RELU, nn.RES_AFTER_ACT, 0, 0, 1221921288),
     (23, 48, 52, 200, 176, 2, 2, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 1221281288),
+    (81, 40, 40, 128, 64, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 1064064837),             # two 64 x 64 tiles per compute unit at most: general kernel
+    (82, 40, 40, 128, 64, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 1210640648),             # 513
 ]
 
 
