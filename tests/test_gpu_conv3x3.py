@@ -16,6 +16,9 @@ CASES = [
     (3, 57, 83, 48, 64, nn.ACT_SILU, nn.RES_NONE, 16, 0, 2, 64, 128),              # 64 x 64 tiles; ragged columns, 3/4 of a slice
     (7, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, None, 0, 0),       # too few tiles: split-K
     (21, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 8, 2, 64, 128),      # 64 x 64 tiles across images
+    (10, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_NONE, 0, 0, None, 0, 0),            # either side of the line: 0.24 tiles per compute unit
+    (11, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_NONE, 0, 0, 2, 64, 128),            # 0.26
+    (25, 7, 7, 512, 512, nn.ACT_RELU, nn.RES_NONE, 0, 0, None, 0, 0),              # 0.30, a long reduction
     (61, 14, 30, 192, 136, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 64, 128),       # slices of 128 bytes, 8 of the last 64 channels
     (90, 14, 14, 248, 96, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 3, 64, 128),       # patch of five passes, 8 of the last slice
     (5, 80, 81, 64, 64, nn.ACT_RELU, nn.RES_BEFORE_ACT, 64, 64, 0, 64, 64),        # one slice of each buffer, columns 41 + 40
