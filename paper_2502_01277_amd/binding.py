@@ -582,8 +582,9 @@ def op_crop_resize(frames: Sequence, rois: np.ndarray, out_h, out_w, dtype: str,
     k, n = len(rois), len(frames)
     cap = cap or max(1, k)
     # The ROI records, their count and the table of the frames travel in one copy, from pinned memory so that the host goes on (15 -> 8 us, and
-    # the 10 of a launch for the table; a copy under capture must fail as one from ordinary memory does).  Crops beyond the count are zeros.
-    pinned = not t.cuda.is_current_stream_capturing()
+    # the 10 of a launch for the table); on a stream of the caller's, which may be capturing, and under capture the host waits for it as it
+    # does for any copy from ordinary memory.  Crops beyond the count are zeros.
+    pinned = stream is None and not t.cuda.is_current_stream_capturing()
     host = t.empty(32 * k + 32 + 16 * n, dtype=t.uint8, pin_memory=pinned)
     h = host.numpy()
     h[:32 * k] = np.ascontiguousarray(rois).view(np.uint8).reshape(-1)
