@@ -505,7 +505,12 @@ inline long long mid_rounds(const ConvArgs& a, long long items, int BC, int BP, 
 //   * below 0.25 the split-K kernel spreads the K loop of the few tiles over more wavefronts.  Against 64 x 64 tiles: 14 x 14 x 256 at
 //     0.22 9.5 : 9.8, at 0.24 9.8 : 9.9, at 0.26 11.9 : 10.0, at 0.33 12.2 : 10.2; 20 x 20 x 64 at 0.24 6.1 : 5.9, at 0.29 6.8 : 6.0; 40 x 40 x 128
 //     at 0.20 7.1 : 7.4, at 0.29 9.2 : 7.6; 13 x 13 x 384 at 0.22 11.8 : 12.4, at 0.25 15.0 : 12.4.  Longer reductions turn at 0.35: 7 x 7 x 512 at
-//     0.24 14.1 : 19.1, at 0.33 18.1 : 19.3; and so do layers that 64-channel slices would pad (40 x 40 x 96 at 0.29 6.8 : 9.9);
+//     0.24 14.1 : 19.1, at 0.33 18.1 : 19.3;
+//   * layers whose last 64-channel slice would be half padding (slices of 32, 64 x 128 or 96 x 128 tiles) turn at 0.5, where split-K's 64 x 64
+//     tiles no longer are one round: 96 -> 96 on 80 x 80 at 0.39 7.9 : 8.8, on 28 x 28 at 0.48 8.0 : 9.0, at 0.53 8.9 : 9.0, at 0.96 11.3 : 9.3; 288 ->
+//     96 on 40 x 40 at 0.49 13.6 : 17.1, at 0.59 18.0 : 17.2; 80 -> 128 on 40 x 40 at 0.49 7.8 : 8.5, at 0.59 8.6 : 8.5; 96 -> 192 there is even from 0.3
+//     on (8.1 : 8.0 at 0.44).  96 x 128 tiles with a last slice that even then is partly padding turn at 1.0: 80 -> 80 on 80 x 80 at 0.39 7.8 :
+//     9.4, at 0.78 9.0 : 9.7, at 1.17 11.3 : 10.3; 72 -> 72 on 40 x 40 at 0.98 8.7 : 9.4, at 1.07 10.2 : 9.6;
 //   * 64 x 64 tiles up to 0.8.  Against 64 x 128: 14 x 14 x 256 at 0.79 13.0 : 13.4, at 1.0 19.8 : 18.1; 7 x 7 x 512 at 0.6 20.7 : 21.3, at 1.0
 //     36.2 : 30.1; 28 x 28 x 128 at 0.81 9.3 : 9.9, at 1.0 13.3 : 12.2;
 //   * tiles of 32 channels for layers with no more: 32 -> 32 with residual on 16 x 160 x 160 24 us (33).  From 0.8: 80 x 80 x 32 at 0.59 5.8
@@ -533,10 +538,10 @@ hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s,
   if (a.Cin * 4 < pad32 * 3) return hipErrorNotSupported;       // more than a quarter of the MFMAs would be padding
   if (a.Cout <= 32) return (double)M / 128 < 0.8 * num_cu ? hipErrorNotSupported : launch_mid_cfg<T, 32, 128, 1, 4, 3, 3, 4>(a, num_cu, s, kernel_id, tm);
   const double per_cu = (double)M / 128 * ((a.Cout + 63) / 64) / num_cu;
-  const bool k8 = pad32 == pad64;
-  if (per_cu < (k8 && a.Cin <= 384 ? 0.25 : 0.35)) return hipErrorNotSupported;
+  const bool k8 = pad32 == pad64, by96 = (a.Cout + 95) / 96 * 96 < (a.Cout + 63) / 64 * 64;
+  if (per_cu < (k8 ? (a.Cin <= 384 ? 0.25 : 0.35) : by96 && a.Cin % 32 ? 1.0 : 0.5)) return hipErrorNotSupported;
   if (k8 && per_cu < 0.8) return launch_mid_cfg<T, 64, 64, 2, 8, 3, 4, 2>(a, num_cu, s, kernel_id, tm);
-  if ((a.Cout + 95) / 96 * 96 < (a.Cout + 63) / 64 * 64 && !(k8 && a.Cin >= 192 && per_cu < 6))
+  if (by96 && !(k8 && a.Cin >= 192 && per_cu < 6))
     return M / 256 * ((a.Cout + 95) / 96) >= 4 * num_cu ? launch_mid_cfg<T, 96, 256, 1, 4, 3, 6, 2>(a, num_cu, s, kernel_id, tm)
                                                         : launch_mid_cfg<T, 96, 128, 1, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm);
   const bool fits128 = (a.Cout + 127) / 128 * 2 == (a.Cout + 63) / 64, long_k = a.Cin >= 192;

@@ -19,6 +19,10 @@ CASES = [
     (10, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_NONE, 0, 0, None, 0, 0),            # either side of the line: 0.24 tiles per compute unit
     (11, 14, 14, 256, 256, nn.ACT_RELU, nn.RES_NONE, 0, 0, 2, 64, 128),            # 0.26
     (25, 7, 7, 512, 512, nn.ACT_RELU, nn.RES_NONE, 0, 0, None, 0, 0),              # 0.30, a long reduction
+    (10, 28, 28, 96, 96, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, None, 0, 0),         # 0.48, half of the last slice of 64 channels
+    (11, 28, 28, 96, 96, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 96, 64),          # 0.53
+    (10, 40, 40, 72, 72, nn.ACT_SILU, nn.RES_NONE, 0, 0, None, 0, 0),              # 0.98, 8 of the last 32 channels
+    (11, 40, 40, 72, 72, nn.ACT_SILU, nn.RES_NONE, 0, 0, 0, 96, 64),               # 1.07
     (61, 14, 30, 192, 136, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 0, 64, 128),       # slices of 128 bytes, 8 of the last 64 channels
     (90, 14, 14, 248, 96, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 3, 64, 128),       # patch of five passes, 8 of the last slice
     (5, 80, 81, 64, 64, nn.ACT_RELU, nn.RES_BEFORE_ACT, 64, 64, 0, 64, 64),        # one slice of each buffer, columns 41 + 40
