@@ -102,54 +102,54 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "23012f1ced29c670": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4364134588,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1700695570,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283045432,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344616210,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1482632946,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553396454,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 848584466,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355685452,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282639453,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2206526540,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 989923098,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910709074,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629437522,
-        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255832383,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078097705,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167838322,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 627951356,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 127853636,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838949,
-        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69133838,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856359,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28734601,
-        "octo::conv1x1_stream_kernel<_Float16, 2>": 29073306,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064053,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727922,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942906,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87608727,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28524645,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77788655,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64436587,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21158480,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31501963,
-        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369389,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873161,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40070187,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39797495,
-        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19103927,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136855,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510211,
-        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376778,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355742,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644835,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223613,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253462,
-        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730482,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506592,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18700328,
+    "9957d582877025b5": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4366020054,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1698904210,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283051107,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344609020,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1483380603,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553413478,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 848479598,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355752227,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282107181,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2207646543,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 988174154,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1911793742,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629434208,
+        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255832788,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1079390844,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167891704,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628227822,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 128136766,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838646,
+        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69133722,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856349,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28735905,
+        "octo::conv1x1_stream_kernel<_Float16, 2>": 29073265,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064045,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727918,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942844,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87626950,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28525928,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77734077,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64466699,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21158472,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31499947,
+        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369379,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873117,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40074042,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39790474,
+        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19103922,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136853,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510205,
+        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376772,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355715,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644831,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223612,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253460,
+        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730480,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39505790,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18701297,
     },
 }
 
