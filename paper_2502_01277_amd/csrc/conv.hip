@@ -679,6 +679,14 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   const GeneralTile t = general_tile(a, M, num_cu, 2);
   const int ks = ksplit_choose(a, M, 1, t.bc, t.bp, num_cu);
   if (ks >= 0) return launch_ksplit<f8>(ks, a, num_cu, s, kernel_id, tm);
+  // conv_flow_kernel as for the 16-bit types, by the same estimate with steps of 128 values (general : flow, us: 96 -> 96 1x1 on 32 x 160 x 160
+  // 76.8 : 50.1, 192 -> 192 148.7 : 97.7, 1024 -> 256 on 60 x 14 x 14 11.2 : 8.1, 48 -> 96, stride 2 on 32 x 640 x 640 435 : 307, 256 -> 512, stride 2 on
+  // 4170 x 14 x 14 298 : 257, 128 -> 256, stride 2 on 8 x 80 x 80 12.2 : 10.2).  Half a step into one 64-channel tile stays on the 64 x 256
+  // tiles with 64-byte steps (48 -> 48 on 32 x 320 x 320 124 : 130, 32 -> 64 on 16 x 160 x 160 20.1 : 21.6).
+  if (flow_fits(a, 1) && !(a.K <= 64 && a.Cout <= 64)) {
+    double us = 0;
+    return launch_flow_f8(flow_choose(a, M, num_cu, &us, 1), a, num_cu, s, kernel_id, tm);
+  }
   if (t.bc == 128) return launch_cfg<f8, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
   if (t.bp == 256) return launch_cfg<f8, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);
   if (t.bp == 128) return launch_cfg<f8, 64, 128, 2, 2, 8, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);

@@ -1,4 +1,4 @@
-// Convolution as an implicit GEMM whose stream of loads runs on across tiles: 1x1 and strided layers of the 16-bit types.
+// Convolution as an implicit GEMM whose stream of loads runs on across tiles: 1x1 and strided layers of the 16-bit types and E4M3.
 //
 // The general kernel (conv.hip) starts every tile with addresses and an empty pipeline and ends it with a pass through LDS between
 // barriers.  The 1x1 layers of a detector have 3 .. 12 K steps per tile, so most of their time was that.  Here
@@ -15,6 +15,9 @@
 // Before (general kernel) and after, bf16, us: 64 -> 128, stride 2 on 4170 x 56 x 56 787 -> 676; 96 -> 192, stride 2 on 32 x 320 x 320 507 -> 387;
 // 48 -> 96, stride 2 on 32 x 640 x 640 696 -> 545; 384 -> 384 on 32 x 80 x 80 124 -> 102 (3.1 TB/s); 384 -> 192 on 32 x 160 x 160 281 -> 213
 // (4.4 TB/s); 192 -> 256 on 32 x 160 x 160 235 -> 164; 256 -> 256 on 64 x 40 x 40 36 -> 26; 512 -> 512 on 8 x 20 x 20 7.9 -> 6.5.
+// E4M3 (a step is 128 values, two matrix instructions deep; scale and bias per channel arrive together): 96 -> 96 on 32 x 160 x 160 77 -> 50,
+// 192 -> 192 149 -> 98 (3.2 TB/s), 48 -> 96, stride 2 on 32 x 640 x 640 435 -> 307, 64 -> 128, stride 2 on 4170 x 56 x 56 513 -> 416.  Its 64 x 64 tiles run
+// two workgroups per compute unit: with the scales three are 2 KB more than the LDS.
 // LDS rows (weights: one output channel, pixels: one output pixel) are KV vectors of 16 bytes, vector v of row r in slot
 // v ^ ((r / (16 / KV)) % KV).  vmcnt bookkeeping: every wavefront issues the same number of loads per K step and of stores per tile.
 #pragma once
@@ -41,13 +44,15 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
   constexpr int WP = NT / 64 / WC, TC = BC / WC / 32, TP = BP / WP / 32;
   constexpr int RPW = 16 / KV, RP = NT / KV, LA = (BC + RP - 1) / RP, LB = BP / RP, NL = LA + LB;
   constexpr int ROW = KV * 16, A_BYTES = LA * RP * ROW, STAGE = A_BYTES + BP * ROW;
-  constexpr int KK = KV / 2, P0 = (NL + KK - 1) / KK;      // groups of MFMAs per K step, loads issued with each group
+  constexpr int KK = ES == 1 ? KV / 4 : KV / 2, P0 = (NL + KK - 1) / KK;      // groups of MFMAs per K step, loads issued with each group
+  constexpr int FV = ES == 1 ? 2 : 1, NB = ES == 1 ? 2 : 1;         // vectors per operand fragment; loads of what the epilogue needs per channel
   constexpr int HV = 16 / VN;                              // vectors of a lane's 16 consecutive output channels of a 32-channel block
   constexpr int PJ = TC * TP * HV <= 8 ? TP : 0;           // pixel blocks whose residual is requested before the K loop ends
   constexpr int NSTO = TC * TP * HV, NRES = TC * PJ * HV;
-  static_assert(ES == 2 && KK >= 2 && KK % 2 == 0 && BP % RP == 0 && TC >= 1 && TP >= 1, "tile shape");
+  static_assert(ES <= 2 && KK >= 2 && KK % 2 == 0 && BP % RP == 0 && TC >= 1 && TP >= 1, "tile shape");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE];
   __shared__ __attribute__((aligned(16))) float sBias[3][NT];               // of this tile and the next; with one channel tile of all, and a dump
+  __shared__ __attribute__((aligned(16))) float sScale[3][ES == 1 ? NT : 1];             // the same of E4M3 layers' scales
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wave % WC, wp = wave / WC;
@@ -67,6 +72,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
   const int rsw = (l32 / RPW) % KV;
   const unsigned lds_ring = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)smem + (unsigned)wave * 1024u));
   const unsigned lds_bias = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)&sBias[0][0] + (unsigned)wave * 256u));
+  const unsigned lds_scale = (unsigned)__builtin_amdgcn_readfirstlane((int)((unsigned)(uintptr_t)&sScale[0][0] + (unsigned)wave * 256u));
   const bool is_silu = a.act == OCTO_ACT_SILU;
   const float act_lo = a.act == OCTO_ACT_RELU ? 0.0f : -INFINITY;
 
@@ -191,17 +197,24 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, any ? a.w_rows * 4 : 0, BUF_FLAGS);
     const int off = tid < BC ? (c0 + tid) * 4 : OOB;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_bias + buf * (NT * 4)), "v"(off), "s"(rb) : "memory");
+    if constexpr (ES == 1) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.scale, 0, any ? a.w_rows * 4 : 0, BUF_FLAGS);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_scale + buf * (NT * 4)), "v"(off), "s"(rs) : "memory");
+    }
   };
 
-  u32x4 fa[2][TC], fb[2][TP];
+  u32x4 fa[2][TC][FV], fb[2][TP][FV];
   const int arow = (wc * (TC * 32) + l32) * ROW, brow = A_BYTES + (wp * (TP * 32) + l32) * ROW;
   auto frags = [&](int set, int st, int kq) __attribute__((always_inline)) {
     const unsigned char* p = smem + st * STAGE;
-    const int v = ((kq * 2 + g) ^ rsw) << 4;
 #pragma unroll
-    for (int i = 0; i < TC; ++i) fa[set][i] = *(const u32x4*)(p + arow + i * (32 * ROW) + v);
+    for (int h = 0; h < FV; ++h) {
+      const int v = (((kq * FV + h) * 2 + g) ^ rsw) << 4;
 #pragma unroll
-    for (int j = 0; j < TP; ++j) fb[set][j] = *(const u32x4*)(p + brow + j * (32 * ROW) + v);
+      for (int i = 0; i < TC; ++i) fa[set][i][h] = *(const u32x4*)(p + arow + i * (32 * ROW) + v);
+#pragma unroll
+      for (int j = 0; j < TP; ++j) fb[set][j][h] = *(const u32x4*)(p + brow + j * (32 * ROW) + v);
+    }
   };
 
   int p0, c0;
@@ -263,7 +276,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
         } else {
           // this wavefront holds all it needs of the stage, and the next step's operands have landed: younger than those are the
           // loads of the step after it, in the last step of a tile its bias and residual, in the first one the stores of the tile before
-          constexpr int N = (NST - 2) * NL + (LAST ? 1 : 0);
+          constexpr int N = (NST - 2) * NL + (LAST ? NB : 0);
           if (LAST && has_res) {
             if (first) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N + NRES + NSTO) : "memory");
             else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N + NRES) : "memory");
@@ -279,7 +292,10 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
 #pragma unroll
         for (int i = 0; i < TC; ++i)
 #pragma unroll
-          for (int j = 0; j < TP; ++j) acc[i][j] = E::mfma(fa[kk & 1][i], fb[kk & 1][j], acc[i][j]);
+          for (int j = 0; j < TP; ++j) {
+            if constexpr (ES == 1) acc[i][j] = E::mfma2(fa[kk & 1][i][0], fa[kk & 1][i][1], fb[kk & 1][j][0], fb[kk & 1][j][1], acc[i][j]);
+            else acc[i][j] = E::mfma(fa[kk & 1][i][0], fb[kk & 1][j][0], acc[i][j]);
+          }
         __builtin_amdgcn_sched_barrier(0);
       }
       st_rd = nxt;
@@ -305,26 +321,44 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
         const bool second = a.split > 0 && c0 + wc * (TC * 32) + i * 32 >= a.split;
 #pragma unroll
         for (int h = 0; h < HV; ++h) {
-          typedef T t4 __attribute__((ext_vector_type(4)));
           u32x4 out;
+          if constexpr (ES == 2) {
+            typedef T t4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            floatx4 v, r4 = floatx4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (RES != OCTO_RES_NONE) {
-              const u32x2 rw = {rv[j][i][h][2 * q], rv[j][i][h][2 * q + 1]};
-              const t4 rt = __builtin_bit_cast(t4, rw);
-              r4 = floatx4{(float)rt[0], (float)rt[1], (float)rt[2], (float)rt[3]};
+            for (int q = 0; q < 2; ++q) {
+              floatx4 v, r4 = floatx4{0.f, 0.f, 0.f, 0.f};
+              if constexpr (RES != OCTO_RES_NONE) {
+                const u32x2 rw = {rv[j][i][h][2 * q], rv[j][i][h][2 * q + 1]};
+                const t4 rt = __builtin_bit_cast(t4, rw);
+                r4 = floatx4{(float)rt[0], (float)rt[1], (float)rt[2], (float)rt[3]};
+              }
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = acc[i][j][h * VN + q * 4 + e];
+              v = finish4<RES, SILU>(v, *(const floatx4*)&sBias[bbuf][wc * (TC * 32) + g * 16 + i * 32 + h * VN + q * 4], r4, act_lo);
+              const t4 o = {(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
+              const u32x2 ob = __builtin_bit_cast(u32x2, o);
+              out[2 * q] = ob[0]; out[2 * q + 1] = ob[1];
             }
+          } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][h * VN + q * 4 + e];
-            v = finish4<RES, SILU>(v, *(const floatx4*)&sBias[bbuf][wc * (TC * 32) + g * 16 + i * 32 + h * VN + q * 4], r4, act_lo);
-            const t4 o = {(T)v[0], (T)v[1], (T)v[2], (T)v[3]};
-            const u32x2 ob = __builtin_bit_cast(u32x2, o);
-            out[2 * q] = ob[0]; out[2 * q + 1] = ob[1];
+            for (int q = 0; q < 4; ++q) {
+              const int cq = wc * (TC * 32) + g * 16 + i * 32 + q * 4;
+              floatx4 v, r4 = floatx4{0.f, 0.f, 0.f, 0.f};
+              if constexpr (RES != OCTO_RES_NONE) r4 = f8_unpack4(rv[j][i][0][q]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                v[e] = acc[i][j][q * 4 + e] * sScale[bbuf][cq + e];
+                r4[e] *= a.res_scale;
+              }
+              v = finish4<RES, SILU>(v, *(const floatx4*)&sBias[bbuf][cq], r4, act_lo);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] *= a.y_inv_scale;
+              out[q] = f8_pack4(v);
+            }
           }
           const bool ok = cw + i * 32 + h * VN + VN <= a.Cout;
           const int left = a.Cout - (c0 + wc * (TC * 32) + i * 32);
-          if (tail && left > 0 && left < 32 && (left / VN) % 2 == h) {    // the vector that ends past the last channel: its values in pairs
+          if (ES == 2 && tail && left > 0 && left < 32 && (left / VN) % 2 == h) {    // the vector that ends past the last channel: its values in pairs
             const int to = !ok && cw + i * 32 + h * VN < a.Cout ? yo + i * 32 * ES + h * 16 : OOB;
 #pragma unroll
             for (int e = 0; e < VN / 2; ++e) {
@@ -364,7 +398,7 @@ static hipError_t launch_flow_cfg(const ConvArgs& a, int num_cu, hipStream_t s, 
   constexpr int BK = KV * Elem<T>::N;
   // The bias of a tile is requested at the last step of the one before: its place must be free (a barrier since the epilogue before),
   // and it must have landed by the epilogue (older than the operands of step NST - 2).  With a single step there must be one channel tile.
-  static_assert(KV == 8 && NST <= 4, "two K steps suffice: a.K > 64");
+  static_assert(KV == 8 && NST <= 4, "two K steps suffice: a.K > BK");
   if (a.K <= BK && a.Cout > BC) return hipErrorNotSupported;
   const long long M = (long long)a.n * a.Ho * a.Wo, tiles_c = (a.Cout + BC - 1) / BC, tiles = (M + BP - 1) / BP * tiles_c;
   if (tiles <= 0) return hipSuccess;
@@ -382,7 +416,7 @@ static hipError_t launch_flow_cfg(const ConvArgs& a, int num_cu, hipStream_t s, 
 template <typename T>
 static hipError_t launch_flow(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   switch (which) {
-    case 0: return launch_flow_cfg<T, 256, 64, 64, 2, 8, 3, 3>(a, num_cu, s, kernel_id, tm);
+    case 0: return launch_flow_cfg<T, 256, 64, 64, 2, 8, 3, sizeof(T) == 1 ? 2 : 3>(a, num_cu, s, kernel_id, tm);
     case 1: return launch_flow_cfg<T, 256, 64, 128, 1, 8, 3, 2>(a, num_cu, s, kernel_id, tm);
     case 2: return launch_flow_cfg<T, 256, 128, 64, 2, 8, 3, 2>(a, num_cu, s, kernel_id, tm);
     case 3: return launch_flow_cfg<T, 512, 128, 128, 2, 8, 3, 1>(a, num_cu, s, kernel_id, tm);

@@ -5,15 +5,16 @@
 
 namespace octo {
 
-// Does a 16-bit layer have the form that conv_flow_kernel takes?
-inline bool flow_fits(const ConvArgs& a) {
-  constexpr int VN = 8, ES = 2;
+// Does a layer of values of ES bytes (16-bit types, E4M3) have the form that conv_flow_kernel takes?
+inline bool flow_fits(const ConvArgs& a, int ES = 2) {
+  const int VN = 16 / ES;
   if (a.out_f32 || a.pair_view || a.pool_y || a.up_y || a.kh > 15 || a.kw > 15) return false;
-  if (a.Cout % VN && (a.res || a.split > 0)) return false;
+  if (a.Cout % VN && (a.res || a.split > 0 || ES == 1)) return false;
+  if (ES == 1 && (a.split > 0 || !a.scale)) return false;
   if (((a.Cin | a.x_ld | a.x_coff | a.y_ld | a.y_coff) % VN) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return false;
   if (a.res && (((a.res_ld | a.res_coff) % VN) || ((uintptr_t)a.res & 15))) return false;
   if (a.split > 0 && a.split % 32) return false;
-  if (a.Cout <= 32 || (a.K <= 64 && a.Cout > 256)) return false;      // nothing to fill a tile with; one K step: one channel tile (launch_flow_cfg)
+  if (a.Cout <= 32 || (a.K <= 128 / ES && a.Cout > 256)) return false;      // nothing to fill a tile with; one K step: one channel tile (launch_flow_cfg)
   // 32-bit offsets: weights, and the pixels of a tile (256 of them) in every tensor
   const long long ld = std::max(std::max(a.x_ld, a.y_ld), std::max(a.res ? a.res_ld : 0, a.split > 0 ? a.y2_ld : 0));
   return (long long)a.w_rows * a.Kp * ES < 0x7FFFFFFFLL && 256 * ld * ES < 0x7FFFFFF0LL && (long long)a.n * a.Ho * a.Wo < 0x7FFFFF00LL &&
@@ -35,19 +36,19 @@ constexpr FlowCost FLOW_COST[8] = {
     {192, 128, 3.22, 0.554, 1.46, 0.000, 0.045, 0.064},
     {128, 256, 3.00, 0.674, 2.06, 0.000, 0.065, 0.093},
     {256, 128, 3.76, 0.653, 1.18, 0.000, 0.061, 0.053}};
-inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, int num_cu) {
+inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, int num_cu, int ES = 2) {
   const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
-  const double per_cu = (double)((tiles + num_cu - 1) / num_cu), nk = (a.K + 63) / 64;
+  const double per_cu = (double)((tiles + num_cu - 1) / num_cu), nk = (a.K + 128 / ES - 1) / (128 / ES);
   const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
-  const double mb = 2e-6 * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
-  return c.base + per_cu * (nk * (c.step + (a.Cin % 64 ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * nk : 0.0) + c.per_mb * mb;
+  const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
+  return c.base + per_cu * (nk * (c.step + (a.Cin % (128 / ES) ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * nk : 0.0) + c.per_mb * mb;
 }
 // The row of FLOW_COST with the smallest estimate for M output pixels.
-inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us) {
+inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us, int ES = 2) {
   int best = -1;
   for (int i = 0; i < 8; ++i) {
-    if (a.K <= 64 && a.Cout > FLOW_COST[i].bc) continue;
-    const double t = flow_cost_us(FLOW_COST[i], a, M, num_cu);
+    if (a.K <= 128 / ES && a.Cout > FLOW_COST[i].bc) continue;
+    const double t = flow_cost_us(FLOW_COST[i], a, M, num_cu, ES);
     if (best < 0 || t < *us) { *us = t; best = i; }
   }
   return best;
@@ -64,5 +65,6 @@ inline bool flow_takes_1x1(const ConvArgs& a) { return a.Cin >= 128 && a.Cin % 6
 
 hipError_t launch_flow_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 hipError_t launch_flow_bf16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
+hipError_t launch_flow_f8(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 
 }  // namespace octo

@@ -71,3 +71,47 @@ def test_flow_parity(octo, dtype, case):
     assert kid == want
     assert rel_err(dy[..., :cout].float().cpu().numpy(), round_storage(y, dtype)) <= TOL[dtype]
     assert (dy[..., cout:].float().cpu().numpy() == -7.0).all()
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,k,stride,res,xe,ye,mode", [
+    (33, 40, 41, 384, 400, 1, 1, nn.RES_BEFORE_ACT, 0, 16, 0),     # three whole K steps, 16 of the last tile's channels
+    (9, 41, 39, 256, 80, 1, 1, nn.RES_NONE, 128, 0, 0),            # two steps, several channel tiles of 64
+    (60, 40, 41, 96, 96, 1, 1, nn.RES_AFTER_ACT, 0, 0, 2),         # one step, part of it
+    (21, 56, 55, 64, 256, 1, 1, nn.RES_NONE, 0, 0, 2),             # half a step, the widest channel tile
+    (5, 33, 31, 528, 176, 1, 1, nn.RES_NONE, 16, 32, 2),           # 16 of the fifth step
+    (25, 61, 63, 128, 128, 3, 2, nn.RES_BEFORE_ACT, 0, 0, 1),      # a tap per step, windows over every border
+    (8, 160, 163, 48, 96, 3, 2, nn.RES_NONE, 0, 0, 2),             # steps across taps
+    (17, 54, 34, 112, 368, 5, 1, nn.RES_AFTER_ACT, 0, 0, 2),
+])
+def test_flow_fp8(octo, n, h, w, cin, cout, k, stride, res, xe, ye, mode):
+    import torch
+    rng = np.random.default_rng(61)
+    pad = k // 2
+    f8 = lambda shape: torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).to(torch.float8_e4m3fn)
+    x, wt = f8((n, h, w, cin)), f8((cout, k, k, cin))
+    scale, bias = (rng.uniform(0.5, 1.0, cout) / np.sqrt(k * k * cin)).astype(np.float32), rng.uniform(-0.1, 0.1, cout).astype(np.float32)
+    layer = octo.ConvOp(wt.view(torch.uint8).numpy(), bias, "f8", stride, pad, nn.ACT_RELU, scale=scale)
+    ho, wo = layer.out_hw(h, w)
+    r = f8((n, ho, wo, cout)) if res else None
+    dx = torch.full((n, h, w, cin + xe), 0x7F, dtype=torch.uint8, device="cuda")       # NaN beside the tensor
+    dx[..., :cin] = x.view(torch.uint8).cuda()
+    dy = torch.full((n, ho, wo, cout + ye), 0x55, dtype=torch.uint8, device="cuda")
+    kid = octo.op_conv(layer, dx[..., :cin], dy[..., :cout], r.view(torch.uint8).cuda() if res else None, res, res_scale=0.5, y_inv_scale=2.0)
+    torch.cuda.synchronize()
+    assert kid // 10000000 == 120 + mode, kid
+    xf, wf = np.zeros((n, h + 2 * pad, w + 2 * pad, cin), np.float32), wt.float().numpy()
+    xf[:, pad:pad + h, pad:pad + w] = x.float().numpy()
+    acc = np.zeros((n * ho * wo, cout), np.float32)
+    for p in range(k):
+        for q in range(k):
+            acc += np.ascontiguousarray(xf[:, p:p + stride * ho:stride, q:q + stride * wo:stride][:, :ho, :wo]).reshape(-1, cin) @ np.ascontiguousarray(wf[:, p, q].T)
+    v = (acc * scale + bias).reshape(n, ho, wo, cout)
+    add = 0.5 * r.float().numpy() if res else 0.0
+    v = np.maximum(v + add, 0.0) if res == nn.RES_BEFORE_ACT else np.maximum(v, 0.0) + add
+    want = torch.from_numpy(np.clip(v * 2.0, -448.0, 448.0)).to(torch.float8_e4m3fn)
+    # one code apart at most, and that only where the sum lies next to a rounding boundary: the matrix instruction cuts products off at 2^-13
+    # of the largest of eight, a code is 2^-4 .. 2^-3 of its value wide, so fewer than one in a hundred.  Codes run as signed magnitudes
+    code = lambda t: torch.where(t.view(torch.uint8) < 128, t.view(torch.uint8).int(), 128 - t.view(torch.uint8).int())
+    diff = (code(dy[..., :cout].cpu().contiguous().view(torch.float8_e4m3fn)) - code(want)).abs()
+    assert int(diff.max()) <= 1 and float((diff > 0).float().mean()) < 0.01, (int(diff.max()), float((diff > 0).float().mean()))
+    assert bool((dy[..., cout:] == 0x55).all())
