@@ -71,7 +71,7 @@ def conv_name(kid: int, dtype: str) -> str:
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
     if 200000000 <= d < 300000000:                       # general form whose loads run across tiles: digits M BBB PPP K
         mode, bc, bp, kv = (d - 200000000) // 10000000, d // 10000 % 1000, d // 10 % 1000, d % 10
-        return "octo::conv_flow_kernel<%s, %d, %d, %d, %d, %d, 3, %d, %d>" % ((ctype, FLOW[(bc, bp)][0], bc, bp, FLOW[(bc, bp)][1], kv, 2 if dtype == "f8" and (bc, bp) == (64, 64) else FLOW[(bc, bp)][2], mode)) if (bc, bp) in FLOW else "convolution kernel %d" % kid
+        return "octo::conv_flow_kernel<%s, %d, %d, %d, %d, %d, 3, %d, %d>" % ((ctype, FLOW[(bc, bp)][0], bc, bp, FLOW[(bc, bp)][1], kv, FLOW[(bc, bp)][2], mode)) if (bc, bp) in FLOW else "convolution kernel %d" % kid
     if 500000000 <= d < 600000000:                       # streaming 1x1 kernel
         return "octo::conv1x1_stream_kernel<%s, %d>" % (ctype, (d - 500000000) // 1000 // 32)
     if 600000000 <= d < 700000000:                       # split-K kernel

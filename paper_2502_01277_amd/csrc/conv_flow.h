@@ -34,10 +34,16 @@ struct FlowGeom { FastDiv div_tc, div_howo, div_wo; };     // divisions by chann
 // tap; any layer (a lane works out the tap of its vector at every step).
 enum { FLOW_POINTWISE = 0, FLOW_TAPS = 1, FLOW_ANY = 2 };
 
+// Workgroups per compute unit: at most MINB, and what the LDS holds (stages, biases, E4M3 scales).
+constexpr int flow_resident(int es, int NT, int BC, int BP, int KV, int NST, int MINB) {
+  const int rp = NT / KV, lds = ((BC + rp - 1) / rp * rp + BP) * KV * 16 * NST + 12 * NT * (es == 1 ? 2 : 1), fit = 160 * 1024 / lds;
+  return fit < MINB ? fit : MINB;
+}
+
 // NT: lanes; BC x BP: tile; WC: wavefronts along the channels (NT / 64 / WC along the pixels); KV: vectors of 16 bytes per LDS row and
-// K step; NST: stages of the ring; MINB: workgroups per compute unit.
+// K step; NST: stages of the ring; MINB: workgroups per compute unit, where the LDS holds them.
 template <typename T, int NT, int BC, int BP, int WC, int KV, int NST, int MINB, int MODE>
-__global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const ConvArgs a, const FlowGeom gm) {
+__global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, MINB) * NT / 256) void conv_flow_kernel(const ConvArgs a, const FlowGeom gm) {
   using E = Elem<T>;
   constexpr int VN = E::N, ES = (int)sizeof(T), BK = KV * VN;
   constexpr bool PW = MODE == FLOW_POINTWISE;
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(NT, MINB * NT / 256) void conv_flow_kernel(const Co
 template <typename T, int NT, int BC, int BP, int WC, int KV, int NST, int MINB, int MODE>
 static hipError_t launch_flow_mode(const ConvArgs& a, const FlowGeom& gm, long long tiles, int num_cu, hipStream_t s, const ConvTiming& tm) {
   long long grid = (tiles + 7) / 8 * 8;
-  const long long cap = ((long long)num_cu * MINB + 7) / 8 * 8;
+  const long long cap = ((long long)num_cu * flow_resident(sizeof(T), NT, BC, BP, KV, NST, MINB) + 7) / 8 * 8;
   if (grid > cap) grid = cap;
   if (tm.start && tm.stop)
     hipExtLaunchKernelGGL((conv_flow_kernel<T, NT, BC, BP, WC, KV, NST, MINB, MODE>), dim3((unsigned)grid), dim3(NT), 0, s, tm.start, tm.stop, 0, a, gm);
@@ -416,7 +422,7 @@ static hipError_t launch_flow_cfg(const ConvArgs& a, int num_cu, hipStream_t s, 
 template <typename T>
 static hipError_t launch_flow(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   switch (which) {
-    case 0: return launch_flow_cfg<T, 256, 64, 64, 2, 8, 3, sizeof(T) == 1 ? 2 : 3>(a, num_cu, s, kernel_id, tm);
+    case 0: return launch_flow_cfg<T, 256, 64, 64, 2, 8, 3, 3>(a, num_cu, s, kernel_id, tm);
     case 1: return launch_flow_cfg<T, 256, 64, 128, 1, 8, 3, 2>(a, num_cu, s, kernel_id, tm);
     case 2: return launch_flow_cfg<T, 256, 128, 64, 2, 8, 3, 2>(a, num_cu, s, kernel_id, tm);
     case 3: return launch_flow_cfg<T, 512, 128, 128, 2, 8, 3, 1>(a, num_cu, s, kernel_id, tm);
