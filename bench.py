@@ -102,54 +102,54 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "9957d582877025b5": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4366020054,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1698904210,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283051107,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344609020,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1483380603,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553413478,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 848479598,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355752227,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282107181,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2207646543,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 988174154,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1911793742,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629434208,
-        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255832788,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1079390844,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167891704,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628227822,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 128136766,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838646,
-        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69133722,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856349,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28735905,
-        "octo::conv1x1_stream_kernel<_Float16, 2>": 29073265,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064045,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727918,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942844,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87626950,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28525928,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77734077,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64466699,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21158472,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31499947,
-        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369379,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873117,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40074042,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39790474,
-        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19103922,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136853,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510205,
-        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376772,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355715,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644831,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223612,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253460,
-        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730480,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39505790,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18701297,
+    "bd58fb1f55b260dc": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4365021734,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1701780210,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283041468,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344656772,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1482962841,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553399159,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 848349985,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355635207,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282191966,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2205215926,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 991088695,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910906934,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629445948,
+        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255825719,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078968943,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167930037,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 627742106,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 127872954,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838666,
+        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69133341,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856321,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28734870,
+        "octo::conv1x1_stream_kernel<_Float16, 2>": 29073144,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064020,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727905,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942834,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87660246,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28524710,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77784270,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64446254,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21159167,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31500846,
+        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369348,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873086,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40069931,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39784767,
+        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19103904,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136847,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510189,
+        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376753,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355739,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644818,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223608,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253453,
+        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730475,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39505689,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18699662,
     },
 }
 
