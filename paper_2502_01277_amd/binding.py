@@ -148,7 +148,7 @@ EXPORTS = [
     "octo_executor_results", "octo_executor_last_error", "octo_executor_destroy", "octo_profile_layers", "octo_set_layer_timing", "octo_get_layer_info", "octo_set_stage_timing", "octo_get_stage_ms",
     "octo_debug_get_tensor", "octo_debug_tensor_shape", "octo_debug_set_head", "octo_set_expected_items", "octo_debug_get_launch_counts", "octo_debug_run_model",
     "octo_debug_get_detections", "octo_debug_get_rois", "octo_debug_get_labels", "octo_letterbox_geometry", "octo_op_frame_table", "octo_op_letterbox",
-    "octo_op_crop_resize", "octo_op_decode", "octo_op_topk", "octo_op_nms", "octo_op_nms_scratch_bytes", "octo_op_nms_static", "octo_op_compact", "octo_probe_copy", "octo_probe_mfma",
+    "octo_op_crop_resize", "octo_op_decode", "octo_op_topk", "octo_op_nms", "octo_op_nms_scratch_bytes", "octo_op_nms_static", "octo_op_compact", "octo_op_compact_dense", "octo_probe_copy", "octo_probe_mfma",
     "octo_op_conv", "octo_op_conv_packed_bytes", "octo_op_conv_padded_cout", "octo_op_conv_pack", "octo_quantize_e4m3", "octo_dequantize_e4m3",
 ]
 
@@ -232,6 +232,7 @@ def lib() -> C.CDLL:
         L.octo_probe_mfma.argtypes = [i32, vp, C.c_size_t, i32, i32, vp, vp]
         L.octo_op_nms_static.argtypes = [vp, vp, i32, i32, f32, i32, vp, vp, vp]
         L.octo_op_compact.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, i32, i32, vp, vp, vp, i32, vp, vp, vp, vp, vp]
+        L.octo_op_compact_dense.argtypes = L.octo_op_compact.argtypes
         L.octo_op_conv.argtypes = [vp, vp, vp]
         L.octo_op_conv_packed_bytes.restype = C.c_size_t
         L.octo_op_conv_packed_bytes.argtypes = [i32, i32, i32, i32, i32]
@@ -686,9 +687,9 @@ def op_compact(top, keep, n_keep, src_hw, in_hw, class_mask: int, cap: int, stre
     base = buf.data_ptr()
     cm = (C.c_uint64 * 2)(class_mask & ((1 << 64) - 1), (class_mask >> 64) & ((1 << 64) - 1))
     side = _order(stream, buf)
-    _st(lib().octo_op_compact(top.data_ptr(), k_cap, keep.data_ptr(), n_keep.data_ptr(), max_det, n, src_hw[0], src_hw[1],
-                              in_hw[0], in_hw[1], cm, base, base + at[4], cap, base + at[2],
-                              base + at[5], base + at[1], base + at[3], _stream_ptr(stream)))
+    _st(lib().octo_op_compact_dense(top.data_ptr(), k_cap, keep.data_ptr(), n_keep.data_ptr(), max_det, n, src_hw[0], src_hw[1],
+                                    in_hw[0], in_hw[1], cm, base, base + at[4], cap, base + at[2],
+                                    base + at[5], base + at[1], base + at[3], _stream_ptr(stream)))
     if side is not None:
         t.cuda.current_stream().wait_stream(side)
     h = buf[:at[5]].cpu().numpy()

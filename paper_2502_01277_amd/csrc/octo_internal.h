@@ -178,6 +178,7 @@ struct CompactArgs {
   int* roi_cnt[OCTO_MAX_EDGES];            // [n] scratch: ROIs per item (required)
   octo_box* boxes;                         // [n][max_det] final boxes in source pixels
   int* flags;                              // [n]
+  int dense;                               // step 1 on its own: roi_of past an item's last kept box becomes -1 (else it is left alone)
 };
 hipError_t launch_compact(const CompactArgs& a, hipStream_t s, bool counted = false);     // counted: step 1 has run (launch_select)
 // Top-k, NMS and (with ca) step 1 of the compaction in one launch; m.mask is not used.

@@ -245,10 +245,10 @@ octo_status octo_op_nms_static(const octo_cand* d_top, const int32_t* d_top_coun
   return from_hip(launch_nms(a, (hipStream_t)hip_stream));
 }
 
-octo_status octo_op_compact(const octo_cand* d_top, int32_t k_cap, const int32_t* d_keep, const int32_t* d_n_keep, int32_t max_det,
-                            int32_t n, int32_t src_h, int32_t src_w, int32_t in_h, int32_t in_w, const uint64_t* class_mask2,
-                            octo_roi* d_rois, int32_t* d_n_rois, int32_t cap, int32_t* d_roi_of, int32_t* d_item_counts, octo_box* d_boxes, int32_t* d_flags,
-                            void* hip_stream) {
+static octo_status op_compact(bool dense, const octo_cand* d_top, int32_t k_cap, const int32_t* d_keep, const int32_t* d_n_keep, int32_t max_det,
+                              int32_t n, int32_t src_h, int32_t src_w, int32_t in_h, int32_t in_w, const uint64_t* class_mask2,
+                              octo_roi* d_rois, int32_t* d_n_rois, int32_t cap, int32_t* d_roi_of, int32_t* d_item_counts, octo_box* d_boxes, int32_t* d_flags,
+                              void* hip_stream) {
   if (!d_top || !d_keep || !d_n_keep || !class_mask2 || !d_rois || !d_n_rois || !d_roi_of || !d_item_counts || n < 0 || cap < 0 || max_det < 1 || k_cap < 1 ||
       src_h <= 0 || src_w <= 0 || in_h <= 0 || in_w <= 0)
     return OCTO_EINVAL;
@@ -260,8 +260,24 @@ octo_status octo_op_compact(const octo_cand* d_top, int32_t k_cap, const int32_t
   a.src_w = (float)src_w; a.src_h = (float)src_h;
   a.n_edges = 1; a.class_mask[0][0] = class_mask2[0]; a.class_mask[0][1] = class_mask2[1];
   a.rois[0] = d_rois; a.n_roi[0] = d_n_rois; a.roi_cap[0] = cap; a.roi_of[0] = d_roi_of; a.roi_cnt[0] = d_item_counts;
-  a.boxes = d_boxes; a.flags = d_flags;
+  a.boxes = d_boxes; a.flags = d_flags; a.dense = dense;
   return from_hip(launch_compact(a, (hipStream_t)hip_stream));
+}
+
+octo_status octo_op_compact(const octo_cand* d_top, int32_t k_cap, const int32_t* d_keep, const int32_t* d_n_keep, int32_t max_det,
+                            int32_t n, int32_t src_h, int32_t src_w, int32_t in_h, int32_t in_w, const uint64_t* class_mask2,
+                            octo_roi* d_rois, int32_t* d_n_rois, int32_t cap, int32_t* d_roi_of, int32_t* d_item_counts, octo_box* d_boxes, int32_t* d_flags,
+                            void* hip_stream) {
+  return op_compact(false, d_top, k_cap, d_keep, d_n_keep, max_det, n, src_h, src_w, in_h, in_w, class_mask2, d_rois, d_n_rois, cap, d_roi_of,
+                    d_item_counts, d_boxes, d_flags, hip_stream);
+}
+
+octo_status octo_op_compact_dense(const octo_cand* d_top, int32_t k_cap, const int32_t* d_keep, const int32_t* d_n_keep, int32_t max_det,
+                                  int32_t n, int32_t src_h, int32_t src_w, int32_t in_h, int32_t in_w, const uint64_t* class_mask2,
+                                  octo_roi* d_rois, int32_t* d_n_rois, int32_t cap, int32_t* d_roi_of, int32_t* d_item_counts, octo_box* d_boxes, int32_t* d_flags,
+                                  void* hip_stream) {
+  return op_compact(true, d_top, k_cap, d_keep, d_n_keep, max_det, n, src_h, src_w, in_h, in_w, class_mask2, d_rois, d_n_rois, cap, d_roi_of,
+                    d_item_counts, d_boxes, d_flags, hip_stream);
 }
 
 }  // extern "C"

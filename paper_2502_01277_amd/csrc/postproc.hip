@@ -649,7 +649,8 @@ __global__ __launch_bounds__(256) void compact_count_kernel(const CompactArgs a)
     if (t == 0) s_run += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
     __syncthreads();
   }
-  for (int r = nk + t; r < a.max_det; r += blockDim.x) a.roi_of[e][(size_t)item * a.max_det + r] = -1;        // no kept box
+  if (a.dense)
+    for (int r = nk + t; r < a.max_det; r += blockDim.x) a.roi_of[e][(size_t)item * a.max_det + r] = -1;
   if (t == 0) a.roi_cnt[e][item] = s_run;
 }
 

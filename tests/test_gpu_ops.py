@@ -593,6 +593,33 @@ def test_topk_nms_compact_bit_exact_from_oracle_candidates(octo, k):
     assert len(rois) == 3 and flags.any()
 
 
+@pytest.mark.parametrize("max_det", [1, 40, 300])           # (a workgroup takes 256 entries at a time)
+def test_compact_leaves_entries_past_the_kept_boxes_alone(octo, max_det):
+    """The C call writes the ROI ids of kept boxes and nothing behind them; its dense form writes -1 there, as op_compact returns it."""
+    import ctypes as C
+    import torch
+    n_keep = [0, 1, max_det, max_det // 2]
+    top = torch.zeros((4, 320, 32), dtype=torch.uint8, device="cuda")
+    keep = torch.arange(max_det, dtype=torch.int32, device="cuda").repeat(4, 1)
+    nk = torch.tensor(n_keep, dtype=torch.int32, device="cuda")
+    rois = torch.zeros((4 * max_det, 32), dtype=torch.uint8, device="cuda")
+    n_rois, counts = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(4, dtype=torch.int32, device="cuda")
+    every = (C.c_uint64 * 2)(2 ** 64 - 1, 2 ** 64 - 1)
+    ids = np.concatenate([[0], np.cumsum(n_keep)])
+    for call, past in ((octo.lib().octo_op_compact, 77), (octo.lib().octo_op_compact_dense, -1)):
+        roi_of = torch.full((4, max_det), 77, dtype=torch.int32, device="cuda")
+        st = call(top.data_ptr(), 320, keep.data_ptr(), nk.data_ptr(), max_det, 4, 270, 480, 320, 320, every, rois.data_ptr(), n_rois.data_ptr(),
+                  4 * max_det, roi_of.data_ptr(), counts.data_ptr(), None, None, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert st == octo.OK and int(n_rois) == sum(n_keep)
+        got = roi_of.cpu().numpy()
+        for f in range(4):
+            assert got[f, :n_keep[f]].tolist() == list(range(ids[f], ids[f + 1]))
+            assert (got[f, n_keep[f]:] == past).all()
+    back = octo.op_compact(top, keep, nk, (270, 480), (320, 320), 2 ** 128 - 1, 4 * max_det)[1]
+    assert np.array_equal(back, got)
+
+
 def test_topk_long_lists_and_ties(octo):
     # more candidates than one LDS pass holds, with many equal scores
     rng = np.random.default_rng(14)
