@@ -132,7 +132,7 @@ struct ResizeArgs {
   FastDiv div_wq, div_h;          // set by the launchers: lanes per output row, rows per item
 };
 void letterbox_geometry(int src_h, int src_w, int dst_h, int dst_w, int* nw, int* nh, int* left, int* top);
-hipError_t launch_letterbox(int dtype, const ResizeArgs& a, hipStream_t s);
+hipError_t launch_letterbox(int dtype, const ResizeArgs& a, int num_cu, hipStream_t s);
 hipError_t launch_crop_resize(int dtype, const ResizeArgs& a, hipStream_t s);
 
 struct DecodeArgs {

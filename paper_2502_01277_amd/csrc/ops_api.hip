@@ -33,6 +33,19 @@ octo_status static_scratch(void** out) {
   *out = g_scratch_addr[dev];
   return OCTO_OK;
 }
+int cached_cu_count() {
+  static std::mutex mu;
+  static int cus[MAX_DEVICES] = {};
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return 0;
+  std::lock_guard<std::mutex> lock(mu);
+  if (!cus[dev]) {
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
+    cus[dev] = prop.multiProcessorCount;
+  }
+  return cus[dev];
+}
 }  // namespace
 
 extern "C" {
@@ -70,7 +83,8 @@ octo_status octo_op_letterbox(const void* d_frame_ptrs, const void* d_pitches, i
   a.frames = (const uint8_t* const*)d_frame_ptrs; a.pitches = (const size_t*)d_pitches; a.src_h = src_h; a.src_w = src_w;
   a.dst = d_dst; a.dst_h = dst_h; a.dst_w = dst_w; a.dst_c = 3; a.pad_value = pad_value; a.n = n; a.n_frames = n;
   for (int c = 0; c < 3; ++c) { a.scale[c] = scale3[c]; a.bias[c] = bias3[c]; }
-  return from_hip(launch_letterbox(dtype, a, (hipStream_t)hip_stream));
+  const int cus = n > 0 ? cached_cu_count() : 0;
+  return from_hip(launch_letterbox(dtype, a, cus > 0 ? cus : 256, (hipStream_t)hip_stream));
 }
 
 octo_status octo_op_crop_resize(const void* d_frame_ptrs, const void* d_pitches, int32_t n_frames, int32_t src_h, int32_t src_w,
@@ -113,19 +127,6 @@ float e4m3_decode(uint8_t c) {
   if (ex == 15 && q == 7) return std::nanf("");
   const float mag = ex == 0 ? std::ldexp((float)q, -9) : std::ldexp(1.0f + (float)q / 8.0f, ex - 7);
   return (c & 0x80) ? -mag : mag;
-}
-int cached_cu_count() {
-  static std::mutex mu;
-  static int cus[MAX_DEVICES] = {};
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return 0;
-  std::lock_guard<std::mutex> lock(mu);
-  if (!cus[dev]) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return 0;
-    cus[dev] = prop.multiProcessorCount;
-  }
-  return cus[dev];
 }
 bool conv_dtype(int dt) { return valid_dtype(dt) || dt == OCTO_F8; }
 }  // namespace

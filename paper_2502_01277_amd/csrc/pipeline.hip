@@ -1085,7 +1085,7 @@ octo_status enqueue_root(octo_pipeline* p, Batch& B, hipStream_t s, int n) {
     const int cn = std::min(chunk, n - c0);
     const bool last = c0 + cn >= n;
     ra.frames = p->d_frames + c0; ra.pitches = p->d_pitch + c0; ra.n = cn; ra.n_frames = cn;
-    HIPCHK(p, launch_letterbox(root.d.dtype, ra, s));
+    HIPCHK(p, launch_letterbox(root.d.dtype, ra, p->num_cu, s));
     if (ev && last) HIPCHK(p, hipEventRecord(ev[1 + ST_LETTERBOX], s));
     HIPCHK(p, run_layers(p, root, cn, nullptr, s, p->layer_timing && last ? &B.layer_ev[0] : nullptr));
     if (ev && last) HIPCHK(p, hipEventRecord(ev[1 + ST_DET_LAYERS], s));

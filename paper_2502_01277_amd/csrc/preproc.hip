@@ -82,11 +82,11 @@ struct LetterboxGeom { int nw, nh, left, top; };
 // EXACT: the source / resized size ratio is an odd integer in both directions, so every output pixel is exactly one
 // source pixel (1080p -> 640x360 and 2160p -> 1280x720 are ratio 3): one window load per pixel, no interpolation.
 //
-// R rows per lane, for launches that still fill the chip then (letterbox_e): a lane's time is two dependent trips to memory, the frame's
-// address and then its pixels, whatever it does behind them.  With one row at a time a launch ran at 2.9 TB/s with the vector units 25 % busy.
 // Four pixels at ratio 3 are 36 consecutive bytes of the source row; where those are aligned to 4 they are loaded as words, and a value
-// is a byte of a word at a place known at compile time.  Measured, us: 64 frames 1080p to 640 x 640 x 4 103 -> 65, 32 of 2160p to 1280 x 1280 x 4
-// 197 -> 124, 8 of 1080p 15.2 -> 11.9.
+// is a byte of a word at a place known at compile time (byte windows : words, frames from memory, us: 8 frames 1080p to 640 x 640 x 4 17.9 :
+// 15.3, 32 50 : 37, 32 of 2160p to 1280 x 1280 x 4 with the rows in groups 204 : 129, 3.7 TB/s).  R rows per lane: a lane's time is two dependent trips to memory, the frame's
+// address and then its pixels, and the rows' words are loaded beside each other.  letterbox_p says when.  Frames whose addresses turn
+// out not to be aligned take their rows one after the other.
 template <typename T, int PX, bool C4, bool EXACT, int R>
 __global__ void letterbox_kernel(const ResizeArgs a, const LetterboxGeom g) {
   const int wq = a.dst_w / PX;
@@ -385,12 +385,15 @@ static bool resize_prepare(ResizeArgs& a) {
 }
 
 constexpr int LETTERBOX_ROWS = 4;
-template <typename T, int PX, bool C4, bool EXACT> static hipError_t letterbox_p(const ResizeArgs& a, const LetterboxGeom& g, hipStream_t s) {
+template <typename T, int PX, bool C4, bool EXACT> static hipError_t letterbox_p(const ResizeArgs& a, const LetterboxGeom& g, int num_cu, hipStream_t s) {
   if constexpr (EXACT && PX == 4) {
-    // Rows in groups once that still gives every compute unit eight wavefronts.  One row : four, 1080p to 640 x 640, us:
-    // 2 frames 4.2 : 4.6, 4 frames 5.6 : 6.0, 5 frames 6.4 : 6.4.
+    // Rows in groups where they are loaded as words (ratio 3, the left border a multiple of four pixels) and the launch is three rounds of
+    // 32 wavefronts per compute unit even so: with fewer, the groups' uneven end costs more than the loads beside each other save.  One
+    // row : four, frames from memory, us: 1080p to 640 x 640 x 4, 8 frames 15.3 : 15.5, 16 21.8 : 24.3, 32 36.7 : 37.9, 64 69.7 : 68.1; 2160p to
+    // 1280 x 1280 x 4, 8 frames 36.9 : 38.1, 16 70.1 : 68.3, 32 138 : 129.  Rows one after the other lose with any number of frames: ratio 5, 32
+    // frames 62.0 : 71.6, a border of 142 pixels 50.9 : 61.9, ratio 1, 64 frames 46 : 57.
     const long long lanes = (long long)a.n * ((a.dst_h + LETTERBOX_ROWS - 1) / LETTERBOX_ROWS) * (a.dst_w / PX);
-    if (lanes >= 256LL * 8 * 64) {
+    if (a.src_w / g.nw == 3 && g.left % 4 == 0 && lanes >= 3LL * 32 * 64 * num_cu) {
       ResizeArgs b = a;
       b.div_h = make_fastdiv((unsigned)((a.dst_h + LETTERBOX_ROWS - 1) / LETTERBOX_ROWS));
       hipLaunchKernelGGL((letterbox_kernel<T, PX, C4, EXACT, LETTERBOX_ROWS>), dim3(resize_grid(lanes)), dim3(256), 0, s, b, g);
@@ -400,15 +403,15 @@ template <typename T, int PX, bool C4, bool EXACT> static hipError_t letterbox_p
   hipLaunchKernelGGL((letterbox_kernel<T, PX, C4, EXACT, 1>), dim3(resize_grid((long long)a.n * a.dst_h * (a.dst_w / PX))), dim3(256), 0, s, a, g);
   return hipGetLastError();
 }
-template <typename T, bool EXACT> static hipError_t letterbox_e(const ResizeArgs& a, const LetterboxGeom& g, hipStream_t s) {
+template <typename T, bool EXACT> static hipError_t letterbox_e(const ResizeArgs& a, const LetterboxGeom& g, int num_cu, hipStream_t s) {
   const bool px4 = a.dst_w % 4 == 0 && ((uintptr_t)a.dst & 15) == 0;
-  if (a.dst_c == 4) return px4 ? letterbox_p<T, 4, true, EXACT>(a, g, s) : letterbox_p<T, 1, true, EXACT>(a, g, s);
-  return px4 ? letterbox_p<T, 4, false, EXACT>(a, g, s) : letterbox_p<T, 1, false, EXACT>(a, g, s);
+  if (a.dst_c == 4) return px4 ? letterbox_p<T, 4, true, EXACT>(a, g, num_cu, s) : letterbox_p<T, 1, true, EXACT>(a, g, num_cu, s);
+  return px4 ? letterbox_p<T, 4, false, EXACT>(a, g, num_cu, s) : letterbox_p<T, 1, false, EXACT>(a, g, num_cu, s);
 }
-template <typename T> static hipError_t letterbox_t(const ResizeArgs& a, hipStream_t s) {
+template <typename T> static hipError_t letterbox_t(const ResizeArgs& a, int num_cu, hipStream_t s) {
   const LetterboxGeom g = letterbox_geom(a.src_h, a.src_w, a.dst_h, a.dst_w);
   const bool exact = a.src_w % g.nw == 0 && a.src_h % g.nh == 0 && ((a.src_w / g.nw) & 1) && ((a.src_h / g.nh) & 1);
-  return exact ? letterbox_e<T, true>(a, g, s) : letterbox_e<T, false>(a, g, s);
+  return exact ? letterbox_e<T, true>(a, g, num_cu, s) : letterbox_e<T, false>(a, g, num_cu, s);
 }
 template <typename T> static hipError_t crop_t(const ResizeArgs& a, hipStream_t s) {
   // one 64-thread workgroup per output row, at most 32 per compute unit at a time; each die strides over the rows of
@@ -427,14 +430,14 @@ template <typename T> static hipError_t crop_t(const ResizeArgs& a, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_letterbox(int dtype, const ResizeArgs& a0, hipStream_t s) {
+hipError_t launch_letterbox(int dtype, const ResizeArgs& a0, int num_cu, hipStream_t s) {
   if (a0.n <= 0) return hipSuccess;
   ResizeArgs a = a0;
   if ((a.dst_c != 3 && a.dst_c != 4) || a.src_w < 4 || !resize_prepare(a)) return hipErrorInvalidValue;
   switch (dtype) {
-    case OCTO_F32: return letterbox_t<float>(a, s);
-    case OCTO_F16: return letterbox_t<_Float16>(a, s);
-    case OCTO_BF16: return letterbox_t<__bf16>(a, s);
+    case OCTO_F32: return letterbox_t<float>(a, num_cu, s);
+    case OCTO_F16: return letterbox_t<_Float16>(a, num_cu, s);
+    case OCTO_BF16: return letterbox_t<__bf16>(a, num_cu, s);
   }
   return hipErrorInvalidValue;
 }
