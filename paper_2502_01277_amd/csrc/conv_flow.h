@@ -187,7 +187,9 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(x_base, 0, x_len, BUF_FLAGS);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, w_now, BUF_FLAGS);
     const unsigned st = lds_ring + l_st * STAGE;
-    const int ox = x_len ? l_x : 0, ow = w_now ? l_w : 0;
+    // A tap that no pixel of the tile can use (a map no taller than the padding) may start behind the end of the buffer, where every lane is
+    // out of range already.  The scalar offset must not be: the range check takes it off the length, which would wrap, and let any lane in.
+    const int ox = l_x < x_len ? l_x : 0, ow = w_now ? l_w : 0;
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
       if (q < from || q >= to) continue;
