@@ -22,6 +22,7 @@
 // Measured against tiles staged in LDS, us: 7x7 with the pool, bf16, 4170 crops of 224 x 224 2146 -> 1300, some 380 crops 232 -> 148, some 6
 // crops 23 -> 18; 6x6 on 32 frames of 1280 x 1280 to 64 channels 496 -> 434, on 64 of 640 x 640 to 32 channels 170 -> 127 (5 TB/s).
 #include "mfma_common.h"
+#include "stem_segment.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -292,19 +293,11 @@ __global__ __launch_bounds__(THREADS, 2) void stem_pool_any_kernel(const ConvArg
 template <typename T, int BC, int KH, int PKW, bool POOL>
 static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (kernel_id) *kernel_id = stem_kernel_id(BC, KH, PKW, POOL);
-  // Output rows per segment: a strip walked by one wavefront is a serial chain (11 crops of 224 x 224 have 22 strips of 112 rows, the chip has
-  // 2048 wavefronts).  Cut into segments it costs, with the pool, one more convolution row for each cut, and about two rows' time to start;
-  // the length with the shortest busiest wavefront is taken, for the expected number of items.
   ConvArgs b = a;
   const int out_w = POOL ? a.pool_wo : a.Wo, out_h = POOL ? a.pool_ho : a.Ho, width = POOL ? SP_POOLED : SP_STRIP;
-  const long long strips = (out_w + width - 1) / width, waves = 8LL * num_cu;
-  const long long items = a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n;
-  long long best = 0;
-  for (int seg = out_h; seg >= 1; --seg) {
-    const long long units = items * strips * ((out_h + seg - 1) / seg), rounds = (units + waves - 1) / waves;
-    const long long rows = rounds * (POOL ? 2 * seg + 3 : seg + 2);
-    if (seg == out_h || rows < best) { best = rows; b.stem_seg = seg; }
-  }
+  const long long strips = (out_w + width - 1) / width;
+  const long long items = a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n;       // expected
+  b.stem_seg = stem_segment(out_h, items * strips, 8LL * num_cu, POOL);
   const long long units = out_h > 0 ? (long long)a.n * strips * ((out_h + b.stem_seg - 1) / b.stem_seg) : 0;
   if (units <= 0) return hipSuccess;
   if (units >= 0x7FFF0000LL) return hipErrorNotSupported;
