@@ -47,3 +47,43 @@ def test_streaming_1x1_parity(octo, dtype, case):
     assert 1500000000 <= kid < 1600000000
     assert rel_err(dy[..., :cout].float().cpu().numpy(), round_storage(y, dtype)) <= TOL[dtype]
     assert (dy[..., cout:].float().cpu().numpy() == -7.0).all()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("cin,cout,res", [(64, 32, False), (96, 32, False), (64, 64, False), (128, 64, True)])
+def test_results_do_not_change_with_the_running_item_count(octo, dtype, cin, cout, res):
+    """1x1 layers of a downstream model: the running average of its item counts must not choose between kernels that sum in different
+    orders.  The model's capacity stands in for the average before the first batch, so the same frame repeated, and then beside frames
+    with many more objects, runs with three different averages.  A larger count is stated last, for which the other order is right."""
+    import torch
+    det = zoo.traffic_cascade(dtype).models[0]
+    det.batch_size = 4
+    B = zoo._Builder("child", dtype, 32, 32, "classifier", np.random.default_rng(19))
+    a = B.conv(0, cin, 3, 2, act=zoo.ACT_RELU)
+    a = B.conv(a, cout, 1, 1, act=zoo.ACT_NONE, **(dict(res=B.conv(a, cout, 3, 1), res_mode=zoo.RES_BEFORE_ACT) if res else {}))
+    at = len(B.m.layers)
+    B.m.outputs = [B.fc(B.gap(a), 10)]
+    B.m.batch_size = 400
+    spec = zoo.PipelineSpec("items", [det, B.m], [zoo.Edge(0, 1)], 1000.0, 540, 960, 4, 100)
+    rng = np.random.default_rng(zoo.SEED0 + 92)
+    scene = synth.make_scene(rng, 4, 540, 960, [9, 120, 120, 120], 16, 200, log_uniform=True)
+    heads = synth.planted_heads(rng, det, scene, 540, 960, octo.letterbox_geometry(540, 960, det.in_h, det.in_w))
+    frames = [torch.from_numpy(f).cuda() for f in scene.frames]
+    P = octo.Pipeline(spec, keep_all_tensors=1)
+    for l, v in enumerate(heads):
+        P.set_head(0, l, octo.to_device(v, dtype))
+    kernels = []
+    for expected in (8, 400):
+        P.set_expected_items(1, expected)
+        first = None
+        for n in (1, 1, 1, 4, 4, 4, 1):
+            P.submit(frames[:n])
+            P.run()
+            P.collect()
+            assert len(P.get_rois(0)) > (4 if n == 1 else 200)
+            got = P.get_tensor(1, at, 5)
+            first = got if first is None else first
+            assert np.array_equal(got, first), (expected, n, P.layer_info(1)[1])
+        kernels.append(int(P.layer_info(1)[1][at - 1]) // 100000000)
+    P.close()
+    assert kernels[1] != 16 and (kernels[0] == 16 or cout == 64), kernels
