@@ -237,11 +237,11 @@ hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipSt
     return hipErrorNotSupported;
   if (((a.Cin | a.x_ld | a.x_coff | a.Cout | a.y_ld | a.y_coff) & 7) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return hipErrorNotSupported;
   if (a.res && (((a.res_ld | a.res_coff) & 7) || ((uintptr_t)a.res & 15))) return hipErrorNotSupported;
-  if (flow_takes_1x1(a)) return hipErrorNotSupported;
   // Below the line lies the split-K kernel too, which sums in another order: as everywhere, that choice is made for a.n_split items where the
   // count is taken on the device, and not for the running one
   const long long hw = (long long)a.Ho * a.Wo, M = (a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * hw;
   const long long M_split = a.n_split > 0 ? (a.n_split < a.n ? a.n_split : a.n) * hw : M;
+  if (flow_takes_1x1(a, M_split)) return hipErrorNotSupported;
   // several channel tiles read the pixels several times and need more of them: with fewer than six blocks per compute unit the
   // general kernel's 64x64 tiles are faster (192 -> 192 on 14336 pixels 7.4 us, 8.9 here; 64 -> 256 on 10240: 6.1, 8.3)
   if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (a.Cout <= 64 ? 4LL : 6LL) * num_cu) return hipErrorNotSupported;

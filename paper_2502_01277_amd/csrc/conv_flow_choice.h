@@ -57,11 +57,22 @@ inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us, i
 // 246 us on the general kernel's plain 128x128 tiles, 191 here, 128 -> 255 on 64 x 80 x 80 112 : 82.  A single K step needs its channels in
 // one tile (64 -> 128, stride 2 on 4170 x 56 x 56 341 : 316).
 // 1x1 / stride-1 layers that the streaming kernel (conv1x1.hip) leaves to this one: whole K steps, two or more.  Streaming : here, us:
-// 128 -> 128 on 64 x 80 x 80 41 : 38, on 8 x 80 x 80 9.9 : 8.5, 128 -> 256 with residual on 16 x 40 x 40 11.6 : 10.5, 192 -> 192 on 32 x 80 x 80
-// 37.5 : 36.3, on 32 x 160 x 160 150 : 150.  Fewer or broken steps are faster there (96 -> 192 on 41 x 40 x 40 11.6 : 14.5, 64 -> 256 on
-// 16 x 32 x 32 8.0 and not possible here).  What adds a residual and writes a channel slice of a wider tensor stays there too: no
-// network here has such a layer, the tests of that kernel's edges do.
-inline bool flow_takes_1x1(const ConvArgs& a) { return a.Cin >= 128 && a.Cin % 64 == 0 && !(a.res && a.y_ld != a.Cout) && flow_fits(a); }
+// 128 -> 128 on 64 x 80 x 80 44.6 : 39, on 8 x 80 x 80 9.9 : 8.5, 192 -> 192 on 32 x 80 x 80 37.5 : 36.3, on 32 x 160 x 160 151 : 150.  Fewer or
+// broken steps are faster there (96 -> 192 on 41 x 40 x 40 11.6 : 14.5).
+// With a residual (requested a K step before the results here, a block of pixels ahead there) by the MB of all tensors together, streaming :
+// here.  Three steps: while they fit the memory-side cache (192 -> 192 37 16.3 : 10.1, 147 36.8 : 32.1, 295 66.7 : 67.6, 472 104 : 111; 192 -> 96
+// 197 41.5 : 35.7, 315 63.6 : 66.6), and with more channel tiles there, each of which reads the pixels, also beyond it (192 -> 256 360 92 : 91,
+// 192 -> 512 311 89 : 86, 996 282 : 259; 192 -> 384 492 125 : 130).  Two steps: the same up to 128 output channels (128 -> 128 197 37.9 : 35.8, 315
+// 64.8 : 71.4; 128 -> 64 210 36.3 : 32.9, 419 83 : 95), up to 64 MB with more (128 -> 192 33 10.5 : 9.3, 66 16.2 : 16.6, 419 93 : 99; 128 -> 256 41
+// 12.2 : 11.8, 82 19.7 : 21.0, 328 78 : 84; 128 -> 384 57 16.4 : 16.1, 115 26.9 : 28.2, 734 169 : 178), and with more than 384 beyond the cache
+// (128 -> 512 74 21.0 : 20.9, 147 33.9 : 36.0, 295 83 : 78, 944 263 : 231).  The same lines hold for a channel slice as the destination.
+inline bool flow_takes_1x1(const ConvArgs& a, long long M) {
+  if (a.Cin < 128 || a.Cin % 64 || !flow_fits(a)) return false;
+  if (!a.res) return true;
+  const double mb = 2e-6 * M * (a.Cin + 2.0 * a.Cout);
+  const bool two = a.Cin == 128;
+  return mb < (two && a.Cout > 128 ? 64.0 : 256.0) || (mb >= 256.0 && a.Cout > (two ? 384 : 192));
+}
 
 hipError_t launch_flow_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 hipError_t launch_flow_bf16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);

@@ -16,9 +16,10 @@ CASES = [
     (3, 107, 103, 96, 96, nn.ACT_SILU, nn.RES_NONE, 0, 0),             # 33063 pixels: 1033 blocks and 7 pixels
     (1, 181, 181, 24, 40, nn.ACT_RELU, nn.RES_AFTER_ACT, 8, 16),       # three vectors of K, 40 channels on a 64-channel tile
     (2, 131, 127, 16, 32, nn.ACT_NONE, nn.RES_NONE, 0, 0),             # the shortest reduction, 32-channel tile
-    (5, 40, 41, 128, 520, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 8),       # nine channel tiles, the last one of 8 channels
+    (5, 40, 41, 120, 520, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 8),       # nine channel tiles, the last one of 8 channels
     (9, 64, 33, 64, 256, nn.ACT_RELU, nn.RES_BEFORE_ACT, 64, 0),       # 128-channel tiles
-    (2, 160, 111, 192, 192, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 192),    # the longest reduction
+    (2, 160, 111, 184, 192, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 192),    # the longest reduction that is never the other kernel's
+    (9, 160, 163, 192, 192, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 192),    # the longest of all, whose tensors exceed the memory-side cache
 ]
 
 

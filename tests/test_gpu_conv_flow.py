@@ -43,10 +43,15 @@ FLAT = [
     (1, 2, 40003, 64, 256, 5, 2, nn.ACT_NONE, nn.RES_NONE, 8, 0, 121),
     (3, 1, 20003, 128, 192, 3, 2, nn.ACT_SILU, nn.RES_BEFORE_ACT, 0, 8, 121),
 ]
+# a residual, written into channel slices
+SLICES = [
+    (5, 40, 41, 128, 520, 1, 1, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 8, 120),
+    (2, 160, 111, 192, 192, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 192, 120),
+]
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("case", CASES + FLAT)
+@pytest.mark.parametrize("case", CASES + FLAT + SLICES)
 def test_flow_parity(octo, dtype, case):
     import torch
     n, h, w, cin, cout, k, stride, act, res_mode, xe, ye, want = case
