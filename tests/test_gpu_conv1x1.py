@@ -68,11 +68,12 @@ def test_results_do_not_change_with_the_running_item_count(octo, dtype, cin, cou
     spec = zoo.PipelineSpec("items", [det, B.m], [zoo.Edge(0, 1)], 1000.0, 540, 960, 4, 100)
     rng = np.random.default_rng(zoo.SEED0 + 92)
     scene = synth.make_scene(rng, 4, 540, 960, [9, 120, 120, 120], 16, 200, log_uniform=True)
-    heads = synth.planted_heads(rng, det, scene, 540, 960, octo.letterbox_geometry(540, 960, det.in_h, det.in_w))
+    planted = synth.planted_heads(rng, det, scene, 540, 960, octo.letterbox_geometry(540, 960, det.in_h, det.in_w))
+    heads = [octo.to_device(v, dtype) for v in planted]
     frames = [torch.from_numpy(f).cuda() for f in scene.frames]
     P = octo.Pipeline(spec, keep_all_tensors=1)
     for l, v in enumerate(heads):
-        P.set_head(0, l, octo.to_device(v, dtype))
+        P.set_head(0, l, v)
     kernels = []
     for expected in (8, 400):
         P.set_expected_items(1, expected)

@@ -8,7 +8,7 @@ import pytest
 from oracle import nn
 from oracle.rounding import round_storage
 from paper_2502_01277_amd import synth, zoo
-from helpers import TOL, rel_err
+from helpers import TOL, rel_err, small_root
 
 pytestmark = pytest.mark.gpu
 
@@ -43,6 +43,12 @@ FLAT = [
     (1, 2, 40003, 64, 256, 5, 2, nn.ACT_NONE, nn.RES_NONE, 8, 0, 121),
     (3, 1, 20003, 128, 192, 3, 2, nn.ACT_SILU, nn.RES_BEFORE_ACT, 0, 8, 121),
 ]
+# maps smaller than the window, a tile over hundreds of images
+TINY = [
+    (40000, 2, 2, 64, 128, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 121),
+    (9000, 3, 4, 128, 96, 3, 2, nn.ACT_SILU, nn.RES_NONE, 0, 8, 121),
+    (6000, 4, 3, 72, 200, 2, 2, nn.ACT_RELU, nn.RES_AFTER_ACT, 0, 0, 122),
+]
 # a residual, written into channel slices
 SLICES = [
     (5, 40, 41, 128, 520, 1, 1, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 8, 120),
@@ -51,7 +57,7 @@ SLICES = [
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("case", CASES + FLAT + SLICES)
+@pytest.mark.parametrize("case", CASES + FLAT + TINY + SLICES)
 def test_flow_parity(octo, dtype, case):
     import torch
     n, h, w, cin, cout, k, stride, act, res_mode, xe, ye, want = case
@@ -127,3 +133,80 @@ def test_flow_fp8(octo, n, h, w, cin, cout, k, stride, res, xe, ye, mode):
     diff = (code(dy[..., :cout].cpu().contiguous().view(torch.float8_e4m3fn)) - code(want)).abs()
     assert int(diff.max()) <= 1 and float((diff > 0).float().mean()) < 0.01, (int(diff.max()), float((diff > 0).float().mean()))
     assert bool((dy[..., cout:] == 0x55).all())
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("case", [
+    (40, 41, 256, 96, 128, 9),         # the second layer begins inside a channel tile, whatever its width, and ends inside one
+    (40, 40, 128, 32, 64, 20),         # at the first block of 32 channels
+    (20, 20, 520, 160, 352, 16),       # a reduction that ends inside a step
+])
+def test_two_layers_in_one_flowing_launch(octo, dtype, case):
+    """Two 1x1 layers of one input, computed by one launch that writes each to a tensor of its own: both against the oracle and, bit for
+    bit, against the launches of their own."""
+    h, w, cin, c1, c2, n = case
+    B = zoo._Builder("t", dtype, h, w, "classifier", np.random.default_rng(63))
+    B.ch = [16]
+    B.m.in_c = 16
+    x = B.conv(0, cin, 1, 1, act=zoo.ACT_SILU)
+    a, b = B.conv(x, c1, 1, 1, act=zoo.ACT_SILU), B.conv(x, c2, 1, 1, act=zoo.ACT_SILU)
+    B.m.outputs = [B.fc(B.gap(B.cat([B.conv(a, c1, 1, 1), b])), 10)]
+    B.m.batch_size = n
+    v = zoo.round_to_dtype(np.random.default_rng(64).uniform(-1, 1, (n, h, w, 16)).astype(np.float32), dtype)
+    got, kids = {}, {}
+    for keep in (1, 2):
+        P = octo.Pipeline(zoo.PipelineSpec("t", [small_root(dtype), B.m], [], 200.0, 32, 32, 1, 1), keep_all_tensors=keep)
+        P.run_model_on(1, octo.to_device(v, dtype))
+        got[keep], kids[keep] = [P.get_tensor(1, t, n) for t in (a, b)], [int(k) for k in P.layer_info(1)[1]][1:3]
+        P.close()
+    assert kids[2][0] // 100000000 == 12 and kids[2][1] == 0, kids
+    ref = nn.run_model(B.m, v, keep_all=True)
+    for j, t in enumerate((a, b)):
+        assert rel_err(got[2][j], ref[t]) <= TOL[dtype], t
+        assert np.array_equal(got[2][j], got[1][j]), t
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_flow_with_the_item_count_on_the_device(octo, dtype):
+    """1x1 and strided layers of a downstream model: the grid is sized for 480 items, and batches bring hundreds, a few dozen and one of
+    them, so that some or nearly all workgroups find no tile.  Every tensor of some ROIs against the oracle on the GPU's own crops; what
+    the larger batch left beyond the smaller one's items is untouched."""
+    import torch
+    det = zoo.traffic_cascade(dtype).models[0]
+    det.batch_size = 4
+    B = zoo._Builder("child", dtype, 56, 56, "classifier", np.random.default_rng(65))
+    a = B.conv(0, 64, 3, 2, act=zoo.ACT_RELU)
+    b = B.conv(B.conv(a, 128, 3, 2, act=zoo.ACT_SILU), 256, 1, 1, act=zoo.ACT_RELU)      # a tap per step; nothing but channels
+    c = B.conv(b, 104, 1, 1, act=zoo.ACT_SILU)
+    d = B.conv(c, 192, 3, 2, act=zoo.ACT_RELU)                                           # steps across taps
+    B.m.outputs = [B.fc(B.gap(d), 10)]
+    B.m.batch_size = 480
+    spec = zoo.PipelineSpec("items", [det, B.m], [zoo.Edge(0, 1)], 1000.0, 540, 960, 4, 120)
+    rng = np.random.default_rng(zoo.SEED0 + 93)
+    geo = octo.letterbox_geometry(540, 960, det.in_h, det.in_w)
+    scenes = [synth.make_scene(rng, 4, 540, 960, counts, 16, 200, log_uniform=True) for counts in ([120] * 4, [5, 0, 17, 9], [0, 1, 0, 0])]
+    n_t = len(B.m.layers)
+    P = octo.Pipeline(spec, keep_all_tensors=1)
+    P.set_expected_items(1, 480)                         # none of these layers is split, whatever the batch brings
+    before, modes = None, set()
+    for k, sc in enumerate(scenes):
+        heads = [octo.to_device(v, dtype) for v in synth.planted_heads(rng, det, sc, 540, 960, geo)]
+        for l, v in enumerate(heads):
+            P.set_head(0, l, v)
+        P.submit([torch.from_numpy(f).cuda() for f in sc.frames])
+        P.run()
+        P.collect()
+        n = len(P.get_rois(0))
+        assert (n > 200, 20 < n < 60, 1 <= n < 5)[k], n
+        at = sorted({0, n // 2, n - 1})
+        got = [np.concatenate([P.get_tensor(1, t, 1, first=i) for i in at]) for t in range(n_t + 1)]
+        beyond = [np.concatenate([P.get_tensor(1, t, 1, first=i) for i in (60, 120, 199)]) for t in range(n_t + 1)]
+        ref = nn.run_model(B.m, got[0], keep_all=True)
+        for t in range(1, n_t + 1):
+            assert rel_err(got[t].reshape(ref[t].shape), ref[t]) <= TOL[dtype], (k, t)
+            if before is not None:
+                assert np.array_equal(beyond[t], before[t]), (k, t)
+        before = beyond
+        modes |= {int(v) // 10000000 for v in P.layer_info(1)[1]}
+    P.close()
+    assert {120, 121, 122} <= modes, modes
