@@ -66,7 +66,8 @@ STREAM3 = {(1, 2): (4, 6, 3, 2), (2, 2): (4, 3, 3, 3), (2, 3): (8, 6, 4, 2), (2,
 
 def conv_name(kid: int, dtype: str) -> str:
     """Template instance behind a conv kernel id (csrc/kernel_ids.h), as rocprofv3 prints it; an id that is none of the library's is
-    named as such."""
+    named as such.  A first layer with its max-pool that ends in SiLU or in a part of a vector has the id of the plain form, which is
+    named, and runs as stem_pool_any_kernel; no workload here has one."""
     d = kid - 1000000000
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
     if 200000000 <= d < 300000000:                       # general form whose loads run across tiles: digits M BBB PPP K

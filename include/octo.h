@@ -395,7 +395,8 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
  * duration, from events attached to its dispatch; other layers: end of layer i-1 to end of layer i on the stream,
  * which includes the launch gap), kernel_id[i] = which kernel ran it (general convolution: decimal digits
  * 1 BBB PPP K M V = channel tile, pixel tile, 16-byte vectors per K step, workgroups per CU, V = vectorised gather
- * + 2 if operands go straight to LDS, + 4 in the pipelined form; 15 00 BBB KKK: streaming 1x1 kernel, channel tile BBB, KKK input
+ * + 2 if operands go straight to LDS, + 4 in the pipelined form; 12 M BBB PPP K: the form whose loads run across tiles, how
+ * addresses are made, channel tile, pixel tile, 16-byte vectors per K step; 15 00 BBB KKK: streaming 1x1 kernel, channel tile BBB, KKK input
  * channels; 160S BBB PPP: split-K kernel, K split over S wavefronts, channel tile BBB, pixel tile PPP; 14, 17 or 18
  * 0Q BBB CCC: 3x3 kernel with the input patch in LDS (17: more than 64 output channels, 18: up to 64, 14: input channels
  * not in whole slices), Q = 0 / 1 / 2 / 3 for tiles of 128 / 256 / 64 / 128 pixels, channel tile BBB, patch of CCC channels in LDS

@@ -549,9 +549,12 @@ static hipError_t launch_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* 
 // traffic - whose channel count the 128-channel tile would pad (192 = 3 x 64): 192 -> 192 on 32 x 160 x 160 runs 11 %
 // faster than on 64x128 tiles; beyond K = 384 the larger K step wins.
 // k_scale: values per 2 bytes of K (2 for 8-bit storage, whose reductions are half as long in bytes).
-// 16-bit layers also have three shapes of the pipelined form, whose deeper ring leaves room for two workgroups per compute unit (three
-// with 64x64): 128x64 (64x128 where 128 channels would pad) where their tiles fill one round of those and not more - 128 -> 256,
-// stride 2 on 8 x 80 x 80 15.6 us (128x128: 19.6), 1024 -> 512 on 60 x 16 x 8 14.7 (18.2); one tile more than a round and the
+// 16-bit layers also have shapes of the pipelined form, whose deeper ring leaves room for two workgroups per compute unit (three
+// with 64x64).  Aligned layers reach one of them only, 64x64 (launch_typed says when; conv_flow_kernel has the rest); the others serve
+// pixel-pair first layers that the first-layer kernel declines, two layers whose split lies inside a block of 32 channels,
+// outputs and residuals that are no whole 16-byte vectors, fp32 outputs and single K steps into more than 256 channels, and their
+// lines were drawn by the aligned layers below, which they took before that kernel: 128x64 (64x128 where 128 channels would pad)
+// where their tiles fill one round of those and not more - 128 -> 256, stride 2 on 8 x 80 x 80 15.6 us (128x128: 19.6), 1024 -> 512 on 60 x 16 x 8 14.7 (18.2); one tile more than a round and the
 // others win again -, 64x64 in the same way for fewer pixels and a reduction of at least 1 KB (256 -> 512, stride 2 on
 // 63 x 14 x 14 16.4 us, split-K 18.2; where 64x128 would do too, up to 1.3 of those per compute unit, beyond which the three
 // per unit that 64x64 tiles fit run out: 192 -> 192, stride 2 on 56 x 56, 64x64 : 64x128 at 1.08 17.0 : 17.1, at 1.29 17.7 : 17.6, at
@@ -597,8 +600,10 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
     if (em != hipErrorNotSupported) return em;
   }
-  // Only the split-K kernel writes an upsampled copy.  Where it is worth that, the same layer on its own takes it too (8 x 20 x 20, 512 -> 256:
-  // 6.5 us estimated, 6.4 for the best other one), so that fused and separate launches sum in one order.
+  // Only the split-K kernel writes an upsampled copy.  Where its estimate is below that of the general kernel's tile one launch beats
+  // conv_flow_kernel and a launch for the upsampling at every size tried (us: 512 -> 256 on 20 x 20, 1 image 5.2 : 7.4, 8 8.4 : 9.4, 12
+  // 9.7 : 11.2; 256 -> 128 on 40 x 40, 2 images 5.8 : 7.5; 384 -> 192 on 40 x 40 5.9 : 7.6; 768 -> 384 on 20 x 20, 8 images 11.1 : 12.5); the next
+  // larger batches are left to those two.  The same layer on its own takes it too, so that fused and separate launches sum in one order.
   if (sizeof(T) == 2 && (a.up_y || a.up_next)) {
     const GeneralTile st = general_tile(a, M_split, num_cu, 1, false);
     const int ks = ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
@@ -746,7 +751,8 @@ hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s,
   ConvArgs a = a0;
   if (!conv_prepare(a, dtype)) return hipErrorInvalidValue;
   if (a.split > 0) {
-    // two layers in one launch: the streaming 1x1 kernel, the split-K kernel and the general kernel's staged epilogue write two tensors
+    // two layers in one launch: the streaming 1x1 kernel, conv_flow_kernel (a split in whole blocks of 32 channels), the split-K kernel and
+    // the general kernel's staged epilogue write two tensors
     const bool ok = (dtype == OCTO_F16 || dtype == OCTO_BF16) && a.y2 && !a.res && !a.out_f32 && !a.pair_view && !a.pool_y && a.split < a.Cout &&
                     ((a.split | a.Cout | a.y_ld | a.y_coff | a.y2_ld | a.y2_coff) & 7) == 0 && ((((uintptr_t)a.y | (uintptr_t)a.y2) & 15) == 0);
     if (!ok) return hipErrorNotSupported;

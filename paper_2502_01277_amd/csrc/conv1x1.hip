@@ -225,9 +225,9 @@ static hipError_t launch_stream_typed(const ConvArgs& a, long long M, int num_cu
 }
 
 // 1x1 / stride-1 layers in the 16-bit types with at most 192 input channels and a block of pixels for every other
-// wavefront of the chip; hipErrorNotSupported otherwise.  Longer reductions have work enough per byte for the general
-// kernel's larger tiles (256 channels: even; 384 -> 192 on 80 x 80: 63 us there, 95 here), and so have channel counts that
-// are no multiple of 8 (their last vectors would be written element by element).  The sums are those of the general kernel.
+// wavefront of the chip; hipErrorNotSupported otherwise.  Longer reductions have work enough per byte for the larger tiles of
+// conv_flow_kernel (flow_takes_1x1 has the line; 384 -> 192 on 80 x 80 took 63 us on the general kernel and 95 here), and channel counts
+// that are no multiple of 8 would have their last vectors written element by element.  The sums are those of both other kernels.
 // Bound by memory.  Measured, bf16, with stores of 32 consecutive bytes per pixel and a contiguous piece of the tensor for every die, and
 // now: 96 -> 96 on 32 x 160 x 160 84 -> 68 us (4.6 TB/s; a copy of that size does 5.3), on 32 x 320 x 320 300 -> 249 (5.0); 64 -> 64 on
 // 64 x 160 x 160 103 -> 81; 64 -> 256 with residual on 119 x 64 x 32 74 -> 57.  A second block per wavefront in flight gave nothing.
@@ -242,8 +242,11 @@ hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipSt
   const long long hw = (long long)a.Ho * a.Wo, M = (a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * hw;
   const long long M_split = a.n_split > 0 ? (a.n_split < a.n ? a.n_split : a.n) * hw : M;
   if (flow_takes_1x1(a, M_split)) return hipErrorNotSupported;
-  // several channel tiles read the pixels several times and need more of them: with fewer than six blocks per compute unit the
-  // general kernel's 64x64 tiles are faster (192 -> 192 on 14336 pixels 7.4 us, 8.9 here; 64 -> 256 on 10240: 6.1, 8.3)
+  // Several channel tiles read the pixels several times and need more of them.  Here : conv_flow_kernel (32 channels: general), us, by blocks
+  // times channel tiles of 64 per compute unit: 16 -> 32 at 3 3.9 : 4.6; 32 -> 64 at 2 4.8 : 4.5, at 3 4.9 : 5.5, at 4 5.1 : 6.1; 96 -> 64 at 3
+  // 5.7 : 5.8, at 4 5.9 : 6.6; 32 -> 96 at 4 5.6 : 5.1, at 5 5.6 : 6.0; 96 -> 192 at 5 6.9 : 6.7, at 6 7.1 : 6.9, at 7 7.2 : 7.5; 120 -> 128 at 4 6.2 : 5.7,
+  // at 5 6.5 : 6.8.  64 input channels, a whole K step there, turn later: 64 -> 64 at 8 6.2 : 5.8, at 12 7.9 : 8.3; 64 -> 128 at 6 5.8 : 5.6, at 12 7.9 :
+  // 8.0; 64 -> 256 at 6 8.0 : 7.1, at 16 11.6 : 11.9.
   if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (a.Cout <= 64 ? 4LL : 6LL) * num_cu) return hipErrorNotSupported;
   return dtype == OCTO_F16 ? launch_stream_typed<_Float16>(a, M, num_cu, s, kernel_id, tm) : launch_stream_typed<__bf16>(a, M, num_cu, s, kernel_id, tm);
 }

@@ -406,7 +406,7 @@ static hipError_t launch_flow_cfg(const ConvArgs& a, int num_cu, hipStream_t s, 
   constexpr int BK = KV * Elem<T>::N;
   // The bias of a tile is requested at the last step of the one before: its place must be free (a barrier since the epilogue before),
   // and it must have landed by the epilogue (older than the operands of step NST - 2).  With a single step there must be one channel tile.
-  static_assert(KV == 8 && NST <= 4, "two K steps suffice: a.K > BK");
+  static_assert(KV == 8 && NST <= 4, "two K steps suffice, or one with one channel tile");
   if (a.K <= BK && a.Cout > BC) return hipErrorNotSupported;
   const long long M = (long long)a.n * a.Ho * a.Wo, tiles_c = (a.Cout + BC - 1) / BC, tiles = (M + BP - 1) / BP * tiles_c;
   if (tiles <= 0) return hipSuccess;

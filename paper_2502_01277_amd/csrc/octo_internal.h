@@ -45,7 +45,7 @@ struct ConvArgs {
   void* pool_y;
   int pool_ho, pool_wo, pool_ld, pool_coff;
   int stem_seg;                   // output rows per segment of a strip (set by launch_stem)
-  // Two layers in one launch (general, split-K and streaming 1x1 kernels, 16-bit types, no residual): output channels below `split` go to y as
+  // Two layers in one launch (general, flowing, split-K and streaming 1x1 kernels, 16-bit types, no residual): output channels below `split` go to y as
   // usual, channels split .. Cout - 1 to y2 as its channels 0 ..; split is a multiple of 8 and 0 when unused.
   void* y2;
   int y2_ld, y2_coff, split;

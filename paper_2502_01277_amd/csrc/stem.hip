@@ -20,7 +20,8 @@
 //     ring then stores the even and the odd pixel pairs of a row apart: either way an operand read is 32 consecutive vectors.
 // Bound by the matrix pipe with the pool (28 vectors of 8 products, of which 147 are real), without it by memory and SiLU.
 // Measured against tiles staged in LDS, us: 7x7 with the pool, bf16, 4170 crops of 224 x 224 2146 -> 1300, some 380 crops 232 -> 148, some 6
-// crops 23 -> 18; 6x6 on 32 frames of 1280 x 1280 to 64 channels 496 -> 434, on 64 of 640 x 640 to 32 channels 170 -> 127 (5 TB/s).
+// crops 23 -> 18, on 224 x 224 with SiLU (stem_pool_any_kernel) 8 crops 19.5 -> 18.5, 380 283 -> 249, 2000 1438 -> 1105, 36 channels with ReLU
+// (the same) 17.1 -> 14.4, 237 -> 163, 1190 -> 800; 6x6 on 32 frames of 1280 x 1280 to 64 channels 496 -> 434, on 64 of 640 x 640 to 32 channels 170 -> 127 (5 TB/s).
 #include "mfma_common.h"
 #include "stem_segment.h"
 #include <hip/hip_ext.h>
