@@ -103,54 +103,54 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "bd58fb1f55b260dc": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4365021734,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1701780210,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283041468,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344656772,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1482962841,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553399159,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 848349985,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355635207,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282191966,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2205215926,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 991088695,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910906934,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629445948,
-        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255825719,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078968943,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167930037,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 627742106,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 127872954,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838666,
-        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69133341,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856321,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28734870,
-        "octo::conv1x1_stream_kernel<_Float16, 2>": 29073144,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064020,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727905,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942834,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87660246,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28524710,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77784270,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64446254,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21159167,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31500846,
-        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369348,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873086,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40069931,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39784767,
-        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19103904,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136847,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510189,
-        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376753,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355739,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644818,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223608,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253453,
-        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730475,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39505689,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18699662,
+    "14d56313a6cb2f0c": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4368196494,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1700410848,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283087895,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344684480,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1483328727,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553384375,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 850076891,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355622832,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281956092,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2205559289,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 993599491,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1911041791,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629432716,
+        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255826470,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1080664148,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167938870,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628534044,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 127803976,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838936,
+        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69134432,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856340,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28733948,
+        "octo::conv1x1_stream_kernel<_Float16, 2>": 29071916,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064036,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727913,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942841,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87615897,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28526532,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77745138,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64520875,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21159503,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31501762,
+        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369370,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873137,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40072658,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39777863,
+        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19105781,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136851,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510200,
+        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376766,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355741,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644826,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223610,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253458,
+        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730478,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506823,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18699675,
     },
 }
 
