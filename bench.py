@@ -60,6 +60,8 @@ MID = {(0, 32, 4): (1, 3, 3, 4), (0, 64, 4): (1, 3, 3, 4), (0, 64, 8): (1, 3, 6,
 # Tiles of the general form whose loads run across tiles: lanes, wavefronts along the channels, workgroups per compute unit.
 FLOW = {(64, 64): (256, 2, 3), (64, 128): (256, 1, 2), (128, 64): (256, 2, 2), (128, 128): (512, 2, 1), (96, 256): (512, 1, 1), (192, 128): (512, 2, 1),
         (128, 256): (512, 2, 1), (256, 128): (512, 4, 1)}
+# Tiles for launches of few tiles: wavefronts along the pixels, workgroups per compute unit.
+SMALL = {(32, 32): (2, 4), (32, 64): (4, 4), (64, 32): (2, 4), (64, 64): (2, 3), (128, 64): (2, 2)}
 # By (blocks of 32 channels, groups of 16 input channels): vectors per LDS row, loader passes, prefetch depth, workgroups per compute unit.
 STREAM3 = {(1, 2): (4, 6, 3, 2), (2, 2): (4, 3, 3, 3), (2, 3): (8, 6, 4, 2), (2, 4): (8, 6, 3, 2)}
 
@@ -73,6 +75,9 @@ def conv_name(kid: int, dtype: str) -> str:
     if 200000000 <= d < 300000000:                       # general form whose loads run across tiles: digits M BBB PPP K
         mode, bc, bp, kv = (d - 200000000) // 10000000, d // 10000 % 1000, d // 10 % 1000, d % 10
         return "octo::conv_flow_kernel<%s, %d, %d, %d, %d, %d, 3, %d, %d>" % ((ctype, FLOW[(bc, bp)][0], bc, bp, FLOW[(bc, bp)][1], kv, FLOW[(bc, bp)][2], mode)) if (bc, bp) in FLOW else "convolution kernel %d" % kid
+    if 300000000 <= d < 400000000:                       # launches of few tiles: digits M BBB PPP W
+        mode, bc, bp, wc = (d - 300000000) // 10000000, d // 10000 % 1000, d // 10 % 1000, d % 10
+        return "octo::conv_small_kernel<%s, %d, %d, %d, %d, %d, %d>" % ((ctype, bc, bp, wc) + SMALL[(bc, bp)] + (mode,)) if (bc, bp) in SMALL else "convolution kernel %d" % kid
     if 500000000 <= d < 600000000:                       # streaming 1x1 kernel
         return "octo::conv1x1_stream_kernel<%s, %d>" % (ctype, (d - 500000000) // 1000 // 32)
     if 600000000 <= d < 700000000:                       # split-K kernel
@@ -162,7 +167,7 @@ TRAFFIC_SOURCE = "profiles/*_hbm_counters.md: rocprofv3 --pmc FETCH_SIZE and --p
 def conv_sources_key() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv.hip", "conv_flow.h", "conv_flow_choice.h", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "conv3x3_stream.h", "stem.hip", "stem_segment.h", "mfma_common.h"):
+    for f in ("conv.hip", "conv_flow.h", "conv_flow_choice.h", "conv_small.h", "conv_small_choice.h", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "conv3x3_stream.h", "stem.hip", "stem_segment.h", "mfma_common.h"):
         try:
             h.update(open(os.path.join(ROOT, "paper_2502_01277_amd", "csrc", f), "rb").read())
         except OSError:

@@ -27,6 +27,7 @@
 #include "conv_ksplit.h"
 #include "conv3x3_mid.h"
 #include "conv_flow_choice.h"
+#include "conv_small_choice.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -596,9 +597,42 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   // That kernel sums in another order, so the choice is made for a.n_split items where the count is taken on the device:
   // unlike the running average behind n_hint it stays the same from batch to batch, and so do the results.
   const long long M_split = a.n_split > 0 ? (long long)(a.n_split < a.n ? a.n_split : a.n) * a.Ho * a.Wo : M;
+  // Launches of few tiles go to conv_small_kernel, or to split-K where that is estimated to be faster; both lines are drawn in conv_small_choice.h.
+  // conv_flow_kernel and the general kernel sum in the order of conv_small_kernel, so that the running count may choose between those (not where
+  // a last vector has less than eight channels, whose values they convert one by one); against split-K and the patch kernel it is M_split.
+  bool to_small = false, not_split = false;
+  [[maybe_unused]] const long long M_small = a.Cout % 8 || a.Cout <= 32 ? M_split : M;
+  [[maybe_unused]] auto run_small = [&](long long m) -> hipError_t {
+    double us = 0;
+    const int which = small_choose(a, m, num_cu, 2, &us);
+    return std::is_same<T, __bf16>::value ? launch_small_bf16(which, a, num_cu, s, kernel_id, tm) : launch_small_f16(which, a, num_cu, s, kernel_id, tm);
+  };
+  [[maybe_unused]] const bool pipe_ok = sizeof(T) == 2, pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
+  // strided layers for the general kernel's pipelined 64x64 tiles, see below
+  [[maybe_unused]] auto stays = [&](long long m) {
+    const GeneralTile t = general_tile(a, m, num_cu, 1, pipe_ok);
+    return !pw && t.pipe && t.bc == 64 && t.bp == 64 && (m + 63) / 64 * ((a.Cout + 63) / 64) <= 2LL * num_cu;
+  };
   if constexpr (sizeof(T) == 2) {
-    const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
-    if (em != hipErrorNotSupported) return em;
+    const bool fits = small_fits(a, 2), patch = fits && small_takes_3x3(a, M_split, num_cu);
+    if (!patch) {
+      const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
+      if (em != hipErrorNotSupported) return em;
+    }
+    // (up to 32 channels only where the count is not taken on the device; not before an upsampling, which the split-K kernel writes along)
+    if (patch || (fits && !a.up_next && (a.Cout > 32 || a.n_split == 0) && small_takes(a, M_split, num_cu))) {
+      // Split-K has to beat every other kernel: below the patch kernel's line, never where the general kernel's pipelined tiles would fill a
+      // round, and conv_flow_kernel's estimate (96 -> 192, stride 2 on 9 x 57 x 83: split-K 14.1, estimated 12.1, conv_flow_kernel 13.3)
+      double us = 0, uf = 0;
+      small_choose(a, M_split, num_cu, 2, &us);
+      if (!patch && flow_fits(a)) { flow_choose(a, M_split, num_cu, &uf); us = std::min(us, uf); }
+      const bool few = patch ? (double)M_split / 128 * ((a.Cout + 63) / 64) < 0.25 * num_cu : !stays(M_split);
+      const int kf = few ? ksplit_best(a, M_split, 2, num_cu, us, pw ? 3 : 4, 4.0) : -1;
+      if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
+      if (patch) return run_small(M_split);
+      not_split = true;
+    }
+    to_small = fits && (not_split || a.Cout > 32) && small_takes(a, M_small, num_cu);
   }
   // Only the split-K kernel writes an upsampled copy.  Where its estimate is below that of the general kernel's tile one launch beats
   // conv_flow_kernel and a launch for the upsampling at every size tried (us: 512 -> 256 on 20 x 20, 1 image 5.2 : 7.4, 8 8.4 : 9.4, 12
@@ -610,7 +644,6 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
   }
   if (a.up_y) return hipErrorNotSupported;
-  const bool pipe_ok = sizeof(T) == 2;
   if constexpr (sizeof(T) == 2) {
     // conv_flow_kernel takes what has its form, except strided layers of up to two pipelined 64x64 tiles per compute unit: 256 -> 512,
     // stride 2 on 42 x 14 x 14 16.1 us here, 18.1 there, 128 -> 128, stride 2 on 8 x 80 x 80 10.5 : 11.1 (a step of such a tile is four matrix
@@ -619,14 +652,9 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     // 2.05 18.0 : 17.2.  Their order of summation is the same, so the running count may choose between those two; split-K or not is
     // decided for M_split.
     if (flow_fits(a)) {
-      const bool pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
-      auto stays = [&](long long m) {
-        const GeneralTile t = general_tile(a, m, num_cu, 1, pipe_ok);
-        return !pw && t.pipe && t.bc == 64 && t.bp == 64 && (m + 63) / 64 * ((a.Cout + 63) / 64) <= 2LL * num_cu;
-      };
       double us = 0;
       int kf = -1;
-      if (!stays(M_split)) {
+      if (!not_split && !stays(M_split)) {
         flow_choose(a, M_split, num_cu, &us);
         // Against this kernel split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
         // on 7 x 40 x 40 at 4.1 38.0 : 28.0, 512 -> 64 1x1 on 82 x 20 x 20 at 4.0 11.1 : 8.2).  Its 64 x 64 tiles serve long reductions (256 -> 256,
@@ -635,16 +663,18 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
         kf = ksplit_best(a, M_split, 2, num_cu, pw ? 0.85 * us : us, pw ? 3 : 4, 4.0);
       }
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
+      if (to_small) return run_small(M_small);
       if (stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
       const int which = flow_choose(a, M, num_cu, &us);
       return std::is_same<T, __bf16>::value ? launch_flow_bf16(which, a, num_cu, s, kernel_id, tm) : launch_flow_f16(which, a, num_cu, s, kernel_id, tm);
     }
   }
   const GeneralTile st = general_tile(a, M_split, num_cu, 1, pipe_ok);
-  const int ks = st.pipe ? -1 : ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
+  const int ks = not_split || st.pipe ? -1 : ksplit_choose(a, M_split, (int)sizeof(T), st.bc, st.bp, num_cu);
   if (ks >= 0) return launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm);
   const GeneralTile t = general_tile(a, M, num_cu, 1, pipe_ok);
   if constexpr (sizeof(T) == 2) {
+    if (to_small) return run_small(M_small);
     if (t.pipe && t.bp == 256) return launch_cfg<T, 128, 256, 2, 2, 4, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);
     if (t.pipe && t.bc == 128) return launch_cfg<T, 128, 64, 2, 2, 8, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);
     if (t.pipe && t.bp == 128) return launch_cfg<T, 64, 128, 2, 2, 8, 2, 2, true, true, true>(a, num_cu, s, kernel_id, tm);

@@ -245,9 +245,9 @@ hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipSt
   // Several channel tiles read the pixels several times and need more of them.  Here : conv_flow_kernel (32 channels: general), us, by blocks
   // times channel tiles of 64 per compute unit: 16 -> 32 at 3 3.9 : 4.6; 32 -> 64 at 2 4.8 : 4.5, at 3 4.9 : 5.5, at 4 5.1 : 6.1; 96 -> 64 at 3
   // 5.7 : 5.8, at 4 5.9 : 6.6; 32 -> 96 at 4 5.6 : 5.1, at 5 5.6 : 6.0; 96 -> 192 at 5 6.9 : 6.7, at 6 7.1 : 6.9, at 7 7.2 : 7.5; 120 -> 128 at 4 6.2 : 5.7,
-  // at 5 6.5 : 6.8.  64 input channels, a whole K step there, turn later: 64 -> 64 at 8 6.2 : 5.8, at 12 7.9 : 8.3; 64 -> 128 at 6 5.8 : 5.6, at 12 7.9 :
-  // 8.0; 64 -> 256 at 6 8.0 : 7.1, at 16 11.6 : 11.9.
-  if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (a.Cout <= 64 ? 4LL : 6LL) * num_cu) return hipErrorNotSupported;
+  // at 5 6.5 : 6.8.  64 input channels, a whole K step there, turn later; against conv_small_kernel: 64 -> 24 at 4.6 4.4 : 3.5, 64 -> 128 at 6.2
+  // 6.1 : 5.2, at 7.7 6.4 : 5.5, 64 -> 64 on 2 x 160 x 160 at 6.2 6.1 : 5.0, on five at 15.6 9.1 : 8.2, on eight 13.2 : 13.4.
+  if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (a.Cin == 64 ? 9LL : a.Cout <= 64 ? 4LL : 6LL) * num_cu) return hipErrorNotSupported;
   return dtype == OCTO_F16 ? launch_stream_typed<_Float16>(a, M, num_cu, s, kernel_id, tm) : launch_stream_typed<__bf16>(a, M, num_cu, s, kernel_id, tm);
 }
 

@@ -1,0 +1,94 @@
+// Which layers take conv_small_kernel (conv_small.h), and with which tile.  Host arithmetic only.
+#pragma once
+#include "octo_internal.h"
+#include <algorithm>
+
+namespace octo {
+
+// How addresses are made: 1x1, stride 1, no padding, whole K steps of channels; any other layer with whole K steps of channels per
+// tap; any layer (a lane works out the tap of its vector at every step).
+enum { SMALL_POINTWISE = 0, SMALL_TAPS = 1, SMALL_ANY = 2 };
+
+// Does a layer of values of ES bytes have the form that the kernel takes?
+inline bool small_fits(const ConvArgs& a, int ES) {
+  const int VN = 16 / ES;
+  if (a.out_f32 || a.pair_view || a.pool_y || a.up_y || a.kh > 15 || a.kw > 15 || a.stride_h != a.stride_w || a.pad_h != a.pad_w) return false;
+  if (a.Cout % VN && (a.res || a.split > 0 || a.kh > 1 || a.kw > 1 || a.stride_h > 1)) return false;      // a last vector in pieces: detector heads
+  if (((a.Cin | a.x_ld | a.x_coff | a.y_ld | a.y_coff) % VN) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return false;
+  if (a.res && (((a.res_ld | a.res_coff) % VN) || ((uintptr_t)a.res & 15))) return false;
+  if (a.x_ld * ES >= 1 << 24 || a.W * 16 >= 1 << 24) return false;      // factors of 24-bit products
+  // 32-bit offsets: weights, and the pixels of a tile (64 of them) in every tensor
+  const long long ld = std::max(std::max(a.x_ld, a.y_ld), std::max(a.res ? a.res_ld : 0, a.split > 0 ? a.y2_ld : 0));
+  return (long long)a.w_rows * a.Kp * ES < 0x7FFFFFFFLL && 256 * ld * ES < 0x7FFFFFF0LL && (long long)a.n * a.Ho * a.Wo < 0x7FFFFF00LL &&
+         (2LL * a.H * a.W + 1024LL * a.stride_h * a.stride_w + (long long)a.pad_h * a.W + a.pad_w) * a.x_ld * ES < 0x7FFFFFF0LL;
+}
+
+// Time of a launch in us from a graph, fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output channels, 1x1 and 3x3 of stride 1 and 2, with and
+// without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16, 256 compute units; residual error 4 - 7 %): a constant, what a
+// compute unit does - its tiles, half way between their mean and the next whole number, times K steps and an epilogue -, a latency per K
+// step and the memory traffic; with input channels in whole K steps, and not.  Over those layers the tile of the smallest estimate loses
+// 0.8 % against the fastest one.
+struct SmallCost { int bc, bp; double base, step, tile, latency, per_mb; };
+constexpr SmallCost SMALL_COST[2][5] = {
+    {{32, 32, 2.317, 0.071, 0.250, 0.054, 0.004},
+     {32, 64, 2.447, 0.114, 0.287, 0.037, 0.018},
+     {64, 32, 2.547, 0.115, 0.261, 0.026, 0.010},
+     {64, 64, 2.557, 0.167, 0.565, 0.033, 0.020},
+     {128, 64, 2.251, 0.300, 1.201, -0.031, 0.025}},
+    {{32, 32, 2.585, 0.072, 0.359, 0.101, -0.016},
+     {32, 64, 2.705, 0.121, 0.474, 0.091, -0.002},
+     {64, 32, 2.686, 0.105, 0.401, 0.100, 0.004},
+     {64, 64, 2.891, 0.167, 0.696, 0.066, 0.020},
+     {128, 64, 2.682, 0.273, 1.154, 0.022, 0.074}}};
+// The row of SMALL_COST with the smallest estimate for M output pixels.
+inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, double* us) {
+  int best = 0;
+  const double nk = (a.K + 128 / ES - 1) / (128 / ES);
+  const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
+  const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
+  for (int i = 0; i < 5; ++i) {
+    const SmallCost& c = SMALL_COST[a.Cin % (128 / ES) ? 1 : 0][i];
+    const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
+    double per_cu = 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu));
+    if (per_cu < 1.0) per_cu = 1.0;
+    const double t = c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk + c.per_mb * mb;
+    if (i == 0 || t < *us) { *us = t; best = i; }
+  }
+  return best;
+}
+
+// Up to how many tiles of 64 x 64 per compute unit the kernel is the faster one (us here : the kernel that took the layer before; both from a
+// graph).  M: output pixels.
+//   * windows (3x3, strides): 2.75; into one channel tile, or with steps across taps, 1.96: beyond, some unit has a third tile.  128 -> 256, stride 2 on 5 x 80 x 80 at 1.95 9.4 : 11.8, 256 -> 256 on 20 x 40 x 40 1.95 15.1 : 18.7, 192 -> 256 on 28 x 40 x 41 2.9 18.3 : 19.8,
+//     96 -> 192 on 9 x 57 x 83 at 2.0 12.3 : 12.1, 128 -> 64 on 82 x 40 x 40 at 2.0 13.8 : 15.2, 32 -> 64 on 8 x 320 x 320 at 12.5 24.2 : 24.4, on 64 207 : 188;
+//   * 1x1 layers in whole K steps: 3, one step 4.5.  1024 -> 512 on 7 x 28 x 29 at 2.8 11.6 : 12.4, 256 -> 255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on
+//     61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 192 on 4 x 80 x 82 at 4.8 6.5 : 7.5.  With channel tiles less than three
+//     quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x 39 at 1.76 4.8 : 5.3);
+//   * 1x1 layers that end inside a step: 2.75 up to eight steps (32 -> 256 on 80 x 81 at 1.6 4.6 : 9.3, 24 -> 256 on 142 x 8 x 10 at 2.8 5.6 : 8.1), 1.25 with
+//     more, whose every step has the taps to work out;
+//   * up to 32 output channels 3: 256 -> 32 on 38 x 28 x 28 at 1.8 3.9 : 6.8, 320 -> 32 on 4 x 112 x 113 at 3.1 6.4 : 9.5.
+inline double small_limit(const ConvArgs& a) {
+  const int nk = (a.K + 63) / 64;
+  if (a.Cout <= 32) return 3.0;
+  if (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h) return a.Cout <= 64 || a.Cin % 64 ? 1.96 : 2.75;
+  if (a.Cin % 64) return nk <= 8 ? 2.75 : 1.25;
+  if (nk == 1) return 4.5;
+  return a.Cout * 4 < (a.Cout + 63) / 64 * 64 * 3 ? 1.75 : 3.0;
+}
+inline bool small_takes(const ConvArgs& a, long long M, int num_cu) {
+  return (double)((M + 63) / 64 * ((a.Cout + 63) / 64)) <= small_limit(a) * num_cu;
+}
+// 3x3 layers of stride 1, against conv3x3_mid_kernel, which reads every pixel once for all nine taps: short reductions, up to 1.96 tiles of
+// 64 x 64 per compute unit.  64 -> 64 on 5 x 80 x 80 at 1.95 7.0 : 8.2, 64 -> 192 on 136 x 8 x 10 at 2.0 7.3 : 9.3, 128 -> 96 on 2 x 80 x 82 at 1.6 9.4 : 11.5, 128 -> 256
+// on 8 x 20 x 22 at 0.9 7.4 : 8.2, on 11 x 28 x 29 at 2.2 13.3 : 13.9; 160 -> 384 on 56 x 57 at 1.2 11.8 : 10.9, 256 -> 128 on 80 x 80 at 0.8 10.6 : 10.1.
+// Reductions that end inside a step from 128 channels on: 48 -> 384 on 13 x 20 x 22 at 2.1 8.3 : 10.4, 96 -> 256 on 4 x 40 x 42 at 1.6 9.2 : 9.1.
+inline bool small_takes_3x3(const ConvArgs& a, long long M, int num_cu) {
+  if (a.kh != 3 || a.kw != 3 || a.stride_h != 1 || a.stride_w != 1 || a.pad_h != 1 || a.pad_w != 1 || a.Cout <= 32) return false;
+  const int nk = (a.K + 63) / 64;
+  return (a.Cin % 64 ? nk <= 14 && a.Cout >= 128 : nk <= 18) && (double)((M + 63) / 64 * ((a.Cout + 63) / 64)) <= 1.96 * num_cu;
+}
+
+hipError_t launch_small_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
+hipError_t launch_small_bf16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
+
+}  // namespace octo

@@ -15,6 +15,9 @@ constexpr int conv_kernel_id(int bc, int bp, int kv, int minb, bool vec, bool dm
 // vectors per K step
 constexpr int flow_kernel_id(int bc, int bp, int kv, int mode) { return 1200000000 + mode * 10000000 + bc * 10000 + bp * 10 + kv; }
 
+// launches of few tiles (conv_small.h), digits 13 M BBB PPP W: how addresses are made, channel tile, pixel tile, wavefronts along the channels
+constexpr int small_kernel_id(int bc, int bp, int wc, int mode) { return 1300000000 + mode * 10000000 + bc * 10000 + bp * 10 + wc; }
+
 // 3x3 layers with the input patch in LDS (conv3x3_mid.h), digits FF Q BBB CCC: family (17: more than 64 output channels, 18: up to
 // 64, 14: input channels not in whole slices), pixel tile (0: 128, 1: 256, 2: 64, 3: 128 with a patch of five passes), channel
 // tile, input channels whose patch the two buffers hold.  vn: values per 16-byte vector

@@ -1,0 +1,94 @@
+"""The convolution kernel for launches of few tiles at its edges: one pixel, pixel and channel counts that are no multiple of a tile, every tile
+and kind of addresses, reductions of one step, of part of one and of many, windows over every border, residuals, channel slices of
+wider buffers, a last vector of less than eight channels; against the oracle's arithmetic."""
+import numpy as np
+import pytest
+
+import bench
+from oracle import nn
+from oracle.rounding import round_storage
+from paper_2502_01277_amd import synth, zoo
+from helpers import TOL, rel_err, small_root
+
+CASES = [
+    # (n, h, w, cin, cout, k, stride, act, res_mode, x_extra, y_extra, kernel id)
+    (1, 1, 1, 64, 40, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 0, 1300320322),                  # one pixel
+    (1, 20, 21, 256, 256, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 64, 8, 1300320322),        # 32 x 32 tiles, four pixels over
+    (3, 31, 33, 128, 136, 1, 1, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 1300320641),        # 32 x 64, 8 channels of the last tile
+    (5, 40, 41, 256, 255, 1, 1, nn.ACT_NONE, nn.RES_NONE, 0, 1, 1301280644),              # 128 x 64, 7 of the last 8 channels
+    (7, 57, 55, 64, 192, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 0, 130),                       # one K step, more tiles than workgroups
+    (2, 56, 57, 24, 256, 1, 1, nn.ACT_RELU, nn.RES_NONE, 8, 0, 132),                      # part of one K step
+    (1, 81, 80, 200, 40, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 1320640322),          # 64 x 32, 8 of the fourth step
+    (6, 28, 27, 256, 24, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 8, 1300320322),               # less than 32 channels
+    (5, 80, 79, 64, 64, 3, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 64, 1310640642),          # nine taps of one step
+    (2, 7, 9, 128, 264, 3, 1, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 131),
+    (8, 57, 83, 96, 192, 3, 2, nn.ACT_SILU, nn.RES_NONE, 0, 0, 132),                      # steps across taps
+    (1, 160, 161, 64, 128, 3, 2, nn.ACT_SILU, nn.RES_NONE, 8, 0, 131),
+    (3, 14, 15, 16, 200, 5, 1, nn.ACT_RELU, nn.RES_AFTER_ACT, 0, 0, 132),
+    (40, 3, 4, 64, 96, 2, 2, nn.ACT_NONE, nn.RES_NONE, 0, 0, 131),                        # a tile over several images
+    (1, 1, 401, 64, 256, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 131),                      # taps that no pixel can use
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("case", CASES)
+def test_small_launch_parity(octo, dtype, case):
+    import torch
+    n, h, w, cin, cout, k, stride, act, res_mode, xe, ye, want = case
+    pad = k // 2
+    rng = np.random.default_rng(83)
+    x = zoo.round_to_dtype(rng.uniform(-1, 1, (n, h, w, cin)).astype(np.float32), dtype)
+    wt = zoo.round_to_dtype((rng.standard_normal((cout, k, k, cin)) / np.sqrt(k * k * cin)).astype(np.float32), dtype)
+    bias = rng.uniform(-0.1, 0.1, cout).astype(np.float32)
+    layer = octo.ConvOp(synth.to_storage(wt, dtype), bias, dtype, stride, pad, act)
+    ho, wo = layer.out_hw(h, w)
+    res = zoo.round_to_dtype(rng.uniform(-1, 1, (n, ho, wo, cout)).astype(np.float32), dtype) if res_mode else None
+    y = nn.conv2d(x, wt, stride, pad) + bias
+    if res_mode == nn.RES_BEFORE_ACT:
+        y = nn.activation(y + res, act)
+    else:
+        y = nn.activation(y, act) + (res if res_mode else 0.0)
+    dx = torch.full((n, h, w, cin + xe), float("inf"), dtype=octo.torch_dtype(dtype), device="cuda")
+    dx[..., :cin] = octo.to_device(x, dtype)
+    dy = torch.full((n, ho, wo, cout + ye), -7.0, dtype=octo.torch_dtype(dtype), device="cuda")
+    kid = octo.op_conv(layer, dx[..., :cin], dy[..., :cout], octo.to_device(res, dtype) if res_mode else None, res_mode)
+    torch.cuda.synchronize()
+    assert want in (kid, kid // 10000000), kid
+    # one rounding to storage on either side; sums of products in fp32
+    assert rel_err(dy[..., :cout].float().cpu().numpy(), round_storage(y, dtype)) <= TOL[dtype]
+    assert (dy[..., cout:].float().cpu().numpy() == -7.0).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_two_layers_in_one_small_launch(octo, dtype):
+    """Two 1x1 layers in one launch, the second one's channels beginning inside a tile: bit for bit what the layers give on their own."""
+    B = zoo._Builder("t", dtype, 20, 22, "classifier", np.random.default_rng(85))
+    B.ch = [16]
+    B.m.in_c = 16
+    x = B.conv(0, 128, 1, 1, act=zoo.ACT_SILU)
+    a, b = B.conv(x, 40, 1, 1, act=zoo.ACT_SILU), B.conv(x, 88, 1, 1, act=zoo.ACT_SILU)
+    d = B.conv(B.cat([a, b]), 96, 3, 2, act=zoo.ACT_SILU)
+    B.m.outputs = [B.fc(B.gap(d), 10)]
+    B.m.batch_size = 3
+    v = zoo.round_to_dtype(np.random.default_rng(86).uniform(-1, 1, (3, 20, 22, 16)).astype(np.float32), dtype)
+    ref = nn.run_model(B.m, v, keep_all=True)
+    got, kids = {}, {}
+    for keep in (1, 2):                                  # every layer on its own; fused, with every buffer kept
+        P = octo.Pipeline(zoo.PipelineSpec("t", [small_root(dtype), B.m], [], 200.0, 32, 32, 1, 1), keep_all_tensors=keep)
+        P.run_model_on(1, octo.to_device(v, dtype))
+        got[keep], kids[keep] = [P.get_tensor(1, q, 3) for q in (a, b, d)], [int(q) for q in P.layer_info(1)[1]]
+        P.close()
+    assert kids[2][a - 1] // 100000000 == 13 and kids[2][b - 1] == 0, kids
+    for j, q in enumerate((a, b, d)):
+        assert rel_err(got[2][j], ref[q]) <= TOL[dtype], q
+        assert np.array_equal(got[2][j], got[1][j]), q
+
+
+def test_the_names_of_the_instances():
+    for (bc, bp), (wp, minb) in bench.SMALL.items():
+        for mode in range(3):
+            wc = {(32, 32): 2, (32, 64): 1, (64, 32): 2, (64, 64): 2, (128, 64): 4}[(bc, bp)]
+            kid = 1300000000 + mode * 10000000 + bc * 10000 + bp * 10 + wc
+            assert bench.conv_name(kid, "bf16") == "octo::conv_small_kernel<__bf16, %d, %d, %d, %d, %d, %d>" % (bc, bp, wc, wp, minb, mode)
