@@ -597,6 +597,15 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   // That kernel sums in another order, so the choice is made for a.n_split items where the count is taken on the device:
   // unlike the running average behind n_hint it stays the same from batch to batch, and so do the results.
   const long long M_split = a.n_split > 0 ? (long long)(a.n_split < a.n ? a.n_split : a.n) * a.Ho * a.Wo : M;
+  // fp32: conv_small_kernel or split-K, wherever the layer has the form of the former (conv_small_choice.h).  Tiles sum in chains of different lengths, so that
+  // every choice is made for M_split.
+  if constexpr (sizeof(T) == 4) {
+    if (small_fits(a, 4) && small_takes_f32(a, M_split, num_cu)) {
+      double us = 0;
+      const int which = small_choose(a, M_split, num_cu, 4, &us), ks = small_split_f32(a, M_split, num_cu, us);
+      return ks >= 0 ? launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm) : launch_small_f32(which, a, num_cu, s, kernel_id, tm);
+    }
+  }
   // Launches of few tiles go to conv_small_kernel, or to split-K where that is estimated to be faster; both lines are drawn in conv_small_choice.h.
   // conv_flow_kernel and the general kernel sum in the order of conv_small_kernel, so that the running count may choose between those (not where
   // a last vector has less than eight channels, whose values they convert one by one); against split-K and the patch kernel it is M_split.

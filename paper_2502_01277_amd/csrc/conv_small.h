@@ -1,4 +1,4 @@
-// Convolution for launches of up to about two tiles per compute unit: an implicit GEMM written for few instructions per wavefront.
+// Convolution for launches of up to about two tiles per compute unit, and of any size in fp32: an implicit GEMM written for few instructions per wavefront.
 //
 // Such a launch is one round of workgroups, and its time is what one of them takes from its first instruction to its last store. A
 // wavefront alone on its SIMD issues an instruction every four cycles at best, so that time is mostly a count of instructions: of the
@@ -14,7 +14,9 @@
 // adds its products in the order of two of 32 x 32 x 16).  Before (the kernel that took the layer) and after, us, bf16, from a graph: 1x1
 // 256 -> 256 on 20 x 20 3.8 -> 2.8, on 5 x 40 x 40 5.4 -> 4.7; 512 -> 512 on 5 x 20 x 20 5.3 -> 4.4; 3x3 64 -> 64 on 5 x 80 x 80 8.2 -> 7.0; stride 2:
 // 128 -> 256 on 5 x 80 x 80 11.8 -> 9.4, 256 -> 512 on 8 x 40 x 40 17.2 -> 13.0.
-// What bounds it: between launches 1.2 us; then latency, and from about 20 K steps on what LDS reads take (8 KB per 32 x 32 block and step).
+// In fp32 the matrix pipe bounds all but the smallest layers (116 of the 153 TFLOP/s that a large product reaches at 128 -> 384, stride 2 on
+// 2 x 160 x 161): three or four workgroups per compute unit hide each other's latency; see conv_small_choice.h for before and after.
+// What bounds it in the 16-bit types: between launches 1.2 us; then latency, and from about 20 K steps on what LDS reads take (8 KB per 32 x 32 block and step).
 // Measured and left out: rings of four to eight stages, two K steps between barriers (both nothing), two or four groups of wavefronts
 // that share K (20 x 20 x 256 -> 256 3x3 7.2 -> 6.7, split-K 5.9; short reductions 0.2 .. 0.5 slower), 128 x 128 tiles.
 #pragma once
@@ -40,32 +42,33 @@ struct SmallArgs {
   int act, res_mode, w_len, w_rows;
 };
 
-// One K step (128 bytes per row) of a 16 x 16 block: lane (r16, q4) supplies vectors q4 and 4 + q4 of its row.
-template <typename T> struct SmallElem;
-template <> struct SmallElem<_Float16> {
-  static __device__ __forceinline__ floatx4 step(const u32x4 (&a)[2], const u32x4 (&b)[2], floatx4 c) {
+// One K step (128 bytes per row) of a 16 x 16 block: lane (r16, q4) supplies vectors q4 and 4 + q4 of its row.  In fp32 the values of a step
+// go to C chains of sums that are added at the end: an instruction need not wait for the one before, and a chain is as short as a
+// wavefront's part of the reduction in the split-K kernel.
+template <typename T, int C>
+__device__ __forceinline__ void small_step(const u32x4 (&a)[2], const u32x4 (&b)[2], floatx4 (&c)[C]) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a[k]), __builtin_bit_cast(half8, b[k]), c, 0, 0, 0);
-    return c;
-  }
-};
-template <> struct SmallElem<__bf16> {
-  static __device__ __forceinline__ floatx4 step(const u32x4 (&a)[2], const u32x4 (&b)[2], floatx4 c) {
+  for (int k = 0; k < 2; ++k) {
+    if constexpr (std::is_same<T, _Float16>::value) c[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a[k]), __builtin_bit_cast(half8, b[k]), c[0], 0, 0, 0);
+    else if constexpr (std::is_same<T, __bf16>::value) c[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[k]), __builtin_bit_cast(bf16x8, b[k]), c[0], 0, 0, 0);
+    else {
+      const floatx4 fa = __builtin_bit_cast(floatx4, a[k]), fb = __builtin_bit_cast(floatx4, b[k]);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[k]), __builtin_bit_cast(bf16x8, b[k]), c, 0, 0, 0);
-    return c;
+      for (int e = 0; e < 4; ++e) c[(4 * k + e) % C] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e], fb[e], c[(4 * k + e) % C], 0, 0, 0);
+    }
   }
-};
+}
 
 // BC x BP: tile; WC, WP: wavefronts along the channels and the pixels; MINB: workgroups per compute unit; MODE: how addresses are made
-// (SMALL_POINTWISE, SMALL_TAPS, SMALL_ANY).
+// (SMALL_POINTWISE and what follows it).
 template <typename T, int BC, int BP, int WC, int WP, int MINB, int MODE>
 __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_kernel(const SmallArgs a) {
-  constexpr bool PW = MODE == SMALL_POINTWISE;
+  constexpr bool PART = MODE == SMALL_PART || MODE == SMALL_STRIDED_PART, PW = MODE == SMALL_POINTWISE || MODE == SMALL_PART;
   constexpr int ES = (int)sizeof(T), VN = 16 / ES, BK = 8 * VN;
   constexpr int NT = 64 * WC * WP, RP = NT / 8, NS = 3;       // lanes, rows that they load per pass, stages of the ring
   constexpr int NB = BC / WC / 16, NP = BP / WP / 16;         // blocks of 16 channels and of 16 pixels of a wavefront
   constexpr int LA = BC / RP, LB = BP / RP, NL = LA + LB, STAGE = (BC + BP) * 128;
+  constexpr int NC = ES == 4 ? (NB * NP <= 2 ? 8 : 4) : 1;    // chains of sums
   constexpr int CH = 4 * NB;                                  // consecutive channels of a lane
   constexpr int UQ = ES == 4 ? 1 : (ES == 2 ? (NB < 2 ? NB : 2) : (NB < 4 ? NB : 4)), VC = 4 * UQ, NV = NB / UQ;     // quads and channels of a store, stores
   typedef uint32_t vec __attribute__((ext_vector_type(UQ * ES)));
@@ -152,7 +155,7 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
         const int slo = w0 < 0 ? -w0 : 0, shi = a.W - w0 < a.kw ? a.W - w0 : a.kw;
         const unsigned rm = rhi > rlo ? ((1u << rhi) - 1u) & ~((1u << rlo) - 1u) : 0u;
         const unsigned sm = shi > slo ? ((1u << shi) - 1u) & ~((1u << slo) - 1u) : 0u;
-        rowoff[i] = (((int)(im - img0) * a.H + (int)ho * a.stride) * a.W + (int)wo * a.stride) * a.x_pitch + (MODE == SMALL_TAPS ? lkv * 16 : 0);
+        rowoff[i] = (((int)(im - img0) * a.H + (int)ho * a.stride) * a.W + (int)wo * a.stride) * a.x_pitch + (MODE == SMALL_ANY ? 0 : lkv * 16);
         ok[i] = m < M ? rm | (sm << 16) : 0u;
       }
       open_tap();
@@ -167,15 +170,20 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
       for (int i = 0; i < LA; ++i)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                      :: "s"(st + i * (NT * 16)), "v"(woff[i]), "s"(rw), "s"(wk) : "memory");
+      const bool cut = PART && l_kb == a.nk - 1 && lkv * VN >= a.K - (a.nk - 1) * BK;      // behind the last channel
 #pragma unroll
-      for (int i = 0; i < LB; ++i)
+      for (int i = 0; i < LB; ++i) {
+        const int vo = cut ? OOB : voff[i];
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     :: "s"(st + BC * 128 + i * (NT * 16)), "v"(voff[i]), "s"(rx), "s"(ox) : "memory");
+                     :: "s"(st + BC * 128 + i * (NT * 16)), "v"(vo), "s"(rx), "s"(ox) : "memory");
+      }
       ist = ist + 1 == NS ? 0 : ist + 1;
       wk += 128; xk += 128;
       if constexpr (MODE == SMALL_ANY) {
         ++l_kb;
         open_tap();
+      } else if constexpr (PART) {
+        ++l_kb;
       } else if constexpr (!PW) {
         if (++l_kb == a.taps_nk) {
           l_kb = 0;
@@ -206,11 +214,13 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
     const int ahead = a.nk < NS - 1 ? a.nk : NS - 1;
     for (int d = 0; d < ahead; ++d) issue();
 
-    floatx4 acc[NB][NP];
+    floatx4 acc[NB][NP][NC];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int j = 0; j < NP; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NP; ++j)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[b][j][c] = floatx4{0.f, 0.f, 0.f, 0.f};
     int rst = 0;
     // one K step; `between` runs while its fragments are on their way from LDS
     auto compute = [&](auto between) __attribute__((always_inline)) {
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
 #pragma unroll
       for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int j = 0; j < NP; ++j) acc[b][j] = SmallElem<T>::step(fa[b], fb[j], acc[b][j]);
+        for (int j = 0; j < NP; ++j) small_step<T, NC>(fa[b], fb[j], acc[b][j]);
       rst = rst + 1 == NS ? 0 : rst + 1;
     };
     int s = NS - 1;                                      // steps requested
@@ -260,7 +270,10 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
             const int b = UQ * h + q;
             floatx4 r4 = floatx4{0.f, 0.f, 0.f, 0.f};
             if constexpr (RES != OCTO_RES_NONE) r4 = load4<T>((const T*)&rv[j][h] + 4 * q);
-            floatx4 v = finish4<RES, SILU>(acc[b][j], bias[b], r4, act_lo);
+            floatx4 v = acc[b][j][0];
+            if constexpr (NC == 4) v = (v + acc[b][j][1]) + (acc[b][j][2] + acc[b][j][3]);
+            if constexpr (NC == 8) v = ((v + acc[b][j][1]) + (acc[b][j][2] + acc[b][j][3])) + ((acc[b][j][4] + acc[b][j][5]) + (acc[b][j][6] + acc[b][j][7]));
+            v = finish4<RES, SILU>(v, bias[b], r4, act_lo);
             if constexpr (std::is_same<T, _Float16>::value) {
               // rounded to 32 bits and then to 16, as in the other kernels (the compiler would fuse SiLU's last product with the conversion)
 #pragma unroll
@@ -306,7 +319,8 @@ static hipError_t launch_small_cfg(const ConvArgs& a, int num_cu, hipStream_t s,
   // where the weights are the larger operand, a die keeps to its channels and all dies read the pixels; see conv_ksplit.h
   o.c_outer = (double)a.Cout * a.Kp > (double)(a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * a.H * a.W * a.Cin;
   o.act = a.act; o.res_mode = a.res_mode; o.w_len = a.w_rows * a.Kp * ES; o.w_rows = a.w_rows;
-  const int mode = a.Cin % BK ? SMALL_ANY : (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h ? SMALL_TAPS : SMALL_POINTWISE);
+  const bool window = a.kh > 1 || a.kw > 1 || a.pad_h, part = ES == 4 && a.Cin % BK && !window;
+  const int mode = part ? (a.stride_h > 1 ? SMALL_STRIDED_PART : SMALL_PART) : a.Cin % BK ? SMALL_ANY : (window || a.stride_h > 1 ? SMALL_TAPS : SMALL_POINTWISE);
   if (kernel_id) *kernel_id = small_kernel_id(BC, BP, WC, mode);
   auto go = [&](auto mode_c) {
     constexpr int MODE = decltype(mode_c)::value;
@@ -314,11 +328,14 @@ static hipError_t launch_small_cfg(const ConvArgs& a, int num_cu, hipStream_t s,
     else hipLaunchKernelGGL((conv_small_kernel<T, BC, BP, WC, WP, MINB, MODE>), dim3((unsigned)grid), dim3(NT), 0, s, o);
     return hipGetLastError();
   };
+  if constexpr (ES == 4) {
+    if (part) return a.stride_h > 1 ? go(std::integral_constant<int, SMALL_STRIDED_PART>{}) : go(std::integral_constant<int, SMALL_PART>{});
+  }
   return mode == SMALL_ANY ? go(std::integral_constant<int, SMALL_ANY>{})
                            : mode == SMALL_TAPS ? go(std::integral_constant<int, SMALL_TAPS>{}) : go(std::integral_constant<int, SMALL_POINTWISE>{});
 }
 
-// One entry point per storage type; `which` counts the rows of SMALL_COST.
+// One entry point per storage type; `which` counts the rows of SMALL_COST (SMALL_COST_F32).
 template <typename T>
 static hipError_t launch_small(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   switch (which) {
@@ -326,7 +343,7 @@ static hipError_t launch_small(int which, const ConvArgs& a, int num_cu, hipStre
     case 1: return launch_small_cfg<T, 32, 64, 1, 4, 4>(a, num_cu, s, kernel_id, tm);
     case 2: return launch_small_cfg<T, 64, 32, 2, 2, 4>(a, num_cu, s, kernel_id, tm);
     case 3: return launch_small_cfg<T, 64, 64, 2, 2, 3>(a, num_cu, s, kernel_id, tm);
-    case 4: return launch_small_cfg<T, 128, 64, 4, 2, 2>(a, num_cu, s, kernel_id, tm);
+    case 4: if constexpr (sizeof(T) == 2) return launch_small_cfg<T, 128, 64, 4, 2, 2>(a, num_cu, s, kernel_id, tm);
   }
   return hipErrorNotSupported;
 }

@@ -6,8 +6,9 @@
 namespace octo {
 
 // How addresses are made: 1x1, stride 1, no padding, whole K steps of channels; any other layer with whole K steps of channels per
-// tap; any layer (a lane works out the tap of its vector at every step).
-enum { SMALL_POINTWISE = 0, SMALL_TAPS = 1, SMALL_ANY = 2 };
+// tap; any layer (a lane works out the tap of its vector at every step); in fp32, 1x1 layers without padding whose channels end inside a
+// step, stride 1 or more.
+enum { SMALL_POINTWISE = 0, SMALL_TAPS = 1, SMALL_ANY = 2, SMALL_PART = 3, SMALL_STRIDED_PART = 4 };
 
 // Does a layer of values of ES bytes have the form that the kernel takes?
 inline bool small_fits(const ConvArgs& a, int ES) {
@@ -40,19 +41,66 @@ constexpr SmallCost SMALL_COST[2][5] = {
      {64, 32, 2.686, 0.105, 0.401, 0.100, 0.004},
      {64, 64, 2.891, 0.167, 0.696, 0.066, 0.020},
      {128, 64, 2.682, 0.273, 1.154, 0.022, 0.074}}};
-// The row of SMALL_COST with the smallest estimate for M output pixels.
+// The same in fp32 (steps of 32 values): input channels in whole K steps, windows that are not, 1x1 layers that are not.  Fitted to 520 layers
+// (4 .. 768 input, 16 .. 512 output channels, 0.04 .. 60 tiles of 64 x 64 per compute unit; residual error 3 - 6 %); 128 x 64 tiles give nothing there.
+constexpr SmallCost SMALL_COST_F32[3][4] = {
+    {{32, 32, 2.159, 0.136, 0.337, 0.079, -0.003},
+     {32, 64, 2.329, 0.262, 0.518, 0.074, 0.018},
+     {64, 32, 2.323, 0.264, 0.500, 0.071, 0.005},
+     {64, 64, 2.327, 0.504, 0.867, 0.067, 0.028}},
+    {{32, 32, 2.419, 0.156, 0.447, 0.126, -0.014},
+     {32, 64, 3.073, 0.282, 0.757, 0.114, 0.050},
+     {64, 32, 2.895, 0.260, 0.760, 0.159, 0.044},
+     {64, 64, 2.674, 0.524, 0.940, 0.109, 0.047}},
+    {{32, 32, 2.297, 0.145, 0.284, 0.050, 0.012},
+     {32, 64, 2.446, 0.277, 0.453, 0.031, 0.033},
+     {64, 32, 2.519, 0.249, 0.361, 0.047, 0.060},
+     {64, 64, 2.705, 0.475, 0.479, 0.052, 0.085}}};
+// The row of SMALL_COST (fp32: SMALL_COST_F32) with the smallest estimate for M output pixels.
 inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, double* us) {
   int best = 0;
+  const int any = a.Cin % (128 / ES) == 0 ? 0 : ES == 4 && a.kh == 1 && a.kw == 1 && !a.pad_h ? 2 : 1;
   const double nk = (a.K + 128 / ES - 1) / (128 / ES);
   const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
   const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
-  for (int i = 0; i < 5; ++i) {
-    const SmallCost& c = SMALL_COST[a.Cin % (128 / ES) ? 1 : 0][i];
+  for (int i = 0; i < (ES == 4 ? 4 : 5); ++i) {
+    const SmallCost& c = ES == 4 ? SMALL_COST_F32[any][i] : SMALL_COST[any][i];
     const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
     double per_cu = 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu));
     if (per_cu < 1.0) per_cu = 1.0;
     const double t = c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk + c.per_mb * mb;
     if (i == 0 || t < *us) { *us = t; best = i; }
+  }
+  return best;
+}
+// Layers in fp32 take the kernel at every size, but windows with steps across taps, where a lane works out addresses at every step, only up to
+// eight tiles of 64 x 64 per compute unit (over 157 of them, the kernel that took the layer : here, by those tiles: up to 0.6 1.06, 2 .. 5 1.15, 8 .. 15
+// 1.06, more 0.95; 4 -> 200 on 5 x 160 x 161 58.1 : 64.7).  The matrix pipe bounds it from a few tiles per compute unit on; the general kernel's blocks of
+// 32 x 32 x 2 wait for one another.  Us, before : here: 16 -> 32, stride 2 on 2 x 160 x 160 5.9 : 5.2; 1x1 64 -> 192 on 10 x 16 x 17 5.4 : 3.7, 128 -> 256 on
+// 11 x 56 x 56 36.8 : 29.4, 768 -> 64 on 3 x 112 x 114 59.2 : 36.5, 200 -> 512 on 837 x 7 x 8 112 : 105; 3x3 160 -> 39 on 324 x 16 x 17 170 : 135; 128 -> 384,
+// stride 2 on 2 x 160 x 161 151 : 99.  Over the 520 layers 0.83 of the time and 0.75 of the error against 64 bits.
+// Long reductions of few tiles stay with the split-K kernel's 32 x 32 and 64 x 32 tiles, by these estimates (same layers, up to three such tiles per
+// compute unit, residual error 4 - 6 %): 284 -> 32 on 2 x 40 x 40 15.4 : 25.5, 512 -> 512 on 16 x 17 26.2 : 33.1, 256 -> 39 on 56 x 58 14.4 : 18.3.
+// 1x1 layers leave beyond 64 tiles: the general kernel's 128 x 128 tiles read the pixels half as often (44 -> 352, stride 2 on 1346 x 33 x 33 at 133 266 : 312,
+// 24 -> 256 on 361 x 32 x 33 at 93 146 : 158, 64 -> 256 on 22 x 153 x 120 at 98 195 : 206; 72 -> 256 on 60 x 56 x 57 at 46 116 : 112, 36 -> 128 on
+// 201 x 40 x 41 at 40 128 : 108).
+inline bool small_takes_f32(const ConvArgs& a, long long M, int num_cu) {
+  const long long tiles = (M + 63) / 64 * ((a.Cout + 63) / 64);
+  if (a.kh == 1 && a.kw == 1 && !a.pad_h) return tiles <= 64LL * num_cu;
+  return a.Cin % 32 == 0 || tiles <= 8LL * num_cu;
+}
+constexpr SmallCost SPLIT_COST_F32[3] = {{32, 32, 2.732, 0.181, 1.363, -0.034, 0.0}, {32, 32, 3.103, 0.174, 0.691, -0.002, 0.0}, {64, 32, 3.364, 0.335, 0.952, -0.049, 0.0}};
+// The split-K shape (launch_ksplit's numbers) with an estimate below `us`, or -1.
+inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us) {
+  int best = -1;
+  const double nk = (a.K + 31) / 32;
+  for (int i = 0; i < 3; ++i) {
+    const SmallCost& c = SPLIT_COST_F32[i];
+    const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
+    if (tiles > 3LL * num_cu) continue;
+    const double per_cu = std::max(1.0, 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu)));
+    const double t = c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk;
+    if (t < us) { us = t; best = i; }
   }
   return best;
 }
@@ -89,6 +137,7 @@ inline bool small_takes_3x3(const ConvArgs& a, long long M, int num_cu) {
 }
 
 hipError_t launch_small_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
+hipError_t launch_small_f32(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 hipError_t launch_small_bf16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm);
 
 }  // namespace octo

@@ -1,6 +1,6 @@
 """The convolution kernel for launches of few tiles at its edges: one pixel, pixel and channel counts that are no multiple of a tile, every tile
 and kind of addresses, reductions of one step, of part of one and of many, windows over every border, residuals, channel slices of
-wider buffers, a last vector of less than eight channels; against the oracle's arithmetic."""
+wider buffers, a last vector of less than eight channels; against the oracle's arithmetic, in fp32 against 64 bits."""
 import numpy as np
 import pytest
 
@@ -58,6 +58,53 @@ def test_small_launch_parity(octo, dtype, case):
     # one rounding to storage on either side; sums of products in fp32
     assert rel_err(dy[..., :cout].float().cpu().numpy(), round_storage(y, dtype)) <= TOL[dtype]
     assert (dy[..., cout:].float().cpu().numpy() == -7.0).all()
+
+
+CASES_F32 = [
+    (1, 1, 1, 32, 20, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 0, 1300320322),                   # one pixel, one step
+    (2, 320, 321, 4, 16, 3, 2, nn.ACT_SILU, nn.RES_NONE, 0, 4, 132),                       # part of a second step, across taps
+    (3, 16, 17, 64, 192, 1, 1, nn.ACT_RELU, nn.RES_AFTER_ACT, 4, 0, 130),
+    (5, 56, 57, 128, 255, 1, 1, nn.ACT_NONE, nn.RES_NONE, 0, 1, 130),                      # three of the last four channels
+    (1, 33, 31, 44, 72, 1, 1, nn.ACT_SILU, nn.RES_BEFORE_ACT, 20, 0, 133),                 # 12 of the second step's channels
+    (9, 31, 33, 36, 136, 1, 2, nn.ACT_RELU, nn.RES_NONE, 12, 8, 134),                      # the same with a stride
+    (20, 56, 57, 72, 256, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 60, 0, 1330640642),         # 64 x 64, several per workgroup
+    (2, 57, 55, 64, 96, 3, 2, nn.ACT_SILU, nn.RES_NONE, 0, 0, 131),
+    (7, 13, 15, 32, 40, 3, 1, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 131),
+    (40, 3, 4, 32, 96, 2, 2, nn.ACT_NONE, nn.RES_NONE, 0, 0, 131),                         # a tile over several images
+    (1, 1, 401, 32, 256, 3, 2, nn.ACT_RELU, nn.RES_NONE, 0, 0, 131),                       # taps that no pixel can use
+    (1, 16, 17, 512, 64, 3, 1, nn.ACT_RELU, nn.RES_NONE, 0, 0, 16),                        # few tiles, 144 steps: split-K
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES_F32)
+def test_small_launch_parity_in_fp32(octo, case):
+    """Against sums in 64 bits: eight chains of at most K / 8 products (four of K / 4 in 64 x 64 tiles), whose roundings are at most
+    2^-24 of the sum of the magnitudes each; with random signs the error is far below K / 4 of them.  Channels behind the slice are
+    infinite, and those behind the output stay as they are."""
+    import torch
+    n, h, w, cin, cout, k, stride, act, res_mode, xe, ye, want = case
+    pad = k // 2
+    rng = np.random.default_rng(89)
+    x = rng.uniform(-1, 1, (n, h, w, cin)).astype(np.float32)
+    wt = (rng.standard_normal((cout, k, k, cin)) / np.sqrt(k * k * cin)).astype(np.float32)
+    bias = rng.uniform(-0.1, 0.1, cout).astype(np.float32)
+    layer = octo.ConvOp(wt, bias, "f32", stride, pad, act)
+    ho, wo = layer.out_hw(h, w)
+    res = rng.uniform(-1, 1, (n, ho, wo, cout)).astype(np.float32) if res_mode else None
+    y = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2), torch.from_numpy(wt).double().permute(0, 3, 1, 2),
+                                   stride=stride, padding=pad).permute(0, 2, 3, 1).numpy() + bias
+    r = res if res_mode else 0.0
+    silu = lambda v: v / (1.0 + np.exp(-v)) if act == nn.ACT_SILU else np.maximum(v, 0.0) if act == nn.ACT_RELU else v   # noqa: E731
+    y = silu(y + r) if res_mode == nn.RES_BEFORE_ACT else silu(y) + r
+    dx = torch.full((n, h, w, cin + xe), float("inf"), device="cuda")
+    dx[..., :cin] = octo.to_device(x, "f32")
+    dy = torch.full((n, ho, wo, cout + ye), -7.0, device="cuda")
+    kid = octo.op_conv(layer, dx[..., :cin], dy[..., :cout], octo.to_device(res, "f32") if res_mode else None, res_mode)
+    torch.cuda.synchronize()
+    assert str(kid).startswith(str(want)), kid
+    assert rel_err(dy[..., :cout].cpu().numpy(), y) <= TOL["f32"] and np.abs(dy[..., :cout].cpu().numpy() - y).max() <= (k * k * cin / 4 + 8) * 2.0 ** -24 * 4
+    assert (dy[..., cout:].cpu().numpy() == -7.0).all()
 
 
 @pytest.mark.gpu
