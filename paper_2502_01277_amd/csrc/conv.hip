@@ -726,8 +726,12 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   // conv_flow_kernel as for the 16-bit types, by the same estimate with steps of 128 values (general : flow, us: 96 -> 96 1x1 on 32 x 160 x 160
   // 76.8 : 50.1, 192 -> 192 148.7 : 97.7, 1024 -> 256 on 60 x 14 x 14 11.2 : 8.1, 48 -> 96, stride 2 on 32 x 640 x 640 435 : 307, 256 -> 512, stride 2 on
   // 4170 x 14 x 14 298 : 257, 128 -> 256, stride 2 on 8 x 80 x 80 12.2 : 10.2).  Half a step into one 64-channel tile stays on the 64 x 256
-  // tiles with 64-byte steps (48 -> 48 on 32 x 320 x 320 124 : 130, 32 -> 64 on 16 x 160 x 160 20.1 : 21.6).
-  if (flow_fits(a, 1) && !(a.K <= 64 && a.Cout <= 64)) {
+  // tiles with 64-byte steps (48 -> 48 on 32 x 320 x 320 124 : 130, 32 -> 64 on 16 x 160 x 160 20.1 : 21.6) but for 56 channels, which those tiles
+  // write byte by byte (16 -> 56 on 104 x 57 x 59 34.9 : 20.7); so do up to 40 channels of short reductions (32 -> 40 on 1651 x 21 x 13 21.9 : 30.3, 3x3
+  // 16 -> 32 on 256 x 73 x 94 79 : 96, 48 -> 24 77 : 87; 96 -> 24 on 56 x 158 x 133 55 : 57, 256 -> 24 on 209 x 34 x 38 25.5 : 18.9, 3x3 304 -> 24 on
+  // 1526 x 25 x 15 268 : 159).  Other half vectors and single steps into several channel tiles: 16 -> 88 on 45 x 159 x 224 339 : 149, 96 -> 184, stride 2 on
+  // 142 x 75 x 96 60.5 : 32.7, 16 -> 648, stride 2 on 780 x 33 x 37 202 : 131; over 164 such layers 0.80 of the general kernel's time.
+  if (flow_fits(a, 1) && (a.Cout >= 48 ? a.K > 64 || a.Cout > 64 || a.Cout % 16 : a.Cin >= 96)) {
     double us = 0;
     return launch_flow_f8(flow_choose(a, M, num_cu, &us, 1), a, num_cu, s, kernel_id, tm);
   }

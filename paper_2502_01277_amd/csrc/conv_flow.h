@@ -17,7 +17,8 @@
 // (4.4 TB/s); 192 -> 256 on 32 x 160 x 160 235 -> 164; 256 -> 256 on 64 x 40 x 40 36 -> 26; 512 -> 512 on 8 x 20 x 20 7.9 -> 6.5.
 // E4M3 (a step is 128 values, two matrix instructions deep; scale and bias per channel arrive together): 96 -> 96 on 32 x 160 x 160 77 -> 50,
 // 192 -> 192 149 -> 98 (3.2 TB/s), 48 -> 96, stride 2 on 32 x 640 x 640 435 -> 307, 64 -> 128, stride 2 on 4170 x 56 x 56 513 -> 416.  Its 64 x 64 tiles run
-// two workgroups per compute unit: with the scales three are 2 KB more than the LDS.
+// two workgroups per compute unit: with the scales three are 2 KB more than the LDS.  Its results and residuals come in vectors of 16 and, behind the
+// last of those, half a one.
 // LDS rows (weights: one output channel, pixels: one output pixel) are KV vectors of 16 bytes, vector v of row r in slot
 // v ^ ((r / (16 / KV)) % KV).  vmcnt bookkeeping: every wavefront issues the same number of loads per K step and of stores per tile.
 #pragma once
@@ -238,6 +239,7 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
 
   const bool has_res = a.res && a.res_mode != OCTO_RES_NONE, tail = a.Cout % VN != 0;
   int st_rd = 0, bbuf = 0;
+  auto next_bias = [](int b) { return ES == 1 ? (b == 2 ? 0 : b + 1) : b ^ 1; };      // where the next tile's bias goes, see launch_flow_cfg
   bool stored = false;                                     // the first wait of a tile counts the stores of the one before
   for (;;) {
     floatx16 acc[TC][TP];
@@ -256,12 +258,15 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
       for (int j = 0; j < TP; ++j) {
         if (j < from || j >= to) continue;
         const int pl = wp * (TP * 32) + j * 32 + l32;
-        const int off = p0 + pl < M ? (pl * a.res_ld + cw) * ES : OOB;
+        const int off = (pl * a.res_ld + cw) * ES;
 #pragma unroll
         for (int i = 0; i < TC; ++i)
 #pragma unroll
-          for (int h = 0; h < HV; ++h)
-            rv[j][i][h] = __builtin_amdgcn_raw_buffer_load_b128(rr, cw + i * 32 + h * VN < a.Cout ? off + i * 32 * ES + h * 16 : OOB, 0, 0);
+          for (int h = 0; h < HV; ++h) {
+            // a half vector (E4M3 only) is asked for with the eight values before it; lanes without a pixel or channel stay out of range
+            const int c = cw + i * 32 + h * VN, back = ES == 1 && c + 8 == a.Cout ? 8 : 0;
+            rv[j][i][h] = __builtin_amdgcn_raw_buffer_load_b128(rr, p0 + pl < M && c < a.Cout ? off + i * 32 * ES + h * 16 - back : OOB, 0, 0);
+          }
       }
     };
     const int tn = next_valid(t + gridDim.x);
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
       constexpr bool LAST = decltype(lastc)::value;
       const int nxt = st_rd + 1 == NST ? 0 : st_rd + 1;
       if constexpr (LAST) {
-        issue_bias(cn0, tiles_c == 1 ? 2 : bbuf ^ 1, more);
+        issue_bias(cn0, tiles_c == 1 ? 2 : next_bias(bbuf), more);
         if (PJ > 0 && has_res) load_res(0, PJ);
       }
 #pragma unroll
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
             for (int q = 0; q < 4; ++q) {
               const int cq = wc * (TC * 32) + g * 16 + i * 32 + q * 4;
               floatx4 v, r4 = floatx4{0.f, 0.f, 0.f, 0.f};
-              if constexpr (RES != OCTO_RES_NONE) r4 = f8_unpack4(rv[j][i][0][q]);
+              if constexpr (RES != OCTO_RES_NONE) r4 = f8_unpack4(tail && q < 2 && cw + i * 32 + 8 == a.Cout ? rv[j][i][0][(q + 2) & 3] : rv[j][i][0][q]);
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
                 v[e] = acc[i][j][q * 4 + e] * sScale[bbuf][cq + e];
@@ -374,6 +379,8 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
               else if (2 * e + 1 == left % VN) __builtin_amdgcn_raw_buffer_store_b16((short)out[e], ry, to + e * 4, 0, 0);
             }
           }
+          if (ES == 1 && tail && left > 0 && left < 32)    // the half vector
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{out[0], out[1]}, ry, cw + i * 32 + 8 == a.Cout ? yo + i * 32 : OOB, 0, 0);
           if (second) __builtin_amdgcn_raw_buffer_store_b128(out, ry2, ok ? yo2 + i * 32 * ES + h * 16 : OOB, 0, 0);
           else __builtin_amdgcn_raw_buffer_store_b128(out, ry, ok ? yo + i * 32 * ES + h * 16 : OOB, 0, 0);
           __builtin_amdgcn_sched_barrier(0);               // one vector at a time: keeps the register demand low
@@ -384,7 +391,7 @@ __global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, M
     if (!more) break;
     stored = true;
     t = tn; p0 = pn0; c0 = cn0;
-    if (tiles_c > 1) bbuf ^= 1;
+    if (tiles_c > 1) bbuf = next_bias(bbuf);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // loads issued past the last step write zeros into LDS
 }
@@ -404,10 +411,11 @@ static hipError_t launch_flow_mode(const ConvArgs& a, const FlowGeom& gm, long l
 template <typename T, int NT, int BC, int BP, int WC, int KV, int NST, int MINB>
 static hipError_t launch_flow_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   constexpr int BK = KV * Elem<T>::N;
-  // The bias of a tile is requested at the last step of the one before: its place must be free (a barrier since the epilogue before),
-  // and it must have landed by the epilogue (older than the operands of step NST - 2).  With a single step there must be one channel tile.
-  static_assert(KV == 8 && NST <= 4, "two K steps suffice, or one with one channel tile");
-  if (a.K <= BK && a.Cout > BC) return hipErrorNotSupported;
+  // The bias of a tile is requested at the last step of the one before: its place must be free, and it must have landed by the epilogue (older than
+  // the operands of step NST - 2).  Other wavefronts may still read that of the tile before in its epilogue: two places do where a barrier
+  // lies between, which takes two K steps or a single channel tile.  E4M3, whose steps are wide, goes round three.
+  static_assert(KV == 8 && NST <= 4, "operands are younger than the bias");
+  if (sizeof(T) == 2 && a.K <= BK && a.Cout > BC) return hipErrorNotSupported;
   const long long M = (long long)a.n * a.Ho * a.Wo, tiles_c = (a.Cout + BC - 1) / BC, tiles = (M + BP - 1) / BP * tiles_c;
   if (tiles <= 0) return hipSuccess;
   if (tiles >= 0x3FFFFFF0LL) return hipErrorNotSupported;

@@ -9,12 +9,13 @@ namespace octo {
 inline bool flow_fits(const ConvArgs& a, int ES = 2) {
   const int VN = 16 / ES;
   if (a.out_f32 || a.pair_view || a.pool_y || a.up_y || a.kh > 15 || a.kw > 15) return false;
-  if (a.Cout % VN && (a.res || a.split > 0 || ES == 1)) return false;
+  const int VO = ES == 1 ? 8 : VN;                         // results and residual: E4M3 in halves of a vector
+  if ((a.Cout % VO && (a.res || a.split > 0 || ES == 1)) || a.Cout < 16) return false;
   if (ES == 1 && (a.split > 0 || !a.scale)) return false;
-  if (((a.Cin | a.x_ld | a.x_coff | a.y_ld | a.y_coff) % VN) || (((uintptr_t)a.x | (uintptr_t)a.y) & 15)) return false;
-  if (a.res && (((a.res_ld | a.res_coff) % VN) || ((uintptr_t)a.res & 15))) return false;
+  if (((a.Cin | a.x_ld | a.x_coff) % VN) || ((uintptr_t)a.x & 15) || ((a.y_ld | a.y_coff) % VO) || ((uintptr_t)a.y & (VO * ES - 1))) return false;
+  if (a.res && (((a.res_ld | a.res_coff) % VO) || ((uintptr_t)a.res & (VO * ES - 1)))) return false;
   if (a.split > 0 && a.split % 32) return false;
-  if (a.Cout <= 32 || (a.K <= 128 / ES && a.Cout > 256)) return false;      // nothing to fill a tile with; one K step: one channel tile (launch_flow_cfg)
+  if (ES == 2 && (a.Cout <= 32 || (a.K <= 64 && a.Cout > 256))) return false;      // nothing to fill a tile with; one K step: conv1x1_stream_kernel's
   // 32-bit offsets: weights, and the pixels of a tile (256 of them) in every tensor
   const long long ld = std::max(std::max(a.x_ld, a.y_ld), std::max(a.res ? a.res_ld : 0, a.split > 0 ? a.y2_ld : 0));
   return (long long)a.w_rows * a.Kp * ES < 0x7FFFFFFFLL && 256 * ld * ES < 0x7FFFFFF0LL && (long long)a.n * a.Ho * a.Wo < 0x7FFFFF00LL &&
@@ -49,7 +50,7 @@ inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, in
 inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us, int ES = 2) {
   int best = -1;
   for (int i = 0; i < 8; ++i) {
-    if (a.K <= 128 / ES && a.Cout > FLOW_COST[i].bc) continue;
+    if (ES == 2 && a.K <= 64 && a.Cout > FLOW_COST[i].bc) continue;
     const double t = flow_cost_us(FLOW_COST[i], a, M, num_cu, ES);
     if (best < 0 || t < *us) { *us = t; best = i; }
   }

@@ -135,6 +135,19 @@ def test_flow_fp8(octo, n, h, w, cin, cout, k, stride, res, xe, ye, mode):
     assert bool((dy[..., cout:] == 0x55).all())
 
 
+@pytest.mark.parametrize("n,h,w,cin,cout,k,stride,res,xe,ye,mode", [
+    (33, 40, 41, 384, 408, 1, 1, nn.RES_BEFORE_ACT, 0, 8, 0),      # half a vector at the end of the last tile's second block
+    (9, 41, 39, 256, 88, 1, 1, nn.RES_AFTER_ACT, 128, 0, 0),       # in the upper half of a block
+    (60, 40, 41, 96, 104, 1, 1, nn.RES_AFTER_ACT, 0, 24, 2),       # one step, part of it
+    (21, 56, 55, 64, 648, 1, 1, nn.RES_NONE, 0, 0, 2),             # one step, several channel tiles
+    (23, 56, 57, 128, 1024, 1, 1, nn.RES_AFTER_ACT, 0, 0, 0),      # the same with whole vectors
+    (209, 34, 38, 256, 24, 1, 1, nn.RES_NONE, 0, 0, 0),            # less than 32 channels
+    (25, 61, 63, 128, 152, 3, 2, nn.RES_BEFORE_ACT, 0, 0, 1),
+])
+def test_flow_fp8_half_vectors_and_single_steps(octo, n, h, w, cin, cout, k, stride, res, xe, ye, mode):
+    test_flow_fp8(octo, n, h, w, cin, cout, k, stride, res, xe, ye, mode)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("case", [
     (40, 41, 256, 96, 128, 9),         # the second layer begins inside a channel tile, whatever its width, and ends inside one
