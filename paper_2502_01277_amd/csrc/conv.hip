@@ -606,7 +606,7 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
       return ks >= 0 ? launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm) : launch_small_f32(which, a, num_cu, s, kernel_id, tm);
     }
   }
-  // Launches of few tiles go to conv_small_kernel, or to split-K where that is estimated to be faster; both lines are drawn in conv_small_choice.h.
+  // Launches of few tiles go to conv_small_kernel, or to split-K where that is estimated to be faster; small_limit and TileCost have the lines.
   // conv_flow_kernel and the general kernel sum in the order of conv_small_kernel, so that the running count may choose between those (not where
   // a last vector has less than eight channels, whose values they convert one by one); against split-K and the patch kernel it is M_split.
   bool to_small = false, not_split = false;
@@ -617,7 +617,7 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     return std::is_same<T, __bf16>::value ? launch_small_bf16(which, a, num_cu, s, kernel_id, tm) : launch_small_f16(which, a, num_cu, s, kernel_id, tm);
   };
   [[maybe_unused]] const bool pipe_ok = sizeof(T) == 2, pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
-  // strided layers for the general kernel's pipelined 64x64 tiles, see below
+  // strided layers of up to two 64x64 tiles per compute unit that the general kernel would run in one round of pipelined tiles: never split
   [[maybe_unused]] auto stays = [&](long long m) {
     const GeneralTile t = general_tile(a, m, num_cu, 1, pipe_ok);
     return !pw && t.pipe && t.bc == 64 && t.bp == 64 && (m + 63) / 64 * ((a.Cout + 63) / 64) <= 2LL * num_cu;
@@ -630,18 +630,28 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     }
     // (up to 32 channels only where the count is not taken on the device; not before an upsampling, which the split-K kernel writes along)
     if (patch || (fits && !a.up_next && (a.Cout > 32 || a.n_split == 0) && small_takes(a, M_split, num_cu))) {
-      // Split-K has to beat every other kernel: below the patch kernel's line, never where the general kernel's pipelined tiles would fill a
-      // round, and conv_flow_kernel's estimate (96 -> 192, stride 2 on 9 x 57 x 83: split-K 14.1, estimated 12.1, conv_flow_kernel 13.3)
+      // Split-K has to beat every other kernel: below the patch kernel's line, never where one round of tiles fills the chip, and
+      // conv_flow_kernel's estimate (96 -> 192, stride 2 on 9 x 57 x 83: split-K 14.1, estimated 12.1, conv_flow_kernel 13.3)
       double us = 0, uf = 0;
       small_choose(a, M_split, num_cu, 2, &us);
       if (!patch && flow_fits(a)) { flow_choose(a, M_split, num_cu, &uf); us = std::min(us, uf); }
+      us = repeated_us(a, us);
       const bool few = patch ? (double)M_split / 128 * ((a.Cout + 63) / 64) < 0.25 * num_cu : !stays(M_split);
       const int kf = few ? ksplit_best(a, M_split, 2, num_cu, us, pw ? 3 : 4, 4.0) : -1;
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
       if (patch) return run_small(M_split);
       not_split = true;
     }
-    to_small = fits && (not_split || a.Cout > 32) && small_takes(a, M_small, num_cu);
+    to_small = fits && (not_split || a.Cout > 32);
+    // (two layers in one launch: by small_limit; beyond it conv_flow_kernel's best tile takes 1.03 .. 1.1 of this kernel's time)
+    if (to_small && by_place(a) && a.split == 0 && flow_fits(a)) {
+      double us = 0, uf = 0;
+      small_choose(a, M_small, num_cu, 2, &us);
+      flow_choose(a, M_small, num_cu, &uf);
+      to_small = us <= uf;
+    } else if (to_small) {
+      to_small = small_takes(a, M_small, num_cu);
+    }
   }
   // Only the split-K kernel writes an upsampled copy.  Where its estimate is below that of the general kernel's tile one launch beats
   // conv_flow_kernel and a launch for the upsampling at every size tried (us: 512 -> 256 on 20 x 20, 1 image 5.2 : 7.4, 8 8.4 : 9.4, 12
@@ -654,26 +664,28 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   }
   if (a.up_y) return hipErrorNotSupported;
   if constexpr (sizeof(T) == 2) {
-    // conv_flow_kernel takes what has its form, except strided layers of up to two pipelined 64x64 tiles per compute unit: 256 -> 512,
+    // conv_flow_kernel takes what has its form, except what conv_small_kernel takes (in a cascade by estimate).  A single strided layer of up to two pipelined
+    // 64x64 tiles per compute unit stays with the general kernel: 256 -> 512,
     // stride 2 on 42 x 14 x 14 16.1 us here, 18.1 there, 128 -> 128, stride 2 on 8 x 80 x 80 10.5 : 11.1 (a step of such a tile is four matrix
     // instructions per wavefront, fewer than the cursor's scalar ones).  By tiles per compute unit: 256 -> 256 on 20 x 40 x 40 at 1.95 17.1 :
     // 18.4, 128 -> 64 on 82 x 40 x 40 at 2.0 (513 tiles) 14.6 : 13.9, 96 -> 192 on 9 x 57 x 83 at 2.02 13.4 : 12.5, 192 -> 192 on 7 x 80 x 80 at
-    // 2.05 18.0 : 17.2.  Their order of summation is the same, so the running count may choose between those two; split-K or not is
+    // 2.05 18.0 : 17.2.  Their order of summation is the same, so the running count may choose between these; split-K or not is
     // decided for M_split.
     if (flow_fits(a)) {
       double us = 0;
       int kf = -1;
       if (!not_split && !stays(M_split)) {
         flow_choose(a, M_split, num_cu, &us);
-        // Against this kernel split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
+        if (by_place(a) && small_fits(a, 2)) { double uf = 0; small_choose(a, M_split, num_cu, 2, &uf); us = std::min(us, uf); }
+        // Against these kernels split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
         // on 7 x 40 x 40 at 4.1 38.0 : 28.0, 512 -> 64 1x1 on 82 x 20 x 20 at 4.0 11.1 : 8.2).  Its 64 x 64 tiles serve long reductions (256 -> 256,
         // stride 2 on 6 x 40 x 40 11.0 : 13.8), not 1x1 layers (512 -> 512 on 5 x 20 x 20 7.3 : 5.8, 1024 -> 512 8.7 : 7.3), where this kernel's
         // estimate is 15 % high while it has few tiles.
-        kf = ksplit_best(a, M_split, 2, num_cu, pw ? 0.85 * us : us, pw ? 3 : 4, 4.0);
+        kf = ksplit_best(a, M_split, 2, num_cu, repeated_us(a, pw ? 0.85 * us : us), pw ? 3 : 4, 4.0);
       }
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
       if (to_small) return run_small(M_small);
-      if (stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
+      if (!by_place(a) && stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
       const int which = flow_choose(a, M, num_cu, &us);
       return std::is_same<T, __bf16>::value ? launch_flow_bf16(which, a, num_cu, s, kernel_id, tm) : launch_flow_f16(which, a, num_cu, s, kernel_id, tm);
     }

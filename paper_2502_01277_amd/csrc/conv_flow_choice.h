@@ -22,15 +22,43 @@ inline bool flow_fits(const ConvArgs& a, int ES = 2) {
          (2LL * a.H * a.W + 1024LL * a.stride_h * a.stride_w + (long long)a.pad_h * a.W + a.pad_w) * a.x_ld * ES < 0x7FFFFFF0LL;
 }
 
-// Time of a launch in us, fitted to 656 layers (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of
-// 64 x 128 per compute unit, bf16, 256 compute units; residual error 8 - 11 %): a constant, what the busiest compute unit does - its tiles,
-// rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the memory traffic.  Over those
-// layers the choice loses 1.3 % against always taking the fastest tile, and takes 0.88 of the time of the kernels it replaced
-// (128 x 256 and 64 x 64 tiles of the general kernel, pipelined: 0.87 and, for 1x1 layers, 0.84; its plain tiles 0.86).  E4M3 uses the same
-// numbers with steps of 128 values: over 64 such layers (32 .. 1024 input, 80 .. 768 output channels) the choice loses 0.9 % against the
-// fastest tile, at most 13 % (512 -> 608 on 36 x 40 x 41: 256 x 128 tiles 32.4 us, 128 x 256 28.5).
+// Is the tile chosen by tile_cost_us?
+inline bool by_place(const ConvArgs& a) { return a.in_place && a.Cin % 64 == 0; }
+// Time of a launch in us in its place in a cascade, 16-bit types, input channels in whole K steps: a constant, what a compute unit does - its tiles, a quarter of the way from the next whole number to
+// their mean, times K steps and an epilogue -, a latency per K step where no unit has a second tile, the memory traffic, and the operands that the
+// tiles fetch.
+//   There a layer's input was written by the kernel before and comes from beyond the L2s.  Fitted to launches traced over 14 batches of four cascades (1 .. 64 frames; 758 layers, 1x1 and strided, 16 .. 2048 channels, 0.03 .. 400 tiles of 64 x 64 per compute
+// unit), each layer in every tile.  Estimates from the same launch repeated on the same tensors (below) are 12 % low there and favour
+// large tiles: 128 -> 128 on 8 x 80 x 80, us, in place: 128 x 256 tiles of conv_flow_kernel 11.6, 128 x 128 12, 64 x 64 of conv_small_kernel 9.3, where three
+// workgroups per unit hide what one of eight wavefronts waits for; 256 -> 64 on that map 14.5 : 10.8, 256 -> 1024 with residual on 96 x 16 x 16 29.0 (256 x
+// 128) : 23.6 (128 x 64).  Over those layers the choice takes 0.945 of the time of the former one, the best tile of each 0.91; left out of the
+// fit one cascade at a time 0.944.
+struct TileCost { int bc, bp; double base, step, tile, latency, per_mb, per_operand_mb; };
+inline double tile_cost_us(const TileCost& c, const ConvArgs& a, long long M, int num_cu) {
+  const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
+  const double nk = (a.K + 63) / 64, per_cu = std::max(1.0, 0.25 * tiles / num_cu + 0.75 * (double)((tiles + num_cu - 1) / num_cu));
+  const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
+  const double mb = 2e-6 * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1)), operands = 128e-6 * tiles * nk * (c.bc + c.bp);
+  return c.base + per_cu * (nk * c.step + c.tile) + (tiles <= num_cu ? c.latency * nk : 0.0) + c.per_mb * mb + c.per_operand_mb * operands;
+}
+// What such a launch takes when it is repeated on the same tensors: the split-K kernel's estimates, fitted to that, are compared with this.
+inline double repeated_us(const ConvArgs& a, double us) { return by_place(a) ? 0.88 * us : us; }
+constexpr TileCost FLOW_COST[8] = {
+    {64, 64, 3.777, 0.169, 0.522, 0.082, 0.002, 0.0},
+    {64, 128, 3.928, 0.236, 0.874, 0.107, 0.028, 0.0062},
+    {128, 64, 4.206, 0.222, 0.870, 0.101, 0.018, 0.0081},
+    {128, 128, 4.343, 0.277, 1.767, 0.055, 0.037, 0.0234},
+    {96, 256, 4.509, 0.000, 3.016, 0.194, 0.000, 0.0593},
+    {192, 128, 4.865, 0.201, 1.925, 0.125, 0.035, 0.0400},
+    {128, 256, 5.580, 0.438, 3.208, -0.033, 0.028, 0.0314},
+    {256, 128, 6.239, 0.579, 1.460, -0.036, 0.083, 0.0083}};
+// Single layers, E4M3, and layers whose channels end inside a K step, of which the cascades have too few to fit: from repeated launches of 656 layers
+// (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of 64 x 128 per compute unit, bf16).  A constant, what
+// the busiest compute unit does - its tiles, rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the
+// memory traffic (residual error 8 - 11 %; the choice loses 1.3 % against always taking the fastest tile).  E4M3 uses the same numbers with steps of 128 values: over 64 such layers (32 .. 1024 input, 80 .. 768 output
+// channels) the choice loses 0.9 % against the fastest tile, at most 13 % (512 -> 608 on 36 x 40 x 41: 256 x 128 tiles 32.4 us, 128 x 256 28.5).
 struct FlowCost { int bc, bp; double base, step, tile, latency, per_mb, any_step; };
-constexpr FlowCost FLOW_COST[8] = {
+constexpr FlowCost FLOW_COST_REPEATED[8] = {
     {64, 64, 3.73, 0.165, 0.22, 0.118, 0.040, 0.031},
     {64, 128, 3.60, 0.258, 0.42, 0.091, 0.052, 0.065},
     {128, 64, 3.65, 0.255, 0.52, 0.092, 0.035, 0.028},
@@ -39,19 +67,19 @@ constexpr FlowCost FLOW_COST[8] = {
     {192, 128, 3.22, 0.554, 1.46, 0.000, 0.045, 0.064},
     {128, 256, 3.00, 0.674, 2.06, 0.000, 0.065, 0.093},
     {256, 128, 3.76, 0.653, 1.18, 0.000, 0.061, 0.053}};
-inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, int num_cu, int ES = 2) {
+inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, int num_cu, int ES) {
   const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
   const double per_cu = (double)((tiles + num_cu - 1) / num_cu), nk = (a.K + 128 / ES - 1) / (128 / ES);
   const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
   const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
   return c.base + per_cu * (nk * (c.step + (a.Cin % (128 / ES) ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * nk : 0.0) + c.per_mb * mb;
 }
-// The row of FLOW_COST with the smallest estimate for M output pixels.
+// The tile (launch_flow's number) with the smallest estimate for M output pixels.
 inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us, int ES = 2) {
   int best = -1;
   for (int i = 0; i < 8; ++i) {
     if (ES == 2 && a.K <= 64 && a.Cout > FLOW_COST[i].bc) continue;
-    const double t = flow_cost_us(FLOW_COST[i], a, M, num_cu, ES);
+    const double t = ES == 2 && by_place(a) ? tile_cost_us(FLOW_COST[i], a, M, num_cu) : flow_cost_us(FLOW_COST_REPEATED[i], a, M, num_cu, ES);
     if (best < 0 || t < *us) { *us = t; best = i; }
   }
   return best;

@@ -1,6 +1,7 @@
 // Which layers take conv_small_kernel (conv_small.h), and with which tile.  Host arithmetic only.
 #pragma once
 #include "octo_internal.h"
+#include "conv_flow_choice.h"
 #include <algorithm>
 
 namespace octo {
@@ -24,13 +25,18 @@ inline bool small_fits(const ConvArgs& a, int ES) {
          (2LL * a.H * a.W + 1024LL * a.stride_h * a.stride_w + (long long)a.pad_h * a.W + a.pad_w) * a.x_ld * ES < 0x7FFFFFF0LL;
 }
 
-// Time of a launch in us from a graph, fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output channels, 1x1 and 3x3 of stride 1 and 2, with and
-// without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16, 256 compute units; residual error 4 - 7 %): a constant, what a
-// compute unit does - its tiles, half way between their mean and the next whole number, times K steps and an epilogue -, a latency per K
-// step and the memory traffic; with input channels in whole K steps, and not.  Over those layers the tile of the smallest estimate loses
-// 0.8 % against the fastest one.
+// Time of a launch in us in its place in a cascade: see tile_cost_us, which has the form and what it was fitted to (here with 3x3 layers of stride 1 of up to four tiles of 64 x 64 per compute unit besides: 0.95 of the time with the former choice among these tiles).
+constexpr TileCost SMALL_COST[5] = {
+    {32, 32, 2.912, 0.079, 0.202, 0.094, 0.000, 0.0},
+    {32, 64, 3.328, 0.112, 0.258, 0.083, 0.000, 0.0},
+    {64, 32, 3.170, 0.115, 0.253, 0.080, 0.000, 0.0},
+    {64, 64, 3.293, 0.132, 0.525, 0.089, 0.002, 0.0069},
+    {128, 64, 3.247, 0.133, 0.816, 0.124, 0.037, 0.0215}};
+// Otherwise, and fp32: from a graph, input channels in whole K steps, and not.  A constant, what a compute unit does - its tiles, half way between their mean and the next whole
+// number, times K steps and an epilogue -, a latency per K step and the memory traffic.  Fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output channels,
+// 1x1 and 3x3 of stride 1 and 2, with and without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16; residual error 4 - 7 %).
 struct SmallCost { int bc, bp; double base, step, tile, latency, per_mb; };
-constexpr SmallCost SMALL_COST[2][5] = {
+constexpr SmallCost SMALL_COST_REPEATED[2][5] = {
     {{32, 32, 2.317, 0.071, 0.250, 0.054, 0.004},
      {32, 64, 2.447, 0.114, 0.287, 0.037, 0.018},
      {64, 32, 2.547, 0.115, 0.261, 0.026, 0.010},
@@ -41,7 +47,7 @@ constexpr SmallCost SMALL_COST[2][5] = {
      {64, 32, 2.686, 0.105, 0.401, 0.100, 0.004},
      {64, 64, 2.891, 0.167, 0.696, 0.066, 0.020},
      {128, 64, 2.682, 0.273, 1.154, 0.022, 0.074}}};
-// The same in fp32 (steps of 32 values): input channels in whole K steps, windows that are not, 1x1 layers that are not.  Fitted to 520 layers
+// fp32 (steps of 32 values): input channels in whole K steps, windows that are not, 1x1 layers that are not.  Fitted to 520 layers
 // (4 .. 768 input, 16 .. 512 output channels, 0.04 .. 60 tiles of 64 x 64 per compute unit; residual error 3 - 6 %); 128 x 64 tiles give nothing there.
 constexpr SmallCost SMALL_COST_F32[3][4] = {
     {{32, 32, 2.159, 0.136, 0.337, 0.079, -0.003},
@@ -56,19 +62,21 @@ constexpr SmallCost SMALL_COST_F32[3][4] = {
      {32, 64, 2.446, 0.277, 0.453, 0.031, 0.033},
      {64, 32, 2.519, 0.249, 0.361, 0.047, 0.060},
      {64, 64, 2.705, 0.475, 0.479, 0.052, 0.085}}};
-// The row of SMALL_COST (fp32: SMALL_COST_F32) with the smallest estimate for M output pixels.
-inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, double* us) {
-  int best = 0;
-  const int any = a.Cin % (128 / ES) == 0 ? 0 : ES == 4 && a.kh == 1 && a.kw == 1 && !a.pad_h ? 2 : 1;
+inline double small_cost_us(const SmallCost& c, const ConvArgs& a, long long M, int num_cu, int ES) {
   const double nk = (a.K + 128 / ES - 1) / (128 / ES);
   const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
   const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
+  const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
+  const double per_cu = std::max(1.0, 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu)));
+  return c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk + c.per_mb * mb;
+}
+// The tile (launch_small's number) with the smallest estimate for M output pixels.
+inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, double* us) {
+  int best = 0;
+  const int any = a.Cin % (128 / ES) == 0 ? 0 : ES == 4 && a.kh == 1 && a.kw == 1 && !a.pad_h ? 2 : 1;
   for (int i = 0; i < (ES == 4 ? 4 : 5); ++i) {
-    const SmallCost& c = ES == 4 ? SMALL_COST_F32[any][i] : SMALL_COST[any][i];
-    const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
-    double per_cu = 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu));
-    if (per_cu < 1.0) per_cu = 1.0;
-    const double t = c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk + c.per_mb * mb;
+    const double t = ES == 4 ? small_cost_us(SMALL_COST_F32[any][i], a, M, num_cu, 4)
+                             : by_place(a) ? tile_cost_us(SMALL_COST[i], a, M, num_cu) : small_cost_us(SMALL_COST_REPEATED[any][i], a, M, num_cu, 2);
     if (i == 0 || t < *us) { *us = t; best = i; }
   }
   return best;
@@ -105,22 +113,23 @@ inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us
   return best;
 }
 
-// Up to how many tiles of 64 x 64 per compute unit the kernel is the faster one (us here : the kernel that took the layer before; both from a
-// graph).  M: output pixels.
+// Up to how many tiles of 64 x 64 per compute unit a layer is one of few tiles: split-K is asked, and where conv_flow_kernel does not fit or the channels end
+// inside a K step, and for single layers, this kernel takes the layer (us here : the kernel that took it before, from a graph unless said).  M: output pixels.
 //   * windows (3x3, strides): 2.75; into one channel tile, or with steps across taps, 1.96: beyond, some unit has a third tile.  128 -> 256, stride 2 on 5 x 80 x 80 at 1.95 9.4 : 11.8, 256 -> 256 on 20 x 40 x 40 1.95 15.1 : 18.7, 192 -> 256 on 28 x 40 x 41 2.9 18.3 : 19.8,
-//     96 -> 192 on 9 x 57 x 83 at 2.0 12.3 : 12.1, 128 -> 64 on 82 x 40 x 40 at 2.0 13.8 : 15.2, 32 -> 64 on 8 x 320 x 320 at 12.5 24.2 : 24.4, on 64 207 : 188;
-//   * 1x1 layers in whole K steps: 3, one step 4.5.  1024 -> 512 on 7 x 28 x 29 at 2.8 11.6 : 12.4, 256 -> 255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on
-//     61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 192 on 4 x 80 x 82 at 4.8 6.5 : 7.5.  With channel tiles less than three
-//     quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x 39 at 1.76 4.8 : 5.3);
+//     96 -> 192 on 9 x 57 x 83 at 2.0 12.3 : 12.1, 128 -> 64 on 82 x 40 x 40 at 2.0 13.8 : 15.2.  Up to five steps across taps 16
+//     in place: 32 -> 64, stride 2 on 8 x 320 x 320 at 12.5 24.2 : 24.4, in place 23.1 : 28.2, on 16 at 25 49.0 : 47.6, on 64 207 : 188;
+//   * 1x1 layers in whole K steps: 3, one step 4.5, or 24 into more channels than conv_flow_kernel takes.  1024 -> 512 on 7 x 28 x 29 at 2.8 11.6 : 12.4, 256 -> 255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on
+//     61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 456 with residual on 2 x 63 x 93 at 5.7 7.0 : 11.4.  With channel
+//     tiles less than three quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x 39 at 1.76 4.8 : 5.3);
 //   * 1x1 layers that end inside a step: 2.75 up to eight steps (32 -> 256 on 80 x 81 at 1.6 4.6 : 9.3, 24 -> 256 on 142 x 8 x 10 at 2.8 5.6 : 8.1), 1.25 with
 //     more, whose every step has the taps to work out;
 //   * up to 32 output channels 3: 256 -> 32 on 38 x 28 x 28 at 1.8 3.9 : 6.8, 320 -> 32 on 4 x 112 x 113 at 3.1 6.4 : 9.5.
 inline double small_limit(const ConvArgs& a) {
   const int nk = (a.K + 63) / 64;
   if (a.Cout <= 32) return 3.0;
-  if (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h) return a.Cout <= 64 || a.Cin % 64 ? 1.96 : 2.75;
+  if (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h) return a.in_place && a.Cin % 64 && nk <= 5 ? 16.0 : a.Cout <= 64 || a.Cin % 64 ? 1.96 : 2.75;
   if (a.Cin % 64) return nk <= 8 ? 2.75 : 1.25;
-  if (nk == 1) return 4.5;
+  if (nk == 1) return a.Cout > 256 ? 24.0 : 4.5;
   return a.Cout * 4 < (a.Cout + 63) / 64 * 64 * 3 ? 1.75 : 3.0;
 }
 inline bool small_takes(const ConvArgs& a, long long M, int num_cu) {

@@ -54,6 +54,7 @@ struct ConvArgs {
   void* up_y;
   int up_next;                    // host only: an upsampling of the output follows; the split-K kernel is chosen as if it were to write it
   int up_ld, up_coff;
+  int in_place;                   // host only: one launch of many; its input was written by the launch before and comes from beyond the L2s
   // 8-bit floating point storage only: y = act(acc * scale[c] + bias[c] (+ res * res_scale)), stored as
   // E4M3(y * y_inv_scale) unless out_f32.  scale: device, one factor per output channel, padded like the bias.
   const float* scale;

@@ -572,7 +572,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (L.n_in == 2) { const TensorView r = view_of(m, L.in[1]); a.res = r.ptr; a.res_ld = r.ld; a.res_coff = r.coff; }
       if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
-      a.up_next = lp.up_next;
+      a.up_next = lp.up_next; a.in_place = 1;
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (lp.fuse_twin) {
         const TensorView y2 = view_of(m, i + 2);
