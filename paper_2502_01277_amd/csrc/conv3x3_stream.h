@@ -255,13 +255,16 @@ hipError_t launch_stream3_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int*
 // 21 against 18), with up to 32 channels and a quarter of the weights after one and a half.  64 -> 64 with residual on
 // 600 x 56 x 56: 179 us, 4.1 TB/s (conv3x3_mid_kernel 248); 48 -> 48 with residual on 32 x 320 x 320: 237 us (395, general kernel
 // 440); 32 -> 32 with residual on 64 x 160 x 160: 64 us, 4.9 TB/s (109, 117 on the patch kernel before it).
+// In its place in a cascade, where the first pixels come late, 64 -> 64 turns later (here : conv3x3_mid_kernel): without residual 8 x 160 x 160 28.0 : 24.8,
+// 96 x 56 x 56 28.0 : 23.7, 192 x 64 x 32 29.2 : 28.0, 16 x 160 x 160 41.2 : 40.5, 256 x 56 x 56 67 : 76; with residual 96 x 56 x 56 28.4 : 27.9, 128 x 56 x 56
+// 37.7 : 41.3.
 template <typename T>
 hipError_t launch_stream3(const ConvArgs& a, long long M, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (a.Cin < 24 || a.Cin > 64 || a.Cout > 64 || ((a.Cout | a.y_ld | a.y_coff) & 7) || ((uintptr_t)a.y & 15) ||
       (a.res && (((a.res_ld | a.res_coff) & 7) || ((uintptr_t)a.res & 15)))) return hipErrorNotSupported;
   const bool narrow = a.Cout <= 32;
   if (narrow && a.Cin > 32) return hipErrorNotSupported;
-  if (M < (long long)(narrow ? 256 * 3 : 128 * (a.Cin <= 32 ? 3 : 6)) * num_cu) return hipErrorNotSupported;
+  if (M < (long long)(narrow ? 256 * 3 : 128 * (a.Cin <= 32 ? 3 : !a.in_place || a.Cin <= 48 ? 6 : a.res ? 10 : 13)) * num_cu) return hipErrorNotSupported;
   if (narrow) return launch_stream3_cfg<T, 1, 2, 4, 6, 3, 2>(a, num_cu, s, kernel_id, tm);
   if (a.Cin <= 32) return launch_stream3_cfg<T, 2, 2, 4, 3, 3, 3>(a, num_cu, s, kernel_id, tm);
   if (a.Cin <= 48) return launch_stream3_cfg<T, 2, 3, 8, 6, 4, 2>(a, num_cu, s, kernel_id, tm);
