@@ -1,4 +1,5 @@
-// Convolution for launches of up to about two tiles per compute unit, and of any size in fp32: an implicit GEMM written for few instructions per wavefront.
+// Convolution for launches of up to about two tiles per compute unit, for layers in a cascade whose operands come late, and for fp32 of any size: an implicit GEMM written for
+// few instructions per wavefront.
 //
 // Such a launch is one round of workgroups, and its time is what one of them takes from its first instruction to its last store. A
 // wavefront alone on its SIMD issues an instruction every four cycles at best, so that time is mostly a count of instructions: of the
