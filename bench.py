@@ -108,54 +108,49 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "14d56313a6cb2f0c": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4368196494,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1700410848,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 283087895,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344684480,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1483328727,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553384375,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 850076891,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355622832,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281956092,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2205559289,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 993599491,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1911041791,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629432716,
-        "octo::conv_flow_kernel<__bf16, 256, 128, 64, 2, 8, 3, 2, 1>": 1255826470,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1080664148,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167938870,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628534044,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 128, 2, 8, 3, 1, 0>": 127803976,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838936,
-        "octo::conv3x3_stream_kernel<_Float16, 2, 4, 8, 6, 3, 2>": 69134432,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 22856340,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 28733948,
-        "octo::conv1x1_stream_kernel<_Float16, 2>": 29071916,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 0>": 30064036,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 0>": 15727913,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 9942841,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87615897,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28526532,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 2>": 77745138,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64520875,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 128, 2, 8, 3, 1, 1>": 21159503,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 1>": 31501762,
-        "octo::conv_mfma_kernel<_Float16, 64, 64, 2, 2, 8, 2, 3, true, true, true>": 24369370,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 40873137,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 0>": 40072658,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39777863,
-        "octo::conv_flow_kernel<_Float16, 512, 96, 256, 1, 8, 3, 1, 1>": 19105781,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 7136851,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 16510200,
-        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376766,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355741,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644826,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223610,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 2>": 7253458,
-        "octo::conv_ksplit_kernel<_Float16, 2, 1, 4, 4>": 4730478,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506823,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 18699675,
+    "e4e5abd8fc8132f7": {
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910876852,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2204265079,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553359597,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629442057,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 993490044,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1079729678,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 272025729,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344670365,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 556106527,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 850163705,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 306417854,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167965400,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 111357444,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355743997,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4368702873,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 2241640183,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1701880699,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838926,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87622590,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 77496298,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 39766269,
+        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376770,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39760323,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 15369514,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 27242084,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 9042494,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 47325814,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 17235789,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 14334212,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 19422840,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 34379692,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14221657,
+        "octo::conv_small_kernel<_Float16, 32, 64, 1, 4, 4, 1>": 18644102,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64431420,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506210,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 22345623,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28510945,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223606,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355740,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644813,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123417,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4642418,
     },
 }
 
