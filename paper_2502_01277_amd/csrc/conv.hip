@@ -281,8 +281,9 @@ __global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs
 #pragma unroll
       for (int d = 0; d < D; ++d) OCTO_CONV_DMA(d, d)
       for (int kb = 0; kb < nk; ++kb) {
-        // loads of the D - 1 later steps may stay in flight; those of step kb (issued before them) are complete
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((D - 1) * NL) : "memory");
+        // loads of the D - 1 later steps may stay in flight; those of step kb (issued before them) are complete, and so are this wavefront's reads of
+        // step kb - 1 (said here: the compiler's own wait for them goes with the matrix instructions, which no barrier holds)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((D - 1) * NL) : "memory");
         __builtin_amdgcn_s_barrier();    // everyone's part of step kb is in LDS, and everyone is done reading step kb - 1
         OCTO_CONV_DMA(kb + D, st_wr)     // refills the stage that step kb - 1 read; past the last step: zeros, never read
         const u32x4* pa = smem + st_rd * STAGE_VECS_OP;

@@ -243,12 +243,13 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
     };
     int s = NS - 1;                                      // steps requested
     for (; s < a.nk; ++s) {
-      // the stage of the step before is free behind the barrier: its fragments were in registers before that step's matrix instructions
-      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NS - 2) * NL) : "memory");
+      // the stage of the step before is free behind the barrier: every wavefront's fragments of it have returned (lgkmcnt; matrix instructions are
+      // no memory accesses, and the compiler may move them, and its own wait for what they read, past this one)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((NS - 2) * NL) : "memory");
       __builtin_amdgcn_s_barrier();
       compute(issue);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     for (s -= NS - 1; s < a.nk; ++s) compute([] {});
 
