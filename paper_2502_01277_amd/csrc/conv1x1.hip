@@ -13,7 +13,7 @@
 // LDS rows (a pixel's or an output channel's K values) have an odd pitch in 16-byte vectors: reads of one vector of 32
 // rows hit all banks evenly.
 #include "mfma_common.h"
-#include "conv_flow_choice.h"
+#include "conv_small_choice.h"
 #include <hip/hip_ext.h>
 
 namespace octo {
@@ -242,13 +242,19 @@ hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipSt
   const long long hw = (long long)a.Ho * a.Wo, M = (a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n) * hw;
   const long long M_split = a.n_split > 0 ? (a.n_split < a.n ? a.n_split : a.n) * hw : M;
   if (flow_takes_1x1(a, M_split)) return hipErrorNotSupported;
-  // Several channel tiles read the pixels several times and need more of them.  Here : conv_flow_kernel (32 channels: general), us, by blocks
-  // times channel tiles of 64 per compute unit: 16 -> 32 at 3 3.9 : 4.6; 32 -> 64 at 2 4.8 : 4.5, at 3 4.9 : 5.5, at 4 5.1 : 6.1; 96 -> 64 at 3
+  // Several channel tiles read the pixels several times and need more of them.  Us, by blocks times channel tiles of 64 per compute unit.
+  // Here : conv_flow_kernel (32 channels: general): 16 -> 32 at 3 3.9 : 4.6; 32 -> 64 at 2 4.8 : 4.5, at 3 4.9 : 5.5, at 4 5.1 : 6.1; 96 -> 64 at 3
   // 5.7 : 5.8, at 4 5.9 : 6.6; 32 -> 96 at 4 5.6 : 5.1, at 5 5.6 : 6.0; 96 -> 192 at 5 6.9 : 6.7, at 6 7.1 : 6.9, at 7 7.2 : 7.5; 120 -> 128 at 4 6.2 : 5.7,
-  // at 5 6.5 : 6.8; 64 -> 128 at 6.2 6.1 : 5.2, at 7.7 6.4 : 5.5 (conv_small_kernel).  In their place in a cascade, where the input comes from beyond the L2s, against conv_small_kernel: 96 -> 96 at 6.2 9.9 : 6.7, at 25 14.0 :
-  // 15.6; 64 input channels, a whole K step there: 64 -> 64 at 12.5 11.8 : 8.3, at 25 14.5 : 11.4, at 50 21.3 : 21.3, at 100 43.7 : 42.4, in two tensors at 12.5
-  // 13.1 : 9.9, at 50 21.2 : 19.7, at 100 49.2 : 53.3; 64 -> 256 at 48 18.4 : 16.5 (conv_flow_kernel), with residual 19.9 : 18.1, at 192 37.0 : 40.8.
-  if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (a.Cin == 64 ? (a.in_place ? 48LL : 9LL) : a.Cout <= 64 ? 4LL : a.in_place ? 9LL : 6LL) * num_cu) return hipErrorNotSupported;
+  // at 5 6.5 : 6.8.
+  // In their place in a cascade, where the input comes from beyond the L2s, here : conv_small_kernel: 96 -> 96 at 6.2 9.9 : 6.7, at 25 14.0 : 15.6.
+  // 64 input channels, a whole K step, go to conv_small_kernel for longer, where it takes them (here : there): alone 64 -> 128 at 6.2 6.1 : 5.2, at 7.7
+  // 6.4 : 5.5, 64 -> 16 at 7 4.3 : 3.6, 64 -> 32 at 10.5 5.8 : 4.5; in place 64 -> 64 at 12.5 11.8 : 8.3, at 25 14.5 : 11.4, at 50 21.3 : 21.3, at 100 43.7 : 42.4, in
+  // two tensors at 12.5 13.1 : 9.9, at 50 21.2 : 19.7, at 100 49.2 : 53.3; 64 -> 256 at 48 18.4 : 16.5 (conv_flow_kernel), with residual 19.9 : 18.1, at
+  // 192 37.0 : 40.8; 64 -> 32 at 6.4 5.7 : 5.1, at 16 7.9 : 7.1, at 33 11.8 : 11.1, with residual at 41 16.7 : 14.8, at 59 15.7 : 15.1, 64 -> 8 at 72 16.3 : 17.1.
+  // Up to 32 channels before an upsampling, or of items counted on the device, have only the general kernel below the line (64 -> 32 in place at 6.4
+  // 5.7 : 7.1, at 33 11.8 : 14.5; alone at 7 4.3 : 5.4).
+  const bool step = a.Cin == 64 && small_fits(a, 2) && (a.Cout > 32 || (a.n_split == 0 && !a.up_next));
+  if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (step ? (a.in_place ? 48LL : 9LL) : a.Cout <= 64 ? 4LL : a.in_place ? 9LL : 6LL) * num_cu) return hipErrorNotSupported;
   return dtype == OCTO_F16 ? launch_stream_typed<_Float16>(a, M, num_cu, s, kernel_id, tm) : launch_stream_typed<__bf16>(a, M, num_cu, s, kernel_id, tm);
 }
 

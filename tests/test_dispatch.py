@@ -20,3 +20,29 @@ def test_fp32_splits_of_eight_stay_splits_of_eight(ids):
     assert ids(layers) == [SPLIT8] * len(cases)
     # and where both have four ahead, four it is
     assert ids([dict(dtype="f32", n=30, h=28, w=23, cin=104, cout=9, k=3), dict(dtype="f32", n=1, h=80, w=77, cin=68, cout=44, k=3)]) == [SPLIT4, SPLIT4_64]
+
+
+SMALL, STREAM = 13, 15
+
+
+def family(kid):
+    return kid // 100000000
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_narrow_outputs_of_one_k_step_have_a_kernel_on_both_sides_of_every_line(ids, dtype):
+    """1x1 layers of 64 channels into up to 32: conv_small_kernel below the streaming kernel's line, and where it does not take them the streaming kernel from four
+    blocks of 32 pixels per compute unit on; never the general kernel in between."""
+    layers, want = [], []
+    for cout in (8, 24, 32):
+        for place, line in ((0, 9), (1, 48)):
+            for res in (0, 2):
+                for blocks in (1, 3.9, 4.1, 5.9, 6.1, line - 0.1, line + 0.1):
+                    h = int(blocks * 256 * 32 / 64)
+                    common = dict(dtype=dtype, n=1, h=h, w=64, cin=64, cout=cout, res=res, place=place)
+                    layers += [common, dict(common, upsampled=1), dict(common, n=4, split=1, hint=2)]
+                    want += [SMALL if blocks < line else STREAM] + [STREAM if blocks > 4 else None] * 2
+    got = ids(layers)
+    assert min(got) > 0
+    bad = [(l, g) for l, g, w in zip(layers, got, want) if w and family(g) != w]
+    assert not bad, bad[:3]

@@ -20,6 +20,7 @@ CASES = [
     (2, 56, 57, 24, 256, 1, 1, nn.ACT_RELU, nn.RES_NONE, 8, 0, 132),                      # part of one K step
     (1, 81, 80, 200, 40, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 0, 1320640322),          # 64 x 32, 8 of the fourth step
     (6, 28, 27, 256, 24, 1, 1, nn.ACT_SILU, nn.RES_NONE, 0, 8, 1300320322),               # less than 32 channels
+    (15, 61, 59, 64, 24, 1, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 8, 1300320641),          # the same of one K step, beyond three tiles per compute unit
     (5, 80, 79, 64, 64, 3, 1, nn.ACT_SILU, nn.RES_AFTER_ACT, 0, 64, 1310640642),          # nine taps of one step
     (2, 7, 9, 128, 264, 3, 1, nn.ACT_RELU, nn.RES_BEFORE_ACT, 0, 0, 131),
     (8, 57, 83, 96, 192, 3, 2, nn.ACT_SILU, nn.RES_NONE, 0, 0, 132),                      # steps across taps
