@@ -122,14 +122,17 @@ inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us
 //     61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 456 with residual on 2 x 63 x 93 at 5.7 7.0 : 11.4.  With channel
 //     tiles less than three quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x 39 at 1.76 4.8 : 5.3);
 //   * 1x1 layers that end inside a step: 2.75 up to eight steps (32 -> 256 on 80 x 81 at 1.6 4.6 : 9.3, 24 -> 256 on 142 x 8 x 10 at 2.8 5.6 : 8.1), 1.25 with
-//     more, whose every step has the taps to work out;
+//     more, whose every step has the taps to work out; in place up to three steps 4.5, as far as the line of the streaming kernel there (this kernel : it :
+//     conv_flow_kernel, 16 -> 128 on 160 x 146 at 2.9 6.1 : 7.1 : 7.4, 96 -> 96 on 16 x 52 x 32 at 3.3 6.6 : 8.5 : 8.4, 120 -> 320 on 4 x 60 x 52 at 3.8 8.2 : 10.5 : 9.0, 184 -> 128
+//     on 42 x 28 x 29 at 4.2 10.0 : 12.2 : 11.2, 48 -> 184 with residual on 2 x 97 x 125 at 4.4 8.6 : 9.5 : 10.3; the other way round 16 -> 128 on 148 x 14 x 16 at 4.1
+//     7.8 : 7.4 : 9.1);
 //   * up to 32 output channels 3: 256 -> 32 on 38 x 28 x 28 at 1.8 3.9 : 6.8, 320 -> 32 on 4 x 112 x 113 at 3.1 6.4 : 9.5; 1x1 layers of one K step as far as the
 //     line of launch_conv1x1_stream, which has the times on both sides.
 inline double small_limit(const ConvArgs& a) {
   const int nk = (a.K + 63) / 64;
   if (a.Cout <= 32) return a.Cin == 64 && nk == 1 && a.stride_h == 1 && !a.pad_h ? (a.in_place ? 24.0 : 4.5) : 3.0;
   if (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h) return a.in_place && a.Cin % 64 && nk <= 5 ? 16.0 : a.Cout <= 64 || a.Cin % 64 ? 1.96 : 2.75;
-  if (a.Cin % 64) return nk <= 8 ? 2.75 : 1.25;
+  if (a.Cin % 64) return a.in_place && nk <= 3 ? 4.5 : nk <= 8 ? 2.75 : 1.25;
   if (nk == 1) return a.Cout > 256 ? 24.0 : 4.5;
   return a.Cout * 4 < (a.Cout + 63) / 64 * 64 * 3 ? 1.75 : 3.0;
 }

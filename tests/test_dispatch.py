@@ -46,3 +46,13 @@ def test_narrow_outputs_of_one_k_step_have_a_kernel_on_both_sides_of_every_line(
     assert min(got) > 0
     bad = [(l, g) for l, g, w in zip(layers, got, want) if w and family(g) != w]
     assert not bad, bad[:3]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_broken_k_steps_in_a_model_go_from_one_kernel_to_the_next(ids, dtype):
+    """1x1 layers whose channels end inside a K step, into several channel tiles, in a model: conv_small_kernel up to the streaming kernel's line; conv_flow_kernel,
+    which loses to both there, has none of them."""
+    layers = [dict(dtype=dtype, n=1, h=int(b * 256 * 32 / ((cout + 63) // 64) / 16), w=16, cin=cin, cout=cout, res=res, place=1, second=second)
+              for cin, cout in ((16, 128), (48, 96), (96, 96), (96, 192), (120, 128), (184, 320)) for b in (5, 6, 7, 8, 8.9, 9.1, 10) for res, second in ((0, 0), (2, 0), (0, 32))]
+    want = [SMALL if (l["h"] * 16 + 31) // 32 * ((l["cout"] + 63) // 64) < 9 * 256 else STREAM for l in layers]
+    assert [family(k) for k in ids(layers)] == want
