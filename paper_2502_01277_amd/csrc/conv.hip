@@ -603,7 +603,7 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   if constexpr (sizeof(T) == 4) {
     if (small_fits(a, 4) && small_takes_f32(a, M_split, num_cu)) {
       double us = 0;
-      const int which = small_choose(a, M_split, num_cu, 4, &us);
+      const int which = small_choose(a, M_split, num_cu, 4, false, &us);
       int ks = small_split_f32(a, M_split, num_cu, us);
       // Shorter sums round less: where the estimates that serve the other types have a split of eight ahead, one of four is no faster than it to speak of,
       // and eight it is (eight : four, us: 3x3 60 .. 130 K steps into 32 x 32 tiles 36.1 : 35.5, 42.4 : 42.0, 63.9 : 64.0, over 40 layers 1.01 of the
@@ -615,14 +615,17 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
       return ks >= 0 ? launch_ksplit<T>(ks, a, num_cu, s, kernel_id, tm) : launch_small_f32(which, a, num_cu, s, kernel_id, tm);
     }
   }
+  // Split-K or not is decided from estimates of repeated launches for M_split, in a cascade too: a layer of a model and a single call sum in one order there.  Over
+  // 726 layers of few tiles in their place that choice, then the tile by place, takes 1.013 of the fastest kernel's time (by the estimates in place times
+  // 0.80 .. 0.92 1.015 .. 1.044, never splitting 1.031).
   // Launches of few tiles go to conv_small_kernel, or to split-K where that is estimated to be faster; small_limit and TileCost have the lines.
-  // conv_flow_kernel and the general kernel sum in the order of conv_small_kernel, so that the running count may choose between those (not where
-  // a last vector has less than eight channels, whose values they convert one by one); against split-K and the patch kernel it is M_split.
+  // conv_flow_kernel and the general kernel sum in the order of conv_small_kernel, so that place and running count may choose between those (the count not where
+  // a last vector has less than eight channels, whose values they convert one by one); against the patch kernel it is M_split as well.
   bool to_small = false, not_split = false;
   [[maybe_unused]] const long long M_small = a.Cout % 8 || a.Cout <= 32 ? M_split : M;
   [[maybe_unused]] auto run_small = [&](long long m) -> hipError_t {
     double us = 0;
-    const int which = small_choose(a, m, num_cu, 2, &us);
+    const int which = small_choose(a, m, num_cu, 2, by_place(a), &us);
     return std::is_same<T, __bf16>::value ? launch_small_bf16(which, a, num_cu, s, kernel_id, tm) : launch_small_f16(which, a, num_cu, s, kernel_id, tm);
   };
   [[maybe_unused]] const bool pipe_ok = sizeof(T) == 2, pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
@@ -638,28 +641,27 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
       if (em != hipErrorNotSupported) return em;
     }
     // (up to 32 channels only where the count is not taken on the device; not before an upsampling, which the split-K kernel writes along)
-    if (patch || (fits && !a.up_next && (a.Cout > 32 || a.n_split == 0) && small_takes(a, M_split, num_cu))) {
+    to_small = fits && (a.Cout > 32 || (a.n_split == 0 && !a.up_next));
+    if (patch || (to_small && !a.up_next && small_takes(a, M_split, num_cu, false))) {
       // Split-K has to beat every other kernel: below the patch kernel's line, never where one round of tiles fills the chip, and
       // conv_flow_kernel's estimate (96 -> 192, stride 2 on 9 x 57 x 83: split-K 14.1, estimated 12.1, conv_flow_kernel 13.3)
       double us = 0, uf = 0;
-      small_choose(a, M_split, num_cu, 2, &us);
-      if (!patch && flow_fits(a)) { flow_choose(a, M_split, num_cu, &uf); us = std::min(us, uf); }
-      us = repeated_us(a, us);
+      small_choose(a, M_split, num_cu, 2, false, &us);
+      if (!patch && flow_fits(a)) { flow_choose(a, M_split, num_cu, 2, false, &uf); us = std::min(us, uf); }
       const bool few = patch ? (double)M_split / 128 * ((a.Cout + 63) / 64) < 0.25 * num_cu : !stays(M_split);
       const int kf = few ? ksplit_best(a, M_split, 2, num_cu, us, pw ? 3 : 4, 4.0) : -1;
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
       if (patch) return run_small(M_split);
       not_split = true;
     }
-    to_small = fits && (not_split || a.Cout > 32);
     // (two layers in one launch: by small_limit; beyond it conv_flow_kernel's best tile takes 1.03 .. 1.1 of this kernel's time)
     if (to_small && by_place(a) && a.split == 0 && flow_fits(a)) {
       double us = 0, uf = 0;
-      small_choose(a, M_small, num_cu, 2, &us);
-      flow_choose(a, M_small, num_cu, &uf);
+      small_choose(a, M_small, num_cu, 2, true, &us);
+      flow_choose(a, M_small, num_cu, 2, true, &uf);
       to_small = us <= uf;
     } else if (to_small) {
-      to_small = small_takes(a, M_small, num_cu);
+      to_small = small_takes(a, M_small, num_cu, a.in_place);
     }
   }
   // Only the split-K kernel writes an upsampled copy.  Where its estimate is below that of the general kernel's tile one launch beats
@@ -684,18 +686,17 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
       double us = 0;
       int kf = -1;
       if (!not_split && !stays(M_split)) {
-        flow_choose(a, M_split, num_cu, &us);
-        if (by_place(a) && small_fits(a, 2)) { double uf = 0; small_choose(a, M_split, num_cu, 2, &uf); us = std::min(us, uf); }
-        // Against these kernels split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
+        flow_choose(a, M_split, num_cu, 2, false, &us);
+        // Against this kernel split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
         // on 7 x 40 x 40 at 4.1 38.0 : 28.0, 512 -> 64 1x1 on 82 x 20 x 20 at 4.0 11.1 : 8.2).  Its 64 x 64 tiles serve long reductions (256 -> 256,
         // stride 2 on 6 x 40 x 40 11.0 : 13.8), not 1x1 layers (512 -> 512 on 5 x 20 x 20 7.3 : 5.8, 1024 -> 512 8.7 : 7.3), where this kernel's
         // estimate is 15 % high while it has few tiles.
-        kf = ksplit_best(a, M_split, 2, num_cu, repeated_us(a, pw ? 0.85 * us : us), pw ? 3 : 4, 4.0);
+        kf = ksplit_best(a, M_split, 2, num_cu, pw ? 0.85 * us : us, pw ? 3 : 4, 4.0);
       }
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
       if (to_small) return run_small(M_small);
       if (!by_place(a) && stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
-      const int which = flow_choose(a, M, num_cu, &us);
+      const int which = flow_choose(a, M, num_cu, 2, by_place(a), &us);
       return std::is_same<T, __bf16>::value ? launch_flow_bf16(which, a, num_cu, s, kernel_id, tm) : launch_flow_f16(which, a, num_cu, s, kernel_id, tm);
     }
   }
@@ -754,7 +755,7 @@ static hipError_t launch_f8(const ConvArgs& a, int num_cu, hipStream_t s, int* k
   // 142 x 75 x 96 60.5 : 32.7, 16 -> 648, stride 2 on 780 x 33 x 37 202 : 131; over 164 such layers 0.80 of the general kernel's time.
   if (flow_fits(a, 1) && (a.Cout >= 48 ? a.K > 64 || a.Cout > 64 || a.Cout % 16 : a.Cin >= 96)) {
     double us = 0;
-    return launch_flow_f8(flow_choose(a, M, num_cu, &us, 1), a, num_cu, s, kernel_id, tm);
+    return launch_flow_f8(flow_choose(a, M, num_cu, 1, false, &us), a, num_cu, s, kernel_id, tm);
   }
   if (t.bc == 128) return launch_cfg<f8, 128, 128, 2, 2, 8, 1, 2, true, true>(a, num_cu, s, kernel_id, tm);
   if (t.bp == 256) return launch_cfg<f8, 64, 256, 1, 4, 4, 1, 3, true, true>(a, num_cu, s, kernel_id, tm);

@@ -22,7 +22,7 @@ inline bool flow_fits(const ConvArgs& a, int ES = 2) {
          (2LL * a.H * a.W + 1024LL * a.stride_h * a.stride_w + (long long)a.pad_h * a.W + a.pad_w) * a.x_ld * ES < 0x7FFFFFF0LL;
 }
 
-// Is the tile chosen by tile_cost_us?
+// Is a layer's tile chosen by tile_cost_us?
 inline bool by_place(const ConvArgs& a) { return a.in_place && a.Cin % 64 == 0; }
 // Time of a launch in us in its place in a cascade, 16-bit types, input channels in whole K steps: a constant, what a compute unit does - its tiles, a quarter of the way from the next whole number to
 // their mean, times K steps and an epilogue -, a latency per K step where no unit has a second tile, the memory traffic, and the operands that the
@@ -41,8 +41,6 @@ inline double tile_cost_us(const TileCost& c, const ConvArgs& a, long long M, in
   const double mb = 2e-6 * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1)), operands = 128e-6 * tiles * nk * (c.bc + c.bp);
   return c.base + per_cu * (nk * c.step + c.tile) + (tiles <= num_cu ? c.latency * nk : 0.0) + c.per_mb * mb + c.per_operand_mb * operands;
 }
-// What such a launch takes when it is repeated on the same tensors: the split-K kernel's estimates, fitted to that, are compared with this.
-inline double repeated_us(const ConvArgs& a, double us) { return by_place(a) ? 0.88 * us : us; }
 constexpr TileCost FLOW_COST[8] = {
     {64, 64, 3.777, 0.169, 0.522, 0.082, 0.002, 0.0},
     {64, 128, 3.928, 0.236, 0.874, 0.107, 0.028, 0.0062},
@@ -74,12 +72,12 @@ inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, in
   const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
   return c.base + per_cu * (nk * (c.step + (a.Cin % (128 / ES) ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * nk : 0.0) + c.per_mb * mb;
 }
-// The tile (launch_flow's number) with the smallest estimate for M output pixels.
-inline int flow_choose(const ConvArgs& a, long long M, int num_cu, double* us, int ES = 2) {
+// The tile (launch_flow's number) with the smallest estimate for M output pixels, in place or repeated.
+inline int flow_choose(const ConvArgs& a, long long M, int num_cu, int ES, bool place, double* us) {
   int best = -1;
   for (int i = 0; i < 8; ++i) {
     if (ES == 2 && a.K <= 64 && a.Cout > FLOW_COST[i].bc) continue;
-    const double t = ES == 2 && by_place(a) ? tile_cost_us(FLOW_COST[i], a, M, num_cu) : flow_cost_us(FLOW_COST_REPEATED[i], a, M, num_cu, ES);
+    const double t = place ? tile_cost_us(FLOW_COST[i], a, M, num_cu) : flow_cost_us(FLOW_COST_REPEATED[i], a, M, num_cu, ES);
     if (best < 0 || t < *us) { *us = t; best = i; }
   }
   return best;

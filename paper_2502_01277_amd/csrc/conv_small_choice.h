@@ -70,13 +70,13 @@ inline double small_cost_us(const SmallCost& c, const ConvArgs& a, long long M, 
   const double per_cu = std::max(1.0, 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu)));
   return c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk + c.per_mb * mb;
 }
-// The tile (launch_small's number) with the smallest estimate for M output pixels.
-inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, double* us) {
+// The tile (launch_small's number) with the smallest estimate for M output pixels, in place or repeated.
+inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, bool place, double* us) {
   int best = 0;
   const int any = a.Cin % (128 / ES) == 0 ? 0 : ES == 4 && a.kh == 1 && a.kw == 1 && !a.pad_h ? 2 : 1;
   for (int i = 0; i < (ES == 4 ? 4 : 5); ++i) {
     const double t = ES == 4 ? small_cost_us(SMALL_COST_F32[any][i], a, M, num_cu, 4)
-                             : by_place(a) ? tile_cost_us(SMALL_COST[i], a, M, num_cu) : small_cost_us(SMALL_COST_REPEATED[any][i], a, M, num_cu, 2);
+                             : place ? tile_cost_us(SMALL_COST[i], a, M, num_cu) : small_cost_us(SMALL_COST_REPEATED[any][i], a, M, num_cu, 2);
     if (i == 0 || t < *us) { *us = t; best = i; }
   }
   return best;
@@ -128,16 +128,16 @@ inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us
 //     7.8 : 7.4 : 9.1);
 //   * up to 32 output channels 3: 256 -> 32 on 38 x 28 x 28 at 1.8 3.9 : 6.8, 320 -> 32 on 4 x 112 x 113 at 3.1 6.4 : 9.5; 1x1 layers of one K step as far as the
 //     line of launch_conv1x1_stream, which has the times on both sides.
-inline double small_limit(const ConvArgs& a) {
+inline double small_limit(const ConvArgs& a, bool place) {
   const int nk = (a.K + 63) / 64;
-  if (a.Cout <= 32) return a.Cin == 64 && nk == 1 && a.stride_h == 1 && !a.pad_h ? (a.in_place ? 24.0 : 4.5) : 3.0;
-  if (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h) return a.in_place && a.Cin % 64 && nk <= 5 ? 16.0 : a.Cout <= 64 || a.Cin % 64 ? 1.96 : 2.75;
-  if (a.Cin % 64) return a.in_place && nk <= 3 ? 4.5 : nk <= 8 ? 2.75 : 1.25;
+  if (a.Cout <= 32) return a.Cin == 64 && nk == 1 && a.stride_h == 1 && !a.pad_h ? (place ? 24.0 : 4.5) : 3.0;
+  if (a.kh > 1 || a.kw > 1 || a.stride_h > 1 || a.pad_h) return place && a.Cin % 64 && nk <= 5 ? 16.0 : a.Cout <= 64 || a.Cin % 64 ? 1.96 : 2.75;
+  if (a.Cin % 64) return place && nk <= 3 ? 4.5 : nk <= 8 ? 2.75 : 1.25;
   if (nk == 1) return a.Cout > 256 ? 24.0 : 4.5;
   return a.Cout * 4 < (a.Cout + 63) / 64 * 64 * 3 ? 1.75 : 3.0;
 }
-inline bool small_takes(const ConvArgs& a, long long M, int num_cu) {
-  return (double)((M + 63) / 64 * ((a.Cout + 63) / 64)) <= small_limit(a) * num_cu;
+inline bool small_takes(const ConvArgs& a, long long M, int num_cu, bool place) {
+  return (double)((M + 63) / 64 * ((a.Cout + 63) / 64)) <= small_limit(a, place) * num_cu;
 }
 // 3x3 layers of stride 1, against conv3x3_mid_kernel, which reads every pixel once for all nine taps: short reductions, up to 1.96 tiles of
 // 64 x 64 per compute unit.  64 -> 64 on 5 x 80 x 80 at 1.95 7.0 : 8.2, 64 -> 192 on 136 x 8 x 10 at 2.0 7.3 : 9.3, 128 -> 96 on 2 x 80 x 82 at 1.6 9.4 : 11.5, 128 -> 256

@@ -1,4 +1,7 @@
 """The lines between the convolution kernels, on both sides of them, by the ids that launch_conv returns (no GPU: see dispatch.py)."""
+import math
+import random
+
 import pytest
 
 import dispatch
@@ -56,3 +59,29 @@ def test_broken_k_steps_in_a_model_go_from_one_kernel_to_the_next(ids, dtype):
               for cin, cout in ((16, 128), (48, 96), (96, 96), (96, 192), (120, 128), (184, 320)) for b in (5, 6, 7, 8, 8.9, 9.1, 10) for res, second in ((0, 0), (2, 0), (0, 32))]
     want = [SMALL if (l["h"] * 16 + 31) // 32 * ((l["cout"] + 63) // 64) < 9 * 256 else STREAM for l in layers]
     assert [family(k) for k in ids(layers)] == want
+
+
+SPLIT, PATCHES = 16, (14, 17, 18)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_split_k_is_chosen_alike_for_a_layer_of_a_model_and_a_single_call(ids, dtype):
+    """Split-K adds in another order than the kernels between which the place may choose."""
+    r, step = random.Random(11), 4 if dtype == "f32" else 8
+    layers = []
+    while len(layers) < 4000:
+        k, stride = r.choice([(1, 1), (1, 1), (1, 2), (3, 1), (3, 2), (5, 2)])
+        cin = r.choice([step, 64]) * r.randint(1, 32)
+        cout = r.choice([8, 16, 64]) * r.randint(1, 24)
+        h = r.choice([1, 7, 14, 20, 40, 57, 80, 160]) * stride
+        n = max(1, int(256 * 4096 * math.exp(r.uniform(math.log(0.02), math.log(6))) / max(cout, 32) / (h // stride) ** 2))
+        if k * k * cin < 60000 and 2 * n * h * h * max(cin, cout) < 1 << 30:
+            layers.append(dict(dtype=dtype, n=n, h=h, w=h, cin=cin, cout=cout, k=k, stride=stride, res=r.choice([0, 0, 2]), upsampled=int(k == 1 and r.random() < 0.1),
+                               split=r.choice([0, 0, max(1, n // 2)]), hint=r.choice([0, 0, max(1, n // 3)])))
+    alone, place = ids(layers), ids([dict(l, place=1) for l in layers])
+    assert sum(family(k) == SPLIT for k in alone) > 300
+    differ = [(l, a, p) for l, a, p in zip(layers, alone, place) if a != p and SPLIT in (family(a), family(p))]
+    assert not differ, (len(differ), differ[:2])
+    # the others that differ: the lines and slices of the 3x3 kernels, else kernels of one order
+    others = {family(k) for a, p in zip(alone, place) if a != p and not (family(a) in PATCHES and family(p) in PATCHES) for k in (a, p)}
+    assert others <= {10, 11, 12, SMALL, STREAM}
