@@ -24,15 +24,19 @@ inline bool flow_fits(const ConvArgs& a, int ES = 2) {
 
 // Is a layer's tile chosen by tile_cost_us?
 inline bool by_place(const ConvArgs& a) { return a.in_place && a.Cin % 64 == 0; }
-// Time of a launch in us in its place in a cascade, 16-bit types, input channels in whole K steps: a constant, what a compute unit does - its tiles, a quarter of the way from the next whole number to
-// their mean, times K steps and an epilogue -, a latency per K step where no unit has a second tile, the memory traffic, and the operands that the
-// tiles fetch.
-//   There a layer's input was written by the kernel before and comes from beyond the L2s.  Fitted to launches traced over 14 batches of four cascades (1 .. 64 frames; 758 layers, 1x1 and strided, 16 .. 2048 channels, 0.03 .. 400 tiles of 64 x 64 per compute
-// unit), each layer in every tile.  Estimates from the same launch repeated on the same tensors (below) are 12 % low there and favour
-// large tiles: 128 -> 128 on 8 x 80 x 80, us, in place: 128 x 256 tiles of conv_flow_kernel 11.6, 128 x 128 12, 64 x 64 of conv_small_kernel 9.3, where three
-// workgroups per unit hide what one of eight wavefronts waits for; 256 -> 64 on that map 14.5 : 10.8, 256 -> 1024 with residual on 96 x 16 x 16 29.0 (256 x
-// 128) : 23.6 (128 x 64).  Over those layers the choice takes 0.945 of the time of the former one, the best tile of each 0.91; left out of the
-// fit one cascade at a time 0.944.
+// Time of a launch in us in its place in a cascade, 16-bit types, input channels in whole K steps: a constant, what a compute unit does - its tiles, a
+// quarter of the way from the next whole number to their mean, times K steps and an epilogue -, a latency per K step where no unit has a second
+// tile, the memory traffic, and the operands that the tiles fetch.
+//   There a layer's input was written by the kernel before and comes from beyond the L2s.  Estimates from the same launch repeated on the same tensors (below)
+// are low there and favour large tiles: 128 -> 128 on 8 x 80 x 80, us, in place: 128 x 256 tiles of conv_flow_kernel 11.6, 128 x 128 12, 64 x 64 of
+// conv_small_kernel 9.3, where three workgroups per unit hide what one of eight wavefronts waits for; 256 -> 64 on that map 14.5 : 10.8, 256 -> 1024 with
+// residual on 96 x 16 x 16 29.0 (256 x 128) : 23.6 (128 x 64).
+//   Fitted, without negative terms, to 1812 layers timed in every tile behind the launch that writes their input and 48 MB of other traffic (the 696 1x1 and
+// strided layers of four cascades, 1 .. 64 frames; 850 random ones, 64 .. 4096 channels, 0.05 .. 200 tiles of 64 x 64 per compute unit; 266 3x3 layers of few
+// tiles), then moved to where the choice loses least: 1.012 of the best tile's time over the cascades' layers, 1.013 over the random ones.  (On a half that the
+// search had not seen 1.011.)  The constants before came from cascades alone, 1.018 and 1.025 here; a tile had no cost per K step and others a negative
+// latency, and reductions that no cascade has lost up to 1.57: 1536 -> 1536 on 56 x 54 26.6 : 21.8, 3072 -> 512 on 11 x 28 x 28 44.8 : 37.2, 4096 -> 2048 on
+// 56 x 41 50.6 : 45.3.
 struct TileCost { int bc, bp; double base, step, tile, latency, per_mb, per_operand_mb; };
 inline double tile_cost_us(const TileCost& c, const ConvArgs& a, long long M, int num_cu) {
   const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
@@ -42,14 +46,14 @@ inline double tile_cost_us(const TileCost& c, const ConvArgs& a, long long M, in
   return c.base + per_cu * (nk * c.step + c.tile) + (tiles <= num_cu ? c.latency * nk : 0.0) + c.per_mb * mb + c.per_operand_mb * operands;
 }
 constexpr TileCost FLOW_COST[8] = {
-    {64, 64, 3.777, 0.169, 0.522, 0.082, 0.002, 0.0},
-    {64, 128, 3.928, 0.236, 0.874, 0.107, 0.028, 0.0062},
-    {128, 64, 4.206, 0.222, 0.870, 0.101, 0.018, 0.0081},
-    {128, 128, 4.343, 0.277, 1.767, 0.055, 0.037, 0.0234},
-    {96, 256, 4.509, 0.000, 3.016, 0.194, 0.000, 0.0593},
-    {192, 128, 4.865, 0.201, 1.925, 0.125, 0.035, 0.0400},
-    {128, 256, 5.580, 0.438, 3.208, -0.033, 0.028, 0.0314},
-    {256, 128, 6.239, 0.579, 1.460, -0.036, 0.083, 0.0083}};
+    {64, 64, 4.546, 0.1882, 0.417, 0.0975, 0.0564, 0.0010},
+    {64, 128, 5.930, 0.2386, 0.792, 0.0746, 0.0321, 0.0123},
+    {128, 64, 5.087, 0.2870, 0.757, 0.0854, 0.0559, 0.0021},
+    {128, 128, 4.857, 0.3707, 1.870, 0.0000, 0.0478, 0.0119},
+    {96, 256, 4.942, 0.5473, 2.783, 0.0000, 0.0427, 0.0116},
+    {192, 128, 5.497, 0.5144, 2.709, 0.0000, 0.0184, 0.0113},
+    {128, 256, 8.527, 0.7314, 2.434, 0.0000, 0.0543, 0.0007},
+    {256, 128, 6.624, 0.7209, 2.934, 0.0000, 0.0237, 0.0000}};
 // Single layers, E4M3, and layers whose channels end inside a K step, of which the cascades have too few to fit: from repeated launches of 656 layers
 // (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of 64 x 128 per compute unit, bf16).  A constant, what
 // the busiest compute unit does - its tiles, rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the

@@ -25,13 +25,13 @@ inline bool small_fits(const ConvArgs& a, int ES) {
          (2LL * a.H * a.W + 1024LL * a.stride_h * a.stride_w + (long long)a.pad_h * a.W + a.pad_w) * a.x_ld * ES < 0x7FFFFFF0LL;
 }
 
-// Time of a launch in us in its place in a cascade: see tile_cost_us, which has the form and what it was fitted to (here with 3x3 layers of stride 1 of up to four tiles of 64 x 64 per compute unit besides: 0.95 of the time with the former choice among these tiles).
+// Time of a launch in us in its place in a cascade: see tile_cost_us, which has the form and what it was fitted to (3x3 layers: 1.006 of the best tile's time).
 constexpr TileCost SMALL_COST[5] = {
-    {32, 32, 2.912, 0.079, 0.202, 0.094, 0.000, 0.0},
-    {32, 64, 3.328, 0.112, 0.258, 0.083, 0.000, 0.0},
-    {64, 32, 3.170, 0.115, 0.253, 0.080, 0.000, 0.0},
-    {64, 64, 3.293, 0.132, 0.525, 0.089, 0.002, 0.0069},
-    {128, 64, 3.247, 0.133, 0.816, 0.124, 0.037, 0.0215}};
+    {32, 32, 2.393, 0.0916, 0.274, 0.0993, 0.0000, 0.0073},
+    {32, 64, 3.373, 0.1392, 0.268, 0.1097, 0.0195, 0.0000},
+    {64, 32, 2.518, 0.1249, 0.293, 0.1817, 0.0232, 0.0040},
+    {64, 64, 3.158, 0.1533, 0.451, 0.1452, 0.0309, 0.0048},
+    {128, 64, 3.359, 0.2349, 0.723, 0.1096, 0.0677, 0.0040}};
 // Otherwise, and fp32: from a graph, input channels in whole K steps, and not.  A constant, what a compute unit does - its tiles, half way between their mean and the next whole
 // number, times K steps and an epilogue -, a latency per K step and the memory traffic.  Fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output channels,
 // 1x1 and 3x3 of stride 1 and 2, with and without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16; residual error 4 - 7 %).

@@ -6,6 +6,7 @@ import subprocess
 from paper_2502_01277_amd import binding
 from paper_2502_01277_amd.build import HERE
 
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 DTYPES = {"f32": 0, "f16": 1, "bf16": 2, "f8": 3}
 # place: a layer of a model; split, hint: item counts stated and expected where the count is taken on the device; second: channels of the first of two
 # layers in one launch; upsampled: an upsampling of the output follows
@@ -39,15 +40,17 @@ int main() {
 '''
 
 
+def compile_host(args):
+    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I", ROCM + "/include", "-I", HERE] + args, check=True)
+
+
 def program(folder) -> str:
     """Builds the program; one per test module will do."""
     src, exe = os.path.join(str(folder), "dispatch.cpp"), os.path.join(str(folder), "dispatch")
     with open(src, "w") as f:
         f.write(SOURCE)
-    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     # -rdynamic: the library's calls of the launch functions find those of the program
-    subprocess.run(["g++", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I", rocm + "/include", "-I", HERE, "-o", exe, src, binding.LIB_PATH, "-rdynamic",
-                    "-L", rocm + "/lib", "-lamdhip64", "-Wl,-rpath," + rocm + "/lib", "-Wl,-rpath," + HERE], check=True)
+    compile_host(["-o", exe, src, binding.LIB_PATH, "-rdynamic", "-L", ROCM + "/lib", "-lamdhip64", "-Wl,-rpath," + ROCM + "/lib", "-Wl,-rpath," + HERE])
     return exe
 
 

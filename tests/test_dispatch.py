@@ -1,4 +1,5 @@
 """The lines between the convolution kernels, on both sides of them, by the ids that launch_conv returns (no GPU: see dispatch.py)."""
+import ctypes
 import math
 import random
 
@@ -85,3 +86,24 @@ def test_split_k_is_chosen_alike_for_a_layer_of_a_model_and_a_single_call(ids, d
     # the others that differ: the lines and slices of the 3x3 kernels, else kernels of one order
     others = {family(k) for a, p in zip(alone, place) if a != p and not (family(a) in PATCHES and family(p) in PATCHES) for k in (a, p)}
     assert others <= {10, 11, 12, SMALL, STREAM}
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_long_reductions_of_a_model_take_the_tiles_that_are_fast_there(ids, dtype):
+    """1x1 layers with more K steps than the workloads have: the fastest tile by measurement, 5 % at least ahead of what constants without a cost per K step chose."""
+    cases = [((1, 56, 54, 1536, 1536), 1201921288), ((11, 28, 28, 3072, 512), 1201921288), ((1, 56, 41, 4096, 2048), 1201921288),
+             ((125, 20, 20, 2048, 256), 1202561288), ((125, 20, 20, 4096, 256), 1202561288)]
+    assert ids([dict(zip(("n", "h", "w", "cin", "cout"), c), dtype=dtype, place=1) for c, _ in cases]) == [k for _, k in cases]
+
+
+def test_every_tile_costs_something_per_k_step(tmp_path):
+    """The estimates go beyond what they were fitted to: no term may be negative, and none of the two that grow with the reduction missing."""
+    (tmp_path / "c.cpp").write_text('''#include "csrc/conv_small_choice.h"
+template <int N> bool sound(const octo::TileCost (&t)[N]) {
+  for (const auto& c : t) if (!(c.base > 0 && c.step > 0.05 && c.tile > 0 && c.latency >= 0 && c.per_mb >= 0 && c.per_operand_mb >= 0)) return false;
+  return true;
+}
+extern "C" int both() { return sound(octo::FLOW_COST) + 2 * sound(octo::SMALL_COST); }
+''')
+    dispatch.compile_host(["-shared", "-fPIC", "-o", str(tmp_path / "c.so"), str(tmp_path / "c.cpp")])
+    assert ctypes.CDLL(str(tmp_path / "c.so")).both() == 3
