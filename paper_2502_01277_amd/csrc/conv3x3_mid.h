@@ -527,9 +527,12 @@ inline long long mid_rounds(const ConvArgs& a, long long items, int BC, int BP, 
 //     96 x 256 tiles where 128 would pad but 96 do not: 192 -> 192 on 32 x 80 x 80 123 us (64 x 256 134).
 // Reductions over at least 192 channels are paced by the operand fetch: 64 x 128 tiles take slices of 128 bytes (whole cache lines)
 // there, and of 64 bytes, half the LDS and up to four workgroups per compute unit elsewhere (28 x 28 x 128 at 2.0 16.0 : 18.8).
-// In place in a cascade, where a tile's first operands come from beyond the L2s, 128 channels take the wide slices up to 2.5 tiles per compute unit, which have
-// half the waits, where the count is not taken on the device (else larger tiles could not be taken for more items) (64-byte : 128-byte slices, 8 x 40 x 40 at 1.5 13.6 : 12.1, with residual at 1.6 17.8 : 16.7, 48 x 28 x 28 at 2.3 14.9 : 14.2, at 4.6 22.7 : 23.0),
-// and 64 x 256 tiles of shorter reductions cost 2.05 (192 x 32 x 16 x 128 at 6 30.3 : 27.1, 192 x 28 x 28 with residual at 9.2 42.8 : 38.9).
+// In place in a cascade, where a tile's first operands come from beyond the L2s, 128 channels take the wide slices, which have half the waits, while every
+// tile has one of the two places that a compute unit has for them, where the count is not taken on the device (else larger tiles could not be taken for
+// more items).  Wide : narrow, over 330 layers of nine maps, 64 .. 384 output channels, with and without residual, 0.91 .. 1.00 of the time up to two tiles per compute unit
+// (8 x 40 x 40 at 1.5 12.1 : 13.6, with residual at 1.6 16.7 : 17.8; 41 x 16 x 17 x 256 at 1.4 14.0 : 14.4, 162 x 14 x 12 with residual at 1.7 15.6 : 16.5), 1.05 ..
+// 1.13 from there to 2.4, as at 2.1 with residual 269 x 16 x 16 x 64 22.3 : 20.5, and 1.00 .. 1.05 at 2.6 .. 3.2.  64 x 256 tiles of shorter reductions cost 2.05
+// (192 x 32 x 16 x 128 at 6 30.3 : 27.1, 192 x 28 x 28 with residual at 9.2 42.8 : 38.9).
 // The two slice widths sum in different orders; the choice between them is made for a count that stays the same from batch to
 // batch (M, from a.n_split), and so the results do.
 template <typename T>
@@ -560,7 +563,10 @@ hipError_t launch_mid(const ConvArgs& a, long long M, int num_cu, hipStream_t s,
     if (a.Cin >= 128 && fits128) offer(3, 128, long_k ? 3.26 : 3.5);
     return best;
   };
-  if (a.in_place && a.n_split == 0 && a.Cin == 128 && per_cu <= 2.5) return launch_mid_cfg<T, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+  if (a.in_place && a.n_split == 0 && a.Cin == 128) {
+    const long long tiles = mid_rounds(a, M / ((long long)a.Ho * a.Wo), 64, 128, 192, num_cu);
+    if (tiles == 1 || tiles == 2) return launch_mid_cfg<T, 64, 128, 1, 8, 3, 6, 2>(a, num_cu, s, kernel_id, tm);
+  }
   const long long hw = (long long)a.Ho * a.Wo, now = a.n_hint > 0 && a.n_hint < a.n ? a.n_hint : a.n;
   if (k8 && long_k) {
     double cost = (double)mid_rounds(a, M / hw, 64, 128, 192, num_cu);

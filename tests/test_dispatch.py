@@ -107,3 +107,17 @@ extern "C" int both() { return sound(octo::FLOW_COST) + 2 * sound(octo::SMALL_CO
 ''')
     dispatch.compile_host(["-shared", "-fPIC", "-o", str(tmp_path / "c.so"), str(tmp_path / "c.cpp")])
     assert ctypes.CDLL(str(tmp_path / "c.so")).both() == 3
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_wide_slices_of_128_channels_end_where_a_compute_unit_has_no_place_left(ids, dtype):
+    """3x3 layers of 128 channels in a model: slices of 64 channels while there are two 64 x 128 tiles per compute unit at most, whole images counted as the
+    kernel cuts them, else slices of 32 (kernel ids end in the channels that two buffers hold)."""
+    common = dict(dtype=dtype, cin=128, k=3, place=1)
+    cases = [(20, 40, 40, 128, 128), (21, 40, 40, 128, 64), (80, 20, 20, 128, 64), (41, 28, 28, 128, 128), (42, 28, 28, 128, 64), (2, 160, 160, 64, 128), (269, 16, 16, 64, 64),
+             (48, 28, 28, 128, 64), (62, 28, 28, 128, 64), (24, 28, 28, 256, 64)]
+    got = ids([dict(common, n=n, h=h, w=w, cout=co) for n, h, w, co, _ in cases])
+    assert [(family(k), k % 1000) for k in got] == [(18 if co == 64 else 17, slices) for _, _, _, co, slices in cases], got
+    # a count taken on the device, and single calls: slices of 32 throughout
+    for change in (dict(place=0), dict(split=20, hint=20)):
+        assert all(k % 1000 == 64 for k in ids([dict(common, n=n, h=h, w=w, cout=co, **change) for n, h, w, co, _ in cases[:1]]))
