@@ -115,11 +115,14 @@ inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us
 
 // Up to how many tiles of 64 x 64 per compute unit a layer is one of few tiles: split-K is asked, and where conv_flow_kernel does not fit or the channels end
 // inside a K step, and for single layers, this kernel takes the layer (us here : the kernel that took it before, from a graph unless said).  M: output pixels.
-//   * windows (3x3, strides): 2.75; into one channel tile, or with steps across taps, 1.96: beyond, some unit has a third tile.  128 -> 256, stride 2 on 5 x 80 x 80 at 1.95 9.4 : 11.8, 256 -> 256 on 20 x 40 x 40 1.95 15.1 : 18.7, 192 -> 256 on 28 x 40 x 41 2.9 18.3 : 19.8,
-//     96 -> 192 on 9 x 57 x 83 at 2.0 12.3 : 12.1, 128 -> 64 on 82 x 40 x 40 at 2.0 13.8 : 15.2.  Up to five steps across taps 16
-//     in place: 32 -> 64, stride 2 on 8 x 320 x 320 at 12.5 24.2 : 24.4, in place 23.1 : 28.2, on 16 at 25 49.0 : 47.6, on 64 207 : 188;
-//   * 1x1 layers in whole K steps: 3, one step 4.5, or 24 into more channels than conv_flow_kernel takes.  1024 -> 512 on 7 x 28 x 29 at 2.8 11.6 : 12.4, 256 -> 255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on
-//     61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 456 with residual on 2 x 63 x 93 at 5.7 7.0 : 11.4.  With channel
+//   * windows (3x3, strides): 2.75; into one channel tile, or with steps across taps, 1.96: beyond, some unit has a third tile.  128 -> 256, stride 2 on
+//     5 x 80 x 80 at 1.95 9.4 : 11.8, 256 -> 256 on 20 x 40 x 40 1.95 15.1 : 18.7, 192 -> 256 on 28 x 40 x 41 2.9 18.3 : 19.8, 96 -> 192 on 9 x 57 x 83 at 2.0 12.3 :
+//     12.1, 128 -> 64 on 82 x 40 x 40 at 2.0 13.8 : 15.2.  In place up to five steps across taps 16: 32 -> 64, stride 2 on 8 x 320 x 320 at 12.5 23.1 : 28.2, on 16
+//     at 25 49.0 : 47.6, on 64 207 : 188; 47 layers of 8 .. 288 channels, windows of 1 .. 5, at 1.5 .. 10 0.80 .. 0.96 of the time (32 -> 48, stride 2 on 18 x 112 x
+//     110 10.8 : 11.6, 96 -> 64 1x1, stride 2 on 220 x 40 x 42 10.5 : 11.4), at 11 .. 15 0.91 .. 1.05 (24 -> 128, stride 2 on 27 x 112 x 140 18.8 : 20.1, 32 -> 128 on
+//     8 x 224 x 262 23.7 : 22.6), at 17 .. 29 0.92 .. 1.11 (32 -> 192 on 31 x 112 x 106 27.2 : 24.5);
+//   * 1x1 layers in whole K steps: 3, one step 4.5, or 24 into more channels than conv_flow_kernel takes.  1024 -> 512 on 7 x 28 x 29 at 2.8 11.6 : 12.4, 256 ->
+//     255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on 61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 456 with residual on 2 x 63 x 93 at 5.7 7.0 : 11.4.  With channel
 //     tiles less than three quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x 39 at 1.76 4.8 : 5.3);
 //   * 1x1 layers that end inside a step: 2.75 up to eight steps (32 -> 256 on 80 x 81 at 1.6 4.6 : 9.3, 24 -> 256 on 142 x 8 x 10 at 2.8 5.6 : 8.1), 1.25 with
 //     more, whose every step has the taps to work out; in place up to three steps 4.5, as far as the line of the streaming kernel there (this kernel : it :

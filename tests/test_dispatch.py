@@ -121,3 +121,15 @@ def test_wide_slices_of_128_channels_end_where_a_compute_unit_has_no_place_left(
     # a count taken on the device, and single calls: slices of 32 throughout
     for change in (dict(place=0), dict(split=20, hint=20)):
         assert all(k % 1000 == 64 for k in ids([dict(common, n=n, h=h, w=w, cout=co, **change) for n, h, w, co, _ in cases[:1]]))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_more_than_four_slices_or_part_of_one_take_256_pixel_tiles_in_a_model_too(ids, dtype):
+    """3x3 layers whose 64 x 256 tiles beat 64 x 128 ones in a model as alone; with three or four whole slices of 32 channels the place decides."""
+    cases = [(35, 80, 80, 184, 128), (13, 80, 70, 184, 256), (615, 14, 12, 184, 64), (23, 80, 51, 160, 192), (157, 40, 34, 112, 128)]
+    layers = [dict(zip(("n", "h", "w", "cin", "cout"), c), dtype=dtype, k=3) for c in cases]
+    alone = ids(layers)
+    assert ids([dict(l, place=1) for l in layers]) == alone
+    assert all(k // 1000 % 10000 == 1064 for k in alone), alone                 # 256 pixels, 64 channels
+    layer = dict(dtype=dtype, n=192, h=32, w=16, cin=128, cout=128, k=3)
+    assert [k // 1000 % 10000 for k in ids([layer, dict(layer, place=1)])] == [1064, 64]
