@@ -623,12 +623,18 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
   // a last vector has less than eight channels, whose values they convert one by one); against the patch kernel it is M_split as well.
   bool to_small = false, not_split = false;
   [[maybe_unused]] const long long M_small = a.Cout % 8 || a.Cout <= 32 ? M_split : M;
+  int small_tile = -1, flow_tile = -1;                     // the cheapest for M_small, where they have been asked for
   [[maybe_unused]] auto run_small = [&](long long m) -> hipError_t {
     double us = 0;
-    const int which = small_choose(a, m, num_cu, 2, by_place(a), &us);
+    const int which = small_tile >= 0 ? small_tile : small_choose(a, m, num_cu, 2, by_place(a), &us);
     return std::is_same<T, __bf16>::value ? launch_small_bf16(which, a, num_cu, s, kernel_id, tm) : launch_small_f16(which, a, num_cu, s, kernel_id, tm);
   };
   [[maybe_unused]] const bool pipe_ok = sizeof(T) == 2, pw = a.kh == 1 && a.kw == 1 && a.stride_h == 1 && a.stride_w == 1 && !a.pad_h && !a.pad_w;
+  // Against the kernels of this order split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
+  // on 7 x 40 x 40 at 4.1 38.0 : 28.0, 512 -> 64 1x1 on 82 x 20 x 20 at 4.0 11.1 : 8.2).  Its 64 x 64 tiles serve long reductions (256 -> 256,
+  // stride 2 on 6 x 40 x 40 11.0 : 13.8), not 1x1 layers (512 -> 512 on 5 x 20 x 20 7.3 : 5.8, 1024 -> 512 8.7 : 7.3).
+  [[maybe_unused]] const int shapes = pw ? 3 : 4;
+  [[maybe_unused]] const bool splittable = (M_split + (pw ? 31 : 63)) / (pw ? 32 : 64) * ((a.Cout + 63) / 64) < 4LL * num_cu;      // the last shape's tiles, the largest
   // strided layers of up to two 64x64 tiles per compute unit that the general kernel would run in one round of pipelined tiles: never split
   [[maybe_unused]] auto stays = [&](long long m) {
     const GeneralTile t = general_tile(a, m, num_cu, 1, pipe_ok);
@@ -645,20 +651,21 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     if (patch || (to_small && !a.up_next && small_takes(a, M_split, num_cu, false))) {
       // Split-K has to beat every other kernel: below the patch kernel's line, never where one round of tiles fills the chip, and
       // conv_flow_kernel's estimate (96 -> 192, stride 2 on 9 x 57 x 83: split-K 14.1, estimated 12.1, conv_flow_kernel 13.3)
-      double us = 0, uf = 0;
-      small_choose(a, M_split, num_cu, 2, false, &us);
-      if (!patch && flow_fits(a)) { flow_choose(a, M_split, num_cu, 2, false, &uf); us = std::min(us, uf); }
-      const bool few = patch ? (double)M_split / 128 * ((a.Cout + 63) / 64) < 0.25 * num_cu : !stays(M_split);
-      const int kf = few ? ksplit_best(a, M_split, 2, num_cu, us, pw ? 3 : 4, 4.0) : -1;
-      if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
+      if (splittable && (patch ? (double)M_split / 128 * ((a.Cout + 63) / 64) < 0.25 * num_cu : !stays(M_split))) {
+        double us = 0, uf = 0;
+        small_choose(a, M_split, num_cu, 2, false, &us);
+        if (!patch && flow_fits(a)) { flow_choose(a, M_split, num_cu, 2, false, &uf); us = std::min(us, uf); }
+        const int kf = ksplit_best(a, M_split, 2, num_cu, us, shapes, 4.0);
+        if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
+      }
       if (patch) return run_small(M_split);
       not_split = true;
     }
     // (two layers in one launch: by small_limit; beyond it conv_flow_kernel's best tile takes 1.03 .. 1.1 of this kernel's time)
     if (to_small && by_place(a) && a.split == 0 && flow_fits(a)) {
       double us = 0, uf = 0;
-      small_choose(a, M_small, num_cu, 2, true, &us);
-      flow_choose(a, M_small, num_cu, 2, true, &uf);
+      small_tile = small_choose(a, M_small, num_cu, 2, true, &us);
+      flow_tile = flow_choose(a, M_small, num_cu, 2, true, &uf);
       to_small = us <= uf;
     } else if (to_small) {
       to_small = small_takes(a, M_small, num_cu, a.in_place);
@@ -685,18 +692,14 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     if (flow_fits(a)) {
       double us = 0;
       int kf = -1;
-      if (!not_split && !stays(M_split)) {
+      if (splittable && !not_split && !stays(M_split)) {
         flow_choose(a, M_split, num_cu, 2, false, &us);
-        // Against this kernel split-K is for few tiles: from four per compute unit on it loses whatever the estimates say (384 -> 768, stride 2
-        // on 7 x 40 x 40 at 4.1 38.0 : 28.0, 512 -> 64 1x1 on 82 x 20 x 20 at 4.0 11.1 : 8.2).  Its 64 x 64 tiles serve long reductions (256 -> 256,
-        // stride 2 on 6 x 40 x 40 11.0 : 13.8), not 1x1 layers (512 -> 512 on 5 x 20 x 20 7.3 : 5.8, 1024 -> 512 8.7 : 7.3), where this kernel's
-        // estimate is 15 % high while it has few tiles.
-        kf = ksplit_best(a, M_split, 2, num_cu, pw ? 0.85 * us : us, pw ? 3 : 4, 4.0);
+        kf = ksplit_best(a, M_split, 2, num_cu, pw ? 0.85 * us : us, shapes, 4.0);      // (this kernel's estimate of 1x1 layers is 15 % high while it has few tiles)
       }
       if (kf >= 0) return launch_ksplit<T>(kf, a, num_cu, s, kernel_id, tm);
       if (to_small) return run_small(M_small);
       if (!by_place(a) && stays(M)) return launch_cfg<T, 64, 64, 2, 2, 8, 2, 3, true, true, true>(a, num_cu, s, kernel_id, tm);
-      const int which = flow_choose(a, M, num_cu, 2, by_place(a), &us);
+      const int which = flow_tile >= 0 && M_small == M ? flow_tile : flow_choose(a, M, num_cu, 2, by_place(a), &us);
       return std::is_same<T, __bf16>::value ? launch_flow_bf16(which, a, num_cu, s, kernel_id, tm) : launch_flow_f16(which, a, num_cu, s, kernel_id, tm);
     }
   }

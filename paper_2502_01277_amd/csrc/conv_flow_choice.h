@@ -24,6 +24,19 @@ inline bool flow_fits(const ConvArgs& a, int ES = 2) {
 
 // Is a layer's tile chosen by tile_cost_us?
 inline bool by_place(const ConvArgs& a) { return a.in_place && a.Cin % 64 == 0; }
+// What the estimates of all tiles of a layer have in common: output pixels, K steps (128 bytes), megabytes.  Of the 2.6 us in which a launch is enqueued the choice
+// of its kernel is 0.37; with everything worked out anew for every tile and estimates asked twice it was 0.49.  The tables are walked unrolled: divisors are constants.
+struct LayerWork {
+  unsigned M, Cout;
+  int num_cu;
+  double nk, mb;
+  LayerWork(const ConvArgs& a, long long M_, int num_cu_, int ES) : M((unsigned)M_), Cout((unsigned)a.Cout), num_cu(num_cu_), nk((double)((a.K * ES + 127) / 128)) {
+    const double pixels_in = (double)M_ * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
+    mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M_ * a.Cout * (a.res ? 2 : 1));
+  }
+  template <typename Cost> long long tiles(const Cost& c) const { return (long long)((M + (unsigned)c.bp - 1) / (unsigned)c.bp) * ((Cout + (unsigned)c.bc - 1) / (unsigned)c.bc); }
+  double rounds(long long t) const { return (double)((t + num_cu - 1) / num_cu); }      // tiles of the busiest compute unit
+};
 // Time of a launch in us in its place in a cascade, 16-bit types, input channels in whole K steps: a constant, what a compute unit does - its tiles, a
 // quarter of the way from the next whole number to their mean, times K steps and an epilogue -, a latency per K step where no unit has a second
 // tile, the memory traffic, and the operands that the tiles fetch.
@@ -38,12 +51,10 @@ inline bool by_place(const ConvArgs& a) { return a.in_place && a.Cin % 64 == 0; 
 // latency, and reductions that no cascade has lost up to 1.57: 1536 -> 1536 on 56 x 54 26.6 : 21.8, 3072 -> 512 on 11 x 28 x 28 44.8 : 37.2, 4096 -> 2048 on
 // 56 x 41 50.6 : 45.3.
 struct TileCost { int bc, bp; double base, step, tile, latency, per_mb, per_operand_mb; };
-inline double tile_cost_us(const TileCost& c, const ConvArgs& a, long long M, int num_cu) {
-  const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
-  const double nk = (a.K + 63) / 64, per_cu = std::max(1.0, 0.25 * tiles / num_cu + 0.75 * (double)((tiles + num_cu - 1) / num_cu));
-  const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
-  const double mb = 2e-6 * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1)), operands = 128e-6 * tiles * nk * (c.bc + c.bp);
-  return c.base + per_cu * (nk * c.step + c.tile) + (tiles <= num_cu ? c.latency * nk : 0.0) + c.per_mb * mb + c.per_operand_mb * operands;
+inline double tile_cost_us(const TileCost& c, const LayerWork& w) {
+  const long long tiles = w.tiles(c);
+  const double per_cu = std::max(1.0, 0.25 * tiles / w.num_cu + 0.75 * w.rounds(tiles)), operands = 128e-6 * tiles * w.nk * (c.bc + c.bp);
+  return c.base + per_cu * (w.nk * c.step + c.tile) + (tiles <= w.num_cu ? c.latency * w.nk : 0.0) + c.per_mb * w.mb + c.per_operand_mb * operands;
 }
 constexpr TileCost FLOW_COST[8] = {
     {64, 64, 4.546, 0.1882, 0.417, 0.0975, 0.0564, 0.0010},
@@ -57,8 +68,8 @@ constexpr TileCost FLOW_COST[8] = {
 // Single layers, E4M3, and layers whose channels end inside a K step, of which the cascades have too few to fit: from repeated launches of 656 layers
 // (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of 64 x 128 per compute unit, bf16).  A constant, what
 // the busiest compute unit does - its tiles, rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the
-// memory traffic (residual error 8 - 11 %; the choice loses 1.3 % against always taking the fastest tile).  E4M3 uses the same numbers with steps of 128 values: over 64 such layers (32 .. 1024 input, 80 .. 768 output
-// channels) the choice loses 0.9 % against the fastest tile, at most 13 % (512 -> 608 on 36 x 40 x 41: 256 x 128 tiles 32.4 us, 128 x 256 28.5).
+// memory traffic (residual error 8 - 11 %; the choice loses 1.3 % against always taking the fastest tile).  E4M3 uses the same numbers with steps of
+// 128 values: over 64 such layers (32 .. 1024 input, 80 .. 768 output channels) the choice loses 0.9 % against the fastest tile, at most 13 % (512 -> 608 on 36 x 40 x 41: 256 x 128 tiles 32.4 us, 128 x 256 28.5).
 struct FlowCost { int bc, bp; double base, step, tile, latency, per_mb, any_step; };
 constexpr FlowCost FLOW_COST_REPEATED[8] = {
     {64, 64, 3.73, 0.165, 0.22, 0.118, 0.040, 0.031},
@@ -69,20 +80,29 @@ constexpr FlowCost FLOW_COST_REPEATED[8] = {
     {192, 128, 3.22, 0.554, 1.46, 0.000, 0.045, 0.064},
     {128, 256, 3.00, 0.674, 2.06, 0.000, 0.065, 0.093},
     {256, 128, 3.76, 0.653, 1.18, 0.000, 0.061, 0.053}};
-inline double flow_cost_us(const FlowCost& c, const ConvArgs& a, long long M, int num_cu, int ES) {
-  const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
-  const double per_cu = (double)((tiles + num_cu - 1) / num_cu), nk = (a.K + 128 / ES - 1) / (128 / ES);
-  const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
-  const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
-  return c.base + per_cu * (nk * (c.step + (a.Cin % (128 / ES) ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * nk : 0.0) + c.per_mb * mb;
+inline double flow_cost_us(const FlowCost& c, const LayerWork& w, bool any) {
+  const double per_cu = w.rounds(w.tiles(c));
+  return c.base + per_cu * (w.nk * (c.step + (any ? c.any_step : 0.0)) + c.tile) + (per_cu <= 1.0 ? c.latency * w.nk : 0.0) + c.per_mb * w.mb;
 }
 // The tile (launch_flow's number) with the smallest estimate for M output pixels, in place or repeated.
 inline int flow_choose(const ConvArgs& a, long long M, int num_cu, int ES, bool place, double* us) {
+  const LayerWork w(a, M, num_cu, ES);
+  const bool one = ES == 2 && a.K <= 64, any = a.Cin % (128 / ES) != 0;
   int best = -1;
-  for (int i = 0; i < 8; ++i) {
-    if (ES == 2 && a.K <= 64 && a.Cout > FLOW_COST[i].bc) continue;
-    const double t = place ? tile_cost_us(FLOW_COST[i], a, M, num_cu) : flow_cost_us(FLOW_COST_REPEATED[i], a, M, num_cu, ES);
-    if (best < 0 || t < *us) { *us = t; best = i; }
+  if (place) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (one && a.Cout > FLOW_COST[i].bc) continue;
+      const double t = tile_cost_us(FLOW_COST[i], w);
+      if (best < 0 || t < *us) { *us = t; best = i; }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (one && a.Cout > FLOW_COST_REPEATED[i].bc) continue;
+      const double t = flow_cost_us(FLOW_COST_REPEATED[i], w, any);
+      if (best < 0 || t < *us) { *us = t; best = i; }
+    }
   }
   return best;
 }

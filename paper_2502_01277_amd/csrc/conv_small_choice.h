@@ -62,22 +62,34 @@ constexpr SmallCost SMALL_COST_F32[3][4] = {
      {32, 64, 2.446, 0.277, 0.453, 0.031, 0.033},
      {64, 32, 2.519, 0.249, 0.361, 0.047, 0.060},
      {64, 64, 2.705, 0.475, 0.479, 0.052, 0.085}}};
-inline double small_cost_us(const SmallCost& c, const ConvArgs& a, long long M, int num_cu, int ES) {
-  const double nk = (a.K + 128 / ES - 1) / (128 / ES);
-  const double pixels_in = (double)M * (a.kh >= a.stride_h ? a.stride_h : 1) * (a.kw >= a.stride_w ? a.stride_w : 1);
-  const double mb = 1e-6 * ES * (pixels_in * a.Cin + (double)M * a.Cout * (a.res ? 2 : 1));
-  const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
-  const double per_cu = std::max(1.0, 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu)));
-  return c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk + c.per_mb * mb;
+// (its tiles: at least one, half way between their mean and the next whole number)
+template <typename Cost> double small_per_cu(const Cost& c, const LayerWork& w) {
+  const long long tiles = w.tiles(c);
+  return std::max(1.0, 0.5 * ((double)tiles / w.num_cu + w.rounds(tiles)));
+}
+inline double small_cost_us(const SmallCost& c, const LayerWork& w) {
+  return c.base + small_per_cu(c, w) * (w.nk * c.step + c.tile) + c.latency * w.nk + c.per_mb * w.mb;
+}
+template <int N> int small_cheapest(const SmallCost (&t)[N], const LayerWork& w, double* us) {
+  int best = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double v = small_cost_us(t[i], w);
+    if (i == 0 || v < *us) { *us = v; best = i; }
+  }
+  return best;
 }
 // The tile (launch_small's number) with the smallest estimate for M output pixels, in place or repeated.
 inline int small_choose(const ConvArgs& a, long long M, int num_cu, int ES, bool place, double* us) {
+  const LayerWork w(a, M, num_cu, ES);
+  const bool whole = a.Cin % (128 / ES) == 0;
+  if (ES == 4) return whole ? small_cheapest(SMALL_COST_F32[0], w, us) : small_cheapest(a.kh == 1 && a.kw == 1 && !a.pad_h ? SMALL_COST_F32[2] : SMALL_COST_F32[1], w, us);
+  if (!place) return whole ? small_cheapest(SMALL_COST_REPEATED[0], w, us) : small_cheapest(SMALL_COST_REPEATED[1], w, us);
   int best = 0;
-  const int any = a.Cin % (128 / ES) == 0 ? 0 : ES == 4 && a.kh == 1 && a.kw == 1 && !a.pad_h ? 2 : 1;
-  for (int i = 0; i < (ES == 4 ? 4 : 5); ++i) {
-    const double t = ES == 4 ? small_cost_us(SMALL_COST_F32[any][i], a, M, num_cu, 4)
-                             : place ? tile_cost_us(SMALL_COST[i], a, M, num_cu) : small_cost_us(SMALL_COST_REPEATED[any][i], a, M, num_cu, 2);
-    if (i == 0 || t < *us) { *us = t; best = i; }
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const double v = tile_cost_us(SMALL_COST[i], w);
+    if (i == 0 || v < *us) { *us = v; best = i; }
   }
   return best;
 }
@@ -100,14 +112,12 @@ inline bool small_takes_f32(const ConvArgs& a, long long M, int num_cu) {
 constexpr SmallCost SPLIT_COST_F32[3] = {{32, 32, 2.732, 0.181, 1.363, -0.034, 0.0}, {32, 32, 3.103, 0.174, 0.691, -0.002, 0.0}, {64, 32, 3.364, 0.335, 0.952, -0.049, 0.0}};
 // The split-K shape (launch_ksplit's numbers) with an estimate below `us`, or -1.
 inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us) {
+  const LayerWork w(a, M, num_cu, 4);
   int best = -1;
-  const double nk = (a.K + 31) / 32;
+#pragma unroll
   for (int i = 0; i < 3; ++i) {
-    const SmallCost& c = SPLIT_COST_F32[i];
-    const long long tiles = (M + c.bp - 1) / c.bp * ((a.Cout + c.bc - 1) / c.bc);
-    if (tiles > 3LL * num_cu) continue;
-    const double per_cu = std::max(1.0, 0.5 * ((double)tiles / num_cu + (double)((tiles + num_cu - 1) / num_cu)));
-    const double t = c.base + per_cu * (nk * c.step + c.tile) + c.latency * nk;
+    if (w.tiles(SPLIT_COST_F32[i]) > 3LL * num_cu) continue;
+    const double t = small_cost_us(SPLIT_COST_F32[i], w);
     if (t < us) { us = t; best = i; }
   }
   return best;
