@@ -44,12 +44,13 @@ struct LayerWork {
 // are low there and favour large tiles: 128 -> 128 on 8 x 80 x 80, us, in place: 128 x 256 tiles of conv_flow_kernel 11.6, 128 x 128 12, 64 x 64 of
 // conv_small_kernel 9.3, where three workgroups per unit hide what one of eight wavefronts waits for; 256 -> 64 on that map 14.5 : 10.8, 256 -> 1024 with
 // residual on 96 x 16 x 16 29.0 (256 x 128) : 23.6 (128 x 64).
-//   Fitted, without negative terms, to 1812 layers timed in every tile behind the launch that writes their input and 48 MB of other traffic (the 696 1x1 and
-// strided layers of four cascades, 1 .. 64 frames; 850 random ones, 64 .. 4096 channels, 0.05 .. 200 tiles of 64 x 64 per compute unit; 266 3x3 layers of few
-// tiles), then moved to where the choice loses least: 1.012 of the best tile's time over the cascades' layers, 1.013 over the random ones.  (On a half that the
-// search had not seen 1.011.)  The constants before came from cascades alone, 1.018 and 1.025 here; a tile had no cost per K step and others a negative
-// latency, and reductions that no cascade has lost up to 1.57: 1536 -> 1536 on 56 x 54 26.6 : 21.8, 3072 -> 512 on 11 x 28 x 28 44.8 : 37.2, 4096 -> 2048 on
-// 56 x 41 50.6 : 45.3.
+//   Fitted, without negative terms, to 1933 layers timed in every tile: behind the launch that writes their input and 48 MB of other traffic the 696 1x1 and
+// strided layers of four cascades (1 .. 64 frames), 850 random ones (64 .. 4096 channels, 0.05 .. 200 tiles of 64 x 64 per compute unit) and 266 3x3 layers of few
+// tiles, in the cascades themselves 121 pairs of layers in one launch; then moved to where the choice loses least.  Of the best tile's time the choice takes
+// 1.012 over the cascades' layers, 1.014 over the random ones and, among this kernel's tiles, 1.010 over the pairs; over 718 layers and pairs then timed in every
+// tile in the cascades 1.015.  The constants before came from cascades alone, 1.018, 1.025, 1.026 and 1.020 here; a tile had no cost per K step and others
+// a negative latency, and reductions that no cascade has lost up to 1.57: 1536 -> 1536 on 56 x 54 26.6 : 21.8, 3072 -> 512 on 11 x 28 x 28 44.8 : 37.2,
+// 4096 -> 2048 on 56 x 41 50.6 : 45.3.  (64 -> 128, stride 2 on 480 x 28 x 28, near the line between the two kernels, stays on this one, 25.5 : 24.0.)
 struct TileCost { int bc, bp; double base, step, tile, latency, per_mb, per_operand_mb; };
 inline double tile_cost_us(const TileCost& c, const LayerWork& w) {
   const long long tiles = w.tiles(c);
@@ -57,14 +58,14 @@ inline double tile_cost_us(const TileCost& c, const LayerWork& w) {
   return c.base + per_cu * (w.nk * c.step + c.tile) + (tiles <= w.num_cu ? c.latency * w.nk : 0.0) + c.per_mb * w.mb + c.per_operand_mb * operands;
 }
 constexpr TileCost FLOW_COST[8] = {
-    {64, 64, 4.546, 0.1882, 0.417, 0.0975, 0.0564, 0.0010},
-    {64, 128, 5.930, 0.2386, 0.792, 0.0746, 0.0321, 0.0123},
-    {128, 64, 5.087, 0.2870, 0.757, 0.0854, 0.0559, 0.0021},
-    {128, 128, 4.857, 0.3707, 1.870, 0.0000, 0.0478, 0.0119},
-    {96, 256, 4.942, 0.5473, 2.783, 0.0000, 0.0427, 0.0116},
-    {192, 128, 5.497, 0.5144, 2.709, 0.0000, 0.0184, 0.0113},
-    {128, 256, 8.527, 0.7314, 2.434, 0.0000, 0.0543, 0.0007},
-    {256, 128, 6.624, 0.7209, 2.934, 0.0000, 0.0237, 0.0000}};
+    {64, 64, 3.626, 0.1860, 0.372, 0.1121, 0.0276, 0.0085},
+    {64, 128, 5.853, 0.2244, 0.596, 0.0847, 0.0394, 0.0097},
+    {128, 64, 5.244, 0.2481, 0.996, 0.0972, 0.0000, 0.0067},
+    {128, 128, 6.590, 0.3440, 1.734, 0.0000, 0.0347, 0.0019},
+    {96, 256, 4.925, 0.5788, 3.260, 0.0000, 0.0185, 0.0000},
+    {192, 128, 5.744, 0.4526, 2.878, 0.0000, 0.0046, 0.0059},
+    {128, 256, 9.813, 0.5896, 2.726, 0.0000, 0.0239, 0.0011},
+    {256, 128, 7.035, 0.6007, 3.308, 0.0000, 0.0012, 0.0000}};
 // Single layers, E4M3, and layers whose channels end inside a K step, of which the cascades have too few to fit: from repeated launches of 656 layers
 // (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of 64 x 128 per compute unit, bf16).  A constant, what
 // the busiest compute unit does - its tiles, rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the

@@ -27,11 +27,11 @@ inline bool small_fits(const ConvArgs& a, int ES) {
 
 // Time of a launch in us in its place in a cascade: see tile_cost_us, which has the form and what it was fitted to (3x3 layers: 1.006 of the best tile's time).
 constexpr TileCost SMALL_COST[5] = {
-    {32, 32, 2.393, 0.0916, 0.274, 0.0993, 0.0000, 0.0073},
-    {32, 64, 3.373, 0.1392, 0.268, 0.1097, 0.0195, 0.0000},
-    {64, 32, 2.518, 0.1249, 0.293, 0.1817, 0.0232, 0.0040},
-    {64, 64, 3.158, 0.1533, 0.451, 0.1452, 0.0309, 0.0048},
-    {128, 64, 3.359, 0.2349, 0.723, 0.1096, 0.0677, 0.0040}};
+    {32, 32, 2.342, 0.0943, 0.257, 0.0996, 0.0000, 0.0057},
+    {32, 64, 3.337, 0.1368, 0.258, 0.1133, 0.0088, 0.0000},
+    {64, 32, 2.488, 0.1123, 0.269, 0.1886, 0.0119, 0.0080},
+    {64, 64, 3.083, 0.1589, 0.444, 0.1503, 0.0159, 0.0010},
+    {128, 64, 3.123, 0.2288, 0.790, 0.1466, 0.0536, 0.0000}};
 // Otherwise, and fp32: from a graph, input channels in whole K steps, and not.  A constant, what a compute unit does - its tiles, half way between their mean and the next whole
 // number, times K steps and an epilogue -, a latency per K step and the memory traffic.  Fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output channels,
 // 1x1 and 3x3 of stride 1 and 2, with and without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16; residual error 4 - 7 %).
