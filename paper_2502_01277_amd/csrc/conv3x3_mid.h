@@ -529,12 +529,12 @@ inline long long mid_rounds(const ConvArgs& a, long long items, int BC, int BP, 
 // there, and of 64 bytes, half the LDS and up to four workgroups per compute unit elsewhere (28 x 28 x 128 at 2.0 16.0 : 18.8).
 // In place in a cascade, where a tile's first operands come from beyond the L2s, 128 channels take the wide slices, which have half the waits, while every
 // tile has one of the two places that a compute unit has for them, where the count is not taken on the device (else larger tiles could not be taken for
-// more items).  Wide : narrow, over 330 layers of nine maps, 64 .. 384 output channels, with and without residual, 0.91 .. 1.00 of the time up to two tiles per compute unit
-// (8 x 40 x 40 at 1.5 12.1 : 13.6, with residual at 1.6 16.7 : 17.8; 41 x 16 x 17 x 256 at 1.4 14.0 : 14.4, 162 x 14 x 12 with residual at 1.7 15.6 : 16.5), 1.05 ..
-// 1.13 from there to 2.4, as at 2.1 with residual 269 x 16 x 16 x 64 22.3 : 20.5, and 1.00 .. 1.05 at 2.6 .. 3.2.  64 x 256 tiles of three or four whole slices
-// cost 2.05 there (64 x 256 : 64 x 128, traced in two cascades, 192 x 32 x 16 x 128 at 6 30.3 : 27.1, 192 x 28 x 28 with residual at 9.2 42.8 : 38.9; where the two
-// costs differ, over 98 layers of 96 channels 1.015, over 78 of 128 0.99), and 1.9 as elsewhere with part of a slice or more of them, which read the patch more
-// often (35 x 80 x 80 x 184 -> 128 100 : 118, 13 x 80 x 70 x 184 -> 256 69 : 78; 67 layers of 112 .. 184 channels 0.92).
+// more items).  Wide : narrow, over 330 layers of nine maps, 64 .. 384 output channels, with and without residual, 0.91 .. 1.00 of the time up to two tiles per
+// compute unit (8 x 40 x 40 at 1.5 12.1 : 13.6, with residual at 1.6 16.7 : 17.8; 41 x 16 x 17 x 256 at 1.4 14.0 : 14.4, 162 x 14 x 12 with residual at 1.7 15.6 :
+// 16.5), 1.05 .. 1.13 from there to 2.4, as at 2.1 with residual 269 x 16 x 16 x 64 22.3 : 20.5, and 1.00 .. 1.05 at 2.6 .. 3.2.  64 x 256 tiles of three or four
+// whole slices cost 2.05 there (64 x 256 : 64 x 128, traced in two cascades, 192 x 32 x 16 x 128 at 6 30.3 : 27.1, 192 x 28 x 28 with residual at 9.2 42.8 : 38.9;
+// where the two costs differ, over 98 layers of 96 channels 1.015, over 78 of 128 0.99), and 1.9 as elsewhere with part of a slice or more of them, which read the
+// patch more often (35 x 80 x 80 x 184 -> 128 100 : 118, 13 x 80 x 70 x 184 -> 256 69 : 78; 67 layers of 112 .. 184 channels 0.92).
 // The two slice widths sum in different orders; the choice between them is made for a count that stays the same from batch to
 // batch (M, from a.n_split), and so the results do.
 template <typename T>

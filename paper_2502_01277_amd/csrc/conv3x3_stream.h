@@ -258,7 +258,8 @@ hipError_t launch_stream3_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int*
 // In its place in a cascade, where the first pixels come late, 64 -> 64 turns later (here : conv3x3_mid_kernel): without residual 8 x 160 x 160 28.0 : 24.8,
 // 96 x 56 x 56 28.0 : 23.7, 192 x 64 x 32 29.2 : 28.0, 16 x 160 x 160 41.2 : 40.5, 256 x 56 x 56 67 : 76; with residual 96 x 56 x 56 28.4 : 27.9, 128 x 56 x 56
 // 37.7 : 41.3.  Over 120 layers of nine maps, 56 and 64 channels into 40 and 64, by tiles of 128 pixels per compute unit, of the other's time: without residual at
-// 8 1.03 .. 1.2, at 11 0.97 .. 1.14, at 12.5 0.92 .. 1.09, at 16 0.88 .. 1.05; with residual at 8 0.99 .. 1.07, at 9.5 0.97 .. 1.08, at 11 0.87 .. 1.01, at 14 0.80 .. 0.93.
+// 8 1.03 .. 1.2, at 11 0.97 .. 1.14, at 12.5 0.92 .. 1.09, at 16 0.88 .. 1.05; with residual at 8 0.99 .. 1.07, at 9.5 0.97 .. 1.08, at 11 0.87 .. 1.01, at 14 0.80
+// .. 0.93.
 template <typename T>
 hipError_t launch_stream3(const ConvArgs& a, long long M, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   if (a.Cin < 24 || a.Cin > 64 || a.Cout > 64 || ((a.Cout | a.y_ld | a.y_coff) & 7) || ((uintptr_t)a.y & 15) ||

@@ -70,7 +70,8 @@ constexpr TileCost FLOW_COST[8] = {
 // (1x1 and 3x3 / stride 2, 24 .. 1536 input and 64 .. 1024 output channels, 0.3 .. 24 tiles of 64 x 128 per compute unit, bf16).  A constant, what
 // the busiest compute unit does - its tiles, rounded up, times K steps and an epilogue -, a latency per K step where it has one tile only, and the
 // memory traffic (residual error 8 - 11 %; the choice loses 1.3 % against always taking the fastest tile).  E4M3 uses the same numbers with steps of
-// 128 values: over 64 such layers (32 .. 1024 input, 80 .. 768 output channels) the choice loses 0.9 % against the fastest tile, at most 13 % (512 -> 608 on 36 x 40 x 41: 256 x 128 tiles 32.4 us, 128 x 256 28.5).
+// 128 values: over 64 such layers (32 .. 1024 input, 80 .. 768 output channels) the choice loses 0.9 % against the fastest tile, at most 13 % (512 -> 608 on 36 x
+// 40 x 41: 256 x 128 tiles 32.4 us, 128 x 256 28.5).
 struct FlowCost { int bc, bp; double base, step, tile, latency, per_mb, any_step; };
 constexpr FlowCost FLOW_COST_REPEATED[8] = {
     {64, 64, 3.73, 0.165, 0.22, 0.118, 0.040, 0.031},

@@ -1,14 +1,17 @@
-// Convolution for launches of up to about two tiles per compute unit, for layers in a cascade whose operands come late, and for fp32 of any size: an implicit GEMM written for
-// few instructions per wavefront.
+// Convolution for launches of few tiles, for layers in a cascade whose operands come late, and for fp32 of nearly any size: an implicit GEMM written for few
+// instructions per wavefront.  small_limit and small_takes_f32 (conv_small_choice.h) have the lines: up to 1.25 .. 24 tiles of 64 x 64 per compute unit in the
+// 16-bit types by the form of the layer, whole K steps of a layer of a model by estimated time without a bound; fp32 1x1 layers up to 64, windows in whole K steps
+// at every size and with steps across taps up to 8.
 //
-// Such a launch is one round of workgroups, and its time is what one of them takes from its first instruction to its last store. A
+// A launch of few tiles is one round of workgroups, and its time is what one of them takes from its first instruction to its last store. A
 // wavefront alone on its SIMD issues an instruction every four cycles at best, so that time is mostly a count of instructions: of the
 // 3.84 us of conv_flow_kernel on 128 -> 128 over 40 x 40 pixels (64 x 64 tile, two K steps, launches back to back from a graph) 1.23 pass
 // between launches, 0.46 go to addresses, 0.34 to the first operands, 0.86 to the two K steps and 0.54 to the epilogue.  Here
 //   * all arguments come in one trip to memory, in a block of their own; bias and residual are asked for before the operands, so that
 //     nothing is waited for after the K loop;
-//   * nothing of the next tile: no second set of addresses, no loads that only keep a count.  Where a workgroup has several tiles (a
-//     count taken on the device that is larger than the stated one) they follow one another;
+//   * nothing of the next tile: no second set of addresses, no loads that only keep a count.  Workgroups are two to four per compute unit; where there are more
+//     tiles than that (fp32, single K steps, layers of a model, a count on the device larger than expected) those of one follow one another, and the others
+//     of its compute unit hide the gap;
 //   * the fragments of a step are on their way from LDS while the loads of two steps on are issued; one barrier per step;
 //   * blocks of 16 x 16, so that small tiles still have four wavefronts and the epilogue few values per lane.
 // Same weights, same LDS layout and, in the 16-bit types, the same sums bit for bit as conv_flow_kernel and the general kernel (a block of 16 x 16 x 32

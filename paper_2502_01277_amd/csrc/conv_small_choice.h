@@ -32,9 +32,9 @@ constexpr TileCost SMALL_COST[5] = {
     {64, 32, 2.488, 0.1123, 0.269, 0.1886, 0.0119, 0.0080},
     {64, 64, 3.083, 0.1589, 0.444, 0.1503, 0.0159, 0.0010},
     {128, 64, 3.123, 0.2288, 0.790, 0.1466, 0.0536, 0.0000}};
-// Otherwise, and fp32: from a graph, input channels in whole K steps, and not.  A constant, what a compute unit does - its tiles, half way between their mean and the next whole
-// number, times K steps and an epilogue -, a latency per K step and the memory traffic.  Fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output channels,
-// 1x1 and 3x3 of stride 1 and 2, with and without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16; residual error 4 - 7 %).
+// Otherwise, and fp32: from a graph, input channels in whole K steps, and not.  A constant, what a compute unit does - its tiles, half way between their mean and
+// the next whole number, times K steps and an epilogue -, a latency per K step and the memory traffic.  Fitted to 1070 layers (16 .. 1024 input, 24 .. 1024 output
+// channels, 1x1 and 3x3 of stride 1 and 2, with and without residual, 0.04 .. 3.5 tiles of 64 x 64 per compute unit, bf16; residual error 4 - 7 %).
 struct SmallCost { int bc, bp; double base, step, tile, latency, per_mb; };
 constexpr SmallCost SMALL_COST_REPEATED[2][5] = {
     {{32, 32, 2.317, 0.071, 0.250, 0.054, 0.004},
@@ -132,13 +132,14 @@ inline int small_split_f32(const ConvArgs& a, long long M, int num_cu, double us
 //     110 10.8 : 11.6, 96 -> 64 1x1, stride 2 on 220 x 40 x 42 10.5 : 11.4), at 11 .. 15 0.91 .. 1.05 (24 -> 128, stride 2 on 27 x 112 x 140 18.8 : 20.1, 32 -> 128 on
 //     8 x 224 x 262 23.7 : 22.6), at 17 .. 29 0.92 .. 1.11 (32 -> 192 on 31 x 112 x 106 27.2 : 24.5);
 //   * 1x1 layers in whole K steps: 3, one step 4.5, or 24 into more channels than conv_flow_kernel takes.  1024 -> 512 on 7 x 28 x 29 at 2.8 11.6 : 12.4, 256 ->
-//     255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on 61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 456 with residual on 2 x 63 x 93 at 5.7 7.0 : 11.4.  With channel
-//     tiles less than three quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x 39 at 1.76 4.8 : 5.3);
+//     255 on 9 x 40 x 40 at 3.5 7.5 : 7.7, 384 -> 384 on 61 x 16 x 18 at 6.4 12.8 : 12.5; 64 -> 128 on 10 x 56 x 56 at 3.8 5.5 : 6.4, 64 -> 456 with residual on 2
+//     x 63 x 93 at 5.7 7.0 : 11.4.  With channel tiles less than three quarters full 1.75: half of what the second tile does is then padding (256 -> 72 on 9 x 41 x
+//     39 at 1.76 4.8 : 5.3);
 //   * 1x1 layers that end inside a step: 2.75 up to eight steps (32 -> 256 on 80 x 81 at 1.6 4.6 : 9.3, 24 -> 256 on 142 x 8 x 10 at 2.8 5.6 : 8.1), 1.25 with
 //     more, whose every step has the taps to work out; in place up to three steps 4.5, as far as the line of the streaming kernel there (this kernel : it :
-//     conv_flow_kernel, 16 -> 128 on 160 x 146 at 2.9 6.1 : 7.1 : 7.4, 96 -> 96 on 16 x 52 x 32 at 3.3 6.6 : 8.5 : 8.4, 120 -> 320 on 4 x 60 x 52 at 3.8 8.2 : 10.5 : 9.0, 184 -> 128
-//     on 42 x 28 x 29 at 4.2 10.0 : 12.2 : 11.2, 48 -> 184 with residual on 2 x 97 x 125 at 4.4 8.6 : 9.5 : 10.3; the other way round 16 -> 128 on 148 x 14 x 16 at 4.1
-//     7.8 : 7.4 : 9.1);
+//     conv_flow_kernel, 16 -> 128 on 160 x 146 at 2.9 6.1 : 7.1 : 7.4, 96 -> 96 on 16 x 52 x 32 at 3.3 6.6 : 8.5 : 8.4, 120 -> 320 on 4 x 60 x 52 at 3.8 8.2 : 10.5
+//     : 9.0, 184 -> 128 on 42 x 28 x 29 at 4.2 10.0 : 12.2 : 11.2, 48 -> 184 with residual on 2 x 97 x 125 at 4.4 8.6 : 9.5 : 10.3; the other way round 16 -> 128
+//     on 148 x 14 x 16 at 4.1 7.8 : 7.4 : 9.1);
 //   * up to 32 output channels 3: 256 -> 32 on 38 x 28 x 28 at 1.8 3.9 : 6.8, 320 -> 32 on 4 x 112 x 113 at 3.1 6.4 : 9.5; 1x1 layers of one K step as far as the
 //     line of launch_conv1x1_stream, which has the times on both sides.
 inline double small_limit(const ConvArgs& a, bool place) {
@@ -153,8 +154,8 @@ inline bool small_takes(const ConvArgs& a, long long M, int num_cu, bool place) 
   return (double)((M + 63) / 64 * ((a.Cout + 63) / 64)) <= small_limit(a, place) * num_cu;
 }
 // 3x3 layers of stride 1, against conv3x3_mid_kernel, which reads every pixel once for all nine taps: short reductions, up to 1.96 tiles of
-// 64 x 64 per compute unit.  64 -> 64 on 5 x 80 x 80 at 1.95 7.0 : 8.2, 64 -> 192 on 136 x 8 x 10 at 2.0 7.3 : 9.3, 128 -> 96 on 2 x 80 x 82 at 1.6 9.4 : 11.5, 128 -> 256
-// on 8 x 20 x 22 at 0.9 7.4 : 8.2, on 11 x 28 x 29 at 2.2 13.3 : 13.9; 160 -> 384 on 56 x 57 at 1.2 11.8 : 10.9, 256 -> 128 on 80 x 80 at 0.8 10.6 : 10.1.
+// 64 x 64 per compute unit.  64 -> 64 on 5 x 80 x 80 at 1.95 7.0 : 8.2, 64 -> 192 on 136 x 8 x 10 at 2.0 7.3 : 9.3, 128 -> 96 on 2 x 80 x 82 at 1.6 9.4 : 11.5, 128
+// -> 256 on 8 x 20 x 22 at 0.9 7.4 : 8.2, on 11 x 28 x 29 at 2.2 13.3 : 13.9; 160 -> 384 on 56 x 57 at 1.2 11.8 : 10.9, 256 -> 128 on 80 x 80 at 0.8 10.6 : 10.1.
 // Reductions that end inside a step from 128 channels on: 48 -> 384 on 13 x 20 x 22 at 2.1 8.3 : 10.4, 96 -> 256 on 4 x 40 x 42 at 1.6 9.2 : 9.1.
 inline bool small_takes_3x3(const ConvArgs& a, long long M, int num_cu) {
   if (a.kh != 3 || a.kw != 3 || a.stride_h != 1 || a.stride_w != 1 || a.pad_h != 1 || a.pad_w != 1 || a.Cout <= 32) return false;

@@ -133,3 +133,22 @@ def test_more_than_four_slices_or_part_of_one_take_256_pixel_tiles_in_a_model_to
     assert all(k // 1000 % 10000 == 1064 for k in alone), alone                 # 256 pixels, 64 channels
     layer = dict(dtype=dtype, n=192, h=32, w=16, cin=128, cout=128, k=3)
     assert [k // 1000 % 10000 for k in ids([layer, dict(layer, place=1)])] == [1064, 64]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("layer,pixels,below,beyond", [
+    # (layer, output pixels per compute unit at the line, families below and beyond it)
+    (dict(cin=32, cout=64, k=3, stride=2, place=1), 16 * 64, 13, 12),            # five steps across taps in a model
+    (dict(cin=32, cout=64, k=3, stride=2), 1.96 * 64, 13, 12),                   # and alone
+    (dict(cin=128, cout=256, k=3, stride=2), 2.75 * 16, 13, 12),
+    (dict(cin=256, cout=128), 3 * 32, 13, 12),
+    (dict(cin=64, cout=256), 9 * 8, 13, 15),                                     # one whole step, then resident weights
+    (dict(cin=64, cout=64, k=3, place=1), 13 * 128, 1800, 1805),                 # weights in registers
+    (dict(cin=64, cout=64, k=3, place=1, res=2), 10 * 128, 1800, 1805),
+    (dict(cin=64, cout=64, k=3), 6 * 128, 1800, 1805),
+    (dict(cin=64, cout=64, k=3), 1.96 * 64, 13, 18),                             # the patch in LDS
+])
+def test_both_sides_of_a_line(ids, dtype, layer, pixels, below, beyond):
+    s, rows = layer.get("stride", 1), int(pixels * 256 / 32) // 8 * 8        # (the streaming kernel cuts maps into whole tiles)
+    got = ids([dict(layer, dtype=dtype, n=1, h=s * (rows + d), w=s * 32) for d in (-8, 8)])
+    assert [k // 10 ** (10 - len(str(want))) for k, want in zip(got, (below, beyond))] == [below, beyond], got

@@ -140,3 +140,52 @@ def test_the_names_of_the_instances():
             wc = {(32, 32): 2, (32, 64): 1, (64, 32): 2, (64, 64): 2, (128, 64): 4}[(bc, bp)]
             kid = 1300000000 + mode * 10000000 + bc * 10000 + bp * 10 + wc
             assert bench.conv_name(kid, "bf16") == "octo::conv_small_kernel<__bf16, %d, %d, %d, %d, %d, %d>" % (bc, bp, wc, wp, minb, mode)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_more_items_on_the_device_than_expected(octo, dtype):
+    """Layers of a downstream model shaped for three items whose batches bring hundreds: a workgroup has many tiles, and while the weights are the larger operand of
+    the expected items tiles go round channels outside, pixels inside, by a number of pixel tiles that only the device knows.  Every tensor of some ROIs against the
+    oracle on the GPU's own crops; a small batch leaves the rest of the larger one's results as they are."""
+    import torch
+    det = zoo.traffic_cascade(dtype).models[0]
+    det.batch_size = 4
+    B = zoo._Builder("child", dtype, 8, 8, "classifier", np.random.default_rng(91))
+    a = B.conv(0, 64, 3, 2, act=zoo.ACT_RELU)
+    b = B.conv(a, 264, 1, 1, act=zoo.ACT_SILU)
+    c = B.conv(b, 512, 3, 2, act=zoo.ACT_RELU)
+    d = B.conv(c, 1024, 1, 1, act=zoo.ACT_SILU)
+    e = B.conv(d, 1000, 1, 1, act=zoo.ACT_RELU)
+    B.m.outputs = [B.fc(B.gap(e), 10)]
+    B.m.batch_size = 480
+    spec = zoo.PipelineSpec("items", [det, B.m], [zoo.Edge(0, 1)], 1000.0, 540, 960, 4, 120)
+    rng = np.random.default_rng(92)
+    geo = octo.letterbox_geometry(540, 960, det.in_h, det.in_w)
+    scenes = [synth.make_scene(rng, 4, 540, 960, counts, 16, 200, log_uniform=True) for counts in ([0, 2, 0, 1], [120] * 4, [1, 0, 2, 0])]
+    n_t = len(B.m.layers)
+    P = octo.Pipeline(spec, keep_all_tensors=1)
+    P.set_expected_items(1, 3)
+    before = None
+    for k, sc in enumerate(scenes):
+        heads = [octo.to_device(v, dtype) for v in synth.planted_heads(rng, det, sc, 540, 960, geo)]
+        for l, v in enumerate(heads):
+            P.set_head(0, l, v)
+        P.submit([torch.from_numpy(f).cuda() for f in sc.frames])
+        P.run()
+        P.collect()
+        n = len(P.get_rois(0))
+        assert (1 <= n < 5, n > 200, 1 <= n < 5)[k], n
+        kids = [int(v) for v in P.layer_info(1)[1]]
+        # (the second batch finds tiles shaped for the three items of the first)
+        assert all(kids[t - 1] // 100000000 == 13 for t in (b, d, e)) and (k != 1 or kids[d - 1] % 10000000 == 320322), kids
+        at = sorted({0, n // 2, n - 1})
+        got = [np.concatenate([P.get_tensor(1, t, 1, first=i) for i in at]) for t in range(n_t + 1)]
+        beyond = [np.concatenate([P.get_tensor(1, t, 1, first=i) for i in (60, 120, 199)]) for t in range(n_t + 1)]
+        ref = nn.run_model(B.m, got[0], keep_all=True)
+        for t in range(1, n_t + 1):
+            assert rel_err(got[t].reshape(ref[t].shape), ref[t]) <= TOL[dtype], (k, t)
+            if k == 2:
+                assert np.array_equal(beyond[t], before[t]), t
+        before = beyond
+    P.close()

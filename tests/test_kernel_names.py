@@ -88,6 +88,20 @@ def test_kernels_whose_loads_run_across_tiles(tmp_path):
             assert bench.conv_name(fn(bc, bp, kv, mode), "bf16") == "octo::conv_flow_kernel<__bf16, %d, %d, %d, %d, %d, %d, %d, %d>" % (nt, bc, bp, wc, kv, nst, minb, mode)
 
 
+def test_kernels_for_launches_of_few_tiles(tmp_path):
+    src = '#include "%s/kernel_ids.h"\nextern "C" int small_kernel_id(int a, int b, int c, int d) { return octo::small_kernel_id(a, b, c, d); }\n' % CSRC
+    (tmp_path / "ids.cpp").write_text(src)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-o", str(tmp_path / "ids.so"), str(tmp_path / "ids.cpp")], check=True)
+    fn = ctypes.CDLL(str(tmp_path / "ids.so")).small_kernel_id
+    found = instances("launch_small_cfg", "conv_small.h")
+    assert {(bc, bp) for _, (bc, bp, *_) in found} == set(bench.SMALL)
+    for _, (bc, bp, wc, wp, minb) in found:
+        # fp32 has two ways to make addresses more, and no 128 x 64 tiles
+        for dt, modes in (("f16", 3), ("bf16", 3), ("f32", 5 if bc < 128 else 0)):
+            for mode in range(modes):
+                assert bench.conv_name(fn(bc, bp, wc, mode), dt) == "octo::conv_small_kernel<%s, %d, %d, %d, %d, %d, %d>" % (CTYPE[dt], bc, bp, wc, wp, minb, mode)
+
+
 def test_an_unknown_id_has_a_name_too():
     for kid in (1403064128 + 4000000, 1804064128, 1700064999, 1899999999, 1499999999, 1805128128):
         for dt in CTYPE:
