@@ -108,49 +108,50 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "e4e5abd8fc8132f7": {
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910876852,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2204265079,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553359597,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629442057,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 993490044,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1079729678,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 272025729,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344670365,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 556106527,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 850163705,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 306417854,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167965400,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 111357444,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355743997,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4368702873,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 2241640183,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1701880699,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838926,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87622590,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 77496298,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 39766269,
+    "23af1573d4d0af0e": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4369331653,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1702666309,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1428750713,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344625210,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250128480,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553370739,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 849458558,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355702077,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282149448,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2200636679,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 353866839,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 992422892,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1909888102,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629428788,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078983983,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 168002115,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628499985,
+        "octo::conv_ksplit_kernel<bool _Accum, int, E, 1, 4, 4>": 29838714,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 47354656,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 22045859,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 34379693,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 32290357,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 29587393,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 14299263,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 8156751,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87631262,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28511216,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 77496285,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64440587,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14285722,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39789453,
         "octo::conv1x1_stream_kernel<_Float16, 1>": 26376770,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39760323,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 15369514,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 27242084,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 9042494,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 47325814,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 128, 1, 8, 3, 2, 0>": 17235789,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 14334212,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 19422840,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 34379692,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 11436854,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21950779,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355778,
         "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14221657,
-        "octo::conv_small_kernel<_Float16, 32, 64, 1, 4, 4, 1>": 18644102,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64431420,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506210,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 22345623,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28510945,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 3223606,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355740,
         "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644813,
         "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123417,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4642418,
+        "octo::conv_small_kernel<_Float16, 32, 32, 2, 2, 4, 1>": 6687054,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1457582,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39505741,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28001393,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42486675,
     },
 }
 
