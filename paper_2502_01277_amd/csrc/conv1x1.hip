@@ -253,8 +253,13 @@ hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipSt
   // 192 37.0 : 40.8; 64 -> 32 at 6.4 5.7 : 5.1, at 16 7.9 : 7.1, at 33 11.8 : 11.1, with residual at 41 16.7 : 14.8, at 59 15.7 : 15.1, 64 -> 8 at 72 16.3 : 17.1.
   // Up to 32 channels before an upsampling, or of items counted on the device, have only the general kernel below the line (64 -> 32 in place at 6.4
   // 5.7 : 7.1, at 33 11.8 : 14.5; alone at 7 4.3 : 5.4).
+  // A count on the device that runs beyond the line of a layer in place, while the stated one lies between that line and the one alone, goes by the running
+  // count: this kernel, conv_small_kernel and conv_flow_kernel sum in one order, and above the line alone nothing is split (here : what the stated count alone would
+  // give, twice as many items as stated: 64 -> 640 on 15 x 57 x 57 21.4 : 32.4, 16 -> 80 with residual on 278 x 14 x 14 8.7 : 11.3, 96 -> 288 on 580 x 7 x 7 12.0 : 14.8).
   const bool step = a.Cin == 64 && small_fits(a, 2) && (a.Cout > 32 || (a.n_split == 0 && !a.up_next));
-  if ((M_split + 31) / 32 * ((a.Cout + 63) / 64) < (step ? (a.in_place ? 48LL : 9LL) : a.Cout <= 64 ? 4LL : a.in_place ? 9LL : 6LL) * num_cu) return hipErrorNotSupported;
+  const long long alone = step ? 9 : a.Cout <= 64 ? 4 : 6, line = !a.in_place ? alone : step ? 48 : a.Cout <= 64 ? 4 : 9;
+  auto below = [&](long long m, long long l) { return (m + 31) / 32 * ((a.Cout + 63) / 64) < l * num_cu; };
+  if (below(M_split, alone) || (below(M_split, line) && below(M, line))) return hipErrorNotSupported;
   return dtype == OCTO_F16 ? launch_stream_typed<_Float16>(a, M, num_cu, s, kernel_id, tm) : launch_stream_typed<__bf16>(a, M, num_cu, s, kernel_id, tm);
 }
 

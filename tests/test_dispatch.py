@@ -152,3 +152,14 @@ def test_both_sides_of_a_line(ids, dtype, layer, pixels, below, beyond):
     s, rows = layer.get("stride", 1), int(pixels * 256 / 32) // 8 * 8        # (the streaming kernel cuts maps into whole tiles)
     got = ids([dict(layer, dtype=dtype, n=1, h=s * (rows + d), w=s * 32) for d in (-8, 8)])
     assert [k // 10 ** (10 - len(str(want))) for k, want in zip(got, (below, beyond))] == [below, beyond], got
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_a_running_count_beyond_the_streaming_kernels_line_in_a_model(ids, dtype):
+    """1x1 layers with the count on the device, the stated one between the streaming kernel's lines alone and in a model: the running count decides.  Where it is
+    large they had gone to conv_flow_kernel and, one K step into more channels than that takes, to the general kernel."""
+    cases = [(669, 7, 176, 232, 334), (580, 7, 96, 288, 290), (15, 57, 64, 640, 7), (71, 7, 40, 2176, 35), (28, 40, 120, 152, 14), (278, 14, 16, 80, 139)]
+    layers = [dict(dtype=dtype, n=n, h=h, w=h, cin=ci, cout=co, split=split, place=1) for n, h, ci, co, split in cases]
+    assert [family(k) for k in ids(layers)] == [STREAM] * len(cases)
+    assert [family(k) for k in ids([dict(l, hint=l["split"] // 2) for l in layers])] == [SMALL] * len(cases)
+    assert [family(k) for k in ids([dict(l, place=0) for l in layers])] == [STREAM] * len(cases)
