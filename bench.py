@@ -108,50 +108,50 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "23af1573d4d0af0e": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4369331653,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1702666309,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1428750713,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344625210,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250128480,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553370739,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 849458558,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355702077,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282149448,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2200636679,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 353866839,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 992422892,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1909888102,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629428788,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078983983,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 168002115,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628499985,
-        "octo::conv_ksplit_kernel<bool _Accum, int, E, 1, 4, 4>": 29838714,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 47354656,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 22045859,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 34379693,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 32290357,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 29587393,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 14299263,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 8156751,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87631262,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28511216,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 77496285,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64440587,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14285722,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39789453,
-        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376770,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 11436854,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21950779,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355778,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14221657,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644813,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123417,
-        "octo::conv_small_kernel<_Float16, 32, 32, 2, 2, 4, 1>": 6687054,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1457582,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39505741,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28001393,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42486675,
+    "b5ae5b93934e0484": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4366556042,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1701517445,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1427621694,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344659777,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250125650,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553380548,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 849818375,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355674081,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282448125,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2201004242,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 353780087,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 992825467,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1909176585,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629432079,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1079049469,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167868577,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628299130,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838938,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 47360214,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 22045870,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 34379723,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 32290465,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 29587421,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 14299272,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 8156755,
+        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87629076,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28511387,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 77496340,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64455996,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14285729,
+        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39783996,
+        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376783,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 11436864,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21950794,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355773,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14221663,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644822,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123422,
+        "octo::conv_small_kernel<_Float16, 32, 32, 2, 2, 4, 1>": 6687060,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1457583,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506704,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28001511,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42487598,
     },
 }
 
