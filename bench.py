@@ -72,6 +72,9 @@ def conv_name(kid: int, dtype: str) -> str:
     named, and runs as stem_pool_any_kernel; no workload here has one."""
     d = kid - 1000000000
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
+    if d >= 1000000000:                                  # 3x3 layers of few tiles, patch of all channels in LDS: digits S K BBB PPP
+        s, ks, bc, bp = d // 10000000 % 10, d // 1000000 % 10, d // 1000 % 1000, d % 1000
+        return "octo::conv3x3_held_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp * ks // 128, ks, s)
     if 200000000 <= d < 300000000:                       # general form whose loads run across tiles: digits M BBB PPP K
         mode, bc, bp, kv = (d - 200000000) // 10000000, d // 10000 % 1000, d // 10 % 1000, d % 10
         return "octo::conv_flow_kernel<%s, %d, %d, %d, %d, %d, 3, %d, %d>" % ((ctype, FLOW[(bc, bp)][0], bc, bp, FLOW[(bc, bp)][1], kv, FLOW[(bc, bp)][2], mode)) if (bc, bp) in FLOW else "convolution kernel %d" % kid

@@ -26,6 +26,7 @@
 #include "mfma_common.h"
 #include "conv_ksplit.h"
 #include "conv3x3_mid.h"
+#include "conv3x3_held.h"
 #include "conv_flow_choice.h"
 #include "conv_small_choice.h"
 #include <hip/hip_ext.h>
@@ -641,6 +642,8 @@ static hipError_t launch_typed(const ConvArgs& a, int num_cu, hipStream_t s, int
     return !pw && t.pipe && t.bc == 64 && t.bp == 64 && (m + 63) / 64 * ((a.Cout + 63) / 64) <= 2LL * num_cu;
   };
   if constexpr (sizeof(T) == 2) {
+    const hipError_t eh = launch_held<T>(a, M_split, num_cu, s, kernel_id, tm);
+    if (eh != hipErrorNotSupported) return eh;
     const bool fits = small_fits(a, 2), patch = fits && small_takes_3x3(a, M_split, num_cu);
     if (!patch) {
       const hipError_t em = launch_mid<T>(a, M_split, num_cu, s, kernel_id, tm);
@@ -813,6 +816,18 @@ bool conv_prepare(ConvArgs& a, int dtype) {
   a.magic_cin = a.Cin > 1 ? (unsigned)((1ull << 32) / (unsigned)a.Cin) + 1u : 0u;
   a.magic_kw = a.kw > 1 ? (unsigned)((1ull << 32) / (unsigned)a.kw) + 1u : 0u;
   return true;
+}
+
+__global__ __launch_bounds__(256) void held_pack_kernel(const u32x4* w, int kp, int cin, int n, u32x4* out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int lane = i & 63, m = lane & 31, g = i >> 6, tap = g % 9, c = g / 9 % (cin / 16), k = g / 9 / (cin / 16) * 32 + 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3);
+  out[i] = w[((size_t)k * kp + tap * cin + c * 16 + (lane >> 5) * 8) / 8];
+}
+hipError_t launch_held_pack(const void* w, int kp, int cin, int cout, void* out, hipStream_t s) {
+  const int n = cout * (cin / 8) * 9;
+  hipLaunchKernelGGL(held_pack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const u32x4*)w, kp, cin, n, (u32x4*)out);
+  return hipGetLastError();
 }
 
 hipError_t launch_conv(int dtype, const ConvArgs& a0, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm) {

@@ -38,6 +38,9 @@ constexpr int stream1_kernel_id(int tc, int cin) { return 1500000000 + 32 * tc *
 // split-K kernel (conv_ksplit.h), digits 16 S BBB PPP: K split, channel tile, pixel tile
 constexpr int ksplit_kernel_id(int bc, int bp, int ks) { return 1600000000 + ks * 1000000 + bc * 1000 + bp; }
 
+// 3x3 layers of few tiles (conv3x3_held.h), digits 20 S K BBB PPP: stride, wavefronts that share K, channel tile, pixel tile
+constexpr int held_kernel_id(int bc, int bp, int ks, int s) { return 2000000000 + s * 10000000 + ks * 1000000 + bc * 1000 + bp; }
+
 // first layers (stem.hip), digits 19 F BBB KK P: with the max-pool behind it, channel tile, kernel height, kernel width on the
 // pixel-pair view.  With the max-pool, SiLU and channel counts that are no multiple of 8 run stem_pool_any_kernel under the same id
 constexpr int stem_kernel_id(int bc, int kh, int pkw, bool pool) { return 1900000000 + (pool ? 1000000 : 0) + bc * 1000 + kh * 10 + pkw; }

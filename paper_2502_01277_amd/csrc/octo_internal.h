@@ -19,6 +19,7 @@ struct TensorView {
   int ld = 0, coff = 0;
 };
 
+struct HeldPlan;
 struct ConvArgs {
   const void* x;
   const void* w;        // packed weights [cout_pad][kp]
@@ -58,6 +59,7 @@ struct ConvArgs {
   // 8-bit floating point storage only: y = act(acc * scale[c] + bias[c] (+ res * res_scale)), stored as
   // E4M3(y * y_inv_scale) unless out_f32.  scale: device, one factor per output channel, padded like the bias.
   const float* scale;
+  const HeldPlan* held;    // host only: what a model keeps for a 3x3 layer that may run on conv3x3_held_kernel (conv3x3_held_choice.h), or null
   float res_scale, y_inv_scale;
 };
 
@@ -72,6 +74,8 @@ hipError_t launch_conv(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, 
 hipError_t launch_stem(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 // 1x1 layers of large maps with resident weights; hipErrorNotSupported when the layer does not fit it
 hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
+// The weights of a 3x3 layer, 16-bit types, from rows of kp values into the order that conv3x3_held_kernel reads them (held_weight_bytes, conv3x3_held_choice.h)
+hipError_t launch_held_pack(const void* w, int kp, int cin, int cout, void* out, hipStream_t s);
 enum { KID_NONE = 0, KID_MAXPOOL = 1, KID_UPSAMPLE = 2, KID_COPY = 3, KID_ADD = 4, KID_GAP = 5 };
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out);
 

@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "octo_internal.h"
+#include "conv3x3_held_choice.h"
 
 using namespace octo;
 
@@ -61,6 +62,8 @@ struct LayerPlan {
   int cin = 0;
   void* d_weight = nullptr;
   float* d_bias = nullptr;
+  bool held = false;              // a 3x3 layer that may run on conv3x3_held_kernel, and what is kept for that
+  HeldPlan held_plan;
   int K = 0, Kp = 0, cout_pad = 0;
   std::vector<int> copy_inputs;   // concat: inputs that could not be aliased into the output buffer
   double flops = 0, bytes = 0;    // per item
@@ -506,6 +509,8 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
     const size_t elems = conv_packed_weight_elems(lp.L.cout, lp.L.kh, pk_kw, pk_cin, m.d.dtype, &lp.Kp, &lp.cout_pad);
     lp.d_weight = ar.alloc(elems * es + 512);   // slack: the conv prefetch may read a K step past the last row
     lp.d_bias = (float*)ar.alloc((size_t)lp.cout_pad * sizeof(float));
+    lp.held = es == 2 && lp.L.op == OCTO_CONV && !lp.pair_view && held_layer(lp.L.kh, lp.L.kw, lp.L.stride, lp.L.pad, m.tensors[lp.L.in[0]].h, lp.cin, lp.L.cout);
+    void* d_held = lp.held ? ar.alloc(held_weight_bytes(lp.L.cout, lp.cin)) : nullptr;
     size_t twin_elems = 0;
     int twin_kp = 0;
     if (lp.fuse_twin) {      // this layer's and the next one's weights as one matrix (both 1x1 on the same input: same K)
@@ -533,6 +538,12 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
         memcpy(host.data() + (size_t)k * lp.Kp * es, (const char*)lp.L.weight + (size_t)k * lp.K * es, (size_t)lp.K * es);
     }
     HIPCHK(p, hipMemcpy(lp.d_weight, host.data(), host.size(), hipMemcpyHostToDevice));
+    if (lp.held) {
+      const TensorPlan &tx = m.tensors[lp.L.in[0]], &ty = m.tensors[li + 1];
+      lp.held_plan = held_plan(lp.L.stride, tx.w, ty.h, ty.w, lp.cin, lp.L.cout);
+      lp.held_plan.w = d_held;
+      HIPCHK(p, launch_held_pack(lp.d_weight, lp.Kp, lp.cin, lp.L.cout, d_held, nullptr));
+    }
     std::vector<float> hb(lp.cout_pad, 0.f);
     memcpy(hb.data(), lp.L.bias, (size_t)lp.L.cout * sizeof(float));
     HIPCHK(p, hipMemcpy(lp.d_bias, hb.data(), hb.size() * sizeof(float), hipMemcpyHostToDevice));
@@ -572,7 +583,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (L.n_in == 2) { const TensorView r = view_of(m, L.in[1]); a.res = r.ptr; a.res_ld = r.ld; a.res_coff = r.coff; }
       if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
-      a.up_next = lp.up_next; a.in_place = 1;
+      a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr;
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (lp.fuse_twin) {
         const TensorView y2 = view_of(m, i + 2);
@@ -1167,6 +1178,7 @@ octo_status octo_pipeline_create(const octo_pipeline_desc* desc, void* device_wo
   Arena ar;
   ar.base = (char*)device_workspace; ar.cap = bytes;
   octo_status st = build(p, desc, ar);
+  if (st == OCTO_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(p, OCTO_EHIP, "rearranging the weights failed");     // the streams of later calls do not wait for it
   if (st == OCTO_OK) {
     int dev = 0; hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) p->num_cu = prop.multiProcessorCount;

@@ -1,0 +1,105 @@
+"""The host side of conv3x3_held_kernel, without a GPU: the geometry of its tiles over random maps - where the loader puts every input pixel of a patch and where
+a tap reads it -, and the lines of its rule on both sides."""
+import random
+import subprocess
+
+import pytest
+
+import dispatch
+
+SOURCE = r'''
+#include "csrc/conv3x3_held_choice.h"
+#include <cstdio>
+int main() {
+  int n, h, w, ci, co, st, res, dyn, hint;
+  while (scanf("%d %d %d %d %d %d %d %d %d", &n, &h, &w, &ci, &co, &st, &res, &dyn, &hint) == 9) {
+    octo::ConvArgs a{};
+    a.n = n; a.H = h; a.W = w; a.Cin = a.x_ld = ci; a.Cout = a.y_ld = co; a.Ho = (h - 1) / st + 1; a.Wo = (w - 1) / st + 1; a.stride_h = a.stride_w = st;
+    a.kh = a.kw = 3; a.n_hint = hint; if (dyn) a.n_dyn = (int*)1; if (res) a.res = (void*)16;
+    octo::HeldPlan p = octo::held_plan(st, a.W, a.Ho, a.Wo, ci, co);
+    a.held = &p;
+    const int can = octo::held_layer(3, 3, st, 1, h, ci, co) && octo::held_fits(a);
+    printf("%d %d", can, can ? octo::held_choose(a, (long long)(dyn ? dyn : n) * a.Ho * a.Wo, 256) : -1);
+    for (int i = 0; i < 3; ++i) { const octo::HeldGeom& g = p.geom[i]; printf(" %d %d %d %d %d %d %d %d", g.rows, g.TH, g.TW, g.PW, g.PH, g.halo, g.tiles_x, g.lds); }
+    printf("\n");
+  }
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("held")
+    (d / "held.cpp").write_text(SOURCE)
+    dispatch.compile_host(["-o", str(d / "held"), str(d / "held.cpp"), "-L", dispatch.ROCM + "/lib", "-lamdhip64", "-Wl,-rpath," + dispatch.ROCM + "/lib"])
+
+    def run(layers):
+        """(n, h, w, cin, cout, stride, residual, items the count on the device is stated as (0: none there), expected): can, tile, [geometry of the three]."""
+        text = "\n".join(" ".join(map(str, l)) for l in layers) + "\n"
+        out = subprocess.run([str(d / "held")], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+        rows = [[int(v) for v in o.split()] for o in out[:len(layers)]]
+        return [(r[0], r[1], [dict(zip(("rows", "TH", "TW", "PW", "PH", "halo", "tiles_x", "lds"), r[2 + 8 * i:10 + 8 * i])) for i in range(3)]) for r in rows]
+    return run
+
+
+def test_every_tap_reads_the_pixel_that_the_loader_put_there(ask):
+    rng = random.Random(3)
+    layers = [(rng.randint(1, 9), rng.randint(4, 90), rng.randint(4, 90), 64 * rng.randint(1, 8), 64, rng.choice([1, 1, 2]), 0, 0, 0) for _ in range(300)]
+    layers = [l if l[5] == 1 else (l[0], l[1] // 2 * 2) + l[2:] for l in layers]
+    seen = 0
+    for (n, h, w, cin, _, s, *_), (_, _, geoms) in zip(layers, ask(layers)):
+        ho, wo = (h - 1) // s + 1, (w - 1) // s + 1
+        for bp, g in zip((32, 64, 128), geoms):
+            if not g["rows"]:
+                continue
+            seen += 1
+            TH, TW, PW, PH, halo, rows = (g[k] for k in ("TH", "TW", "PW", "PH", "halo", "rows"))
+            assert TH * TW <= bp and 4 * wo * TH >= 3 * bp * g["tiles_x"] and TW * g["tiles_x"] >= wo
+            assert PH * PW + 2 <= rows and rows % 32 == 0 and cin // 64 * rows * 128 <= g["lds"] <= 160 * 1024
+            tv, tx = rng.randrange((n * ho + TH - 1) // TH), rng.randrange(g["tiles_x"])
+            v0, x0 = tv * TH, tx * TW
+            # the loader: row p of LDS holds input pixel (stack row, column), and its 16-byte vectors in an order that depends on a position
+            holds = {}
+            for p in range(rows):
+                pr, pc = divmod(p, PW)
+                v, x = s * v0 - 1 + pr, s * x0 - halo + pc
+                if pr < PH and 0 <= v < n * h and 0 <= x < w:
+                    holds[p] = (v, x, (pr * TW + pc if s == 1 else p) >> 1 & 7)
+            assert not {rows - 2, rows - 1} & set(holds)
+            for q in range(bp):
+                ty, ox = divmod(q, TW)
+                v = v0 + ty
+                if ty >= TH or v >= n * ho or x0 + ox >= wo:
+                    continue
+                img, yy = divmod(v, ho)
+                for tap in range(9):
+                    r, c = tap // 3, tap % 3 - 1
+                    iy, ix = s * yy + r - 1, s * (x0 + ox) + c
+                    if not (0 <= iy < h and 0 <= ix < w):
+                        continue
+                    p = (s * ty + r) * PW + s * ox + c + halo
+                    pos = p - (ty + r) * (PW - TW) if s == 1 else p
+                    assert holds[p] == (img * h + iy, ix, pos >> 1 & 7)
+    assert seen > 500
+
+
+def test_which_layers_have_the_form(ask):
+    can = [c for c, _, _ in ask([(4, 20, 20, 256, 256, 1, 0, 0, 0), (4, 20, 20, 96, 256, 1, 0, 0, 0), (4, 20, 20, 256, 255, 1, 0, 0, 0), (4, 20, 20, 576, 256, 1, 0, 0, 0),
+                                 (4, 21, 20, 256, 256, 2, 0, 0, 0), (4, 20, 21, 256, 256, 2, 0, 0, 0)])]
+    assert can == [1, 0, 0, 0, 0, 1]
+
+
+def test_both_sides_of_the_lines(ask):
+    cases = [
+        ((4, 20, 20, 256, 256, 1, 0, 0, 0), 0), ((8, 20, 20, 256, 256, 1, 0, 0, 0), 1), ((16, 20, 20, 256, 256, 1, 0, 0, 0), 2),
+        ((32, 20, 20, 256, 256, 1, 0, 0, 0), -1),                                       # more than are resident
+        ((63, 7, 7, 512, 512, 1, 0, 0, 0), 2), ((134, 7, 7, 512, 512, 1, 0, 0, 0), -1),
+        ((48, 40, 40, 128, 128, 1, 0, 0, 0), 2), ((64, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # six per compute unit
+        ((480, 40, 40, 128, 128, 1, 0, 48, 48), -1), ((480, 40, 40, 128, 128, 1, 0, 16, 16), 2), ((16, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # with the count on the device two
+        ((5, 80, 80, 64, 64, 1, 0, 0, 0), -1), ((6, 80, 80, 64, 64, 1, 0, 0, 0), 2), ((12, 80, 80, 64, 64, 1, 0, 0, 0), -1),
+        ((2, 80, 80, 128, 128, 2, 0, 0, 0), 0), ((6, 80, 80, 128, 128, 2, 0, 0, 0), -1), ((1, 14, 14, 128, 256, 2, 0, 0, 0), -1), ((1, 160, 160, 64, 128, 2, 0, 0, 0), -1),
+        ((30, 14, 14, 256, 512, 2, 0, 0, 0), 1), ((134, 14, 14, 256, 512, 2, 0, 0, 0), -1),
+        # 64 x 32 and 64 x 64 tiles by the running count; what else is decided by the stated one
+        ((480, 14, 14, 256, 256, 1, 0, 4, 4), 0), ((480, 14, 14, 256, 256, 1, 0, 4, 300), 1), ((480, 14, 14, 256, 256, 1, 0, 41, 3), 2),
+        ((480, 14, 14, 256, 256, 1, 0, 200, 3), -1)]
+    assert [t for _, t, _ in ask([c for c, _ in cases])] == [t for _, t in cases]
