@@ -45,4 +45,7 @@ constexpr int held_kernel_id(int bc, int bp, int ks, int s) { return 2000000000 
 // pixel-pair view.  With the max-pool, SiLU and channel counts that are no multiple of 8 run stem_pool_any_kernel under the same id
 constexpr int stem_kernel_id(int bc, int kh, int pkw, bool pool) { return 1900000000 + (pool ? 1000000 : 0) + bc * 1000 + kh * 10 + pkw; }
 
+// the first layers of a detector in one launch (entry.hip)
+constexpr int KID_ENTRY = 2100000000;
+
 }  // namespace octo

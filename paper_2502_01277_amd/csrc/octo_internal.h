@@ -76,6 +76,14 @@ hipError_t launch_stem(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, 
 hipError_t launch_conv1x1_stream(int dtype, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 // The weights of a 3x3 layer, 16-bit types, from rows of kp values into the order that conv3x3_held_kernel reads them (held_weight_bytes, conv3x3_held_choice.h)
 hipError_t launch_held_pack(const void* w, int kp, int cin, int cout, void* out, hipStream_t s);
+// The first layers of a detector in one launch (16-bit types, SiLU): 3 -> 32, 6x6 / stride 2 / pad 2 on the pixel-pair view; 32 -> 64, 3x3 / stride 2 / pad 1; two 1x1
+// layers 64 -> 32 whose weights are stacked.  w, bias, kp: of those three.  hipErrorNotSupported when a tensor does not fit.
+struct EntryArgs {
+  const void* x; int n, H, W;
+  const void* w[3]; const float* bias[3]; int kp[3];
+  void* y[2]; int y_ld[2], y_coff[2];
+};
+hipError_t launch_entry(int dtype, const EntryArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 enum { KID_NONE = 0, KID_MAXPOOL = 1, KID_UPSAMPLE = 2, KID_COPY = 3, KID_ADD = 4, KID_GAP = 5 };
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out);
 

@@ -75,6 +75,9 @@ struct LayerPlan {
   // stride 1 and horizontal padding pair_pad, on an image of half the width.
   bool pair_view = false;
   int pair_kw = 0, pair_pad = 0, pair_shift = 0;
+  // This first layer, the down-sampling layer behind it and the two 1x1 layers behind that are one launch where the kernel takes them (entry_done: it did; the next three
+  // layers then do nothing).
+  bool fuse_entry = false, entry_done = false;
   // The next layer is a 3x3 / stride-2 / pad-1 max-pool and the only reader of this first layer's output: the
   // convolution kernel pools its own tile and writes the pooled tensor, the pool layer does nothing (its kernel id
   // then reads KID_NONE).  Cleared for good the first time no kernel accepts the fused form.
@@ -95,7 +98,7 @@ struct LayerPlan {
   bool fuse_twin = false;
   void* d_weight_twin = nullptr;
   float* d_bias_twin = nullptr;
-  int twin_cout_pad = 0;
+  int twin_cout_pad = 0, twin_kp = 0;
 };
 
 struct TensorPlan {
@@ -418,6 +421,19 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     if (ta.f32 || tb.f32 || ((a.L.cout | b.L.cout | ta.ld | ta.coff | tb.ld | tb.coff) & 7)) continue;
     a.fuse_twin = true;
   }
+  // the first layers of a detector: 6x6 / stride 2 from the image, 3x3 / stride 2, two 1x1 layers, each the only reader of what is before it
+  for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_entry = false;
+  if (allow_fusion && dtype_size(m.d.dtype) == 2 && m.layers.size() > 4 && m.layers[0].pair_view && m.layers[2].fuse_twin) {
+    const octo_layer &A = m.layers[0].L, &B = m.layers[1].L, &C = m.layers[2].L, &D = m.layers[3].L;
+    auto plain = [](const octo_layer& L, int in, int k, int st, int pad, int cout) {
+      return L.op == OCTO_CONV && L.n_in == 1 && L.in[0] == in && L.kh == k && L.kw == k && L.stride == st && L.pad == pad && L.cout == cout && L.act == OCTO_ACT_SILU;
+    };
+    int readers[3] = {0, 0, 0};
+    for (const LayerPlan& q : m.layers)
+      for (int k = 0; k < q.L.n_in; ++k) if (q.L.in[k] <= 2) ++readers[q.L.in[k]];
+    m.layers[0].fuse_entry = plain(A, 0, 6, 2, 2, 32) && plain(B, 1, 3, 2, 1, 64) && plain(C, 2, 1, 1, 0, 32) && plain(D, 2, 1, 1, 0, 32) &&
+                             readers[0] == 1 && readers[1] == 1 && readers[2] == 2 && !is_output[1] && !is_output[2];
+  }
   // the end of a classifier (also with every layer on its own: the launch writes every tensor, and a logit's order of summation stays the same)
   for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_label = false;
   if (const int i = (int)m.layers.size() - 2; m.d.kind == OCTO_CLASSIFIER && i >= 0 && m.d.outputs[0] == i + 2) {
@@ -436,6 +452,8 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
       const int r = m.tensors[i + 2].root;
       birth[r] = std::min(birth[r], i);
     }
+  if (m.layers[0].fuse_entry)
+    for (int t = 3; t <= 4; ++t) birth[m.tensors[t].root] = std::min(birth[m.tensors[t].root], 0);
   for (int i = 0; i < (int)m.layers.size(); ++i)
     if (m.layers[i].fuse_chain)
       for (int q = 2; q <= 3; ++q) { const int r = m.tensors[i + q].root; birth[r] = std::min(birth[r], i); }
@@ -512,7 +530,7 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
     lp.held = es == 2 && lp.L.op == OCTO_CONV && !lp.pair_view && held_layer(lp.L.kh, lp.L.kw, lp.L.stride, lp.L.pad, m.tensors[lp.L.in[0]].h, lp.cin, lp.L.cout);
     void* d_held = lp.held ? ar.alloc(held_weight_bytes(lp.L.cout, lp.cin)) : nullptr;
     size_t twin_elems = 0;
-    int twin_kp = 0;
+    int& twin_kp = lp.twin_kp;
     if (lp.fuse_twin) {      // this layer's and the next one's weights as one matrix (both 1x1 on the same input: same K)
       twin_elems = conv_packed_weight_elems(lp.L.cout + m.layers[li + 1].L.cout, 1, 1, lp.cin, m.d.dtype, &twin_kp, &lp.twin_cout_pad);
       lp.d_weight_twin = ar.alloc(twin_elems * es + 512);
@@ -585,6 +603,16 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (n_dyn) a.n_split = m.items_split;
       a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr;
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
+      if (i > 0 && i <= 3 && m.layers[0].fuse_entry && m.layers[0].entry_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
+      if (lp.fuse_entry && !n_dyn) {
+        const LayerPlan &B = m.layers[1], &C = m.layers[2];
+        const TensorView c = view_of(m, 3), d = view_of(m, 4);
+        const EntryArgs f{x.ptr, n, x.h, x.w, {lp.d_weight, B.d_weight, C.d_weight_twin}, {lp.d_bias, B.d_bias, C.d_bias_twin}, {lp.Kp, B.Kp, C.twin_kp},
+                          {c.ptr, d.ptr}, {c.ld, d.ld}, {c.coff, d.coff}};
+        const hipError_t e = launch_entry(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
+        lp.entry_done = e == hipSuccess;
+        if (e != hipErrorNotSupported) return e;
+      }
       if (lp.fuse_twin) {
         const TensorView y2 = view_of(m, i + 2);
         ConvArgs f = a;
@@ -1464,6 +1492,16 @@ octo_status octo_set_layer_timing(octo_pipeline* p, int32_t enable) {
   return OCTO_OK;
 }
 
+// Per item work, and bytes of weights, of the first layers of a model where they ran as one launch: all of it with the first.
+static bool entry_work(const ModelPlan& m, int i, double* flops, double* bytes, double* weight_bytes) {
+  if (!m.layers[0].fuse_entry || i > 3 || m.layers[0].kernel_id != KID_ENTRY) return false;
+  const LayerPlan *L = m.layers.data(), &C = L[2], &D = L[3];
+  if (flops) *flops = i ? 0.0 : L[0].flops + L[1].flops + C.flops + D.flops;
+  if (bytes) *bytes = i ? 0.0 : L[0].input_bytes + C.bytes - C.input_bytes + D.bytes - D.input_bytes;
+  if (weight_bytes) *weight_bytes = i ? 0.0 : L[0].weight_bytes + L[1].weight_bytes + C.weight_bytes + D.weight_bytes;
+  return true;
+}
+
 octo_status octo_get_layer_info(octo_pipeline* p, int32_t model, float* ms, int32_t* kernel_id, double* flops, double* bytes,
                                 double* weight_bytes, int32_t cap, int32_t* n) {
   if (!p) return OCTO_EINVAL;
@@ -1473,7 +1511,8 @@ octo_status octo_get_layer_info(octo_pipeline* p, int32_t model, float* ms, int3
   for (int i = 0; i < *n; ++i) {
     if (ms) ms[i] = (model < (int)p->last_layer_ms.size() && i < (int)p->last_layer_ms[model].size()) ? p->last_layer_ms[model][i] : 0.f;
     if (kernel_id) kernel_id[i] = m.layers[i].kernel_id;
-    // two layers in one launch: the work is reported with the first, the second did nothing
+    // layers in one launch: the work is reported with the first, the others did nothing
+    if (entry_work(m, i, flops ? flops + i : nullptr, bytes ? bytes + i : nullptr, weight_bytes ? weight_bytes + i : nullptr)) continue;
     const bool first = m.layers[i].fuse_twin && i + 1 < (int)m.layers.size(), second = i > 0 && m.layers[i - 1].fuse_twin;
     if (flops) flops[i] = second ? 0.0 : m.layers[i].flops + (first ? m.layers[i + 1].flops : 0.0);
     if (bytes) bytes[i] = second ? 0.0 : m.layers[i].bytes + (first ? m.layers[i + 1].bytes - m.layers[i].input_bytes : 0.0);
@@ -1501,6 +1540,12 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
     float t = 0.f;
     HIPCHK(p, hipEventElapsedTime(&t, e0, e1));
     ms[i] = t / iters;
+    double f = 0, b = 0, w = 0;
+    if (entry_work(m, i, &f, &b, &w)) {
+      if (flops) flops[i] = f * n;
+      if (bytes) bytes[i] = b * n + w;
+      continue;
+    }
     const bool first = m.layers[i].fuse_twin && i + 1 < (int)m.layers.size(), second = i > 0 && m.layers[i - 1].fuse_twin;
     if (flops) flops[i] = second ? 0.0 : (m.layers[i].flops + (first ? m.layers[i + 1].flops : 0.0)) * n;
     if (bytes) bytes[i] = second ? 0.0 : (m.layers[i].bytes + (first ? m.layers[i + 1].bytes - m.layers[i].input_bytes : 0.0)) * n +
