@@ -74,6 +74,8 @@ def conv_name(kid: int, dtype: str) -> str:
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
     if kid == 2100000000:                                # the first layers of a detector in one launch
         return "octo::entry_kernel<%s>" % ctype
+    if kid == 2110000000:                                # a cross-stage block of 32 channels in one launch, with a shortcut as the detectors have it
+        return "octo::block_kernel<%s, true>" % ctype
     if d >= 1000000000:                                  # 3x3 layers of few tiles, patch of all channels in LDS: digits S K BBB PPP
         s, ks, bc, bp = d // 10000000 % 10, d // 1000000 % 10, d // 1000 % 1000, d % 1000
         return "octo::conv3x3_held_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp * ks // 128, ks, s)

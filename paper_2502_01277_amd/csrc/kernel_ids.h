@@ -47,5 +47,7 @@ constexpr int stem_kernel_id(int bc, int kh, int pkw, bool pool) { return 190000
 
 // the first layers of a detector in one launch (entry.hip)
 constexpr int KID_ENTRY = 2100000000;
+// a cross-stage block of 32 channels in one launch (block.hip)
+constexpr int KID_BLOCK = 2110000000;
 
 }  // namespace octo

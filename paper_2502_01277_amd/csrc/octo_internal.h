@@ -84,6 +84,16 @@ struct EntryArgs {
   void* y[2]; int y_ld[2], y_coff[2];
 };
 hipError_t launch_entry(int dtype, const EntryArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
+// A cross-stage block of 32 channels behind its entry convolutions in one launch (16-bit types, SiLU): 1x1 32 -> 32 of x, 3x3 / pad 1 32 -> 32 of that (plus x with a
+// shortcut), 1x1 64 -> 64 of the concatenation of that and z.  w, bias, kp: of those three.  hipErrorNotSupported when a tensor does not fit.
+struct BlockArgs {
+  const void* x; int x_ld, x_coff;
+  const void* z; int z_ld, z_coff;
+  void* y; int y_ld, y_coff;
+  int n, H, W, shortcut;
+  const void* w[3]; const float* bias[3]; int kp[3];
+};
+hipError_t launch_block(int dtype, const BlockArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 enum { KID_NONE = 0, KID_MAXPOOL = 1, KID_UPSAMPLE = 2, KID_COPY = 3, KID_ADD = 4, KID_GAP = 5 };
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out);
 

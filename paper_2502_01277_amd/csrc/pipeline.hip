@@ -78,6 +78,9 @@ struct LayerPlan {
   // This first layer, the down-sampling layer behind it and the two 1x1 layers behind that are one launch where the kernel takes them (entry_done: it did; the next three
   // layers then do nothing).
   bool fuse_entry = false, entry_done = false;
+  // This 1x1 layer and the next three - 3x3, concatenation with another tensor, 1x1 - are one launch where the kernel takes them (block_done: it did; the next three layers
+  // then do nothing).
+  bool fuse_block = false, block_done = false;
   // The next layer is a 3x3 / stride-2 / pad-1 max-pool and the only reader of this first layer's output: the
   // convolution kernel pools its own tile and writes the pooled tensor, the pool layer does nothing (its kernel id
   // then reads KID_NONE).  Cleared for good the first time no kernel accepts the fused form.
@@ -434,6 +437,22 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     m.layers[0].fuse_entry = plain(A, 0, 6, 2, 2, 32) && plain(B, 1, 3, 2, 1, 64) && plain(C, 2, 1, 1, 0, 32) && plain(D, 2, 1, 1, 0, 32) &&
                              readers[0] == 1 && readers[1] == 1 && readers[2] == 2 && !is_output[1] && !is_output[2];
   }
+  // a cross-stage block of 32 channels behind its entry convolutions, each layer the only reader of the one before
+  for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_block = false;
+  for (int i = 0; allow_fusion && dtype_size(m.d.dtype) == 2 && i + 3 < (int)m.layers.size(); ++i) {
+    const octo_layer &A = m.layers[i].L, &B = m.layers[i + 1].L, &C = m.layers[i + 2].L, &D = m.layers[i + 3].L;
+    auto conv = [&](const octo_layer& L, int in, int k, int cin, int cout) {
+      return L.op == OCTO_CONV && L.in[0] == in && L.kh == k && L.kw == k && L.stride == 1 && L.pad == k / 2 && L.act == OCTO_ACT_SILU && L.cout == cout && m.tensors[in].c == cin;
+    };
+    if (!conv(A, A.in[0], 1, 32, 32) || A.n_in != 1 || m.layers[i].pair_view || m.layers[i].fuse_twin || (i > 0 && m.layers[i - 1].fuse_twin) || !conv(B, i + 1, 3, 32, 32)) continue;
+    if (!(B.n_in == 1 || (B.n_in == 2 && B.in[1] == A.in[0] && B.res_mode == OCTO_RES_AFTER_ACT))) continue;
+    if (C.op != OCTO_CONCAT || C.n_in != 2 || C.in[0] != i + 2 || C.in[1] > i || m.tensors[C.in[1]].c != 32 || !conv(D, i + 3, 1, 64, 64) || D.n_in != 1) continue;
+    int readers[3] = {0, 0, 0};
+    for (const LayerPlan& q : m.layers)
+      for (int k = 0; k < q.L.n_in; ++k) if (q.L.in[k] > i && q.L.in[k] <= i + 3) ++readers[q.L.in[k] - i - 1];
+    m.layers[i].fuse_block = readers[0] == 1 && readers[1] == 1 && readers[2] == 1 && !is_output[i + 1] && !is_output[i + 2] && !is_output[i + 3] &&
+                             !m.layers[i + 3].fuse_twin && !m.layers[i + 3].fuse_up;
+  }
   // the end of a classifier (also with every layer on its own: the launch writes every tensor, and a logit's order of summation stays the same)
   for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_label = false;
   if (const int i = (int)m.layers.size() - 2; m.d.kind == OCTO_CLASSIFIER && i >= 0 && m.d.outputs[0] == i + 2) {
@@ -452,6 +471,8 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
       const int r = m.tensors[i + 2].root;
       birth[r] = std::min(birth[r], i);
     }
+  for (int i = 0; i < (int)m.layers.size(); ++i)
+    if (m.layers[i].fuse_block) { const int r = m.tensors[i + 4].root; birth[r] = std::min(birth[r], i); }
   if (m.layers[0].fuse_entry)
     for (int t = 3; t <= 4; ++t) birth[m.tensors[t].root] = std::min(birth[m.tensors[t].root], 0);
   for (int i = 0; i < (int)m.layers.size(); ++i)
@@ -589,6 +610,8 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
   const octo_layer& L = lp.L;
   const TensorView x = view_of(m, L.in[0]);
   const TensorView y = view_of(m, i + 1);
+  for (int b = std::max(0, i - 3); b < i; ++b)
+    if (m.layers[b].fuse_block && m.layers[b].block_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
   switch (L.op) {
     case OCTO_CONV: case OCTO_FC: {
       ConvArgs a{};
@@ -604,6 +627,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr;
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (i > 0 && i <= 3 && m.layers[0].fuse_entry && m.layers[0].entry_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
+      lp.entry_done = false;
       if (lp.fuse_entry && !n_dyn) {
         const LayerPlan &B = m.layers[1], &C = m.layers[2];
         const TensorView c = view_of(m, 3), d = view_of(m, 4);
@@ -611,6 +635,16 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
                           {c.ptr, d.ptr}, {c.ld, d.ld}, {c.coff, d.coff}};
         const hipError_t e = launch_entry(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
         lp.entry_done = e == hipSuccess;
+        if (e != hipErrorNotSupported) return e;
+      }
+      lp.block_done = false;
+      if (lp.fuse_block && !n_dyn) {
+        const LayerPlan &B = m.layers[i + 1], &D = m.layers[i + 3];
+        const TensorView z = view_of(m, m.layers[i + 2].L.in[1]), o = view_of(m, i + 4);
+        const BlockArgs f{x.ptr, x.ld, x.coff, z.ptr, z.ld, z.coff, o.ptr, o.ld, o.coff, n, x.h, x.w, B.L.n_in == 2,
+                          {lp.d_weight, B.d_weight, D.d_weight}, {lp.d_bias, B.d_bias, D.d_bias}, {lp.Kp, B.Kp, D.Kp}};
+        const hipError_t e = launch_block(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
+        lp.block_done = e == hipSuccess;
         if (e != hipErrorNotSupported) return e;
       }
       if (lp.fuse_twin) {
@@ -1492,14 +1526,20 @@ octo_status octo_set_layer_timing(octo_pipeline* p, int32_t enable) {
   return OCTO_OK;
 }
 
-// Per item work, and bytes of weights, of the first layers of a model where they ran as one launch: all of it with the first.
-static bool entry_work(const ModelPlan& m, int i, double* flops, double* bytes, double* weight_bytes) {
-  if (!m.layers[0].fuse_entry || i > 3 || m.layers[0].kernel_id != KID_ENTRY) return false;
-  const LayerPlan *L = m.layers.data(), &C = L[2], &D = L[3];
-  if (flops) *flops = i ? 0.0 : L[0].flops + L[1].flops + C.flops + D.flops;
-  if (bytes) *bytes = i ? 0.0 : L[0].input_bytes + C.bytes - C.input_bytes + D.bytes - D.input_bytes;
-  if (weight_bytes) *weight_bytes = i ? 0.0 : L[0].weight_bytes + L[1].weight_bytes + C.weight_bytes + D.weight_bytes;
-  return true;
+// Per item work, and bytes of weights, of four layers that ran as one launch: all of it with the first.  False for a layer that is none of those.
+static bool fused_work(const ModelPlan& m, int i, double* flops, double* bytes, double* weight_bytes) {
+  for (int b = std::max(0, i - 3); b <= i; ++b) {
+    const LayerPlan* L = m.layers.data() + b;
+    const bool entry = L[0].fuse_entry && L[0].kernel_id == KID_ENTRY;
+    if (!entry && !(L[0].fuse_block && L[0].kernel_id == KID_BLOCK)) continue;
+    const bool first = b == i;
+    if (flops) *flops = first ? L[0].flops + L[1].flops + L[2].flops + L[3].flops : 0.0;
+    if (weight_bytes) *weight_bytes = first ? L[0].weight_bytes + L[1].weight_bytes + L[2].weight_bytes + L[3].weight_bytes : 0.0;
+    // what lies between the layers stays on the chip: the input, the other half of a block, and the outputs
+    if (bytes) *bytes = !first ? 0.0 : entry ? L[0].input_bytes + L[2].bytes - L[2].input_bytes + L[3].bytes - L[3].input_bytes : L[0].input_bytes + L[3].bytes - 0.5 * L[3].input_bytes;
+    return true;
+  }
+  return false;
 }
 
 octo_status octo_get_layer_info(octo_pipeline* p, int32_t model, float* ms, int32_t* kernel_id, double* flops, double* bytes,
@@ -1512,7 +1552,7 @@ octo_status octo_get_layer_info(octo_pipeline* p, int32_t model, float* ms, int3
     if (ms) ms[i] = (model < (int)p->last_layer_ms.size() && i < (int)p->last_layer_ms[model].size()) ? p->last_layer_ms[model][i] : 0.f;
     if (kernel_id) kernel_id[i] = m.layers[i].kernel_id;
     // layers in one launch: the work is reported with the first, the others did nothing
-    if (entry_work(m, i, flops ? flops + i : nullptr, bytes ? bytes + i : nullptr, weight_bytes ? weight_bytes + i : nullptr)) continue;
+    if (fused_work(m, i, flops ? flops + i : nullptr, bytes ? bytes + i : nullptr, weight_bytes ? weight_bytes + i : nullptr)) continue;
     const bool first = m.layers[i].fuse_twin && i + 1 < (int)m.layers.size(), second = i > 0 && m.layers[i - 1].fuse_twin;
     if (flops) flops[i] = second ? 0.0 : m.layers[i].flops + (first ? m.layers[i + 1].flops : 0.0);
     if (bytes) bytes[i] = second ? 0.0 : m.layers[i].bytes + (first ? m.layers[i + 1].bytes - m.layers[i].input_bytes : 0.0);
@@ -1541,7 +1581,7 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
     HIPCHK(p, hipEventElapsedTime(&t, e0, e1));
     ms[i] = t / iters;
     double f = 0, b = 0, w = 0;
-    if (entry_work(m, i, &f, &b, &w)) {
+    if (fused_work(m, i, &f, &b, &w)) {
       if (flops) flops[i] = f * n;
       if (bytes) bytes[i] = b * n + w;
       continue;
