@@ -31,21 +31,6 @@
 
 namespace octo {
 
-// What the kernel reads.  Pointers are to the first channel of the first pixel (y2: less the split's channels), pitches in bytes.
-struct SmallArgs {
-  const char* x; const char* w; const float* bias; char* y;
-  const int* n_dyn;
-  const char* res; char* y2;
-  int n, HoWo, tiles_c, per_row;         // per_row: bytes of a weight row
-  int grid, c_outer;
-  FastDiv div_tc, div_tp, div_howo, div_wo;       // div_tp: by the pixel tiles of n items
-  int x_pitch, y_pitch, y2_pitch, res_pitch;
-  int Cout, split, nk, taps_nk;          // K steps, and those of a tap
-  int H, W, Wo, kw, kh, stride, pad, Cin, K;
-  unsigned magic_cin, magic_kw;
-  int act, res_mode, w_len, w_rows;
-};
-
 // One K step (128 bytes per row) of a 16 x 16 block: lane (r16, q4) supplies vectors q4 and 4 + q4 of its row.  In fp32 the values of a step
 // go to C chains of sums that are added at the end: an instruction need not wait for the one before, and a chain is as short as a
 // wavefront's part of the reduction in the split-K kernel.
@@ -65,8 +50,8 @@ __device__ __forceinline__ void small_step(const u32x4 (&a)[2], const u32x4 (&b)
 
 // BC x BP: tile; WC, WP: wavefronts along the channels and the pixels; MINB: workgroups per compute unit; MODE: how addresses are made
 // (SMALL_POINTWISE and what follows it).
-template <typename T, int BC, int BP, int WC, int WP, int MINB, int MODE>
-__global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_kernel(const SmallArgs a) {
+template <typename T, int BC, int BP, int WC, int WP, int MODE>
+__device__ __forceinline__ void conv_small_tiles(const SmallArgs& a, const int block) {
   constexpr bool PART = MODE == SMALL_PART || MODE == SMALL_STRIDED_PART, PW = MODE == SMALL_POINTWISE || MODE == SMALL_PART;
   constexpr int ES = (int)sizeof(T), VN = 16 / ES, BK = 8 * VN;
   constexpr int NT = 64 * WC * WP, RP = NT / 8, NS = 3;       // lanes, rows that they load per pass, stages of the ring
@@ -103,7 +88,7 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
   const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)a.w, 0, a.w_len, BUF_FLAGS);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)a.bias, 0, a.w_rows * 4, BUF_FLAGS);      // padded to whole tiles like the weights
 
-  for (int t = blockIdx.x; t < per_die * 8; t += a.grid) {
+  for (int t = block; t < per_die * 8; t += a.grid) {
     const int tile = (t & 7) * per_die + (t >> 3);       // contiguous chunk of the tile list per die, see conv_mfma_kernel
     if (tile >= n_tiles) continue;
     int tc, tp;
@@ -301,8 +286,24 @@ __global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_k
   }
 }
 
+template <typename T, int BC, int BP, int WC, int WP, int MINB, int MODE>
+__global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_kernel(const SmallArgs a) {
+  conv_small_tiles<T, BC, BP, WC, WP, MODE>(a, blockIdx.x);
+}
+// Up to three layers that do not depend on one another in one launch: the workgroups of one follow those of the one before (SmallGroup, conv_small_choice.h).  A launch of few
+// tiles leaves compute units idle and costs 3.5 us whatever it does.  Cascades with separate launches and with a shortcut and the layer beside it, and the heads, as one, us: sweep of 1
+// frame 484 -> 475, of 4 605 -> 592, traffic of 8 1050 -> 1024, surveillance of 4 953 -> 944, sweep of 64 3825 -> 3809.
+struct SmallGroupArgs { SmallArgs layer[SmallGroup::MAX]; int second, third; };      // their first workgroups, multiples of 8
+template <typename T, int BC, int BP, int WC, int WP, int MINB, int MODE>
+__global__ __launch_bounds__(64 * WC * WP, MINB * WC * WP / 4) void conv_small_group_kernel(const SmallGroupArgs g) {
+  const int b = blockIdx.x, which = b < g.second ? 0 : b < g.third ? 1 : 2, first = which == 0 ? 0 : which == 1 ? g.second : g.third;
+  // straight from the arguments' memory: a copy that is indexed would live in scratch
+  const SmallArgs a = *(const SmallArgs*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + which * sizeof(SmallArgs));
+  conv_small_tiles<T, BC, BP, WC, WP, MODE>(a, b - first);
+}
+
 template <typename T, int BC, int BP, int WC, int WP, int MINB>
-static hipError_t launch_small_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
+static hipError_t launch_small_cfg(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
   constexpr int ES = (int)sizeof(T), BK = 128 / ES, NT = 64 * WC * WP;
   const long long M = (long long)a.n * a.Ho * a.Wo, tiles_c = (a.Cout + BC - 1) / BC, tiles_p = (M + BP - 1) / BP, tiles = tiles_p * tiles_c;
   if (tiles <= 0) return hipSuccess;
@@ -327,6 +328,11 @@ static hipError_t launch_small_cfg(const ConvArgs& a, int num_cu, hipStream_t s,
   const bool window = a.kh > 1 || a.kw > 1 || a.pad_h, part = ES == 4 && a.Cin % BK && !window;
   const int mode = part ? (a.stride_h > 1 ? SMALL_STRIDED_PART : SMALL_PART) : a.Cin % BK ? SMALL_ANY : (window || a.stride_h > 1 ? SMALL_TAPS : SMALL_POINTWISE);
   if (kernel_id) *kernel_id = small_kernel_id(BC, BP, WC, mode);
+  if (a.group && a.group->count < SmallGroup::MAX) {       // launched with the others of its group
+    SmallGroup& g = *a.group;
+    g.tile[g.count] = which; g.mode[g.count] = mode; g.layer[g.count++] = o;
+    return hipSuccess;
+  }
   auto go = [&](auto mode_c) {
     constexpr int MODE = decltype(mode_c)::value;
     if (tm.start && tm.stop) hipExtLaunchKernelGGL((conv_small_kernel<T, BC, BP, WC, WP, MINB, MODE>), dim3((unsigned)grid), dim3(NT), 0, s, tm.start, tm.stop, 0, o);
@@ -343,14 +349,48 @@ static hipError_t launch_small_cfg(const ConvArgs& a, int num_cu, hipStream_t s,
 // One entry point per storage type; `which` counts the rows of SMALL_COST (SMALL_COST_F32).
 template <typename T>
 static hipError_t launch_small(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
+  if (a.group && a.group->count > 0) which = a.group->tile[0];
   switch (which) {
-    case 0: return launch_small_cfg<T, 32, 32, 2, 2, 4>(a, num_cu, s, kernel_id, tm);
-    case 1: return launch_small_cfg<T, 32, 64, 1, 4, 4>(a, num_cu, s, kernel_id, tm);
-    case 2: return launch_small_cfg<T, 64, 32, 2, 2, 4>(a, num_cu, s, kernel_id, tm);
-    case 3: return launch_small_cfg<T, 64, 64, 2, 2, 3>(a, num_cu, s, kernel_id, tm);
-    case 4: if constexpr (sizeof(T) == 2) return launch_small_cfg<T, 128, 64, 4, 2, 2>(a, num_cu, s, kernel_id, tm);
+    case 0: return launch_small_cfg<T, 32, 32, 2, 2, 4>(which, a, num_cu, s, kernel_id, tm);
+    case 1: return launch_small_cfg<T, 32, 64, 1, 4, 4>(which, a, num_cu, s, kernel_id, tm);
+    case 2: return launch_small_cfg<T, 64, 32, 2, 2, 4>(which, a, num_cu, s, kernel_id, tm);
+    case 3: return launch_small_cfg<T, 64, 64, 2, 2, 3>(which, a, num_cu, s, kernel_id, tm);
+    case 4: if constexpr (sizeof(T) == 2) return launch_small_cfg<T, 128, 64, 4, 2, 2>(which, a, num_cu, s, kernel_id, tm);
   }
   return hipErrorNotSupported;
+}
+
+// Launches what a group has collected.
+template <typename T, int BC, int BP, int WC, int WP, int MINB>
+static hipError_t launch_small_group_cfg(const SmallGroup& g, hipStream_t s) {
+  auto go = [&](auto mode_c) {
+    constexpr int MODE = decltype(mode_c)::value, NT = 64 * WC * WP;
+    if (g.count == 1) {
+      hipLaunchKernelGGL((conv_small_kernel<T, BC, BP, WC, WP, MINB, MODE>), dim3((unsigned)g.layer[0].grid), dim3(NT), 0, s, g.layer[0]);
+      return hipGetLastError();
+    }
+    SmallGroupArgs a{};
+    for (int i = 0; i < g.count; ++i) a.layer[i] = g.layer[i];
+    a.second = g.layer[0].grid;
+    a.third = a.second + g.layer[1].grid;
+    const int grid = a.third + (g.count > 2 ? g.layer[2].grid : 0);
+    hipLaunchKernelGGL((conv_small_group_kernel<T, BC, BP, WC, WP, MINB, MODE>), dim3((unsigned)grid), dim3(NT), 0, s, a);
+    return hipGetLastError();
+  };
+  return g.mode[0] == SMALL_TAPS ? go(std::integral_constant<int, SMALL_TAPS>{}) : go(std::integral_constant<int, SMALL_POINTWISE>{});
+}
+template <typename T>
+static hipError_t launch_small_group_t(const SmallGroup& g, hipStream_t s) {
+  for (int i = 1; i < g.count; ++i) if (g.mode[i] != g.mode[0] || g.tile[i] != g.tile[0]) return hipErrorInvalidValue;
+  if (g.count < 1 || (g.mode[0] != SMALL_TAPS && g.mode[0] != SMALL_POINTWISE)) return hipErrorInvalidValue;
+  switch (g.tile[0]) {
+    case 0: return launch_small_group_cfg<T, 32, 32, 2, 2, 4>(g, s);
+    case 1: return launch_small_group_cfg<T, 32, 64, 1, 4, 4>(g, s);
+    case 2: return launch_small_group_cfg<T, 64, 32, 2, 2, 4>(g, s);
+    case 3: return launch_small_group_cfg<T, 64, 64, 2, 2, 3>(g, s);
+    case 4: return launch_small_group_cfg<T, 128, 64, 4, 2, 2>(g, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace octo

@@ -6,6 +6,31 @@
 
 namespace octo {
 
+// What the kernel reads.  Pointers are to the first channel of the first pixel (y2: less the split's channels), pitches in bytes.
+struct SmallArgs {
+  const char* x; const char* w; const float* bias; char* y;
+  const int* n_dyn;
+  const char* res; char* y2;
+  int n, HoWo, tiles_c, per_row;         // per_row: bytes of a weight row
+  int grid, c_outer;
+  FastDiv div_tc, div_tp, div_howo, div_wo;       // div_tp: by the pixel tiles of n items
+  int x_pitch, y_pitch, y2_pitch, res_pitch;
+  int Cout, split, nk, taps_nk;          // K steps, and those of a tap
+  int H, W, Wo, kw, kh, stride, pad, Cin, K;
+  unsigned magic_cin, magic_kw;
+  int act, res_mode, w_len, w_rows;
+};
+
+// Layers that do not depend on one another and whose arguments are collected for one launch; the first one's tile is everyone's (all tiles sum in one order).
+struct SmallGroup {
+  static constexpr int MAX = 3;
+  int count = 0;
+  int tile[MAX], mode[MAX];
+  SmallArgs layer[MAX];
+};
+hipError_t launch_small_group_f16(const SmallGroup& g, hipStream_t s);
+hipError_t launch_small_group_bf16(const SmallGroup& g, hipStream_t s);
+
 // How addresses are made: 1x1, stride 1, no padding, whole K steps of channels; any other layer with whole K steps of channels per
 // tap; any layer (a lane works out the tap of its vector at every step); in fp32, 1x1 layers without padding whose channels end inside a
 // step, stride 1 or more.

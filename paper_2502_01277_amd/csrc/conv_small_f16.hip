@@ -2,4 +2,5 @@
 #include "conv_small.h"
 namespace octo {
 hipError_t launch_small_f16(int which, const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) { return launch_small<_Float16>(which, a, num_cu, s, kernel_id, tm); }
+hipError_t launch_small_group_f16(const SmallGroup& g, hipStream_t s) { return launch_small_group_t<_Float16>(g, s); }
 }  // namespace octo

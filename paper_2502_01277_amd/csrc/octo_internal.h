@@ -20,6 +20,7 @@ struct TensorView {
 };
 
 struct HeldPlan;
+struct SmallGroup;
 struct ConvArgs {
   const void* x;
   const void* w;        // packed weights [cout_pad][kp]
@@ -59,6 +60,7 @@ struct ConvArgs {
   // 8-bit floating point storage only: y = act(acc * scale[c] + bias[c] (+ res * res_scale)), stored as
   // E4M3(y * y_inv_scale) unless out_f32.  scale: device, one factor per output channel, padded like the bias.
   const float* scale;
+  SmallGroup* group;              // host only: conv_small_kernel's launch is collected here instead (conv_small_choice.h); null: launched
   const HeldPlan* held;    // host only: what a model keeps for a 3x3 layer that may run on conv3x3_held_kernel (conv3x3_held_choice.h), or null
   float res_scale, y_inv_scale;
 };

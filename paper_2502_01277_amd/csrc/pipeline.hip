@@ -18,6 +18,7 @@
 
 #include "octo_internal.h"
 #include "conv3x3_held_choice.h"
+#include "conv_small_choice.h"
 
 using namespace octo;
 
@@ -78,6 +79,8 @@ struct LayerPlan {
   // This first layer, the down-sampling layer behind it and the two 1x1 layers behind that are one launch where the kernel takes them (entry_done: it did; the next three
   // layers then do nothing).
   bool fuse_entry = false, entry_done = false;
+  // So many convolutions from this one on do not depend on one another and may run at a time: where conv_small_kernel takes several of them they are one launch.
+  int group = 1;
   // This 1x1 layer and the next three - 3x3, concatenation with another tensor, 1x1 - are one launch where the kernel takes them (block_done: it did; the next three layers
   // then do nothing).
   bool fuse_block = false, block_done = false;
@@ -459,6 +462,17 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     const octo_layer &G = m.layers[i].L, &F = m.layers[i + 1].L;
     m.layers[i].fuse_label = G.op == OCTO_GAP && F.op == OCTO_FC && F.in[0] == i + 1 && F.n_in == 1 && F.act == OCTO_ACT_NONE;
   }
+  // convolutions in a row that do not depend on one another and have the same form of addresses: a shortcut and the layer beside it, a detector's heads
+  for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].group = 1;
+  auto groups = [&](int i, int j) {           // may layer j run beside those from i on?
+    const LayerPlan& q = m.layers[j];
+    if (q.L.op != OCTO_CONV || q.pair_view || q.cin % 64 || q.fuse_pool || q.fuse_up || q.fuse_twin || q.fuse_block || q.fuse_entry || (j > 0 && m.layers[j - 1].fuse_twin)) return false;
+    for (int b = std::max(0, j - 3); b < j; ++b) if (m.layers[b].fuse_block || (b == 0 && m.layers[0].fuse_entry)) return false;
+    for (int k = 0; k < q.L.n_in; ++k) if (q.L.in[k] > i) return false;
+    return (q.L.kh > 1 || q.L.kw > 1 || q.L.stride > 1 || q.L.pad > 0) == (m.layers[i].L.kh > 1 || m.layers[i].L.kw > 1 || m.layers[i].L.stride > 1 || m.layers[i].L.pad > 0);
+  };
+  for (int i = 0; allow_fusion && dtype_size(m.d.dtype) == 2 && i + 1 < (int)m.layers.size(); i += m.layers[i].group)
+    while (m.layers[i].group < SmallGroup::MAX && i + m.layers[i].group < (int)m.layers.size() && groups(i, i) && groups(i, i + m.layers[i].group)) ++m.layers[i].group;
   // lifetimes of root buffers in layer steps: tensor t is written at step t-1 (input: -1)
   std::vector<int> birth(nt, 1 << 30), death(nt, -2);
   for (int t = 0; t < nt; ++t) {
@@ -482,6 +496,13 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     for (int k = 0; k < m.layers[i].L.n_in; ++k) {
       const int r = m.tensors[m.layers[i].L.in[k]].root;
       death[r] = std::max(death[r], i);
+    }
+  // layers of a group run at a time: the inputs of all live until the last, the outputs of all from the first
+  for (int i = 0; i < (int)m.layers.size(); i += m.layers[i].group)
+    for (int j = i; m.layers[i].group > 1 && j < i + m.layers[i].group; ++j) {
+      for (int k = 0; k < m.layers[j].L.n_in; ++k) { const int r = m.tensors[m.layers[j].L.in[k]].root; death[r] = std::max(death[r], i + m.layers[i].group - 1); }
+      const int r = m.tensors[j + 1].root;
+      birth[r] = std::min(birth[r], i);
     }
   const int forever = (int)m.layers.size() + 1;
   for (int t = 0; t < nt; ++t) if (is_output[t] || keep_all) death[m.tensors[t].root] = forever;
@@ -605,7 +626,7 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
 }
 
 // ---- one layer ----------------------------------------------------------------
-hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_dyn, hipStream_t s, ConvTiming tm = ConvTiming()) {
+hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_dyn, hipStream_t s, ConvTiming tm = ConvTiming(), SmallGroup* group = nullptr) {
   LayerPlan& lp = m.layers[i];
   const octo_layer& L = lp.L;
   const TensorView x = view_of(m, L.in[0]);
@@ -624,7 +645,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (L.n_in == 2) { const TensorView r = view_of(m, L.in[1]); a.res = r.ptr; a.res_ld = r.ld; a.res_coff = r.coff; }
       if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
-      a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr;
+      a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr; a.group = group;
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (i > 0 && i <= 3 && m.layers[0].fuse_entry && m.layers[0].entry_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
       lp.entry_done = false;
@@ -745,6 +766,18 @@ hipError_t run_layers(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, h
   const int L = (int)m.layers.size();
   if (evs && (e = hipEventRecord((*evs)[0], s)) != hipSuccess) return e;
   for (int i = 0; i < L; ++i) {
+    if (const int count = m.layers[i].group; count > 1 && !evs) {       // (with timing every layer has a launch of its own)
+      // the one with the most work first: the group has its tile
+      SmallGroup g;
+      int most = i;
+      for (int j = i; j < i + count; ++j) if (m.layers[j].flops > m.layers[most].flops) most = j;
+      if ((e = run_layer(p, m, most, n, n_dyn, s, ConvTiming(), &g)) != hipSuccess) return e;
+      for (int j = i; j < i + count; ++j)
+        if (j != most && (e = run_layer(p, m, j, n, n_dyn, s, ConvTiming(), &g)) != hipSuccess) return e;
+      if (g.count > 0 && (e = m.d.dtype == OCTO_F16 ? launch_small_group_f16(g, s) : launch_small_group_bf16(g, s)) != hipSuccess) return e;
+      i += count - 1;
+      continue;
+    }
     ConvTiming tm;
     if (evs) { tm.start = (*evs)[L + 1 + 2 * i]; tm.stop = (*evs)[L + 2 + 2 * i]; }
     if ((e = run_layer(p, m, i, n, n_dyn, s, tm)) != hipSuccess) return e;
