@@ -74,6 +74,8 @@ def conv_name(kid: int, dtype: str) -> str:
     ctype = {"f16": "_Float16", "bf16": "__bf16", "f32": "float", "f8": "octo::f8"}[dtype]
     if kid == 2100000000:                                # the first layers of a detector in one launch
         return "octo::entry_kernel<%s>" % ctype
+    if kid // 10**7 == 212:                              # the entry of a cross-stage block in one launch: pixel tile / 16, channels, input channels
+        return "octo::lead_kernel<%s, %d, %d, %d>" % (ctype, kid // 1000 % 1000, kid % 1000 // 32, kid // 10**6 % 10)
     if kid == 2110000000:                                # a cross-stage block of 32 channels in one launch, with a shortcut as the detectors have it
         return "octo::block_kernel<%s, true>" % ctype
     if d >= 1000000000:                                  # 3x3 layers of few tiles, patch of all channels in LDS: digits S K BBB PPP

@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libocto.so")
-SOURCES = ["conv_bf16.hip", "conv_f16.hip", "conv_flow_bf16.hip", "conv_flow_f16.hip", "conv_flow_f8.hip", "conv_small_bf16.hip", "conv_small_f16.hip", "conv_small_f32.hip", "conv_f32.hip", "conv_f8.hip", "conv.hip", "stem.hip", "entry.hip", "block.hip", "conv1x1.hip", "glue.hip", "preproc.hip", "postproc.hip", "pipeline.hip", "ops_api.hip", "probes.hip", "executor.hip", "sched.cpp", "runtime.cpp", "placement.cpp"]
+SOURCES = ["conv_bf16.hip", "conv_f16.hip", "conv_flow_bf16.hip", "conv_flow_f16.hip", "conv_flow_f8.hip", "conv_small_bf16.hip", "conv_small_f16.hip", "conv_small_f32.hip", "conv_f32.hip", "conv_f8.hip", "conv.hip", "stem.hip", "entry.hip", "block.hip", "lead.hip", "conv1x1.hip", "glue.hip", "preproc.hip", "postproc.hip", "pipeline.hip", "ops_api.hip", "probes.hip", "executor.hip", "sched.cpp", "runtime.cpp", "placement.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-result", "-Wno-unused-value"]
 

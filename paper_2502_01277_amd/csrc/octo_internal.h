@@ -95,6 +95,17 @@ struct BlockArgs {
   int n, H, W, shortcut;
   const void* w[3]; const float* bias[3]; int kp[3];
 };
+// The two entry 1x1 layers of a cross-stage block (a, b; weights stacked) and a 1x1 layer on the first one's output (h), SiLU; a.a may be null: not written.
+struct LeadArgs {
+  const void* x; int x_ld, x_coff;
+  void* a; int a_ld, a_coff;
+  void* b; int b_ld, b_coff;
+  void* h; int h_ld, h_coff;
+  long long pixels; int Cin, C;
+  const void* w[2]; const float* bias[2]; int kp[2];
+};
+bool lead_fits(int c, int cin);
+hipError_t launch_lead(int dtype, const LeadArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 hipError_t launch_block(int dtype, const BlockArgs& a, int num_cu, hipStream_t s, int* kernel_id, ConvTiming tm);
 enum { KID_NONE = 0, KID_MAXPOOL = 1, KID_UPSAMPLE = 2, KID_COPY = 3, KID_ADD = 4, KID_GAP = 5 };
 size_t conv_packed_weight_elems(int cout, int kh, int kw, int cin, int dtype, int* kp_out, int* cout_pad_out);

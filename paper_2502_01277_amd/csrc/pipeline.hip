@@ -102,6 +102,9 @@ struct LayerPlan {
   // its own tensor - so the input is read once.  The next layer then does nothing (kernel id KID_NONE).  Cleared for
   // good the first time the kernel refuses the fused form.
   bool fuse_twin = false;
+  // And the layer behind those two is a 1x1 convolution of this one's output: one launch computes all three where the kernel takes them (lead_done: it did; the layer two further
+  // on then does nothing).  lead_keep: this layer's output has other readers too.
+  bool fuse_lead = false, lead_done = false, lead_keep = false;
   void* d_weight_twin = nullptr;
   float* d_bias_twin = nullptr;
   int twin_cout_pad = 0, twin_kp = 0;
@@ -456,6 +459,20 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     m.layers[i].fuse_block = readers[0] == 1 && readers[1] == 1 && readers[2] == 1 && !is_output[i + 1] && !is_output[i + 2] && !is_output[i + 3] &&
                              !m.layers[i + 3].fuse_twin && !m.layers[i + 3].fuse_up;
   }
+  // the two entry convolutions of a cross-stage block and the 1x1 layer behind the first
+  for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_lead = false;
+  for (int i = 0; i + 2 < (int)m.layers.size(); ++i) {
+    LayerPlan& lp = m.layers[i];
+    const octo_layer &A = lp.L, &B = m.layers[i + 1].L, &C = m.layers[i + 2].L;
+    if (!lp.fuse_twin || A.act != OCTO_ACT_SILU || A.cout != B.cout || !lead_fits(A.cout, m.tensors[A.in[0]].c)) continue;
+    if (C.op != OCTO_CONV || C.n_in != 1 || C.in[0] != i + 1 || C.kh != 1 || C.kw != 1 || C.stride != 1 || C.pad != 0 || C.act != OCTO_ACT_SILU || C.cout != A.cout) continue;
+    if (m.layers[i + 2].fuse_twin || m.layers[i + 2].fuse_up || m.layers[i + 2].fuse_block || m.tensors[i + 3].f32) continue;
+    int readers = 0;
+    for (const LayerPlan& q : m.layers)
+      for (int k = 0; k < q.L.n_in; ++k) readers += q.L.in[k] == i + 1;
+    lp.fuse_lead = true;
+    lp.lead_keep = keep_all || readers > 1 || is_output[i + 1];
+  }
   // the end of a classifier (also with every layer on its own: the launch writes every tensor, and a logit's order of summation stays the same)
   for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].fuse_label = false;
   if (const int i = (int)m.layers.size() - 2; m.d.kind == OCTO_CLASSIFIER && i >= 0 && m.d.outputs[0] == i + 2) {
@@ -466,7 +483,8 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
   for (int i = 0; i < (int)m.layers.size(); ++i) m.layers[i].group = 1;
   auto groups = [&](int i, int j) {           // may layer j run beside those from i on?
     const LayerPlan& q = m.layers[j];
-    if (q.L.op != OCTO_CONV || q.pair_view || q.cin % 64 || q.fuse_pool || q.fuse_up || q.fuse_twin || q.fuse_block || q.fuse_entry || (j > 0 && m.layers[j - 1].fuse_twin)) return false;
+    if (q.L.op != OCTO_CONV || q.pair_view || q.cin % 64 || q.fuse_pool || q.fuse_up || q.fuse_twin || q.fuse_block || q.fuse_entry || (j > 0 && m.layers[j - 1].fuse_twin) ||
+        (j > 1 && m.layers[j - 2].fuse_lead)) return false;
     for (int b = std::max(0, j - 3); b < j; ++b) if (m.layers[b].fuse_block || (b == 0 && m.layers[0].fuse_entry)) return false;
     for (int k = 0; k < q.L.n_in; ++k) if (q.L.in[k] > i) return false;
     return (q.L.kh > 1 || q.L.kw > 1 || q.L.stride > 1 || q.L.pad > 0) == (m.layers[i].L.kh > 1 || m.layers[i].L.kw > 1 || m.layers[i].L.stride > 1 || m.layers[i].L.pad > 0);
@@ -487,6 +505,8 @@ void plan_activations(ModelPlan& m, bool keep_all, bool allow_fusion) {
     }
   for (int i = 0; i < (int)m.layers.size(); ++i)
     if (m.layers[i].fuse_block) { const int r = m.tensors[i + 4].root; birth[r] = std::min(birth[r], i); }
+  for (int i = 0; i < (int)m.layers.size(); ++i)
+    if (m.layers[i].fuse_lead) { const int r = m.tensors[i + 3].root; birth[r] = std::min(birth[r], i); }
   if (m.layers[0].fuse_entry)
     for (int t = 3; t <= 4; ++t) birth[m.tensors[t].root] = std::min(birth[m.tensors[t].root], 0);
   for (int i = 0; i < (int)m.layers.size(); ++i)
@@ -648,6 +668,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr; a.group = group;
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (i > 0 && i <= 3 && m.layers[0].fuse_entry && m.layers[0].entry_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
+      if (i > 1 && m.layers[i - 2].fuse_lead && m.layers[i - 2].lead_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
       lp.entry_done = false;
       if (lp.fuse_entry && !n_dyn) {
         const LayerPlan &B = m.layers[1], &C = m.layers[2];
@@ -666,6 +687,16 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
                           {lp.d_weight, B.d_weight, D.d_weight}, {lp.d_bias, B.d_bias, D.d_bias}, {lp.Kp, B.Kp, D.Kp}};
         const hipError_t e = launch_block(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
         lp.block_done = e == hipSuccess;
+        if (e != hipErrorNotSupported) return e;
+      }
+      lp.lead_done = false;
+      if (lp.fuse_lead && !n_dyn) {
+        const LayerPlan& C = m.layers[i + 2];
+        const TensorView b = view_of(m, i + 2), h = view_of(m, i + 3);
+        const LeadArgs f{x.ptr, x.ld, x.coff, lp.lead_keep ? y.ptr : nullptr, y.ld, y.coff, b.ptr, b.ld, b.coff, h.ptr, h.ld, h.coff, (long long)n * x.h * x.w, x.c, L.cout,
+                         {lp.d_weight_twin, C.d_weight}, {lp.d_bias_twin, C.d_bias}, {lp.twin_kp, C.Kp}};
+        const hipError_t e = launch_lead(m.d.dtype, f, p->num_cu, s, &lp.kernel_id, tm);
+        lp.lead_done = e == hipSuccess;
         if (e != hipErrorNotSupported) return e;
       }
       if (lp.fuse_twin) {
@@ -1559,7 +1590,7 @@ octo_status octo_set_layer_timing(octo_pipeline* p, int32_t enable) {
   return OCTO_OK;
 }
 
-// Per item work, and bytes of weights, of four layers that ran as one launch: all of it with the first.  False for a layer that is none of those.
+// Per item work, and bytes of weights, of three or four layers that ran as one launch: all of it with the first.  False for a layer that is none of those.
 static bool fused_work(const ModelPlan& m, int i, double* flops, double* bytes, double* weight_bytes) {
   for (int b = std::max(0, i - 3); b <= i; ++b) {
     const LayerPlan* L = m.layers.data() + b;
@@ -1570,6 +1601,15 @@ static bool fused_work(const ModelPlan& m, int i, double* flops, double* bytes, 
     if (weight_bytes) *weight_bytes = first ? L[0].weight_bytes + L[1].weight_bytes + L[2].weight_bytes + L[3].weight_bytes : 0.0;
     // what lies between the layers stays on the chip: the input, the other half of a block, and the outputs
     if (bytes) *bytes = !first ? 0.0 : entry ? L[0].input_bytes + L[2].bytes - L[2].input_bytes + L[3].bytes - L[3].input_bytes : L[0].input_bytes + L[3].bytes - 0.5 * L[3].input_bytes;
+    return true;
+  }
+  for (int b = std::max(0, i - 2); b <= i; ++b) {
+    const LayerPlan* L = m.layers.data() + b;
+    if (!L[0].fuse_lead || !is_lead(L[0].kernel_id)) continue;
+    const bool first = b == i;
+    if (flops) *flops = first ? L[0].flops + L[1].flops + L[2].flops : 0.0;
+    if (weight_bytes) *weight_bytes = first ? L[0].weight_bytes + L[1].weight_bytes + L[2].weight_bytes : 0.0;
+    if (bytes) *bytes = !first ? 0.0 : (L[0].lead_keep ? L[0].bytes : L[0].input_bytes) + L[1].bytes - L[1].input_bytes + L[2].bytes - L[2].input_bytes;
     return true;
   }
   return false;
