@@ -153,6 +153,23 @@ inline FastDiv make_fastdiv(unsigned d) {
 __device__ __forceinline__ unsigned fast_div(unsigned n, const FastDiv& f) { return f.is_one ? n : __umulhi(n, f.mul) >> f.shift; }
 #endif
 
+// First launch of a batch: the frame table (passed by value, at most MAX frames per launch) and cleared counters.
+struct BeginArgs {
+  static constexpr int MAX = 64, REGIONS = 4;
+  const uint8_t* ptr[MAX]; size_t pitch[MAX];
+  int n;                                   // frames of this launch
+  const uint8_t** d_ptr; size_t* d_pitch;
+  int* clear[REGIONS]; int clear_count[REGIONS];      // ranges of ints to zero (nullptr / 0: unused)
+};
+#ifdef __HIPCC__
+__device__ __forceinline__ void begin_batch(const BeginArgs& a, int i0, int step) {      // thread i0 of step
+  if (i0 < a.n) { a.d_ptr[i0] = a.ptr[i0]; a.d_pitch[i0] = a.pitch[i0]; }
+#pragma unroll
+  for (int r = 0; r < BeginArgs::REGIONS; ++r)
+    for (int i = i0; i < a.clear_count[r]; i += step) a.clear[r][i] = 0;
+}
+#endif
+
 struct ResizeArgs {
   const uint8_t* const* frames;   // device table of frame base pointers
   const size_t* pitches;          // device table of row pitches in bytes
@@ -168,7 +185,7 @@ struct ResizeArgs {
   FastDiv div_wq, div_h;          // set by the launchers: lanes per output row, rows per item
 };
 void letterbox_geometry(int src_h, int src_w, int dst_h, int dst_w, int* nw, int* nh, int* left, int* top);
-hipError_t launch_letterbox(int dtype, const ResizeArgs& a, int num_cu, hipStream_t s);
+hipError_t launch_letterbox(int dtype, const ResizeArgs& a, int num_cu, hipStream_t s, const BeginArgs* begin = nullptr);      // begin: the launch does that too
 hipError_t launch_crop_resize(int dtype, const ResizeArgs& a, hipStream_t s);
 
 struct DecodeArgs {
@@ -222,14 +239,6 @@ constexpr int SELECT_MAX = 1024;           // boxes per item, at most
 bool select_fits(const TopkArgs& a);
 hipError_t launch_select(const TopkArgs& a, const NmsArgs& m, const CompactArgs* ca, hipStream_t s);
 
-// First launch of a batch: the frame table (passed by value, at most MAX frames per launch) and cleared counters.
-struct BeginArgs {
-  static constexpr int MAX = 64, REGIONS = 4;
-  const uint8_t* ptr[MAX]; size_t pitch[MAX];
-  int n;                                   // frames of this launch
-  const uint8_t** d_ptr; size_t* d_pitch;
-  int* clear[REGIONS]; int clear_count[REGIONS];      // ranges of ints to zero (nullptr / 0: unused)
-};
 hipError_t launch_begin(const BeginArgs& a, hipStream_t s);
 
 // Last launch of a batch: the result block's header and the boxes in use go straight to pinned host memory.

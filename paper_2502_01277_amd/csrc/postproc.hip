@@ -710,11 +710,7 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t s, bool counted) {
 }
 
 __global__ __launch_bounds__(256) void begin_kernel(const BeginArgs a) {
-  const int i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
-  if (i0 < a.n) { a.d_ptr[i0] = a.ptr[i0]; a.d_pitch[i0] = a.pitch[i0]; }
-#pragma unroll
-  for (int r = 0; r < BeginArgs::REGIONS; ++r)
-    for (int i = i0; i < a.clear_count[r]; i += step) a.clear[r][i] = 0;
+  begin_batch(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 hipError_t launch_begin(const BeginArgs& a, hipStream_t s) {

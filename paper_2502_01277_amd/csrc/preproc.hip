@@ -87,8 +87,11 @@ struct LetterboxGeom { int nw, nh, left, top; };
 // 15.3, 32 50 : 37, 32 of 2160p to 1280 x 1280 x 4 with the rows in groups 204 : 129, 3.7 TB/s).  R rows per lane: a lane's time is two dependent trips to memory, the frame's
 // address and then its pixels, and the rows' words are loaded beside each other.  letterbox_p says when.  Frames whose addresses turn
 // out not to be aligned take their rows one after the other.
-template <typename T, int PX, bool C4, bool EXACT, int R>
-__global__ void letterbox_kernel(const ResizeArgs a, const LetterboxGeom g) {
+// BEGIN: the launch is also the batch's first, begin_kernel's work included, and takes the frames from its arguments instead of the table that it writes for the later ones.
+struct NoBegin {};
+template <typename T, int PX, bool C4, bool EXACT, int R, bool BEGIN>
+__global__ void letterbox_kernel(const ResizeArgs a, const LetterboxGeom g, const std::conditional_t<BEGIN, BeginArgs, NoBegin> b) {
+  if constexpr (BEGIN) begin_batch(b, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
   const int wq = a.dst_w / PX;
   int n_items = a.n;
   if (a.n_dyn) { int d = *a.n_dyn; n_items = d < a.n ? d : a.n; }
@@ -101,8 +104,10 @@ __global__ void letterbox_kernel(const ResizeArgs a, const LetterboxGeom g) {
     const int xq = (int)(i - t * (unsigned)wq);
     const int img = (int)fast_div(t, a.div_h);
     const int y0 = (int)(t - (unsigned)img * groups) * R;
-    const Src base = frame_of(a, img);
-    const size_t pitch = a.pitches[img];
+    Src base;
+    size_t pitch;
+    if constexpr (BEGIN) { base = (Src)b.ptr[img]; pitch = b.pitch[img]; }
+    else { base = frame_of(a, img); pitch = a.pitches[img]; }
     T* out = dst + (((size_t)img * a.dst_h + y0) * a.dst_w + (size_t)xq * PX) * (C4 ? 4 : 3);
     const size_t out_pitch = (size_t)a.dst_w * (C4 ? 4 : 3);
     if constexpr (EXACT && PX == 4) {
@@ -385,7 +390,12 @@ static bool resize_prepare(ResizeArgs& a) {
 }
 
 constexpr int LETTERBOX_ROWS = 4;
-template <typename T, int PX, bool C4, bool EXACT> static hipError_t letterbox_p(const ResizeArgs& a, const LetterboxGeom& g, int num_cu, hipStream_t s) {
+template <typename T, int PX, bool C4, bool EXACT> static hipError_t letterbox_p(const ResizeArgs& a, const LetterboxGeom& g, int num_cu, const BeginArgs* begin, hipStream_t s) {
+  auto go = [&](auto with, auto without, long long lanes, const ResizeArgs& b) {
+    if (begin) hipLaunchKernelGGL(with, dim3(resize_grid(lanes)), dim3(256), 0, s, b, g, *begin);
+    else hipLaunchKernelGGL(without, dim3(resize_grid(lanes)), dim3(256), 0, s, b, g, NoBegin{});
+    return hipGetLastError();
+  };
   if constexpr (EXACT && PX == 4) {
     // Rows in groups where they are loaded as words (ratio 3, the left border a multiple of four pixels) and the launch is three rounds of
     // 32 wavefronts per compute unit even so: with fewer, the groups' uneven end costs more than the loads beside each other save.  One
@@ -396,22 +406,20 @@ template <typename T, int PX, bool C4, bool EXACT> static hipError_t letterbox_p
     if (a.src_w / g.nw == 3 && g.left % 4 == 0 && lanes >= 3LL * 32 * 64 * num_cu) {
       ResizeArgs b = a;
       b.div_h = make_fastdiv((unsigned)((a.dst_h + LETTERBOX_ROWS - 1) / LETTERBOX_ROWS));
-      hipLaunchKernelGGL((letterbox_kernel<T, PX, C4, EXACT, LETTERBOX_ROWS>), dim3(resize_grid(lanes)), dim3(256), 0, s, b, g);
-      return hipGetLastError();
+      return go(letterbox_kernel<T, PX, C4, EXACT, LETTERBOX_ROWS, true>, letterbox_kernel<T, PX, C4, EXACT, LETTERBOX_ROWS, false>, lanes, b);
     }
   }
-  hipLaunchKernelGGL((letterbox_kernel<T, PX, C4, EXACT, 1>), dim3(resize_grid((long long)a.n * a.dst_h * (a.dst_w / PX))), dim3(256), 0, s, a, g);
-  return hipGetLastError();
+  return go(letterbox_kernel<T, PX, C4, EXACT, 1, true>, letterbox_kernel<T, PX, C4, EXACT, 1, false>, (long long)a.n * a.dst_h * (a.dst_w / PX), a);
 }
-template <typename T, bool EXACT> static hipError_t letterbox_e(const ResizeArgs& a, const LetterboxGeom& g, int num_cu, hipStream_t s) {
+template <typename T, bool EXACT> static hipError_t letterbox_e(const ResizeArgs& a, const LetterboxGeom& g, int num_cu, const BeginArgs* begin, hipStream_t s) {
   const bool px4 = a.dst_w % 4 == 0 && ((uintptr_t)a.dst & 15) == 0;
-  if (a.dst_c == 4) return px4 ? letterbox_p<T, 4, true, EXACT>(a, g, num_cu, s) : letterbox_p<T, 1, true, EXACT>(a, g, num_cu, s);
-  return px4 ? letterbox_p<T, 4, false, EXACT>(a, g, num_cu, s) : letterbox_p<T, 1, false, EXACT>(a, g, num_cu, s);
+  if (a.dst_c == 4) return px4 ? letterbox_p<T, 4, true, EXACT>(a, g, num_cu, begin, s) : letterbox_p<T, 1, true, EXACT>(a, g, num_cu, begin, s);
+  return px4 ? letterbox_p<T, 4, false, EXACT>(a, g, num_cu, begin, s) : letterbox_p<T, 1, false, EXACT>(a, g, num_cu, begin, s);
 }
-template <typename T> static hipError_t letterbox_t(const ResizeArgs& a, int num_cu, hipStream_t s) {
+template <typename T> static hipError_t letterbox_t(const ResizeArgs& a, int num_cu, const BeginArgs* begin, hipStream_t s) {
   const LetterboxGeom g = letterbox_geom(a.src_h, a.src_w, a.dst_h, a.dst_w);
   const bool exact = a.src_w % g.nw == 0 && a.src_h % g.nh == 0 && ((a.src_w / g.nw) & 1) && ((a.src_h / g.nh) & 1);
-  return exact ? letterbox_e<T, true>(a, g, num_cu, s) : letterbox_e<T, false>(a, g, num_cu, s);
+  return exact ? letterbox_e<T, true>(a, g, num_cu, begin, s) : letterbox_e<T, false>(a, g, num_cu, begin, s);
 }
 template <typename T> static hipError_t crop_t(const ResizeArgs& a, hipStream_t s) {
   // one 64-thread workgroup per output row, at most 32 per compute unit at a time; each die strides over the rows of
@@ -430,14 +438,15 @@ template <typename T> static hipError_t crop_t(const ResizeArgs& a, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_letterbox(int dtype, const ResizeArgs& a0, int num_cu, hipStream_t s) {
+hipError_t launch_letterbox(int dtype, const ResizeArgs& a0, int num_cu, hipStream_t s, const BeginArgs* begin) {
   if (a0.n <= 0) return hipSuccess;
+  if (begin && a0.n > begin->n) return hipErrorInvalidValue;          // every item's frame is in the arguments
   ResizeArgs a = a0;
   if ((a.dst_c != 3 && a.dst_c != 4) || a.src_w < 4 || !resize_prepare(a)) return hipErrorInvalidValue;
   switch (dtype) {
-    case OCTO_F32: return letterbox_t<float>(a, num_cu, s);
-    case OCTO_F16: return letterbox_t<_Float16>(a, num_cu, s);
-    case OCTO_BF16: return letterbox_t<__bf16>(a, num_cu, s);
+    case OCTO_F32: return letterbox_t<float>(a, num_cu, begin, s);
+    case OCTO_F16: return letterbox_t<_Float16>(a, num_cu, begin, s);
+    case OCTO_BF16: return letterbox_t<__bf16>(a, num_cu, begin, s);
   }
   return hipErrorInvalidValue;
 }
