@@ -495,7 +495,7 @@ __device__ __forceinline__ float to_src(float v, float off, float r, float hi) {
   return fminf(fmaxf(s, 0.0f), hi);
 }
 
-// A kept box in source pixels, no child labels yet; and whether a class is routed along edge e.
+// A kept box in source pixels, no child labels yet; its ROI; and whether a class is routed along edge e.
 __device__ __forceinline__ octo_box final_box(const CompactArgs& a, const octo_cand& c) {
   octo_box b;
   b.x1 = to_src(c.x1, a.left, a.rx, a.src_w); b.x2 = to_src(c.x2, a.left, a.rx, a.src_w);
@@ -503,6 +503,13 @@ __device__ __forceinline__ octo_box final_box(const CompactArgs& a, const octo_c
   b.score = c.score; b.cls = c.cls;
   for (int k = 0; k < OCTO_MAX_CHILD_LABELS; ++k) b.child_label[k] = -1;
   return b;
+}
+__device__ __forceinline__ octo_roi source_roi(const CompactArgs& a, const octo_cand& c, int item, int rank) {
+  octo_roi o;
+  o.frame = item; o.rank = rank; o.cls = c.cls; o.pad_ = 0;
+  o.x1 = to_src(c.x1, a.left, a.rx, a.src_w); o.x2 = to_src(c.x2, a.left, a.rx, a.src_w);
+  o.y1 = to_src(c.y1, a.top_pad, a.ry, a.src_h); o.y2 = to_src(c.y2, a.top_pad, a.ry, a.src_h);
+  return o;
 }
 __device__ __forceinline__ bool routed(const CompactArgs& a, int e, int cls) {
   return cls >= 0 && cls < 128 && ((a.class_mask[e][cls < 64 ? 0 : 1] >> (cls & 63)) & 1ull);
@@ -515,7 +522,7 @@ __device__ __forceinline__ bool routed(const CompactArgs& a, int e, int cls) {
 // same order, same boxes as nms_mask_kernel + nms_reduce_kernel.  Bound by latency.  Measured, us: 8 frames of about 20 candidates 6.6 + 4.8 + 5.3 +
 // 4.6 -> 8.1; 32 frames of 1000 candidates crowded around 40 spots 29 + 23 + 81 + 4.8 -> 117.
 static_assert(SELECT_MAX == TOPK_THREADS, "a thread per box");
-__global__ __launch_bounds__(TOPK_THREADS) void select_kernel(const TopkArgs a, const NmsArgs m, const CompactArgs ca, const int compact) {
+__global__ __launch_bounds__(TOPK_THREADS) void select_kernel(const TopkArgs a, const NmsArgs m, const CompactArgs ca, const int compact, const int single) {
   __shared__ unsigned long long key[TOPK_P];
   __shared__ unsigned val[TOPK_P];
   __shared__ float4 kept[2][64];             // corners of the boxes kept in a block; area and class
@@ -590,7 +597,14 @@ __global__ __launch_bounds__(TOPK_THREADS) void select_kernel(const TopkArgs a, 
         __syncthreads();
         int before = 0, all = 0;
         for (int w = 0; w < SELECT_MAX / 64; ++w) { if (w < wave) before += s_wave[w]; all += s_wave[w]; }
-        if (mine) ca.roi_of[e][(size_t)item * ca.max_det + t] = hit ? before + __popcll(bal & ((1ull << lane) - 1ull)) : -1;      // rank inside the item for now
+        const int rank = before + __popcll(bal & ((1ull << lane) - 1ull));
+        if (single) {                        // the only item: its ranks are the ROIs' ids
+          const bool fits = hit && rank < ca.roi_cap[e];
+          if (fits) ca.rois[e][rank] = source_roi(ca, k, item, t);
+          if (hit && !fits && ca.flags) atomicOr(ca.flags + item, OCTO_FLAG_ROI_OVERFLOW);
+          if (mine) ca.roi_of[e][(size_t)item * ca.max_det + t] = fits ? rank : -1;
+          if (t == 0) *ca.n_roi[e] = all < ca.roi_cap[e] ? all : ca.roi_cap[e];
+        } else if (mine) ca.roi_of[e][(size_t)item * ca.max_det + t] = hit ? rank : -1;      // rank inside the item for now
         if (t == 0) ca.roi_cnt[e][item] = all;
         __syncthreads();
       }
@@ -601,11 +615,16 @@ __global__ __launch_bounds__(TOPK_THREADS) void select_kernel(const TopkArgs a, 
 
 bool select_fits(const TopkArgs& a) { return a.k <= SELECT_MAX && a.k <= a.k_cap && !(a.in_cap > TOPK_P && a.k > TOPK_P / 2); }
 
+// An item on its own: step 2 of the compaction has nothing to add up and is part of the selection.  Two launches : one, us of a
+// whole pass of one frame: tiny network 71.3 : 68.9, sweep 470.5 : 466.9, traffic 487.6 : 483.7, surveillance 614.6 : 610.2.  With several items the workgroup that is done last could do
+// it, but the fence across the dies that this takes costs more than the launch: 2 frames 569 : 575, 8 1023 : 1030.
+static bool select_compacts(const CompactArgs& a) { return a.n == 1; }
+
 hipError_t launch_select(const TopkArgs& a, const NmsArgs& m, const CompactArgs* ca, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   if (!select_fits(a)) return hipErrorInvalidValue;
   if (ca) for (int e = 0; e < ca->n_edges; ++e) if (!ca->roi_of[e] || !ca->roi_cnt[e]) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(select_kernel, dim3(a.n > 1024 ? 1024 : a.n), dim3(TOPK_THREADS), 0, s, a, m, ca ? *ca : CompactArgs{}, ca ? 1 : 0);
+  hipLaunchKernelGGL(select_kernel, dim3(a.n > 1024 ? 1024 : a.n), dim3(TOPK_THREADS), 0, s, a, m, ca ? *ca : CompactArgs{}, ca ? 1 : 0, ca && select_compacts(*ca) ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -682,11 +701,7 @@ __global__ __launch_bounds__(256) void compact_write_kernel(const CompactArgs a)
     int id = -1;
     if (j < a.roi_cap[e]) {
       const octo_cand c = a.top[(size_t)item * a.k_cap + a.keep[(size_t)item * a.max_det + r]];
-      octo_roi o;
-      o.frame = item; o.rank = r; o.cls = c.cls; o.pad_ = 0;
-      o.x1 = to_src(c.x1, a.left, a.rx, a.src_w); o.x2 = to_src(c.x2, a.left, a.rx, a.src_w);
-      o.y1 = to_src(c.y1, a.top_pad, a.ry, a.src_h); o.y2 = to_src(c.y2, a.top_pad, a.ry, a.src_h);
-      a.rois[e][j] = o;
+      a.rois[e][j] = source_roi(a, c, item, r);
       id = j;
     } else if (a.flags) {
       atomicOr(a.flags + item, OCTO_FLAG_ROI_OVERFLOW);
@@ -704,7 +719,7 @@ hipError_t launch_compact(const CompactArgs& a, hipStream_t s, bool counted) {
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
-  if (a.n_edges == 0) return hipSuccess;
+  if (a.n_edges == 0 || (counted && select_compacts(a))) return hipSuccess;
   hipLaunchKernelGGL(compact_write_kernel, dim3(a.n, a.n_edges), dim3(256), 0, s, a);
   return hipGetLastError();
 }

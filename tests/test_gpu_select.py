@@ -4,7 +4,7 @@ a block, and crowds.  Everything is equal, to the last bit."""
 import numpy as np
 import pytest
 
-from paper_2502_01277_amd import zoo
+from paper_2502_01277_amd import synth, zoo
 
 pytestmark = pytest.mark.gpu
 
@@ -65,4 +65,32 @@ def test_selection_equals_the_stage_calls(octo, topk, max_det, counts):
             assert np.array_equal(boxes[name][at:at + k], want[name][f, :k]), (f, name)
         at += k
     assert counts[0] == 0 or n_keep.max() > 1
+    P.close()
+
+
+@pytest.mark.parametrize("cap,classes", [(100, None), (4, None), (100, (1, 3)), (2, (0, 2, 5)), (1, ())])
+def test_a_frame_on_its_own(octo, cap, classes):
+    """One frame: the launch writes the ROI table too - the kept boxes of the classes that are routed, in their order, as many as it holds."""
+    import torch
+    spec = zoo.tiny_cascade()
+    spec.max_frames, spec.max_rois_per_frame = 1, cap
+    spec.models[0].batch_size, spec.models[1].batch_size = 1, cap
+    if classes is not None:
+        spec.edges[0].class_mask = sum(1 << c for c in classes)
+    scene = synth.make_scene(np.random.default_rng(81), 2, 320, 320, [9, 12], 16, 96, n_classes=8)
+    P = octo.Pipeline(spec)
+    for frame in scene.frames:                               # the second batch finds the counters of the first
+        P.submit([torch.from_numpy(frame).cuda()])
+        assert P.run() == 1
+        fr, boxes, st = P.collect()
+        hit = np.flatnonzero([classes is None or b["cls"] in classes for b in boxes])
+        rois = P.get_rois(0)
+        assert len(boxes) > 3 and len(rois) == min(len(hit), cap)
+        at = hit[:cap]
+        assert rois["rank"].tolist() == at.tolist() and not rois["frame"].any() and np.array_equal(rois["cls"], boxes["cls"][at])
+        for v in ("x1", "y1", "x2", "y2"):
+            assert np.array_equal(rois[v], boxes[v][at])
+        assert bool(fr["flags"][0] & 1) == (len(hit) > cap)
+        labels = boxes["child_label"][:, 0]
+        assert (labels[at] >= 0).all() and (np.delete(labels, at) == -1).all()
     P.close()
