@@ -123,7 +123,9 @@ typedef struct {
                                                          2: layers are fused as in normal operation (a first layer followed by
                                                          a 3x3 / stride-2 max-pool writes only the pooled tensor; the tensor
                                                          in between then holds nothing; two consecutive 1x1 convolutions of
-                                                         one input with one activation run as one launch) */
+                                                         one input with one activation run as one launch; so do the
+                                                         first layers and the 32-channel cross-stage block of a
+                                                         detector, whose tensors in between then hold nothing) */
 } octo_pipeline_desc;
 
 typedef struct octo_pipeline octo_pipeline;
@@ -401,11 +403,15 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
  * 0Q BBB CCC: 3x3 kernel with the input patch in LDS (17: more than 64 output channels, 18: up to 64, 14: input channels
  * not in whole slices), Q = 0 / 1 / 2 / 3 for tiles of 128 / 256 / 64 / 128 pixels, channel tile BBB, patch of CCC channels in LDS
  * (two slices), Q = 5 for the form with resident weights; 19 0F BBB KK P: first-layer kernel, channel tile, kernel height, kernel width in pixel pairs,
- * F = 1 when it also computes the 3x3 / stride-2 max-pool that follows (that layer then reports kernel 0 and 0 ms);
+ * F = 1 when it also computes the 3x3 / stride-2 max-pool that follows (that layer then reports kernel 0 and 0 ms); 20 S K BBB PPP: 3x3
+ * kernel with the patch of the whole reduction in LDS, stride S, wavefronts that share K, channel tile, pixel tile; several layers in one launch: 2100000000 the first
+ * layers of a detector, 2110000000 a cross-stage block of 32 channels, 212 P BBB KKK the entry of a cross-stage block, P blocks of 16 pixels, BBB channels a layer, KKK
+ * input channels;
  * 1 max-pool, 2 upsample, 3 channel copy, 4 add, 5 global average pool, 0 none), per ITEM dense FLOPs and activation
  * bytes (input, output and residual elements), and per LAUNCH weight and bias bytes.  When two 1x1 convolutions of
  * the same input run as one launch, the first reports the kernel, the time and the work of both (the shared input
- * counted once) and the second kernel 0 and no work. */
+ * counted once) and the second kernel 0 and no work; so with the layers of 21....  Layers that do not depend on one another and share a
+ * launch in normal operation have launches of their own while layer timing is on. */
 octo_status octo_set_layer_timing(octo_pipeline* p, int32_t enable);
 octo_status octo_get_layer_info(octo_pipeline* p, int32_t model, float* ms, int32_t* kernel_id, double* flops, double* bytes,
                                 double* weight_bytes, int32_t cap, int32_t* n);
