@@ -117,50 +117,54 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "b5ae5b93934e0484": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4366556042,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1701517445,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1427621694,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344659777,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250125650,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553380548,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 849818375,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355674081,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 282448125,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2201004242,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 353780087,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 992825467,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1909176585,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629432079,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1079049469,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167868577,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 628299130,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29838938,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 47360214,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 22045870,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 64, 2, 8, 3, 4, 2>": 34379723,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 32290465,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 29587421,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 14299272,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 8156755,
-        "octo::stem_conv_kernel<_Float16, 32, 6, 3, false>": 87629076,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 8, 3, 5, 2>": 28511387,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 77496340,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64455996,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14285729,
-        "octo::conv3x3_stream_kernel<_Float16, 1, 2, 4, 6, 3, 2>": 39783996,
-        "octo::conv1x1_stream_kernel<_Float16, 1>": 26376783,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 11436864,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21950794,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355773,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14221663,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13644822,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123422,
-        "octo::conv_small_kernel<_Float16, 32, 32, 2, 2, 4, 1>": 6687060,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1457583,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39506704,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28001511,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42487598,
+    "e9e8113c37c68b73": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4365613276,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1697996274,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1427022025,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344461344,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250181339,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553512197,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 847396187,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355694162,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281286273,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2201348479,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 353564727,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 994047175,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910196162,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629440633,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078258887,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167763262,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 626990223,
+        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29839916,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 59805773,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 2, 1>": 24368638,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 17681938,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 32124356,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 7120121,
+        "octo::conv_small_group_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 42849089,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 19790144,
+        "octo::block_kernel<_Float16, true>": 65915778,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64499135,
+        "octo::entry_kernel<_Float16>": 53067907,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14280331,
+        "octo::lead_kernel<_Float16, 64, 8, 2>": 39983164,
+        "octo::conv_small_group_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 65335100,
+        "octo::lead_kernel<_Float16, 64, 4, 2>": 33160750,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 14319781,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 1>": 14151301,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21950786,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 2>": 18567976,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355277,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14237018,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13668367,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123490,
+        "octo::conv3x3_held_kernel<_Float16, 2, 1, 4, 2>": 6728012,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4634229,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1464174,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39507907,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 27998460,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42486624,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 7168982,
     },
 }
 
