@@ -34,13 +34,14 @@ def _run(octo, m, dtype, x, keep, tensors, n):
     return got
 
 
+FORMS = [(dtype, cin, c, *size) for dtype in ("bf16", "f16") for cin, c in ((128, 64), (256, 64), (256, 128))
+         for size in ((1, 3, 5, True), (2, 9, 17, False), (1, 16, 16, True), (5, 37, 89, True))]
+FORMS += [("bf16", cin, 64, 9, 121, 123, False) for cin in (128, 256)]      # tiles of 64 pixels, which 64 channels have
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("cin,c", [(128, 64), (256, 64), (256, 128)])
-@pytest.mark.parametrize("n,h,w,shortcut", [(1, 3, 5, True), (2, 9, 17, False), (1, 16, 16, True), (5, 37, 89, True), (9, 121, 123, False)])
+@pytest.mark.parametrize("dtype,cin,c,n,h,w,shortcut", FORMS)
 def test_parity(octo, dtype, cin, c, n, h, w, shortcut):
-    if n == 9 and (c, dtype) != (64, "bf16"):
-        pytest.skip("tiles of 64 pixels are for 64 channels")
     taken = c == 64 or n * h * w >= 64 * octo.device_cu_count()
     m, a, b, d, f = _model(dtype, h, w, n, cin, c, shortcut)
     x = zoo.round_to_dtype(np.random.default_rng(62).uniform(-1, 1, (n, h, w, cin)).astype(np.float32), dtype)
