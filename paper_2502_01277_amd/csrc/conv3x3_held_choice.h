@@ -92,6 +92,23 @@ inline double held_cost_us(const ConvArgs& a, long long items, int which, int nu
   const double mb = 2e-6 * items * ((double)a.H * a.W * a.Cin + (double)a.Ho * a.Wo * a.Cout * (a.res ? 2 : 1));
   return c[0] + c[1] * k + per_cu * (c[2] * k + c[3] + c[4] * k * a.held->geom[which].rows / 32) + c[5] * mb;
 }
+// Where the count is taken on the device the choice is made for the stated one, so that an item's results do not depend on its neighbours' number, and the running count may be many times that.
+// A kernel of the common order follows it with larger tiles, this one cannot; so it takes such a layer only where it is ahead at any count: in place of kernels that are tied
+// to the stated count themselves, split-K and the narrow tiles of conv3x3_mid_kernel.  Us, the kernel before : this one, by tiles of 64 x 64 per compute unit at the stated count.
+//   * 512 channels, while resident: 7 x 7 at 1.5, stated 64, 59 items 26.0 : 19.0, 455 122 : 97, 843 217 : 183; at 1.95, stated 80, 78 items 27.2 : 18.4, 571 110 : 116, 1074 215 : 228, so
+//     from 1.7 on only where no more than 16 times the stated count has room;
+//   * 128 .. 448 up to 2.5: 256 -> 256 on 14 x 14 at 2.3, stated 48, 42 items 17.4 : 17.3, 344 73.9 : 74.5, 656 132 : 133, at 3.1, 59 items 18.5 : 17.9, 843 172 : 180; 128 -> 128 on 28 x 28 at
+//     2.3, 22 items 13.3 : 12.8, 177 45.8 : 44.9, 331 78.8 : 81.2, at 3.8, 33 items 13.3 : 12.4, 294 67.2 : 74.2, 542 113 : 135;
+//   * not with 64: 56 x 56, stated 16, 19 items 11.1 : 10.5, 71 23.5 : 25.2, 228 66.8 : 72.9;
+//   * stride 2, in place of split-K only: 256 -> 512 on 14 x 14 at 0.22, stated 8, 6 items 7.2 : 6.9, 111 38.3 : 23.3, at 0.7, stated 24, 22 items 10.4 : 9.0, 57 13.3 : 15.6, 331 50.4 : 62.4,
+//     stated 40, 542 65 : 104; 512 -> 512 on 16 x 8 at 0.5, stated 32, 27 items 18.3 : 14.0, 240 72.8 : 76.1; 128 -> 256 on 8 x 8, stated 128, 118 items 8.1 : 6.5, 923 16.5 : 20.4.
+inline bool held_counted(const ConvArgs& a, long long M, int num_cu) {
+  const double per_cu = (double)((M + 63) / 64 * (a.Cout / 64)) / num_cu;
+  if (a.stride_h == 2) return a.Cin >= 256 && per_cu <= (a.Cin >= 512 ? 0.5 : 0.25);
+  if (a.Cin < 128) return false;
+  if (a.Cin < 512) return per_cu <= 2.5;
+  return per_cu <= 1.7 || M * 16 >= (long long)a.n * a.Ho * a.Wo;
+}
 // The tile of a layer with M output pixels, or -1 where another kernel is the faster one.  Measured in place, the kernels before : this one, us, by tiles of 64 x 64 per
 // compute unit.  A launch is taken
 //   * while its tiles are resident at a time (two workgroups per compute unit, one with more than 80 KB of patch).  256 -> 256 on 20 x 20 at 0.2 7.3 : 6.6, at 0.4
@@ -112,6 +129,7 @@ inline double held_cost_us(const ConvArgs& a, long long items, int which, int nu
 // one order, so that a running count may choose between them; all else is chosen for M, which stays the same from batch to batch.
 inline int held_choose(const ConvArgs& a, long long M, int num_cu) {
   const int S = a.stride_h;
+  if (a.n_dyn && !held_counted(a, M, num_cu)) return -1;
   if (a.Cin < 128 && (S == 2 || (double)((M + 63) / 64 * (a.Cout / 64)) <= 1.96 * num_cu)) return -1;
   const long long hw = (long long)a.Ho * a.Wo, items = M / hw;
   if (S == 1 && a.Cin == 128 && !a.n_dyn && a.held->geom[2].rows && held_tiles(a, items, 2) > num_cu && held_tiles(a, items, 2) <= 2 * num_cu) return -1;

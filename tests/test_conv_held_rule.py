@@ -95,7 +95,7 @@ def test_both_sides_of_the_lines(ask):
         ((32, 20, 20, 256, 256, 1, 0, 0, 0), -1),                                       # more than are resident
         ((63, 7, 7, 512, 512, 1, 0, 0, 0), 2), ((134, 7, 7, 512, 512, 1, 0, 0, 0), -1),
         ((48, 40, 40, 128, 128, 1, 0, 0, 0), 2), ((64, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # six per compute unit
-        ((480, 40, 40, 128, 128, 1, 0, 48, 48), -1), ((480, 40, 40, 128, 128, 1, 0, 16, 16), 2), ((16, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # with the count on the device two
+        ((480, 40, 40, 128, 128, 1, 0, 48, 48), -1), ((480, 40, 40, 128, 128, 1, 0, 12, 12), 2), ((16, 40, 40, 128, 128, 1, 0, 0, 0), -1),
         ((5, 80, 80, 64, 64, 1, 0, 0, 0), -1), ((6, 80, 80, 64, 64, 1, 0, 0, 0), 2), ((12, 80, 80, 64, 64, 1, 0, 0, 0), -1),
         ((2, 80, 80, 128, 128, 2, 0, 0, 0), 0), ((6, 80, 80, 128, 128, 2, 0, 0, 0), -1), ((1, 14, 14, 128, 256, 2, 0, 0, 0), -1), ((1, 160, 160, 64, 128, 2, 0, 0, 0), -1),
         ((30, 14, 14, 256, 512, 2, 0, 0, 0), 1), ((134, 14, 14, 256, 512, 2, 0, 0, 0), -1),
@@ -103,3 +103,21 @@ def test_both_sides_of_the_lines(ask):
         ((480, 14, 14, 256, 256, 1, 0, 4, 4), 0), ((480, 14, 14, 256, 256, 1, 0, 4, 300), 1), ((480, 14, 14, 256, 256, 1, 0, 41, 3), 2),
         ((480, 14, 14, 256, 256, 1, 0, 200, 3), -1)]
     assert [t for _, t, _ in ask([c for c, _ in cases])] == [t for _, t in cases]
+
+
+def test_a_count_on_the_device_may_be_many_times_the_stated_one(ask):
+    """(Stated count, capacity, map, channels, stride): layers of downstream classifiers whose running count is 14 times the stated one, on both sides of the lines."""
+    cases = [
+        ((40, 1500, 14, 256, 512, 2), False), ((24, 900, 14, 256, 512, 2), False), ((8, 300, 14, 256, 512, 2), True),          # 65 : 104 us, 50 : 62, 38 : 23
+        ((32, 256, 8, 512, 512, 2), True), ((72, 256, 8, 512, 512, 2), False), ((64, 512, 8, 128, 256, 2), False),
+        ((16, 600, 56, 64, 64, 1), False), ((32, 1200, 56, 64, 64, 1), False),                                                   # 67 : 73
+        ((24, 900, 28, 128, 128, 1), True), ((32, 1200, 28, 128, 128, 1), False), ((40, 1500, 28, 128, 128, 1), False),         # 79 : 81, 98 : 106, 113 : 135
+        ((48, 1800, 14, 256, 256, 1), True), ((64, 2400, 14, 256, 256, 1), False), ((72, 2700, 14, 256, 256, 1), False),        # 132 : 133, 172 : 180, 200 : 210
+        ((64, 2400, 7, 512, 512, 1), True), ((72, 2700, 7, 512, 512, 1), False), ((72, 576, 7, 512, 512, 1), True)]             # 217 : 183, 186 : 199, and at 7 times 110 : 116
+    got = ask([(cap, hw, hw, ci, co, s, 0, stated, h) for (stated, cap, hw, ci, co, s), _ in cases for h in (0, min(cap, 14 * stated))])
+    taken = [t >= 0 for _, t, _ in got]
+    assert taken[::2] == taken[1::2]                       # a matter of the stated count alone
+    assert taken[::2] == [w for _, w in cases]
+    # the same layers with a count that the host knows
+    known = [t >= 0 for _, t, _ in ask([(stated, hw, hw, ci, co, s, 0, 0, 0) for (stated, _, hw, ci, co, s), _ in cases])]
+    assert known.count(True) > taken[::2].count(True)
