@@ -115,14 +115,11 @@ inline bool held_counted(const ConvArgs& a, long long M, int num_cu) {
 //     12.9 : 7.6, at 0.8 15.6 : 9.0, at 1.6 16.0 : 11.6, at 2.3 (three rounds of 64 x 64) 17.9 : 17.1, at 3.1 19.3 : 20.4, on 14 x 14 at 3.7 19.0 : 18.6, at 6.4
 //     31.1 : 33.2; 512 -> 512 on 7 x 7 at 0.1 9.6 : 9.1, at 0.36 17.5 : 9.7, at 1.0 25.6 : 15.0, at 1.8 26.7 : 18.1, at 3.2 29.8 : 31.0; 384 -> 384 on 40 x 40 at
 //     0.6 19.7 : 11.5, at 1.2 20.3 : 14.7, at 2.3 22.4 : 25.8.  At stride 2 256 -> 512 on 7 x 7 at 0.36 9.2 : 7.3, at 1.0 14.9 : 10.0, at 1.8 17.9 : 16.7;
-//   * with 128 and 192 channels, whose patch leaves room for two workgroups, up to six 64 x 128 tiles per compute unit, where no count is taken on the device:
-//     128 -> 128 on 40 x 40 at 0.2 5.6 : 5.1, at 1.6 9.6 : 8.2, at 3.1 12.4 : 11.8, at 4.7 16.5 : 16.9, at 9.4 27.6 : 25.3, on 28 x 28 at 12.8 33.2 : 33.0, at 15.3
-//     39.3 : 39.8; 192 -> 192 on 80 x 80 at 1.2 12.4 : 9.8, at 9.4 34.1 : 32.6.  With a count larger than expected the large tiles of conv3x3_mid_kernel win (128 -> 128
-//     on 843 x 28 x 28, chosen for 64, 160 : 207);
+//   * with 128 and 192 channels, whose patch leaves room for two workgroups, up to five 64 x 128 tiles per compute unit, where no count is taken on the device: 128 -> 128 on 40 x 40 at 0.2
+//     5.6 : 5.1, at 1.6 9.4 : 8.7, at 2.1 13.5 : 13.2, at 3.9 16.2 : 15.6, at 4.1 (conv3x3_mid_kernel leaves its wide slices) 17.4 : 17.9, at 4.9 18.3 : 18.3, at 5.9 19.7 : 18.6, at 9.4
+//     30.0 : 27.8, beyond at 10.2 35.8 : 36.6; 192 -> 192 on 80 x 80 at 1.2 13.3 : 10.7, at 4.7 23.8 : 21.2, at 9.4 36.4 : 34.3, beyond at 10.5 38.8 : 42.2, at 11.7 40.8 : 42.7;
 //   * with 64 only from where conv_small_kernel leaves: 64 -> 64 on 80 x 80 at 0.8 4.7 : 5.0, at 1.6 6.8 : 7.1, at 2.3 9.2 : 8.4, at 3.9 11.1 : 9.4, at 4.7 (more than are
 //     resident) 12.6 : 12.9;
-//   * not with 128 between one and two 64 x 128 tiles per compute unit where no count is taken on the device: there conv3x3_mid_kernel has its wide slices, and little
-//     is left to gain (128 -> 128 on 40 x 40 at 2.3 12.3 : 11.4, at 3.1 12.4 : 11.8);
 //   * at stride 2 with 128 only a quarter to one 64 x 32 tile per compute unit: 128 -> 256 on 4 x 4 at 0.3 8.1 : 6.3, 128 -> 128 on 40 x 40 at 0.4 5.8 : 5.4, at 0.6 6.7 :
 //     6.8, 128 -> 256 on 4 x 4 at 0.07 5.5 : 5.3; not with 64 (64 -> 128 on 40 x 40 at 0.8 4.9 : 5.7).
 // Over 408 layers of three detectors and three classifiers (1 .. 48 frames) 0.85 of the time of the kernels before, at most 1.07.  Tiles of 64 x 32 and 64 x 64 sum in
@@ -132,14 +129,13 @@ inline int held_choose(const ConvArgs& a, long long M, int num_cu) {
   if (a.n_dyn && !held_counted(a, M, num_cu)) return -1;
   if (a.Cin < 128 && (S == 2 || (double)((M + 63) / 64 * (a.Cout / 64)) <= 1.96 * num_cu)) return -1;
   const long long hw = (long long)a.Ho * a.Wo, items = M / hw;
-  if (S == 1 && a.Cin == 128 && !a.n_dyn && a.held->geom[2].rows && held_tiles(a, items, 2) > num_cu && held_tiles(a, items, 2) <= 2 * num_cu) return -1;
   int best = -1;
   double us = 0;
   for (int i = 0; i < (S == 2 ? (a.Cin < 256 ? 1 : 2) : 3); ++i) {
     if (a.held->geom[i].rows == 0) continue;
     const bool wide = i == 2 && a.Cin >= 128 && a.Cin <= 192 && !a.n_dyn;
     const long long tiles = held_tiles(a, items, i);
-    if (tiles > (wide ? 6 * num_cu : S == 2 && a.Cin < 256 ? num_cu : held_resident(a, i, num_cu))) continue;
+    if (tiles > (wide ? 5 * num_cu : S == 2 && a.Cin < 256 ? num_cu : held_resident(a, i, num_cu))) continue;
     if (S == 2 && a.Cin < 256 && tiles * 4 < num_cu) continue;
     const double t = held_cost_us(a, items, i, num_cu);
     if (best < 0 || t < us) { us = t; best = i; }

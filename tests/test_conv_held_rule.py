@@ -94,8 +94,9 @@ def test_both_sides_of_the_lines(ask):
         ((4, 20, 20, 256, 256, 1, 0, 0, 0), 0), ((8, 20, 20, 256, 256, 1, 0, 0, 0), 1), ((16, 20, 20, 256, 256, 1, 0, 0, 0), 2),
         ((32, 20, 20, 256, 256, 1, 0, 0, 0), -1),                                       # more than are resident
         ((63, 7, 7, 512, 512, 1, 0, 0, 0), 2), ((134, 7, 7, 512, 512, 1, 0, 0, 0), -1),
-        ((48, 40, 40, 128, 128, 1, 0, 0, 0), 2), ((64, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # six per compute unit
-        ((480, 40, 40, 128, 128, 1, 0, 48, 48), -1), ((480, 40, 40, 128, 128, 1, 0, 12, 12), 2), ((16, 40, 40, 128, 128, 1, 0, 0, 0), -1),
+        ((48, 40, 40, 128, 128, 1, 0, 0, 0), 2), ((52, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # five per compute unit
+        ((8, 80, 80, 192, 192, 1, 0, 0, 0), 2), ((9, 80, 80, 192, 192, 1, 0, 0, 0), -1), ((10, 80, 80, 192, 192, 1, 0, 0, 0), -1),
+        ((480, 40, 40, 128, 128, 1, 0, 48, 48), -1), ((480, 40, 40, 128, 128, 1, 0, 12, 12), 2), ((480, 14, 14, 256, 256, 1, 0, 41, 41), 2),
         ((5, 80, 80, 64, 64, 1, 0, 0, 0), -1), ((6, 80, 80, 64, 64, 1, 0, 0, 0), 2), ((12, 80, 80, 64, 64, 1, 0, 0, 0), -1),
         ((2, 80, 80, 128, 128, 2, 0, 0, 0), 0), ((6, 80, 80, 128, 128, 2, 0, 0, 0), -1), ((1, 14, 14, 128, 256, 2, 0, 0, 0), -1), ((1, 160, 160, 64, 128, 2, 0, 0, 0), -1),
         ((30, 14, 14, 256, 512, 2, 0, 0, 0), 1), ((134, 14, 14, 256, 512, 2, 0, 0, 0), -1),
@@ -121,3 +122,10 @@ def test_a_count_on_the_device_may_be_many_times_the_stated_one(ask):
     # the same layers with a count that the host knows
     known = [t >= 0 for _, t, _ in ask([(stated, hw, hw, ci, co, s, 0, 0, 0) for (stated, _, hw, ci, co, s), _ in cases])]
     assert known.count(True) > taken[::2].count(True)
+
+
+def test_no_hole_between_the_lines(ask):
+    """Once a batch has outgrown the kernel, no larger one takes it again."""
+    for h, ci, top in ((40, 128, 51), (80, 192, 8), (20, 256, 20), (40, 384, 3)):
+        taken = [t >= 0 for _, t, _ in ask([(n, h, h, ci, ci, 1, 0, 0, 0) for n in range(1, 80)])]
+        assert taken.index(False) == top and not any(taken[top:]), (h, ci, taken.index(False))
