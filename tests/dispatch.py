@@ -9,19 +9,19 @@ from paper_2502_01277_amd.build import HERE
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 DTYPES = {"f32": 0, "f16": 1, "bf16": 2, "f8": 3}
 # place: a layer of a model; split, hint: item counts stated and expected where the count is taken on the device; second: channels of the first of two
-# layers in one launch; upsampled: an upsampling of the output follows
-FIELDS = ("n", "h", "w", "cin", "cout", "k", "stride", "res", "place", "split", "hint", "second", "upsampled")
+# layers in one launch; upsampled: an upsampling of the output follows; bare: of a model, but without what one keeps for conv3x3_held_kernel
+FIELDS = ("n", "h", "w", "cin", "cout", "k", "stride", "res", "place", "split", "hint", "second", "upsampled", "bare")
 
 SOURCE = r'''
-#include "csrc/octo_internal.h"
+#include "csrc/conv3x3_held_choice.h"
 #include <cstdio>
 extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
 extern "C" hipError_t hipExtLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) { return hipSuccess; }
 extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 int main() {
-  int dt, n, h, w, ci, co, k, st, res, place, split, hint, second, up;
-  while (scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d", &dt, &n, &h, &w, &ci, &co, &k, &st, &res, &place, &split, &hint, &second, &up) == 14) {
+  int dt, n, h, w, ci, co, k, st, res, place, split, hint, second, up, bare;
+  while (scanf("%d %d %d %d %d %d %d %d %d %d %d %d %d %d %d", &dt, &n, &h, &w, &ci, &co, &k, &st, &res, &place, &split, &hint, &second, &up, &bare) == 15) {
     octo::ConvArgs a{};
     a.x = (void*)0x10000; a.w = (void*)0x20000; a.bias = (float*)0x30000; a.y = (void*)0x40000;      // never followed
     if (res) { a.res = (void*)0x50000; a.res_mode = res; a.res_ld = co; }
@@ -31,6 +31,12 @@ int main() {
     a.in_place = place; a.n_split = split; a.n_hint = hint; a.up_next = up; a.act = OCTO_ACT_SILU;
     if (split || hint) a.n_dyn = (int*)0x60000;
     if (second) { a.split = a.y_ld = second; a.y2 = (void*)0x70000; a.y2_ld = co - second; }
+    octo::HeldPlan plan;
+    if (place && !bare && (dt == OCTO_F16 || dt == OCTO_BF16) && octo::held_layer(k, k, st, k / 2, h, ci, co)) {
+      plan = octo::held_plan(st, w, a.Ho, a.Wo, ci, co);
+      plan.w = (void*)0x90000;
+      a.held = &plan;
+    }
     if (dt == OCTO_F8) { a.scale = (float*)0x80000; a.res_scale = a.y_inv_scale = 1; }
     int kid = -1;
     const hipError_t e = octo::launch_conv(dt, a, 256, nullptr, &kid);

@@ -62,7 +62,7 @@ def test_broken_k_steps_in_a_model_go_from_one_kernel_to_the_next(ids, dtype):
     assert [family(k) for k in ids(layers)] == want
 
 
-SPLIT, PATCHES = 16, (14, 17, 18)
+SPLIT, PATCHES, HELD = 16, (14, 17, 18), (20,)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
@@ -79,13 +79,16 @@ def test_split_k_is_chosen_alike_for_a_layer_of_a_model_and_a_single_call(ids, d
         if k * k * cin < 60000 and 2 * n * h * h * max(cin, cout) < 1 << 30:
             layers.append(dict(dtype=dtype, n=n, h=h, w=h, cin=cin, cout=cout, k=k, stride=stride, res=r.choice([0, 0, 2]), upsampled=int(k == 1 and r.random() < 0.1),
                                split=r.choice([0, 0, max(1, n // 2)]), hint=r.choice([0, 0, max(1, n // 3)])))
-    alone, place = ids(layers), ids([dict(l, place=1) for l in layers])
+    alone, place, model = ids(layers), ids([dict(l, place=1, bare=1) for l in layers]), ids([dict(l, place=1) for l in layers])
     assert sum(family(k) == SPLIT for k in alone) > 300
     differ = [(l, a, p) for l, a, p in zip(layers, alone, place) if a != p and SPLIT in (family(a), family(p))]
     assert not differ, (len(differ), differ[:2])
     # the others that differ: the lines and slices of the 3x3 kernels, else kernels of one order
     others = {family(k) for a, p in zip(alone, place) if a != p and not (family(a) in PATCHES and family(p) in PATCHES) for k in (a, p)}
     assert others <= {10, 11, 12, SMALL, STREAM}
+    # and what a model keeps for conv3x3_held_kernel makes no difference but that this takes the layer
+    assert all(m == p or family(m) in HELD for p, m in zip(place, model))
+    assert sum(family(m) in HELD for m in model) > (25 if dtype != "f32" else -1)
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -113,7 +116,7 @@ extern "C" int both() { return sound(octo::FLOW_COST) + 2 * sound(octo::SMALL_CO
 def test_wide_slices_of_128_channels_end_where_a_compute_unit_has_no_place_left(ids, dtype):
     """3x3 layers of 128 channels in a model: slices of 64 channels while there are two 64 x 128 tiles per compute unit at most, whole images counted as the
     kernel cuts them, else slices of 32 (kernel ids end in the channels that two buffers hold)."""
-    common = dict(dtype=dtype, cin=128, k=3, place=1)
+    common = dict(dtype=dtype, cin=128, k=3, place=1, bare=1)
     cases = [(20, 40, 40, 128, 128), (21, 40, 40, 128, 64), (80, 20, 20, 128, 64), (41, 28, 28, 128, 128), (42, 28, 28, 128, 64), (2, 160, 160, 64, 128), (269, 16, 16, 64, 64),
              (48, 28, 28, 128, 64), (62, 28, 28, 128, 64), (24, 28, 28, 256, 64)]
     got = ids([dict(common, n=n, h=h, w=w, cout=co) for n, h, w, co, _ in cases])
@@ -121,6 +124,27 @@ def test_wide_slices_of_128_channels_end_where_a_compute_unit_has_no_place_left(
     # a count taken on the device, and single calls: slices of 32 throughout
     for change in (dict(place=0), dict(split=20, hint=20)):
         assert all(k % 1000 == 64 for k in ids([dict(common, n=n, h=h, w=w, cout=co, **change) for n, h, w, co, _ in cases[:1]]))
+    # in a model it is the layers whose output channels are no multiple of 64 that come here with few tiles
+    for cout, want in ((120, [(17, 128), (17, 64)]), (128, [(20, 128), (20, 128)])):
+        assert [(family(k), k % 1000) for k in ids([dict(common, n=n, h=40, w=40, cout=cout, bare=0) for n in (20, 21)])] == want
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_layers_of_a_model_with_the_patch_of_the_whole_reduction_in_lds(ids, dtype):
+    """conv3x3_held_kernel is asked first: where it takes a layer and who has it beyond each line - the patch kernel, split-K, conv_small_kernel, conv_flow_kernel.
+    Single calls keep nothing for it."""
+    cases = [(dict(n=1, h=20, cin=256, cout=256), 2014064032), (dict(n=20, h=20, cin=256, cout=256), 2014064064), (dict(n=21, h=20, cin=256, cout=256), 17),
+             (dict(n=51, h=40, cin=128, cout=128), 2012064128), (dict(n=52, h=40, cin=128, cout=128), 17), (dict(n=8, h=80, cin=192, cout=192), 2012064128),
+             (dict(n=9, h=80, cin=192, cout=192), 1701096064), (dict(n=5, h=80, cin=64, cout=64), 13), (dict(n=6, h=80, cin=64, cout=64), 2012064128),
+             (dict(n=8, h=40, cin=256, cout=256, stride=2), 2024064064), (dict(n=16, h=40, cin=256, cout=256, stride=2), 13),
+             (dict(n=300, h=14, cin=256, cout=512, stride=2, split=8, hint=111), 2024064064), (dict(n=1500, h=14, cin=256, cout=512, stride=2, split=40, hint=542), 12),
+             (dict(n=900, h=28, cin=128, cout=128, split=24, hint=331), 2012064128), (dict(n=1500, h=28, cin=128, cout=128, split=40, hint=542), 17),
+             (dict(n=600, h=56, cin=64, cout=64, split=16, hint=228), 18)]
+    layers = [dict(l, dtype=dtype, w=l["h"], k=3) for l, _ in cases]
+    got = ids([dict(l, place=1) for l in layers])
+    assert [k // 10 ** (10 - len(str(w))) for k, (_, w) in zip(got, cases)] == [w for _, w in cases], got
+    assert not any(family(k) in HELD for k in ids(layers))
+    assert 16 in {family(k) for k in ids(layers)}                   # among them layers that are split-K's alone
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
