@@ -76,6 +76,10 @@ def conv_name(kid: int, dtype: str) -> str:
         return "octo::entry_kernel<%s>" % ctype
     if kid // 10**7 == 212:                              # the entry of a cross-stage block in one launch: pixel tile / 16, channels, input channels
         return "octo::lead_kernel<%s, %d, %d, %d>" % (ctype, kid // 1000 % 1000, kid % 1000 // 32, kid // 10**6 % 10)
+    if kid // 10**7 == 213:                              # layers that do not depend on one another: twice their number + how addresses are made, tile
+        bc, bp, mode = kid // 1000 % 1000, kid % 1000, kid // 10**6 % 2
+        wc = {(32, 64): 1, (128, 64): 4}.get((bc, bp), 2)
+        return "octo::conv_small_group_kernel<%s, %d, %d, %d, %d, %d, %d>" % ((ctype, bc, bp, wc) + SMALL[(bc, bp)] + (mode,)) if (bc, bp) in SMALL else "convolution kernel %d" % kid
     if kid == 2110000000:                                # a cross-stage block of 32 channels in one launch, with a shortcut as the detectors have it
         return "octo::block_kernel<%s, true>" % ctype
     if d >= 1000000000:                                  # 3x3 layers of few tiles, patch of all channels in LDS: digits S K BBB PPP

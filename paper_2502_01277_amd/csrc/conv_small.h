@@ -330,7 +330,8 @@ static hipError_t launch_small_cfg(int which, const ConvArgs& a, int num_cu, hip
   if (kernel_id) *kernel_id = small_kernel_id(BC, BP, WC, mode);
   if (a.group && a.group->count < SmallGroup::MAX) {       // launched with the others of its group
     SmallGroup& g = *a.group;
-    g.tile[g.count] = which; g.mode[g.count] = mode; g.layer[g.count++] = o;
+    if (g.count == 0) g.timing = tm;
+    g.tile[g.count] = which; g.mode[g.count] = mode; g.kernel_id[g.count] = kernel_id; g.layer[g.count++] = o;
     return hipSuccess;
   }
   auto go = [&](auto mode_c) {
@@ -365,17 +366,19 @@ template <typename T, int BC, int BP, int WC, int WP, int MINB>
 static hipError_t launch_small_group_cfg(const SmallGroup& g, hipStream_t s) {
   auto go = [&](auto mode_c) {
     constexpr int MODE = decltype(mode_c)::value, NT = 64 * WC * WP;
-    if (g.count == 1) {
-      hipLaunchKernelGGL((conv_small_kernel<T, BC, BP, WC, WP, MINB, MODE>), dim3((unsigned)g.layer[0].grid), dim3(NT), 0, s, g.layer[0]);
+    auto start = [&](auto kernel, int grid, const auto& args) {
+      if (g.timing.start && g.timing.stop) hipExtLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NT), 0, s, g.timing.start, g.timing.stop, 0, args);
+      else hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(NT), 0, s, args);
       return hipGetLastError();
-    }
+    };
+    if (g.count == 1) return start(conv_small_kernel<T, BC, BP, WC, WP, MINB, MODE>, g.layer[0].grid, g.layer[0]);
+    for (int i = 0; i < g.count; ++i)
+      if (g.kernel_id[i]) *g.kernel_id[i] = i ? KID_NONE : group_kernel_id(BC, BP, g.count, MODE);
     SmallGroupArgs a{};
     for (int i = 0; i < g.count; ++i) a.layer[i] = g.layer[i];
     a.second = g.layer[0].grid;
     a.third = a.second + g.layer[1].grid;
-    const int grid = a.third + (g.count > 2 ? g.layer[2].grid : 0);
-    hipLaunchKernelGGL((conv_small_group_kernel<T, BC, BP, WC, WP, MINB, MODE>), dim3((unsigned)grid), dim3(NT), 0, s, a);
-    return hipGetLastError();
+    return start(conv_small_group_kernel<T, BC, BP, WC, WP, MINB, MODE>, a.third + (g.count > 2 ? g.layer[2].grid : 0), a);
   };
   return g.mode[0] == SMALL_TAPS ? go(std::integral_constant<int, SMALL_TAPS>{}) : go(std::integral_constant<int, SMALL_POINTWISE>{});
 }

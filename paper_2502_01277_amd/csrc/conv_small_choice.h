@@ -26,6 +26,8 @@ struct SmallGroup {
   static constexpr int MAX = 3;
   int count = 0;
   int tile[MAX], mode[MAX];
+  int* kernel_id[MAX];                   // of the layers: what they report; may be null
+  ConvTiming timing;                     // of the first one's dispatch
   SmallArgs layer[MAX];
 };
 hipError_t launch_small_group_f16(const SmallGroup& g, hipStream_t s);

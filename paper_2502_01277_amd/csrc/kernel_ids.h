@@ -52,5 +52,9 @@ constexpr int KID_BLOCK = 2110000000;
 // the entry of a cross-stage block in one launch (lead.hip), digits 212 P BBB KKK: pixel tile / 16, channels of a layer, input channels
 constexpr int lead_kernel_id(int c, int cin, int np) { return 2120000000 + np * 1000000 + c * 1000 + cin; }
 constexpr bool is_lead(int id) { return id / 10000000 == 212; }
+// several layers of conv_small_kernel in one launch (conv_small.h), digits 213 G BBB PPP: G = twice the number of layers + how addresses are made, tile.  The layer that had its
+// arguments collected first reports it, the others KID_NONE
+constexpr int group_kernel_id(int bc, int bp, int count, int mode) { return 2130000000 + (2 * count + mode) * 1000000 + bc * 1000 + bp; }
+constexpr int group_layers(int id) { return id / 10000000 == 213 ? id / 1000000 % 10 / 2 : 0; }
 
 }  // namespace octo

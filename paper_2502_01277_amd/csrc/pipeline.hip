@@ -793,27 +793,35 @@ hipError_t run_labels(ModelPlan& m, int n, const int* n_dyn, hipStream_t s) {
   return launch_argmax((const float*)lg.ptr + lg.coff, lg.ld, m.n_logits, n_dyn, n, m.labels, m.label_dest, s);
 }
 
+// The first layer of the group that layer i belongs to, and whether that group has others.
+int group_of(const ModelPlan& m, int i) {
+  int from = 0;
+  while (from + m.layers[from].group <= i) from += m.layers[from].group;
+  return from;
+}
+bool in_group(const ModelPlan& m, int i) { return m.layers[group_of(m, i)].group > 1; }
+
 hipError_t run_layers(octo_pipeline* p, ModelPlan& m, int n, const int* n_dyn, hipStream_t s, std::vector<hipEvent_t>* evs = nullptr) {
   hipError_t e;
   // timing events: [0..L] bracket the layers on the stream; [L+1+2i], [L+2+2i] ride on layer i's convolution dispatch
   const int L = (int)m.layers.size();
   if (evs && (e = hipEventRecord((*evs)[0], s)) != hipSuccess) return e;
   for (int i = 0; i < L; ++i) {
-    if (const int count = m.layers[i].group; count > 1 && !evs) {       // (with timing every layer has a launch of its own)
+    auto timing = [&](int j) { return evs ? ConvTiming{(*evs)[L + 1 + 2 * j], (*evs)[L + 2 + 2 * j]} : ConvTiming(); };
+    if (const int count = m.layers[i].group; count > 1) {
       // the one with the most work first: the group has its tile
       SmallGroup g;
       int most = i;
       for (int j = i; j < i + count; ++j) if (m.layers[j].flops > m.layers[most].flops) most = j;
-      if ((e = run_layer(p, m, most, n, n_dyn, s, ConvTiming(), &g)) != hipSuccess) return e;
+      if ((e = run_layer(p, m, most, n, n_dyn, s, timing(most), &g)) != hipSuccess) return e;
       for (int j = i; j < i + count; ++j)
-        if (j != most && (e = run_layer(p, m, j, n, n_dyn, s, ConvTiming(), &g)) != hipSuccess) return e;
+        if (j != most && (e = run_layer(p, m, j, n, n_dyn, s, timing(j), &g)) != hipSuccess) return e;
       if (g.count > 0 && (e = m.d.dtype == OCTO_F16 ? launch_small_group_f16(g, s) : launch_small_group_bf16(g, s)) != hipSuccess) return e;
+      for (int j = i; evs && j < i + count; ++j) if ((e = hipEventRecord((*evs)[j + 1], s)) != hipSuccess) return e;
       i += count - 1;
       continue;
     }
-    ConvTiming tm;
-    if (evs) { tm.start = (*evs)[L + 1 + 2 * i]; tm.stop = (*evs)[L + 2 + 2 * i]; }
-    if ((e = run_layer(p, m, i, n, n_dyn, s, tm)) != hipSuccess) return e;
+    if ((e = run_layer(p, m, i, n, n_dyn, s, timing(i))) != hipSuccess) return e;
     if (evs && (e = hipEventRecord((*evs)[i + 1], s)) != hipSuccess) return e;
   }
   // with every buffer kept, the tensors that an entry or a block has left inside its launch are written all the same: behind the timed layers, and reported by none
@@ -1527,8 +1535,9 @@ octo_status octo_collect(octo_pipeline* p, octo_frame_result* frames, int32_t fr
         // failed query must not stay behind as the runtime's last error either: the next launch would report it)
         const LayerPlan& lq = p->models[k].layers[i];
         const bool conv = (lq.L.op == OCTO_CONV || lq.L.op == OCTO_FC) && lq.kernel_id != KID_NONE;
+        const bool grouped = lq.L.op == OCTO_CONV && lq.kernel_id == KID_NONE && in_group(p->models[k], (int)i);       // (its bracket may hold the others' launch)
         float ms = 0.f;
-        if (!B.model_ran[k]) ms = 0.f;
+        if (!B.model_ran[k] || grouped) ms = 0.f;
         else if (conv && hipEventElapsedTime(&ms, le[L + 1 + 2 * i], le[L + 2 + 2 * i]) == hipSuccess) {}
         else {
           if (conv) (void)hipGetLastError();
@@ -1606,7 +1615,8 @@ octo_status octo_set_layer_timing(octo_pipeline* p, int32_t enable) {
   return OCTO_OK;
 }
 
-// Per item work, and bytes of weights, of three or four layers that ran as one launch: all of it with the first.  False for a layer that is none of those.
+// Per item work, and bytes of weights, of layers that ran as one launch, two 1x1 layers of one input apart: all of it with the one that reports the kernel.  False for a layer that is none of
+// those.
 static bool fused_work(const ModelPlan& m, int i, double* flops, double* bytes, double* weight_bytes) {
   for (int b = std::max(0, i - 3); b <= i; ++b) {
     const LayerPlan* L = m.layers.data() + b;
@@ -1628,7 +1638,20 @@ static bool fused_work(const ModelPlan& m, int i, double* flops, double* bytes, 
     if (bytes) *bytes = !first ? 0.0 : (L[0].lead_keep ? L[0].bytes : L[0].input_bytes) + L[1].bytes - L[1].input_bytes + L[2].bytes - L[2].input_bytes;
     return true;
   }
-  return false;
+  // layers that do not depend on one another: each reads its own input, and the ones that report no kernel were in the launch
+  const int from = group_of(m, i);
+  int owner = -1;
+  for (int b = from; b < from + m.layers[from].group; ++b) if (group_layers(m.layers[b].kernel_id) > 1) owner = b;
+  if (owner < 0 || (i != owner && m.layers[i].kernel_id != KID_NONE)) return false;
+  double f = 0, y = 0, w = 0;
+  for (int b = from; i == owner && b < from + m.layers[from].group; ++b) {
+    const LayerPlan& q = m.layers[b];
+    if (b == owner || q.kernel_id == KID_NONE) { f += q.flops; y += q.bytes; w += q.weight_bytes; }
+  }
+  if (flops) *flops = f;
+  if (bytes) *bytes = y;
+  if (weight_bytes) *weight_bytes = w;
+  return true;
 }
 
 octo_status octo_get_layer_info(octo_pipeline* p, int32_t model, float* ms, int32_t* kernel_id, double* flops, double* bytes,
