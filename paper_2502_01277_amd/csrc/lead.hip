@@ -177,7 +177,7 @@ hipError_t launch_lead(int dtype, const LeadArgs& a, int num_cu, hipStream_t s, 
   };
   auto form = [&](auto zero) {
     using T = decltype(zero);
-    if (a.C == 128) return np == 1 ? go(lead_kernel<T, 128, 8, 1>) : go(lead_kernel<T, 128, 8, 2>);
+    if (a.C == 128) return go(lead_kernel<T, 128, 8, 2>);          // (refused where tiles of 16 pixels would be chosen)
     if (a.Cin == 128) return np == 1 ? go(lead_kernel<T, 64, 4, 1>) : np == 2 ? go(lead_kernel<T, 64, 4, 2>) : go(lead_kernel<T, 64, 4, 4>);
     return np == 1 ? go(lead_kernel<T, 64, 8, 1>) : np == 2 ? go(lead_kernel<T, 64, 8, 2>) : go(lead_kernel<T, 64, 8, 4>);
   };
