@@ -29,19 +29,6 @@ struct BlockKernelArgs {
   FastDiv div_tx, div_ty;
 };
 
-template <typename T>
-__device__ __forceinline__ floatx4 block_mfma(u32x4 a, u32x4 b, floatx4 c) {
-  if constexpr (std::is_same<T, _Float16>::value) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
-  else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-template <typename T>
-__device__ __forceinline__ u32x4 block_silu(floatx4 lo, floatx4 hi) {
-  u32x4 out;
-  store4<T>((T*)&out, floatx4{silu(lo[0]), silu(lo[1]), silu(lo[2]), silu(lo[3])});
-  store4<T>((T*)&out + 4, floatx4{silu(hi[0]), silu(hi[1]), silu(hi[2]), silu(hi[3])});
-  return out;
-}
-
 template <typename T, bool SHORTCUT>
 __global__ __launch_bounds__(256, 2) void block_kernel(const BlockKernelArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char s_h[2][192 * 64];
@@ -123,7 +110,7 @@ __global__ __launch_bounds__(256, 2) void block_kernel(const BlockKernelArgs a) 
     const bool inside = cy > 0 && cx > 0 && cy + BLOCK_TH < a.H && cx + BLOCK_TW < a.W;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      u32x4 out = block_silu<T>(block_mfma<T>(w0[0], f0[i], b0[0]), block_mfma<T>(w0[1], f0[i], b0[1]));
+      u32x4 out = silu8<T>(mfma16<T>(w0[0], f0[i], b0[0]), mfma16<T>(w0[1], f0[i], b0[1]));
       if (!inside && ((unsigned)(cy - 1 + (at0[i] >> 16)) >= (unsigned)a.H || (unsigned)(cx - 1 + (at0[i] & 0xFFFF)) >= (unsigned)a.W)) out = u32x4{0u, 0u, 0u, 0u};
       *(u32x4*)(s_h[buf] + wr0[i]) = out;
     }
@@ -138,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void block_kernel(const BlockKernelArgs a) 
       for (int tap = 0; tap < 9; ++tap) {
         const u32x4 f = *(const u32x4*)(s_h[buf] + rd1[j][tap]);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[b] = block_mfma<T>(w1[b][tap], f, tap == 0 ? b1[b] : acc[b]);
+        for (int b = 0; b < 2; ++b) acc[b] = mfma16<T>(w1[b][tap], f, tap == 0 ? b1[b] : acc[b]);
       }
       // a lane's 8 channels of its pixel are its operand of the last layer
       u32x4 h;
@@ -154,13 +141,13 @@ __global__ __launch_bounds__(256, 2) void block_kernel(const BlockKernelArgs a) 
       }
       floatx4 o[4];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) o[b] = block_mfma<T>(w2[b][1], other[j], block_mfma<T>(w2[b][0], h, b2[b]));
+      for (int b = 0; b < 4; ++b) o[b] = mfma16<T>(w2[b][1], other[j], mfma16<T>(w2[b][0], h, b2[b]));
       if (more) other[j] = load(a.z, a.z_pitch, y0 + wave * 2 + j, x0 + r16);
       const int Y = cy + wave * 2 + j, X = cx + r16;
       if (Y < a.H && X < a.W) {
         u32x4* q = (u32x4*)(yb + (size_t)(Y * a.W + X) * a.y_pitch + q4 * 16);
-        q[0] = block_silu<T>(o[0], o[1]);
-        q[4] = block_silu<T>(o[2], o[3]);
+        q[0] = silu8<T>(o[0], o[1]);
+        q[4] = silu8<T>(o[2], o[3]);
       }
     }
     if (!more) break;

@@ -33,21 +33,6 @@ struct EntryKernelArgs {
   FastDiv div_tx, div_ty;
 };
 
-// D = A B for a block of 16 x 16 and 32 of K
-template <typename T>
-__device__ __forceinline__ floatx4 mfma16(u32x4 a, u32x4 b, floatx4 c) {
-  if constexpr (std::is_same<T, _Float16>::value) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
-  else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-// Activation and storage type of a lane's 8 channels.
-template <typename T>
-__device__ __forceinline__ u32x4 silu8(const floatx4 (&v)[2]) {
-  u32x4 out;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) store4<T>((T*)&out + h * 4, floatx4{silu(v[h][0]), silu(v[h][1]), silu(v[h][2]), silu(v[h][3])});
-  return out;
-}
-
 template <typename T>
 __global__ __launch_bounds__(256, 2) void entry_kernel(const EntryKernelArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char s_in[2][ENTRY_BYTES];
@@ -155,7 +140,7 @@ __global__ __launch_bounds__(256, 2) void entry_kernel(const EntryKernelArgs a) 
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[b] = mfma16<T>(w0[b][s], f[i & 1][s], s == 0 ? b0[b] : acc[b]);
       if (next) read0(i + 1);
-      u32x4 out = silu8<T>(acc);
+      u32x4 out = silu8<T>(acc[0], acc[1]);
       if (!inside) {
         const int Y = 2 * cy - 1 + (at0[i] >> 16), X = 2 * cx - 1 + (at0[i] & 0xFFFF);
         if ((unsigned)Y >= (unsigned)a.H0 || (unsigned)X >= (unsigned)a.W0) out = u32x4{0u, 0u, 0u, 0u};
@@ -178,7 +163,7 @@ __global__ __launch_bounds__(256, 2) void entry_kernel(const EntryKernelArgs a) 
           for (int b = 0; b < 2; ++b) acc[j][b] = mfma16<T>(w1[b][tap], f, tap == 0 ? b1[b] : acc[j][b]);
         }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) *(u32x4*)(s_t1 + wr1[j]) = silu8<T>(acc[j]);
+      for (int j = 0; j < 2; ++j) *(u32x4*)(s_t1 + wr1[j]) = silu8<T>(acc[j][0], acc[j][1]);
     }
     __syncthreads();
 #pragma unroll
@@ -190,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void entry_kernel(const EntryKernelArgs a) 
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[b] = mfma16<T>(w2[b][s], f, s == 0 ? b2[b] : acc[b]);
       }
-      const u32x4 out = silu8<T>(acc);
+      const u32x4 out = silu8<T>(acc[0], acc[1]);
       const int q = (wp * 2 + j) * 16 + r16, Y = cy + (q >> 3), X = cx + (q & 7);
       if (Y < a.H1 && X < a.W1) *(u32x4*)(a.y[wc] + ((size_t)(cur_img * a.H1 + Y) * a.W1 + X) * a.y_pitch[wc] + q4 * 16) = out;
     }

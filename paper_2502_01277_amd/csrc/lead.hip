@@ -25,19 +25,6 @@ struct LeadKernelArgs {
   int n_tiles, grid;
 };
 
-template <typename T>
-__device__ __forceinline__ floatx4 lead_mfma(u32x4 a, u32x4 b, floatx4 c) {
-  if constexpr (std::is_same<T, _Float16>::value) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
-  else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-template <typename T>
-__device__ __forceinline__ u32x4 lead_silu(floatx4 lo, floatx4 hi) {
-  u32x4 out;
-  store4<T>((T*)&out, floatx4{silu(lo[0]), silu(lo[1]), silu(lo[2]), silu(lo[3])});
-  store4<T>((T*)&out + 4, floatx4{silu(hi[0]), silu(hi[1]), silu(hi[2]), silu(hi[3])});
-  return out;
-}
-
 // C: channels of each layer; KS: input channels / 32; NP: blocks of 16 pixels of a tile
 template <typename T, int C, int KS, int NP>
 __global__ __launch_bounds__(C * 4, 1) void lead_kernel(const LeadKernelArgs a) {
@@ -113,9 +100,9 @@ __global__ __launch_bounds__(C * 4, 1) void lead_kernel(const LeadKernelArgs a) 
       for (int s = 0; s < KS; ++s) {
         const u32x4 f = *(const u32x4*)(s_x + (p * XV + ((s * 4 + q4) ^ r16)) * 16);
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[b] = lead_mfma<T>(w0[b][s], f, acc[b]);
+        for (int b = 0; b < 2; ++b) acc[b] = mfma16<T>(w0[b][s], f, acc[b]);
       }
-      const u32x4 o = lead_silu<T>(acc[0], acc[1]);
+      const u32x4 o = silu8<T>(acc[0], acc[1]);
       if (first) *(u32x4*)(s_h + (p * HV + ((c0 >> 3) ^ (p & (HV - 1)))) * 16) = o;
       if (p < cl && y0) *(u32x4*)(y0 + (size_t)(cp + p) * y0_pitch + c0 * 2) = o;
     }
@@ -130,12 +117,12 @@ __global__ __launch_bounds__(C * 4, 1) void lead_kernel(const LeadKernelArgs a) 
       for (int s = 0; s < K2; ++s) {
         const u32x4 f = *(const u32x4*)(s_h + (p * HV + ((s * 4 + q4) ^ (p & (HV - 1)))) * 16);
 #pragma unroll
-        for (int b = 0; b < CB; ++b) acc[b] = lead_mfma<T>(w1[b][s], f, acc[b]);
+        for (int b = 0; b < CB; ++b) acc[b] = mfma16<T>(w1[b][s], f, acc[b]);
       }
       if (p < cl) {
         char* q = a.h + (size_t)(cp + p) * a.h_pitch + c2 * 2;
         if constexpr (CB == 1) store4<T>((T*)q + q4 * 4, floatx4{silu(acc[0][0]), silu(acc[0][1]), silu(acc[0][2]), silu(acc[0][3])});
-        else *(u32x4*)(q + q4 * 16) = lead_silu<T>(acc[0], acc[CB - 1]);
+        else *(u32x4*)(q + q4 * 16) = silu8<T>(acc[0], acc[CB - 1]);
       }
     }
     if (!more) break;

@@ -159,6 +159,21 @@ __device__ __forceinline__ void with_epilogue_mode(int res_mode, bool is_silu, F
   }
 }
 
+// D = A B + C for a block of 16 x 16 and 32 of K, 16-bit types: lane (row or column l % 16, l / 16) supplies 8 consecutive values of K per operand and gets rows 4 (l / 16) .. + 3 of its column.
+template <typename T>
+__device__ __forceinline__ floatx4 mfma16(u32x4 a, u32x4 b, floatx4 c) {
+  if constexpr (std::is_same<T, _Float16>::value) return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), c, 0, 0, 0);
+  else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// SiLU of eight values, in the storage type (16 bits).
+template <typename T>
+__device__ __forceinline__ u32x4 silu8(floatx4 lo, floatx4 hi) {
+  u32x4 out;
+  store4<T>((T*)&out, floatx4{silu(lo[0]), silu(lo[1]), silu(lo[2]), silu(lo[3])});
+  store4<T>((T*)&out + 4, floatx4{silu(hi[0]), silu(hi[1]), silu(hi[2]), silu(hi[3])});
+  return out;
+}
+
 // One vector (8 or 16 bytes) of output pixel p, channels c .., to the 2x upsampled copy of the output.
 template <typename T, typename V>
 __device__ __forceinline__ void store_upsampled(const ConvArgs& a, unsigned p, int c, V val) {
