@@ -49,3 +49,35 @@ def test_frames_and_counters(octo, n, bz):
     cls = spec.models[1]
     want = octo.op_crop_resize(frames, used[2], cls.in_h, cls.in_w, cls.dtype, cap=len(used[2]))[-1].float().cpu().numpy()
     assert np.array_equal(crop[..., :3].reshape(want.shape), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("h,w", [(1080, 1920), (1920, 1080)])
+def test_frames_of_a_launch_with_four_rows_per_lane(octo, dtype, h, w):
+    """64 frames at three times the detector's size, where the first launch takes its rows in groups: borders above and below, and at the sides.  The detector's input and the crops against the stage
+    calls, which read the frames from a table."""
+    import torch
+    n = 64
+    det = zoo.plain_detector("det", dtype, 640, (8, 8, 8), 8, zoo.SEED0 + 5, batch_size=n, topk=100, max_det=100)
+    B = zoo._Builder("child", dtype, 32, 32, "classifier", np.random.default_rng(72))
+    B.m.outputs = [B.fc(B.gap(B.conv(0, 16, 3, 2, act=zoo.ACT_RELU)), 4)]
+    B.m.batch_size = 4 * n
+    spec = zoo.PipelineSpec("rows", [det, B.m], [zoo.Edge(0, 1)], 1000.0, h, w, n, 4)
+    few = torch.randint(0, 256, (3, h, w, 3), dtype=torch.uint8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(8))
+    frames = [few[(i * i) % 3] for i in range(n)]
+    P = octo.Pipeline(spec, keep_all_tensors=2)
+    P.submit(frames)
+    assert P.run() == n
+    P.collect()
+    rois = P.get_rois(0).copy()
+    at = (0, n - 1)                                      # (a copy of short rows is slow: a few items)
+    got = [P.get_tensor(0, 0, 1, first=i) for i in at]
+    assert len(rois) > n
+    crops = P.get_tensor(1, 0, 6, first=len(rois) - 6)
+    P.close()
+    want = octo.op_letterbox([frames[i] for i in at], 640, 640, dtype).float().cpu().numpy()
+    for k in range(len(at)):
+        assert np.array_equal(got[k][..., :3].reshape(want[k].shape), want[k]), at[k]
+    want = octo.op_crop_resize(frames, rois, 32, 32, dtype, cap=len(rois))[-6:].float().cpu().numpy()
+    assert np.array_equal(crops[..., :3].reshape(want.shape), want)

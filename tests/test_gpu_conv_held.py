@@ -33,12 +33,25 @@ CASES = [
 ]
 
 
+def _check(dtype, L, x, y, res, stride, act, res_mode):
+    """The layer's output against sums in 64 bits of its own input.  One rounding to storage (half a unit in the last place), and fp32 sums of K products in parts of at most K / 2: with random signs
+    far below K / 8 roundings of 2^-24 of the sum of the magnitudes."""
+    nchw = lambda t: torch.from_numpy(np.ascontiguousarray(t)).double().permute(0, 3, 1, 2)   # noqa: E731
+    conv = lambda a, b: torch.nn.functional.conv2d(a, b, stride=stride, padding=1).permute(0, 2, 3, 1).numpy()   # noqa: E731
+    s, mag = conv(nchw(x), nchw(L.weight)) + L.bias, conv(nchw(x).abs(), nchw(L.weight).abs())
+    res = res.astype(np.float64) if res_mode else 0.0
+    f = {zoo.ACT_SILU: lambda t: t / (1.0 + np.exp(-t)), zoo.ACT_RELU: lambda t: np.maximum(t, 0.0), zoo.ACT_NONE: lambda t: t}[act]
+    ref = f(s + res) if res_mode == zoo.RES_BEFORE_ACT else f(s) + res
+    half_ulp = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype] * 2
+    bound = half_ulp * np.abs(ref) + (9 * x.shape[3] / 8 + 16) * 2.0 ** -24 * (mag + np.abs(res) + 1.0)
+    err = np.abs(y - ref)
+    assert (err <= bound).all(), (err / bound).max()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("case", CASES)
 def test_parity(octo, dtype, case):
-    """One rounding to storage (half a unit in the last place), and fp32 sums of K products in parts of at most K / 2: with random signs far below K / 8 roundings of
-    2^-24 of the sum of the magnitudes."""
     n, h, w, cin, cout, stride, act, res_mode, want = case
     B = zoo._Builder("t", dtype, h, w, "classifier", np.random.default_rng(17))
     B.ch = [16]
@@ -59,17 +72,35 @@ def test_parity(octo, dtype, case):
         got[keep] = {t: P.get_tensor(1, t, n) for t in ((x, y, B.m.outputs[0]) + ((r,) if r else ()) if keep else (B.m.outputs[0],))}
         P.close()
     assert np.array_equal(got[0][B.m.outputs[0]], got[1][B.m.outputs[0]])
-    nchw = lambda t: torch.from_numpy(np.ascontiguousarray(t)).double().permute(0, 3, 1, 2)   # noqa: E731
-    L = B.m.layers[y - 1]
-    conv = lambda a, b: torch.nn.functional.conv2d(a, b, stride=stride, padding=1).permute(0, 2, 3, 1).numpy()   # noqa: E731
-    s, mag = conv(nchw(got[1][x]), nchw(L.weight)) + L.bias, conv(nchw(got[1][x]).abs(), nchw(L.weight).abs())
-    res = got[1][r].astype(np.float64) if res_mode else 0.0
-    f = {zoo.ACT_SILU: lambda t: t / (1.0 + np.exp(-t)), zoo.ACT_RELU: lambda t: np.maximum(t, 0.0), zoo.ACT_NONE: lambda t: t}[act]
-    ref = f(s + res) if res_mode == zoo.RES_BEFORE_ACT else f(s) + res
-    half_ulp = {"bf16": 2.0 ** -9, "f16": 2.0 ** -12}[dtype] * 2
-    bound = half_ulp * np.abs(ref) + (9 * cin / 8 + 16) * 2.0 ** -24 * (mag + np.abs(res) + 1.0)
-    err = np.abs(got[1][y] - ref)
-    assert (err <= bound).all(), (err / bound).max()
+    _check(dtype, B.m.layers[y - 1], got[1][x], got[1][y], got[1][r] if res_mode else None, stride, act, res_mode)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,h,w,c,cout,stride,want", [(1, 20, 20, 256, 256, 1, T32), (8, 20, 21, 256, 256, 1, T64), (9, 41, 39, 192, 192, 1, T128), (3, 40, 40, 256, 192, 2, S32),
+                                                      (27, 16, 15, 256, 512, 2, S64)])
+def test_channel_slices_of_wider_tensors(octo, dtype, n, h, w, c, cout, stride, want):
+    """Input, residual and output each in the channels behind others of a concatenation: pitches and first channels of their own."""
+    B = zoo._Builder("t", dtype, h, w, "classifier", np.random.default_rng(19))
+    B.ch = [16]
+    B.m.in_c = 16
+    x = B.conv(0, c, 1, 1, act=zoo.ACT_RELU)
+    r = B.conv(0, cout, 1, stride, act=zoo.ACT_NONE)
+    y = B.conv(x, cout, 3, stride, act=zoo.ACT_SILU, res=r, res_mode=zoo.RES_BEFORE_ACT)
+    wide_x = B.cat([B.conv(0, 72, 1, 1, act=zoo.ACT_NONE), x])
+    wide_r = B.cat([B.conv(0, 40, 1, stride, act=zoo.ACT_NONE), r])
+    wide_y = B.cat([B.conv(0, 24, 1, stride, act=zoo.ACT_NONE), y])
+    B.m.outputs = [B.fc(B.gap(B.cat([B.conv(wide_x, 64, 1, stride), B.conv(wide_r, 64, 1), B.conv(wide_y, 64, 1)])), 8)]
+    B.m.batch_size = n
+    v = zoo.round_to_dtype(np.random.default_rng(20).uniform(-1, 1, (n, h, w, 16)).astype(np.float32), dtype)
+    P = octo.Pipeline(zoo.PipelineSpec("t", [small_root(dtype), B.m], [], 200.0, 32, 32, 1, 1), keep_all_tensors=1)
+    P.run_model_on(1, octo.to_device(v, dtype))
+    assert int(P.layer_info(1)[1][y - 1]) == want
+    got = {t: P.get_tensor(1, t, n) for t in (x, r, y, wide_x, wide_r, wide_y)}
+    P.close()
+    for t, wide, first in ((x, wide_x, 72), (r, wide_r, 40), (y, wide_y, 24)):
+        assert np.array_equal(got[t], got[wide][..., first:])
+    _check(dtype, B.m.layers[y - 1], got[x], got[y], got[r], stride, zoo.ACT_SILU, zoo.RES_BEFORE_ACT)
 
 
 @pytest.mark.gpu
