@@ -80,8 +80,8 @@ def conv_name(kid: int, dtype: str) -> str:
         bc, bp, mode = kid // 1000 % 1000, kid % 1000, kid // 10**6 % 2
         wc = {(32, 64): 1, (128, 64): 4}.get((bc, bp), 2)
         return "octo::conv_small_group_kernel<%s, %d, %d, %d, %d, %d, %d>" % ((ctype, bc, bp, wc) + SMALL[(bc, bp)] + (mode,)) if (bc, bp) in SMALL else "convolution kernel %d" % kid
-    if kid == 2110000000:                                # a cross-stage block of 32 channels in one launch, with a shortcut as the detectors have it
-        return "octo::block_kernel<%s, true>" % ctype
+    if kid // 10**7 == 211:                              # a cross-stage block of 32 channels in one launch
+        return "octo::block_kernel<%s, %s>" % (ctype, "false" if kid % 10 else "true")
     if d >= 1000000000:                                  # 3x3 layers of few tiles, patch of all channels in LDS: digits S K BBB PPP
         s, ks, bc, bp = d // 10000000 % 10, d // 1000000 % 10, d // 1000 % 1000, d % 1000
         return "octo::conv3x3_held_kernel<%s, %d, %d, %d, %d>" % (ctype, bc // 32, bp * ks // 128, ks, s)

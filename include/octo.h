@@ -406,7 +406,7 @@ octo_status octo_profile_layers(octo_pipeline* p, int32_t model, int32_t n, int3
  * (two slices), Q = 5 for the form with resident weights; 19 0F BBB KK P: first-layer kernel, channel tile, kernel height, kernel width in pixel pairs,
  * F = 1 when it also computes the 3x3 / stride-2 max-pool that follows (that layer then reports kernel 0 and 0 ms); 20 S K BBB PPP: 3x3
  * kernel with the patch of the whole reduction in LDS, stride S, wavefronts that share K, channel tile, pixel tile; several layers in one launch: 2100000000 the first
- * layers of a detector, 2110000000 a cross-stage block of 32 channels, 212 P BBB KKK the entry of a cross-stage block, P blocks of 16 pixels, BBB channels a layer, KKK
+ * layers of a detector, 2110000000 a cross-stage block of 32 channels, 2110000001 one without a shortcut, 212 P BBB KKK the entry of a cross-stage block, P blocks of 16 pixels, BBB channels a layer, KKK
  * input channels, 213 G BBB PPP layers that do not depend on one another, G / 2 of them (odd: windows or strides), in tiles of BBB channels x PPP pixels;
  * 1 max-pool, 2 upsample, 3 channel copy, 4 add, 5 global average pool, 0 none), per ITEM dense FLOPs and activation
  * bytes (input, output and residual elements), and per LAUNCH weight and bias bytes.  When two 1x1 convolutions of

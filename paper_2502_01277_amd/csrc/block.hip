@@ -172,7 +172,7 @@ hipError_t launch_block(int dtype, const BlockArgs& a, int num_cu, hipStream_t s
   k.n_tiles = (int)tiles;
   k.div_tx = make_fastdiv((unsigned)k.tiles_x); k.div_ty = make_fastdiv((unsigned)tiles_y);
   k.grid = (int)std::min((tiles + 7) / 8 * 8, ((long long)num_cu * 2 + 7) / 8 * 8);
-  if (kernel_id) *kernel_id = KID_BLOCK;
+  if (kernel_id) *kernel_id = block_kernel_id(a.shortcut);
   auto go = [&](auto kernel) {
     if (tm.start && tm.stop) hipExtLaunchKernelGGL(kernel, dim3((unsigned)k.grid), dim3(256), 0, s, tm.start, tm.stop, 0, k);
     else hipLaunchKernelGGL(kernel, dim3((unsigned)k.grid), dim3(256), 0, s, k);

@@ -47,8 +47,9 @@ constexpr int stem_kernel_id(int bc, int kh, int pkw, bool pool) { return 190000
 
 // the first layers of a detector in one launch (entry.hip)
 constexpr int KID_ENTRY = 2100000000;
-// a cross-stage block of 32 channels in one launch (block.hip)
-constexpr int KID_BLOCK = 2110000000;
+// a cross-stage block of 32 channels in one launch (block.hip), last digit 1: without a shortcut
+constexpr int block_kernel_id(bool shortcut) { return 2110000000 + (shortcut ? 0 : 1); }
+constexpr bool is_block(int id) { return id / 10000000 == 211; }
 // the entry of a cross-stage block in one launch (lead.hip), digits 212 P BBB KKK: pixel tile / 16, channels of a layer, input channels
 constexpr int lead_kernel_id(int c, int cin, int np) { return 2120000000 + np * 1000000 + c * 1000 + cin; }
 constexpr bool is_lead(int id) { return id / 10000000 == 212; }

@@ -1621,7 +1621,7 @@ static bool fused_work(const ModelPlan& m, int i, double* flops, double* bytes, 
   for (int b = std::max(0, i - 3); b <= i; ++b) {
     const LayerPlan* L = m.layers.data() + b;
     const bool entry = L[0].fuse_entry && L[0].kernel_id == KID_ENTRY;
-    if (!entry && !(L[0].fuse_block && L[0].kernel_id == KID_BLOCK)) continue;
+    if (!entry && !(L[0].fuse_block && is_block(L[0].kernel_id))) continue;
     const bool first = b == i;
     if (flops) *flops = first ? L[0].flops + L[1].flops + L[2].flops + L[3].flops : 0.0;
     if (weight_bytes) *weight_bytes = first ? L[0].weight_bytes + L[1].weight_bytes + L[2].weight_bytes + L[3].weight_bytes : 0.0;
