@@ -3,10 +3,11 @@
 //
 // Three launches moved 15 MB a frame of 160 x 160 for 420 MFLOP, of which the block's inputs and its output are 6.6.  Here a workgroup takes 16 x 8 pixels at a time.  Layers of 1x1 need no
 // LDS: a lane's 16 bytes of a pixel are its operand of a block of 16 x 16 x 32, and with the rows of the weights permuted its 8 results are consecutive channels of that pixel - the
-// operand of the next 1x1 layer as they are.  Only the 3x3 layer's input, 18 x 10 pixels, goes through LDS (vector v of pixel p in slot v ^ (p / 4) % 4: no two
-// lanes of a read on one bank; two buffers, one barrier per tile).  All weights and biases are in registers for the workgroup's lifetime, sums start from the bias, and the next tile's
+// operand of the next 1x1 layer as they are.  Only the 3x3 layer's input, 18 x 10 pixels, goes through LDS (vector v of pixel p in slot v ^ (p / 4) % 4; two
+// buffers, one barrier per tile).  All weights and biases are in registers for the workgroup's lifetime, sums start from the bias, and the next tile's
 // pixels are asked for a tile ahead.
-// What bounds it: issue slots, half of them the exponential and the reciprocal of 72 activations a lane and tile, and the memory traffic of its tensors (420 MB in 121 us, 3.5 TB/s).
+// What bounds it, by counters on 64 frames (122 us): issue and memory together.  The vector units are active in half of the cycles (two fifths of that the exponential and the reciprocal of 72
+// activations a lane and tile), the matrix pipe in 17 %, LDS in 13 % - 47 % of that conflicts of banks, which the slots do not prevent -, and its tensors move at 3.5 TB/s (420 MB).
 // Before, the three launches, and after, us: 1 frame 13.5 -> 8.3, 5 28.4 -> 16.7, 8 40.5 -> 23.0, 16 58.8 -> 36.5, 64 200 -> 121 (130 with stores of 32 bytes of a pixel and the other half
 // asked for at the start of its own tile).
 #include "octo_internal.h"

@@ -10,7 +10,8 @@
 //     fetched twice by a workgroup, and takes 64 x 32 or 64 x 64 results of it, half an LDS read per matrix instruction.  Partial sums meet in LDS, in fp32.
 // A tile is TH x TW output pixels of the image stack (see conv3x3_mid.h), its patch in slices of 64 channels; pixel p keeps vector v of a slice in slot
 // v ^ (p / 2) % 8, p counted without the halo columns at stride 1; taps outside the image read a row of zeros.
-// What bounds it: start, first trip to memory and drain (about 4 us), then the weights, which every pixel tile reads once, at about 50 bytes per clock and compute unit.  Before (the
+// What bounds it: start, first trip to memory and drain (about 4 us), then the time that loads take from the L2: every pixel tile reads its weights once, with the patch some 16 bytes per clock and
+// compute unit (counters; a stream of loads alone reaches 54).  Wavefronts wait in 27 - 56 % of their cycles, the matrix pipe is busy in 9 - 32 % of a launch.  Before (the
 // fastest kernel that could take the layer) and after, us, in place in a model: 512 -> 512 on 11 x 7 x 7 14.3 -> 9.6, on 63 x 7 x 7 26.5 -> 20.0 (735 TFLOP/s); 256 -> 256 on
 // 4 x 20 x 20 12.1 -> 7.1, on 8 x 20 x 20 15.6 -> 9.0, on 11 x 14 x 14 10.3 -> 7.8; 384 -> 384 on 40 x 40 19.7 -> 11.5; 128 -> 128 on 40 x 40 5.6 -> 5.1, on 8 x 40 x 40 9.6 ->
 // 8.3; stride 2: 256 -> 512 on 15 x 14 x 14 9.2 -> 7.3, 256 -> 256 on 8 x 40 x 40 14.5 -> 9.9.

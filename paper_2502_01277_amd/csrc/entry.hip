@@ -6,9 +6,10 @@
 // first layer's 17 x 17 and the second's 8 x 8 pixels stay there.  All weights and biases are in registers for the workgroup's lifetime.  13 % of the first layer is computed twice.
 // Blocks of 16 x 16 x 32, a block's rows permuted so that a lane gets 8 consecutive channels of its pixel: one LDS write or store per block.  The first layer's pixels
 // lie in LDS by parity of their column, even ones first, so that the stride-2 taps of 8 neighbouring pixels read neighbours; vector v of pixel p in slot v ^ (p / 4) % 4,
-// of the second layer's in v ^ (p / 2) % 8: no two lanes of a read on one bank.
-// What bounds it: issue slots, more than half of them the exponential and the reciprocal of 72 activations a lane and tile (32 of 44 cycles each); sums start from the bias, which saves
-// an addition each (252 -> 235 us on 64 frames with that and the next block's operands read ahead of a block's activations).  Before, the three launches, and after, us: 1 frame 21.0 ->
+// of the second layer's in v ^ (p / 2) % 8.
+// What bounds it, by counters on 64 frames (223 us): issue.  The vector units are active in 56 % of the cycles (two fifths of that the exponential and the reciprocal of 72 activations a lane
+// and tile), the matrix pipe in 29 %, LDS in 35 % - 45 % of that conflicts of banks, which the slots do not prevent -, and an instruction of some kind is under way in 74 %.  Sums start from the
+// bias, which saves an addition each (252 -> 235 us on 64 frames with that and the next block's operands read ahead of a block's activations).  Before, the three launches, and after, us: 1 frame 21.0 ->
 // 14.5, 5 42.5 -> 29.2, 8 57.5 -> 37.6, 16 109 -> 62, 64 399 -> 235.
 #include "octo_internal.h"
 #include "mfma_common.h"
