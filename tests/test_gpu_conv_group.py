@@ -129,8 +129,8 @@ def test_with_the_count_on_the_device(octo, dtype):
             tensors = [t for g in members for t in g] + B.m.outputs
             got[keep].append([n] + [P.get_tensor(1, t, n) if n else None for t in tensors])
             after = [P.get_tensor(1, t, 3, first=60) for t in tensors]
-            if behind is not None and n < 60:
-                assert all(np.array_equal(p, q) for p, q in zip(behind, after))
+            if behind is not None and n < 60:            # (before the large batch: whatever the memory held, NaN too)
+                assert all(np.array_equal(p, q, equal_nan=True) for p, q in zip(behind, after)), k
             behind = after
         P.close()
     counts = [b[0] for b in got[1]]
