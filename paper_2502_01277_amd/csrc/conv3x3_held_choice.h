@@ -66,6 +66,13 @@ inline HeldPlan held_plan(int S, int W, int Ho, int Wo, int cin, int cout) {
   p.div_ho = make_fastdiv((unsigned)Ho); p.div_tc = make_fastdiv((unsigned)(cout / 64));
   return p;
 }
+// Can any launch of the layer, whatever its number of items and the device, go to the kernel (held_choose)?  Where none can, no second copy of its weights is kept.
+inline bool held_ever(const HeldPlan& p, int stride, int cin) {
+  if (stride == 2 && cin < 128) return false;
+  bool any = false;
+  for (int i = 0; i < (stride == 1 ? 3 : cin < 256 ? 1 : 2); ++i) any = any || p.geom[i].rows > 0;
+  return any;
+}
 
 // Weights in the order that the kernel reads them: for every block of 32 output channels, group of 16 input channels and tap the 1 KB of one wavefront's operand.
 // Lane l holds channel 16 ((m / 4) % 2) + 4 (m / 8) + m % 4 of the block, m = l % 32, and input channels 8 (l / 32) .. 8 (l / 32) + 7 of the group; with that order of

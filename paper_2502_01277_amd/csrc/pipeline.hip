@@ -590,6 +590,11 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
     lp.d_weight = ar.alloc(elems * es + 512);   // slack: the conv prefetch may read a K step past the last row
     lp.d_bias = (float*)ar.alloc((size_t)lp.cout_pad * sizeof(float));
     lp.held = es == 2 && lp.L.op == OCTO_CONV && !lp.pair_view && held_layer(lp.L.kh, lp.L.kw, lp.L.stride, lp.L.pad, m.tensors[lp.L.in[0]].h, lp.cin, lp.L.cout);
+    if (lp.held) {
+      const TensorPlan &tx = m.tensors[lp.L.in[0]], &ty = m.tensors[li + 1];
+      lp.held_plan = held_plan(lp.L.stride, tx.w, ty.h, ty.w, lp.cin, lp.L.cout);
+      lp.held = held_ever(lp.held_plan, lp.L.stride, lp.cin);
+    }
     void* d_held = lp.held ? ar.alloc(held_weight_bytes(lp.L.cout, lp.cin)) : nullptr;
     size_t twin_elems = 0;
     int& twin_kp = lp.twin_kp;
@@ -619,8 +624,6 @@ octo_status pack_weights(octo_pipeline* p, ModelPlan& m, Arena& ar) {
     }
     HIPCHK(p, hipMemcpy(lp.d_weight, host.data(), host.size(), hipMemcpyHostToDevice));
     if (lp.held) {
-      const TensorPlan &tx = m.tensors[lp.L.in[0]], &ty = m.tensors[li + 1];
-      lp.held_plan = held_plan(lp.L.stride, tx.w, ty.h, ty.w, lp.cin, lp.L.cout);
       lp.held_plan.w = d_held;
       HIPCHK(p, launch_held_pack(lp.d_weight, lp.Kp, lp.cin, lp.L.cout, d_held, nullptr));
     }

@@ -1,11 +1,15 @@
 """The host side of conv3x3_held_kernel, without a GPU: the geometry of its tiles over random maps - where the loader puts every input pixel of a patch and where
 a tap reads it -, and the lines of its rule on both sides."""
+import ctypes as C
 import random
 import subprocess
 
+import numpy as np
 import pytest
 
 import dispatch
+from helpers import small_root
+from paper_2502_01277_amd import binding, zoo
 
 SOURCE = r'''
 #include "csrc/conv3x3_held_choice.h"
@@ -94,7 +98,7 @@ def test_both_sides_of_the_lines(ask):
         ((4, 20, 20, 256, 256, 1, 0, 0, 0), 0), ((8, 20, 20, 256, 256, 1, 0, 0, 0), 1), ((16, 20, 20, 256, 256, 1, 0, 0, 0), 2),
         ((32, 20, 20, 256, 256, 1, 0, 0, 0), -1),                                       # more than are resident
         ((63, 7, 7, 512, 512, 1, 0, 0, 0), 2), ((134, 7, 7, 512, 512, 1, 0, 0, 0), -1),
-        ((48, 40, 40, 128, 128, 1, 0, 0, 0), 2), ((52, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # five per compute unit
+        ((48, 40, 40, 128, 128, 1, 0, 0, 0), 2), ((52, 40, 40, 128, 128, 1, 0, 0, 0), -1), ((64, 40, 40, 128, 128, 1, 0, 0, 0), -1),      # five per compute unit
         ((8, 80, 80, 192, 192, 1, 0, 0, 0), 2), ((9, 80, 80, 192, 192, 1, 0, 0, 0), -1), ((10, 80, 80, 192, 192, 1, 0, 0, 0), -1),
         ((480, 40, 40, 128, 128, 1, 0, 48, 48), -1), ((480, 40, 40, 128, 128, 1, 0, 12, 12), 2), ((480, 14, 14, 256, 256, 1, 0, 41, 41), 2),
         ((5, 80, 80, 64, 64, 1, 0, 0, 0), -1), ((6, 80, 80, 64, 64, 1, 0, 0, 0), 2), ((12, 80, 80, 64, 64, 1, 0, 0, 0), -1),
@@ -129,3 +133,24 @@ def test_no_hole_between_the_lines(ask):
     for h, ci, top in ((40, 128, 51), (80, 192, 8), (20, 256, 20), (40, 384, 3)):
         taken = [t >= 0 for _, t, _ in ask([(n, h, h, ci, ci, 1, 0, 0, 0) for n in range(1, 80)])]
         assert taken.index(False) == top and not any(taken[top:]), (h, ci, taken.index(False))
+
+
+@pytest.mark.parametrize("stride,cin,cout,h,kept", [(2, 64, 128, 40, False), (1, 64, 128, 40, True), (2, 128, 128, 40, True), (1, 64, 64, 3, False), (1, 512, 64, 131, True), (2, 512, 64, 20, True)])
+def test_weights_are_kept_twice_only_where_a_launch_can_read_them(ask, stride, cin, cout, h, kept):
+    """A model's device memory with a layer of padding 1 against the same of padding 0, which has smaller tensors and is never kept twice."""
+    size = []
+    for pad in (0, 1):
+        B = zoo._Builder("t", "bf16", h, h, "classifier", np.random.default_rng(1))
+        B.ch = [cin]
+        B.m.in_c = cin
+        B.m.outputs = [B.fc(B.gap(B.conv(0, cout, 3, stride, p=pad)), 8)]
+        B.m.batch_size = 1
+        keep, n = [], C.c_size_t()
+        d = binding.pipeline_desc(zoo.PipelineSpec("t", [small_root("bf16"), B.m], [], 200.0, 32, 32, 1, 1), keep)
+        assert binding.lib().octo_pipeline_workspace_size(C.byref(d), C.byref(n)) == binding.OK
+        size.append(n.value)
+    copy, tensors = 18 * cin * cout, 2 * cout * (((h - 1) // stride + 1) ** 2 - ((h - 3) // stride + 1) ** 2)
+    assert tensors + 1024 < copy and (size[1] - size[0] >= copy) == kept and size[1] - size[0] <= copy * kept + tensors + 1024
+    # and no launch of a layer without the copy would be taken
+    taken = any(t >= 0 for _, t, _ in ask([(n, h, h, cin, cout, stride, 0, 0, 0) for n in range(1, 200)]))
+    assert taken == kept
