@@ -13,7 +13,8 @@ CASES = [
     (8, 81, 79, [(128, 1, 1, False, None, None, False), (128, 1, 1, False, 13, 12, True), (256, 1, 1, False, 13, 12, True), (64, 1, 1, False, 13, 12, True)]),
     (8, 160, 161, [(32, 1, 1, False, None, None, False), (64, 3, 2, False, 13, 12, True)]),            # steps across taps
     (4, 81, 79, [(96, 1, 1, False, None, None, False), (120, 1, 1, False, 13, 15, True), (120, 1, 1, True, 13, 15, True), (128, 1, 1, False, 13, 15, True)]),          # steps of part of 64 channels
-    (13, 41, 40, [(128, 1, 1, False, None, None, False), (128, 3, 1, False, 17, 17, False), (128, 3, 1, True, 17, 17, False)]),      # slices of 64 : 32 channels
+    (13, 41, 40, [(128, 1, 1, False, None, None, False), (128, 3, 1, False, 20, 17, False), (128, 3, 1, True, 20, 17, False)]),      # the whole patch in LDS : slices of 32 channels
+    (13, 41, 40, [(128, 1, 1, False, None, None, False), (120, 3, 1, False, 17, 17, False)]),                                          # slices of 64 : 32 channels
     (8, 161, 160, [(64, 1, 1, False, None, None, False), (64, 1, 1, False, 13, 15, True), (64, 1, 1, True, 13, 15, True), (64, 3, 1, False, 18, 18, False),
                     (32, 1, 1, False, 13, 15, True)]),                          # resident weights alone
     (1, 7, 7, [(1024, 1, 1, False, None, None, False), (512, 1, 1, False, None, None, True)]),                                          # split-K or not, in both
