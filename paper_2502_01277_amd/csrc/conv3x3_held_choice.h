@@ -100,21 +100,27 @@ inline double held_cost_us(const ConvArgs& a, long long items, int which, int nu
   return c[0] + c[1] * k + per_cu * (c[2] * k + c[3] + c[4] * k * a.held->geom[which].rows / 32) + c[5] * mb;
 }
 // Where the count is taken on the device the choice is made for the stated one, so that an item's results do not depend on its neighbours' number, and the running count may be many times that.
-// A kernel of the common order follows it with larger tiles, this one cannot; so it takes such a layer only where it is ahead at any count: in place of kernels that are tied
-// to the stated count themselves, split-K and the narrow tiles of conv3x3_mid_kernel.  Us, the kernel before : this one, by tiles of 64 x 64 per compute unit at the stated count.
-//   * 512 channels, while resident: 7 x 7 at 1.5, stated 64, 59 items 26.0 : 19.0, 455 122 : 97, 843 217 : 183; at 1.95, stated 80, 78 items 27.2 : 18.4, 571 110 : 116, 1074 215 : 228, so
-//     from 1.7 on only where no more than 16 times the stated count has room;
-//   * 128 .. 448 up to 2.5: 256 -> 256 on 14 x 14 at 2.3, stated 48, 42 items 17.4 : 17.3, 344 73.9 : 74.5, 656 132 : 133, at 3.1, 59 items 18.5 : 17.9, 843 172 : 180; 128 -> 128 on 28 x 28 at
-//     2.3, 22 items 13.3 : 12.8, 177 45.8 : 44.9, 331 78.8 : 81.2, at 3.8, 33 items 13.3 : 12.4, 294 67.2 : 74.2, 542 113 : 135;
+// A kernel of the common order follows it with larger tiles, this one cannot.  Where the capacity is no more than eight times the stated count a layer goes by that like any other: up to about three
+// times it this kernel is ahead, at most five behind by little.  Us in place, the kernel before : this one, items: 16 x 8 x 256, stated 128, 58 15.9 : 11.4, 116 18.3 : 18.0, 177 26.4 : 25.0, 336
+// 47.3 : 48.4, 883 110 : 110; 14 x 14 x 256, stated 64, 32 15.0 : 11.0, 64 17.6 : 17.5, 191 43.0 : 41.9, 478 101 : 100; 28 x 28 x 128, stated 32, 24 12.0 : 11.7, 70 22.3 : 21.0, 183 46 : 43.6, 242 60 : 60;
+// 32 x 16 x 128, stated 64, 32 12.4 : 8.9, 64 14.7 : 13.1, 191 30.8 : 30.9, 478 61 : 72; 8 x 8, stride 2, 128 -> 256, stated 64, 64 7.1 : 6.3, 191 10.3 : 8.7, 478 11.2 : 11.4.
+// With more room than that only where it is about even at fourteen times the stated count too: in place of kernels that are tied to the stated count themselves, split-K and the narrow tiles of
+// conv3x3_mid_kernel.  By tiles of 64 x 64 per compute unit at the stated count:
+//   * 512 channels up to 1.7, 256 .. 448 up to 2.5: 7 x 7 x 512 at 1.5, stated 64, 59 items 26.0 : 19.0, 455 122 : 97, 843 217 : 183, at 1.95, stated 80, 78 items 27.2 : 18.4, 571 110 : 116, 1074
+//     215 : 228; 14 x 14 x 256 at 2.3, stated 48, 42 items 17.4 : 17.3, 344 73.9 : 74.5, 656 132 : 133, at 3.1, stated 64, 32 items 15 : 11, 59 18.5 : 17.9, 843 172 : 180.  Beyond, where it loses
+//     some 5 % at many times the stated count and gains up to a third at less than it, while no more than 32 times that count has room: passes of 10 frames with 200 items each at most and 4 or
+//     8 there 903 : 869 and 1047 : 1016, of 9 with 300 and 109 there 7520 : 7580;
+//   * 128 and 192 up to 2.5: 28 x 28 at 2.3, 22 items 13.3 : 12.8, 177 45.8 : 44.9, 331 78.8 : 81.2, at 3.8, 33 items 13.3 : 12.4, 294 67.2 : 74.2, 542 113 : 135;
 //   * not with 64: 56 x 56, stated 16, 19 items 11.1 : 10.5, 71 23.5 : 25.2, 228 66.8 : 72.9;
 //   * stride 2, in place of split-K only: 256 -> 512 on 14 x 14 at 0.22, stated 8, 6 items 7.2 : 6.9, 111 38.3 : 23.3, at 0.7, stated 24, 22 items 10.4 : 9.0, 57 13.3 : 15.6, 331 50.4 : 62.4,
 //     stated 40, 542 65 : 104; 512 -> 512 on 16 x 8 at 0.5, stated 32, 27 items 18.3 : 14.0, 240 72.8 : 76.1; 128 -> 256 on 8 x 8, stated 128, 118 items 8.1 : 6.5, 923 16.5 : 20.4.
 inline bool held_counted(const ConvArgs& a, long long M, int num_cu) {
   const double per_cu = (double)((M + 63) / 64 * (a.Cout / 64)) / num_cu;
+  const long long room = (long long)a.n * a.Ho * a.Wo;
+  if (M * 8 >= room) return true;
   if (a.stride_h == 2) return a.Cin >= 256 && per_cu <= (a.Cin >= 512 ? 0.5 : 0.25);
-  if (a.Cin < 128) return false;
-  if (a.Cin < 512) return per_cu <= 2.5;
-  return per_cu <= 1.7 || M * 16 >= (long long)a.n * a.Ho * a.Wo;
+  if (a.Cin < 256) return a.Cin >= 128 && per_cu <= 2.5;
+  return per_cu <= (a.Cin >= 512 ? 1.7 : 2.5) || M * 32 >= room;
 }
 // The tile of a layer with M output pixels, or -1 where another kernel is the faster one.  Measured in place, the kernels before : this one, us, by tiles of 64 x 64 per
 // compute unit.  A launch is taken

@@ -111,14 +111,17 @@ def test_both_sides_of_the_lines(ask):
 
 
 def test_a_count_on_the_device_may_be_many_times_the_stated_one(ask):
-    """(Stated count, capacity, map, channels, stride): layers of downstream classifiers whose running count is 14 times the stated one, on both sides of the lines."""
+    """(Stated count, capacity, map, channels, stride): layers of downstream classifiers whose running count may be many times the stated one, on both sides of the lines."""
     cases = [
         ((40, 1500, 14, 256, 512, 2), False), ((24, 900, 14, 256, 512, 2), False), ((8, 300, 14, 256, 512, 2), True),          # 65 : 104 us, 50 : 62, 38 : 23
-        ((32, 256, 8, 512, 512, 2), True), ((72, 256, 8, 512, 512, 2), False), ((64, 512, 8, 128, 256, 2), False),
+        ((32, 1200, 8, 512, 512, 2), True), ((72, 2700, 8, 512, 512, 2), False), ((128, 4800, 8, 128, 256, 2), False),
         ((16, 600, 56, 64, 64, 1), False), ((32, 1200, 56, 64, 64, 1), False),                                                   # 67 : 73
         ((24, 900, 28, 128, 128, 1), True), ((32, 1200, 28, 128, 128, 1), False), ((40, 1500, 28, 128, 128, 1), False),         # 79 : 81, 98 : 106, 113 : 135
-        ((48, 1800, 14, 256, 256, 1), True), ((64, 2400, 14, 256, 256, 1), False), ((72, 2700, 14, 256, 256, 1), False),        # 132 : 133, 172 : 180, 200 : 210
-        ((64, 2400, 7, 512, 512, 1), True), ((72, 2700, 7, 512, 512, 1), False), ((72, 576, 7, 512, 512, 1), True)]             # 217 : 183, 186 : 199, and at 7 times 110 : 116
+        ((48, 1800, 14, 256, 256, 1), True), ((64, 2400, 14, 256, 256, 1), False), ((64, 2048, 14, 256, 256, 1), True),         # 132 : 133, 172 : 180; no room for more than 32 times
+        ((64, 2400, 7, 512, 512, 1), True), ((72, 2700, 7, 512, 512, 1), False), ((80, 2560, 7, 512, 512, 1), True), ((80, 2561, 7, 512, 512, 1), False),      # 217 : 183, 215 : 228
+        # no room for more than eight times the stated count: as with a count that the host knows
+        ((64, 512, 8, 128, 256, 2), True), ((64, 513, 8, 128, 256, 2), False), ((32, 256, 28, 128, 128, 1), True), ((32, 257, 28, 128, 128, 1), False),
+        ((16, 128, 56, 64, 64, 1), True), ((16, 129, 56, 64, 64, 1), False)]
     got = ask([(cap, hw, hw, ci, co, s, 0, stated, h) for (stated, cap, hw, ci, co, s), _ in cases for h in (0, min(cap, 14 * stated))])
     taken = [t >= 0 for _, t, _ in got]
     assert taken[::2] == taken[1::2]                       # a matter of the stated count alone
