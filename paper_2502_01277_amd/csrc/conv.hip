@@ -42,7 +42,7 @@ namespace octo {
 // vmcnt waits whose counts rely on every wave issuing the same number of loads per K step.  M0 is reserved by the
 // compiler (it writes M0 immediately before each of its own uses), so setting it inside the asm statement is safe.
 template <typename T, int BC, int BP, int WC, int WP, int KV, int D, int MINB, bool VEC, bool DMA = false, bool PIPE = false>
-__global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvArgs a) {
+__global__ __launch_bounds__(THREADS, MINB) void conv_mfma_kernel(const ConvKernelArgs a) {
   using E = Elem<T>;
   constexpr int VN = E::N;
   constexpr int ES = (int)sizeof(T);

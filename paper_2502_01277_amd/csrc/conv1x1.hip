@@ -32,7 +32,7 @@ struct StreamGeom {
 __device__ __forceinline__ int row_channel(int m) { return 16 * ((m >> 2) & 1) + 4 * (m >> 3) + (m & 3); }
 
 template <typename T, int TC>
-__global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvArgs a, const StreamGeom gm) {
+__global__ __launch_bounds__(512) void conv1x1_stream_kernel(const ConvKernelArgs a, const StreamGeom gm) {
   using E = Elem<T>;
   static_assert(sizeof(T) == 2, "16-bit storage types");
   constexpr int BC = 32 * TC;

@@ -99,7 +99,7 @@ __device__ __forceinline__ u32x4 mid_load_pieces(const T* p, int n) {
 // BC x BP: tile; WC: wavefronts along the channels (4 / WC along the pixels); KV: vectors of 16 bytes per LDS row; NST: stages
 // of the weight ring; MAXP: passes of the 256 loader lanes that cover a patch buffer; MINB: workgroups per compute unit.
 template <typename T, int BC, int BP, int WC, int KV, int NST, int MAXP, int MINB>
-__global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvArgs a, const MidGeom gm) {
+__global__ __launch_bounds__(THREADS, MINB) void conv3x3_mid_kernel(const ConvKernelArgs a, const MidGeom gm) {
   using E = Elem<T>;
   constexpr int VN = E::N, ES = (int)sizeof(T), BK = KV * VN;
   constexpr int WP = 4 / WC, TC = BC / WC / 32, TP = BP / WP / 32;

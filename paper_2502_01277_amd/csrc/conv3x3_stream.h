@@ -29,7 +29,7 @@ struct Stream3Geom {
 // of the input; KV: 16-byte vectors per patch row; MAXP: passes of the loader lanes that cover a patch; PD: depth of the ring of
 // pixel fragments.
 template <typename T, int WC, int KC, int KV, int MAXP, int PD, int MINB>
-__global__ __launch_bounds__(THREADS, MINB) void conv3x3_stream_kernel(const ConvArgs a, const Stream3Geom gm) {
+__global__ __launch_bounds__(THREADS, MINB) void conv3x3_stream_kernel(const ConvKernelArgs a, const Stream3Geom gm) {
   using E = Elem<T>;
   constexpr int VN = 8, ES = 2, TP = 2, NTAP = 9, NT = THREADS;
   constexpr int RPW = 16 / KV, RP = NT / KV, ROW = KV * 16, PATCH = MAXP * NT * 16;

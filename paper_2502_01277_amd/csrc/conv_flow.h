@@ -44,7 +44,7 @@ constexpr int flow_resident(int es, int NT, int BC, int BP, int KV, int NST, int
 // NT: lanes; BC x BP: tile; WC: wavefronts along the channels (NT / 64 / WC along the pixels); KV: vectors of 16 bytes per LDS row and
 // K step; NST: stages of the ring; MINB: workgroups per compute unit, where the LDS holds them.
 template <typename T, int NT, int BC, int BP, int WC, int KV, int NST, int MINB, int MODE>
-__global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, MINB) * NT / 256) void conv_flow_kernel(const ConvArgs a, const FlowGeom gm) {
+__global__ __launch_bounds__(NT, flow_resident(sizeof(T), NT, BC, BP, KV, NST, MINB) * NT / 256) void conv_flow_kernel(const ConvKernelArgs a, const FlowGeom gm) {
   using E = Elem<T>;
   constexpr int VN = E::N, ES = (int)sizeof(T), BK = KV * VN;
   constexpr bool PW = MODE == FLOW_POINTWISE;

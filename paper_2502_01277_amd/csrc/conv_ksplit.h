@@ -30,7 +30,7 @@ constexpr int ksplit_region(int tc, int tp) {
 }
 
 template <typename T, int TC, int TP, int NW, int KS>
-__global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(const ConvArgs a, const int c_outer) {
+__global__ __launch_bounds__(64 * NW) void conv_ksplit_kernel(const ConvKernelArgs a, const int c_outer) {
   using E = Elem<T>;
   constexpr int VN = E::N, ES = (int)sizeof(T);
   constexpr int KV = 8, BK = KV * VN;                    // a K step: eight 16-byte vectors per row

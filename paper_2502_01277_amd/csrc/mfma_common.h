@@ -176,7 +176,7 @@ __device__ __forceinline__ u32x4 silu8(floatx4 lo, floatx4 hi) {
 
 // One vector (8 or 16 bytes) of output pixel p, channels c .., to the 2x upsampled copy of the output.
 template <typename T, typename V>
-__device__ __forceinline__ void store_upsampled(const ConvArgs& a, unsigned p, int c, V val) {
+__device__ __forceinline__ void store_upsampled(const ConvKernelArgs& a, unsigned p, int c, V val) {
   const unsigned img = a.HoWo_is_one ? p : udiv(p, a.magic_howo, a.shift_howo);
   const unsigned rem = p - img * (unsigned)(a.Ho * a.Wo);
   const unsigned ho = a.Wo == 1 ? rem : udiv(rem, a.magic_wo, a.shift_wo);

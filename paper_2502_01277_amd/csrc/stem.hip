@@ -42,7 +42,7 @@ constexpr int SP_PAIRS = 8, SP_ROW = 68, SP_PAIR = 2 * SP_ROW * 16;      // ring
 
 // PLAIN: no SiLU and a multiple of 8 channels; with the pool the other code would cost the row loop registers that it has not got
 template <typename T, int BC, int KH, int PKW, bool POOL, bool PLAIN>
-__device__ __forceinline__ void stem_walk(const ConvArgs& a) {
+__device__ __forceinline__ void stem_walk(const ConvKernelArgs& a) {
   using E = Elem<T>;
   static_assert(sizeof(T) == 2 && E::N == 8, "pixel pairs are 16-byte vectors of 8 values");
   constexpr int TC = BC / 32, NV = KH * PKW, NJ = NV / 2, PD = 3, NP = (KH + 1) / 2;
@@ -287,9 +287,9 @@ __device__ __forceinline__ void stem_walk(const ConvArgs& a) {
 }
 
 template <typename T, int BC, int KH, int PKW, bool POOL>
-__global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvArgs a) { stem_walk<T, BC, KH, PKW, POOL, true>(a); }
+__global__ __launch_bounds__(THREADS, 2) void stem_conv_kernel(const ConvKernelArgs a) { stem_walk<T, BC, KH, PKW, POOL, true>(a); }
 template <typename T, int BC, int KH, int PKW>
-__global__ __launch_bounds__(THREADS, 2) void stem_pool_any_kernel(const ConvArgs a) { stem_walk<T, BC, KH, PKW, true, false>(a); }
+__global__ __launch_bounds__(THREADS, 2) void stem_pool_any_kernel(const ConvKernelArgs a) { stem_walk<T, BC, KH, PKW, true, false>(a); }
 
 template <typename T, int BC, int KH, int PKW, bool POOL>
 static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, int* kernel_id, const ConvTiming& tm) {
@@ -304,7 +304,7 @@ static hipError_t launch_stem_cfg(const ConvArgs& a, int num_cu, hipStream_t s, 
   if (units >= 0x7FFF0000LL) return hipErrorNotSupported;
   long long grid = ((units + 3) / 4 + 7) / 8 * 8;
   if (grid > 2LL * num_cu) grid = 2LL * num_cu;
-  void (*kernel)(ConvArgs) = stem_conv_kernel<T, BC, KH, PKW, POOL>;
+  void (*kernel)(ConvKernelArgs) = stem_conv_kernel<T, BC, KH, PKW, POOL>;
   if constexpr (POOL) {
     if (a.act == OCTO_ACT_SILU || a.Cout % 8 != 0) kernel = stem_pool_any_kernel<T, BC, KH, PKW>;
   }
