@@ -180,7 +180,7 @@ TRAFFIC_SOURCE = "profiles/*_hbm_counters.md: rocprofv3 --pmc FETCH_SIZE and --p
 def conv_sources_key() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("conv.hip", "conv_flow.h", "conv_flow_choice.h", "conv_small.h", "conv_small_choice.h", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "conv3x3_stream.h", "conv3x3_held.h", "conv3x3_held_choice.h", "entry.hip", "block.hip", "lead.hip", "stem.hip",
+    for f in ("conv.hip", "conv_flow.h", "conv_flow_choice.h", "conv_small.h", "conv_small_body.h", "conv_small_choice.h", "conv_ksplit.h", "conv1x1.hip", "conv3x3_mid.h", "conv3x3_stream.h", "conv3x3_held.h", "conv3x3_held_choice.h", "entry.hip", "block.hip", "lead.hip", "stem.hip",
               "stem_segment.h", "mfma_common.h"):
         try:
             h.update(open(os.path.join(ROOT, "paper_2502_01277_amd", "csrc", f), "rb").read())
