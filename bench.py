@@ -121,54 +121,54 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "e9e8113c37c68b73": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4365613276,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1697996274,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1427022025,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344461344,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250181339,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553512197,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 847396187,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355694162,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281286273,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2201348479,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 353564727,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 994047175,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1910196162,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629440633,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078258887,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 167763262,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 626990223,
-        "octo::conv_ksplit_kernel<__bf16, 1, 1, 4, 4>": 29839916,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 59805773,
-        "octo::conv3x3_held_kernel<_Float16, 2, 2, 2, 1>": 24368638,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 17681938,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 32124356,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 7120121,
-        "octo::conv_small_group_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 42849089,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 19790144,
-        "octo::block_kernel<_Float16, true>": 65915778,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64499135,
-        "octo::entry_kernel<_Float16>": 53067907,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14280331,
-        "octo::lead_kernel<_Float16, 64, 8, 2>": 39983164,
-        "octo::conv_small_group_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 65335100,
-        "octo::lead_kernel<_Float16, 64, 4, 2>": 33160750,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 14319781,
-        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 1>": 14151301,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21950786,
-        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 2>": 18567976,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18355277,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14237018,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13668367,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7123490,
-        "octo::conv3x3_held_kernel<_Float16, 2, 1, 4, 2>": 6728012,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4634229,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1464174,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39507907,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 27998460,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42486624,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 7168982,
+    "f2cc676d3e796fdb": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4364007513,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1698217494,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1431125081,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344598676,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250144787,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553467549,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 847967795,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355728862,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281015743,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2199268012,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 354353763,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 994872567,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1909267792,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629435674,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078841825,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 168093805,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 626785707,
+        "octo::conv_ksplit_kernel<bool _Accum, int, E, 1, 4, 4>": 29840687,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 59842513,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 2, 1>": 24379508,
+        "octo::conv_small_group_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 42841755,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 16651260,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 7120125,
+        "octo::block_kernel<_Float16, true>": 65916683,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 31747653,
+        "octo::conv_small_group_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 65337162,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64504534,
+        "octo::entry_kernel<_Float16>": 53067930,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 24286475,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14286001,
+        "octo::lead_kernel<_Float16, 64, 8, 2>": 39983190,
+        "octo::lead_kernel<_Float16, 64, 4, 2>": 33160763,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 14324908,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 1>": 14150290,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21926228,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 2>": 18575160,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18346783,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14227809,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13661209,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7124448,
+        "octo::conv3x3_held_kernel<_Float16, 2, 1, 4, 2>": 6733138,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4634233,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1463407,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39500402,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28010257,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42498427,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 7169115,
     },
 }
 
