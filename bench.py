@@ -121,54 +121,54 @@ def conv_name(kid: int, dtype: str) -> str:
 # calibration pass of known size).  Valid only for the kernel sources it was taken with: keyed by their hash.
 TRAFFIC = {
     # hash of the convolution sources (conv_sources_key): {kernel name: HBM bytes per launch}
-    "f2cc676d3e796fdb": {
-        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4364007513,
-        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1698217494,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1431125081,
-        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344598676,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250144787,
-        "octo::conv1x1_stream_kernel<__bf16, 3>": 553467549,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 847967795,
-        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355728862,
-        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281015743,
-        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2199268012,
-        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 354353763,
-        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 994872567,
-        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1909267792,
-        "octo::conv1x1_stream_kernel<__bf16, 2>": 629435674,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1078841825,
-        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 168093805,
-        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 626785707,
-        "octo::conv_ksplit_kernel<bool _Accum, int, E, 1, 4, 4>": 29840687,
-        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 59842513,
-        "octo::conv3x3_held_kernel<_Float16, 2, 2, 2, 1>": 24379508,
-        "octo::conv_small_group_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 42841755,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 16651260,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 7120125,
-        "octo::block_kernel<_Float16, true>": 65916683,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 31747653,
-        "octo::conv_small_group_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 65337162,
-        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64504534,
-        "octo::entry_kernel<_Float16>": 53067930,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 24286475,
-        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14286001,
-        "octo::lead_kernel<_Float16, 64, 8, 2>": 39983190,
-        "octo::lead_kernel<_Float16, 64, 4, 2>": 33160763,
-        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 14324908,
-        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 1>": 14150290,
-        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21926228,
-        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 2>": 18575160,
-        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18346783,
-        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14227809,
-        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13661209,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7124448,
-        "octo::conv3x3_held_kernel<_Float16, 2, 1, 4, 2>": 6733138,
-        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4634233,
-        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1463407,
-        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39500402,
-        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28010257,
-        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42498427,
-        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 7169115,
+    "986c06c94894f33d": {
+        "octo::conv3x3_stream_kernel<__bf16, 2, 4, 8, 6, 3, 2>": 4365499504,
+        "octo::conv3x3_mid_kernel<__bf16, 128, 256, 1, 4, 3, 6, 2>": 1698345659,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 1>": 1431045680,
+        "octo::conv3x3_mid_kernel<__bf16, 96, 256, 1, 4, 3, 6, 2>": 344587641,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 0>": 250147279,
+        "octo::conv1x1_stream_kernel<__bf16, 3>": 553458448,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 1>": 847139425,
+        "octo::stem_conv_kernel<__bf16, 64, 7, 4, true>": 3355701498,
+        "octo::conv_flow_kernel<__bf16, 512, 256, 128, 4, 8, 3, 1, 0>": 281003571,
+        "octo::conv_flow_kernel<__bf16, 512, 96, 256, 1, 8, 3, 1, 2>": 2197688389,
+        "octo::conv_flow_kernel<__bf16, 512, 128, 256, 2, 8, 3, 1, 0>": 354328024,
+        "octo::conv3x3_stream_kernel<__bf16, 2, 3, 8, 6, 4, 2>": 995804044,
+        "octo::stem_conv_kernel<__bf16, 64, 6, 3, false>": 1908744690,
+        "octo::conv1x1_stream_kernel<__bf16, 2>": 629433505,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 2>": 1077408571,
+        "octo::conv3x3_mid_kernel<__bf16, 64, 256, 1, 4, 3, 6, 2>": 168017144,
+        "octo::conv_flow_kernel<__bf16, 512, 192, 128, 2, 8, 3, 1, 1>": 626974681,
+        "octo::conv_ksplit_kernel<bool _Accum, int, E, 1, 4, 4>": 29840422,
+        "octo::conv3x3_mid_kernel<_Float16, 64, 128, 1, 4, 3, 3, 4>": 59848608,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 2, 1>": 24379453,
+        "octo::conv_small_group_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 42837093,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 16651245,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 0>": 7120119,
+        "octo::block_kernel<_Float16, true>": 65916209,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 1>": 31746941,
+        "octo::conv_small_group_kernel<_Float16, 64, 64, 2, 2, 3, 0>": 65337120,
+        "octo::stem_conv_kernel<_Float16, 64, 7, 4, true>": 64497991,
+        "octo::entry_kernel<_Float16>": 53067890,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 1>": 24286446,
+        "octo::conv_small_kernel<_Float16, 128, 64, 4, 2, 2, 0>": 14285989,
+        "octo::lead_kernel<_Float16, 64, 8, 2>": 39983152,
+        "octo::lead_kernel<_Float16, 64, 4, 2>": 33160744,
+        "octo::conv_flow_kernel<_Float16, 256, 64, 64, 2, 8, 3, 3, 0>": 14324897,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 1>": 14150272,
+        "octo::conv_flow_kernel<_Float16, 256, 128, 64, 2, 8, 3, 2, 0>": 21926206,
+        "octo::conv3x3_held_kernel<_Float16, 2, 2, 4, 2>": 18575135,
+        "octo::stem_conv_kernel<_Float16, 32, 3, 2, false>": 18347061,
+        "octo::conv_ksplit_kernel<_Float16, 2, 2, 4, 4>": 14227801,
+        "octo::conv_mfma_kernel<_Float16, 32, 128, 1, 4, 4, 2, 4, true, false, false>": 13661195,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 2>": 7124441,
+        "octo::conv3x3_held_kernel<_Float16, 2, 1, 4, 2>": 6733129,
+        "octo::conv_small_kernel<_Float16, 64, 32, 2, 2, 4, 1>": 4634228,
+        "octo::conv_ksplit_kernel<_Float16, 1, 1, 4, 4>": 1463406,
+        "octo::conv3x3_mid_kernel<_Float16, 128, 256, 1, 4, 3, 6, 2>": 39500216,
+        "octo::conv_flow_kernel<_Float16, 512, 256, 128, 4, 8, 3, 1, 1>": 28008752,
+        "octo::conv_flow_kernel<_Float16, 512, 128, 256, 2, 8, 3, 1, 1>": 42499217,
+        "octo::conv_small_kernel<_Float16, 64, 64, 2, 2, 3, 2>": 7168980,
     },
 }
 

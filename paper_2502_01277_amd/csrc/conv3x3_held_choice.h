@@ -101,7 +101,7 @@ inline double held_cost_us(const ConvArgs& a, long long items, int which, int nu
 }
 // Where the count is taken on the device the choice is made for the stated one, so that an item's results do not depend on its neighbours' number, and the running count may be many times that.
 // A kernel of the common order follows it with larger tiles, this one cannot.  Where the capacity is no more than eight times the stated count a layer goes by that like any other: up to about three
-// times it this kernel is ahead, at most five behind by little.  Us in place, the kernel before : this one, items: 16 x 8 x 256, stated 128, 58 15.9 : 11.4, 116 18.3 : 18.0, 177 26.4 : 25.0, 336
+// times it this kernel is ahead, at eight times even or, at worst, 16 % behind.  Us in place, the kernel before : this one, items: 16 x 8 x 256, stated 128, 58 15.9 : 11.4, 116 18.3 : 18.0, 177 26.4 : 25.0, 336
 // 47.3 : 48.4, 883 110 : 110; 14 x 14 x 256, stated 64, 32 15.0 : 11.0, 64 17.6 : 17.5, 191 43.0 : 41.9, 478 101 : 100; 28 x 28 x 128, stated 32, 24 12.0 : 11.7, 70 22.3 : 21.0, 183 46 : 43.6, 242 60 : 60;
 // 32 x 16 x 128, stated 64, 32 12.4 : 8.9, 64 14.7 : 13.1, 191 30.8 : 30.9, 478 61 : 72; 8 x 8, stride 2, 128 -> 256, stated 64, 64 7.1 : 6.3, 191 10.3 : 8.7, 478 11.2 : 11.4.
 // With more room than that only where it is about even at fourteen times the stated count too: in place of kernels that are tied to the stated count themselves, split-K and the narrow tiles of
